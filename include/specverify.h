@@ -157,15 +157,15 @@ int verify_kv_read(sv_ctx *, int32_t seq_id, int32_t layer, int32_t pos0, int32_
 
 /* Plain causal pass over n tokens (device int32) appended to the sequence; every token is cached.
  * last_logits (device [vocab] fp32, may be NULL) receives the logits of the last token.  A batch of one prompt
- * for verify_prefill_batch; the sequence needs room for n more tokens plus one pass of rows (see there). */
+ * for verify_prefill_batch (see there). */
 int verify_prefill(sv_ctx *, int32_t seq_id, const int32_t *tokens, int32_t n, float *last_logits);
 
 /* The same for B sequences at once (HOST arrays seq_ids[B], n[B]; all distinct and live): prompt b is row b of
  * the device int32 matrix tokens [B, ld], n[b] <= ld tokens long, and the prompts must come longest first.
- * The prompts advance together, a few tokens of each per pass (as many rows as the context's workspace holds for B
- * requests, at most 256 / (q heads per kv head)), so that the projections of a pass work on B times that many rows
- * instead of streaming the weights for one sequence's chunk; max_pages_per_seq must leave room for one pass of rows
- * beyond the longest prompt.  last_logits (device [B, vocab] fp32, may be NULL) receives each
+ * The prompts go through packed, in prompt order, in as few passes of equal size as hold all their tokens: a pass takes
+ * up to 4096 rows (never fewer than a step of the context, nor more than the cache holds; fewer for mixture-of-experts
+ * models with many experts), so that the weights stream once for all of them.  max_pages_per_seq must cover cached length
+ * + prompt.  last_logits (device [B, vocab] fp32, may be NULL) receives each
  * prompt's last-token logits.  Errors leave lengths and pages as they were before the failing pass. */
 int verify_prefill_batch(sv_ctx *, const int32_t *seq_ids, int32_t B, const int32_t *tokens, int32_t ld,
                          const int32_t *n, float *last_logits);

@@ -265,13 +265,14 @@ class Verifier:
         B = len(seq_ids)
         order = sorted(range(B), key=lambda b: -int(lens[b]))
         tokens = tokens.to(device=self.device, dtype=torch.int32)
-        tok = tokens[torch.as_tensor(order, device=self.device)].contiguous()
+        sorted_already = order == list(range(B))             # then the rows are handed over, and the logits returned, as they are
+        tok = tokens.contiguous() if sorted_already else tokens[torch.as_tensor(order, device=self.device)].contiguous()
         ids = (C.c_int32 * B)(*[int(seq_ids[b]) for b in order])
         n = (C.c_int32 * B)(*[int(lens[b]) for b in order])
         out = torch.empty((B, self.vocab), dtype=torch.float32, device=self.device) if want_logits else None
         self._check(self.lib.verify_prefill_batch(self.ctx, ids, B, _ptr(tok), tok.shape[1], n, _ptr(out)))
-        if out is None:
-            return None
+        if out is None or sorted_already:
+            return out
         inv = torch.empty(B, dtype=torch.long)
         inv[torch.as_tensor(order)] = torch.arange(B)
         return out[inv.to(self.device)]

@@ -15,8 +15,12 @@
 // the other; with more rows, tiles travel through an LDS ring and the three stages of consecutive tiles are woven
 // into one instruction stream.
 //
-// Generic path (fp32 models, other head sizes, more than 64 stacked rows): one wave per (row, head),
-// plain online softmax; correct for every shape, not tuned.
+// More stacked rows than one work-group takes are split over row groups.  A prefill has hundreds of them per request and
+// mostly one piece of keys: its work items are (request, 64 stacked rows, piece), their keys end at the last one the rows
+// see, and a request of one piece is finished in the kernel (no partials, no merge).
+//
+// Generic path (fp32 models, other head sizes): one wave per (row, head), plain online softmax; correct for every
+// shape, not tuned.
 #include <math.h>
 #include <algorithm>
 #include <type_traits>
@@ -61,16 +65,17 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
     const int n_items = a.n_work_dev ? *a.n_work_dev : a.n_work;
     if (pair >= n_items * a.Hkv) return;
     const int hkv = pair % a.Hkv;
-    const int4 item = reinterpret_cast<const int4*>(a.work)[pair / a.Hkv];
-    const int b = item.x >> 16, chunk = item.x & 0xffff;
-    const int seq = item.y;
+    const int4* item = reinterpret_cast<const int4*>(a.work) + 2 * (pair / a.Hkv);
+    const int4 keys = item[0], where = item[1];
+    const int seq = keys.x, n = keys.w, t0 = where.x;
     const int L = a.seq_len[seq];
-    const int total = L + a.n;
-    const int kbeg = item.z;
+    const int total = L + n;
+    const int kbeg = keys.y;
     if (kbeg >= total) return;                            // the live length fell short of the host's bound
-    const int kend = min(item.w, total);
-    const int row0 = rg * R * 16;                         // first stacked row of this work-group
-    const int G = a.Hq / a.Hkv, rows = G * a.n;
+    const int G = a.Hq / a.Hkv, rows = G * n;
+    const int row0 = where.y + rg * R * 16;               // first stacked row of this work-group
+    // a prefill item's rows see no further than their last one; a piece beyond that still takes one (masked) tile
+    const int kend = a.row_items ? max(kbeg + 1, min(min(keys.z, total), L + (min(row0 + R * 16, rows) - 1) / G + 1)) : min(keys.z, total);
 
     const int tid = threadIdx.x, lane = tid & 63;
     // wave index as a scalar: tile numbers, page-table reads and page addresses stay on the scalar unit
@@ -88,7 +93,7 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
         const int r = row0 + rt * 16 + l16;
         const bool ok = r < rows;
         const int j = ok ? r / G : 0, hl = ok ? r % G : 0;
-        const bf16_t* qp = reinterpret_cast<const bf16_t*>(a.q) + (((int64_t)b * a.n + j) * a.Hq + hkv * G + hl) * HD;
+        const bf16_t* qp = reinterpret_cast<const bf16_t*>(a.q) + ((int64_t)(t0 + j) * a.Hq + hkv * G + hl) * HD;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
             qf[rt][kk] = ok ? *reinterpret_cast<const u32x4*>(qp + kk * 32 + lg * 8) : u32x4{0, 0, 0, 0};
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) m_run[rt] = m_run[rt] == -INFINITY ? -INFINITY : mc[rt];
     constexpr int RP = 16 * R;
-    __shared__ float m_sh[4][RP], l_sh[4][RP];
+    __shared__ float m_sh[4][RP], l_sh[4][RP], l_fin[RP];
     extern __shared__ __attribute__((aligned(16))) float o_dyn[];          // [4 waves][HD][RP + 1]
     float (*o_sh)[HD][RP + 1] = reinterpret_cast<float (*)[HD][RP + 1]>(o_dyn);
 #pragma unroll
@@ -294,6 +299,7 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
         fac[rt] = exp2f(m_run[rt] - ms);
         m_all[rt] = mm;
         l_all[rt] = ll;
+        if (wave == 0 && lg == 0) l_fin[r] = ll;
     }
     // every wave lays its rescaled accumulators down in its own LDS plane, all four at once; after one barrier
     // the work-group adds the planes up on the way out (taking turns on a single plane cost four serialised
@@ -305,8 +311,21 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 #pragma unroll
             for (int i = 0; i < 4; ++i) o_sh[wave][ht * 16 + 4 * lg + i][rt * 16 + l16] = o[ht][rt][i] * fac[rt];
     __syncthreads();
-    const int64_t pbase = (((int64_t)b * a.Hkv + hkv) * a.max_chunks + chunk) * a.rows_pad + row0;
     const int rows_here = min(rows - row0, RP);
+    if (where.z < 0) {                                    // the request's only piece: the finished rows leave here
+        for (int e = tid; e < rows_here * (HD / 4); e += 256) {
+            const int r = e / (HD / 4), d = (e % (HD / 4)) * 4;
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                v[i] = ((o_sh[0][d + i][r] + o_sh[1][d + i][r]) + (o_sh[2][d + i][r] + o_sh[3][d + i][r])) / l_fin[r];
+            const int g = row0 + r, h = hkv * G + g % G;
+            *reinterpret_cast<u32x2*>(reinterpret_cast<bf16_t*>(a.out) + act_index(t0 + g / G, h * HD + d, a.Hq * HD, a.out_packed)) =
+                u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
+        }
+        return;
+    }
+    const int64_t pbase = (int64_t)where.z + (int64_t)hkv * where.w + row0;
     for (int e = tid; e < rows_here * HD; e += 256) {
         const int r = e / HD, d = e % HD;
         a.part_o[(pbase + r) * HD + d] = (o_sh[0][d][r] + o_sh[1][d][r]) + (o_sh[2][d][r] + o_sh[3][d][r]);
@@ -341,22 +360,23 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
     // half of the CU's LDS: two work-groups share a CU, so that while one starts an item (three dependent reads:
     // item, page table, first tile) or merges its waves, the other keeps streaming.
     constexpr int RP = 16 * R;
-    __shared__ float m_sh[W][RP], l_sh[W][RP];
+    __shared__ float m_sh[W][RP], l_sh[W][RP], l_fin[RP];
     const int slot_id = blockIdx.x / (8 * a.row_groups), rem = blockIdx.x % (8 * a.row_groups);
     const int rg = rem >> 3, pair = slot_id * 8 + (rem & 7);
     const int n_items = a.n_work_dev ? *a.n_work_dev : a.n_work;
     if (pair >= n_items * a.Hkv) return;
     const int hkv = pair % a.Hkv;
-    const int4 item = reinterpret_cast<const int4*>(a.work)[pair / a.Hkv];
-    const int b = item.x >> 16, chunk = item.x & 0xffff;
-    const int seq = item.y;
+    const int4* item = reinterpret_cast<const int4*>(a.work) + 2 * (pair / a.Hkv);
+    const int4 keys = item[0], where = item[1];
+    const int seq = keys.x, n = keys.w, t0 = where.x;
     const int L = a.seq_len[seq];
-    const int total = L + a.n;
-    const int kbeg = item.z;
+    const int total = L + n;
+    const int kbeg = keys.y;
     if (kbeg >= total) return;                            // the live length fell short of the host's bound
-    const int kend = min(item.w, total);
-    const int row0 = rg * R * 16;                         // first stacked row of this work-group
-    const int G = a.Hq / a.Hkv, rows = G * a.n;
+    const int G = a.Hq / a.Hkv, rows = G * n;
+    const int row0 = where.y + rg * R * 16;               // first stacked row of this work-group
+    // a prefill item's rows see no further than their last one; a piece beyond that still takes one (masked) tile
+    const int kend = a.row_items ? max(kbeg + 1, min(min(keys.z, total), L + (min(row0 + R * 16, rows) - 1) / G + 1)) : min(keys.z, total);
 
     const int tid = threadIdx.x, lane = tid & 63;
     // wave index as a scalar: tile numbers, page-table reads and page addresses stay on the scalar unit
@@ -379,7 +399,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
         const int r = row0 + rt * 16 + l16;
         const bool ok = r < rows;
         const int j = ok ? r / G : 0, hl = ok ? r % G : 0;
-        const bf16_t* qp = reinterpret_cast<const bf16_t*>(a.q) + (((int64_t)b * a.n + j) * a.Hq + hkv * G + hl) * HD;
+        const bf16_t* qp = reinterpret_cast<const bf16_t*>(a.q) + ((int64_t)(t0 + j) * a.Hq + hkv * G + hl) * HD;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
             qf[rt][kk] = ok ? *reinterpret_cast<const u32x4*>(qp + kk * 32 + lg * 8) : u32x4{0, 0, 0, 0};
@@ -687,6 +707,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
         fac[rt] = exp2f(m_run[rt] - ms);
         m_all[rt] = mm;
         l_all[rt] = ll;
+        if (wave == 0 && lg == 0) l_fin[r] = ll;
     }
     // every wave lays its rescaled accumulators down in its own LDS plane, all four at once; after one barrier
     // the work-group adds the planes up on the way out (taking turns on a single plane cost four serialised
@@ -698,8 +719,25 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
 #pragma unroll
             for (int i = 0; i < 4; ++i) o_sh[wave][ht * 16 + 4 * lg + i][rt * 16 + l16] = o[ht][rt][i] * fac[rt];
     __syncthreads();
-    const int64_t pbase = (((int64_t)b * a.Hkv + hkv) * a.max_chunks + chunk) * a.rows_pad + row0;
     const int rows_here = min(rows - row0, RP);
+    if (where.z < 0) {                                    // the request's only piece: the finished rows leave here
+        for (int e = tid; e < rows_here * (HD / 4); e += 64 * W) {
+            const int r = e / (HD / 4), d = (e % (HD / 4)) * 4;
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = o_sh[0][d + i][r];
+#pragma unroll
+                for (int w = 1; w < W; ++w) v[i] += o_sh[w][d + i][r];
+                v[i] /= l_fin[r];
+            }
+            const int g = row0 + r, h = hkv * G + g % G;
+            *reinterpret_cast<u32x2*>(reinterpret_cast<bf16_t*>(a.out) + act_index(t0 + g / G, h * HD + d, a.Hq * HD, a.out_packed)) =
+                u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
+        }
+        return;
+    }
+    const int64_t pbase = (int64_t)where.z + (int64_t)hkv * where.w + row0;
     for (int e = tid; e < rows_here * HD; e += 64 * W) {
         const int r = e / HD, d = e % HD;
         float acc = o_sh[0][d][r];
@@ -722,21 +760,19 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
 // Combine the chunk partials of one row: out = sum_c 2^(m_c - M) O_c / sum_c 2^(m_c - M) l_c.  A thread
 // owns four consecutive dimensions of one q head; a work-group covers 256 / 32 = 8 heads of the row.
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
-    const int rows_pad = a.rows_pad;
     const int t = blockIdx.x, h = blockIdx.y * 8 + (threadIdx.x >> 5), d = (threadIdx.x & 31) * 4;
     if (h >= a.Hq) return;
-    const int b = t / a.n, j = t % a.n;
-    const int G = a.Hq / a.Hkv, hkv = h / G, r = j * G + h % G;
-    const int total = a.seq_len[a.batch_seq[b]] + a.n;
-    const int clen = a.req_chunk[2 * b];
-    const int nch = min(a.req_chunk[2 * b + 1], (total + clen - 1) / clen);   // pieces that start below the live end
-    const int64_t base = ((int64_t)b * a.Hkv + hkv) * a.max_chunks;
+    const int4 pt = reinterpret_cast<const int4*>(a.row_part)[t];
+    const int nch = pt.w;                                 // 0: a request of one piece, already written
+    if (nch == 0) return;
+    const int G = a.Hq / a.Hkv, hkv = h / G;
+    const int64_t base = (int64_t)pt.x + (int64_t)hkv * pt.y + h % G;
     float M = -INFINITY;
-    for (int c = 0; c < nch; ++c) M = fmaxf(M, a.part_ml[((base + c) * rows_pad + r) * 2]);
+    for (int c = 0; c < nch; ++c) M = fmaxf(M, a.part_ml[(base + (int64_t)c * pt.z) * 2]);
     floatx4 num = {0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
     for (int c = 0; c < nch; ++c) {
-        const int64_t pr = (base + c) * rows_pad + r;
+        const int64_t pr = base + (int64_t)c * pt.z;
         const floatx2 ml = *reinterpret_cast<const floatx2*>(a.part_ml + pr * 2);
         const float f = exp2f(ml.x - M);
         den += f * ml.y;
@@ -753,9 +789,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 template <typename T, int D>
 __global__ __launch_bounds__(64) void attn_generic_kernel(AttnArgs a, float scale) {
     const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const int b = t / a.n, j = t % a.n;
-    const int seq = a.batch_seq[b];
-    const int L = a.seq_len[seq], total = L + a.n;
+    const int4 info = reinterpret_cast<const int4*>(a.row_info)[t];
+    const int seq = info.x, j = info.y;
+    const int L = a.seq_len[seq], total = L + info.z;
     const int hkv = h / (a.Hq / a.Hkv);
     const int32_t* pages = a.page_table + (int64_t)seq * a.max_pages_per_seq;
     const T* pool = reinterpret_cast<const T*>(a.pool);
@@ -791,24 +827,19 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(AttnArgs a, float scal
     }
 }
 
-int attn_rows_pad(int n, int group) {
-    const int rows = n * group;
-    if (rows > 256) return 0;
-    return (rows + 15) / 16 * 16;
+bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic) {
+    return !force_generic && dtype == 1 && hd == HD && page_size % TILE_KEYS == 0 && (page_size & (page_size - 1)) == 0;
 }
 
 hipError_t attention(const AttnArgs& a, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)a.hd);
     const int G = a.Hq / a.Hkv;
-    const int rp = (!a.force_generic && a.dtype == 1 && a.hd == HD && a.geom.page_size % TILE_KEYS == 0 &&
-                    (a.geom.page_size & (a.geom.page_size - 1)) == 0 && a.chunk_keys % 128 == 0)
-                       ? attn_rows_pad(a.n, G) : 0;
-    if (rp && rp <= a.rows_pad) {
+    if (attn_mfma_ok(a.dtype, a.hd, a.geom.page_size, a.force_generic)) {
         const float sl2 = scale * 1.44269504088896340736f;
         // up to four 16-row tiles per work-group; more stacked rows are split over row groups
         AttnArgs b = a;
-        const int tiles = rp / 16;
-        const int cap = std::min(4, std::max(1, a.max_row_tiles));
+        const int tiles = a.row_items ? kItemRows / 16 : (G * a.n_max + 15) / 16;
+        const int cap = a.row_items ? 4 : std::min(4, std::max(1, a.max_row_tiles));
         b.row_groups = (tiles + cap - 1) / cap;
         const int R = b.row_groups == 1 ? std::max(tiles, a.min_row_tiles) : (tiles + b.row_groups - 1) / b.row_groups;
         const int items = a.grid_items > 0 ? a.grid_items : a.n_work;
@@ -843,10 +874,10 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
             }
         }
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(attn_merge_kernel, dim3(a.B * a.n, (a.Hq + 7) / 8), dim3(256), 0, st, b);
+        if (a.merge) hipLaunchKernelGGL(attn_merge_kernel, dim3(a.T, (a.Hq + 7) / 8), dim3(256), 0, st, b);
         return hipGetLastError();
     }
-    dim3 grid(a.B * a.n, a.Hq);
+    dim3 grid(a.T, a.Hq);
     if (a.dtype == 1 && a.hd == 128)
         hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 128>), grid, dim3(64), 0, st, a, scale);
     else if (a.dtype == 1 && a.hd == 64)

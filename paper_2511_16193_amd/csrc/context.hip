@@ -22,6 +22,14 @@ constexpr int kRing = 8;              // pinned staging slots for per-step host 
 constexpr int kMaxSplits = 8;
 constexpr int kMaxSplitsWs = 16;       // weight-streaming kernel: any divisor of the slice count up to this
 constexpr int kChunkKeys = 1024;      // keys per split-KV chunk of the bf16 attention
+// Rows a prefill pass may hold whatever the context was sized for.  A pass streams every weight once, so a prompt that
+// goes through in passes of a step's few dozen rows pays for that stream again and again: one prompt of 777 tokens
+// through a context sized for 40 rows took 22 passes, 29.2 ms over 7 layers of the 7B shape; in one pass 4.7 ms (with the
+// first token's step, 1.2 ms of it).  24 prompts of 100-500 tokens, 7 layers: 47.4 ms in 14 passes with the LM head on
+// every row, 26.4 ms in two passes with it on the prompts' last rows.  From about a thousand rows on the projections are
+// bound by their products; four thousand rows cost 0.4-1 GB of workspace.
+constexpr int kPrefillRows = 4096;
+constexpr int kCausalK = 1 << 20;     // "drafts per chain" of a prefill pass: one chain, never ending
 
 struct SeqState {
     bool live = false;
@@ -50,7 +58,7 @@ int pick_splits(int M, int N, int K) {
 // 2304), except the lone work-group's pace, which is taken from whole steps (cold weights); on the sweep the plan
 // chosen was within 0.3 % of the best on average and 4.5 % at worst.
 struct WsPlan { int splits; bool wide; int row_tiles; };
-WsPlan plan_ws(int M, int N, int K, bool allow_split, int tile_mode = -1) {
+WsPlan plan_ws(int M, int N, int K, bool allow_split, int tile_mode = -1, int max_splits = kMaxSplitsWs) {
     const int slices_all = K / 16;
     const int tiles = (M + 31) / 32;
     WsPlan best{1, false, gemm_bf16_ws_row_tiles(M)};
@@ -70,7 +78,7 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int tile_mode = -1) {
             // share of that rate a CU reaches with one resp. two work-groups of mt tiles
             static const double kOne[6] = {0, 0.56, 0.97, 0.94, 0.93, 0.98}, kTwo[6] = {0, 0.58, 0.82, 0.90, 0.96, 0.95};
             auto cu_rate = [&](int g) { return base * (g == 1 ? kOne[mt] : kTwo[mt]) * 1e6; };   // flop per microsecond
-            for (int s = 1; s <= (allow_split ? kMaxSplitsWs : 1); ++s) {
+            for (int s = 1; s <= (allow_split ? max_splits : 1); ++s) {
                 if (slices_all % (4 * s) != 0) continue;
                 if ((K / s) % 128 != 0 && tiles > 5 && mt != 5) continue;     // short fills exist in the five-tile form only
                 const double slices = (double)slices_all / s;
@@ -100,10 +108,15 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int tile_mode = -1) {
 }
 
 struct Layout {                       // byte offsets into the workspace
-    size_t seq_len, page_table, batch_seq, upd, work, req_chunk, row_tok, row_pos, row_slot, chain_acc, chain_tok, chain_row, draw_part;
+    size_t seq_len, page_table, upd, stage, row_info, row_part, row_slot, chain_acc, chain_tok, chain_row, draw_part;
     size_t rope, row_stat, h, a_norm, q, attn, part, act, logits, part_o, part_ml, total;
     size_t moe_ids, moe_w, moe_cnt, moe_off, moe_perm, moe_inv, moe_act, moe_y, moe_logits;   // mixture-of-experts scratch
-    int T, rows_pad, max_chunks;
+    int T, P;                         // rows of a step, rows of a pass (a prefill pass may hold more)
+    int max_chunks, max_items, max_upd;
+    size_t part_floats;               // capacity of part
+    long long part_rows;              // capacity of part_o / part_ml
+    int st_seq, st_req, st_work, st_upd;   // ints from the start of the staged block: sequence ids, requests, work items, page updates
+    int st_total;
 };
 
 bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
@@ -115,62 +128,79 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
     const int T = r.max_batch * (1 + r.max_chains * r.max_k);
     const int qw = m.n_q_heads * m.head_dim, qkvw = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
     const int F = m.n_experts ? m.d_expert : m.d_ff;
+    const int G = m.n_q_heads / std::max(1, m.n_kv_heads);
+    int extra = (int)std::min<long long>(kPrefillRows, (long long)r.num_pages * r.page_size);   // no more than the cache holds
+    if (m.n_experts > 0)
+        while (extra > T && !moe_shape_ok(extra, m.d_model, m.n_experts, m.top_k, m.d_expert)) extra -= std::min(extra - T, 256);
+    const int P = std::max(T, extra);
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
     L.T = T;
+    L.P = P;
     L.seq_len = take(sizeof(int32_t) * r.max_seqs);
     L.page_table = take(sizeof(int32_t) * (size_t)r.max_seqs * r.max_pages_per_seq);
-    L.batch_seq = take(sizeof(int32_t) * r.max_batch);
-    L.upd = take(sizeof(int32_t) * 3 * (size_t)r.max_batch * 8);
+    L.upd = take(sizeof(int32_t) * 2 * (size_t)r.max_batch);
     L.max_chunks = (int)(((size_t)r.max_pages_per_seq * r.page_size + kChunkKeys - 1) / kChunkKeys);
-    L.work = take(sizeof(int32_t) * 4 * (size_t)r.max_batch * L.max_chunks);
-    L.req_chunk = take(sizeof(int32_t) * (2 * (size_t)r.max_batch + 1));      // + the number of work items
-    L.row_tok = take(sizeof(int32_t) * T);
-    L.row_pos = take(sizeof(int32_t) * T);
-    L.row_slot = take(sizeof(int32_t) * T);
+    L.max_items = r.max_batch * L.max_chunks + P * G / kItemRows + r.max_batch + 2048;
+    L.max_upd = std::max(8 * r.max_batch, P / r.page_size + 2 * r.max_batch);
+    L.st_seq = 4;                                          // (the first int: the number of work items)
+    L.st_req = L.st_seq + (r.max_batch + 3) / 4 * 4;
+    L.st_work = L.st_req + kReqInts * r.max_batch;
+    L.st_upd = L.st_work + kItemInts * L.max_items;
+    L.st_total = L.st_upd + 3 * L.max_upd;
+    L.stage = take(sizeof(int32_t) * (size_t)L.st_total);
+    L.row_info = take(sizeof(int32_t) * 4 * (size_t)P);
+    L.row_part = take(sizeof(int32_t) * 4 * (size_t)P);
+    L.row_slot = take(sizeof(int32_t) * P);
     L.chain_acc = take(sizeof(int32_t) * r.max_batch * r.max_chains);
     L.chain_tok = take(sizeof(int32_t) * r.max_batch * r.max_chains);
     L.chain_row = take(sizeof(int32_t) * r.max_batch * r.max_chains);
     L.draw_part = take(sizeof(float) * 4 * kDrawParts * T);       // per (request, chain); per row in match mode
-    L.rope = take(sizeof(float) * (size_t)T * m.head_dim);
+    L.rope = take(sizeof(float) * (size_t)P * m.head_dim);
     L.row_stat = take(sizeof(float) * 4 * T);
-    L.h = take(sizeof(float) * (size_t)T * m.d_model);
-    const size_t Tp = (size_t)(T + 31) / 32 * 32;          // packed activations come in 32-row tiles
+    L.h = take(sizeof(float) * (size_t)P * m.d_model);
+    const size_t Tp = (size_t)(P + 31) / 32 * 32;          // packed activations come in 32-row tiles
     L.a_norm = take(es * Tp * m.d_model);
-    L.q = take(es * (size_t)T * qw);
+    L.q = take(es * (size_t)P * qw);
     L.attn = take(es * Tp * qw);
-    // split-K partial products: the largest splits * rows * features any projection can ask for
+    // split-K partial products: the most splits * rows * features a projection's plan asks for at any number of row
+    // tiles (a plan between two of these sizes that would ask for more is made again with fewer splits)
     size_t part = 0;
     const int shapes[4][2] = {{qkvw, m.d_model}, {m.d_model, qw}, {2 * F, m.d_model}, {m.d_model, F}};
-    for (int tm = 1; tm <= (T + 127) / 128; ++tm) {
-        const int M = std::min(tm * 128, T);
+    for (int tm = 1; tm <= (P + 127) / 128; ++tm) {
+        const int M = std::min(tm * 128, P);
         for (auto& sh : shapes)
             part = std::max(part, (size_t)(m.dtype == SV_BF16 ? pick_splits(M, sh[0], sh[1]) : 1) * M * sh[0]);
     }
     if (m.dtype == SV_BF16)                                 // the same for the plans of the weight-streaming kernel
-        for (int M = 1; M <= T; ++M)                       // every row count a call can bring (the plan weighs M itself)
+        for (int tm = 1; tm <= (P + 31) / 32; ++tm) {
+            const int M = std::min(tm * 32, P);
             for (auto& sh : shapes)
                 if (sh[1] % 64 == 0) part = std::max(part, (size_t)plan_ws(M, sh[0], sh[1], true).splits * M * sh[0]);
+        }
+    L.part_floats = part;
     L.part = take(sizeof(float) * part);
     L.act = take(es * Tp * F);
     L.logits = take(sizeof(float) * (size_t)T * m.vocab);
-    const int G = m.n_q_heads / std::max(1, m.n_kv_heads);
-    // the MFMA attention stacks G * n rows per kv head; its chunk partials are kept for up to 256 of them
-    L.rows_pad = std::max(64, std::min(256, (G * (1 + r.max_chains * r.max_k) + 15) / 16 * 16));
-    L.part_o = take(sizeof(float) * (size_t)r.max_batch * m.n_kv_heads * L.max_chunks * L.rows_pad * m.head_dim);
-    L.part_ml = take(sizeof(float) * (size_t)r.max_batch * m.n_kv_heads * L.max_chunks * L.rows_pad * 2);
+    // the MFMA attention stacks G * n rows per kv head and keeps the partials of a request cut into pieces
+    const int rows_pad = std::max(64, (G * (1 + r.max_chains * r.max_k) + 15) / 16 * 16);
+    L.part_rows = (long long)r.max_batch * m.n_kv_heads * L.max_chunks * rows_pad;
+    if (attn_mfma_ok(m.dtype, m.head_dim, r.page_size, false)) L.part_rows = std::max(L.part_rows, 2LL * (P * m.n_q_heads + kItemRows * m.n_kv_heads));
+    if (L.part_rows > 0x7fffffffLL) return false;          // partial rows are numbered in 32 bits
+    L.part_o = take(sizeof(float) * (size_t)L.part_rows * m.head_dim);
+    L.part_ml = take(sizeof(float) * (size_t)L.part_rows * 2);
     L.moe_ids = L.moe_w = L.moe_cnt = L.moe_off = L.moe_perm = L.moe_inv = L.moe_act = L.moe_y = L.moe_logits = 0;
     if (m.n_experts > 0) {
-        const size_t tiles = (size_t)moe_max_tiles(T, m.n_experts, m.top_k);
-        L.moe_ids = take(sizeof(int32_t) * (size_t)T * m.top_k);
-        L.moe_w = take(sizeof(float) * (size_t)T * m.top_k);
+        const size_t tiles = (size_t)moe_max_tiles(P, m.n_experts, m.top_k);
+        L.moe_ids = take(sizeof(int32_t) * (size_t)P * m.top_k);
+        L.moe_w = take(sizeof(float) * (size_t)P * m.top_k);
         L.moe_cnt = take(sizeof(int32_t) * m.n_experts);
         L.moe_off = take(sizeof(int32_t) * (m.n_experts + 1));
         L.moe_perm = take(sizeof(int32_t) * 32 * tiles);
-        L.moe_inv = take(sizeof(int32_t) * (size_t)T * m.top_k);
+        L.moe_inv = take(sizeof(int32_t) * (size_t)P * m.top_k);
         L.moe_act = take(es * 32 * tiles * m.d_expert);
         L.moe_y = take(sizeof(float) * 32 * tiles * m.d_model);
-        L.moe_logits = take(sizeof(float) * 4 * (size_t)T * m.n_experts);
+        L.moe_logits = take(sizeof(float) * 4 * (size_t)P * m.n_experts);
     }
     L.total = o;
     return true;
@@ -209,10 +239,8 @@ struct sv_ctx {
     hipEvent_t staged[kRing];
     bool staged_valid[kRing];
     int ring_pos;
-    int n_work;                                           // attention work items staged for the current batch
-    const int32_t* tok_matrix = nullptr;                  // batched prefill: the prompts the next forward pass reads its rows from
-    const int32_t* tok_len = nullptr;
-    int tok_ld = 0, tok_col0 = 0;
+    int n_work;                                           // attention work items staged for the current pass
+    bool pass_merge;                                      // some request of it has its keys cut into several pieces
     int gemm_variant;                                     // -1 = choose per shape
     int gemm_tile;                                        // 256 x 256 projection kernel: -1 = where it pays, 0 = never, 1 = wherever the shape allows
     bool packed;                                          // projection weights are in fragment order
@@ -229,7 +257,6 @@ struct sv_ctx {
     };
     std::vector<GraphEntry> graphs;
     unsigned long long graph_clock;
-    int attn_chunk;                                       // keys per split-KV chunk of the staged batch
     int attn_chunk_opt;                                   // 0 = chosen per batch, else fixed by option
     unsigned prof_mask;                                   // kinds of kernels to time with events
     struct ProfRec { int kind; hipEvent_t a, b; };
@@ -363,10 +390,9 @@ extern "C" int verify_init(const sv_model* m, const sv_weights* w, const sv_runt
     c->graph_launch_shape = false;
     c->graph_clock = 0;
     c->attn_max_rt = 4;
-    c->attn_chunk = kChunkKeys;
     c->attn_chunk_opt = 0;
     c->prof_mask = 0;
-    const size_t slot_ints = (size_t)r->max_batch * (1 + 3 * 8 + 4 * L.max_chunks + 2) + 16;
+    const size_t slot_ints = std::max<size_t>(L.st_total, 2 * (size_t)r->max_batch);
     for (int i = 0; i < kRing; ++i) { c->staging[i] = nullptr; c->staged[i] = nullptr; c->staged_valid[i] = false; }
     for (int i = 0; i < kRing; ++i) {
         if (hipHostMalloc(reinterpret_cast<void**>(&c->staging[i]), slot_ints * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
@@ -484,110 +510,174 @@ extern "C" int verify_kv_read(sv_ctx* c, int32_t id, int32_t layer, int32_t pos0
 
 // ---------------------------------------------------------- forward pass ---
 
-// Make sure every listed sequence holds pages for `extra` more entries; push ids and new page-table
-// entries to the device.  Nothing changes if the pool cannot cover the whole batch.
-static int stage_batch(sv_ctx* c, const int32_t* ids, int B, int extra) {
+// What a pass takes from one request: n rows of its sequence; in a prefill they are columns col0 .. col0+n-1 of prompt pb.
+struct PassReq { int32_t seq; int n, pb, col0; };
+struct Pass {
+    const PassReq* rq; int B;
+    int n;                            // rows of every request; 0: they differ (prefill)
+    int n_max, T, k;
+};
+
+// A slot of the pinned staging ring, free to be written.
+static int take_slot(sv_ctx* c, int& slot) {
+    slot = c->ring_pos;
+    if (c->staged_valid[slot]) SV_HIP(c, hipEventSynchronize(c->staged[slot]));
+    return SV_OK;
+}
+static int release_slot(sv_ctx* c, int slot) {
+    SV_HIP(c, hipEventRecord(c->staged[slot], c->stream));
+    c->staged_valid[slot] = true;
+    c->ring_pos = (slot + 1) % kRing;
+    return SV_OK;
+}
+
+// Keys per piece for a step's attention, unless fixed by option: each candidate's launch is simulated -- every piece
+// goes to the CU that frees up first and costs its keys plus a fixed ~300 keys' worth (measured: ~6 us of start-up and
+// merge per work-group against ~46 keys per us per CU) -- and the shortest makespan wins.
+static int pick_chunk(const sv_ctx* c, const Pass& ps) {
+    if (c->attn_chunk_opt) return c->attn_chunk_opt;
+    int chunk = kChunkKeys;
+    double best = 1e300;
+    std::vector<int> lens;
+    std::vector<double> cu(256);
+    for (int cand : {1024, 1536, 2048, 3072, 4096, 6144, 8192, 12288, 16384, 24576, 32768}) {
+        lens.clear();
+        for (int b = 0; b < ps.B; ++b) {
+            const int total = c->seqs[ps.rq[b].seq].len_ub + ps.rq[b].n;
+            const int nch = std::max(1, std::min((total + cand - 1) / cand, c->lay.max_chunks));
+            for (int ch = 0; ch < nch; ++ch) lens.push_back((total + nch - 1) / nch);
+        }
+        std::sort(lens.begin(), lens.end(), std::greater<int>());
+        std::fill(cu.begin(), cu.end(), 0.0);
+        for (int len : lens)
+            for (int h = 0; h < c->model.n_kv_heads; ++h) {
+                std::pop_heap(cu.begin(), cu.end(), std::greater<double>());
+                cu.back() += len + 300.0;
+                std::push_heap(cu.begin(), cu.end(), std::greater<double>());
+            }
+        const double makespan = *std::max_element(cu.begin(), cu.end());
+        if (makespan < best) { best = makespan; chunk = cand; }
+    }
+    return chunk;
+}
+
+// The attention's work list: every (request, piece of its keys) -- in a prefill (request, 64 stacked rows, piece) --
+// that can exist given the upper bounds of the lengths, longest first (the hardware hands work-groups to CUs in order, so
+// this is longest-processing-time-first list scheduling).  An item carries all a work-group needs to start streaming, so
+// that its first K/V load is two dependent reads away (item, then page table; the live length is read beside it and
+// only clips the end).  A request is cut into equal parts of whole 32-key tiles.  Fills the requests' piece fields
+// beside the items.
+static void build_work(sv_ctx* c, const Pass& ps, int32_t* req, int32_t* work) {
+    const sv_model& m = c->model;
+    const Layout& L = c->lay;
+    const int G = m.n_q_heads / m.n_kv_heads;
+    const bool prefill = ps.n == 0;
+    int chunk = 0, cut = 1;
+    if (prefill) {
+        // 64-row groups make the parallelism; where they are too few for two work-groups per CU the keys are cut as well
+        long long groups = 0;
+        for (int b = 0; b < ps.B; ++b) groups += (G * ps.rq[b].n + kItemRows - 1) / kItemRows;
+        cut = (int)std::max(1LL, 512 / (groups * m.n_kv_heads));
+    } else {
+        chunk = pick_chunk(c, ps);
+    }
+    struct Item { int len, v[kItemInts]; };
+    std::vector<Item> items;
+    long long prow = 0;
+    c->pass_merge = false;
+    int t0 = 0;
+    for (int b = 0; b < ps.B; ++b) {
+        const PassReq& r = ps.rq[b];
+        const int start = c->seqs[r.seq].len_ub, total = start + r.n;
+        const int rows_pad = (G * r.n + 15) / 16 * 16, groups = prefill ? (G * r.n + kItemRows - 1) / kItemRows : 1;
+        int nch = prefill ? std::min(cut, (total + kChunkKeys - 1) / kChunkKeys) : (total + chunk - 1) / chunk;
+        nch = std::max(1, std::min(nch, L.max_chunks));
+        if (prow + (long long)nch * m.n_kv_heads * rows_pad > L.part_rows || (long long)items.size() + (long long)nch * groups + (ps.B - b) > L.max_items)
+            nch = 1;                                       // no room for partials: one piece, written directly
+        const int clen = ((total + nch - 1) / nch + 31) / 32 * 32;
+        int32_t* q = req + b * kReqInts;
+        q[2] = clen; q[3] = nch; q[4] = (int32_t)prow; q[5] = nch * rows_pad; q[6] = rows_pad;
+        for (int g = 0; g < groups; ++g) {
+            const int last_key = prefill ? start + (std::min((g + 1) * kItemRows, G * r.n) - 1) / G + 1 : total;
+            for (int ch = 0; ch < nch && ch * clen < total; ++ch) {
+                const int kbeg = ch * clen, kend = std::min(kbeg + clen, total);
+                items.push_back({std::min(kend, last_key) - kbeg,
+                                 {r.seq, kbeg, kend, r.n, t0, g * kItemRows, nch > 1 ? (int32_t)(prow + ch * rows_pad) : -1, nch * rows_pad}});
+            }
+        }
+        if (nch > 1) { prow += (long long)nch * m.n_kv_heads * rows_pad; c->pass_merge = true; }
+        t0 += r.n;
+    }
+    std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.len > y.len; });
+    for (size_t i = 0; i < items.size(); ++i) memcpy(work + i * kItemInts, items[i].v, sizeof(items[i].v));
+    c->n_work = (int)items.size();
+}
+
+// Make sure every request's sequence holds pages for its new rows; describe the pass (requests, attention work list,
+// new page-table entries) to the device in one copy.  Nothing changes if the pool cannot cover the whole batch.
+static int stage_pass(sv_ctx* c, const Pass& ps) {
+    const Layout& L = c->lay;
     int need_total = 0;
-    for (int b = 0; b < B; ++b) {
-        const int id = ids[b];
+    for (int b = 0; b < ps.B; ++b) {
+        const int id = ps.rq[b].seq;
         if (id < 0 || id >= c->rt.max_seqs || !c->seqs[id].live) return c->fail(SV_ENOSEQ, "sequence id %d not live", id);
         for (int b2 = 0; b2 < b; ++b2)
-            if (ids[b2] == id) return c->fail(SV_ENOSEQ, "sequence id %d appears twice in the batch", id);
-        const int need = pages_for(c, c->seqs[id].len_ub + extra);
+            if (ps.rq[b2].seq == id) return c->fail(SV_ENOSEQ, "sequence id %d appears twice in the batch", id);
+        const int need = pages_for(c, c->seqs[id].len_ub + ps.rq[b].n);
         if (need > c->rt.max_pages_per_seq) return c->fail(SV_ENOPAGES, "sequence %d would exceed max_pages_per_seq", id);
         need_total += std::max(0, need - (int)c->seqs[id].pages.size());
     }
     if (need_total > (int)c->free_pages.size())
         return c->fail(SV_ENOPAGES, "need %d more pages, %zu free", need_total, c->free_pages.size());
-    if (need_total > B * 8) return c->fail(SV_EINVAL, "more than %d new pages in one step", B * 8);
+    if (need_total > L.max_upd) return c->fail(SV_EINVAL, "more than %d new pages in one pass", L.max_upd);
 
-    const int slot = c->ring_pos;
-    if (c->staged_valid[slot]) SV_HIP(c, hipEventSynchronize(c->staged[slot]));
+    int slot;
+    SV_TRY(take_slot(c, slot));
     int32_t* st = c->staging[slot];
+    int t0 = 0;
+    for (int b = 0; b < ps.B; ++b) {
+        const PassReq& r = ps.rq[b];
+        st[L.st_seq + b] = r.seq;
+        int32_t* q = st + L.st_req + b * kReqInts;
+        const int32_t v[kReqInts] = {t0, r.n, 1, 1, 0, 0, 0, r.seq, r.pb, r.col0, 0, 0};
+        memcpy(q, v, sizeof(v));
+        t0 += r.n;
+    }
+    c->n_work = 0;
+    c->pass_merge = false;
+    if (attn_mfma_ok(c->model.dtype, c->model.head_dim, c->rt.page_size, c->attn_generic))
+        build_work(c, ps, st + L.st_req, st + L.st_work);
+    st[0] = c->n_work;                                    // read by launches that were captured into a graph
     int nupd = 0;
-    int32_t* upd = st + B;
-    for (int b = 0; b < B; ++b) {
-        SeqState& s = c->seqs[ids[b]];
-        st[b] = ids[b];
-        const int need = pages_for(c, s.len_ub + extra);
+    const int upd_at = L.st_work + kItemInts * c->n_work;
+    int32_t* upd = st + upd_at;
+    for (int b = 0; b < ps.B; ++b) {
+        SeqState& s = c->seqs[ps.rq[b].seq];
+        const int need = pages_for(c, s.len_ub + ps.rq[b].n);
         while ((int)s.pages.size() < need) {
             const int32_t p = c->free_pages.back();
             c->free_pages.pop_back();
-            upd[3 * nupd] = ids[b]; upd[3 * nupd + 1] = (int32_t)s.pages.size(); upd[3 * nupd + 2] = p;
+            upd[3 * nupd] = ps.rq[b].seq; upd[3 * nupd + 1] = (int32_t)s.pages.size(); upd[3 * nupd + 2] = p;
             s.pages.push_back(p);
             ++nupd;
         }
     }
-    SV_HIP(c, hipMemcpyAsync(c->at<int32_t>(c->lay.batch_seq), st, B * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+    int32_t* dev = c->at<int32_t>(L.stage);
+    SV_HIP(c, hipMemcpyAsync(dev, st, sizeof(int32_t) * (size_t)(upd_at + 3 * nupd), hipMemcpyHostToDevice, c->stream));
     if (nupd) {
-        SV_HIP(c, hipMemcpyAsync(c->at<int32_t>(c->lay.upd), upd, 3 * nupd * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
         hipLaunchKernelGGL(apply_page_updates_kernel, dim3((nupd + 63) / 64), dim3(64), 0, c->stream,
-                           c->at<int32_t>(c->lay.page_table), c->rt.max_pages_per_seq, c->at<int32_t>(c->lay.upd), nupd);
+                           c->at<int32_t>(L.page_table), c->rt.max_pages_per_seq, dev + upd_at, nupd);
         SV_HIP(c, hipGetLastError());
     }
-    // attention work list: every (request, chunk) that can exist given the upper bounds of the lengths,
-    // longest pieces first (the hardware hands work-groups to CUs in order, so this is longest-processing-
-    // time-first list scheduling).  Keys per chunk, unless fixed by option: each candidate's launch is
-    // simulated -- every piece goes to the CU that frees up first and costs its keys plus a fixed ~300 keys'
-    // worth (measured: ~6 us of start-up and merge per work-group against ~46 keys per us per CU) -- and the
-    // shortest makespan wins.
-    {
-        int chunk = c->attn_chunk_opt;
-        if (chunk == 0) {
-            double best = 1e300;
-            std::vector<int> lens;
-            std::vector<double> cu(256);
-            for (int cand : {1024, 1536, 2048, 3072, 4096, 6144, 8192, 12288, 16384, 24576, 32768}) {
-                lens.clear();
-                for (int b = 0; b < B; ++b) {
-                    const int total = c->seqs[ids[b]].len_ub + extra;
-                    const int nch = std::max(1, std::min((total + cand - 1) / cand, c->lay.max_chunks));
-                    for (int ch = 0; ch < nch; ++ch) lens.push_back((total + nch - 1) / nch);
-                }
-                std::sort(lens.begin(), lens.end(), std::greater<int>());
-                std::fill(cu.begin(), cu.end(), 0.0);
-                for (int len : lens)
-                    for (int h = 0; h < c->model.n_kv_heads; ++h) {
-                        std::pop_heap(cu.begin(), cu.end(), std::greater<double>());
-                        cu.back() += len + 300.0;
-                        std::push_heap(cu.begin(), cu.end(), std::greater<double>());
-                    }
-                const double makespan = *std::max_element(cu.begin(), cu.end());
-                if (makespan < best) { best = makespan; chunk = cand; }
-            }
-        }
-        c->attn_chunk = chunk;
-        // An item carries all a work-group needs to start streaming -- (request << 16 | chunk), sequence id,
-        // first key, end of the piece -- so that its first K/V load is two dependent reads away (item, then
-        // page table; the live length is read beside it and only clips the end).  Pieces are cut from the
-        // upper bounds of the lengths: equal parts, whole 32-key tiles.
-        int32_t* req = upd + 3 * nupd;                   // per request: keys per piece, pieces
-        int32_t* work = req + 2 * c->rt.max_batch + 1;
-        struct Item { int len, b, ch, seq, kbeg, kend; };
-        std::vector<Item> items;
-        for (int b = 0; b < B; ++b) {
-            const int total = c->seqs[ids[b]].len_ub + extra;
-            const int nch = std::max(1, std::min((total + chunk - 1) / chunk, c->lay.max_chunks));
-            const int clen = ((total + nch - 1) / nch + 31) / 32 * 32;
-            req[2 * b] = clen; req[2 * b + 1] = nch;
-            for (int ch = 0; ch < nch && ch * clen < total; ++ch)
-                items.push_back({std::min(clen, total - ch * clen), b, ch, ids[b], ch * clen, std::min((ch + 1) * clen, total)});
-        }
-        std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.len > y.len; });
-        int nw = 0;
-        for (auto& t : items) {
-            work[4 * nw] = (t.b << 16) | t.ch; work[4 * nw + 1] = t.seq; work[4 * nw + 2] = t.kbeg; work[4 * nw + 3] = t.kend;
-            ++nw;
-        }
-        req[2 * c->rt.max_batch] = nw;                    // read by launches that were captured into a graph
-        SV_HIP(c, hipMemcpyAsync(c->at<int32_t>(c->lay.req_chunk), req, (2 * c->rt.max_batch + 1) * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
-        SV_HIP(c, hipMemcpyAsync(c->at<int32_t>(c->lay.work), work, 4 * nw * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
-        c->n_work = nw;
-    }
-    SV_HIP(c, hipEventRecord(c->staged[slot], c->stream));
-    c->staged_valid[slot] = true;
-    c->ring_pos = (slot + 1) % kRing;
-    return SV_OK;
+    return release_slot(c, slot);
+}
+
+// The requests of a step or of a single-operation call: n rows each.
+static int stage_batch(sv_ctx* c, const int32_t* ids, int B, int n, int k, std::vector<PassReq>& rq, Pass& ps) {
+    rq.resize(B);
+    for (int b = 0; b < B; ++b) rq[b] = {ids[b], n, 0, 0};
+    ps = {rq.data(), B, n, n, B * n, k};
+    return stage_pass(c, ps);
 }
 
 // Work-group tile of the row-major projection kernel for M rows: 64, 128 or 256 tokens x 128 features.
@@ -601,7 +691,8 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
     if (c->model.dtype == SV_BF16) {
         if (c->packed) {
             // packed weights + packed activations: the weight-streaming kernel
-            const WsPlan p = plan_ws(M, N, K, allow_split, c->gemm_tile);
+            WsPlan p = plan_ws(M, N, K, allow_split, c->gemm_tile);
+            while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_ws(M, N, K, allow_split, c->gemm_tile, p.splits - 1);
             *splits_out = p.splits;
             SV_HIP(c, gemm_bf16_ws((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, p.wide, c->stream, p.row_tiles));
         } else {
@@ -616,17 +707,23 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
     return SV_OK;
 }
 
-// Row preparation of a pass: positions, cache slots, rotary table, token ids of the B * n new rows.
-static int prepare_rows(sv_ctx* c, int B, int n, int k, const int32_t* last_tokens, const int32_t* drafts) {
+// What prep_rows reads of a prefill's prompts (null: a step's last_tokens and drafts).
+struct Prompts { const int32_t* tokens; int ld; };
+
+// Row preparation of a pass: cache slots, rotary table, where the attention partials lie; with_embed: also the rows'
+// embeddings as the residual stream.
+static int prepare_rows(sv_ctx* c, const Pass& ps, const int32_t* last_tokens, const int32_t* drafts, const Prompts* pr, bool with_embed) {
     const sv_model& m = c->model;
     const Layout& L = c->lay;
     RowPrep rp;
-    rp.batch_seq = c->at<int32_t>(L.batch_seq); rp.seq_len = c->at<int32_t>(L.seq_len);
-    rp.last_tokens = last_tokens; rp.drafts = drafts;
-    rp.row_tok = c->at<int32_t>(L.row_tok); rp.row_pos = c->at<int32_t>(L.row_pos); rp.row_slot = c->at<int32_t>(L.row_slot);
+    rp.req = c->at<int32_t>(L.stage) + L.st_req; rp.seq_len = c->at<int32_t>(L.seq_len);
+    rp.page_table = c->at<int32_t>(L.page_table); rp.max_pages_per_seq = c->rt.max_pages_per_seq; rp.page_size = c->rt.page_size;
+    rp.last_tokens = last_tokens; rp.drafts = drafts; rp.tok_matrix = pr ? pr->tokens : nullptr; rp.tok_ld = pr ? pr->ld : 0;
+    rp.embed = with_embed ? c->embed : nullptr; rp.dtype = m.dtype; rp.h = c->at<float>(L.h); rp.d = m.d_model;
+    rp.row_slot = c->at<int32_t>(L.row_slot); rp.row_info = c->at<int32_t>(L.row_info); rp.row_part = c->at<int32_t>(L.row_part);
     rp.rope = c->at<float>(L.rope);
-    rp.B = B; rp.n = n; rp.k = k; rp.head_dim = m.head_dim; rp.vocab = m.vocab; rp.rope_theta = m.rope_theta;
-    rp.tok_matrix = c->tok_matrix; rp.tok_len = c->tok_len; rp.tok_ld = c->tok_ld; rp.tok_col0 = c->tok_col0;
+    rp.T = ps.T; rp.B = ps.B; rp.n = ps.n; rp.k = ps.k; rp.head_dim = m.head_dim; rp.vocab = m.vocab;
+    rp.group = m.n_q_heads / m.n_kv_heads; rp.rope_theta = m.rope_theta;
     SV_HIP(c, prep_rows(rp, c->stream));
     return SV_OK;
 }
@@ -634,50 +731,50 @@ static int prepare_rows(sv_ctx* c, int B, int n, int k, const int32_t* last_toke
 // Residual add of what the previous projection left behind, then RMSNorm into the packed operand buffer.
 // pending > 0: that many split-K planes in `part`; 0: nothing to add; -1: the expert outputs of a
 // mixture-of-experts layer, still to be combined with the routing weights and added.
-static int add_norm(sv_ctx* c, int T, int pending, const void* gain) {
+// n_last > 0: only the last rows of the pass's first n_last requests, to rows 0 .. n_last-1 of the buffer.
+static int add_norm(sv_ctx* c, int T, int pending, const void* gain, int n_last = 0) {
     const sv_model& m = c->model;
     const Layout& L = c->lay;
     float* h = c->at<float>(L.h);
     void* a_norm = c->at<void>(L.a_norm);
+    const int32_t* last_of = n_last > 0 ? c->at<int32_t>(L.stage) + L.st_req : nullptr;
     if (pending < 0)
         SV_HIP(c, add_rmsnorm_experts(h, c->at<float>(L.moe_y), c->at<int32_t>(L.moe_inv), c->at<float>(L.moe_w), m.top_k, gain, a_norm,
-                                      T, m.d_model, m.rms_eps, c->packed, c->stream));
+                                      T, m.d_model, m.rms_eps, c->packed, c->stream, last_of, n_last));
     else
-        SV_HIP(c, add_rmsnorm(h, c->at<float>(L.part), pending, gain, a_norm, m.dtype, T, m.d_model, m.rms_eps, c->packed, c->stream));
+        SV_HIP(c, add_rmsnorm(h, c->at<float>(L.part), pending, gain, a_norm, m.dtype, T, m.d_model, m.rms_eps, c->packed, c->stream,
+                              last_of, n_last));
     return SV_OK;
 }
 
-// Row pitch of the split-KV partials for a pass of B requests with n rows each.  The buffers are sized for
-// max_batch requests with the rows of a verification step; a pass of fewer requests with more rows each (a prompt
-// prefilled in long chunks) may spread over the same memory with a larger pitch, up to the 256 stacked rows the MFMA
-// attention takes.
-static int attn_partial_pitch(const sv_ctx* c, int B, int n, int max_chunks) {
+static AttnArgs attn_args(const sv_ctx* c, const Pass& ps, int layer, const void* q, void* out, bool out_packed) {
+    const sv_model& m = c->model;
     const Layout& L = c->lay;
-    const int G = c->model.n_q_heads / c->model.n_kv_heads;
-    const int need = attn_rows_pad(n, G);                 // padded stacked rows per kv head; 0: more than the kernels take
-    if (need == 0 || need <= L.rows_pad) return L.rows_pad;
-    const long long room = (long long)c->rt.max_batch * L.max_chunks * L.rows_pad / ((long long)B * std::max(1, max_chunks));
-    return room >= need ? need : L.rows_pad;
-}
-
-// Rows per request and pass when B prompts are prefilled together: what the workspace holds rows for, at most the 256
-// stacked rows per kv head of the MFMA attention, and no more than the split-KV partials have room for.
-static int prefill_width(const sv_ctx* c, int B) {
-    const Layout& L = c->lay;
-    const int G = c->model.n_q_heads / c->model.n_kv_heads;
-    int width = std::max(1, std::min(L.T / B, 256 / G));
-    while (width > 1 && attn_rows_pad(width, G) > L.rows_pad &&
-           (long long)c->rt.max_batch * L.rows_pad / B < attn_rows_pad(width, G))
-        --width;                                          // (the pitch is checked against the chunk count of the pass again)
-    return width;
+    AttnArgs aa;
+    aa.q = q; aa.pool = c->rt.kv_pool; aa.geom = c->geom; aa.layer = layer;
+    aa.page_table = c->at<int32_t>(L.page_table); aa.max_pages_per_seq = c->rt.max_pages_per_seq;
+    aa.seq_len = c->at<int32_t>(L.seq_len); aa.row_info = c->at<int32_t>(L.row_info); aa.row_part = c->at<int32_t>(L.row_part);
+    aa.out = out; aa.part_o = c->at<float>(L.part_o); aa.part_ml = c->at<float>(L.part_ml); aa.row_groups = 1;
+    aa.T = ps.T; aa.n_max = ps.n_max; aa.k = ps.k; aa.Hq = m.n_q_heads; aa.Hkv = m.n_kv_heads; aa.hd = m.head_dim; aa.dtype = m.dtype;
+    aa.work = c->at<int32_t>(L.stage) + L.st_work; aa.n_work = c->n_work;
+    aa.row_items = ps.n == 0; aa.merge = c->pass_merge;
+    aa.n_work_dev = nullptr; aa.grid_items = 0;
+    if (c->graph_launch_shape) {      // nothing in the launch may depend on the lengths
+        aa.n_work_dev = c->at<int32_t>(L.stage);
+        aa.grid_items = ps.B * L.max_chunks;
+        aa.merge = true;
+    }
+    aa.out_packed = out_packed;
+    aa.force_generic = c->attn_generic; aa.min_row_tiles = c->attn_min_rt; aa.max_row_tiles = c->attn_max_rt;
+    return aa;
 }
 
 // One decoder layer over the prepared rows.  On entry the residual stream h lacks `pending` (see add_norm) of
 // the previous layer; on exit it lacks this layer's feed-forward output, described by the new `pending`.
-static int layer_rows(sv_ctx* c, int l, int B, int n, int k, int max_len_ub, int& pending) {
+static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     const sv_model& m = c->model;
     const Layout& L = c->lay;
-    const int T = B * n, d = m.d_model, qw = m.n_q_heads * m.head_dim, qkvw = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
+    const int T = ps.T, d = m.d_model, qw = m.n_q_heads * m.head_dim, qkvw = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
     hipStream_t st = c->stream;
     float* h = c->at<float>(L.h);
     float* part = c->at<float>(L.part);
@@ -689,29 +786,11 @@ static int layer_rows(sv_ctx* c, int l, int B, int n, int k, int max_len_ub, int
     SV_TRY(gemm(c, a_norm, c->wqkv[l], part, T, qkvw, d, &s_qkv));
     RopeAppend ra;
     ra.qkv_part = part; ra.S = s_qkv; ra.rope = c->at<float>(L.rope); ra.row_slot = c->at<int32_t>(L.row_slot);
-    ra.batch_seq = c->at<int32_t>(L.batch_seq);
-    ra.page_table = c->at<int32_t>(L.page_table); ra.max_pages_per_seq = c->rt.max_pages_per_seq;
     ra.q_out = c->at<void>(L.q); ra.pool = c->rt.kv_pool; ra.geom = c->geom; ra.layer = l;
-    ra.T = T; ra.n = n; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.dtype = m.dtype;
+    ra.T = T; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.dtype = m.dtype;
     SV_HIP(c, rope_append(ra, st));
 
-    AttnArgs aa;
-    aa.q = ra.q_out; aa.pool = c->rt.kv_pool; aa.geom = c->geom; aa.layer = l;
-    aa.page_table = ra.page_table; aa.max_pages_per_seq = c->rt.max_pages_per_seq;
-    aa.batch_seq = ra.batch_seq; aa.seq_len = c->at<int32_t>(L.seq_len); aa.out = c->at<void>(L.attn);
-    aa.part_o = c->at<float>(L.part_o); aa.part_ml = c->at<float>(L.part_ml); aa.rows_pad = L.rows_pad; aa.row_groups = 1;
-    aa.B = B; aa.n = n; aa.k = k; aa.Hq = m.n_q_heads; aa.Hkv = m.n_kv_heads; aa.hd = m.head_dim; aa.dtype = m.dtype;
-    aa.chunk_keys = c->attn_chunk; aa.work = c->at<int32_t>(L.work); aa.n_work = c->n_work; aa.req_chunk = c->at<int32_t>(L.req_chunk);
-    aa.out_packed = c->packed;
-    aa.force_generic = c->attn_generic; aa.min_row_tiles = c->attn_min_rt; aa.max_row_tiles = c->attn_max_rt;
-    aa.max_chunks = std::min(L.max_chunks, (max_len_ub + n + c->attn_chunk - 1) / c->attn_chunk);
-    aa.n_work_dev = nullptr; aa.grid_items = 0;
-    if (c->graph_launch_shape) {      // nothing in the launch may depend on the lengths
-        aa.max_chunks = L.max_chunks;
-        aa.n_work_dev = c->at<int32_t>(L.req_chunk) + 2 * c->rt.max_batch;
-        aa.grid_items = B * L.max_chunks;
-    }
-    aa.rows_pad = attn_partial_pitch(c, B, n, aa.max_chunks);
+    const AttnArgs aa = attn_args(c, ps, l, ra.q_out, c->at<void>(L.attn), c->packed);
     {
         ProfScope prof(c, SV_PROF_ATTENTION);
         SV_HIP(c, attention(aa, st));
@@ -747,19 +826,18 @@ static int layer_rows(sv_ctx* c, int l, int B, int n, int k, int max_len_ub, int
     return SV_OK;
 }
 
-// Rows are already described by batch_seq / last_tokens / drafts.  Leaves logits in the workspace.
-static int forward_rows(sv_ctx* c, int B, int n, int k, const int32_t* last_tokens, const int32_t* drafts, int max_len_ub) {
-    const sv_model& m = c->model;
-    const Layout& L = c->lay;
-    const int T = B * n;
-    SV_TRY(prepare_rows(c, B, n, k, last_tokens, drafts));
-    SV_HIP(c, embed_rows(c->embed, m.dtype, c->at<int32_t>(L.row_tok), c->at<float>(L.h), T, m.d_model, c->stream));
-    int pending = 0;
-    for (int l = 0; l < m.n_layers; ++l) SV_TRY(layer_rows(c, l, B, n, k, max_len_ub, pending));
-    SV_TRY(add_norm(c, T, pending, c->final_norm));
-    int one = 1;
-    SV_TRY(gemm(c, c->at<void>(L.a_norm), c->lm_head, c->at<float>(L.logits), T, m.vocab, m.d_model, &one, false));
+// The staged pass through all layers: rows prepared, residual stream complete but for the returned `pending`.
+static int forward_layers(sv_ctx* c, const Pass& ps, const int32_t* last_tokens, const int32_t* drafts, const Prompts* pr, int& pending) {
+    SV_TRY(prepare_rows(c, ps, last_tokens, drafts, pr, true));
+    pending = 0;
+    for (int l = 0; l < c->model.n_layers; ++l) SV_TRY(layer_rows(c, l, ps, pending));
     return SV_OK;
+}
+
+// Logits of M normalised rows in the operand buffer.
+static int head_rows(sv_ctx* c, int M, float* logits) {
+    int one = 1;
+    return gemm(c, c->at<void>(c->lay.a_norm), c->lm_head, logits, M, c->model.vocab, c->model.d_model, &one, false);
 }
 
 extern "C" int verify_prefill(sv_ctx* c, int32_t id, const int32_t* tokens, int32_t n, float* last_logits) {
@@ -769,66 +847,66 @@ extern "C" int verify_prefill(sv_ctx* c, int32_t id, const int32_t* tokens, int3
     return verify_prefill_batch(c, &id, 1, tokens, n, &n, last_logits);
 }
 
-// Prompts of several sequences at once.  Pass p covers tokens p*c .. p*c+c-1 of every prompt that is that long
-// (the prompts come longest first, so those are the first B_act of them): B_act * c rows through the same kernels as
-// a verification step -- a chunk is x0 plus one chain of c-1 "drafts", causal visibility, every row kept -- with
-// c the rows per request the workspace was sized for (1 + max_chains * max_k; at most 256 / G so that the rows of
-// a kv head fit the attention kernel's tiles).  Rows past the end of a shorter prompt are padding: they sit
-// behind the real rows, which therefore never see them, their cache entries lie beyond the new length, and
-// the length advances by the real count.
+// Prompts of several sequences at once, packed: a pass takes the next rows in prompt order, however many of each prompt
+// fit, through the same kernels as a verification step (requests of different sizes, one causal chain each).  The passes
+// are as few as hold all tokens, and of equal size.  Only the rows that end a prompt go through the final norm and the
+// LM head, straight into the caller's logits; within a pass they belong to its first requests.
 extern "C" int verify_prefill_batch(sv_ctx* c, const int32_t* seq_ids, int32_t B, const int32_t* tokens, int32_t ld,
                                     const int32_t* n, float* last_logits) {
     if (!c || !seq_ids || !tokens || !n) return SV_EINVAL;
     if (B <= 0 || B > c->rt.max_batch || ld <= 0) return c->fail(SV_EINVAL, "prefill of %d prompts (limit %d), row pitch %d", B, c->rt.max_batch, ld);
-    const int width_max = prefill_width(c, B);
+    long long left = 0;
     for (int b = 0; b < B; ++b) {
         if (n[b] <= 0 || n[b] > ld) return c->fail(SV_EINVAL, "prompt %d has %d tokens (row pitch %d)", b, n[b], ld);
         if (b && n[b] > n[b - 1]) return c->fail(SV_EINVAL, "prompts must come longest first (prompt %d: %d after %d)", b, n[b], n[b - 1]);
         const int id = seq_ids[b];
         if (id < 0 || id >= c->rt.max_seqs || !c->seqs[id].live) return c->fail(SV_ENOSEQ, "sequence id %d not live", id);
-        if (pages_for(c, c->seqs[id].len_ub + n[b] + width_max) > c->rt.max_pages_per_seq)     // the last pass may carry padding rows
+        for (int b2 = 0; b2 < b; ++b2)
+            if (seq_ids[b2] == id) return c->fail(SV_ENOSEQ, "sequence id %d appears twice in the batch", id);
+        if (pages_for(c, c->seqs[id].len_ub + n[b]) > c->rt.max_pages_per_seq)
             return c->fail(SV_ENOPAGES, "sequence %d would exceed max_pages_per_seq", id);
+        left += n[b];
     }
-    int32_t* len_dev = c->at<int32_t>(c->lay.chain_acc);          // free outside a verification step
-    {   // the lengths travel through a slot of the pinned staging ring, like a batch's ids
-        const int slot = c->ring_pos;
-        if (c->staged_valid[slot]) SV_HIP(c, hipEventSynchronize(c->staged[slot]));
-        for (int b = 0; b < B; ++b) c->staging[slot][b] = n[b];
-        SV_HIP(c, hipMemcpyAsync(len_dev, c->staging[slot], sizeof(int32_t) * B, hipMemcpyHostToDevice, c->stream));
-        SV_HIP(c, hipEventRecord(c->staged[slot], c->stream));
-        c->staged_valid[slot] = true;
-        c->ring_pos = (slot + 1) % kRing;
-    }
-    for (int col0 = 0; col0 < n[0]; col0 += width_max) {
-        int B_act = 0;
-        while (B_act < B && n[B_act] > col0) ++B_act;
-        const int width = std::min(width_max, n[0] - col0);
-        SV_TRY(stage_batch(c, seq_ids, B_act, width));
-        int max_ub = 0;
-        for (int b = 0; b < B_act; ++b) max_ub = std::max(max_ub, c->seqs[seq_ids[b]].len_ub);
-        c->tok_matrix = tokens; c->tok_len = len_dev; c->tok_ld = ld; c->tok_col0 = col0;
-        const int rc = forward_rows(c, B_act, width, width - 1, nullptr, nullptr, max_ub);
-        c->tok_matrix = nullptr; c->tok_len = nullptr;
-        if (rc != SV_OK) return rc;
-        SV_HIP(c, add_len_ragged(c->at<int32_t>(c->lay.seq_len), c->at<int32_t>(c->lay.batch_seq), B_act, len_dev, col0, width, c->stream));
-        for (int b = 0; b < B_act; ++b) {
-            const int real = std::min(width, n[b] - col0);
-            c->seqs[seq_ids[b]].len_ub += real;
-            if (last_logits && n[b] <= col0 + width)              // this pass holds the prompt's last token
-                SV_HIP(c, hipMemcpyAsync(last_logits + (size_t)b * c->model.vocab,
-                                         c->at<float>(c->lay.logits) + ((size_t)b * width + real - 1) * c->model.vocab,
-                                         sizeof(float) * c->model.vocab, hipMemcpyDeviceToDevice, c->stream));
+    const Prompts pr{tokens, ld};
+    std::vector<PassReq> rq;
+    long long passes = (left + c->lay.P - 1) / c->lay.P;
+    for (int b = 0, col = 0; b < B; --passes) {
+        const long long room = std::min<long long>(c->lay.P, ((left + passes - 1) / passes + 31) / 32 * 32);
+        rq.clear();
+        const int first = b;
+        int T = 0, n_max = 0, ended = 0;
+        while (b < B && T < room) {
+            const int take = (int)std::min<long long>(n[b] - col, room - T);
+            rq.push_back({seq_ids[b], take, b, col});
+            T += take;
+            n_max = std::max(n_max, take);
+            col += take;
+            if (col == n[b]) { ++ended; ++b; col = 0; }
         }
+        left -= T;
+        const Pass ps{rq.data(), (int)rq.size(), 0, n_max, T, kCausalK};
+        SV_TRY(stage_pass(c, ps));
+        int pending = 0;
+        SV_TRY(forward_layers(c, ps, nullptr, nullptr, &pr, pending));
+        if (last_logits && ended > 0) {
+            SV_TRY(add_norm(c, T, pending, c->final_norm, ended));
+            SV_TRY(head_rows(c, ended, last_logits + (size_t)first * c->model.vocab));
+        }
+        SV_HIP(c, add_rows(c->at<int32_t>(c->lay.seq_len), c->at<int32_t>(c->lay.stage) + c->lay.st_req, ps.B, c->stream));
+        for (const PassReq& r : rq) c->seqs[r.seq].len_ub += r.n;
     }
     return SV_OK;
 }
 
 // Everything verify_step enqueues after the batch is staged: forward pass, accept/reject + draw, chain choice,
 // rollback, optional copy of the logits.
-static int step_device_work(sv_ctx* c, const sv_batch* bt, const int32_t* drafts, const float* draft_probs,
-                            const float* uniforms, const sv_out* out, int max_ub) {
-    const int B = bt->B, k = bt->k, N = bt->N, n = 1 + N * k;
-    SV_TRY(forward_rows(c, B, n, k, bt->last_tokens, drafts, max_ub));
+static int step_device_work(sv_ctx* c, const sv_batch* bt, const Pass& ps, const int32_t* drafts, const float* draft_probs,
+                            const float* uniforms, const sv_out* out) {
+    const int B = bt->B, k = bt->k, N = bt->N;
+    int pending = 0;
+    SV_TRY(forward_layers(c, ps, bt->last_tokens, drafts, nullptr, pending));
+    SV_TRY(add_norm(c, ps.T, pending, c->final_norm));
+    SV_TRY(head_rows(c, ps.T, c->at<float>(c->lay.logits)));
 
     const Layout& L = c->lay;
     SampleArgs sa;
@@ -846,14 +924,14 @@ static int step_device_work(sv_ctx* c, const sv_batch* bt, const int32_t* drafts
     RollbackArgs rb;
     rb.pool = c->rt.kv_pool; rb.geom = c->geom; rb.n_layers = c->model.n_layers; rb.dtype = c->model.dtype;
     rb.page_table = c->at<int32_t>(L.page_table); rb.max_pages_per_seq = c->rt.max_pages_per_seq;
-    rb.batch_seq = c->at<int32_t>(L.batch_seq); rb.seq_len = c->at<int32_t>(L.seq_len);
+    rb.batch_seq = c->at<int32_t>(L.stage) + L.st_seq; rb.seq_len = c->at<int32_t>(L.seq_len);
     rb.accepted_len = out->accepted_len; rb.best_chain = out->best_chain; rb.B = B; rb.N = N; rb.k = k;
     {
         ProfScope prof(c, SV_PROF_ROLLBACK);
         SV_HIP(c, rollback(rb, c->stream));
     }
     if (out->logits)
-        SV_HIP(c, hipMemcpyAsync(out->logits, sa.logits, sizeof(float) * (size_t)B * n * c->model.vocab,
+        SV_HIP(c, hipMemcpyAsync(out->logits, sa.logits, sizeof(float) * (size_t)ps.T * c->model.vocab,
                                  hipMemcpyDeviceToDevice, c->stream));
     return SV_OK;
 }
@@ -873,8 +951,8 @@ static void drop_graphs(sv_ctx* c) {
 // The first step of a kind runs as plain launches (one-off set-up calls are not capturable), the second is
 // captured, later ones replay.  Returns 1 if the work was enqueued through a graph, 0 if the caller should
 // enqueue it itself, < 0 on error.
-static int step_through_graph(sv_ctx* c, const sv_batch* bt, const int32_t* drafts, const float* draft_probs,
-                              const float* uniforms, const sv_out* out, int max_ub) {
+static int step_through_graph(sv_ctx* c, const sv_batch* bt, const Pass& ps, const int32_t* drafts, const float* draft_probs,
+                              const float* uniforms, const sv_out* out) {
     if (!c->use_graph || c->stream == nullptr || c->prof_mask != 0) return 0;
     const void* ptr[9] = {bt->last_tokens, drafts, draft_probs, uniforms, bt->draft_lens,
                           out->accepted_len, out->out_tokens, out->best_chain, out->logits};
@@ -905,7 +983,7 @@ static int step_through_graph(sv_ctx* c, const sv_batch* bt, const int32_t* draf
         hipGraph_t graph = nullptr;
         SV_HIP(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         c->graph_launch_shape = true;
-        const int rc = step_device_work(c, bt, drafts, draft_probs, uniforms, out, max_ub);
+        const int rc = step_device_work(c, bt, ps, drafts, draft_probs, uniforms, out);
         c->graph_launch_shape = false;
         const hipError_t ec = hipStreamEndCapture(c->stream, &graph);
         if (rc != SV_OK || ec != hipSuccess || !graph) {
@@ -930,12 +1008,12 @@ extern "C" int verify_step(sv_ctx* c, const sv_batch* bt, const int32_t* drafts,
         return c->fail(SV_EINVAL, "null argument");
     if (c->rt.verify_mode != SV_GREEDY && !uniforms) return c->fail(SV_EINVAL, "stochastic and match verification need uniforms");
     const int n = 1 + N * k;
-    SV_TRY(stage_batch(c, bt->seq_ids, B, n));
-    int max_ub = 0;
-    for (int b = 0; b < B; ++b) max_ub = std::max(max_ub, c->seqs[bt->seq_ids[b]].len_ub);
-    const int via_graph = step_through_graph(c, bt, drafts, draft_probs, uniforms, out, max_ub);
+    std::vector<PassReq> rq;
+    Pass ps;
+    SV_TRY(stage_batch(c, bt->seq_ids, B, n, k, rq, ps));
+    const int via_graph = step_through_graph(c, bt, ps, drafts, draft_probs, uniforms, out);
     if (via_graph < 0) return via_graph;
-    if (via_graph == 0) SV_TRY(step_device_work(c, bt, drafts, draft_probs, uniforms, out, max_ub));
+    if (via_graph == 0) SV_TRY(step_device_work(c, bt, ps, drafts, draft_probs, uniforms, out));
     for (int b = 0; b < B; ++b) c->seqs[bt->seq_ids[b]].len_ub += k + 1;
     return SV_OK;
 }
@@ -1057,23 +1135,11 @@ extern "C" int sv_op_attention(sv_ctx* c, const int32_t* seq_ids, int B, int n, 
     if (B <= 0 || B > c->rt.max_batch || n <= 0 || B * n > c->lay.T || k < 0 || layer < 0 || layer >= c->model.n_layers ||
         (k > 0 && (n - 1) % k != 0) || (k == 0 && n != 1))
         return c->fail(SV_EINVAL, "attention of %d x %d rows (k=%d, layer %d) outside the limits given at init", B, n, k, layer);
-    SV_TRY(stage_batch(c, seq_ids, B, n));
-    int max_ub = 0;
-    for (int b = 0; b < B; ++b) max_ub = std::max(max_ub, c->seqs[seq_ids[b]].len_ub);
-    const sv_model& m = c->model;
-    AttnArgs aa;
-    aa.q = q; aa.pool = c->rt.kv_pool; aa.geom = c->geom; aa.layer = layer;
-    aa.page_table = c->at<int32_t>(c->lay.page_table); aa.max_pages_per_seq = c->rt.max_pages_per_seq;
-    aa.batch_seq = c->at<int32_t>(c->lay.batch_seq); aa.seq_len = c->at<int32_t>(c->lay.seq_len); aa.out = out;
-    aa.part_o = c->at<float>(c->lay.part_o); aa.part_ml = c->at<float>(c->lay.part_ml); aa.rows_pad = c->lay.rows_pad; aa.row_groups = 1;
-    aa.B = B; aa.n = n; aa.k = k; aa.Hq = m.n_q_heads; aa.Hkv = m.n_kv_heads; aa.hd = m.head_dim; aa.dtype = m.dtype;
-    aa.chunk_keys = c->attn_chunk; aa.work = c->at<int32_t>(c->lay.work); aa.n_work = c->n_work; aa.req_chunk = c->at<int32_t>(c->lay.req_chunk);
-    aa.out_packed = false;
-    aa.force_generic = c->attn_generic; aa.min_row_tiles = c->attn_min_rt; aa.max_row_tiles = c->attn_max_rt;
-    aa.max_chunks = std::min(c->lay.max_chunks, (max_ub + n + c->attn_chunk - 1) / c->attn_chunk);
-    aa.n_work_dev = nullptr; aa.grid_items = 0;
-    aa.rows_pad = attn_partial_pitch(c, B, n, aa.max_chunks);
-    SV_HIP(c, attention(aa, c->stream));
+    std::vector<PassReq> rq;
+    Pass ps;
+    SV_TRY(stage_batch(c, seq_ids, B, n, k, rq, ps));
+    SV_TRY(prepare_rows(c, ps, nullptr, nullptr, nullptr, false));
+    SV_HIP(c, attention(attn_args(c, ps, layer, q, out, false), c->stream));
     return SV_OK;
 }
 
@@ -1083,17 +1149,17 @@ extern "C" int sv_op_layer(sv_ctx* c, const int32_t* seq_ids, int B, int n, int 
     if (B <= 0 || B > c->rt.max_batch || n <= 0 || B * n > c->lay.T || k < 0 || layer < 0 || layer >= c->model.n_layers ||
         (k > 0 && (n - 1) % k != 0) || (k == 0 && n != 1))
         return c->fail(SV_EINVAL, "layer %d over %d x %d rows (k=%d) outside the limits given at init", layer, B, n, k);
-    SV_TRY(stage_batch(c, seq_ids, B, n));
-    int max_ub = 0;
-    for (int b = 0; b < B; ++b) max_ub = std::max(max_ub, c->seqs[seq_ids[b]].len_ub);
+    std::vector<PassReq> rq;
+    Pass ps;
+    SV_TRY(stage_batch(c, seq_ids, B, n, k, rq, ps));
     const sv_model& m = c->model;
     const Layout& L = c->lay;
     const int T = B * n;
     const size_t bytes = sizeof(float) * (size_t)T * m.d_model;
-    SV_TRY(prepare_rows(c, B, n, k, nullptr, nullptr));
+    SV_TRY(prepare_rows(c, ps, nullptr, nullptr, nullptr, false));
     SV_HIP(c, hipMemcpyAsync(c->at<float>(L.h), h_in, bytes, hipMemcpyDeviceToDevice, c->stream));
     int pending = 0;
-    SV_TRY(layer_rows(c, layer, B, n, k, max_ub, pending));
+    SV_TRY(layer_rows(c, layer, ps, pending));
     // the feed-forward output is still pending: the residual add that the next layer's (or the final) norm would do
     SV_TRY(add_norm(c, T, pending, c->final_norm));
     SV_HIP(c, hipMemcpyAsync(h_out, c->at<float>(L.h), bytes, hipMemcpyDeviceToDevice, c->stream));
@@ -1109,11 +1175,13 @@ extern "C" int sv_op_rollback(sv_ctx* c, const int32_t* seq_ids, int B, int N, i
     if (!c || !seq_ids || !accepted_len || !best_chain) return SV_EINVAL;
     if (B <= 0 || B > c->rt.max_batch || k < 0 || k > c->rt.max_k || N <= 0 || N > c->rt.max_chains)
         return c->fail(SV_EINVAL, "batch %d / k %d / chains %d outside the limits given at init", B, k, N);
-    SV_TRY(stage_batch(c, seq_ids, B, 1 + N * k));       // the slots of a pass: L .. L + N*k
+    std::vector<PassReq> rq;
+    Pass ps;
+    SV_TRY(stage_batch(c, seq_ids, B, 1 + N * k, k, rq, ps));   // the slots of a pass: L .. L + N*k
     RollbackArgs rb;
     rb.pool = c->rt.kv_pool; rb.geom = c->geom; rb.n_layers = c->model.n_layers; rb.dtype = c->model.dtype;
     rb.page_table = c->at<int32_t>(c->lay.page_table); rb.max_pages_per_seq = c->rt.max_pages_per_seq;
-    rb.batch_seq = c->at<int32_t>(c->lay.batch_seq); rb.seq_len = c->at<int32_t>(c->lay.seq_len);
+    rb.batch_seq = c->at<int32_t>(c->lay.stage) + c->lay.st_seq; rb.seq_len = c->at<int32_t>(c->lay.seq_len);
     rb.accepted_len = accepted_len; rb.best_chain = best_chain; rb.B = B; rb.N = N; rb.k = k;
     {
         ProfScope prof(c, SV_PROF_ROLLBACK);
@@ -1157,17 +1225,15 @@ extern "C" int sv_seq_set_lens(sv_ctx* c, const int32_t* seq_ids, const int32_t*
         if (lens[i] < 0 || lens[i] > (int)c->seqs[id].pages.size() * c->rt.page_size)
             return c->fail(SV_EINVAL, "length %d beyond the pages sequence %d holds", lens[i], id);
     }
-    const int slot = c->ring_pos;
-    if (c->staged_valid[slot]) SV_HIP(c, hipEventSynchronize(c->staged[slot]));
+    int slot;
+    SV_TRY(take_slot(c, slot));
     int32_t* st = c->staging[slot];
     for (int i = 0; i < n; ++i) { st[2 * i] = seq_ids[i]; st[2 * i + 1] = lens[i]; }
     SV_HIP(c, hipMemcpyAsync(c->at<int32_t>(c->lay.upd), st, 2 * n * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     hipLaunchKernelGGL(set_lens_kernel, dim3((n + 63) / 64), dim3(64), 0, c->stream, c->at<int32_t>(c->lay.seq_len),
                        c->at<int32_t>(c->lay.upd), n);
     SV_HIP(c, hipGetLastError());
-    SV_HIP(c, hipEventRecord(c->staged[slot], c->stream));
-    c->staged_valid[slot] = true;
-    c->ring_pos = (slot + 1) % kRing;
+    SV_TRY(release_slot(c, slot));
     for (int i = 0; i < n; ++i) c->seqs[seq_ids[i]].len_ub = lens[i];
     return SV_OK;
 }

@@ -6,43 +6,60 @@
 
 namespace sv {
 
-// One group per new row t = b*n + j.  Position = L + index-in-chain, cache slot = L + j.  The rotary
-// angle pos * theta^(-2i/hd) is formed in double: at positions of tens of thousands a float angle is
-// off by ~1e-3 rad, which is visible after rounding q and k to bf16.
-__global__ void prep_rows_kernel(RowPrep p) {
-    const int t = blockIdx.x, b = t / p.n, j = t % p.n;
-    const int L = p.seq_len[p.batch_seq[b]];
-    const int pos = L + row_index_in_chain(j, p.k);
-    if (threadIdx.x == 0) {
-        int tok;
-        if (p.tok_matrix) {
-            const int col = min(p.tok_col0 + j, p.tok_len[b] - 1);
-            tok = p.tok_matrix[(int64_t)b * p.tok_ld + col];
-        } else {
-            // (a pass over given residual rows brings no tokens at all)
-            tok = !p.last_tokens ? 0 : j == 0 ? p.last_tokens[b] : p.drafts[(int64_t)b * (p.n - 1) + (j - 1)];
+// One group per new row t, row j of its request.  Position = L + index-in-chain, cache slot = L + j.  What every layer
+// asks of a row (physical slot, where its attention partials lie) is worked out here once, so that no layer's kernel
+// follows request -> sequence -> page table again.  The rotary angle pos * theta^(-2i/hd) is formed in double: at
+// positions of tens of thousands a float angle is off by ~1e-3 rad, which is visible after rounding q and k to bf16.
+// The row's embedding becomes the residual stream in the same launch.
+template <typename E>
+__global__ __launch_bounds__(256) void prep_rows_kernel(RowPrep p) {
+    const int t = blockIdx.x;
+    int b;
+    if (p.n > 0) b = t / p.n;
+    else {                                                 // requests of different sizes: exactly one holds row t
+        __shared__ int owner;
+        for (int i = threadIdx.x; i < p.B; i += 256) {
+            const int t0 = p.req[i * kReqInts], n = p.req[i * kReqInts + 1];
+            if (t >= t0 && t < t0 + n) owner = i;
         }
-        // ids arrive in device memory from another process and cannot be checked on the host: an id outside the
-        // vocabulary is embedded as the nearest valid one (the sampler rejects such a draft whatever its row yields)
-        p.row_tok[t] = min(max(tok, 0), p.vocab - 1);
-        p.row_pos[t] = pos;
-        p.row_slot[t] = L + j;
+        __syncthreads();
+        b = owner;
+    }
+    const int32_t* rq = p.req + b * kReqInts;
+    const int j = t - rq[0], n = rq[1], seq = rq[7];
+    int tok;
+    if (p.tok_matrix) tok = p.tok_matrix[(int64_t)rq[8] * p.tok_ld + rq[9] + j];
+    else              // (a pass over given residual rows brings no tokens at all)
+        tok = !p.last_tokens ? 0 : j == 0 ? p.last_tokens[b] : p.drafts[(int64_t)b * (n - 1) + (j - 1)];
+    // ids arrive in device memory from another process and cannot be checked on the host: an id outside the
+    // vocabulary is embedded as the nearest valid one (the sampler rejects such a draft whatever its row yields)
+    tok = min(max(tok, 0), p.vocab - 1);
+    const int L = p.seq_len[seq];
+    if (p.embed) {
+        const E* src = reinterpret_cast<const E*>(p.embed) + (int64_t)tok * p.d;
+        float* dst = p.h + (int64_t)t * p.d;
+        for (int i = threadIdx.x * 4; i < p.d; i += 1024) {                  // d % 4 == 0
+            const floatx4 v = {Store<E>::load(src + i), Store<E>::load(src + i + 1), Store<E>::load(src + i + 2), Store<E>::load(src + i + 3)};
+            *reinterpret_cast<floatx4*>(dst + i) = v;
+        }
+    }
+    if (threadIdx.x == 0) {
+        const int slot = L + j;
+        p.row_slot[t] = p.page_table[(int64_t)seq * p.max_pages_per_seq + slot / p.page_size] * p.page_size + slot % p.page_size;
+        reinterpret_cast<int4*>(p.row_info)[t] = int4{seq, j, n, 0};
+        // pieces that start below the live end (they were cut from the host's upper bound of the length)
+        const int nch = rq[3] > 1 ? min(rq[3], (L + n + rq[2] - 1) / rq[2]) : 0;
+        reinterpret_cast<int4*>(p.row_part)[t] = int4{rq[4] + j * p.group, rq[5], rq[6], nch};
     }
     const int half = p.head_dim / 2;
-    for (int i = threadIdx.x; i < half; i += blockDim.x) {
+    const int pos = L + row_index_in_chain(j, p.k);
+    for (int i = threadIdx.x; i < half; i += 256) {
         const double inv_freq = pow((double)p.rope_theta, -2.0 * (double)i / (double)p.head_dim);
         double s, c;
         sincos((double)pos * inv_freq, &s, &c);
         p.rope[((int64_t)t * half + i) * 2 + 0] = (float)c;
         p.rope[((int64_t)t * half + i) * 2 + 1] = (float)s;
     }
-}
-
-template <typename T>
-__global__ void embed_kernel(const T* __restrict__ embed, const int32_t* __restrict__ row_tok, float* __restrict__ h, int d) {
-    const int t = blockIdx.x;
-    const T* src = embed + (int64_t)row_tok[t] * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) h[(int64_t)t * d + i] = Store<T>::load(src + i);
 }
 
 // One 256-thread group per row.  Each thread owns up to NV float4 pieces of the row; the loads of the
@@ -56,9 +73,10 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
                                                           int64_t part_stride, const T* __restrict__ w,
                                                           T* __restrict__ a, int d, float eps, bool packed,
                                                           const int32_t* __restrict__ inv, const float* __restrict__ wts,
-                                                          int top_k) {
+                                                          int top_k, const int32_t* __restrict__ last_of) {
     __shared__ float red[4];
-    const int t = blockIdx.x;
+    const int t_out = blockIdx.x;
+    const int t = last_of ? last_of[t_out * kReqInts] + last_of[t_out * kReqInts + 1] - 1 : t_out;
     const int nq = d >> 2;                               // float4 pieces per row
     floatx4* hr = reinterpret_cast<floatx4*>(h + (int64_t)t * d);
     floatx4 x[NV];
@@ -120,7 +138,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
     for (int v = 0; v < NV; ++v) {
         const int i = threadIdx.x + v * 256;
         if (i < nq) {
-            if (S | (inv != nullptr)) hr[i] = x[v];
+            if ((S > 0 || inv) && !last_of) hr[i] = x[v];
             ss = fmaf(x[v][0], x[v][0], ss);
             ss = fmaf(x[v][1], x[v][1], ss);
             ss = fmaf(x[v][2], x[v][2], ss);
@@ -140,7 +158,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = x[v][e] * r * Store<T>::load(w + 4 * i + e);
             // four consecutive columns are contiguous in either output order
-            Store<T>::store4(a + act_index(t, 4 * i, d, packed), o);
+            Store<T>::store4(a + act_index(t_out, 4 * i, d, packed), o);
         }
     }
 }
@@ -151,14 +169,13 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
 // in the cache's K tiles); V is stored transposed, one element at a time.  head_dim % 8 == 0 (it is 64 or 128).
 template <typename T>
 __global__ __launch_bounds__(256) void rope_append_vec_kernel(RopeAppend p) {
-    const int t = blockIdx.x, b = t / p.n;
+    const int t = blockIdx.x;
     const int hd = p.hd, half = hd / 2, upq = half / 4;   // units of four pairs per head
     const int nheads = p.Hq + 2 * p.Hkv;
     const int ncol = nheads * hd;
     const int64_t stride = (int64_t)p.T * ncol;
     const int slot = p.row_slot[t];
-    const int page = p.page_table[(int64_t)p.batch_seq[b] * p.max_pages_per_seq + slot / p.geom.page_size];
-    const int tok = slot % p.geom.page_size;
+    const int page = slot / p.geom.page_size, tok = slot % p.geom.page_size;
     T* pool = reinterpret_cast<T*>(p.pool);
     for (int u = threadIdx.x; u < nheads * upq; u += 256) {
         const int head = u / upq, i = (u % upq) * 4;
@@ -234,55 +251,45 @@ __global__ void kv_copy_kernel(T* pool, KvGeom g, int layer, const int32_t* __re
 }
 
 __global__ void set_i32_kernel(int32_t* p, int32_t v) { *p = v; }
-__global__ void add_len_kernel(int32_t* seq_len, const int32_t* batch_seq, int B, int delta) {
+__global__ void add_rows_kernel(int32_t* seq_len, const int32_t* req, int B) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < B) seq_len[batch_seq[b]] += delta;
-}
-
-__global__ void add_len_ragged_kernel(int32_t* seq_len, const int32_t* batch_seq, int B, const int32_t* len, int col0, int width) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < B) seq_len[batch_seq[b]] += max(0, min(width, len[b] - col0));
+    if (b < B) seq_len[req[b * kReqInts + 7]] += req[b * kReqInts + 1];
 }
 
 // ---------------------------------------------------------------- launchers ---
 
 hipError_t prep_rows(const RowPrep& p, hipStream_t st) {
-    hipLaunchKernelGGL(prep_rows_kernel, dim3(p.B * p.n), dim3(64), 0, st, p);
-    return hipGetLastError();
-}
-
-hipError_t embed_rows(const void* embed, int dtype, const int32_t* row_tok, float* h, int T, int d, hipStream_t st) {
-    if (dtype == 1)
-        hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(T), dim3(256), 0, st, (const bf16_t*)embed, row_tok, h, d);
-    else
-        hipLaunchKernelGGL(embed_kernel<float>, dim3(T), dim3(256), 0, st, (const float*)embed, row_tok, h, d);
+    if (p.dtype == 1) hipLaunchKernelGGL(prep_rows_kernel<bf16_t>, dim3(p.T), dim3(256), 0, st, p);
+    else hipLaunchKernelGGL(prep_rows_kernel<float>, dim3(p.T), dim3(256), 0, st, p);
     return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t add_rmsnorm_t(float* h, const float* part, int S, const T* w, T* a, int T_, int d, float eps, bool packed,
-                                const int32_t* inv, const float* wts, int top_k, hipStream_t st) {
+                                const int32_t* inv, const float* wts, int top_k, const int32_t* last_of, int n_out, hipStream_t st) {
     const int64_t stride = (int64_t)T_ * d;
     const int nq = d / 4;
     if (d % 4 != 0 || nq > 256 * 8) return hipErrorInvalidValue;
-    if (nq <= 256 * 2)
-        hipLaunchKernelGGL((add_rmsnorm_kernel<T, 2>), dim3(T_), dim3(256), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k);
-    else if (nq <= 256 * 4)
-        hipLaunchKernelGGL((add_rmsnorm_kernel<T, 4>), dim3(T_), dim3(256), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k);
-    else
-        hipLaunchKernelGGL((add_rmsnorm_kernel<T, 8>), dim3(T_), dim3(256), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k);
+    const dim3 grid(last_of ? n_out : T_);
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k, last_of);
+    };
+    if (nq <= 256 * 2) launch(add_rmsnorm_kernel<T, 2>);
+    else if (nq <= 256 * 4) launch(add_rmsnorm_kernel<T, 4>);
+    else launch(add_rmsnorm_kernel<T, 8>);
     return hipGetLastError();
 }
 
 hipError_t add_rmsnorm(float* h, const float* part, int S, const void* w, void* a, int dtype, int T, int d, float eps,
-                       bool packed, hipStream_t st) {
-    if (dtype == 1) return add_rmsnorm_t<bf16_t>(h, part, S, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, nullptr, nullptr, 0, st);
-    return add_rmsnorm_t<float>(h, part, S, (const float*)w, (float*)a, T, d, eps, packed, nullptr, nullptr, 0, st);
+                       bool packed, hipStream_t st, const int32_t* last_of, int n_out) {
+    if (dtype == 1)
+        return add_rmsnorm_t<bf16_t>(h, part, S, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, nullptr, nullptr, 0, last_of, n_out, st);
+    return add_rmsnorm_t<float>(h, part, S, (const float*)w, (float*)a, T, d, eps, packed, nullptr, nullptr, 0, last_of, n_out, st);
 }
 
 hipError_t add_rmsnorm_experts(float* h, const float* y, const int32_t* inv, const float* wts, int top_k, const void* w, void* a,
-                               int T, int d, float eps, bool packed, hipStream_t st) {
-    return add_rmsnorm_t<bf16_t>(h, y, 0, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, inv, wts, top_k, st);
+                               int T, int d, float eps, bool packed, hipStream_t st, const int32_t* last_of, int n_out) {
+    return add_rmsnorm_t<bf16_t>(h, y, 0, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, inv, wts, top_k, last_of, n_out, st);
 }
 
 hipError_t rope_append(const RopeAppend& p, hipStream_t st) {
@@ -321,13 +328,8 @@ hipError_t set_i32(int32_t* p, int32_t v, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t add_len_ragged(int32_t* seq_len, const int32_t* batch_seq, int B, const int32_t* len, int col0, int width, hipStream_t st) {
-    hipLaunchKernelGGL(add_len_ragged_kernel, dim3((B + 63) / 64), dim3(64), 0, st, seq_len, batch_seq, B, len, col0, width);
-    return hipGetLastError();
-}
-
-hipError_t add_len(int32_t* seq_len, const int32_t* batch_seq, int B, int delta, hipStream_t st) {
-    hipLaunchKernelGGL(add_len_kernel, dim3((B + 63) / 64), dim3(64), 0, st, seq_len, batch_seq, B, delta);
+hipError_t add_rows(int32_t* seq_len, const int32_t* req, int B, hipStream_t st) {
+    hipLaunchKernelGGL(add_rows_kernel, dim3((B + 63) / 64), dim3(64), 0, st, seq_len, req, B);
     return hipGetLastError();
 }
 

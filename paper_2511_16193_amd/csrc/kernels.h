@@ -27,72 +27,81 @@ hipError_t gemm_bf16_ws_glu(const bf16_t* Ap, const bf16_t* Wp, bf16_t* act_out,
 hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st);
 
 // ---- elementwise.hip ----
+// One pass of rows, described by the host in one staged block (ints): per request kReqInts of
+//   first row t0, rows n, keys per split-KV piece, pieces, first row of the request's attention partials, partial rows
+//   per kv head, partial rows per piece, sequence id, prompt index and first column (prefill; else 0), 2 unused.
+// Rows of a request are consecutive; requests may have different numbers of rows (prefill).
+constexpr int kReqInts = 12;
 struct RowPrep {
-    const int32_t* batch_seq;   // [B] sequence id per request
+    const int32_t* req;         // [B][kReqInts]
     const int32_t* seq_len;     // [max_seqs] live lengths
+    const int32_t* page_table; int max_pages_per_seq, page_size;
     const int32_t* last_tokens; // [B]
     const int32_t* drafts;      // [B, N*k] (may be null when k == 0)
-    int32_t* row_tok;           // [T]
-    int32_t* row_pos;           // [T]
-    int32_t* row_slot;          // [T]
+    const int32_t* tok_matrix; int tok_ld;   // prefill: the prompts instead of last_tokens / drafts
+    const void* embed; int dtype; float* h; int d;   // embed != null: h[t,:] = the row's embedding (fp32)
+    int32_t* row_slot;          // [T] physical cache slot: page * page_size + position in the page
+    int32_t* row_info;          // [T][4] sequence id, index among the request's rows, the request's rows, 0
+    int32_t* row_part;          // [T][4] row of the first attention partial (kv head 0, piece 0, q head 0 of the group), partial
+                                //        rows per kv head, per piece, pieces to merge (0: the attention writes the row itself)
     float* rope;                // [T, head_dim/2, 2] cos, sin
-    int B, n, k, head_dim, vocab;
+    int T, B, n, k, head_dim, vocab, group;  // n > 0: every request has n rows; 0: look t0 / n up.  group = q heads per kv head
     float rope_theta;
-    // when set, the tokens come from a matrix of prompts instead: row t = b*n + j holds tok_matrix[b*tok_ld + tok_col0 + j],
-    // or, past the end of prompt b (tok_len[b] tokens), its last token (a padding row whose results are never used)
-    const int32_t* tok_matrix; const int32_t* tok_len; int tok_ld, tok_col0;
 };
 hipError_t prep_rows(const RowPrep& p, hipStream_t st);
-hipError_t embed_rows(const void* embed, int dtype, const int32_t* row_tok, float* h, int T, int d, hipStream_t st);
 // h[t,:] += sum_s part[s][t,:] (S may be 0), then a[t,:] = storage(h * rsqrt(mean(h^2)+eps) * w)
+// last_of != null (a prefill's final norm): only the last row of each of n_out requests of that table is normalised, to
+// rows 0 .. n_out-1 of a, and h is left as it was
 hipError_t add_rmsnorm(float* h, const float* part, int S, const void* w, void* a, int dtype, int T, int d, float eps,
-                       bool packed, hipStream_t st);
+                       bool packed, hipStream_t st, const int32_t* last_of = nullptr, int n_out = 0);
 // the same with the addend = weighted sum of the row's top_k expert outputs y[inv[t*top_k + j]] (bf16 models)
 hipError_t add_rmsnorm_experts(float* h, const float* y, const int32_t* inv, const float* wts, int top_k, const void* w, void* a,
-                               int T, int d, float eps, bool packed, hipStream_t st);
+                               int T, int d, float eps, bool packed, hipStream_t st, const int32_t* last_of = nullptr, int n_out = 0);
 struct RopeAppend {
     const float* qkv_part; int S;       // [S][T][(Hq+2Hkv)*hd]
     const float* rope;                  // [T][hd/2][2]
-    const int32_t* row_slot;            // [T]
-    const int32_t* batch_seq;           // [B]
-    const int32_t* page_table; int max_pages_per_seq;
+    const int32_t* row_slot;            // [T] physical cache slots
     void* q_out;                        // [T][Hq][hd] storage type
     void* pool; KvGeom geom; int layer;
-    int T, n, Hq, Hkv, hd, dtype;
+    int T, Hq, Hkv, hd, dtype;
 };
 hipError_t rope_append(const RopeAppend& p, hipStream_t st);
 hipError_t swiglu(const float* gu_part, int S, void* act, int dtype, int T, int F, bool packed, hipStream_t st);
 hipError_t kv_copy(void* pool, const KvGeom& geom, int layer, const int32_t* page_table_row, int pos0, int n,
                    void* k, void* v, int dtype, bool to_pool, hipStream_t st);
 hipError_t set_i32(int32_t* p, int32_t v, hipStream_t st);
-hipError_t add_len(int32_t* seq_len, const int32_t* batch_seq, int B, int delta, hipStream_t st);
-// seq_len[batch_seq[b]] += min(width, len[b] - col0): what request b really holds of a pass over columns col0 .. col0+width-1
-hipError_t add_len_ragged(int32_t* seq_len, const int32_t* batch_seq, int B, const int32_t* len, int col0, int width, hipStream_t st);
+// seq_len[request's sequence] += the request's rows (end of a prefill pass)
+hipError_t add_rows(int32_t* seq_len, const int32_t* req, int B, hipStream_t st);
 
 // ---- attention.hip ----
+constexpr int kItemInts = 8;
 struct AttnArgs {
     const void* q;                      // [T][Hq][hd] storage type
     const void* pool; KvGeom geom; int layer;
     const int32_t* page_table; int max_pages_per_seq;
-    const int32_t* batch_seq;           // [B]
     const int32_t* seq_len;             // [max_seqs]
+    const int32_t* row_info;            // [T][4], see RowPrep
+    const int32_t* row_part;            // [T][4]
     void* out;                          // [T][Hq*hd] storage type
-    float* part_o;                      // [B][Hkv][max_chunks][rows_pad][hd]
-    int rows_pad;                       // row pitch of the partials (a multiple of 16, >= stacked rows for the MFMA path)
+    float* part_o;                      // split-KV partials [partial row][hd]
+    float* part_ml;                     // [partial row][2] reference maximum, sum
     int row_groups;                     // set by attention(): work-groups that share one (item, head)
-    float* part_ml;                     // [B][Hkv][max_chunks][rows_pad][2]
-    int B, n, k, Hq, Hkv, hd, dtype;
-    int chunk_keys, max_chunks;
-    const int32_t* work; int n_work;    // items of the bf16 kernel, 4 ints each: request << 16 | chunk, sequence id, first key, end
-    const int32_t* req_chunk;           // [B][2] keys per piece, pieces (from the host's upper bounds of the lengths)
+    int T, n_max, k, Hq, Hkv, hd, dtype;   // n_max: most rows of a request
+    // items of the bf16 kernels, kItemInts ints each: sequence id, first key, end, rows n of the request; its first row t0,
+    // first stacked row of the item (row_items), first partial row of the piece (kv head 0; -1: the request has one piece,
+    // the kernel writes the output itself), partial rows per kv head
+    const int32_t* work; int n_work;
     const int32_t* n_work_dev;          // when set: the item count lives here (a captured launch cannot carry it)
     int grid_items;                     // when > 0: items the grid is sized for (an upper bound of the item count)
+    bool row_items;                     // prefill: an item is 64 stacked rows of a request, whose keys end at the last one it sees
+    bool merge;                         // some request has several pieces
     int min_row_tiles;                  // lower bound on the 16-row tiles of the bf16 kernel (tuning)
     int max_row_tiles;                  // most 16-row tiles one work-group takes (1..4); more rows -> row groups
     bool out_packed;                    // write `out` in the packed activation order (see act_index)
     bool force_generic;                 // take the untuned one-wave-per-row path whatever the shape
 };
-int attn_rows_pad(int n, int group);        // padded query rows per (request, kv head); 0 = MFMA path not applicable
+constexpr int kItemRows = 64;               // stacked rows of a prefill item
+bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic);   // the bf16 kernels cover the shape
 hipError_t attention(const AttnArgs& a, hipStream_t st);
 
 // ---- moe.hip ----
