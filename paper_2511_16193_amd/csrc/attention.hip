@@ -19,8 +19,7 @@
 // mostly one piece of keys: its work items are (request, 64 stacked rows, piece), their keys end at the last one the rows
 // see, and a request of one piece is finished in the kernel (no partials, no merge).
 //
-// Generic path (fp32 models, other head sizes): one wave per (row, head), plain online softmax; correct for every
-// shape, not tuned.
+// Generic path (fp32 models, other head sizes): one work-group per (row, head).
 #include <math.h>
 #include <algorithm>
 #include <type_traits>
@@ -784,46 +783,90 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     *reinterpret_cast<u32x2*>(reinterpret_cast<bf16_t*>(a.out) + act_index(t, h * HD + d, a.Hq * HD, a.out_packed)) = pk;
 }
 
-// Generic path: one wave per (new row, q head).  Lane-strided keys, per-lane online softmax with the
-// accumulator in registers, wave reduction at the end.
+// Generic path: one work-group of four waves per (new row, q head), keys in chunks of 256.  Scores with a thread per
+// key (eight consecutive dimensions of a key are one contiguous piece), softmax weights in LDS, then a thread per
+// (dimension, share of the chunk's tiles): the cache keeps eight keys of a dimension side by side, so V comes in whole
+// pieces too.  fp32 throughout, online softmax from chunk to chunk.  (With a lane per key holding all D accumulators, V
+// element by element and D wave reductions at the end, the step of 20 rows with 132 keys took 43 us a layer; 5.7 us now.)
 template <typename T, int D>
-__global__ __launch_bounds__(64) void attn_generic_kernel(AttnArgs a, float scale) {
-    const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
+__global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float scale) {
+    constexpr int CK = 256, GROUPS = 256 / D, EP = 16 / (int)sizeof(T);
+    const int t = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
     const int4 info = reinterpret_cast<const int4*>(a.row_info)[t];
     const int seq = info.x, j = info.y;
     const int L = a.seq_len[seq], total = L + info.z;
+    const int end = a.row_items ? L + j + 1 : total;      // a prefill row sees nothing beyond itself
     const int hkv = h / (a.Hq / a.Hkv);
     const int32_t* pages = a.page_table + (int64_t)seq * a.max_pages_per_seq;
     const T* pool = reinterpret_cast<const T*>(a.pool);
-    __shared__ float q[D];
-    for (int d = lane; d < D; d += 64) q[d] = Store<T>::load(reinterpret_cast<const T*>(a.q) + ((int64_t)t * a.Hq + h) * D + d);
+    __shared__ __attribute__((aligned(16))) float q[D];
+    __shared__ __attribute__((aligned(16))) float p[CK];
+    __shared__ float red[4], acc_sh[GROUPS][D];
+    for (int d = tid; d < D; d += 256) q[d] = Store<T>::load(reinterpret_cast<const T*>(a.q) + ((int64_t)t * a.Hq + h) * D + d);
     __syncthreads();
-    float m = -INFINITY, l = 0.f, acc[D];
+    auto load8 = [](const T* src, float* dst) {            // eight elements, 16-byte aligned
 #pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] = 0.f;
-    for (int key = lane; key < total; key += 64) {
-        if (key >= L && !row_sees(j, key - L, a.k)) continue;
-        const int page = pages[key / a.geom.page_size], tok = key % a.geom.page_size;
-        float s = 0.f;
-#pragma unroll 8
-        for (int d = 0; d < D; ++d) s = fmaf(q[d], Store<T>::load(pool + kv_k_index(a.geom, a.layer, page, hkv, tok, d)), s);
-        s *= scale;
-        const float mn = fmaxf(m, s);
-        const float alpha = expf(m - mn), p = expf(s - mn);
-        l = l * alpha + p;
-#pragma unroll 8
-        for (int d = 0; d < D; ++d)
-            acc[d] = acc[d] * alpha + p * Store<T>::load(pool + kv_v_index(a.geom, a.layer, page, hkv, tok, d));
-        m = mn;
+        for (int u = 0; u < 8 / EP; ++u) {
+            const u32x4 w = *reinterpret_cast<const u32x4*>(src + u * EP);
+#pragma unroll
+            for (int e = 0; e < EP; ++e)
+                dst[u * EP + e] = EP == 4 ? __uint_as_float(w[e]) : __uint_as_float((e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
+        }
+    };
+    const int dim = tid % D, grp = tid / D;
+    float m = -INFINITY, l = 0.f, acc = 0.f;
+    for (int c0 = 0; c0 < end; c0 += CK) {
+        const int key = c0 + tid;
+        float s = -INFINITY;
+        if (key < end && (key < L || row_sees(j, key - L, a.k))) {
+            const T* kp = pool + kv_k_index(a.geom, a.layer, pages[key / a.geom.page_size], hkv, key % a.geom.page_size, 0);
+            s = 0.f;
+#pragma unroll
+            for (int c = 0; c < D / 8; ++c) {               // dims 8 c ..: slice c / 4 of 32 dims, lane group c % 4 (16 keys of 8 each)
+                float kv[8];
+                load8(kp + ((c >> 2) * 64 + (c & 3) * 16) * 8, kv);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s = fmaf(q[8 * c + e], kv[e], s);
+            }
+            s *= scale;
+        }
+        const float mw = wave_max(s);
+        if ((tid & 63) == 0) red[tid >> 6] = mw;
+        __syncthreads();
+        const float m_new = fmaxf(m, fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+        const float ms = m_new == -INFINITY ? 0.f : m_new;
+        const float pv = expf(s - ms), alpha = expf(m - ms);
+        p[tid] = pv;
+        l = l * alpha + pv;
+        acc *= alpha;
+        m = m_new;
+        __syncthreads();
+        for (int tile = grp; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) {
+            const int k0 = c0 + tile * TILE_KEYS;           // a tile lies inside a page; keys past the end have weight 0
+            const T* vp = pool + kv_v_index(a.geom, a.layer, pages[k0 / a.geom.page_size], hkv, k0 % a.geom.page_size, dim);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float v[8];
+                load8(vp + g * 128, v);                     // keys 4 g .. 4 g + 3 and 16 + 4 g .. of the tile
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc = fmaf(p[tile * TILE_KEYS + 4 * g + e], v[e], acc);
+                    acc = fmaf(p[tile * TILE_KEYS + 16 + 4 * g + e], v[4 + e], acc);
+                }
+            }
+        }
+        __syncthreads();
     }
-    const float M = wave_max(m);
-    const float f = m == -INFINITY ? 0.f : expf(m - M);
-    const float den = wave_sum(l * f);
-    T* out = reinterpret_cast<T*>(a.out);
+    acc_sh[grp][dim] = acc;
+    l = wave_sum(l);
+    if ((tid & 63) == 0) red[tid >> 6] = l;
+    __syncthreads();
+    if (tid < D) {
+        float v = acc_sh[0][tid];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const float v = wave_sum(acc[d] * f);
-        if (lane == 0) Store<T>::store(out + act_index(t, h * D + d, a.Hq * D, a.out_packed), v / den);
+        for (int g = 1; g < GROUPS; ++g) v += acc_sh[g][tid];
+        const float den = (red[0] + red[1]) + (red[2] + red[3]);
+        Store<T>::store(reinterpret_cast<T*>(a.out) + act_index(t, h * D + tid, a.Hq * D, a.out_packed), v / den);
     }
 }
 
@@ -879,13 +922,13 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
     }
     dim3 grid(a.T, a.Hq);
     if (a.dtype == 1 && a.hd == 128)
-        hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 128>), grid, dim3(64), 0, st, a, scale);
+        hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 128>), grid, dim3(256), 0, st, a, scale);
     else if (a.dtype == 1 && a.hd == 64)
-        hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 64>), grid, dim3(64), 0, st, a, scale);
+        hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 64>), grid, dim3(256), 0, st, a, scale);
     else if (a.dtype == 0 && a.hd == 128)
-        hipLaunchKernelGGL((attn_generic_kernel<float, 128>), grid, dim3(64), 0, st, a, scale);
+        hipLaunchKernelGGL((attn_generic_kernel<float, 128>), grid, dim3(256), 0, st, a, scale);
     else if (a.dtype == 0 && a.hd == 64)
-        hipLaunchKernelGGL((attn_generic_kernel<float, 64>), grid, dim3(64), 0, st, a, scale);
+        hipLaunchKernelGGL((attn_generic_kernel<float, 64>), grid, dim3(256), 0, st, a, scale);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

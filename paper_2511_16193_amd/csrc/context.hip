@@ -817,10 +817,13 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         // gate/up projection with SwiGLU in its epilogue: the [T, 2F] fp32 intermediate never exists
         ProfScope prof(c, SV_PROF_GEMM);
         SV_HIP(c, gemm_bf16_ws_glu((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<bf16_t>(L.act), T, m.d_ff, d, st, c->gemm_tile));
+    } else if (m.dtype == SV_FP32) {
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, gemm_f32_glu((const float*)a_norm, (const float*)c->wgu[l], c->at<float>(L.act), T, m.d_ff, d, st));
     } else {
         int s_gu = 1;
         SV_TRY(gemm(c, a_norm, c->wgu[l], part, T, 2 * m.d_ff, d, &s_gu));
-        SV_HIP(c, swiglu(part, s_gu, c->at<void>(L.act), m.dtype, T, m.d_ff, c->packed, st));
+        SV_HIP(c, swiglu(part, s_gu, c->at<void>(L.act), T, m.d_ff, c->packed, st));
     }
     SV_TRY(gemm(c, c->at<void>(L.act), c->wdown[l], part, T, d, m.d_ff, &pending));
     return SV_OK;

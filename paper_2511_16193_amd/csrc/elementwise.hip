@@ -215,9 +215,9 @@ __global__ __launch_bounds__(256) void rope_append_vec_kernel(RopeAppend p) {
     }
 }
 
-template <typename T>
+// Row-major bf16 models (packed and fp32 ones have the product in the epilogue of their gate/up projection).
 __global__ __launch_bounds__(256) void swiglu_kernel(const float* __restrict__ part, int S, int64_t stride,
-                                                     T* __restrict__ act, int F, bool packed) {
+                                                     bf16_t* __restrict__ act, int F, bool packed) {
     const int t = blockIdx.y;
     const int f = blockIdx.x * 256 + threadIdx.x;
     if (f >= F) return;
@@ -227,8 +227,7 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const float* __restrict__ p
         g += src[s * stride + f];
         u += src[s * stride + F + f];
     }
-    const float y = g / (1.0f + expf(-g)) * u;
-    Store<T>::store(act + act_index(t, f, F, packed), y);
+    act[act_index(t, f, F, packed)] = f2bf(g / (1.0f + expf(-g)) * u);
 }
 
 template <typename T>
@@ -301,13 +300,8 @@ hipError_t rope_append(const RopeAppend& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t swiglu(const float* gu_part, int S, void* act, int dtype, int T, int F, bool packed, hipStream_t st) {
-    const int64_t stride = (int64_t)T * 2 * F;
-    dim3 grid((F + 255) / 256, T);
-    if (dtype == 1)
-        hipLaunchKernelGGL(swiglu_kernel<bf16_t>, grid, dim3(256), 0, st, gu_part, S, stride, (bf16_t*)act, F, packed);
-    else
-        hipLaunchKernelGGL(swiglu_kernel<float>, grid, dim3(256), 0, st, gu_part, S, stride, (float*)act, F, packed);
+hipError_t swiglu(const float* gu_part, int S, void* act, int T, int F, bool packed, hipStream_t st) {
+    hipLaunchKernelGGL(swiglu_kernel, dim3((F + 255) / 256, T), dim3(256), 0, st, gu_part, S, (int64_t)T * 2 * F, (bf16_t*)act, F, packed);
     return hipGetLastError();
 }
 

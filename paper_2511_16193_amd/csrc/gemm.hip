@@ -728,36 +728,124 @@ hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, i
     }
 }
 
-// fp32 path (small models only): 32x32 output tile per 256-thread group, 4 outputs per thread, every
-// access bounds-checked.  Accumulates in fp32 in ascending k.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
-                                                       float* __restrict__ out, int M, int N, int K) {
-    __shared__ float As[32][33], Ws[32][33];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;      // ty 0..7
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 32) {
+// fp32 path (small models): v_mfma_f32_16x16x4_f32, operands straight from global memory.  A wave holds MT x NT tiles of
+// 16 rows x 16 features; lane 16 g + r of an operand tile loads four consecutive k (4 g .. 4 g + 3) of its row r in one
+// 16-byte piece and feeds them to four MFMAs, the reduction index of an MFMA being only a label as long as both operands
+// agree on it.  Two groups of 16 k are in flight.  KW waves of a work-group share the reduction (each takes every KW-th group
+// of 32 k) and add their tiles up in LDS; the other waves of the work-group have tiles of their own.
+// What bounds it at the few rows of a small model's step is one chain of load latencies, so the reduction is spread over
+// eight waves: 20 rows, K = 256..1024: 38 us with a scalar 32 x 32 tile per work-group (one FMA per 1.25 LDS reads, 24-64
+// work-groups, K walked serially), 5 us now.  Many rows take 64 x 64 tiles per wave.
+// GLU: NT = 2, tile 0 gate rows, tile 1 the up rows of the same features (W has 2 F rows); out [M][F] = silu(gate) * up.
+// N, K and M are arbitrary: rows and features beyond the end read the last one and are not stored, k beyond the end counts
+// as zero.
+template <int MT, int NT, int KW, int WAVES, bool GLU, bool VEC>
+__global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
+                                                              float* __restrict__ out, int M, int N, int K, int tiles_m) {
+    constexpr int TILES = WAVES / KW;                      // wave tiles per work-group, side by side along the features
+    static_assert(TILES == 1 || KW == 1, "the exchange area holds one wave tile");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & 15, g = lane >> 4;
+    const int kw = wave % KW, sub = wave / KW;
+    const int m0 = (blockIdx.x % tiles_m) * 16 * MT;
+    const int n0 = ((blockIdx.x / tiles_m) * TILES + sub) * 16 * (GLU ? 1 : NT);
+    const float* a_row[MT];
+    const float* w_row[NT];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = ty + 8 * r;
-            const int k = k0 + tx;
-            As[row][tx] = (m0 + row < M && k < K) ? A[(int64_t)(m0 + row) * K + k] : 0.f;
-            Ws[row][tx] = (n0 + row < N && k < K) ? W[(int64_t)(n0 + row) * K + k] : 0.f;
+    for (int j = 0; j < MT; ++j) a_row[j] = A + (int64_t)min(m0 + 16 * j + r, M - 1) * K;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+        w_row[i] = W + (int64_t)(GLU ? i * N + min(n0 + r, N - 1) : min(n0 + 16 * i + r, N - 1)) * K;
+    floatx4 acc[NT][MT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](const float* row, int k) {
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        if (VEC) {                                         // K % 4 == 0: a piece lies inside or outside as a whole
+            if (k < K) v = *reinterpret_cast<const floatx4*>(row + k);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = k + e < K ? row[k + e] : 0.f;
         }
-        __syncthreads();
-#pragma unroll 8
-        for (int k = 0; k < 32; ++k) {
-            const float w = Ws[tx][k];
+        return v;
+    };
+    for (int k0 = kw * 32; k0 < K; k0 += 32 * KW) {
+        floatx4 a[2][MT], w[2][NT];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] = fmaf(As[ty + 8 * r][k], w, acc[r]);
+        for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int j = 0; j < MT; ++j) a[u][j] = load(a_row[j], k0 + 16 * u + 4 * g);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) w[u][i] = load(w_row[i], k0 + 16 * u + 4 * g);
         }
-        __syncthreads();
-    }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = m0 + ty + 8 * r, n = n0 + tx;
-        if (m < M && n < N) out[(int64_t)m * N + n] = acc[r];
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+#pragma unroll
+                    for (int j = 0; j < MT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][e], a[u][j][e], acc[i][j], 0, 0, 0);
     }
+    if (KW > 1) {
+        __shared__ floatx4 part[KW > 1 ? KW : 1][NT * MT][64];
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) part[kw][i * MT + j][lane] = acc[i][j];
+        __syncthreads();
+        // every wave adds up and stores a share of the tiles; gate and up of a feature stay together
+        for (int j = kw; j < MT; j += KW)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                floatx4 s = part[0][i * MT + j][lane];
+#pragma unroll
+                for (int q = 1; q < KW; ++q) s += part[q][i * MT + j][lane];
+                acc[i][0] = s;
+                if (!GLU || i == NT - 1) {
+                    const int m = m0 + 16 * j + r;
+                    const int n = n0 + (GLU ? 0 : 16 * i) + 4 * g;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (m < M && n + e < N)
+                            out[(int64_t)m * N + n + e] = GLU ? acc[0][0][e] / (1.0f + expf(-acc[0][0][e])) * s[e] : s[e];
+                }
+            }
+        return;
+    }
+    // acc[i][j][e] <-> feature n0 + 16 i + 4 g + e, row m0 + 16 j + r
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+        const int m = m0 + 16 * j + r;
+#pragma unroll
+        for (int i = 0; i < (GLU ? 1 : NT); ++i) {
+            const int n = n0 + 16 * i + 4 * g;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (m < M && n + e < N)
+                    out[(int64_t)m * N + n + e] =
+                        GLU ? acc[0][j][e] / (1.0f + expf(-acc[0][j][e])) * acc[NT - 1][j][e] : acc[i][j][e];
+        }
+    }
+}
+
+template <bool GLU>
+static hipError_t launch_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st) {
+    auto launch = [&](auto vec, auto novec, int rows, int feats, int threads) {
+        const int tiles_m = (M + rows - 1) / rows, tiles_n = (N + feats - 1) / feats;
+        if (K % 4 == 0) hipLaunchKernelGGL(vec, dim3(tiles_m * tiles_n), dim3(threads), 0, st, A, W, out, M, N, K, tiles_m);
+        else hipLaunchKernelGGL(novec, dim3(tiles_m * tiles_n), dim3(threads), 0, st, A, W, out, M, N, K, tiles_m);
+        return hipGetLastError();
+    };
+    // 64-row wave tiles once they make a work-group for every other CU; below that eight waves share a reduction
+    constexpr int NTB = GLU ? 2 : 4, NTS = GLU ? 2 : 1, FB = GLU ? 64 : 256, FS = 16;
+    if ((long long)((M + 63) / 64) * ((N + FB - 1) / FB) >= 128)
+        return launch(gemm_f32_kernel<4, NTB, 1, 4, GLU, true>, gemm_f32_kernel<4, NTB, 1, 4, GLU, false>, 64, FB, 256);
+    if (M <= 16) return launch(gemm_f32_kernel<1, NTS, 8, 8, GLU, true>, gemm_f32_kernel<1, NTS, 8, 8, GLU, false>, 16, FS, 512);
+    return launch(gemm_f32_kernel<2, NTS, 8, 8, GLU, true>, gemm_f32_kernel<2, NTS, 8, 8, GLU, false>, 32, FS, 512);
 }
 
 template <int MT, int NT, int WM, int WN>
@@ -817,8 +905,11 @@ hipError_t gemm_bf16(const bf16_t* A, const bf16_t* W, float* out, int M, int N,
 }
 
 hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st) {
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 31) / 32, (M + 31) / 32), dim3(256), 0, st, A, W, out, M, N, K);
-    return hipGetLastError();
+    return launch_f32<false>(A, W, out, M, N, K, st);
+}
+
+hipError_t gemm_f32_glu(const float* A, const float* W, float* act, int M, int F, int K, hipStream_t st) {
+    return launch_f32<true>(A, W, act, M, F, K, st);
 }
 
 }  // namespace sv

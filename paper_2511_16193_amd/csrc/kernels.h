@@ -25,6 +25,8 @@ constexpr double kTileRateGlu = 4.85;
 // tile_mode: -1 = the 256 x 256 kernel where it pays, 0 = never, 1 = whenever the shape allows
 hipError_t gemm_bf16_ws_glu(const bf16_t* Ap, const bf16_t* Wp, bf16_t* act_out, int M, int F, int K, hipStream_t st, int tile_mode = -1);
 hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st);
+// W [2F][K] (gate rows, then up rows): act [M][F] = silu(gate) * up
+hipError_t gemm_f32_glu(const float* A, const float* W, float* act, int M, int F, int K, hipStream_t st);
 
 // ---- elementwise.hip ----
 // One pass of rows, described by the host in one staged block (ints): per request kReqInts of
@@ -66,7 +68,7 @@ struct RopeAppend {
     int T, Hq, Hkv, hd, dtype;
 };
 hipError_t rope_append(const RopeAppend& p, hipStream_t st);
-hipError_t swiglu(const float* gu_part, int S, void* act, int dtype, int T, int F, bool packed, hipStream_t st);
+hipError_t swiglu(const float* gu_part, int S, void* act, int T, int F, bool packed, hipStream_t st);   // bf16
 hipError_t kv_copy(void* pool, const KvGeom& geom, int layer, const int32_t* page_table_row, int pos0, int n,
                    void* k, void* v, int dtype, bool to_pool, hipStream_t st);
 hipError_t set_i32(int32_t* p, int32_t v, hipStream_t st);

@@ -1,0 +1,28 @@
+"""fp32 models at sizes where the projection tiles and the attention's chunks end raggedly, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import verify as OV
+import workloads as W
+from harness import Case, compare_step, LOGIT_TOL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch,k,chains,hd,d,ff,vocab,lo,hi", [
+    (1, 0, 1, 64, 128, 333, 1001, 0, 0),        # one row, reductions of 333 and vocabularies of 1001: no whole 16-byte pieces
+    (4, 3, 1, 64, 252, 64, 515, 254, 258),      # 16 rows; contexts that end around a chunk of 256 keys
+    (3, 5, 2, 128, 128, 1024, 640, 30, 700),    # 33 rows; several chunks, two chains, head_dim 128
+    (220, 4, 1, 64, 64, 128, 2053, 1, 40),      # 1100 rows: 64-row tiles per wave, remainders in rows and features
+])
+def test_fp32_step(batch, k, chains, hd, d, ff, vocab, lo, hi):
+    shape = W.Shape("f32-edge", 2, d, 4, 2, hd, ff, vocab, dtype="fp32", rope_theta=1e4, batch=batch, k=k, n_chains=chains, seed=31)
+    rng = np.random.default_rng(7)
+    case = Case(shape, rng.integers(lo, hi + 1, size=batch), verify_mode=OV.STOCHASTIC, sample_mode=OV.SAMPLE_EXP_RACE)
+    x0 = W.make_tokens((batch,), vocab, shape.seed, "x0")
+    q = W.make_random_q((batch, chains, k), vocab, 1.0, shape.seed) if k else None
+    drafts = W.sample_from(q, shape.seed).numpy() if k else np.zeros((batch, 1, 0), dtype=np.int64)
+    r, g = case.step(x0, drafts, q, W.make_uniforms((batch, chains, k + 1), shape.seed))
+    err, exempt, diverged = compare_step(r, g, "fp32", k)
+    assert err < LOGIT_TOL["fp32"] and len(diverged) <= 1
+    case.close()
