@@ -123,7 +123,7 @@ typedef struct {
     int32_t *accepted_len; /* device [B]       a_b in 0..k                                  */
     int32_t *out_tokens;   /* device [B, k+1]  a_b accepted drafts, then the supplied token; rest -1 */
     int32_t *best_chain;   /* device [B]       chain that was kept                          */
-    float *logits;         /* device [B*n, vocab] or NULL: copy of the target logits (row order = b, then x0, chain 0 drafts, chain 1 ...) */
+    float *logits;         /* device [B*n, vocab] or NULL: receives the target logits (row order = b, then x0, chain 0 drafts, chain 1 ...) */
 } sv_out;
 
 /* Sizes of the two caller-provided device buffers for (model, runtime). 0 on invalid arguments. */

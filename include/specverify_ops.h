@@ -61,7 +61,7 @@ int sv_op_sample(const float *logits, const int32_t *drafts, const float *draft_
 
 /* sv_op_sample for callers that cannot allocate device memory or bring a scratch buffer: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as
- * sv_op_sample without `scratch`: the scratch lives in a static device array of the library (624 KiB, held on
+ * sv_op_sample without `scratch`: the scratch lives in a static device array of the library (1.2 MiB, held on
  * every GPU the library runs on until the process ends).  Limits: B * (1 + N * k) <= 4096 logits rows and
  * B * N <= 4096 chains; beyond them SV_EINVAL and nothing is enqueued.  The call allocates nothing (no
  * hipMalloc / hipFree, no allocating library routine); the caller still provides inputs and outputs.  All

@@ -108,8 +108,8 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int tile_mode = -1, int ma
 }
 
 struct Layout {                       // byte offsets into the workspace
-    size_t seq_len, page_table, upd, stage, row_info, row_part, row_slot, chain_acc, chain_tok, chain_row, draw_part;
-    size_t rope, row_stat, h, a_norm, q, attn, part, act, logits, part_o, part_ml, total;
+    size_t seq_len, page_table, stage, row_info, row_part, row_slot, stat_part, draw_part;
+    size_t rope, h, a_norm, q, attn, part, act, logits, part_o, part_ml, total;
     size_t moe_ids, moe_w, moe_cnt, moe_off, moe_perm, moe_inv, moe_act, moe_y, moe_logits;   // mixture-of-experts scratch
     int T, P;                         // rows of a step, rows of a pass (a prefill pass may hold more)
     int max_chunks, max_items, max_upd;
@@ -139,7 +139,6 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
     L.P = P;
     L.seq_len = take(sizeof(int32_t) * r.max_seqs);
     L.page_table = take(sizeof(int32_t) * (size_t)r.max_seqs * r.max_pages_per_seq);
-    L.upd = take(sizeof(int32_t) * 2 * (size_t)r.max_batch);
     L.max_chunks = (int)(((size_t)r.max_pages_per_seq * r.page_size + kChunkKeys - 1) / kChunkKeys);
     L.max_items = r.max_batch * L.max_chunks + P * G / kItemRows + r.max_batch + 2048;
     L.max_upd = std::max(8 * r.max_batch, P / r.page_size + 2 * r.max_batch);
@@ -152,12 +151,9 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
     L.row_info = take(sizeof(int32_t) * 4 * (size_t)P);
     L.row_part = take(sizeof(int32_t) * 4 * (size_t)P);
     L.row_slot = take(sizeof(int32_t) * P);
-    L.chain_acc = take(sizeof(int32_t) * r.max_batch * r.max_chains);
-    L.chain_tok = take(sizeof(int32_t) * r.max_batch * r.max_chains);
-    L.chain_row = take(sizeof(int32_t) * r.max_batch * r.max_chains);
-    L.draw_part = take(sizeof(float) * 4 * kDrawParts * T);       // per (request, chain); per row in match mode
+    L.stat_part = take(sizeof(float) * 4 * sample_part_entries(T));
+    L.draw_part = take(sizeof(float) * 4 * sample_part_entries(T));
     L.rope = take(sizeof(float) * (size_t)P * m.head_dim);
-    L.row_stat = take(sizeof(float) * 4 * T);
     L.h = take(sizeof(float) * (size_t)P * m.d_model);
     const size_t Tp = (size_t)(P + 31) / 32 * 32;          // packed activations come in 32-row tiles
     L.a_norm = take(es * Tp * m.d_model);
@@ -217,9 +213,11 @@ __global__ void apply_page_updates_kernel(int32_t* page_table, int mpps, const i
     if (i < n) page_table[(int64_t)upd[3 * i] * mpps + upd[3 * i + 1]] = upd[3 * i + 2];
 }
 
-__global__ void set_lens_kernel(int32_t* seq_len, const int32_t* pairs, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) seq_len[pairs[2 * i]] = pairs[2 * i + 1];
+constexpr int kLenPairs = 240;        // (sequence, length) pairs that travel as one launch's arguments
+struct LenPairs { int32_t v[2 * kLenPairs]; };
+__global__ void set_lens_kernel(int32_t* seq_len, LenPairs pairs, int n) {
+    const int i = threadIdx.x;
+    if (i < n) seq_len[pairs.v[2 * i]] = pairs.v[2 * i + 1];
 }
 
 }  // namespace
@@ -392,7 +390,7 @@ extern "C" int verify_init(const sv_model* m, const sv_weights* w, const sv_runt
     c->attn_max_rt = 4;
     c->attn_chunk_opt = 0;
     c->prof_mask = 0;
-    const size_t slot_ints = std::max<size_t>(L.st_total, 2 * (size_t)r->max_batch);
+    const size_t slot_ints = L.st_total;
     for (int i = 0; i < kRing; ++i) { c->staging[i] = nullptr; c->staged[i] = nullptr; c->staged_valid[i] = false; }
     for (int i = 0; i < kRing; ++i) {
         if (hipHostMalloc(reinterpret_cast<void**>(&c->staging[i]), slot_ints * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
@@ -902,20 +900,21 @@ extern "C" int verify_prefill_batch(sv_ctx* c, const int32_t* seq_ids, int32_t B
 }
 
 // Everything verify_step enqueues after the batch is staged: forward pass, accept/reject + draw, chain choice,
-// rollback, optional copy of the logits.
+// rollback.
 static int step_device_work(sv_ctx* c, const sv_batch* bt, const Pass& ps, const int32_t* drafts, const float* draft_probs,
                             const float* uniforms, const sv_out* out) {
     const int B = bt->B, k = bt->k, N = bt->N;
     int pending = 0;
     SV_TRY(forward_layers(c, ps, bt->last_tokens, drafts, nullptr, pending));
     SV_TRY(add_norm(c, ps.T, pending, c->final_norm));
-    SV_TRY(head_rows(c, ps.T, c->at<float>(c->lay.logits)));
-
     const Layout& L = c->lay;
+    float* logits = out->logits ? out->logits : c->at<float>(L.logits);   // a caller that wants them has them written in place
+    SV_TRY(head_rows(c, ps.T, logits));
+
     SampleArgs sa;
-    sa.logits = c->at<float>(L.logits); sa.drafts = drafts; sa.draft_probs = draft_probs; sa.uniforms = uniforms;
-    sa.draft_lens = bt->draft_lens; sa.row_stat = c->at<float>(L.row_stat);
-    sa.chain_acc = c->at<int32_t>(L.chain_acc); sa.chain_tok = c->at<int32_t>(L.chain_tok); sa.chain_row = c->at<int32_t>(L.chain_row); sa.draw_part = c->at<float>(L.draw_part);
+    sa.logits = logits; sa.drafts = drafts; sa.draft_probs = draft_probs; sa.uniforms = uniforms;
+    sa.draft_lens = bt->draft_lens; sa.stat_part = c->at<float>(L.stat_part); sa.draw_part = c->at<float>(L.draw_part);
+    sa.seq_len = c->at<int32_t>(L.seq_len); sa.batch_seq = c->at<int32_t>(L.stage) + L.st_seq;
     sa.accepted_len = out->accepted_len; sa.out_tokens = out->out_tokens; sa.best_chain = out->best_chain;
     sa.B = B; sa.N = N; sa.k = k; sa.V = c->model.vocab; sa.verify_mode = c->rt.verify_mode; sa.sample_mode = c->rt.sample_mode;
     sa.temperature = c->rt.temperature;
@@ -931,11 +930,8 @@ static int step_device_work(sv_ctx* c, const sv_batch* bt, const Pass& ps, const
     rb.accepted_len = out->accepted_len; rb.best_chain = out->best_chain; rb.B = B; rb.N = N; rb.k = k;
     {
         ProfScope prof(c, SV_PROF_ROLLBACK);
-        SV_HIP(c, rollback(rb, c->stream));
+        SV_HIP(c, compact_kept(rb, true, c->stream));
     }
-    if (out->logits)
-        SV_HIP(c, hipMemcpyAsync(out->logits, sa.logits, sizeof(float) * (size_t)ps.T * c->model.vocab,
-                                 hipMemcpyDeviceToDevice, c->stream));
     return SV_OK;
 }
 
@@ -1063,15 +1059,12 @@ extern "C" int sv_op_sample(const float* logits, const int32_t* drafts, const fl
     if (!logits || (k > 0 && !drafts) || !scratch || !accepted_len || !out_tokens || !best_chain || B <= 0 || N <= 0 ||
         k < 0 || V <= 0 || !(temperature > 0.f) || verify_mode < 0 || verify_mode > 2 || (verify_mode != SV_GREEDY && !uniforms))
         return SV_EINVAL;
-    const int T = B * (1 + N * k), S = B * N;
-    char* p = reinterpret_cast<char*>(scratch);
+    const int T = B * (1 + N * k);
     SampleArgs sa;
     sa.logits = logits; sa.drafts = drafts; sa.draft_probs = draft_probs; sa.uniforms = uniforms; sa.draft_lens = draft_lens;
-    sa.row_stat = reinterpret_cast<float*>(p); p += align_up(sizeof(float) * 4 * T);
-    sa.chain_acc = reinterpret_cast<int32_t*>(p); p += align_up(sizeof(int32_t) * S);
-    sa.chain_tok = reinterpret_cast<int32_t*>(p); p += align_up(sizeof(int32_t) * S);
-    sa.chain_row = reinterpret_cast<int32_t*>(p); p += align_up(sizeof(int32_t) * S);
-    sa.draw_part = reinterpret_cast<float*>(p);
+    sa.stat_part = reinterpret_cast<float*>(scratch);
+    sa.draw_part = sa.stat_part + 4 * sample_part_entries(T);
+    sa.seq_len = nullptr; sa.batch_seq = nullptr;
     sa.accepted_len = accepted_len; sa.out_tokens = out_tokens; sa.best_chain = best_chain;
     sa.B = B; sa.N = N; sa.k = k; sa.V = V; sa.verify_mode = verify_mode; sa.sample_mode = sample_mode; sa.temperature = temperature;
     return sample_verify(sa, (hipStream_t)stream) == hipSuccess ? SV_OK : SV_EHIP;
@@ -1079,8 +1072,7 @@ extern "C" int sv_op_sample(const float* logits, const int32_t* drafts, const fl
 
 extern "C" size_t sv_op_sample_scratch_bytes(int B, int N, int k) {
     if (B <= 0 || N <= 0 || k < 0) return 0;
-    return align_up(sizeof(float) * 4 * (size_t)B * (1 + N * k)) + 3 * align_up(sizeof(int32_t) * (size_t)B * N) +
-           align_up(sizeof(float) * 4 * kDrawParts * (size_t)B * (1 + N * k));      // match mode draws per row
+    return 2 * sizeof(float) * 4 * sample_part_entries(B * (1 + N * k));
 }
 
 struct MoeScratch { size_t ids, w, cnt, off, perm, inv, act, y, logits, total; };
@@ -1188,7 +1180,8 @@ extern "C" int sv_op_rollback(sv_ctx* c, const int32_t* seq_ids, int B, int N, i
     rb.accepted_len = accepted_len; rb.best_chain = best_chain; rb.B = B; rb.N = N; rb.k = k;
     {
         ProfScope prof(c, SV_PROF_ROLLBACK);
-        SV_HIP(c, rollback(rb, c->stream, commit != 0));
+        SV_HIP(c, compact_kept(rb, false, c->stream));
+        if (commit) SV_HIP(c, commit_lens(rb, c->stream));
     }
     if (commit)
         for (int b = 0; b < B; ++b) c->seqs[seq_ids[b]].len_ub += k + 1;
@@ -1228,15 +1221,13 @@ extern "C" int sv_seq_set_lens(sv_ctx* c, const int32_t* seq_ids, const int32_t*
         if (lens[i] < 0 || lens[i] > (int)c->seqs[id].pages.size() * c->rt.page_size)
             return c->fail(SV_EINVAL, "length %d beyond the pages sequence %d holds", lens[i], id);
     }
-    int slot;
-    SV_TRY(take_slot(c, slot));
-    int32_t* st = c->staging[slot];
-    for (int i = 0; i < n; ++i) { st[2 * i] = seq_ids[i]; st[2 * i + 1] = lens[i]; }
-    SV_HIP(c, hipMemcpyAsync(c->at<int32_t>(c->lay.upd), st, 2 * n * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL(set_lens_kernel, dim3((n + 63) / 64), dim3(64), 0, c->stream, c->at<int32_t>(c->lay.seq_len),
-                       c->at<int32_t>(c->lay.upd), n);
-    SV_HIP(c, hipGetLastError());
-    SV_TRY(release_slot(c, slot));
+    for (int i0 = 0; i0 < n; i0 += kLenPairs) {
+        const int m = std::min(kLenPairs, n - i0);
+        LenPairs pairs;
+        for (int i = 0; i < m; ++i) { pairs.v[2 * i] = seq_ids[i0 + i]; pairs.v[2 * i + 1] = lens[i0 + i]; }
+        hipLaunchKernelGGL(set_lens_kernel, dim3(1), dim3(256), 0, c->stream, c->at<int32_t>(c->lay.seq_len), pairs, m);
+        SV_HIP(c, hipGetLastError());
+    }
     for (int i = 0; i < n; ++i) c->seqs[seq_ids[i]].len_ub = lens[i];
     return SV_OK;
 }

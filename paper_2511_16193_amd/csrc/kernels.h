@@ -136,18 +136,18 @@ struct SampleArgs {
     const float* draft_probs;           // [B][N][k][V] or null
     const float* uniforms;              // [B][N][k+1] or null (greedy)
     const int32_t* draft_lens;          // [B] or null
-    float* row_stat;                    // [T][4]: max logit, sum exp((x-max)/temp), argmax id (as int bits), unused
-    int32_t* chain_acc;                 // [B][N]
-    int32_t* chain_tok;                 // [B][N]
-    int32_t* chain_row;                 // [B][N] scratch
-    float* draw_part;                   // [B][N][kDrawParts][4] winners of the parts of the exponential race
+    float* stat_part;                   // [sample_part_entries(T)][4] a row part's max, sum exp((x-max)/temp), argmax id (as int bits)
+    float* draw_part;                   // [sample_part_entries(T)][4] winners of the parts of a race
     int32_t* accepted_len;              // [B]
     int32_t* out_tokens;                // [B][k+1]
     int32_t* best_chain;                // [B]
     int B, N, k, V, verify_mode, sample_mode;
     float temperature;
+    int32_t* seq_len; const int32_t* batch_seq;   // when set: live lengths, advanced by accepted + 1
+    int stat_parts, draw_parts;         // set by sample_verify()
 };
 constexpr int kDrawParts = 8;
+size_t sample_part_entries(int rows);
 hipError_t sample_verify(const SampleArgs& a, hipStream_t st);
 struct RollbackArgs {
     void* pool; KvGeom geom; int n_layers, dtype;
@@ -158,7 +158,9 @@ struct RollbackArgs {
     const int32_t* best_chain;
     int B, N, k;
 };
-// move the kept chain's accepted K/V entries next to x0 (N > 1 only); commit: also advance the live lengths by a + 1
-hipError_t rollback(const RollbackArgs& a, hipStream_t st, bool commit = true);
+// move the kept chain's accepted K/V entries next to x0 (N > 1 only); committed: the live lengths have been advanced already
+hipError_t compact_kept(const RollbackArgs& a, bool committed, hipStream_t st);
+// advance the live lengths by accepted + 1
+hipError_t commit_lens(const RollbackArgs& a, hipStream_t st);
 
 }  // namespace sv

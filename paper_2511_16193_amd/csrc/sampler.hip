@@ -1,78 +1,103 @@
-// Accept / reject over the target logits, the replacement or bonus draw, the choice of the chain to
-// keep, and the cache rollback.  Three passes over vocabulary-wide data, all bound by HBM:
-//   row_stats   every logits row once: max, sum exp((x - max)/temp), argmax (lowest id on ties)
-//   accept      per (request, chain), scalar: walk the drafts; p_i(d_i) from the row statistics and
-//               one gathered logit; u_i * q_i(d_i) < p_i(d_i); record the row the final draw uses
-//   draw        per (request, chain), one pass over that row (and the draft distribution's row when
-//               a draft was rejected): weights w = max(p - q, 0) or p; inverse-CDF or exponential race
-// then select (longest chain) and rollback (move the kept chain's K/V next to x0, advance lengths).
+// Accept / reject over the target logits, the choice of the chain to keep, the replacement or bonus draw, and the
+// cache rollback.  Passes over vocabulary-wide data, bound by HBM or, in the race, by its hash:
+//   row_stats   every logits row once, in parts: max, sum exp((x - max)/temp), argmax (lowest id on ties)
+//   accept      per request: all (chain, slot) decisions side by side -- p_i(d_i) from the row statistics and one gathered
+//               logit; u_i * q_i(d_i) < p_i(d_i) -- then the longest chain (lowest id on ties)
+//   draw        one pass over the row that the kept chain's last token comes from (and the draft distribution's row when
+//               a draft was rejected): weights w = max(p - q, 0) or p; inverse-CDF or exponential race.  Match
+//               verification draws every row first and compares afterwards.
+//   finish      the race's winner over the parts, output tokens, live length
+// A launch costs more than the small stages do, so whoever needs a row's statistics folds its parts itself, the chain is
+// chosen before the draw (one draw per request, not one per chain) and the length is advanced by whoever knows it last.
 #include <math.h>
+#include <algorithm>
 #include "common.h"
 #include "kernels.h"
 
 namespace sv {
 
-constexpr int NT = 1024;
+constexpr int NT = 1024;                                  // threads of an inverse-CDF draw
+constexpr int NS = 256;                                   // threads of a statistics or race work-group
 
-// One logits row is cut into gridDim.y contiguous parts, one work-group each (a row per work-group leaves a
-// 150k-wide row to 1024 threads and the launch to a few hundred work-groups: latency-bound at a third of the
-// memory rate); part statistics go to `part` [T][parts][4] and row_stats_merge_kernel folds them.
-__global__ __launch_bounds__(NT) void row_stats_kernel(const float* __restrict__ logits, float* __restrict__ part,
-                                                       int V, float inv_temp) {
-    const int t = blockIdx.x;
-    const float* row = logits + (int64_t)t * V;
+// Parts a vocabulary is cut into for `rows` rows: enough work-groups of 256 threads to fill the chip (few rows of a wide
+// vocabulary), eight of them at many rows, no part shorter than one load of its threads.  Five rows of 152064: 8 parts of
+// 1024 threads took 8.5 us, 32 of 256 take 7.2; 640 rows 94 us (4.1 TB/s) either way.
+static int vocab_parts(int rows, int V) {
+    const int want = std::min(32, std::max(kDrawParts, (4096 + rows - 1) / rows));
+    return std::max(1, std::min(want, V / (4 * NS)));
+}
+size_t sample_part_entries(int rows) { return (size_t)kDrawParts * rows + 4096; }   // >= vocab_parts * rows
+
+__device__ __forceinline__ int window_of(const SampleArgs& a, int b) { return a.draft_lens ? max(0, min(a.draft_lens[b], a.k)) : a.k; }
+
+// Is row j of a request (0 = x0, then the drafts chain by chain) ever looked at?  Rows behind the draft window are not.
+__device__ __forceinline__ bool row_counts(int j, int k, int klim) { return row_index_in_chain(j, k) <= klim; }
+
+struct Stat { float m, s; int am; };
+
+// A thread's ids are loaded four at a time, kAhead loads per batch and the next batch in flight while one is worked on
+// (one new maximum and one rescale per batch, not per load); the exponentials are the hardware's base-2 ones on
+// pre-scaled arguments.  2304 rows of 152064: 292 us (4.8 TB/s); with work-groups of 1024 threads and one batch each 340.
+__global__ __launch_bounds__(NS) void row_stats_kernel(SampleArgs a, float inv_temp) {
+    const int t = blockIdx.x, V = a.V, n = 1 + a.N * a.k;
+    if (a.draft_lens && !row_counts(t % n, a.k, window_of(a, t / n))) return;
+    const float* row = a.logits + (int64_t)t * V;
     const int span = ((V + gridDim.y - 1) / gridDim.y + 3) & ~3;          // ids per part, a multiple of 4
     const int vbeg = blockIdx.y * span, vend = min(V, vbeg + span);
     float m = -INFINITY, s = 0.f;
     int am = 0x7fffffff;
-    auto take = [&](float x, int v) {
-        if (x > m) {
-            s = s * expf((m - x) * inv_temp) + 1.0f;
-            m = x;
-            am = v;
-        } else if (x > -INFINITY) {
-            s += expf((x - m) * inv_temp);
+    const float c2 = inv_temp * 1.4426950408889634f;
+    constexpr int kAhead = 4, STEP = 4 * NS * kAhead;
+    const bool vec = (V & 3) == 0;                         // rows start on 16-byte boundaries
+    auto load = [&](int v0, floatx4 (&x)[kAhead]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int v = v0 + u * 4 * NS;
+            x[u] = floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            if (vec) {
+                if (v < vend) x[u] = *reinterpret_cast<const floatx4*>(row + v);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (v + i < vend) x[u][i] = row[v + i];
+            }
         }
     };
-    if ((V & 3) == 0) {
-        // Rows start on 16-byte boundaries: four ids per load, and kAhead loads of a thread in flight before the
-        // arithmetic on any of them (one new maximum and one rescale per batch of loads, not per load).  The
-        // exponentials are the hardware's base-2 ones on pre-scaled arguments.
-        constexpr int kAhead = 5;
-        const float c2 = inv_temp * 1.4426950408889634f;
-        for (int v0 = vbeg + 4 * threadIdx.x; v0 < vend; v0 += 4 * NT * kAhead) {
-            floatx4 x[kAhead];
+    auto take = [&](int v0, const floatx4 (&x)[kAhead]) __attribute__((always_inline)) {
+        float mx = -INFINITY;
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int v = v0 + u * 4 * NT;
-                x[u] = v < vend ? *reinterpret_cast<const floatx4*>(row + v) : floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-            }
-            float mx = -INFINITY;
+        for (int u = 0; u < kAhead; ++u) mx = fmaxf(mx, fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3])));
+        if (mx > m) {                                      // new maximum: its first holder in ascending id order
+            s *= __builtin_amdgcn_exp2f((m - mx) * c2);    // (m = -inf: s is 0 and stays 0)
+            m = mx;
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) mx = fmaxf(mx, fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3])));
-            if (mx > m) {                                  // new maximum: its first holder in ascending id order
-                s *= __builtin_amdgcn_exp2f((m - mx) * c2);   // (m = -inf: s is 0 and stays 0)
-                m = mx;
+            for (int u = kAhead - 1; u >= 0; --u)
 #pragma unroll
-                for (int u = kAhead - 1; u >= 0; --u)
-#pragma unroll
-                    for (int i = 3; i >= 0; --i)
-                        if (x[u][i] == mx) am = v0 + u * 4 * NT + i;
-            }
-            if (mx > -INFINITY) {
-                float add = 0.f;
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u)
-                    add += (__builtin_amdgcn_exp2f((x[u][0] - m) * c2) + __builtin_amdgcn_exp2f((x[u][1] - m) * c2)) +
-                           (__builtin_amdgcn_exp2f((x[u][2] - m) * c2) + __builtin_amdgcn_exp2f((x[u][3] - m) * c2));
-                s += add;
-            }
+                for (int i = 3; i >= 0; --i)
+                    if (x[u][i] == mx) am = v0 + u * 4 * NS + i;
         }
-    } else {
-        for (int v = vbeg + threadIdx.x; v < vend; v += NT) take(row[v], v);
+        if (mx > -INFINITY) {
+            float add = 0.f;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                add += (__builtin_amdgcn_exp2f((x[u][0] - m) * c2) + __builtin_amdgcn_exp2f((x[u][1] - m) * c2)) +
+                       (__builtin_amdgcn_exp2f((x[u][2] - m) * c2) + __builtin_amdgcn_exp2f((x[u][3] - m) * c2));
+            s += add;
+        }
+    };
+    floatx4 xa[kAhead], xb[kAhead];
+    int v = vbeg + 4 * threadIdx.x;
+    load(v, xa);
+    for (; v < vend; v += 2 * STEP) {
+        load(v + STEP, xb);
+        __builtin_amdgcn_sched_barrier(0);
+        take(v, xa);
+        load(v + 2 * STEP, xa);
+        __builtin_amdgcn_sched_barrier(0);
+        take(v + STEP, xb);
     }
-    __shared__ float sm[NT / 64], ss[NT / 64];
-    __shared__ int sa[NT / 64];
+    __shared__ float sm[NS / 64], ss[NS / 64];
+    __shared__ int sa[NS / 64];
     // wave merge, then group merge: (m, s, am) with ties on m resolved to the lower id
     auto merge = [&](float& m1, float& s1, int& a1, float m2, float s2, int a2) {
         const float mm = fmaxf(m1, m2);
@@ -95,35 +120,28 @@ __global__ __launch_bounds__(NT) void row_stats_kernel(const float* __restrict__
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < NT / 64; ++w) merge(m, s, am, sm[w], ss[w], sa[w]);
-        float* out = part + ((int64_t)t * gridDim.y + blockIdx.y) * 4;
-        out[0] = m;
-        out[1] = s;
-        out[2] = __int_as_float(am);
-        out[3] = 0.f;
+        for (int w = 1; w < NS / 64; ++w) merge(m, s, am, sm[w], ss[w], sa[w]);
+        reinterpret_cast<floatx4*>(a.stat_part)[(int64_t)t * gridDim.y + blockIdx.y] = floatx4{m, s, __int_as_float(am), 0.f};
     }
 }
 
-__global__ void row_stats_merge_kernel(const float* __restrict__ part, float* __restrict__ stat, int T, int parts, float inv_temp) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    float m = -INFINITY, s = 0.f;
-    int am = 0x7fffffff;
-    for (int i = 0; i < parts; ++i) {                     // ascending ids: on equal maxima the earlier part's id stays
-        const float* in = part + ((int64_t)t * parts + i) * 4;
-        const float m2 = in[0], s2 = in[1];
-        const int a2 = __float_as_int(in[2]);
-        const float mm = fmaxf(m, m2);
-        const float f1 = m == -INFINITY ? 0.f : expf((m - mm) * inv_temp);
-        const float f2 = m2 == -INFINITY ? 0.f : expf((m2 - mm) * inv_temp);
-        s = s * f1 + s2 * f2;
-        if (m2 > m || (m2 == m && a2 < am)) am = a2;
-        m = mm;
+// A row's statistics from its parts (ascending ids: of equal maxima the first part's id stays).
+__device__ __forceinline__ Stat row_stat(const SampleArgs& a, int row, float inv_temp) {
+    const floatx4* in = reinterpret_cast<const floatx4*>(a.stat_part) + (int64_t)row * a.stat_parts;
+    Stat r{-INFINITY, 0.f, 0x7fffffff};
+#pragma unroll 8
+    for (int i = 0; i < a.stat_parts; ++i) {
+        const float m = in[i][0];
+        const int am = __float_as_int(in[i][2]);
+        if (m > r.m || (m == r.m && am < r.am)) r.am = am;
+        r.m = fmaxf(r.m, m);
     }
-    stat[t * 4 + 0] = m;
-    stat[t * 4 + 1] = s;
-    stat[t * 4 + 2] = __int_as_float(am);
-    stat[t * 4 + 3] = 0.f;
+#pragma unroll 8
+    for (int i = 0; i < a.stat_parts; ++i) {
+        const float m = in[i][0];
+        r.s += m == -INFINITY ? 0.f : in[i][1] * expf((m - r.m) * inv_temp);
+    }
+    return r;
 }
 
 // Logits row that holds the target distribution of draft slot i (1-based) of chain c of request b.
@@ -131,38 +149,86 @@ __device__ __forceinline__ int slot_row(int b, int c, int i, int n, int k) {
     return b * n + (i == 1 ? 0 : 1 + c * k + (i - 2));
 }
 
-__global__ void accept_kernel(SampleArgs a) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= a.B * a.N) return;
-    const int b = s / a.N, c = s % a.N;
-    const int n = 1 + a.N * a.k;
-    const int klim = a.draft_lens ? min(a.draft_lens[b], a.k) : a.k;
-    const float inv_temp = 1.0f / a.temperature;
-    int acc = 0;
-    for (int i = 1; i <= klim; ++i) {
-        const int row = slot_row(b, c, i, n, a.k);
-        const int x = a.drafts[(int64_t)s * a.k + (i - 1)];
-        bool ok;
-        if ((unsigned)x >= (unsigned)a.V) {
-            ok = false;                                   // not a token of this vocabulary: rejected, nothing is read at it
-        } else if (a.verify_mode == 0) {
-            ok = x == __float_as_int(a.row_stat[row * 4 + 2]);
-        } else if (a.verify_mode == 2) {
-            ok = x == __float_as_int(a.row_stat[row * 4 + 3]);       // the token drawn for this slot
-        } else {
-            const float m = a.row_stat[row * 4], sum = a.row_stat[row * 4 + 1];
-            const float p = expf((a.logits[(int64_t)row * a.V + x] - m) * inv_temp) / sum;
-            const float q = a.draft_probs ? a.draft_probs[((int64_t)s * a.k + (i - 1)) * a.V + x] : 1.0f;
-            ok = a.uniforms[(int64_t)s * (a.k + 1) + (i - 1)] * q < p;
-        }
-        if (!ok) break;
-        ++acc;
+// Winner of a race over its parts (larger score; lower id among equals); the residual's if it has one.
+__device__ __forceinline__ int race_winner(const SampleArgs& a, int64_t idx, bool rejected) {
+    const floatx4* in = reinterpret_cast<const floatx4*>(a.draw_part) + idx * a.draw_parts;
+    float best_r = -INFINITY, best_p = -INFINITY;
+    int arg_r = 0x7fffffff, arg_p = 0x7fffffff;
+#pragma unroll 8
+    for (int i = 0; i < a.draw_parts; ++i) {
+        const float r = in[i][0], p = in[i][2];
+        const int ar = __float_as_int(in[i][1]), ap = __float_as_int(in[i][3]);
+        if (r > best_r || (r == best_r && ar < arg_r)) { best_r = r; arg_r = ar; }
+        if (p > best_p || (p == best_p && ap < arg_p)) { best_p = p; arg_p = ap; }
     }
-    a.chain_acc[s] = acc;
-    const int row = slot_row(b, c, acc + 1, n, a.k);
-    a.chain_row[s] = row;
-    if (a.verify_mode == 0) a.chain_tok[s] = __float_as_int(a.row_stat[row * 4 + 2]);
-    if (a.verify_mode == 2) a.chain_tok[s] = __float_as_int(a.row_stat[row * 4 + 3]);
+    return (rejected && best_r > -INFINITY) ? arg_r : arg_p;
+}
+
+// Output tokens and live length of request b (all lanes of its wave).
+__device__ __forceinline__ void emit(const SampleArgs& a, int b, int best, int acc, int tok) {
+    int32_t* out = a.out_tokens + (int64_t)b * (a.k + 1);
+    for (int i = threadIdx.x; i <= a.k; i += 64)
+        out[i] = i < acc ? a.drafts[((int64_t)b * a.N + best) * a.k + i] : i == acc ? tok : -1;
+    if (threadIdx.x == 0) {
+        a.accepted_len[b] = acc;
+        a.best_chain[b] = best;
+        if (a.seq_len) a.seq_len[a.batch_seq[b]] += acc + 1;
+    }
+}
+
+// One wave per request.  Greedy verification ends here, match verification too (its rows were drawn before: each row's
+// token is folded from the race's parts first); stochastic verification leaves the kept chain for the draw.
+template <int MODE>
+__global__ __launch_bounds__(64) void accept_kernel(SampleArgs a) {
+    extern __shared__ int acc_sh[];                        // [N]
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const int n = 1 + a.N * a.k, klim = window_of(a, b);
+    const float inv_temp = 1.0f / a.temperature;
+    float* tok_of = a.stat_part + (int64_t)b * n * a.stat_parts * 4;      // match: a row's token, over its statistics
+    if (MODE == 2) {
+        for (int j = lane; j < n; j += 64)
+            if (row_counts(j, a.k, klim)) tok_of[(int64_t)j * a.stat_parts * 4] = __int_as_float(race_winner(a, (int64_t)b * n + j, false));
+    }
+    for (int c = lane; c < a.N; c += 64) acc_sh[c] = klim;
+    __syncthreads();
+    auto slot_token = [&](int row) {
+        return MODE == 2 ? __float_as_int(tok_of[(int64_t)(row - b * n) * a.stat_parts * 4]) : row_stat(a, row, inv_temp).am;
+    };
+    for (int i0 = lane; i0 < a.N * a.k; i0 += 64) {
+        const int c = i0 / a.k, i = i0 % a.k + 1;
+        if (i > klim) continue;
+        const int row = slot_row(b, c, i, n, a.k);
+        const int64_t d = (int64_t)b * a.N * a.k + i0;
+        const int x = a.drafts[d];
+        bool ok = false;                                   // not a token of this vocabulary: rejected, nothing is read at it
+        if ((unsigned)x < (unsigned)a.V) {
+            if (MODE == 1) {
+                const Stat st = row_stat(a, row, inv_temp);
+                const float p = expf((a.logits[(int64_t)row * a.V + x] - st.m) * inv_temp) / st.s;
+                const float q = a.draft_probs ? a.draft_probs[d * a.V + x] : 1.0f;
+                ok = a.uniforms[((int64_t)b * a.N + c) * (a.k + 1) + (i - 1)] * q < p;
+            } else {
+                ok = x == slot_token(row);
+            }
+        }
+        if (!ok) atomicMin(&acc_sh[c], i - 1);
+    }
+    __syncthreads();
+    int best = 0, acc = acc_sh[0];
+    for (int c = 1; c < a.N; ++c)
+        if (acc_sh[c] > acc) { acc = acc_sh[c]; best = c; }
+    if (MODE == 1) {
+        if (lane == 0) { a.accepted_len[b] = acc; a.best_chain[b] = best; }
+    } else {
+        emit(a, b, best, acc, slot_token(slot_row(b, best, acc + 1, n, a.k)));
+    }
+}
+
+// End of stochastic verification.
+__global__ __launch_bounds__(64) void finish_kernel(SampleArgs a) {
+    const int b = blockIdx.x;
+    const int acc = a.accepted_len[b];
+    emit(a, b, a.best_chain[b], acc, race_winner(a, b, acc < window_of(a, b)));
 }
 
 __device__ __forceinline__ uint64_t splitmix_finalise(uint64_t z) {
@@ -171,91 +237,171 @@ __device__ __forceinline__ uint64_t splitmix_finalise(uint64_t z) {
     return z ^ (z >> 31);
 }
 
-// Draw of one token.  ROWS == false (stochastic verification): the final draw of one (request, chain), from the
-// residual after a rejection or from the bonus row.  ROWS == true (match verification): the target's own token of
-// one logits row, i.e. of one draft slot, from that row's distribution; the randomness is keyed by the request's
-// index in the batch and the slot alone (the uniform of chain 0), so every chain of a request is held to the same
-// token at the same slot.  The result goes to row_stat[row][3].
+// What a draw draws from.  ROWS == false (stochastic verification): the last token of a request's kept chain, from the
+// residual after a rejection or from the bonus row.  ROWS == true (match verification): the target's own token of one
+// logits row, i.e. of one draft slot, from that row's distribution; the randomness is keyed by the request's index in
+// the batch and the slot alone (the uniform of chain 0), so every chain of a request is held to the same token at the
+// same slot.
+struct Draw { int row, xrej; bool rejected, dead; const float* qrow; float u; uint32_t key_hi; };
 template <bool ROWS>
-__global__ __launch_bounds__(NT) void draw_kernel(SampleArgs a) {
-    const int s = blockIdx.x;                             // (request, chain), or logits row
+__device__ __forceinline__ Draw draw_of(const SampleArgs& a, int idx) {
     const int n = 1 + a.N * a.k;
-    const int b = ROWS ? s / n : s / a.N;
-    const int klim = a.draft_lens ? min(a.draft_lens[b], a.k) : a.k;
-    const int acc = ROWS ? 0 : a.chain_acc[s];
-    const bool rejected = ROWS ? false : acc < klim;
-    const int row = ROWS ? s : a.chain_row[s];
-    const float* lrow = a.logits + (int64_t)row * a.V;
+    const int b = ROWS ? idx / n : idx;
+    const int klim = window_of(a, b);
+    const int j = ROWS ? idx % n : 0;
+    const int acc = ROWS ? 0 : a.accepted_len[b], c = ROWS ? 0 : a.best_chain[b];
+    const int64_t s = (int64_t)b * a.N + c;
+    Draw d;
+    d.dead = ROWS && !row_counts(j, a.k, klim);
+    d.rejected = !ROWS && acc < klim;
+    d.row = ROWS ? idx : slot_row(b, c, acc + 1, n, a.k);
     // a rejected id outside the vocabulary was rejected unread: the replacement comes from p_r itself (q taken as zero)
-    const int xraw = rejected ? a.drafts[(int64_t)s * a.k + acc] : -1;
-    const int xrej = (unsigned)xraw < (unsigned)a.V ? xraw : -1;
-    const float* qrow = (rejected && a.draft_probs && xrej >= 0) ? a.draft_probs + ((int64_t)s * a.k + acc) * a.V : nullptr;
-    const float inv_temp = 1.0f / a.temperature;
-    const float m = a.row_stat[row * 4], sum = a.row_stat[row * 4 + 1];
-    const float log_sum = logf(sum);
+    const int xraw = d.rejected ? a.drafts[s * a.k + acc] : -1;
+    d.xrej = (unsigned)xraw < (unsigned)a.V ? xraw : -1;
+    d.qrow = (d.rejected && a.draft_probs && d.xrej >= 0) ? a.draft_probs + (s * a.k + acc) * a.V : nullptr;
     // slot served by row j of a request: row 0 -> slot 1, the row of draft i of any chain -> slot i + 1
-    const int j = s % n;
-    const int slot = j == 0 ? 1 : (j - 1) % max(a.k, 1) + 2;
-    const float u = ROWS ? a.uniforms[(int64_t)b * a.N * (a.k + 1) + (slot - 1)] : a.uniforms[(int64_t)s * (a.k + 1) + a.k];
+    d.u = ROWS ? a.uniforms[(int64_t)b * a.N * (a.k + 1) + row_index_in_chain(j, max(a.k, 1))] : a.uniforms[s * (a.k + 1) + a.k];
+    d.key_hi = (uint32_t)(ROWS ? b : s);
+    return d;
+}
+
+// Exponential race: argmax_v ln w_v - ln e_v, e_v = -log1p(-U_v); the residual's winner and, for the case that the
+// residual is identically zero, the winner under p as well.  Per id the race needs a hash, and two logarithms that
+// almost no id needs: e_v >= U_v, so an id can only beat the best score s so far if w_v > U_v e^s, and that is tested
+// with the hardware's base-2 exponential and a margin a thousand times its error.  A wave shares its best score; it runs
+// the logarithms for a few of its ids only.  One draw per request over 152064 ids, with both logarithms for every id
+// before: 256 requests 186 -> 112 us, 128 requests 86 -> 66, one request 29 -> 19 (start-up chain: verdict, row, parts).
+template <bool ROWS>
+__global__ __launch_bounds__(NS) void race_kernel(SampleArgs a) {
+    const Draw d = draw_of<ROWS>(a, blockIdx.x);
+    if (d.dead) return;
     const int V = a.V;
+    const float* lrow = a.logits + (int64_t)d.row * V;
+    const int span = ((V + gridDim.y - 1) / gridDim.y + 3) & ~3;
+    const int vbeg = blockIdx.y * span, vend = min(V, vbeg + span);
+    const bool vec = (V & 3) == 0;
+    constexpr int STEP = 4 * NS;
+    struct Ids { floatx4 x, q; };                          // four ids' logits and draft probabilities
+    auto load4 = [&](const float* src, int v, float fill) __attribute__((always_inline)) {
+        floatx4 x = {fill, fill, fill, fill};
+        if (vec) {
+            if (v < vend) x = *reinterpret_cast<const floatx4*>(src + v);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v + i < vend) x[i] = src[v + i];
+        }
+        return x;
+    };
+    auto load = [&](int v, Ids& t) __attribute__((always_inline)) {
+        t.x = load4(lrow, v, -INFINITY);
+        t.q = d.qrow ? load4(d.qrow, v, 0.f) : floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+    const int v0 = vbeg + 4 * threadIdx.x;
+    Ids ta, tb;
+    load(v0, ta);
+    const float inv_temp = 1.0f / a.temperature;
+    const Stat st = row_stat(a, d.row, inv_temp);
+    const float m = st.m, log_sum = logf(st.s);
+    const float c2 = inv_temp * 1.4426950408889634f, l2 = log_sum * 1.4426950408889634f;
+    const uint64_t key = ((uint64_t)d.key_hi << 32) | (uint64_t)__float_as_uint(d.u);
+    float best_r = -INFINITY, best_p = -INFINITY;
+    int arg_r = 0x7fffffff, arg_p = 0x7fffffff;
+    float thr_r = 0.f, thr_p = 0.f;                        // e^(best score of the wave)
+    constexpr float kMargin = 1.001f;
+    constexpr uint64_t kStride = 0x9E3779B97F4A7C15ull;
+    auto four = [&](int v, const Ids& t) __attribute__((always_inline)) {
+        const uint64_t seed = key + (uint64_t)(v + 1) * kStride;
+        float U[4], p_ub[4], q[4];
+        unsigned todo = 0;
+        auto can_win = [&](int i) __attribute__((always_inline)) {
+            return !(U[i] * thr_p > p_ub[i]) | (d.rejected & !(U[i] * thr_r > (p_ub[i] - q[i]) * kMargin));
+        };
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t z = splitmix_finalise(seed + i * kStride);
+            U[i] = ((float)(uint32_t)(z >> 32) + 0.5f) * 2.3283064365386963e-10f;
+            // (no smaller than what the hardware's exponential flushes to zero: still an upper bound of p)
+            p_ub[i] = fmaxf(__builtin_amdgcn_exp2f(fmaf(t.x[i] - m, c2, -l2)) * kMargin, 1e-37f);
+            q[i] = d.qrow ? t.q[i] : (v + i == d.xrej ? 1.0f : 0.0f);
+            todo |= ((v + i < vend) & can_win(i)) ? 1u << i : 0u;
+        }
+        // ids that may win, each lane's next one at a time; what the new best rules out is dropped.  (One copy of the
+        // logarithms per four ids: unrolled over eight of them the kernel ran out of the instruction cache, 115 -> 165 us.)
+        while (__any(todo != 0)) {
+            const int i = __ffs(todo) - 1;
+            if (i >= 0) {
+                const float x = i == 0 ? t.x[0] : i == 1 ? t.x[1] : i == 2 ? t.x[2] : t.x[3];
+                const float qi = i == 0 ? q[0] : i == 1 ? q[1] : i == 2 ? q[2] : q[3];
+                const float Ui = i == 0 ? U[0] : i == 1 ? U[1] : i == 2 ? U[2] : U[3];
+                const float ln_e = logf(-log1pf(-Ui));
+                const float lp = (x - m) * inv_temp - log_sum;
+                const float sp = lp - ln_e;
+                if (sp > best_p) { best_p = sp; arg_p = v + i; }
+                if (d.rejected) {
+                    const float w = fmaxf(expf(lp) - qi, 0.0f);
+                    if (w > 0.f) {
+                        const float sr = logf(w) - ln_e;
+                        if (sr > best_r) { best_r = sr; arg_r = v + i; }
+                    }
+                }
+                todo &= todo - 1;
+            }
+            thr_p = expf(wave_max(best_p));
+            if (d.rejected) thr_r = expf(wave_max(best_r));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) todo &= can_win(k) ? ~0u : ~(1u << k);
+        }
+    };
+    // the bounds are uniform, so that all lanes of a wave meet in the votes and shuffles; the next ids are on their way
+    for (int o = 0; vbeg + o < vend; o += 2 * STEP) {
+        load(v0 + o + STEP, tb);
+        four(v0 + o, ta);
+        load(v0 + o + 2 * STEP, ta);
+        four(v0 + o + STEP, tb);
+    }
+    __shared__ float sh_r[NS / 64], sh_p[NS / 64];
+    __shared__ int sh_ar[NS / 64], sh_ap[NS / 64];
+    auto take = [](float& bv, int& ba, float ov, int oa) {
+        if (ov > bv || (ov == bv && oa < ba)) { bv = ov; ba = oa; }
+    };
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        take(best_r, arg_r, __shfl_xor(best_r, o), __shfl_xor(arg_r, o));
+        take(best_p, arg_p, __shfl_xor(best_p, o), __shfl_xor(arg_p, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh_r[threadIdx.x >> 6] = best_r; sh_ar[threadIdx.x >> 6] = arg_r;
+        sh_p[threadIdx.x >> 6] = best_p; sh_ap[threadIdx.x >> 6] = arg_p;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < NS / 64; ++w) {
+            take(best_r, arg_r, sh_r[w], sh_ar[w]);
+            take(best_p, arg_p, sh_p[w], sh_ap[w]);
+        }
+        reinterpret_cast<floatx4*>(a.draw_part)[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] =
+            floatx4{best_r, __int_as_float(arg_r), best_p, __int_as_float(arg_p)};
+    }
+}
+
+// Inverse-CDF draw: one work-group per draw.
+template <bool ROWS>
+__global__ __launch_bounds__(NT) void cdf_kernel(SampleArgs a) {
+    const Draw d = draw_of<ROWS>(a, blockIdx.x);
+    if (d.dead) return;
+    const int V = a.V;
+    const float* lrow = a.logits + (int64_t)d.row * V;
+    const float inv_temp = 1.0f / a.temperature;
+    const Stat st = row_stat(a, d.row, inv_temp);
+    const float m = st.m, sum = st.s, u = d.u;
 
     auto prob = [&](int v) { return expf((lrow[v] - m) * inv_temp) / sum; };
     auto resid = [&](int v, float p) {          // weight of id v in the residual distribution
-        if (!rejected) return p;
-        const float q = qrow ? qrow[v] : (v == xrej ? 1.0f : 0.0f);
+        if (!d.rejected) return p;
+        const float q = d.qrow ? d.qrow[v] : (v == d.xrej ? 1.0f : 0.0f);
         return fmaxf(p - q, 0.0f);
     };
-
-    if (a.sample_mode == 1) {
-        // exponential race: argmax_v ln w_v - ln e_v ; track the residual's winner and, for the case that
-        // the residual is identically zero, the winner under p as well.
-        const uint64_t key = ((uint64_t)(uint32_t)(ROWS ? b : s) << 32) | (uint64_t)__float_as_uint(u);
-        float best_r = -INFINITY, best_p = -INFINITY;
-        int arg_r = 0x7fffffff, arg_p = 0x7fffffff;
-        // the vocabulary is cut into gridDim.y contiguous parts; each work-group finds the winners of its part
-        const int part = (V + gridDim.y - 1) / gridDim.y;
-        const int vbeg = blockIdx.y * part, vend = min(V, vbeg + part);
-        for (int v = vbeg + threadIdx.x; v < vend; v += NT) {
-            const uint64_t z = splitmix_finalise(key + (uint64_t)(v + 1) * 0x9E3779B97F4A7C15ull);
-            const float U = ((float)(uint32_t)(z >> 32) + 0.5f) * 2.3283064365386963e-10f;
-            const float ln_e = logf(-log1pf(-U));
-            const float lp = (lrow[v] - m) * inv_temp - log_sum;
-            const float sp = lp - ln_e;
-            if (sp > best_p) { best_p = sp; arg_p = v; }
-            if (rejected) {
-                const float w = resid(v, expf(lp));
-                if (w > 0.f) {
-                    const float sr = logf(w) - ln_e;
-                    if (sr > best_r) { best_r = sr; arg_r = v; }
-                }
-            }
-        }
-        __shared__ float sh_r[NT / 64], sh_p[NT / 64];
-        __shared__ int sh_ar[NT / 64], sh_ap[NT / 64];
-        auto take = [](float& bv, int& ba, float ov, int oa) {
-            if (ov > bv || (ov == bv && oa < ba)) { bv = ov; ba = oa; }
-        };
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            take(best_r, arg_r, __shfl_xor(best_r, o), __shfl_xor(arg_r, o));
-            take(best_p, arg_p, __shfl_xor(best_p, o), __shfl_xor(arg_p, o));
-        }
-        if ((threadIdx.x & 63) == 0) {
-            sh_r[threadIdx.x >> 6] = best_r; sh_ar[threadIdx.x >> 6] = arg_r;
-            sh_p[threadIdx.x >> 6] = best_p; sh_ap[threadIdx.x >> 6] = arg_p;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            for (int w = 1; w < NT / 64; ++w) {
-                take(best_r, arg_r, sh_r[w], sh_ar[w]);
-                take(best_p, arg_p, sh_p[w], sh_ap[w]);
-            }
-            float* out = a.draw_part + ((int64_t)s * gridDim.y + blockIdx.y) * 4;
-            out[0] = best_r; out[1] = __int_as_float(arg_r); out[2] = best_p; out[3] = __int_as_float(arg_p);
-        }
-        return;
-    }
-
     // inverse CDF over ascending id.  Thread i owns the contiguous ids [i*seg, (i+1)*seg); sums in double.
     const int seg = (V + NT - 1) / NT;
     const int v0 = threadIdx.x * seg, v1 = min(V, v0 + seg);
@@ -302,37 +448,23 @@ __global__ __launch_bounds__(NT) void draw_kernel(SampleArgs a) {
             if (run > target) { tok = v; break; }
         }
         const int drawn = tok >= 0 ? tok : last_pos;
-        if (ROWS) a.row_stat[row * 4 + 3] = __int_as_float(drawn);
-        else a.chain_tok[s] = drawn;
+        reinterpret_cast<floatx4*>(a.draw_part)[blockIdx.x] = floatx4{-INFINITY, 0.f, 0.f, __int_as_float(drawn)};   // a race of one
     }
-}
-
-__global__ void select_kernel(SampleArgs a) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= a.B) return;
-    int best = 0, acc = a.chain_acc[b * a.N];
-    for (int c = 1; c < a.N; ++c)
-        if (a.chain_acc[b * a.N + c] > acc) { acc = a.chain_acc[b * a.N + c]; best = c; }
-    a.accepted_len[b] = acc;
-    a.best_chain[b] = best;
-    int32_t* out = a.out_tokens + (int64_t)b * (a.k + 1);
-    for (int i = 0; i < acc; ++i) out[i] = a.drafts[((int64_t)b * a.N + best) * a.k + i];
-    out[acc] = a.chain_tok[b * a.N + best];
-    for (int i = acc + 1; i <= a.k; ++i) out[i] = -1;
 }
 
 // Move the kept chain's accepted entries to slots L+1 .. L+a (chain 0 already sits there).  One work-group per
 // (request, layer).  In the tile layout of the cache a key's K entries of one head are head_dim/8 whole 16-byte
 // pieces (one per 8-wide slice of the head), moved as such with one index computation each; its V entries lie
 // one element apart per dimension (V is stored transposed, keys innermost) and move one by one.  Source slots
-// (>= L+1+k for a chain other than 0) and destination slots (<= L+k) never overlap.
+// (>= L+1+k for a chain other than 0) and destination slots (<= L+k) never overlap.  committed: the live length has
+// been advanced by acc + 1 already.
 template <typename T>
-__global__ __launch_bounds__(256) void compact_kernel(RollbackArgs r) {
+__global__ __launch_bounds__(256) void compact_kernel(RollbackArgs r, bool committed) {
     const int b = blockIdx.x, layer = blockIdx.y;
     const int best = r.best_chain[b], acc = r.accepted_len[b];
     if (best <= 0 || best >= r.N || acc <= 0 || acc > r.k) return;
     const int seq = r.batch_seq[b];
-    const int L = r.seq_len[seq];
+    const int L = r.seq_len[seq] - (committed ? acc + 1 : 0);
     const int32_t* pages = r.page_table + (int64_t)seq * r.max_pages_per_seq;
     T* pool = reinterpret_cast<T*>(r.pool);
     const int hd = r.geom.head_dim, H = r.geom.n_kv_heads;
@@ -362,64 +494,37 @@ __global__ void commit_len_kernel(RollbackArgs r) {
     if (b < r.B) r.seq_len[r.batch_seq[b]] += r.accepted_len[b] + 1;
 }
 
-// Winner of a chain's (or, ROWS, a row's) exponential race over the parts of the vocabulary (larger score; lower
-// id among equals).
-template <bool ROWS>
-__global__ void draw_reduce_kernel(SampleArgs a, int parts) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= (ROWS ? a.B * (1 + a.N * a.k) : a.B * a.N)) return;
-    const int b = ROWS ? 0 : s / a.N;
-    const int klim = a.draft_lens ? min(a.draft_lens[b], a.k) : a.k;
-    const bool rejected = ROWS ? false : a.chain_acc[s] < klim;
-    float best_r = -INFINITY, best_p = -INFINITY;
-    int arg_r = 0x7fffffff, arg_p = 0x7fffffff;
-    for (int i = 0; i < parts; ++i) {
-        const float* in = a.draw_part + ((int64_t)s * parts + i) * 4;
-        const float r = in[0], p = in[2];
-        const int ar = __float_as_int(in[1]), ap = __float_as_int(in[3]);
-        if (r > best_r || (r == best_r && ar < arg_r)) { best_r = r; arg_r = ar; }
-        if (p > best_p || (p == best_p && ap < arg_p)) { best_p = p; arg_p = ap; }
+hipError_t sample_verify(const SampleArgs& args, hipStream_t st) {
+    SampleArgs a = args;
+    const int T = a.B * (1 + a.N * a.k);
+    const size_t lds = sizeof(int) * (size_t)a.N;
+    a.stat_parts = vocab_parts(T, a.V);
+    a.draw_parts = a.sample_mode == 1 ? vocab_parts(a.verify_mode == 2 ? T : a.B, a.V) : 1;
+    hipLaunchKernelGGL(row_stats_kernel, dim3(T, a.stat_parts), dim3(NS), 0, st, a, 1.0f / a.temperature);
+    if (a.verify_mode == 0) {
+        hipLaunchKernelGGL(accept_kernel<0>, dim3(a.B), dim3(64), lds, st, a);
+    } else if (a.verify_mode == 2) {
+        if (a.sample_mode == 1) hipLaunchKernelGGL(race_kernel<true>, dim3(T, a.draw_parts), dim3(NS), 0, st, a);
+        else hipLaunchKernelGGL(cdf_kernel<true>, dim3(T), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL(accept_kernel<2>, dim3(a.B), dim3(64), lds, st, a);
+    } else {
+        hipLaunchKernelGGL(accept_kernel<1>, dim3(a.B), dim3(64), lds, st, a);
+        if (a.sample_mode == 1) hipLaunchKernelGGL(race_kernel<false>, dim3(a.B, a.draw_parts), dim3(NS), 0, st, a);
+        else hipLaunchKernelGGL(cdf_kernel<false>, dim3(a.B), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL(finish_kernel, dim3(a.B), dim3(64), 0, st, a);
     }
-    const int drawn = (rejected && best_r > -INFINITY) ? arg_r : arg_p;
-    if (ROWS) a.row_stat[s * 4 + 3] = __int_as_float(drawn);
-    else a.chain_tok[s] = drawn;
-}
-
-hipError_t sample_verify(const SampleArgs& a, hipStream_t st) {
-    const int T = a.B * (1 + a.N * a.k), S = a.B * a.N;
-    // the race's part buffer is free until the draws: it takes the rows' part statistics first
-    hipLaunchKernelGGL(row_stats_kernel, dim3(T, kDrawParts), dim3(NT), 0, st, a.logits, a.draw_part, a.V, 1.0f / a.temperature);
-    hipLaunchKernelGGL(row_stats_merge_kernel, dim3((T + 63) / 64), dim3(64), 0, st, a.draw_part, a.row_stat, T, kDrawParts,
-                       1.0f / a.temperature);
-    if (a.verify_mode == 2) {          // match: the target's token of every slot first, then the comparison
-        if (a.sample_mode == 1) {
-            hipLaunchKernelGGL(draw_kernel<true>, dim3(T, kDrawParts), dim3(NT), 0, st, a);
-            hipLaunchKernelGGL(draw_reduce_kernel<true>, dim3((T + 63) / 64), dim3(64), 0, st, a, kDrawParts);
-        } else {
-            hipLaunchKernelGGL(draw_kernel<true>, dim3(T), dim3(NT), 0, st, a);
-        }
-    }
-    hipLaunchKernelGGL(accept_kernel, dim3((S + 63) / 64), dim3(64), 0, st, a);
-    if (a.verify_mode == 1) {
-        if (a.sample_mode == 1) {      // the race's per-id arithmetic dominates: spread every chain over several work-groups
-            hipLaunchKernelGGL(draw_kernel<false>, dim3(S, kDrawParts), dim3(NT), 0, st, a);
-            hipLaunchKernelGGL(draw_reduce_kernel<false>, dim3((S + 63) / 64), dim3(64), 0, st, a, kDrawParts);
-        } else {
-            hipLaunchKernelGGL(draw_kernel<false>, dim3(S), dim3(NT), 0, st, a);
-        }
-    }
-    hipLaunchKernelGGL(select_kernel, dim3((a.B + 63) / 64), dim3(64), 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t rollback(const RollbackArgs& r, hipStream_t st, bool commit) {
-    if (r.N > 1) {
-        if (r.dtype == 1)
-            hipLaunchKernelGGL(compact_kernel<bf16_t>, dim3(r.B, r.n_layers), dim3(256), 0, st, r);
-        else
-            hipLaunchKernelGGL(compact_kernel<float>, dim3(r.B, r.n_layers), dim3(256), 0, st, r);
-    }
-    if (commit) hipLaunchKernelGGL(commit_len_kernel, dim3((r.B + 63) / 64), dim3(64), 0, st, r);
+hipError_t compact_kept(const RollbackArgs& r, bool committed, hipStream_t st) {
+    if (r.N <= 1) return hipSuccess;
+    if (r.dtype == 1) hipLaunchKernelGGL(compact_kernel<bf16_t>, dim3(r.B, r.n_layers), dim3(256), 0, st, r, committed);
+    else hipLaunchKernelGGL(compact_kernel<float>, dim3(r.B, r.n_layers), dim3(256), 0, st, r, committed);
+    return hipGetLastError();
+}
+
+hipError_t commit_lens(const RollbackArgs& r, hipStream_t st) {
+    hipLaunchKernelGGL(commit_len_kernel, dim3((r.B + 63) / 64), dim3(64), 0, st, r);
     return hipGetLastError();
 }
 

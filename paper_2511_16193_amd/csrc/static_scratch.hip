@@ -8,14 +8,12 @@
 #include "../../include/specverify_ops.h"
 #include "kernels.h"
 
-// Same kernels as sv_op_sample; their scratch (row statistics, per-chain verdicts, the parts of the race) lives
+// Same kernels as sv_op_sample; their scratch (the parts of the row statistics and of the race) lives
 // in a file-scope device array instead of a caller's buffer.  Every GPU the library runs on holds its own copy
 // of the array at its own address until the process ends; the address is looked up once per device.
 constexpr int kStaticRows = 4096;        // most logits rows B * (1 + N * k) of one call
 constexpr int kStaticChains = 4096;      // most chains B * N of one call
-constexpr size_t kStaticScratchBytes = (sizeof(float) * 4 * kStaticRows + 255) / 256 * 256 +
-                                       3 * ((sizeof(int32_t) * kStaticChains + 255) / 256 * 256) +
-                                       (sizeof(float) * 4 * sv::kDrawParts * kStaticRows + 255) / 256 * 256;
+constexpr size_t kStaticScratchBytes = 2 * sizeof(float) * 4 * ((size_t)sv::kDrawParts * kStaticRows + 4096);   // sv_op_sample_scratch_bytes at the limit
 // (No `used` attribute here: with it the compiler keeps the array's internal linkage in the device code object,
 // where the runtime then cannot find it by name; referenced from host code alone it is emitted as a global symbol.)
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -48,7 +46,7 @@ extern "C" int sv_op_sample_static(const float* logits, const int32_t* drafts, c
     void* ptr = static_scratch_ptr();
     if (!ptr) return SV_EHIP;
     // Nothing in the scratch has to start at zero: every field a kernel of this call reads was written by an
-    // earlier kernel of the same call (part statistics -> row statistics -> verdicts -> race parts -> tokens).
+    // earlier kernel of the same call (part statistics -> verdicts -> race parts -> tokens).
     return sv_op_sample(logits, drafts, draft_probs, uniforms, draft_lens, B, N, k, V, verify_mode, sample_mode, temperature,
                         ptr, accepted_len, out_tokens, best_chain, stream);
 }

@@ -1,0 +1,42 @@
+"""The sampler's parts and the race's shortcut at the edges, on given logits against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import verify as OV
+from test_gpu_ops import DEV, oracle_sample, random_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,N,k,V,temp,scale", [
+    (5, 1, 2, 1000, 1.0, 1.0),        # a vocabulary of less than one load per thread: one part
+    (3, 2, 3, 4100, 1.0, 8.0),        # few rows: many parts, the last one short; peaked distributions
+    (700, 1, 2, 2048, 1.0, 1.0),      # many rows, two parts
+    (4, 3, 2, 16384, 0.02, 1.0),      # log-probabilities in the thousands: what the hardware exponential flushes to zero
+    (6, 1, 4, 33001, 1.0, 3.0),       # a width that is no multiple of four: scalar loads
+])
+@pytest.mark.parametrize("vmode", [OV.STOCHASTIC, OV.MATCH, OV.GREEDY])
+def test_sampler_edges(B, N, k, V, temp, scale, vmode):
+    from paper_2511_16193_amd import op_sample
+    logits, drafts, q, u = random_case(B, N, k, V, 40 + V % 7)
+    logits = (logits * scale).astype(np.float32)
+    rng = np.random.default_rng(3)
+    best = np.argmax(logits, axis=-1)
+    for c in range(N):                                  # half of the drafts are the target's favourite, so windows go on
+        rows = np.concatenate([best[:, :1], best[:, 1 + c * k: 1 + (c + 1) * k]], axis=1)[:, :k]
+        drafts[:, c] = np.where(rng.random((B, k)) < 0.5, rows, drafts[:, c])
+    lens = rng.integers(0, k + 1, B)
+    lens[0] = 0
+    with_q = vmode == OV.STOCHASTIC
+    a, out, chain, margin = oracle_sample(logits, drafts, q if with_q else None, u, vmode, OV.SAMPLE_EXP_RACE, temp, lens)
+    ga, gout, gchain = op_sample(torch.from_numpy(logits).to(DEV), torch.from_numpy(drafts).to(torch.int32).to(DEV).contiguous(),
+                                 torch.as_tensor(q).to(DEV).contiguous() if with_q else None, torch.from_numpy(u).to(DEV),
+                                 verify_mode=vmode, sample_mode=OV.SAMPLE_EXP_RACE, temperature=temp,
+                                 draft_lens=torch.from_numpy(lens).to(torch.int32).to(DEV))
+    ga, gout, gchain = ga.cpu().numpy(), gout.cpu().numpy(), gchain.cpu().numpy()
+    bad = [b for b in range(B) if not (ga[b] == a[b] and gchain[b] == chain[b] and np.array_equal(gout[b], out[b]))]
+    # fp32 logits of magnitude |x| / temp carry 2^-24 of it: closer decisions than twice that are not decided
+    tol = max(1e-5, 2.0 ** -22 * float(np.abs(logits).max()) / temp)
+    assert all(margin[b] < tol for b in bad), [(b, margin[b], ga[b], a[b], gout[b], out[b]) for b in bad]
+    assert len(bad) <= max(1, B // 8)
