@@ -757,27 +757,40 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
 }
 
 // Combine the chunk partials of one row: out = sum_c 2^(m_c - M) O_c / sum_c 2^(m_c - M) l_c.  A thread
-// owns four consecutive dimensions of one q head; a work-group covers 256 / 32 = 8 heads of the row.
+// owns four consecutive dimensions of one q head; a work-group covers 256 / 32 = 8 heads of the row.  The 32 threads of a
+// head take one piece's (m, l) each, all at once, and share the factors; eight pieces' O are in flight at a time.
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
-    const int t = blockIdx.x, h = blockIdx.y * 8 + (threadIdx.x >> 5), d = (threadIdx.x & 31) * 4;
-    if (h >= a.Hq) return;
+    const int t = blockIdx.x, h = blockIdx.y * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31, d = lane * 4;
+    if (h >= a.Hq) return;                                // (whole groups of 32)
     const int4 pt = reinterpret_cast<const int4*>(a.row_part)[t];
     const int nch = pt.w;                                 // 0: a request of one piece, already written
     if (nch == 0) return;
     const int G = a.Hq / a.Hkv, hkv = h / G;
     const int64_t base = (int64_t)pt.x + (int64_t)hkv * pt.y + h % G;
+    const floatx2* ml = reinterpret_cast<const floatx2*>(a.part_ml) + base;
     float M = -INFINITY;
-    for (int c = 0; c < nch; ++c) M = fmaxf(M, a.part_ml[(base + (int64_t)c * pt.z) * 2]);
+    for (int c = lane; c < nch; c += 32) M = fmaxf(M, ml[(int64_t)c * pt.z].x);
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 32));
     floatx4 num = {0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
-    for (int c = 0; c < nch; ++c) {
-        const int64_t pr = base + (int64_t)c * pt.z;
-        const floatx2 ml = *reinterpret_cast<const floatx2*>(a.part_ml + pr * 2);
-        const float f = exp2f(ml.x - M);
-        den += f * ml.y;
-        const floatx4 o = *reinterpret_cast<const floatx4*>(a.part_o + pr * HD + d);
-        num[0] += f * o[0]; num[1] += f * o[1]; num[2] += f * o[2]; num[3] += f * o[3];
+    for (int c0 = 0; c0 < nch; c0 += 32) {
+        const floatx2 x = c0 + lane < nch ? ml[(int64_t)(c0 + lane) * pt.z] : floatx2{-INFINITY, 0.f};
+        const float f = exp2f(x.x - M);
+        den += f * x.y;
+        for (int c = c0; c < min(nch, c0 + 32); c += 8) {
+            floatx4 o[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o[u] = *reinterpret_cast<const floatx4*>(a.part_o + (base + (int64_t)min(c + u, nch - 1) * pt.z) * HD + d);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float fu = __shfl(f, (c + u) & 31, 32);             // pieces past the end: factor 0
+                num[0] += fu * o[u][0]; num[1] += fu * o[u][1]; num[2] += fu * o[u][2]; num[3] += fu * o[u][3];
+            }
+        }
     }
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o, 32);
     // four consecutive dimensions stay inside one 8-element piece of either output order
     u32x2 pk = {pack2bf(num[0] / den, num[1] / den), pack2bf(num[2] / den, num[3] / den)};
     *reinterpret_cast<u32x2*>(reinterpret_cast<bf16_t*>(a.out) + act_index(t, h * HD + d, a.Hq * HD, a.out_packed)) = pk;

@@ -28,6 +28,10 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
 template <typename T> struct Store;
 template <> struct Store<float> {
     static __device__ __forceinline__ float load(const float* p) { return *p; }
+    static __device__ __forceinline__ void load4(const float* p, float* v) {       // p 16-byte aligned
+        const floatx4 x = *reinterpret_cast<const floatx4*>(p);
+        v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
+    }
     static __device__ __forceinline__ void store(float* p, float v) { *p = v; }
     static __device__ __forceinline__ void store4(float* p, const float* v) {      // p 16-byte aligned
         *reinterpret_cast<floatx4*>(p) = floatx4{v[0], v[1], v[2], v[3]};
@@ -35,6 +39,11 @@ template <> struct Store<float> {
 };
 template <> struct Store<bf16_t> {
     static __device__ __forceinline__ float load(const bf16_t* p) { return bf2f(*p); }
+    static __device__ __forceinline__ void load4(const bf16_t* p, float* v) {      // p 8-byte aligned
+        const u32x2 x = *reinterpret_cast<const u32x2*>(p);
+        v[0] = __uint_as_float(x[0] << 16); v[1] = __uint_as_float(x[0] & 0xffff0000u);
+        v[2] = __uint_as_float(x[1] << 16); v[3] = __uint_as_float(x[1] & 0xffff0000u);
+    }
     static __device__ __forceinline__ void store(bf16_t* p, float v) { *p = f2bf(v); }
     static __device__ __forceinline__ void store4(bf16_t* p, const float* v) {     // p 8-byte aligned
         *reinterpret_cast<u32x2*>(p) = u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};

@@ -529,32 +529,60 @@ static int release_slot(sv_ctx* c, int slot) {
     return SV_OK;
 }
 
-// Keys per piece for a step's attention, unless fixed by option: each candidate's launch is simulated -- every piece
-// goes to the CU that frees up first and costs its keys plus a fixed ~300 keys' worth (measured: ~6 us of start-up and
-// merge per work-group against ~46 keys per us per CU) -- and the shortest makespan wins.
+// Pieces of less than kChunkKeys are for the last few requests of a rollout, and at most kFinePieces of them each (a
+// captured launch has its grid sized for the most pieces there can be).
+constexpr int kFinePieces = 64;
+static bool fine_pieces_ok(const sv_ctx* c, int B) { return B * c->model.n_kv_heads <= 128; }
+static int pieces_of(const sv_ctx* c, int total, int chunk) {
+    return std::max(1, std::min((total + chunk - 1) / chunk, chunk < kChunkKeys ? kFinePieces : c->lay.max_chunks));
+}
+
+// Keys per piece for a step's attention, unless fixed by option: each candidate's launch is simulated and the shortest
+// makespan, in keys of a CU's share of the stream (46 per us), wins.
+//  - Every piece costs a fixed ~300 (6 us of start-up and merge per work-group, measured).
+//  - A launch of more than 256 work-groups: every piece goes to the CU that frees up first and costs its keys.  (The kv heads
+//    of a piece are alike: 256 / heads places, each taking all heads of a piece.)
+//  - Fewer work-groups do not share the stream with enough others to be bound by it: a lone one works off some 98 keys per us
+//    (three row tiles, measured), so for the handful of requests at the end of a rollout fine pieces are better.
+//  - Every piece adds its share to the merge launch, ~0.15 us.
+// One request of 6000 keys: pieces of 1024 take 22.2 + 7.2 us per layer (attention + merge), fine ones 13.4 + 5.2; seven
+// requests of 900-5000 keys 23.8 + 6.0 against 21.4 + 4.9.
 static int pick_chunk(const sv_ctx* c, const Pass& ps) {
     if (c->attn_chunk_opt) return c->attn_chunk_opt;
+    const int Hkv = c->model.n_kv_heads, G = c->model.n_q_heads / Hkv;
+    const int row_groups = (G * ps.n_max + kItemRows - 1) / kItemRows;
     int chunk = kChunkKeys;
     double best = 1e300;
     std::vector<int> lens;
-    std::vector<double> cu(256);
-    for (int cand : {1024, 1536, 2048, 3072, 4096, 6144, 8192, 12288, 16384, 24576, 32768}) {
+    std::vector<double> place(std::max(1, 256 / Hkv));
+    for (int cand : {128, 256, 384, 512, 768, 1024, 1536, 2048, 3072, 4096, 6144, 8192, 12288, 16384, 24576, 32768}) {
+        if (cand < kChunkKeys && !fine_pieces_ok(c, ps.B)) continue;
         lens.clear();
+        int most = 0;
         for (int b = 0; b < ps.B; ++b) {
             const int total = c->seqs[ps.rq[b].seq].len_ub + ps.rq[b].n;
-            const int nch = std::max(1, std::min((total + cand - 1) / cand, c->lay.max_chunks));
+            const int nch = pieces_of(c, total, cand);
+            most = std::max(most, nch);
             for (int ch = 0; ch < nch; ++ch) lens.push_back((total + nch - 1) / nch);
         }
-        std::sort(lens.begin(), lens.end(), std::greater<int>());
-        std::fill(cu.begin(), cu.end(), 0.0);
-        for (int len : lens)
-            for (int h = 0; h < c->model.n_kv_heads; ++h) {
-                std::pop_heap(cu.begin(), cu.end(), std::greater<double>());
-                cu.back() += len + 300.0;
-                std::push_heap(cu.begin(), cu.end(), std::greater<double>());
+        const double wgs = (double)lens.size() * Hkv * row_groups;
+        double makespan = 0.0;
+        if (wgs <= 256) {
+            const int longest = *std::max_element(lens.begin(), lens.end());
+            makespan = 300.0 + longest * std::max(0.47, wgs / 256.0);
+        } else {
+            std::sort(lens.begin(), lens.end(), std::greater<int>());
+            std::fill(place.begin(), place.end(), 0.0);
+            for (int len : lens) {
+                std::pop_heap(place.begin(), place.end(), std::greater<double>());
+                place.back() += len + 300.0;
+                std::push_heap(place.begin(), place.end(), std::greater<double>());
             }
-        const double makespan = *std::max_element(cu.begin(), cu.end());
+            makespan = *std::max_element(place.begin(), place.end());
+        }
+        if (most > 1) makespan += 7.0 * most;
         if (makespan < best) { best = makespan; chunk = cand; }
+        if (most == 1) break;                              // coarser candidates cut nothing either
     }
     return chunk;
 }
@@ -588,8 +616,7 @@ static void build_work(sv_ctx* c, const Pass& ps, int32_t* req, int32_t* work) {
         const PassReq& r = ps.rq[b];
         const int start = c->seqs[r.seq].len_ub, total = start + r.n;
         const int rows_pad = (G * r.n + 15) / 16 * 16, groups = prefill ? (G * r.n + kItemRows - 1) / kItemRows : 1;
-        int nch = prefill ? std::min(cut, (total + kChunkKeys - 1) / kChunkKeys) : (total + chunk - 1) / chunk;
-        nch = std::max(1, std::min(nch, L.max_chunks));
+        int nch = prefill ? std::min(cut, pieces_of(c, total, kChunkKeys)) : pieces_of(c, total, chunk);
         if (prow + (long long)nch * m.n_kv_heads * rows_pad > L.part_rows || (long long)items.size() + (long long)nch * groups + (ps.B - b) > L.max_items)
             nch = 1;                                       // no room for partials: one piece, written directly
         const int clen = ((total + nch - 1) / nch + 31) / 32 * 32;
@@ -759,7 +786,7 @@ static AttnArgs attn_args(const sv_ctx* c, const Pass& ps, int layer, const void
     aa.n_work_dev = nullptr; aa.grid_items = 0;
     if (c->graph_launch_shape) {      // nothing in the launch may depend on the lengths
         aa.n_work_dev = c->at<int32_t>(L.stage);
-        aa.grid_items = ps.B * L.max_chunks;
+        aa.grid_items = ps.B * (fine_pieces_ok(c, ps.B) ? std::max(L.max_chunks, kFinePieces) : L.max_chunks);
         aa.merge = true;
     }
     aa.out_packed = out_packed;

@@ -62,49 +62,53 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(RowPrep p) {
     }
 }
 
-// One 256-thread group per row.  Each thread owns up to NV float4 pieces of the row; the loads of the
-// residual and of every split-K partial product are issued before the first use, so the row costs a
-// few memory round trips rather than one per element.
+// One work-group of NTH threads per row.  Each thread owns up to NV float4 pieces of the row; the loads of the residual, of
+// the gain and of a batch of split-K partial products (plane order kept in the additions) are issued before the first
+// use, so the row costs a few memory round trips rather than one per element.
 // With `inv` set the addend is not S planes but the weighted sum of the row's top_k expert outputs
 // (part = expert outputs [padded row][d], row of assignment j at inv[t*top_k + j], weight wts[t*top_k + j]),
 // accumulated in slot order.
-template <typename T, int NV>
-__global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h, const float* __restrict__ part, int S,
+template <typename T, int NV, int NTH>
+__global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h, const float* __restrict__ part, int S,
                                                           int64_t part_stride, const T* __restrict__ w,
                                                           T* __restrict__ a, int d, float eps, bool packed,
                                                           const int32_t* __restrict__ inv, const float* __restrict__ wts,
                                                           int top_k, const int32_t* __restrict__ last_of) {
-    __shared__ float red[4];
+    constexpr int U = NV == 1 ? 8 : 4;                   // planes, or expert rows, in flight
+    __shared__ float red[NTH / 64];
     const int t_out = blockIdx.x;
     const int t = last_of ? last_of[t_out * kReqInts] + last_of[t_out * kReqInts + 1] - 1 : t_out;
     const int nq = d >> 2;                               // float4 pieces per row
     floatx4* hr = reinterpret_cast<floatx4*>(h + (int64_t)t * d);
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
     floatx4 x[NV];
+    float gain[NV][4];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int i = threadIdx.x + v * 256;
-        x[v] = i < nq ? hr[i] : floatx4{0.f, 0.f, 0.f, 0.f};
+        const int i = threadIdx.x + v * NTH;
+        x[v] = i < nq ? hr[i] : zero;
+        if (i < nq) Store<T>::load4(w + 4 * i, gain[v]);
     }
     if (inv) {
         floatx4 acc[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] = floatx4{0.f, 0.f, 0.f, 0.f};
-        for (int j0 = 0; j0 < top_k; j0 += 4) {             // four expert rows in flight at a time
-            floatx4 y[4][NV];
-            float wj[4];
+        for (int v = 0; v < NV; ++v) acc[v] = zero;
+        for (int j0 = 0; j0 < top_k; j0 += U) {
+            floatx4 y[U][NV];
+            float wj[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int j = j0 + u < top_k ? j0 + u : j0;
                 wj[u] = j0 + u < top_k ? wts[(int64_t)t * top_k + j] : 0.f;
                 const floatx4* pr = reinterpret_cast<const floatx4*>(part + (int64_t)inv[(int64_t)t * top_k + j] * d);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    const int i = threadIdx.x + v * 256;
-                    y[u][v] = ((i < nq) & (j0 + u < top_k)) ? pr[i] : floatx4{0.f, 0.f, 0.f, 0.f};
+                    const int i = threadIdx.x + v * NTH;
+                    y[u][v] = ((i < nq) & (j0 + u < top_k)) ? pr[i] : zero;
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < U; ++u)
                 if (j0 + u < top_k) {
 #pragma unroll
                     for (int v = 0; v < NV; ++v)
@@ -115,20 +119,19 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
 #pragma unroll
         for (int v = 0; v < NV; ++v) x[v] = x[v] + acc[v];
     } else {
-    // partial planes four at a time: all their loads are in flight together, the additions keep plane order
-        for (int s0 = 0; s0 < S; s0 += 4) {
-            floatx4 y[4][NV];
+        for (int s0 = 0; s0 < S; s0 += U) {
+            floatx4 y[U][NV];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const floatx4* pr = reinterpret_cast<const floatx4*>(part + (s0 + u < S ? s0 + u : s0) * part_stride + (int64_t)t * d);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    const int i = threadIdx.x + v * 256;
-                    y[u][v] = ((i < nq) & (s0 + u < S)) ? pr[i] : floatx4{0.f, 0.f, 0.f, 0.f};
+                    const int i = threadIdx.x + v * NTH;
+                    y[u][v] = ((i < nq) & (s0 + u < S)) ? pr[i] : zero;
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int v = 0; v < NV; ++v) x[v] = x[v] + y[u][v];
         }
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
     float ss = 0.f;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int i = threadIdx.x + v * 256;
+        const int i = threadIdx.x + v * NTH;
         if (i < nq) {
             if ((S > 0 || inv) && !last_of) hr[i] = x[v];
             ss = fmaf(x[v][0], x[v][0], ss);
@@ -148,25 +151,28 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
     __syncthreads();
-    const float tot = red[0] + red[1] + red[2] + red[3];
+    float tot = red[0];
+#pragma unroll
+    for (int i = 1; i < NTH / 64; ++i) tot += red[i];
     const float r = 1.0f / sqrtf(tot / (float)d + eps);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int i = threadIdx.x + v * 256;
+        const int i = threadIdx.x + v * NTH;
         if (i < nq) {
             float o[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = x[v][e] * r * Store<T>::load(w + 4 * i + e);
+            for (int e = 0; e < 4; ++e) o[e] = x[v][e] * r * gain[v][e];
             // four consecutive columns are contiguous in either output order
             Store<T>::store4(a + act_index(t_out, 4 * i, d, packed), o);
         }
     }
 }
 
-// q and k heads are rotated, k and v heads go to the row's cache slot.  One work-group per row, four consecutive
-// dimensions (and their partners half a head away) per thread: 16-byte reads of the partial planes and of the
-// rotary table, one 8- or 16-byte store per four q or K values (four consecutive dimensions of a key are contiguous
-// in the cache's K tiles); V is stored transposed, one element at a time.  head_dim % 8 == 0 (it is 64 or 128).
+// q and k heads are rotated, k and v heads go to the row's cache slot.  Four consecutive dimensions (and their partners
+// half a head away) per thread, a row spread over gridDim.y work-groups: 16-byte reads of the partial planes, four planes in
+// flight, and of the rotary table, one 8- or 16-byte store per four q or K values (four consecutive dimensions of a key are
+// contiguous in the cache's K tiles); V is stored transposed, one element at a time.  head_dim % 8 == 0 (it is 64 or 128).
+// Five rows, eight planes: 4.8 us; with one work-group per row and the planes one after the other 10.5.
 template <typename T>
 __global__ __launch_bounds__(256) void rope_append_vec_kernel(RopeAppend p) {
     const int t = blockIdx.x;
@@ -174,43 +180,51 @@ __global__ __launch_bounds__(256) void rope_append_vec_kernel(RopeAppend p) {
     const int nheads = p.Hq + 2 * p.Hkv;
     const int ncol = nheads * hd;
     const int64_t stride = (int64_t)p.T * ncol;
+    const int u = blockIdx.y * 256 + threadIdx.x;
+    if (u >= nheads * upq) return;
     const int slot = p.row_slot[t];
     const int page = slot / p.geom.page_size, tok = slot % p.geom.page_size;
     T* pool = reinterpret_cast<T*>(p.pool);
-    for (int u = threadIdx.x; u < nheads * upq; u += 256) {
-        const int head = u / upq, i = (u % upq) * 4;
-        const float* src = p.qkv_part + (int64_t)t * ncol + head * hd + i;
-        floatx4 x1 = {0.f, 0.f, 0.f, 0.f}, x2 = {0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < p.S; ++s) {
-            x1 += *reinterpret_cast<const floatx4*>(src + s * stride);
-            x2 += *reinterpret_cast<const floatx4*>(src + s * stride + half);
+    const int head = u / upq, i = (u % upq) * 4;
+    const float* src = p.qkv_part + (int64_t)t * ncol + head * hd + i;
+    const floatx4 r0 = *reinterpret_cast<const floatx4*>(p.rope + ((int64_t)t * half + i) * 2);
+    const floatx4 r1 = *reinterpret_cast<const floatx4*>(p.rope + ((int64_t)t * half + i) * 2 + 4);
+    floatx4 x1 = {0.f, 0.f, 0.f, 0.f}, x2 = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < p.S; s0 += 4) {
+        floatx4 y1[4], y2[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float* ps = src + min(s0 + q, p.S - 1) * stride;
+            y1[q] = *reinterpret_cast<const floatx4*>(ps);
+            y2[q] = *reinterpret_cast<const floatx4*>(ps + half);
         }
-        if (head < p.Hq + p.Hkv) {
-            const floatx4 r0 = *reinterpret_cast<const floatx4*>(p.rope + ((int64_t)t * half + i) * 2);
-            const floatx4 r1 = *reinterpret_cast<const floatx4*>(p.rope + ((int64_t)t * half + i) * 2 + 4);
-            const float c[4] = {r0[0], r0[2], r1[0], r1[2]}, sn[4] = {r0[1], r0[3], r1[1], r1[3]};
-            float o1[4], o2[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                o1[e] = x1[e] * c[e] - x2[e] * sn[e];
-                o2[e] = x2[e] * c[e] + x1[e] * sn[e];
-            }
-            if (head < p.Hq) {
-                T* q = reinterpret_cast<T*>(p.q_out) + ((int64_t)t * p.Hq + head) * hd;
-                Store<T>::store4(q + i, o1);
-                Store<T>::store4(q + i + half, o2);
-            } else {
-                const int kh = head - p.Hq;
-                Store<T>::store4(pool + kv_k_index(p.geom, p.layer, page, kh, tok, i), o1);
-                Store<T>::store4(pool + kv_k_index(p.geom, p.layer, page, kh, tok, i + half), o2);
-            }
+        for (int q = 0; q < 4; ++q)
+            if (s0 + q < p.S) { x1 += y1[q]; x2 += y2[q]; }
+    }
+    if (head < p.Hq + p.Hkv) {
+        const float c[4] = {r0[0], r0[2], r1[0], r1[2]}, sn[4] = {r0[1], r0[3], r1[1], r1[3]};
+        float o1[4], o2[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            o1[e] = x1[e] * c[e] - x2[e] * sn[e];
+            o2[e] = x2[e] * c[e] + x1[e] * sn[e];
+        }
+        if (head < p.Hq) {
+            T* q = reinterpret_cast<T*>(p.q_out) + ((int64_t)t * p.Hq + head) * hd;
+            Store<T>::store4(q + i, o1);
+            Store<T>::store4(q + i + half, o2);
         } else {
-            const int kh = head - p.Hq - p.Hkv;
+            const int kh = head - p.Hq;
+            Store<T>::store4(pool + kv_k_index(p.geom, p.layer, page, kh, tok, i), o1);
+            Store<T>::store4(pool + kv_k_index(p.geom, p.layer, page, kh, tok, i + half), o2);
+        }
+    } else {
+        const int kh = head - p.Hq - p.Hkv;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                Store<T>::store(pool + kv_v_index(p.geom, p.layer, page, kh, tok, i + e), x1[e]);
-                Store<T>::store(pool + kv_v_index(p.geom, p.layer, page, kh, tok, i + half + e), x2[e]);
-            }
+        for (int e = 0; e < 4; ++e) {
+            Store<T>::store(pool + kv_v_index(p.geom, p.layer, page, kh, tok, i + e), x1[e]);
+            Store<T>::store(pool + kv_v_index(p.geom, p.layer, page, kh, tok, i + half + e), x2[e]);
         }
     }
 }
@@ -263,6 +277,8 @@ hipError_t prep_rows(const RowPrep& p, hipStream_t st) {
     return hipGetLastError();
 }
 
+constexpr int kWideNormRows = 640;
+
 template <typename T>
 static hipError_t add_rmsnorm_t(float* h, const float* part, int S, const T* w, T* a, int T_, int d, float eps, bool packed,
                                 const int32_t* inv, const float* wts, int top_k, const int32_t* last_of, int n_out, hipStream_t st) {
@@ -270,12 +286,19 @@ static hipError_t add_rmsnorm_t(float* h, const float* part, int S, const T* w, 
     const int nq = d / 4;
     if (d % 4 != 0 || nq > 256 * 8) return hipErrorInvalidValue;
     const dim3 grid(last_of ? n_out : T_);
-    auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k, last_of);
+    auto launch = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k, last_of);
     };
-    if (nq <= 256 * 2) launch(add_rmsnorm_kernel<T, 2>);
-    else if (nq <= 256 * 4) launch(add_rmsnorm_kernel<T, 4>);
-    else launch(add_rmsnorm_kernel<T, 8>);
+    // Few rows: the more threads the fewer round trips (five rows of 896 pieces: 6.0 us with 256 threads, 4.7 with 1024).
+    // Many: as few idle lanes and registers as the width allows (800 rows of 1280 pieces and four planes in flight: eight
+    // pieces for each of 256 threads 31.8 us, three for each of 512 17.8).
+    const bool wide = T_ <= kWideNormRows;
+    if (nq <= 512) launch(add_rmsnorm_kernel<T, 1, 512>, 512);
+    else if (nq <= 1024 && wide) launch(add_rmsnorm_kernel<T, 1, 1024>, 1024);
+    else if (nq <= 1024) launch(add_rmsnorm_kernel<T, 2, 512>, 512);
+    else if (wide) launch(add_rmsnorm_kernel<T, 2, 1024>, 1024);
+    else if (nq <= 1536) launch(add_rmsnorm_kernel<T, 3, 512>, 512);
+    else launch(add_rmsnorm_kernel<T, 4, 512>, 512);
     return hipGetLastError();
 }
 
@@ -293,10 +316,9 @@ hipError_t add_rmsnorm_experts(float* h, const float* y, const int32_t* inv, con
 
 hipError_t rope_append(const RopeAppend& p, hipStream_t st) {
     if (p.hd % 8 != 0) return hipErrorInvalidValue;
-    if (p.dtype == 1)
-        hipLaunchKernelGGL(rope_append_vec_kernel<bf16_t>, dim3(p.T), dim3(256), 0, st, p);
-    else
-        hipLaunchKernelGGL(rope_append_vec_kernel<float>, dim3(p.T), dim3(256), 0, st, p);
+    const dim3 grid(p.T, ((p.Hq + 2 * p.Hkv) * (p.hd / 8) + 255) / 256);
+    if (p.dtype == 1) hipLaunchKernelGGL(rope_append_vec_kernel<bf16_t>, grid, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL(rope_append_vec_kernel<float>, grid, dim3(256), 0, st, p);
     return hipGetLastError();
 }
 
