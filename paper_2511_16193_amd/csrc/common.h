@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <utility>
 
 namespace sv {
 
@@ -115,6 +116,18 @@ __device__ __forceinline__ void dma4(const char* src, __attribute__((address_spa
     __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 2048, 0);
     __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 3072, 0);
 }
+
+// ... and 2 KB
+__device__ __forceinline__ void dma2(const char* src, __attribute__((address_space(3))) void* dst) {
+    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 1024, 0);
+}
+
+// f(std::integral_constant<int, 0>{}), ... , f(std::integral_constant<int, N - 1>{}): a loop whose index is a constant expression
+template <typename F, int... I> __device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
 
 template <typename T> __device__ __forceinline__ T wave_max(T v) {
 #pragma unroll

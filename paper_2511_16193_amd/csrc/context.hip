@@ -29,6 +29,7 @@ constexpr int kChunkKeys = 1024;      // keys per split-KV chunk of the bf16 att
 // every row, 26.4 ms in two passes with it on the prompts' last rows.  From about a thousand rows on the projections are
 // bound by their products; four thousand rows cost 0.4-1 GB of workspace.
 constexpr int kPrefillRows = 4096;
+constexpr int kPlans = 64;            // launch plans a context remembers (five shapes per number of rows)
 constexpr int kCausalK = 1 << 20;     // "drafts per chain" of a prefill pass: one chain, never ending
 
 struct SeqState {
@@ -57,12 +58,11 @@ int pick_splits(int M, int N, int K) {
 // fit to a sweep of every (tiles, width, splits) over thirty shapes of the benchmark models on MI355X (rows 5 to
 // 2304), except the lone work-group's pace, which is taken from whole steps (cold weights); on the sweep the plan
 // chosen was within 0.3 % of the best on average and 4.5 % at worst.
-struct WsPlan { int splits; bool wide; int row_tiles; };
-WsPlan plan_ws(int M, int N, int K, bool allow_split, int tile_mode = -1, int max_splits = kMaxSplitsWs) {
+struct WsPlan { int splits; bool wide; int row_tiles; double us; };
+WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplitsWs) {
     const int slices_all = K / 16;
     const int tiles = (M + 31) / 32;
-    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M)};
-    double best_t = 1e30;
+    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M), 1e30};
     // up to 160 rows: one work-group along the rows (cutting so few rows only multiplies the readers of a strip)
     const int mt_lo = tiles <= 5 ? tiles : 1, mt_hi = tiles <= 5 ? tiles : 5;
     for (int mt = mt_lo; mt <= mt_hi; ++mt)
@@ -94,17 +94,25 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int tile_mode = -1, int ma
                 t = std::max(t, (double)N * K * 2.0 / 4.98e6);                // a weight stream cannot beat the memory system
                 if (s > 1) t += (double)s * M * N * 4.0 / 5.4e6 + (double)(s - 1) * M * N * 4.0 / 4.0e6;   // planes written here, read by the consumer
                 t += 2.3;
-                if (t < best_t - 1e-9) { best_t = t; best = WsPlan{s, wide != 0, mt}; }
+                if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t};
             }
         }
-    // The 256 x 256 kernel (row_tiles 8) from a thousand rows on, where its tiles fill the chip at least four times
-    // over (the LM head): measured inside the steps of the 7B shape it takes 8 % off that launch at 1280 and at 2304
-    // rows.  Narrower projections (QKV, O, down: fewer tiles than CUs) stay with the weight-streaming kernel.
-    if (tile_mode != 0 && N % 256 == 0 && K % 64 == 0) {
-        const long long blocks = (long long)((M + 255) / 256) * (N / 256);
-        if (tile_mode == 1 || (M >= 1024 && blocks >= 4 * 256)) best = WsPlan{1, true, 8};
-    }
     return best;
+}
+
+// Launch plan of a packed projection: the weight-streaming kernel, or from more rows than one of its work-groups holds on the
+// tall kernel (row_tiles 6, 8, 10) where that is expected to take less.  Inside a step the weight-streaming launches
+// take 1.10 times the estimate above, which was fitted to single projections in a loop (7B at 2304 rows: QKV 89 us against 78,
+// down 282 against 263); the tall ones take theirs.
+// us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
+// 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
+// tile_mode: -1 = this rule, 0 = never the tall kernel, 1 = 256-row tiles wherever the width allows.
+WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, int max_splits = kMaxSplitsWs) {
+    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 8, 0.0};
+    const WsPlan ws = plan_ws(M, N, K, allow_split, max_splits);
+    if (tile_mode == 0 || M <= 128) return ws;
+    const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
+    return t.us < 1.10 * ws.us ? WsPlan{t.splits, true, 2 * t.rw, t.us} : ws;
 }
 
 struct Layout {                       // byte offsets into the workspace
@@ -168,11 +176,11 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
         for (auto& sh : shapes)
             part = std::max(part, (size_t)(m.dtype == SV_BF16 ? pick_splits(M, sh[0], sh[1]) : 1) * M * sh[0]);
     }
-    if (m.dtype == SV_BF16)                                 // the same for the plans of the weight-streaming kernel
+    if (m.dtype == SV_BF16)                                 // the same for the plans of packed weights
         for (int tm = 1; tm <= (P + 31) / 32; ++tm) {
             const int M = std::min(tm * 32, P);
             for (auto& sh : shapes)
-                if (sh[1] % 64 == 0) part = std::max(part, (size_t)plan_ws(M, sh[0], sh[1], true).splits * M * sh[0]);
+                if (sh[1] % 64 == 0) part = std::max(part, (size_t)plan_packed(M, sh[0], sh[1], true, -1).splits * M * sh[0]);
         }
     L.part_floats = part;
     L.part = take(sizeof(float) * part);
@@ -240,7 +248,9 @@ struct sv_ctx {
     int n_work;                                           // attention work items staged for the current pass
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
     int gemm_variant;                                     // -1 = choose per shape
-    int gemm_tile;                                        // 256 x 256 projection kernel: -1 = where it pays, 0 = never, 1 = wherever the shape allows
+    int gemm_tile;                                        // tall projection kernel: -1 = where it pays, 0 = never, 1 = wherever the shape allows
+    struct PlannedShape { int M, N, K; bool allow_split; WsPlan plan; };
+    std::vector<PlannedShape> plans;                      // launch plans of packed projections made so far, at most kPlans
     bool packed;                                          // projection weights are in fragment order
     bool attn_generic;
     int attn_min_rt;
@@ -711,13 +721,22 @@ static int pick_variant(const sv_ctx* c, int M) {
     return M <= 64 ? 1 : M >= 512 ? 2 : 0;
 }
 
+// The plan of a packed projection, made once per shape (some microseconds of host arithmetic).
+static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split) {
+    for (const auto& p : c->plans)
+        if (p.M == M && p.N == N && p.K == K && p.allow_split == allow_split) return p.plan;
+    WsPlan p = plan_packed(M, N, K, allow_split, c->gemm_tile);
+    while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_packed(M, N, K, allow_split, c->gemm_tile, p.splits - 1);
+    if (c->plans.size() >= kPlans) c->plans.clear();
+    c->plans.push_back({M, N, K, allow_split, p});
+    return p;
+}
+
 static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int N, int K, int* splits_out, bool allow_split = true) {
     ProfScope prof(c, SV_PROF_GEMM);
     if (c->model.dtype == SV_BF16) {
         if (c->packed) {
-            // packed weights + packed activations: the weight-streaming kernel
-            WsPlan p = plan_ws(M, N, K, allow_split, c->gemm_tile);
-            while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_ws(M, N, K, allow_split, c->gemm_tile, p.splits - 1);
+            const WsPlan p = planned(c, M, N, K, allow_split);
             *splits_out = p.splits;
             SV_HIP(c, gemm_bf16_ws((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, p.wide, c->stream, p.row_tiles));
         } else {
@@ -841,7 +860,15 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     if (c->packed && m.d_ff % 64 == 0) {
         // gate/up projection with SwiGLU in its epilogue: the [T, 2F] fp32 intermediate never exists
         ProfScope prof(c, SV_PROF_GEMM);
-        SV_HIP(c, gemm_bf16_ws_glu((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<bf16_t>(L.act), T, m.d_ff, d, st, c->gemm_tile));
+        // More than five 32-row tiles: the tall tiles (one work-group of the weight-streaming kernel along the rows no longer
+        // holds them, and every further one reads the strip again).  us of the 7B shape at 147 / 192 / 256 / 320 / 512 / 800 rows,
+        // weight-streaming against tall: 65 / 86 / 104 / 100 / 160 / 221 against 65 / 66 / 77 / 98 / 144 / 218.
+        if (m.d_ff % 128 == 0 && (c->gemm_tile == 1 || (c->gemm_tile != 0 && T > 160))) {
+            const int rw = c->gemm_tile == 1 ? 4 : gemm_bf16_tall_plan(T, 2 * m.d_ff, d, 1).rw;
+            SV_HIP(c, gemm_bf16_tall((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, rw, st));
+        } else {
+            SV_HIP(c, gemm_bf16_ws_glu((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<bf16_t>(L.act), T, m.d_ff, d, st));
+        }
     } else if (m.dtype == SV_FP32) {
         ProfScope prof(c, SV_PROF_GEMM);
         SV_HIP(c, gemm_f32_glu((const float*)a_norm, (const float*)c->wgu[l], c->at<float>(L.act), T, m.d_ff, d, st));
@@ -1064,7 +1091,9 @@ extern "C" int sv_op_gemm_bf16_ws(const void* Ap, const void* Wp, float* out, in
 
 extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int* row_tiles) {
     if (!splits || !wide || !row_tiles || M <= 0 || N <= 0 || K <= 0 || N % 128 != 0 || K % 64 != 0) return SV_EINVAL;
-    const WsPlan p = plan_ws(M, N, K, true);
+    // of the weight-streaming kernel, but where the 256-row tiles fill the chip four times over
+    WsPlan p = plan_ws(M, N, K, true);
+    if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0};
     *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
     return SV_OK;
 }
@@ -1271,6 +1300,7 @@ extern "C" int sv_set_option(sv_ctx* c, int option, int value) {
         case SV_OPT_GEMM_TILE:
             if (value < -1 || value > 1) return c->fail(SV_EINVAL, "gemm tile mode %d", value);
             c->gemm_tile = value;
+            c->plans.clear();
             return SV_OK;
         case SV_OPT_ATTN_GENERIC:
             c->attn_generic = value != 0;

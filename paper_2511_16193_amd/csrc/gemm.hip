@@ -9,6 +9,9 @@
 // elements: the 16 lanes of a quarter-wave hit 64 distinct banks), double buffered, with the next
 // tile's global loads in flight during the MFMAs of the current one.  Work-group ids are remapped so
 // that the groups that share one weight panel run on the same XCD (one L2) at about the same time.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
 #include "common.h"
 #include "kernels.h"
 
@@ -378,236 +381,296 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ws_glu_mixed_kernel(
         gemm_bf16_ws_body<2, 1, 8, 8, true>(Ap, Wp, out, M, N, K, K, 1, tiles_m2, 2 * strips_tail, 2 * strips_main, blockIdx.x - n_main);
 }
 
-// ---- third bf16 kernel: 256 rows x 256 features per work-group, both operands through LDS ----
-// For a thousand rows and more the weights no longer dominate the traffic and what a work-group pulls through
-// the caches per product decides: a 256 x 256 tile asks for (256 + 256) x 32 bytes per 16-wide slice of the
-// reduction where the weight-streaming kernel's 160 x 256 asks for (160 + 256) x 32 for 5/8 of the products.
-// Four waves, each a 128 x 128 quarter (sixteen 32x32 accumulators); a fill is four slices of both operands,
-// 64 KB, copied global -> LDS by direct-to-LDS loads with no register in between (in the packed orders a fill
-// is sixteen contiguous 4 KB runs: four slices of one 32-row activation tile, or the four 32-feature tiles of
-// one 128-feature strip at one slice), double buffered, one barrier per fill.  Every wave reads its eight
-// operand fragments of a slice from LDS as 1 KB pieces, the next slice's between the products of this one.
-// Measured alone on MI355X (LM head, 2304 rows): 1.16 (K = 3584) and 1.21 PFLOP/s (K = 5120) against 1.02 and 1.06
-// of the weight-streaming kernel and 1.39 and 1.31 of the vendor library; the matrix unit is busy 62 % of the cycles.
+// ---- third bf16 kernel: tall tiles, 64 RW rows x 256 features per work-group, both operands through LDS ----
+// From a few hundred rows on the weights no longer dominate the traffic, and what bounds a projection is the chip's power:
+// alone on the chip a work-group of this kernel runs its CU at 2.3 PFLOP/s / 256, with all CUs busy the clock drops until
+// the whole makes 1.2-1.3 PFLOP/s on random operands, whatever the pipeline depth (three fills in flight 1.24 PFLOP/s on the
+// LM head at 2304 rows, four and five 1.21; longer fills, raised wave priorities, a persistent grid: no gain).  What counts
+// is that the matrix units never wait and that nothing is fetched twice:
+//   * eight waves, two per SIMD, so that one multiplies while the other waits for LDS or the barrier.  (Four waves of 128 x 128
+//     with a hand-woven stream, alone on their SIMDs, reached 1.07.)  A wave holds 32 RW rows x 64 features.
+//   * a fill is two 16-wide slices of both operands, copied global -> LDS by direct-to-LDS loads in the packed orders, a ring
+//     of three fills, one barrier per fill.
+//   * rows that do not fill the last tile make a shorter one in the same launch (RWT), so that no product is padding beyond
+//     63 rows: beside its strip's other tiles where the launch takes several rounds (they share the strip through L2), behind
+//     them all in a launch of one or two rounds (they run on the CUs that the tall tiles leave idle).
 // GLU: the tile's features are 128 gate rows and the 128 up rows of the same features; a wave holds both for its
-// 64 features and writes silu(gate) * up, rounded to bf16, in the packed order of the next projection.
-template <bool GLU>
-__global__ __launch_bounds__(256, 1) void gemm_bf16_tile_kernel(
-    const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
-    int M, int N, int K, int k_per_split, int splits, int tiles_m, int tiles_n) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];   // two fills
-    constexpr int KA = 4;                                 // 16-wide slices per fill
-    constexpr int FILL = KA * 16 * 1024;                  // KA slices of 8 activation and 8 weight fragments
-    constexpr int B_OFF = KA * 8 * 1024;                  // weights behind the activations of a fill
-    constexpr int RW = KA / 2;                            // 4 KB weight runs (strip, slice) per wave and fill
-    constexpr int LPF = 4 * KA;                           // loads per wave and fill
+// 32 features and writes silu(gate) * up, rounded to bf16, in the packed order of the next projection.
+// Measured on MI355X (K = 3584), against the weight-streaming kernel / the four-wave one: gate/up of 37888 at 2304 rows
+// 617 / 588 -> 525 us, at 1280 348 / 310 -> 279, at 256 104 -> 77; LM head of 152064 at 2304 rows 2480 / 2340 -> 2050, at 640
+// 820 -> 611, at 256 402 -> 308; down (K = 18944) at 2304 rows 282 / 273 -> 243, at 3500 500 -> 411; QKV (4608) 98 -> 71.
+constexpr int kTallFills = 3;                             // fills in the LDS ring
+constexpr int kTallSlices = 2;                            // 16-wide slices per fill
 
-    const int nblk = tiles_m * tiles_n * splits;
-    int logical = xcd_remap(blockIdx.x, nblk);
-    const int tm = logical % tiles_m;
-    logical /= tiles_m;
-    const int sp = logical % splits;
-    const int tn = logical / splits;
-    const int m0 = tm * 256;
-    const int ks0 = sp * (k_per_split / 16);
-    const int nfill = k_per_split / (16 * KA);
-    const int kslices = K / 16;
+template <int OFF> __device__ __forceinline__ void lds_read16(u32x4& d, uint32_t addr) {
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
+}
+__device__ __forceinline__ void lds_landed(u32x4& d) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d)); }
+__device__ __forceinline__ void lds_landed_too(u32x4& d) { asm volatile("" : "+v"(d)); }     // no use of d moves above the wait
 
+template <bool GLU, int RW>
+__device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
+                                                    int M, int N, int K, int k_per_split, int m0, int tn, int sp) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char tall_lds[];   // kTallFills fills
+    constexpr int KA = kTallSlices, NB = kTallFills;
+    constexpr int B_OFF = KA * 2 * RW * 1024;             // weights (2 strips x 4 tiles a slice) behind the 2 RW row tiles
+    constexpr int FILL = B_OFF + KA * 8 * 1024;
+    const int nfill = k_per_split / (16 * KA), kslices = K / 16, ks0 = sp * (k_per_split / 16);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, lg = lane >> 5;
-    const int m_tiles_total = (M + 31) / 32;
+    const int wm = wave >> 2, wn = wave & 3, l32 = lane & 31, lg = lane >> 5;
+    const int m_tiles = (M + 31) / 32;
 
-    // this wave's share of a fill: activation row tiles 2 wave, 2 wave + 1 (KA slices each, contiguous) and RW of
-    // the 2 KA weight runs (strip, slice), 4 KB each
-    const char* a_src[2];
-    const char* w_src[RW];
-    int a_dst[2], w_dst[RW];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        int mt = m0 / 32 + 2 * wave + i;
-        mt = mt < m_tiles_total ? mt : m_tiles_total - 1;        // rows beyond M: any valid tile, never stored
-        a_src[i] = reinterpret_cast<const char*>(Ap + ((int64_t)mt * kslices + ks0) * 512) + lane * 16;
-        a_dst[i] = (2 * wave + i) * KA * 1024;
-    }
-#pragma unroll
-    for (int i = 0; i < RW; ++i) {
-        const int run = wave * RW + i, strip = run / KA, sl = run % KA;
-        const int strip_g = GLU ? (strip == 0 ? tn : N / 256 + tn) : 2 * tn + strip;
-        w_src[i] = reinterpret_cast<const char*>(Wp + (((int64_t)strip_g * kslices + ks0 + sl) * 4) * 512) + lane * 16;
-        w_dst[i] = B_OFF + (strip * KA + sl) * 4096;
-    }
-    auto issue_fill = [&](int fill, int buf) __attribute__((always_inline)) {
-        unsigned char* base = tile_lds + buf * FILL;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const char* src = a_src[i] + (int64_t)fill * (KA * 1024);
-            dma4(src, SV_LDS_PTR(base + a_dst[i]));
-        }
-#pragma unroll
-        for (int i = 0; i < RW; ++i) dma4(w_src[i] + (int64_t)fill * (KA * 4096), SV_LDS_PTR(base + w_dst[i]));
+    // This wave's share of a fill.  Activations: one of the 2 RW row tiles (RW = 5: waves 0 and 1 a second one; RW < 4: some
+    // waves none); weights: half of one 4 KB run (strip, slice).  Row tiles beyond M and a strip beyond N (N an odd
+    // multiple of 128) are read as the last one and never stored.
+    const bool loads_a = RW >= 4 || wave < 2 * RW, loads_a2 = RW == 5 && wave < 2;
+    auto row_tile = [&](int i) {
+        const int mt = m0 / 32 + i;
+        return reinterpret_cast<const char*>(Ap + ((int64_t)(mt < m_tiles ? mt : m_tiles - 1) * kslices + ks0) * 512) + lane * 16;
     };
-    // fragment offsets of this wave inside a fill, slice 0
-    int a_off[4], b_off[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) a_off[j] = ((wm * 4 + j) * KA) * 1024 + lane * 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int strip = GLU ? (i >> 1) : wn, tile = GLU ? 2 * wn + (i & 1) : i;
-        b_off[i] = B_OFF + (strip * KA * 4 + tile) * 1024 + lane * 16;
-    }
+    const char* a_src = row_tile(wave);
+    const char* a_src2 = row_tile(RW == 5 ? 8 + wave : wave);
+    const int run = wave >> 1, half = wave & 1, strip = run / KA, sl = run % KA;
+    const int strip_n = 2 * tn + strip;
+    const int strip_g = GLU ? (strip == 0 ? tn : N / 256 + tn) : strip_n < N / 128 ? strip_n : N / 128 - 1;
+    const char* w_src = reinterpret_cast<const char*>(Wp + (((int64_t)strip_g * kslices + ks0 + sl) * 4 + 2 * half) * 512) + lane * 16;
+    const int a_dst = wave * KA * 1024, w_dst = B_OFF + run * 4096 + half * 2048;
+    int ahead = 0;
+    auto request = [&](unsigned char* base) __attribute__((always_inline)) {
+        if (loads_a) dma2(a_src, SV_LDS_PTR(base + a_dst));
+        if (loads_a2) dma2(a_src2, SV_LDS_PTR(base + a_dst + 8 * KA * 1024));
+        dma2(w_src, SV_LDS_PTR(base + w_dst));
+    };
+    auto advance = [&]() __attribute__((always_inline)) {  // past the end: the last fill again, so that the counts below hold
+        if (++ahead < nfill) { a_src += KA * 1024; a_src2 += KA * 1024; w_src += KA * 4096; }
+    };
+    auto wait_fills = [&](auto in_flight) __attribute__((always_inline)) {   // all but the newest in_flight fills have landed
+        constexpr int L = decltype(in_flight)::value;
+        if (loads_a2) wait_vmcnt<6 * L>(); else if (loads_a) wait_vmcnt<4 * L>(); else wait_vmcnt<2 * L>();
+    };
 
-    floatx16 acc[4][4];                                   // [feature tile i][row tile j]
+    // Operands of a slice, two sets.  The LDS reads are placed by hand, with hand-counted waits: the compiler would wait for
+    // every read as soon as a direct-to-LDS load is in flight.  It takes the reads' registers as written at once, so a
+    // set is waited for in the basic block that reads it (a branch in between may copy registers still in flight).
+    u32x4 a[2][RW], b[2][2];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)SV_LDS_PTR(tall_lds);
+    const uint32_t a_off = lds0 + wm * RW * KA * 1024 + lane * 16;
+    const uint32_t b_off = lds0 + B_OFF + (GLU ? wn * 1024 : (wn >> 1) * KA * 4096 + (wn & 1) * 2048) + lane * 16;
+    constexpr int B_STEP = GLU ? KA * 4096 : 1024;        // from the wave's first feature tile to its second
+    uint32_t a_addr = a_off, b_addr = b_off;
+    auto read = [&](auto set, auto which, auto slice) __attribute__((always_inline)) {   // which: 0, 1 weights, then activations
+        constexpr int SET = decltype(set)::value, R = decltype(which)::value, S = decltype(slice)::value;
+        if constexpr (R < 2) lds_read16<R * B_STEP + S * 4096>(b[SET][R], b_addr);
+        else lds_read16<(R - 2) * KA * 1024 + S * 1024>(a[SET][R - 2], a_addr);
+    };
+    auto wait_set = [&](auto set) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set)::value;
+        lds_landed(b[SET][0]);
+        lds_landed_too(b[SET][1]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < RW; ++j) lds_landed_too(a[SET][j]);
+    };
+    floatx16 acc[2][RW];                                  // [feature tile][row tile]
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < RW; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    // The loop is written out instruction by instruction.  A wave alone on its SIMD issues in order, and the matrix
-    // unit runs dry whenever anything else is issued in a block: with the eight LDS reads of a slice and the sixteen
-    // loads of a fill issued together it was busy 55 % of the cycles.  So the LDS reads of the next slice and the
-    // loads of the fill after next sit between the products, one or two at a time, and execute in their shadow (the
-    // last read of a slice early enough for its data to be there when the slice ends).  The reads are
-    // hand-placed instructions with hand-counted waits because a direct-to-LDS load in flight makes the compiler
-    // wait for every LDS read at once.
-    u32x4 af[2][4], wf[2][4];
-    const uint32_t lds0 = (uint32_t)(uintptr_t)SV_LDS_PTR(tile_lds);
-    uint32_t a_addr[4], b_addr[4];
-    auto set_buf = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) a_addr[j] = lds0 + buf * FILL + a_off[j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b_addr[i] = lds0 + buf * FILL + b_off[i];
+    // The products of set SET, one read of the given slice into the other set after each; with `base` the loads of the
+    // fill NB ahead before the last two (only where every wave loads the same: a branch must not come between).
+    auto multiply = [&](auto set, auto next, auto loads, unsigned char* base) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set)::value, NR = RW + 2, NM = 2 * RW;
+        static_assert(NR <= NM + 1, "a read after each product");
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<NM>([&](auto mi) __attribute__((always_inline)) {
+            constexpr int m = decltype(mi)::value, i = m & 1, j = m >> 1;
+            const bf16x8 wf = __builtin_bit_cast(bf16x8, b[SET][i]), af = __builtin_bit_cast(bf16x8, a[SET][j]);
+            // gated form: weights first, so that a lane holds one row and consecutive features; plain form: activations
+            // first, so that a lane holds one feature and a half wave writes 128 contiguous bytes
+            acc[i][j] = GLU ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af, acc[i][j], 0, 0, 0)
+                            : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, wf, acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int first = m < NR ? m : NR, last = m + 1 == NM ? NR : m + 1 < NR ? m + 1 : NR;
+            static_for<last - first>([&](auto r) __attribute__((always_inline)) {
+                read(std::integral_constant<int, 1 - SET>{}, std::integral_constant<int, first + decltype(r)::value>{}, next);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if (decltype(loads)::value && RW == 4 && m == NM - 2) { request(base); __builtin_amdgcn_sched_barrier(0); }
+        });
     };
-#define SV_FENCE __builtin_amdgcn_sched_barrier(0)
-#define SV_RA(SET, J, S) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(af[SET][J]) : "v"(a_addr[J]), "n"((S) * 1024))
-#define SV_RB(SET, I, S) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(wf[SET][I]) : "v"(b_addr[I]), "n"((S) * 4096))
-    // gated form: weights first, so that a lane holds one row and consecutive features; plain form: activations first,
-    // so that a lane holds one feature and a half wave writes 128 contiguous bytes
-#define SV_MF(SET, I, J)                                                                                              \
-    acc[I][J] = GLU ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[SET][I]),                 \
-                                                              __builtin_bit_cast(bf16x8, af[SET][J]), acc[I][J], 0, 0, 0) \
-                    : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[SET][J]),                 \
-                                                              __builtin_bit_cast(bf16x8, wf[SET][I]), acc[I][J], 0, 0, 0)
-    // the products of one slice (operands in SET), the reads of slice S into the other set woven into the first half
-#define SV_SLICE_HEAD(SET, S)                                                                                         \
-    SV_FENCE; SV_MF(SET, 0, 0); SV_MF(SET, 0, 1); SV_FENCE; SV_RA(1 - SET, 0, S); SV_RA(1 - SET, 1, S); SV_FENCE;     \
-    SV_MF(SET, 0, 2); SV_MF(SET, 0, 3); SV_FENCE; SV_RA(1 - SET, 2, S); SV_RA(1 - SET, 3, S); SV_FENCE;               \
-    SV_MF(SET, 1, 0); SV_MF(SET, 1, 1); SV_FENCE; SV_RB(1 - SET, 0, S); SV_FENCE;                                     \
-    SV_MF(SET, 1, 2); SV_MF(SET, 1, 3); SV_FENCE; SV_RB(1 - SET, 1, S); SV_FENCE
-#define SV_SLICE_TAIL(SET, S)                                                                                         \
-    SV_MF(SET, 2, 0); SV_MF(SET, 2, 1); SV_FENCE; SV_RB(1 - SET, 2, S); SV_FENCE;                                     \
-    SV_MF(SET, 2, 2); SV_MF(SET, 2, 3); SV_FENCE; SV_RB(1 - SET, 3, S); SV_FENCE;                                     \
-    SV_MF(SET, 3, 0); SV_MF(SET, 3, 1); SV_MF(SET, 3, 2); SV_MF(SET, 3, 3); SV_FENCE
 
-    issue_fill(0, 0);
-    issue_fill(nfill > 1 ? 1 : 0, 1);
-    wait_vmcnt<LPF>();                                    // the first fill has landed (loads return in order)
+    const std::integral_constant<int, 0> i0;
+    const std::integral_constant<int, 1> i1;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) { request(tall_lds + i * FILL); advance(); }
+    wait_fills(std::integral_constant<int, NB - 1>{});
     __builtin_amdgcn_s_barrier();
-    set_buf(0);
-    SV_RA(0, 0, 0); SV_RA(0, 1, 0); SV_RA(0, 2, 0); SV_RA(0, 3, 0);
-    SV_RB(0, 0, 0); SV_RB(0, 1, 0); SV_RB(0, 2, 0); SV_RB(0, 3, 0);
-    for (int fill = 0; fill < nfill; ++fill) {
-        const int buf = fill & 1;
-        wait_lgkmcnt0();
-        SV_SLICE_HEAD(0, 1); SV_SLICE_TAIL(0, 1);
-        wait_lgkmcnt0();
-        SV_SLICE_HEAD(1, 2); SV_SLICE_TAIL(1, 2);
-        wait_lgkmcnt0();
-        SV_SLICE_HEAD(0, 3); SV_SLICE_TAIL(0, 3);
-        // This wave holds everything it needs of the buffer; its share of the next fill has landed; after the barrier
-        // so has everyone's, and nobody reads this buffer any more.
-        wait_lgkmcnt0();
-        wait_vmcnt<0>();
+    static_for<RW + 2>([&](auto r) __attribute__((always_inline)) { read(i0, r, i0); });
+    wait_set(i0);
+    int slot = 0;
+    for (int f = 0; f < nfill; ++f) {
+        multiply(i0, i1, std::false_type{}, tall_lds);
+        wait_set(i1);
+        // This wave holds all it needs of the fill and its share of the next one has landed; after the barrier so has
+        // everyone's, and nobody reads this fill's place in the ring any more.
+        wait_fills(std::integral_constant<int, NB - 2>{});
         __builtin_amdgcn_s_barrier();
-        set_buf(buf ^ 1);
-        // last slice: the first slice of the next fill is read, and the fill after next (past the end: the last one
-        // again, so that the loop has no branch) is requested into the buffer just given up
-        SV_SLICE_HEAD(1, 0);
-        {
-            const int ahead = fill + 2 < nfill ? fill + 2 : nfill - 1;
-            unsigned char* base = tile_lds + buf * FILL;
-            SV_MF(1, 2, 0); SV_MF(1, 2, 1); SV_FENCE; SV_RB(0, 2, 0); SV_FENCE;
-            dma4(a_src[0] + (int64_t)ahead * (KA * 1024), SV_LDS_PTR(base + a_dst[0])); SV_FENCE;
-            SV_MF(1, 2, 2); SV_MF(1, 2, 3); SV_FENCE; SV_RB(0, 3, 0); SV_FENCE;
-            dma4(a_src[1] + (int64_t)ahead * (KA * 1024), SV_LDS_PTR(base + a_dst[1])); SV_FENCE;
-            SV_MF(1, 3, 0); SV_MF(1, 3, 1); SV_FENCE;
-            dma4(w_src[0] + (int64_t)ahead * (KA * 4096), SV_LDS_PTR(base + w_dst[0])); SV_FENCE;
-            SV_MF(1, 3, 2); SV_MF(1, 3, 3); SV_FENCE;
-            dma4(w_src[1] + (int64_t)ahead * (KA * 4096), SV_LDS_PTR(base + w_dst[1])); SV_FENCE;
-        }
+        unsigned char* base = tall_lds + slot * FILL;
+        slot = slot + 1 == NB ? 0 : slot + 1;
+        a_addr = a_off + slot * FILL;
+        b_addr = b_off + slot * FILL;
+        multiply(i1, i0, std::true_type{}, base);
+        wait_set(i0);
+        if (RW != 4) request(base);
+        advance();
     }
-    wait_lgkmcnt0();
-#undef SV_FENCE
-#undef SV_RA
-#undef SV_RB
-#undef SV_MF
-#undef SV_SLICE_HEAD
-#undef SV_SLICE_TAIL
     wait_vmcnt<0>();                                      // nothing of this work-group may land in LDS after it has gone
 
     if (GLU) {
         const int F = N / 2;
         bf16_t* act = reinterpret_cast<bf16_t*>(out);
+        const int fs = (tn * 128 + wn * 32) / 16;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int fs = (tn * 128 + (2 * wn + i) * 32) / 16;
+        for (int j = 0; j < RW; ++j) {
+            const int mt = m0 / 32 + wm * RW + j;
+            if (mt < m_tiles) {
+                bf16_t* dst = act + ((int64_t)mt * (F / 16) + fs) * 512;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int mt = m0 / 32 + wm * 4 + j;
-                if (mt < m_tiles_total) {
-                    bf16_t* dst = act + ((int64_t)mt * (F / 16) + fs) * 512;
+                for (int q = 0; q < 4; ++q) {
+                    float r[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float r[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float g = acc[i][j][4 * q + e];
-                            r[e] = g / (1.0f + expf(-g)) * acc[2 + i][j][4 * q + e];
-                        }
-                        u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
-                        *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
+                    for (int e = 0; e < 4; ++e) {
+                        const float g = acc[0][j][4 * q + e];
+                        r[e] = g / (1.0f + expf(-g)) * acc[1][j][4 * q + e];
                     }
+                    u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
+                    *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
                 }
             }
         }
         return;
     }
-    // acc[i][j][4 q + r] <-> row m0 + 32 (4 wm + j) + 8 q + 4 lg + r, feature 256 tn + 32 (4 wn + i) + l32
+    // acc[i][j][4 q + r] <-> row m0 + 32 (RW wm + j) + 8 q + 4 lg + r, feature 256 tn + 64 wn + 32 i + l32
+    if (tn * 256 + wn * 64 >= N) return;
     float* dst = out + (int64_t)sp * M * N;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int n = tn * 256 + (wn * 4 + i) * 32 + l32;
+    for (int i = 0; i < 2; ++i) {
+        const int n = tn * 256 + wn * 64 + i * 32 + l32;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < RW; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int m = m0 + (wm * 4 + j) * 32 + 8 * q + 4 * lg + r;
+                    const int m = m0 + (wm * RW + j) * 32 + 8 * q + 4 * lg + r;
                     if (m < M) dst[(int64_t)m * N + n] = acc[i][j][4 * q + r];
                 }
     }
 }
 
-// plain: out [splits][M][N] fp32, N % 256 == 0.  gated: N = 2 F weight rows, out = packed bf16 [ceil(M/32)*32, F],
-// F % 128 == 0, splits == 1.  (K / splits) % 64 == 0.
-hipError_t gemm_bf16_tile(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, hipStream_t st) {
-    if (splits < 1 || K % splits != 0 || (K / splits) % 64 != 0 || N % 256 != 0 || (glu && splits != 1))
+// tiles_m tiles of 64 RW rows along the rows, then (RWT > 0) one of 64 RWT; tail_last: the short ones behind all others.
+template <bool GLU, int RW, int RWT>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_tall_kernel(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp,
+                                                                float* __restrict__ out, int M, int N, int K, int k_per_split, int splits,
+                                                                int tiles_m, int tiles_n, int tail_last) {
+    const int n_main = tiles_m * tiles_n * splits;
+    int tm, logical;
+    if (RWT > 0 && tail_last && (int)blockIdx.x >= n_main) {
+        logical = xcd_remap(blockIdx.x - n_main, tiles_n * splits);
+        tm = tiles_m;
+    } else {
+        const int along = tiles_m + (RWT > 0 && !tail_last ? 1 : 0);
+        logical = xcd_remap(blockIdx.x, along * tiles_n * splits);
+        tm = logical % along;
+        logical /= along;
+    }
+    const int sp = logical % splits, tn = logical / splits;
+    if (RWT == 0 || tm < tiles_m) gemm_bf16_tall_body<GLU, RW>(Ap, Wp, out, M, N, K, k_per_split, tm * 64 * RW, tn, sp);
+    else gemm_bf16_tall_body<GLU, RWT == 0 ? RW : RWT>(Ap, Wp, out, M, N, K, k_per_split, tm * 64 * RW, tn, sp);
+}
+
+// Microseconds a launch of the tall kernel takes, by the same kind of play-through as the weight-streaming plan (fitted to 900
+// launches of 17 row counts from 128 to 3500, three shapes and four split counts; half of the estimates lie below 0.97 of the
+// measured time, nine in ten between 0.77 and 1.05).
+// A tile costs its slices at the pace of a CU alone; the chip as a whole sustains kRate; whole rounds take the
+// larger of the two (rounded over the corner), a last round that is not full is hidden in part where there are several;
+// the weight stream adds to both, as it draws on the same power.
+double gemm_bf16_tall_us(int M, int N, int K, int splits, int rw) {
+    static const double kSlice[6] = {0, 0.130, 0.165, 0.208, 0.245, 0.327};            // us per slice of a lone tile of 64 rw rows
+    static const double kRate[6] = {1, 0.70e9, 1.00e9, 1.15e9, 1.25e9, 1.25e9};        // flop per us over the chip
+    const int need = (M + 63) / 64;
+    if (need < rw) rw = need < 3 ? 3 : need;
+    const int q = std::max(1, need / rw), rt = need > rw ? need % rw : 0;
+    const double slices = (double)K / 16 / splits, wgs = (double)((N + 255) / 256) * splits;
+    auto alone = [&](int r) { return kSlice[r] * slices + 4.0; };
+    auto share = [&](int r) { return 2.0 * 64 * r * 256 * 16 * slices / kRate[r]; };
+    auto corner = [](double x, double y) { return std::sqrt(std::sqrt(x * x * x * x + y * y * y * y)); };
+    const double n1 = q * wgs, n2 = rt ? wgs : 0, d1 = alone(rw), p1 = share(rw), d2 = rt ? alone(rt) : 0, p2 = rt ? share(rt) : 0;
+    const double rounds = std::floor(n1 / 256), rem = n1 - 256 * rounds;
+    double t = rounds > 0 ? rounds * corner(d1, 256 * p1) : 0;
+    const double power = rem * p1 + n2 * p2;
+    if (rounds >= 2) {
+        if (rem > 0 || n2 > 0) t += std::max(0.5 * d1, power);
+    } else {
+        const double beside = rem > 0 && n2 > 0 ? (256 - rem) * std::floor(d1 / d2) : 0;    // short tiles that run beside the tall ones
+        const double d = (rem > 0 ? d1 : 0) + std::ceil(std::max(0.0, n2 - beside) / 256) * d2;
+        if (d > 0) t += corner(d, power);
+    }
+    const double stream = (double)N * K * 2.0 / 5.5e6;
+    return std::sqrt(t * t + stream * stream) + (splits - 1) * (double)M * N * 4.0 / 4.0e6 + 2.3;             // the consumer reads the planes
+}
+
+// Rows per tile (in 64s) and splits for the tall kernel: the best by the estimate.
+TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits) {
+    TallPlan best{1, 4, 1e30};
+    const int need = (M + 63) / 64;
+    for (int rw = 3; rw <= 5 && (rw == 3 || rw <= need); ++rw)
+        for (int s = 1; s <= max_splits; ++s) {
+            if ((K / 16) % (kTallSlices * s) != 0) continue;
+            const double t = gemm_bf16_tall_us(M, N, K, s, rw);
+            if (t < best.us) best = TallPlan{s, rw, t};
+        }
+    return best;
+}
+
+// plain: out [splits][M][N] fp32, N % 128 == 0.  gated: N = 2 F weight rows, out = packed bf16 [ceil(M/32)*32, F],
+// F % 128 == 0, splits == 1.  (K / splits) % 32 == 0.  rw: 3 to 5, tiles of 64 rw rows.
+hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, int rw, hipStream_t st) {
+    if (splits < 1 || K % splits != 0 || (K / splits) % (16 * kTallSlices) != 0 || N % (glu ? 256 : 128) != 0 || (glu && splits != 1) ||
+        rw < 3 || rw > 5)
         return hipErrorInvalidValue;
-    const int tiles_m = (M + 255) / 256, tiles_n = glu ? N / 2 / 128 : N / 256;
+    const int need = (M + 63) / 64;
+    if (need < rw) rw = need < 3 ? 3 : need;              // rows beyond M read as the last tile
+    const int q = std::max(1, need / rw), rt = need > rw ? need % rw : 0;
+    const int tiles_n = (N + 255) / 256, blocks = (q + (rt ? 1 : 0)) * tiles_n * splits;
+    const int tail_last = q * tiles_n * splits < 2 * 256;
     auto launch = [&](auto kern) -> hipError_t {
-        const size_t lds = 2 * 4 * 16 * 1024;             // two fills of four slices
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const int lds = kTallFills * kTallSlices * (2 * rw + 8) * 1024;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(256), lds, st, Ap, Wp, out, M, N, K, K / splits, splits,
-                           tiles_m, tiles_n);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(512), lds, st, Ap, Wp, out, M, N, K, K / splits, splits, q, tiles_n, tail_last);
         return hipGetLastError();
     };
-    return glu ? launch(gemm_bf16_tile_kernel<true>) : launch(gemm_bf16_tile_kernel<false>);
+    auto form = [&](auto g) -> hipError_t {
+        constexpr bool G = decltype(g)::value;
+        switch (rw * 8 + rt) {
+            case 24: return launch(gemm_bf16_tall_kernel<G, 3, 0>);
+            case 25: return launch(gemm_bf16_tall_kernel<G, 3, 1>);
+            case 26: return launch(gemm_bf16_tall_kernel<G, 3, 2>);
+            case 32: return launch(gemm_bf16_tall_kernel<G, 4, 0>);
+            case 33: return launch(gemm_bf16_tall_kernel<G, 4, 1>);
+            case 34: return launch(gemm_bf16_tall_kernel<G, 4, 2>);
+            case 35: return launch(gemm_bf16_tall_kernel<G, 4, 3>);
+            case 40: return launch(gemm_bf16_tall_kernel<G, 5, 0>);
+            case 41: return launch(gemm_bf16_tall_kernel<G, 5, 1>);
+            case 42: return launch(gemm_bf16_tall_kernel<G, 5, 2>);
+            case 43: return launch(gemm_bf16_tall_kernel<G, 5, 3>);
+            default: return launch(gemm_bf16_tall_kernel<G, 5, 4>);
+        }
+    };
+    return glu ? form(std::true_type{}) : form(std::false_type{});
 }
 
 // Activations [M, K] row-major -> packed [ceil(M/32)][K/16][64 lanes][8]: lane 32*g + r of a fragment holds
@@ -643,16 +706,9 @@ static hipError_t launch_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int 
 
 // Gate/up projection fused with SwiGLU: Wp packed [2F, K] (gate rows, then up rows); act_out packed
 // [ceil(M/32)*32, F] bf16.  F a multiple of 64.
-hipError_t gemm_bf16_ws_glu(const bf16_t* Ap, const bf16_t* Wp, bf16_t* act_out, int M, int F, int K, hipStream_t st, int tile_mode) {
+hipError_t gemm_bf16_ws_glu(const bf16_t* Ap, const bf16_t* Wp, bf16_t* act_out, int M, int F, int K, hipStream_t st) {
     if (F % 64 != 0 || K % 64 != 0) return hipErrorInvalidValue;
     float* out = reinterpret_cast<float*>(act_out);
-    if (F % 128 == 0 && tile_mode != 0) {
-        // From a thousand rows on the 256-row tiles win where their launch fills its rounds about as well as the
-        // 160-row one does: rounds x rows per work-group / the rate a CU reaches with either (TFLOP/s, measured).
-        const long long n_ws = (long long)((M + 159) / 160) * (F / 128), n_tile = (long long)((M + 255) / 256) * (F / 128);
-        const double t_ws = (double)((n_ws + 255) / 256) * 160.0 / 4.47, t_tile = (double)((n_tile + 255) / 256) * 256.0 / kTileRateGlu;
-        if (tile_mode == 1 || (M >= 1024 && t_tile < 0.97 * t_ws)) return gemm_bf16_tile(Ap, Wp, out, M, 2 * F, K, 1, true, st);
-    }
     if (F % 128 == 0 && K % 128 == 0) {
         // 128-feature strips, gate and up in one wave.  One work-group per CU: the launch runs in rounds of 256,
         // and a last round that is less than half full would leave most CUs idle for a whole work-group's time.
@@ -705,7 +761,7 @@ int gemm_bf16_ws_row_tiles(int M) {
 
 hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool wide,
                         hipStream_t st, int row_tiles) {
-    if (row_tiles == 8) return gemm_bf16_tile(Ap, Wp, out, M, N, K, splits, false, st);
+    if (row_tiles >= 6) return gemm_bf16_tall(Ap, Wp, out, M, N, K, splits, false, row_tiles / 2, st);
     const bool long_fill = (K / splits) % 128 == 0;
     const int mt = row_tiles >= 1 && row_tiles <= 5 ? row_tiles : gemm_bf16_ws_row_tiles(M);
     if (!long_fill) {        // short fills (small models; many splits of a deep reduction at a few rows): narrow strips of

@@ -1,0 +1,64 @@
+"""The tall projection kernel: every combination of tall and short row tiles, strips beyond the output's width, reductions
+shorter than its ring, against float64 products and against the weight-streaming kernel inside a step."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import model as M
+from harness import LOGIT_TOL
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def bf16(shape, std, seed):
+    return (torch.randn(shape, generator=torch.Generator().manual_seed(seed)) * std).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("rows", [1, 64, 193, 257, 385, 512, 961])
+@pytest.mark.parametrize("K,splits", [(64, 1), (192, 3), (1024, 2)])
+def test_whole_and_short_row_tiles_match_float64_product(rows, K, splits):
+    """Tolerance as in the other projection tests: fp32 sums of K <= 1024 products of magnitude 0.02."""
+    from paper_2511_16193_amd import op_gemm_bf16_ws, op_pack_rows, op_pack_weight
+    a, w = bf16((rows, K), 1.0, rows), bf16((512, K), 0.02, K)
+    want = M.matmul_wt(a.float().numpy().astype(np.float64), w.float().numpy())
+    got = op_gemm_bf16_ws(op_pack_rows(a.to(DEV)), op_pack_weight(w.to(DEV)), rows, splits=splits, wide=True, row_tiles=8)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(got.cpu().numpy().astype(np.float64).sum(axis=0) - want)) < 1e-4
+
+
+@pytest.mark.parametrize("rows", [129, 161, 225, 321, 385, 450, 650, 865, 897, 1025, 1601, 1665])
+def test_step_equals_the_weight_streaming_kernel(rows):
+    """One decoding step of `rows` requests with the launch plan's own tiles (192, 256 and 320 rows with every remainder: the
+    gated gate/up form, an LM head of 297 strips, the narrow projections), against the same step without the tall kernel.
+    One layer: two correct implementations stay within the tolerance of the step tests."""
+    import paper_2511_16193_amd as P
+    d, ff, V = 256, 18944, 38016
+    lw = {"ln1": bf16((d,), 0.05, 1) + 1, "wqkv": bf16((512, d), 0.02, 2), "wo": bf16((d, 256), 0.02, 3),
+          "ln2": bf16((d,), 0.05, 4) + 1, "w_gate_up": bf16((2 * ff, d), 0.02, 5), "w_down": bf16((d, ff), 0.02, 6)}
+    lw = {n: P.op_pack_weight(t.to(DEV)) if t.dim() == 2 else t.to(DEV) for n, t in lw.items()}
+    w = {"embed": bf16((V, d), 0.5, 7).to(DEV), "lm_head": P.op_pack_weight(bf16((V, d), 0.02, 8).to(DEV)),
+         "final_norm": (bf16((d,), 0.05, 9) + 1).to(DEV), "layers": [lw]}
+    model = dict(n_layers=1, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=ff, vocab=V, n_experts=0, top_k=0,
+                 d_expert=0, dtype="bf16", rope_theta=1.0e4, rms_eps=1.0e-6)
+    ver = P.Verifier(model, w, packed=True, max_batch=rows, max_k=1, max_chains=1, max_seqs=rows, page_size=32, num_pages=rows + 4,
+                     max_pages_per_seq=2, verify_mode=P.SV_MATCH, sample_mode=P.SV_EXP_RACE, temperature=1.0, device=DEV)
+    ids = list(range(rows))
+    kv = bf16((2, 7, 1, 128), 1.0, 10).to(DEV)
+    for b in ids:
+        ver.seq_add(b, 7)
+        ver.kv_write(b, 0, 0, kv[0], kv[1])
+    x0 = torch.arange(rows, dtype=torch.int32, device=DEV) * 19 % V
+    u = torch.rand((rows, 1, 1), generator=torch.Generator().manual_seed(11)).to(DEV)
+    logits = []
+    for mode in (0, -1):
+        ver.set_option(P.SV_OPT_GEMM_TILE, mode)
+        ver.seq_set_lens(ids, [7] * rows)
+        out = {"accepted_len": torch.zeros(rows, dtype=torch.int32, device=DEV), "out_tokens": torch.zeros((rows, 1), dtype=torch.int32, device=DEV),
+               "best_chain": torch.zeros(rows, dtype=torch.int32, device=DEV), "logits": torch.full((rows, 1, V), float("nan"), device=DEV)}
+        ver.step(ids, x0, None, None, u, out=out)
+        torch.cuda.synchronize()
+        logits.append(out["logits"])
+    assert float((logits[0] - logits[1]).abs().max()) < LOGIT_TOL["bf16"]
+    assert float(logits[0].std()) > 0.1
+    ver.close()
