@@ -123,6 +123,15 @@ __device__ __forceinline__ void dma2(const char* src, __attribute__((address_spa
     __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 1024, 0);
 }
 
+// 16 bytes per lane from base + lane_off + off, off the same for all lanes, through a buffer descriptor over [base, base + bytes):
+// beyond it nothing is read and zeros return.  base: the same for all lanes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t d, uint32_t lane_off, uint32_t off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(d, lane_off, off, 0));
+}
+
 // f(std::integral_constant<int, 0>{}), ... , f(std::integral_constant<int, N - 1>{}): a loop whose index is a constant expression
 template <typename F, int... I> __device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, I>{}), ...);
@@ -138,6 +147,18 @@ template <typename T> __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
+}
+
+// Largest of 64 lanes' unsigned values, in all lanes: six DPP steps (within rows of 16 lanes, then across rows) and a read of
+// lane 63, no LDS-crossbar latency on the way.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));            // row_shr:1
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));            // row_shr:2
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));            // row_shr:4
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));            // row_shr:8
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));      // row_bcast:15
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));      // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 }  // namespace sv

@@ -23,15 +23,18 @@ typedef __attribute__((ext_vector_type(16))) float floatx16;
 // first operand straight from the row-major router matrix, the activation fragment straight from the packed
 // activations (1 KB contiguous), four slices of loads in flight ahead of the products.  The waves' partial
 // logits meet in LDS and leave as one plane [part][row][expert] in global memory.
+// A single tile of rows makes KQ work-groups, which is few for a cold router matrix: there every wave is a work-group
+// of its own and leaves its own plane, which the choice adds up in the order in which LDS would have (20 rows: 11.9 -> 5.4 us).
 constexpr int kRouterRows = 32;
 
 template <int ET>
-__global__ __launch_bounds__(256) void moe_logits_kernel(MoeArgs a, int KQ) {
+__global__ __launch_bounds__(256) void moe_logits_kernel(MoeArgs a, int KQ, int wave_planes) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     float* logit = reinterpret_cast<float*>(smem);           // [4 waves][32][E + 1]
     const int pitch = a.E + 1, plane = kRouterRows * pitch;
-    const int tile = blockIdx.x, kq = blockIdx.y;            // 32-row tile of the packed activations, part of the reduction
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // 32-row tile of the packed activations, part of the reduction; wave_planes: work-groups of one wave, a quarter part each
+    const int tile = blockIdx.x, kq = wave_planes ? blockIdx.y >> 2 : blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = wave_planes ? blockIdx.y & 3 : threadIdx.x >> 6;
     const int l32 = lane & 31, lg = lane >> 5;
     const int kslices = a.d / 16, nks = kslices / (4 * KQ), ks0 = (kq * 4 + wave) * nks;
     const bf16_t* a_src = a.a + ((int64_t)tile * kslices + ks0) * 512 + lane * 8;
@@ -76,6 +79,17 @@ __global__ __launch_bounds__(256) void moe_logits_kernel(MoeArgs a, int KQ) {
         __builtin_amdgcn_sched_barrier(0);
     }
     // acc[et][4 q + i] <-> expert et*32 + 8 q + 4 lg + i, row l32
+    if (wave_planes) {
+        if (tile * 32 + l32 < a.T) {
+            float* dst = a.router_logits + ((int64_t)blockIdx.y * a.T + tile * 32 + l32) * a.E + 4 * lg;
+#pragma unroll
+            for (int et = 0; et < ET; ++et)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<floatx4*>(dst + et * 32 + 8 * q) = floatx4{acc[et][4 * q], acc[et][4 * q + 1], acc[et][4 * q + 2], acc[et][4 * q + 3]};
+        }
+        return;
+    }
 #pragma unroll
     for (int et = 0; et < ET; ++et)
 #pragma unroll
@@ -91,60 +105,131 @@ __global__ __launch_bounds__(256) void moe_logits_kernel(MoeArgs a, int KQ) {
     }
 }
 
-// One wave per row: the KQ planes are added in order, softmax over the experts, top_k by repeated arg-max
-// (lowest id among equals), renormalisation.
-__global__ __launch_bounds__(256) void moe_select_kernel(MoeArgs a, int KQ) {
-    const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= a.T) return;
+// Router choice of one row by one wave: the planes are added in order (four in flight together; one plane per part, or
+// with QUADS four, of the part's waves), softmax over
+// the experts, top_k by repeated arg-max (lowest id among equals), renormalisation.  Lane j < top_k returns choice j.  The
+// arg-max runs on the probabilities' bit patterns (ordered like the numbers; 0 = taken) by DPP: through shuffles
+// its sixteen reductions were near half of the time (640 rows: 9.7 -> 5.8 us).
+template <bool QUADS>
+__device__ __forceinline__ void route_row(const MoeArgs& a, int planes, int t, int lane, int& id, float& weight) {
     constexpr int PER = 4;                                   // experts per lane: E <= 256
-    float v[PER];
+    float x[PER] = {0.f, 0.f, 0.f, 0.f};
+    for (int kq0 = 0; kq0 < planes; kq0 += 4) {
+        float part[4][PER];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                part[u][i] = kq0 + u < planes && lane + 64 * i < a.E ? a.router_logits[((int64_t)(kq0 + u) * a.T + t) * a.E + lane + 64 * i] : 0.f;
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (QUADS) x[i] += (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
+            else for (int u = 0; u < 4; ++u) x[i] += part[u][i];
+    }
     float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int e = lane + 64 * i;
-        float x = -INFINITY;
-        if (e < a.E) {
-            x = 0.f;
-            for (int kq = 0; kq < KQ; ++kq) x += a.router_logits[((int64_t)kq * a.T + t) * a.E + e];
-        }
-        v[i] = x;
-        mx = fmaxf(mx, x);
-    }
+    for (int i = 0; i < PER; ++i) mx = lane + 64 * i < a.E ? fmaxf(mx, x[i]) : mx;
     mx = wave_max(mx);
     float sum = 0.f;
+    uint32_t key[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        v[i] = lane + 64 * i < a.E ? expf(v[i] - mx) : -1.f;  // -1 marks "not a candidate"
-        sum += v[i] > 0.f ? v[i] : 0.f;
+        const float p = lane + 64 * i < a.E ? expf(x[i] - mx) : 0.f;
+        sum += p > 0.f ? p : 0.f;
+        key[i] = lane + 64 * i < a.E ? min(__float_as_uint(p), 0xfffffffeu) + 1 : 0;
     }
     sum = wave_sum(sum);
     float kept_sum = 0.f, mine = 0.f;
     int mine_id = 0;
     for (int j = 0; j < a.top_k; ++j) {
-        float best = -1.f;
-        int best_e = 1 << 20;
+        uint32_t best = key[0];
+        int best_e = lane;
+#pragma unroll
+        for (int i = 1; i < PER; ++i)
+            if (key[i] > best) { best = key[i]; best_e = lane + 64 * i; }    // ascending ids: the first maximum is kept
+        const uint32_t top = wave_max_u32(best);
+        const int win = 255 - (int)wave_max_u32(best == top ? 255 - best_e : 0);      // lowest id among the equal maxima
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            if (v[i] > best) { best = v[i]; best_e = lane + 64 * i; }     // ascending ids: the first maximum is kept
-        const float top = wave_max(best);
-        const float cand = best == top ? -(float)best_e : -(float)(1 << 20);
-        int win = (int)(-wave_max(cand));                                   // lowest id among the equal maxima
-        if (win >= a.E) win = j;                                            // NaN inputs: still a valid expert id
-#pragma unroll
-        for (int i = 0; i < PER; ++i)
-            if (lane + 64 * i == win) v[i] = -1.f;
-        const float p = top / sum;
+            if (lane + 64 * i == win) key[i] = 0;
+        const float p = __uint_as_float(top - 1) / sum;
         kept_sum += p;
         if (lane == j) { mine = p; mine_id = win; }
     }
+    id = mine_id;
+    weight = mine / kept_sum;
+}
+
+__global__ __launch_bounds__(256) void moe_select_kernel(MoeArgs a, int KQ) {
+    const int lane = threadIdx.x & 63;
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (t >= a.T) return;
+    int id;
+    float w;
+    route_row<false>(a, KQ, t, lane, id, w);
     if (lane < a.top_k) {
-        a.top_ids[(size_t)t * a.top_k + lane] = mine_id;
-        a.top_w[(size_t)t * a.top_k + lane] = mine / kept_sum;
+        a.top_ids[(size_t)t * a.top_k + lane] = id;
+        a.top_w[(size_t)t * a.top_k + lane] = w;
     }
 }
 
 // ------------------------------------------------------------------ grouping
+// First tile of every bucket: exclusive prefix sum of the buckets' tile counts, `mine` that of expert threadIdx.x (E <= 256:
+// four waves scan their 64 experts with lane shifts, then add the totals of the waves before them).  All threads call it.
+__device__ __forceinline__ void bucket_offsets(int mine, int32_t* offs, int E) {
+    __shared__ int wave_tot[4];
+    const int e = threadIdx.x, lane = e & 63;
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(incl, d);
+        if (lane >= d) incl += up;
+    }
+    if (e < 256 && lane == 63) wave_tot[e >> 6] = incl;
+    __syncthreads();
+    if (e < E) {
+        int base = 0;
+        for (int w = 0; w < (e >> 6); ++w) base += wave_tot[w];
+        offs[e] = base + incl - mine;
+        if (e == E - 1) offs[E] = base + incl;
+    }
+    __syncthreads();
+}
+
+// Up to 32 rows (one operand tile): choice and grouping in one work-group, two rows per wave.  Every expert that is
+// chosen at all gets one tile, in which a row stands where it stands in the activations: the products then read the
+// activations' own tile, and there is nothing to gather.  20 rows: choice, grouping and gather 8.9 + 4.7 + 6.1 us in three
+// launches, 11.6 in this one.
+template <bool QUADS>
+__global__ __launch_bounds__(1024) void moe_route_tile_kernel(MoeArgs a, int planes) {
+    __shared__ int32_t chosen[256], offs[257];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x < 256) chosen[threadIdx.x] = 0;
+    __syncthreads();
+    int id[2] = {0, 0};
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int t = wave + 16 * r;
+        if (t < a.T) {
+            float w;
+            route_row<QUADS>(a, planes, t, lane, id[r], w);
+            if (lane < a.top_k) {
+                chosen[id[r]] = 1;
+                a.top_ids[t * a.top_k + lane] = id[r];
+                a.top_w[t * a.top_k + lane] = w;
+            }
+        }
+    }
+    __syncthreads();
+    bucket_offsets(threadIdx.x < a.E ? chosen[threadIdx.x] : 0, offs, a.E);
+    if (threadIdx.x <= a.E) a.tile_off[threadIdx.x] = offs[threadIdx.x];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int t = wave + 16 * r;
+        if (t < a.T && lane < a.top_k) a.inv[t * a.top_k + lane] = offs[id[r]] * 32 + t;
+    }
+}
+
 // One work-group.  Every (row, expert) assignment sets bit `row` in its expert's bitmap (an OR: the result
 // does not depend on the order of the atomics); the rank of a row inside its expert's bucket is the number of
 // set bits below it.  Buckets are padded to whole 32-row tiles: bucket e owns padded rows
@@ -174,28 +259,7 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(MoeArgs a) {
         cnts[e] = run;
     }
     __syncthreads();
-    // first tile of every bucket: exclusive prefix sum of the buckets' tile counts (E <= 256: four waves scan
-    // their 64 experts with lane shifts, then add the totals of the waves before them)
-    {
-        __shared__ int wave_tot[4];
-        const int e = threadIdx.x, lane = e & 63;
-        const int mine = e < a.E ? (cnts[e] + 31) / 32 : 0;
-        int incl = mine;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int up = __shfl_up(incl, d);
-            if (lane >= d) incl += up;
-        }
-        if (e < 256 && lane == 63) wave_tot[e >> 6] = incl;
-        __syncthreads();
-        if (e < 256) {
-            int base = 0;
-            for (int w = 0; w < (e >> 6); ++w) base += wave_tot[w];
-            if (e < a.E) offs[e] = base + incl - mine;
-            if (e == a.E - 1) offs[a.E] = base + incl;
-        }
-    }
-    __syncthreads();
+    bucket_offsets(threadIdx.x < a.E ? (cnts[threadIdx.x] + 31) / 32 : 0, offs, a.E);
     for (int e = threadIdx.x; e <= a.E; e += 1024) {
         a.tile_off[e] = offs[e];
         if (e < a.E) {
@@ -237,17 +301,157 @@ __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
 }
 
 // ------------------------------------------------------------------ expert products
-// MODE 0: rows = the gathered tiles; waves 0,1 produce 64 gate features, waves 2,3 the 64 up
-//         features of the same indices; the epilogue forms silu(gate) * up and writes it, rounded to bf16, as
-//         packed MFMA operand tiles for MODE 1.
+// MODE 0: rows = the gathered tiles (up to 32 rows: the activations' only tile); waves 0,1 produce 64 gate features,
+//         waves 2,3 the 64 up features of the same indices; the epilogue forms silu(gate) * up and writes it, rounded to
+//         bf16, as packed MFMA operand tiles for MODE 1.
 // MODE 1: rows = those tiles; four waves produce 128 output features; fp32 results go to y[padded row][d].
-// A work-group handles the expert's row tiles four at a time (re-streaming its weight strip for experts with
-// more than 128 rows).  Products of row tiles beyond the bucket are skipped.
-template <int MODE>
-__global__ __launch_bounds__(256, 2) void moe_gemm_kernel(MoeArgs a) {
-    constexpr int MT = 4, KA = 8, PD = 8;
-    __shared__ __attribute__((aligned(16))) unsigned char abuf[2][MT * KA * 1024];
+// A work-group handles the expert's row tiles MTMAX at a time (re-streaming its weight strip for experts with more).  Most
+// experts hold one or two tiles, and what a group of MT tiles costs beside the weights grows with MT: a fill copies
+// MT x 8 KB through L2, LDS and registers, as much as the weights themselves at MT = 4.  So the loop exists for one, two
+// and four tiles, and the launch takes the smallest MTMAX that holds an ordinary expert, with as many work-groups per CU as
+// its registers and LDS leave room for.  128 experts of 3 x 2048 x 768, against four tiles throughout: 640 rows (two tiles an
+// expert) 171.9 + 88.8 -> 160.5 + 85.6 us, 20 rows (one) 129.7 + 65.7 -> 118.1 + 63.9 (4.9 TB/s of weights; a plain
+// stream reaches 6.0).  Sixteen weight fragments in flight instead of eight, where one tile leaves registers for them, 2 %;
+// with two tiles they cost the fourth work-group and gain nothing.
+constexpr int kMoeSlices = 8;                               // 16-wide slices per fill
+
+template <int MODE, int MT>
+__device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf, const char* w_base, int p, int tile, int nt_here, bool one_tile) {
+    constexpr int KA = kMoeSlices, PD = (MT == 1 ? 2 : 1) * kMoeSlices, APW = MT * KA / 4;
     const int K = MODE == 0 ? a.d : a.F;                    // reduction width
+    const int kslices = K / 16, nfill = kslices / KA;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lg = lane >> 5;
+
+    // this wave's share of a fill: APW slices of row tile wave * MT / 4; tiles past the bucket repeat its last
+    const int my = wave * MT / 4, ks_mine = (wave * APW) % KA;
+    const bf16_t* rows = MODE == 1 ? a.act : one_tile ? a.a : reinterpret_cast<const bf16_t*>(a.y);
+    // Both streams are read through buffer descriptors: a slice is a scalar offset, so that the ring needs no lane addresses
+    // (sixteen of them spilled), and a slice past the end is out of the descriptor's range: no memory access, zeros.
+    const char* a_base = reinterpret_cast<const char*>(rows + ((int64_t)(MODE == 0 && one_tile ? 0 : tile + (my < nt_here ? my : nt_here - 1)) * kslices + ks_mine) * 512);
+    const auto a_desc = buffer_of(a_base, (kslices - ks_mine) * 1024), w_desc = buffer_of(w_base, (kslices - 1) * 4096 + 1024);
+    auto load_a = [&](int slice) __attribute__((always_inline)) { return buffer_load16(a_desc, lane * 16, slice * 1024); };
+    auto load_w = [&](int slice) __attribute__((always_inline)) { return buffer_load16(w_desc, lane * 16, slice * 4096); };
+    unsigned char* a_dst = abuf + (wave * APW) * 1024 + lane * 16;
+    constexpr int BUF = MT * KA * 1024;
+
+    floatx16 acc[MT];
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
+
+    u32x4 wring[PD];
+    // The rows of a fill are requested two fills ahead: loads return in order, so what is waited for at the end of a fill
+    // must be older than the weights that are to stay in flight.
+    u32x4 areg[2][APW];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int i = 0; i < APW; ++i) areg[f][i] = load_a(f * KA + i);
+#pragma unroll
+    for (int s = 0; s < PD; ++s) wring[s] = load_w(s);
+#pragma unroll
+    for (int i = 0; i < APW; ++i) *reinterpret_cast<u32x4*>(a_dst + i * 1024) = areg[0][i];
+
+    // a fill from LDS buffer (MT = 1: and ring half) H = fill % 2
+    auto do_fill = [&](int fill, auto half) __attribute__((always_inline)) {
+        constexpr int H = decltype(half)::value;
+        __builtin_amdgcn_s_waitcnt(0xC07F);                 // own LDS writes done
+        __builtin_amdgcn_s_barrier();
+#pragma unroll
+        for (int i = 0; i < APW; ++i) areg[H][i] = load_a((fill + 2) * KA + i);
+        const unsigned char* ab = abuf + H * BUF + lane * 16;
+        bf16x8 af[2][MT];
+#pragma unroll
+        for (int j = 0; j < MT; ++j) af[0][j] = *reinterpret_cast<const bf16x8*>(ab + (j * KA) * 1024);
+#pragma unroll
+        for (int s = 0; s < KA; ++s) {
+            const int slice = fill * KA + s;
+            if (s + 1 < KA) {
+#pragma unroll
+                for (int j = 0; j < MT; ++j)
+                    af[(s + 1) & 1][j] = *reinterpret_cast<const bf16x8*>(ab + (j * KA + s + 1) * 1024);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const bf16x8 wf = __builtin_bit_cast(bf16x8, wring[(H * KA + s) % PD]);
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+                if (MT < 4 || j < nt_here)    // MODE 1: rows first, so that a half wave stores 128 contiguous bytes of an output row
+                    acc[j] = MODE == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af[s & 1][j], acc[j], 0, 0, 0)
+                                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][j], wf, acc[j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            // refill the slot just consumed (after its readers, so the load lands in place)
+            wring[(H * KA + s) % PD] = load_w(slice + PD);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < APW; ++i) *reinterpret_cast<u32x4*>(a_dst + (1 - H) * BUF + i * 1024) = areg[1 - H][i];
+    };
+    for (int fill = 0; fill + 1 < nfill; fill += 2) {
+        do_fill(fill, std::integral_constant<int, 0>{});
+        do_fill(fill + 1, std::integral_constant<int, 1>{});
+    }
+    if (nfill & 1) do_fill(nfill - 1, std::integral_constant<int, 0>{});
+
+    if (MODE == 1) {
+#pragma unroll
+        for (int j = 0; j < MT; ++j) {
+            if (j < nt_here) {
+                // acc[j][4 q + r] <-> padded row 32 (tile + j) + 8 q + 4 lg + r, feature 128 p + 32 wave + l32
+                float* dst = a.y + ((int64_t)(tile + j) * 32 + 4 * lg) * a.d + p * 128 + wave * 32 + l32;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) dst[(int64_t)(8 * q + r) * a.d] = acc[j][4 * q + r];
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();                       // every wave is done with abuf before the next group refills it
+    } else {
+        // up halves travel through LDS to the waves that hold the gate halves of the same features
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();                       // all reads of abuf are over
+        float* xbuf = reinterpret_cast<float*>(abuf);       // [2 waves][MT][16][64] floats
+        if (wave >= 2) {
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) xbuf[(((wave - 2) * MT + j) * 16 + q) * 64 + lane] = acc[j][q];
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        if (wave < 2) {
+            const int fs = (p * 64 + wave * 32) / 16;       // first 16-wide feature slice of this wave
+#pragma unroll
+            for (int j = 0; j < MT; ++j) {
+                if (j < nt_here) {
+                    bf16_t* dst = a.act + ((int64_t)(tile + j) * (a.F / 16) + fs) * 512;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float r[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float g = acc[j][4 * q + i];
+                            const float u = xbuf[((wave * MT + j) * 16 + 4 * q + i) * 64 + lane];
+                            r[i] = g / (1.0f + expf(-g)) * u;
+                        }
+                        // features 8q + 4 lg .. +3 of this wave's 32: slice q/2, half q%2, elements 4 lg ..
+                        u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
+                        *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();                       // xbuf is read before the next group overwrites it
+    }
+}
+
+template <int MODE, int MTMAX>
+__global__ __launch_bounds__(256, MTMAX == 4 ? 2 : 4) void moe_gemm_kernel(MoeArgs a, int one_tile) {
+    __shared__ __attribute__((aligned(16))) unsigned char abuf[2 * MTMAX * kMoeSlices * 1024];
     const int Ntot = MODE == 0 ? 2 * a.F : a.d;             // weight rows per expert
     const int strips = MODE == 0 ? a.F / 64 : a.d / 128;
     // consecutive work-group ids go round the eight XCDs: the strips of an expert are given ids eight apart, so
@@ -256,129 +460,17 @@ __global__ __launch_bounds__(256, 2) void moe_gemm_kernel(MoeArgs a) {
     const int e = grp * 8 + (in_grp & 7), p = in_grp >> 3;
     const int tile0 = a.tile_off[e], ntile = a.tile_off[e + 1] - tile0;
     if (ntile == 0) return;
-    const int kslices = K / 16, nfill = kslices / KA;
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, lg = lane >> 5;
-
     int nt_local;                                           // this wave's 32-feature tile among the expert's rows
     if (MODE == 0) nt_local = wave < 2 ? 2 * p + wave : a.F / 32 + 2 * p + (wave - 2);
     else nt_local = 4 * p + wave;
-    const int nt = e * (Ntot / 32) + nt_local;
-    const bf16_t* w_src = (MODE == 0 ? a.w_gate_up : a.w_down) + (((int64_t)(nt >> 2) * kslices) * 4 + (nt & 3)) * 512 + lane * 8;
-    constexpr int W_STEP = 4 * 512;
-
-    for (int g0 = 0; g0 < ntile; g0 += MT) {
-        const int nt_here = ntile - g0 < MT ? ntile - g0 : MT;
-        // wave w fills row tile w of the group (all KA slices of a fill); tiles past the bucket repeat its last
-        const int my_tile = tile0 + (g0 + wave < ntile ? g0 + wave : ntile - 1);
-        const bf16_t* a_src = (MODE == 0 ? reinterpret_cast<const bf16_t*>(a.y) : a.act) + ((int64_t)my_tile * kslices) * 512 + lane * 8;
-
-        floatx16 acc[MT];
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
-
-        u32x4 wring[PD];
-#pragma unroll
-        for (int s = 0; s < PD; ++s)
-            wring[s] = *reinterpret_cast<const u32x4*>(w_src + (int64_t)(s < kslices ? s : kslices - 1) * W_STEP);
-        u32x4 areg[KA];
-#pragma unroll
-        for (int i = 0; i < KA; ++i) areg[i] = *reinterpret_cast<const u32x4*>(a_src + (int64_t)i * 512);
-#pragma unroll
-        for (int i = 0; i < KA; ++i) *reinterpret_cast<u32x4*>(&abuf[0][(wave * KA + i) * 1024 + lane * 16]) = areg[i];
-
-        for (int fill = 0; fill < nfill; ++fill) {
-            __builtin_amdgcn_s_waitcnt(0xC07F);             // own LDS writes done
-            __builtin_amdgcn_s_barrier();
-            const int nxt = fill + 1 < nfill ? fill + 1 : fill;
-#pragma unroll
-            for (int i = 0; i < KA; ++i) areg[i] = *reinterpret_cast<const u32x4*>(a_src + (int64_t)(nxt * KA + i) * 512);
-            const unsigned char* ab = abuf[fill & 1] + lane * 16;
-            bf16x8 af[2][MT];
-#pragma unroll
-            for (int j = 0; j < MT; ++j) af[0][j] = *reinterpret_cast<const bf16x8*>(ab + (j * KA) * 1024);
-#pragma unroll
-            for (int s = 0; s < KA; ++s) {
-                const int slice = fill * KA + s;
-                if (s + 1 < KA) {
-#pragma unroll
-                    for (int j = 0; j < MT; ++j)
-                        af[(s + 1) & 1][j] = *reinterpret_cast<const bf16x8*>(ab + (j * KA + s + 1) * 1024);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int j = 0; j < MT; ++j)
-                    if (j < nt_here)      // MODE 1: rows first, so that a half wave stores 128 contiguous bytes of an output row
-                        acc[j] = MODE == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wring[s % PD]),
-                                                                                     af[s & 1][j], acc[j], 0, 0, 0)
-                                           : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][j], __builtin_bit_cast(bf16x8, wring[s % PD]),
-                                                                                     acc[j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                // refill the slot just consumed (after its readers, so the load lands in place)
-                const int ahead = slice + PD < kslices ? slice + PD : kslices - 1;
-                wring[s % PD] = *reinterpret_cast<const u32x4*>(w_src + (int64_t)ahead * W_STEP);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int i = 0; i < KA; ++i)
-                *reinterpret_cast<u32x4*>(&abuf[(fill + 1) & 1][(wave * KA + i) * 1024 + lane * 16]) = areg[i];
-        }
-
-        if (MODE == 1) {
-#pragma unroll
-            for (int j = 0; j < MT; ++j) {
-                if (j < nt_here) {
-                    // acc[j][4 q + r] <-> padded row 32 (tile0 + g0 + j) + 8 q + 4 lg + r, feature 128 p + 32 wave + l32
-                    float* dst = a.y + ((int64_t)(tile0 + g0 + j) * 32 + 4 * lg) * a.d + p * 128 + wave * 32 + l32;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) dst[(int64_t)(8 * q + r) * a.d] = acc[j][4 * q + r];
-                }
-            }
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            __builtin_amdgcn_s_barrier();                   // every wave is done with abuf before the next group refills it
-        } else {
-            // up halves travel through LDS to the waves that hold the gate halves of the same features
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            __builtin_amdgcn_s_barrier();                   // all reads of abuf are over
-            float* xbuf = reinterpret_cast<float*>(&abuf[0][0]);     // [2 waves][MT][16][64] floats = 32 KB
-            if (wave >= 2) {
-#pragma unroll
-                for (int j = 0; j < MT; ++j)
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) xbuf[(((wave - 2) * MT + j) * 16 + q) * 64 + lane] = acc[j][q];
-            }
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            __builtin_amdgcn_s_barrier();
-            if (wave < 2) {
-                const int fs = (p * 64 + wave * 32) / 16;     // first 16-wide feature slice of this wave
-#pragma unroll
-                for (int j = 0; j < MT; ++j) {
-                    if (j < nt_here) {
-                        bf16_t* dst = a.act + ((int64_t)(tile0 + g0 + j) * (a.F / 16) + fs) * 512;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            float r[4];
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const float g = acc[j][4 * q + i];
-                                const float u = xbuf[((wave * MT + j) * 16 + 4 * q + i) * 64 + lane];
-                                r[i] = g / (1.0f + expf(-g)) * u;
-                            }
-                            // features 8q + 4 lg .. +3 of this wave's 32: slice q/2, half q%2, elements 4 lg ..
-                            u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
-                            *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
-                        }
-                    }
-                }
-            }
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            __builtin_amdgcn_s_barrier();                   // xbuf is read before the next group overwrites it
-        }
+    const int nt = e * (Ntot / 32) + nt_local, kslices = (MODE == 0 ? a.d : a.F) / 16;
+    const char* w_base = reinterpret_cast<const char*>((MODE == 0 ? a.w_gate_up : a.w_down) + (((int64_t)(nt >> 2) * kslices) * 4 + (nt & 3)) * 512);
+    for (int g0 = 0; g0 < ntile; g0 += MTMAX) {
+        const int left = ntile - g0, nt_here = left < MTMAX ? left : MTMAX;
+        if (MTMAX == 1 || nt_here == 1) moe_tiles<MODE, 1>(a, abuf, w_base, p, tile0 + g0, 1, one_tile);
+        else if (MTMAX == 2 || nt_here == 2) moe_tiles<MODE, 2>(a, abuf, w_base, p, tile0 + g0, 2, one_tile);
+        else if constexpr (MTMAX == 4) moe_tiles<MODE, 4>(a, abuf, w_base, p, tile0 + g0, nt_here, one_tile);
     }
 }
 
@@ -429,20 +521,32 @@ hipError_t moe_ffn(const MoeArgs& a, hipStream_t st) {
     const int kslices = a.d / 16;
     int KQ = 4;
     while (KQ > 1 && (kslices % (4 * KQ) != 0 || kslices / (4 * KQ) < 2)) KQ >>= 1;
+    const bool one_tile = a.T <= 32, wave_planes = one_tile && a.router_parts >= 4 * KQ;
     const size_t router_lds = (size_t)4 * kRouterRows * (a.E + 1) * 4;
-    const dim3 rgrid((a.T + kRouterRows - 1) / kRouterRows, KQ);
+    const dim3 rgrid((a.T + kRouterRows - 1) / kRouterRows, wave_planes ? 4 * KQ : KQ), rblock(wave_planes ? 64 : 256);
     switch (a.E / 32) {
-        case 2: hipLaunchKernelGGL(moe_logits_kernel<2>, rgrid, dim3(256), router_lds, st, a, KQ); break;
-        case 4: hipLaunchKernelGGL(moe_logits_kernel<4>, rgrid, dim3(256), router_lds, st, a, KQ); break;
-        case 6: hipLaunchKernelGGL(moe_logits_kernel<6>, rgrid, dim3(256), router_lds, st, a, KQ); break;
-        case 8: hipLaunchKernelGGL(moe_logits_kernel<8>, rgrid, dim3(256), router_lds, st, a, KQ); break;
+        case 2: hipLaunchKernelGGL(moe_logits_kernel<2>, rgrid, rblock, wave_planes ? 0 : router_lds, st, a, KQ, (int)wave_planes); break;
+        case 4: hipLaunchKernelGGL(moe_logits_kernel<4>, rgrid, rblock, wave_planes ? 0 : router_lds, st, a, KQ, (int)wave_planes); break;
+        case 6: hipLaunchKernelGGL(moe_logits_kernel<6>, rgrid, rblock, wave_planes ? 0 : router_lds, st, a, KQ, (int)wave_planes); break;
+        case 8: hipLaunchKernelGGL(moe_logits_kernel<8>, rgrid, rblock, wave_planes ? 0 : router_lds, st, a, KQ, (int)wave_planes); break;
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(moe_select_kernel, dim3((a.T + 3) / 4), dim3(256), 0, st, a, KQ);
-    hipLaunchKernelGGL(moe_group_kernel, dim3(1), dim3(1024), moe_group_lds_bytes(a.T, a.E), st, a);
-    hipLaunchKernelGGL(moe_gather_kernel, dim3(moe_max_tiles(a.T, a.E, a.top_k), 2), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(moe_gemm_kernel<0>, dim3(a.E * (a.F / 64)), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(moe_gemm_kernel<1>, dim3(a.E * (a.d / 128)), dim3(256), 0, st, a);
+    if (one_tile) {
+        if (wave_planes) hipLaunchKernelGGL(moe_route_tile_kernel<true>, dim3(1), dim3(1024), 0, st, a, 4 * KQ);
+        else hipLaunchKernelGGL(moe_route_tile_kernel<false>, dim3(1), dim3(1024), 0, st, a, KQ);
+    } else {
+        hipLaunchKernelGGL(moe_select_kernel, dim3((a.T + 3) / 4), dim3(256), 0, st, a, KQ);
+        hipLaunchKernelGGL(moe_group_kernel, dim3(1), dim3(1024), moe_group_lds_bytes(a.T, a.E), st, a);
+        hipLaunchKernelGGL(moe_gather_kernel, dim3(moe_max_tiles(a.T, a.E, a.top_k), 2), dim3(256), 0, st, a);
+    }
+    // tiles an ordinary expert holds: one if the rows are, two up to 48 rows an expert, else four
+    auto products = [&](auto up, auto down) {
+        hipLaunchKernelGGL(up, dim3(a.E * (a.F / 64)), dim3(256), 0, st, a, (int)one_tile);
+        hipLaunchKernelGGL(down, dim3(a.E * (a.d / 128)), dim3(256), 0, st, a, (int)one_tile);
+    };
+    if (one_tile) products(moe_gemm_kernel<0, 1>, moe_gemm_kernel<1, 1>);
+    else if ((long long)a.T * a.top_k <= 48LL * a.E) products(moe_gemm_kernel<0, 2>, moe_gemm_kernel<1, 2>);
+    else products(moe_gemm_kernel<0, 4>, moe_gemm_kernel<1, 4>);
     if (a.out) hipLaunchKernelGGL(moe_combine_kernel, dim3(a.T), dim3(256), 0, st, a);
     return hipGetLastError();
 }
