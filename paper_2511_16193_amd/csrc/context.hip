@@ -58,11 +58,11 @@ int pick_splits(int M, int N, int K) {
 // fit to a sweep of every (tiles, width, splits) over thirty shapes of the benchmark models on MI355X (rows 5 to
 // 2304), except the lone work-group's pace, which is taken from whole steps (cold weights); on the sweep the plan
 // chosen was within 0.3 % of the best on average and 4.5 % at worst.
-struct WsPlan { int splits; bool wide; int row_tiles; double us; };
+struct WsPlan { int splits; bool wide; int row_tiles; double us; TallTiles tall; };   // tall.n > 0: the tall kernel with those tiles
 WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplitsWs) {
     const int slices_all = K / 16;
     const int tiles = (M + 31) / 32;
-    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M), 1e30};
+    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M), 1e30, {}};
     // up to 160 rows: one work-group along the rows (cutting so few rows only multiplies the readers of a strip)
     const int mt_lo = tiles <= 5 ? tiles : 1, mt_hi = tiles <= 5 ? tiles : 5;
     for (int mt = mt_lo; mt <= mt_hi; ++mt)
@@ -94,25 +94,25 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
                 t = std::max(t, (double)N * K * 2.0 / 4.98e6);                // a weight stream cannot beat the memory system
                 if (s > 1) t += (double)s * M * N * 4.0 / 5.4e6 + (double)(s - 1) * M * N * 4.0 / 4.0e6;   // planes written here, read by the consumer
                 t += 2.3;
-                if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t};
+                if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t, {}};
             }
         }
     return best;
 }
 
 // Launch plan of a packed projection: the weight-streaming kernel, or from more rows than one of its work-groups holds on the
-// tall kernel (row_tiles 6, 8, 10) where that is expected to take less.  Inside a step the weight-streaming launches
+// tall kernel where that is expected to take less.  Inside a step the weight-streaming launches
 // take 1.10 times the estimate above, which was fitted to single projections in a loop (7B at 2304 rows: QKV 89 us against 78,
 // down 282 against 263); the tall ones take theirs.
 // us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
 // 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
 // tile_mode: -1 = this rule, 0 = never the tall kernel, 1 = 256-row tiles wherever the width allows.
 WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, int max_splits = kMaxSplitsWs) {
-    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 8, 0.0};
+    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, gemm_bf16_tall_256(M)};
     const WsPlan ws = plan_ws(M, N, K, allow_split, max_splits);
     if (tile_mode == 0 || M <= 128) return ws;
     const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
-    return t.us < 1.10 * ws.us ? WsPlan{t.splits, true, 2 * t.rw, t.us} : ws;
+    return t.us < 1.10 * ws.us ? WsPlan{t.splits, true, 0, t.us, t.tiles} : ws;
 }
 
 struct Layout {                       // byte offsets into the workspace
@@ -738,7 +738,8 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
         if (c->packed) {
             const WsPlan p = planned(c, M, N, K, allow_split);
             *splits_out = p.splits;
-            SV_HIP(c, gemm_bf16_ws((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, p.wide, c->stream, p.row_tiles));
+            if (p.tall.n > 0) SV_HIP(c, gemm_bf16_tall((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.tall, c->stream));
+            else SV_HIP(c, gemm_bf16_ws((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, p.wide, c->stream, p.row_tiles));
         } else {
             const int s = allow_split ? pick_splits(M, N, K) : 1;
             *splits_out = s;
@@ -865,8 +866,8 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         // holds them, and every further one reads the strip again).  us of the 7B shape at 147 / 192 / 256 / 320 / 512 / 800 rows,
         // weight-streaming against tall: 65 / 86 / 104 / 100 / 160 / 221 against 65 / 66 / 77 / 98 / 144 / 218.
         if (m.d_ff % 128 == 0 && (c->gemm_tile == 1 || (c->gemm_tile != 0 && T > 160))) {
-            const int rw = c->gemm_tile == 1 ? 4 : gemm_bf16_tall_plan(T, 2 * m.d_ff, d, 1).rw;
-            SV_HIP(c, gemm_bf16_tall((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, rw, st));
+            const TallTiles tiles = c->gemm_tile == 1 ? gemm_bf16_tall_256(T) : gemm_bf16_tall_plan(T, 2 * m.d_ff, d, 1).tiles;
+            SV_HIP(c, gemm_bf16_tall((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, tiles, st));
         } else {
             SV_HIP(c, gemm_bf16_ws_glu((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<bf16_t>(L.act), T, m.d_ff, d, st));
         }
@@ -1086,15 +1087,16 @@ extern "C" int sv_op_gemm_bf16_ws(const void* Ap, const void* Wp, float* out, in
     if (!Ap || !Wp || !out || M <= 0 || N <= 0 || K <= 0 || splits <= 0 || N % (wide ? 256 : 128) != 0 ||
         K % (64 * splits) != 0 || row_tiles < 0 || (row_tiles > 5 && row_tiles != 8) || (row_tiles == 8 && N % 256 != 0))
         return SV_EINVAL;
-    return gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, wide != 0, (hipStream_t)stream, row_tiles) == hipSuccess
-               ? SV_OK : SV_EHIP;
+    const hipError_t e = row_tiles == 8 ? gemm_bf16_tall((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, false, gemm_bf16_tall_256(M), (hipStream_t)stream)
+                                        : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, wide != 0, (hipStream_t)stream, row_tiles);
+    return e == hipSuccess ? SV_OK : SV_EHIP;
 }
 
 extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int* row_tiles) {
     if (!splits || !wide || !row_tiles || M <= 0 || N <= 0 || K <= 0 || N % 128 != 0 || K % 64 != 0) return SV_EINVAL;
     // of the weight-streaming kernel, but where the 256-row tiles fill the chip four times over
     WsPlan p = plan_ws(M, N, K, true);
-    if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0};
+    if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0, {}};
     *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
     return SV_OK;
 }

@@ -391,9 +391,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ws_glu_mixed_kernel(
 //     with a hand-woven stream, alone on their SIMDs, reached 1.07.)  A wave holds 32 RW rows x 64 features.
 //   * a fill is two 16-wide slices of both operands, copied global -> LDS by direct-to-LDS loads in the packed orders, a ring
 //     of three fills, one barrier per fill.
-//   * rows that do not fill the last tile make a shorter one in the same launch (RWT), so that no product is padding beyond
-//     63 rows: beside its strip's other tiles where the launch takes several rounds (they share the strip through L2), behind
-//     them all in a launch of one or two rounds (they run on the CUs that the tall tiles leave idle).
+//   * tiles of two heights in one launch (RW, RWT), so that little of what is multiplied is padding: the shorter ones beside their
+//     strip's other tiles where the launch takes several rounds (they share the strip through L2), behind them all in a launch of one or two rounds (they run on the CUs that the tall tiles leave idle).
 // GLU: the tile's features are 128 gate rows and the 128 up rows of the same features; a wave holds both for its
 // 32 features and writes silu(gate) * up, rounded to bf16, in the packed order of the next projection.
 // Measured on MI355X (K = 3584), against the weight-streaming kernel / the four-wave one: gate/up of 37888 at 2304 rows
@@ -570,44 +569,44 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     }
 }
 
-// tiles_m tiles of 64 RW rows along the rows, then (RWT > 0) one of 64 RWT; tail_last: the short ones behind all others.
+// n tiles of 64 RW rows along the rows, then nt of 64 RWT; tail_last: the short ones behind all others.
 template <bool GLU, int RW, int RWT>
 __global__ __launch_bounds__(512, 2) void gemm_bf16_tall_kernel(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp,
                                                                 float* __restrict__ out, int M, int N, int K, int k_per_split, int splits,
-                                                                int tiles_m, int tiles_n, int tail_last) {
-    const int n_main = tiles_m * tiles_n * splits;
+                                                                int n, int nt, int tiles_n, int tail_last) {
+    const int n_main = n * tiles_n * splits;
     int tm, logical;
     if (RWT > 0 && tail_last && (int)blockIdx.x >= n_main) {
-        logical = xcd_remap(blockIdx.x - n_main, tiles_n * splits);
-        tm = tiles_m;
+        logical = xcd_remap(blockIdx.x - n_main, nt * tiles_n * splits);
+        tm = n + logical % nt;
+        logical /= nt;
     } else {
-        const int along = tiles_m + (RWT > 0 && !tail_last ? 1 : 0);
+        const int along = n + (RWT > 0 && !tail_last ? nt : 0);
         logical = xcd_remap(blockIdx.x, along * tiles_n * splits);
         tm = logical % along;
         logical /= along;
     }
     const int sp = logical % splits, tn = logical / splits;
-    if (RWT == 0 || tm < tiles_m) gemm_bf16_tall_body<GLU, RW>(Ap, Wp, out, M, N, K, k_per_split, tm * 64 * RW, tn, sp);
-    else gemm_bf16_tall_body<GLU, RWT == 0 ? RW : RWT>(Ap, Wp, out, M, N, K, k_per_split, tm * 64 * RW, tn, sp);
+    if (RWT == 0 || tm < n) gemm_bf16_tall_body<GLU, RW>(Ap, Wp, out, M, N, K, k_per_split, tm * 64 * RW, tn, sp);
+    else gemm_bf16_tall_body<GLU, RWT == 0 ? RW : RWT>(Ap, Wp, out, M, N, K, k_per_split, n * 64 * RW + (tm - n) * 64 * RWT, tn, sp);
 }
 
 // Microseconds a launch of the tall kernel takes, by the same kind of play-through as the weight-streaming plan (fitted to 900
-// launches of 17 row counts from 128 to 3500, three shapes and four split counts; half of the estimates lie below 0.97 of the
-// measured time, nine in ten between 0.77 and 1.05).
+// launches of 17 row counts from 128 to 3500, three shapes and four split counts; nine in ten estimates lie between 0.77 and
+// 1.05 of the measured time, and over 63 other launches the tiles it prefers take 2 % longer than the best on average.  Two
+// heights against one and a remainder: gate/up of 55296 over K = 5120 at 800 rows, one tile of 320 and two of 256: 445 us,
+// three of 256 and one of 64: 468; of 37888 over 3584 at 777 rows 198 us against 224).
 // A tile costs its slices at the pace of a CU alone; the chip as a whole sustains kRate; whole rounds take the
 // larger of the two (rounded over the corner), a last round that is not full is hidden in part where there are several;
 // the weight stream adds to both, as it draws on the same power.
-double gemm_bf16_tall_us(int M, int N, int K, int splits, int rw) {
+static double gemm_bf16_tall_us(int M, int N, int K, int splits, const TallTiles& tl) {
     static const double kSlice[6] = {0, 0.130, 0.165, 0.208, 0.245, 0.327};            // us per slice of a lone tile of 64 rw rows
     static const double kRate[6] = {1, 0.70e9, 1.00e9, 1.15e9, 1.25e9, 1.25e9};        // flop per us over the chip
-    const int need = (M + 63) / 64;
-    if (need < rw) rw = need < 3 ? 3 : need;
-    const int q = std::max(1, need / rw), rt = need > rw ? need % rw : 0;
     const double slices = (double)K / 16 / splits, wgs = (double)((N + 255) / 256) * splits;
     auto alone = [&](int r) { return kSlice[r] * slices + 4.0; };
     auto share = [&](int r) { return 2.0 * 64 * r * 256 * 16 * slices / kRate[r]; };
     auto corner = [](double x, double y) { return std::sqrt(std::sqrt(x * x * x * x + y * y * y * y)); };
-    const double n1 = q * wgs, n2 = rt ? wgs : 0, d1 = alone(rw), p1 = share(rw), d2 = rt ? alone(rt) : 0, p2 = rt ? share(rt) : 0;
+    const double n1 = tl.n * wgs, n2 = tl.nt * wgs, d1 = alone(tl.rw), p1 = share(tl.rw), d2 = tl.nt ? alone(tl.rwt) : 0, p2 = tl.nt ? share(tl.rwt) : 0;
     const double rounds = std::floor(n1 / 256), rem = n1 - 256 * rounds;
     double t = rounds > 0 ? rounds * corner(d1, 256 * p1) : 0;
     const double power = rem * p1 + n2 * p2;
@@ -622,40 +621,62 @@ double gemm_bf16_tall_us(int M, int N, int K, int splits, int rw) {
     return std::sqrt(t * t + stream * stream) + (splits - 1) * (double)M * N * 4.0 / 4.0e6 + 2.3;             // the consumer reads the planes
 }
 
-// Rows per tile (in 64s) and splits for the tall kernel: the best by the estimate.
-TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits) {
-    TallPlan best{1, 4, 1e30};
+// The tiles that cover M rows with heights 64 rw and 64 rwt (0: one height only): least padding, then most tall ones.  Heights
+// of one and two waves' row tiles multiply at a poor rate and come once at most.
+static bool gemm_bf16_tall_tiles(int M, int rw, int rwt, TallTiles& tl) {
     const int need = (M + 63) / 64;
-    for (int rw = 3; rw <= 5 && (rw == 3 || rw <= need); ++rw)
-        for (int s = 1; s <= max_splits; ++s) {
-            if ((K / 16) % (kTallSlices * s) != 0) continue;
-            const double t = gemm_bf16_tall_us(M, N, K, s, rw);
-            if (t < best.us) best = TallPlan{s, rw, t};
+    if (rwt == 0) { tl = TallTiles{rw, (need + rw - 1) / rw, 0, 0}; return rw == 3 || rw <= need; }
+    int over = rw;
+    for (int n = need / rw; n >= 1; --n) {
+        const int nt = (need - n * rw + rwt - 1) / rwt, pad = n * rw + nt * rwt - need;
+        if (nt < 1 || (rwt < 3 && nt > 1) || pad >= over) continue;
+        over = pad;
+        tl = TallTiles{rw, n, rwt, nt};
+    }
+    return over < rw;
+}
+
+// Tiles and splits for the tall kernel: the best by the estimate.
+TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits) {
+    TallPlan best{1, {4, (M + 255) / 256, 0, 0}, 1e30};
+    TallTiles tl;
+    for (int rw = 3; rw <= 5; ++rw)
+        for (int rwt = 0; rwt < rw; ++rwt) {
+            if (!gemm_bf16_tall_tiles(M, rw, rwt, tl)) continue;
+            for (int s = 1; s <= max_splits; ++s) {
+                if ((K / 16) % (kTallSlices * s) != 0) continue;
+                const double t = gemm_bf16_tall_us(M, N, K, s, tl);
+                if (t < best.us) best = TallPlan{s, tl, t};
+            }
         }
     return best;
 }
 
+// 256-row tiles and one shorter tile for the rows that are left.
+TallTiles gemm_bf16_tall_256(int M) {
+    const int need = (M + 63) / 64, rest = need % 4;
+    return need <= 3 ? TallTiles{3, 1, 0, 0} : TallTiles{4, need / 4, rest, rest ? 1 : 0};
+}
+
 // plain: out [splits][M][N] fp32, N % 128 == 0.  gated: N = 2 F weight rows, out = packed bf16 [ceil(M/32)*32, F],
-// F % 128 == 0, splits == 1.  (K / splits) % 32 == 0.  rw: 3 to 5, tiles of 64 rw rows.
-hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, int rw, hipStream_t st) {
+// F % 128 == 0, splits == 1.  (K / splits) % 32 == 0.
+hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const TallTiles& tl, hipStream_t st) {
     if (splits < 1 || K % splits != 0 || (K / splits) % (16 * kTallSlices) != 0 || N % (glu ? 256 : 128) != 0 || (glu && splits != 1) ||
-        rw < 3 || rw > 5)
+        tl.rw < 3 || tl.rw > 5 || tl.n < 1 || tl.rwt < 0 || tl.rwt >= tl.rw || tl.nt < 0 || (tl.nt > 0) != (tl.rwt > 0) ||
+        64LL * (tl.rw * tl.n + tl.rwt * tl.nt) < M)
         return hipErrorInvalidValue;
-    const int need = (M + 63) / 64;
-    if (need < rw) rw = need < 3 ? 3 : need;              // rows beyond M read as the last tile
-    const int q = std::max(1, need / rw), rt = need > rw ? need % rw : 0;
-    const int tiles_n = (N + 255) / 256, blocks = (q + (rt ? 1 : 0)) * tiles_n * splits;
-    const int tail_last = q * tiles_n * splits < 2 * 256;
+    const int tiles_n = (N + 255) / 256, blocks = (tl.n + tl.nt) * tiles_n * splits;
+    const int tail_last = tl.n * tiles_n * splits < 2 * 256;
     auto launch = [&](auto kern) -> hipError_t {
-        const int lds = kTallFills * kTallSlices * (2 * rw + 8) * 1024;
+        const int lds = kTallFills * kTallSlices * (2 * tl.rw + 8) * 1024;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(512), lds, st, Ap, Wp, out, M, N, K, K / splits, splits, q, tiles_n, tail_last);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(512), lds, st, Ap, Wp, out, M, N, K, K / splits, splits, tl.n, tl.nt, tiles_n, tail_last);
         return hipGetLastError();
     };
     auto form = [&](auto g) -> hipError_t {
         constexpr bool G = decltype(g)::value;
-        switch (rw * 8 + rt) {
+        switch (tl.rw * 8 + tl.rwt) {
             case 24: return launch(gemm_bf16_tall_kernel<G, 3, 0>);
             case 25: return launch(gemm_bf16_tall_kernel<G, 3, 1>);
             case 26: return launch(gemm_bf16_tall_kernel<G, 3, 2>);
@@ -761,7 +782,6 @@ int gemm_bf16_ws_row_tiles(int M) {
 
 hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool wide,
                         hipStream_t st, int row_tiles) {
-    if (row_tiles >= 6) return gemm_bf16_tall(Ap, Wp, out, M, N, K, splits, false, row_tiles / 2, st);
     const bool long_fill = (K / splits) % 128 == 0;
     const int mt = row_tiles >= 1 && row_tiles <= 5 ? row_tiles : gemm_bf16_ws_row_tiles(M);
     if (!long_fill) {        // short fills (small models; many splits of a deep reduction at a few rows): narrow strips of

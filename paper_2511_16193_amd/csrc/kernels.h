@@ -13,16 +13,17 @@ hipError_t gemm_bf16(const bf16_t* A, const bf16_t* W, float* out, int M, int N,
                      hipStream_t st);
 hipError_t pack_weight(const bf16_t* src, bf16_t* dst, int N, int K, hipStream_t st);
 hipError_t pack_rows(const bf16_t* src, bf16_t* dst, int M, int K, hipStream_t st);
-// row_tiles: 32-row tiles per work-group (1..5; 0 = as few work-groups along the rows as five tiles each allow; 6, 8, 10:
-// the tall kernel)
+// row_tiles: 32-row tiles per work-group (1..5; 0 = as few work-groups along the rows as five tiles each allow)
 hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool wide,
                         hipStream_t st, int row_tiles = 0);
 int gemm_bf16_ws_row_tiles(int M);
-// Tall tiles, 64 rw rows (rw 3..5) x 256 features, both operands through LDS.  glu: N = 2 F gate and up rows, out =
-// packed bf16 activations [ceil(M/32)*32, F]
-hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, int rw, hipStream_t st);
-struct TallPlan { int splits, rw; double us; };
+// Tall tiles, 64 rw rows (rw 3..5) x 256 features, both operands through LDS: n of them along the rows, then nt of 64 rwt
+// rows (rwt < rw).  glu: N = 2 F gate and up rows, out = packed bf16 activations [ceil(M/32)*32, F]
+struct TallTiles { int rw, n, rwt, nt; };
+struct TallPlan { int splits; TallTiles tiles; double us; };
+hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const TallTiles& tiles, hipStream_t st);
 TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits);
+TallTiles gemm_bf16_tall_256(int M);
 hipError_t gemm_bf16_ws_glu(const bf16_t* Ap, const bf16_t* Wp, bf16_t* act_out, int M, int F, int K, hipStream_t st);
 hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st);
 // W [2F][K] (gate rows, then up rows): act [M][F] = silu(gate) * up
