@@ -547,26 +547,59 @@ static int pieces_of(const sv_ctx* c, int total, int chunk) {
     return std::max(1, std::min((total + chunk - 1) / chunk, chunk < kChunkKeys ? kFinePieces : c->lay.max_chunks));
 }
 
-// Keys per piece for a step's attention, unless fixed by option: each candidate's launch is simulated and the shortest
-// makespan, in keys of a CU's share of the stream (46 per us), wins.
-//  - Every piece costs a fixed ~300 (6 us of start-up and merge per work-group, measured).
-//  - A launch of more than 256 work-groups: every piece goes to the CU that frees up first and costs its keys.  (The kv heads
-//    of a piece are alike: 256 / heads places, each taking all heads of a piece.)
-//  - Fewer work-groups do not share the stream with enough others to be bound by it: a lone one works off some 98 keys per us
-//    (three row tiles, measured), so for the handful of requests at the end of a rollout fine pieces are better.
-//  - Every piece adds its share to the merge launch, ~0.15 us.
-// One request of 6000 keys: pieces of 1024 take 22.2 + 7.2 us per layer (attention + merge), fine ones 13.4 + 5.2; seven
-// requests of 900-5000 keys 23.8 + 6.0 against 21.4 + 4.9.
+// Microseconds of an attention launch over pieces of the given keys, each standing for `alike` work-groups (the kv heads and
+// row groups of a piece), longest first.  The work-groups that are resident share the stream (11500 keys of one head per us over
+// the chip, 5.9 TB/s), none of them faster than its CU streams for one work-group alone; whenever one ends the next starts.  So
+// a launch that begins with all its pieces in place is not as long as its longest piece at an even share: what ends leaves
+// its share to the others.  Since all resident pieces advance alike, one clock of keys per piece serves them all.
+// Constants by row tiles, fitted to 182 launches of 14 batches on MI355X: places (work-groups resident), keys per us of a CU,
+// keys' worth of start-up and merge per piece.  The piece sizes chosen were within 0.3 % of the best measured on average (2.5 %
+// at most); list scheduling of even shares, before, 3.4 % (8.8): 64 requests of 1024-8192 keys 150 -> 138 us, 21 of 2000-9000
+// with 8 kv heads 136 -> 126, 96 with one row each 178 -> 172.
+struct AttnPace { int places; double alone, extra; };
+static AttnPace attn_pace(int row_tiles) {
+    static const AttnPace k[4] = {{512, 70, 75}, {256, 70, 150}, {256, 70, 400}, {512, 60, 100}};
+    return k[std::min(row_tiles, 4) - 1];
+}
+static double attn_launch_us(const std::vector<int>& lens, int alike, const AttnPace& pace, std::vector<double>& ends) {
+    const size_t room = std::max(1, pace.places / alike);
+    const auto later = std::greater<double>();
+    ends.clear();
+    double clock = 0.0, t = 0.0;
+    size_t i = 0;
+    while (i < lens.size() && ends.size() < room) { ends.push_back(lens[i++] + pace.extra); std::push_heap(ends.begin(), ends.end(), later); }
+    while (!ends.empty()) {
+        const double wgs = (double)ends.size() * alike;
+        std::pop_heap(ends.begin(), ends.end(), later);
+        const double end = ends.back();
+        t += (end - clock) / std::min(pace.alone / std::ceil(wgs / 256), 11500.0 / wgs);
+        clock = end;
+        if (i < lens.size()) { ends.back() = clock + lens[i++] + pace.extra; std::push_heap(ends.begin(), ends.end(), later); }
+        else ends.pop_back();
+    }
+    return t;
+}
+
+// Keys per piece for a step's attention, unless fixed by option: each candidate's launch is played through and the shortest
+// wins.
+//  - Up to 128 (request, kv head) pairs, the last few requests of a rollout, a launch of 256 work-groups at most does not
+//    share the stream with enough others to be bound by it: a lone one works off some 98 keys per us, so fine pieces are
+//    better.  Estimate, in keys of a CU's share (46 per us): 300 per launch for start-up and merge.
+//    One request of 6000 keys: pieces of 1024 take 22.2 + 7.2 us per layer (attention + merge), fine ones 13.4 + 5.2; seven
+//    requests of 900-5000 keys 23.8 + 6.0 against 21.4 + 4.9.
+//  - Else as above; a cut costs the merge launch as well.
 static int pick_chunk(const sv_ctx* c, const Pass& ps) {
     if (c->attn_chunk_opt) return c->attn_chunk_opt;
     const int Hkv = c->model.n_kv_heads, G = c->model.n_q_heads / Hkv;
-    const int row_groups = (G * ps.n_max + kItemRows - 1) / kItemRows;
+    const int row_groups = (G * ps.n_max + kItemRows - 1) / kItemRows, alike = Hkv * row_groups;
+    const AttnPace pace = attn_pace((G * ps.n_max + 15) / 16);
+    const bool few = fine_pieces_ok(c, ps.B);
     int chunk = kChunkKeys;
     double best = 1e300;
     std::vector<int> lens;
-    std::vector<double> place(std::max(1, 256 / Hkv));
-    for (int cand : {128, 256, 384, 512, 768, 1024, 1536, 2048, 3072, 4096, 6144, 8192, 12288, 16384, 24576, 32768}) {
-        if (cand < kChunkKeys && !fine_pieces_ok(c, ps.B)) continue;
+    std::vector<double> ends;
+    for (int cand : {128, 256, 384, 512, 768, 1024, 1280, 1536, 2048, 2560, 3072, 4096, 5120, 6144, 8192, 12288, 16384, 24576, 32768}) {
+        if (cand < kChunkKeys && !few) continue;
         lens.clear();
         int most = 0;
         for (int b = 0; b < ps.B; ++b) {
@@ -575,23 +608,16 @@ static int pick_chunk(const sv_ctx* c, const Pass& ps) {
             most = std::max(most, nch);
             for (int ch = 0; ch < nch; ++ch) lens.push_back((total + nch - 1) / nch);
         }
-        const double wgs = (double)lens.size() * Hkv * row_groups;
-        double makespan = 0.0;
-        if (wgs <= 256) {
-            const int longest = *std::max_element(lens.begin(), lens.end());
-            makespan = 300.0 + longest * std::max(0.47, wgs / 256.0);
+        const double wgs = (double)lens.size() * alike;
+        double us;
+        if (few && wgs <= 256) {
+            us = (300.0 + *std::max_element(lens.begin(), lens.end()) * std::max(0.47, wgs / 256.0) + 7.0 * (most > 1 ? most : 0)) / 46.0;
         } else {
+            if (most > 1 && wgs > 6.0 * pace.places && cand < 32768) continue;       // so many rounds of pieces only cost
             std::sort(lens.begin(), lens.end(), std::greater<int>());
-            std::fill(place.begin(), place.end(), 0.0);
-            for (int len : lens) {
-                std::pop_heap(place.begin(), place.end(), std::greater<double>());
-                place.back() += len + 300.0;
-                std::push_heap(place.begin(), place.end(), std::greater<double>());
-            }
-            makespan = *std::max_element(place.begin(), place.end());
+            us = attn_launch_us(lens, alike, pace, ends) + (most > 1 ? 6.0 + 0.1 * most : 0.0);
         }
-        if (most > 1) makespan += 7.0 * most;
-        if (makespan < best) { best = makespan; chunk = cand; }
+        if (us < best) { best = us; chunk = cand; }
         if (most == 1) break;                              // coarser candidates cut nothing either
     }
     return chunk;
