@@ -549,17 +549,23 @@ static int pieces_of(const sv_ctx* c, int total, int chunk) {
 
 // Microseconds of an attention launch over pieces of the given keys, each standing for `alike` work-groups (the kv heads and
 // row groups of a piece), longest first.  The work-groups that are resident share the stream (11500 keys of one head per us over
-// the chip, 5.9 TB/s), none of them faster than its CU streams for one work-group alone; whenever one ends the next starts.  So
-// a launch that begins with all its pieces in place is not as long as its longest piece at an even share: what ends leaves
-// its share to the others.  Since all resident pieces advance alike, one clock of keys per piece serves them all.
-// Constants by row tiles, fitted to 182 launches of 14 batches on MI355X: places (work-groups resident), keys per us of a CU,
-// keys' worth of start-up and merge per piece.  The piece sizes chosen were within 0.3 % of the best measured on average (2.5 %
-// at most); list scheduling of even shares, before, 3.4 % (8.8): 64 requests of 1024-8192 keys 150 -> 138 us, 21 of 2000-9000
-// with 8 kv heads 136 -> 126, 96 with one row each 178 -> 172.
-struct AttnPace { int places; double alone, extra; };
+// the chip, 5.9 TB/s; a row group's second reader finds them in L2), none of them faster than it streams by itself; whenever
+// one ends the next starts.  So a launch that begins with all its pieces in place is not as long as its longest piece at an
+// even share: what ends leaves its share to the others.  Since all resident pieces advance alike, one clock of keys per piece
+// serves them all.
+// Constants by row tiles, fitted to 182 launches of 14 batches and, from four tiles on, 58 of seven handfuls of requests on
+// MI355X: places (work-groups resident), keys per us of a work-group with a CU to itself and of two on a CU, keys' worth of
+// start-up and merge per piece.  The sizes chosen were within 0.3 % of the best measured on average (2.3 % at most); list
+// scheduling of even shares, before, 3.4 % (8.8): 64 requests of 1024-8192 keys 150 -> 138 us, 21 of 2000-9000 with 8 kv heads
+// 136 -> 126, 96 with one row each 178 -> 172.
+struct AttnPace { int places; double alone, paired, extra, stream; };
 static AttnPace attn_pace(int row_tiles) {
-    static const AttnPace k[4] = {{512, 70, 75}, {256, 70, 150}, {256, 70, 400}, {512, 60, 100}};
-    return k[std::min(row_tiles, 4) - 1];
+    static const AttnPace k[4] = {{512, 70, 35, 75, 11500}, {256, 70, 70, 150, 11500}, {256, 70, 70, 400, 11500}, {512, 51, 40, 300, 11500}};
+    AttnPace p = k[std::min(row_tiles, 4) - 1];
+    const int groups = (row_tiles + 3) / 4;
+    p.stream *= groups;
+    if (groups > 1 && (row_tiles + groups - 1) / groups == 3) { p.alone *= 1.27; p.paired *= 1.27; }      // three tiles a work-group
+    return p;
 }
 static double attn_launch_us(const std::vector<int>& lens, int alike, const AttnPace& pace, std::vector<double>& ends) {
     const size_t room = std::max(1, pace.places / alike);
@@ -572,7 +578,7 @@ static double attn_launch_us(const std::vector<int>& lens, int alike, const Attn
         const double wgs = (double)ends.size() * alike;
         std::pop_heap(ends.begin(), ends.end(), later);
         const double end = ends.back();
-        t += (end - clock) / std::min(pace.alone / std::ceil(wgs / 256), 11500.0 / wgs);
+        t += (end - clock) / std::min(wgs <= 256 ? pace.alone : pace.paired, pace.stream / wgs);
         clock = end;
         if (i < lens.size()) { ends.back() = clock + lens[i++] + pace.extra; std::push_heap(ends.begin(), ends.end(), later); }
         else ends.pop_back();
@@ -580,26 +586,43 @@ static double attn_launch_us(const std::vector<int>& lens, int alike, const Attn
     return t;
 }
 
+// The same by list scheduling, in keys of a CU's share of the stream: every piece goes to the place that frees up first.
+static double attn_list_keys(const std::vector<int>& lens, int kv_heads, std::vector<double>& places) {
+    const auto later = std::greater<double>();
+    places.assign(std::max(1, 256 / kv_heads), 0.0);
+    for (int len : lens) {
+        std::pop_heap(places.begin(), places.end(), later);
+        places.back() += len + 300.0;
+        std::push_heap(places.begin(), places.end(), later);
+    }
+    return *std::max_element(places.begin(), places.end());
+}
+
 // Keys per piece for a step's attention, unless fixed by option: each candidate's launch is played through and the shortest
 // wins.
-//  - Up to 128 (request, kv head) pairs, the last few requests of a rollout, a launch of 256 work-groups at most does not
-//    share the stream with enough others to be bound by it: a lone one works off some 98 keys per us, so fine pieces are
-//    better.  Estimate, in keys of a CU's share (46 per us): 300 per launch for start-up and merge.
+//  - Up to 128 (request, kv head) pairs of up to three row tiles, the last few requests of a rollout, a launch of 256
+//    work-groups at most does not share the stream with enough others to be bound by it: a lone one works off some 98 keys
+//    per us, so fine pieces are better.  Estimate, in keys of a CU's share (46 per us): 300 per launch for start-up and merge.
 //    One request of 6000 keys: pieces of 1024 take 22.2 + 7.2 us per layer (attention + merge), fine ones 13.4 + 5.2; seven
 //    requests of 900-5000 keys 23.8 + 6.0 against 21.4 + 4.9.
 //  - Else as above; a cut costs the merge launch as well.
+//  - Models with experts take no finer pieces and the coarser estimate: where a row's last kept and first dropped expert are
+//    close, the rounding of another order of the attention's sums picks the other one, and with the few rows of such a step
+//    that is 1-3 % of the logits (20 rows over 406-486 keys, eight inputs: 0.005-0.030 between pieces of 128 and of 1024
+//    keys, 0.000-0.009 with the same pieces).  It costs 4 us of a layer's attention at five requests of 700-3000 keys.
 static int pick_chunk(const sv_ctx* c, const Pass& ps) {
     if (c->attn_chunk_opt) return c->attn_chunk_opt;
     const int Hkv = c->model.n_kv_heads, G = c->model.n_q_heads / Hkv;
     const int row_groups = (G * ps.n_max + kItemRows - 1) / kItemRows, alike = Hkv * row_groups;
-    const AttnPace pace = attn_pace((G * ps.n_max + 15) / 16);
-    const bool few = fine_pieces_ok(c, ps.B);
+    const int row_tiles = (G * ps.n_max + 15) / 16;
+    const AttnPace pace = attn_pace(row_tiles);
+    const bool experts = c->model.n_experts > 0, few = !experts && fine_pieces_ok(c, ps.B);
     int chunk = kChunkKeys;
     double best = 1e300;
     std::vector<int> lens;
     std::vector<double> ends;
     for (int cand : {128, 256, 384, 512, 768, 1024, 1280, 1536, 2048, 2560, 3072, 4096, 5120, 6144, 8192, 12288, 16384, 24576, 32768}) {
-        if (cand < kChunkKeys && !few) continue;
+        if ((cand < kChunkKeys && !few) || (experts && (cand == 1280 || cand == 2560 || cand == 5120))) continue;
         lens.clear();
         int most = 0;
         for (int b = 0; b < ps.B; ++b) {
@@ -610,8 +633,11 @@ static int pick_chunk(const sv_ctx* c, const Pass& ps) {
         }
         const double wgs = (double)lens.size() * alike;
         double us;
-        if (few && wgs <= 256) {
+        if (few && row_tiles <= 3 && wgs <= 256) {
             us = (300.0 + *std::max_element(lens.begin(), lens.end()) * std::max(0.47, wgs / 256.0) + 7.0 * (most > 1 ? most : 0)) / 46.0;
+        } else if (experts) {
+            std::sort(lens.begin(), lens.end(), std::greater<int>());
+            us = attn_list_keys(lens, Hkv, ends);
         } else {
             if (most > 1 && wgs > 6.0 * pace.places && cand < 32768) continue;       // so many rounds of pieces only cost
             std::sort(lens.begin(), lens.end(), std::greater<int>());
