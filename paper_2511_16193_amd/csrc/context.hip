@@ -609,7 +609,8 @@ static double attn_list_keys(const std::vector<int>& lens, int kv_heads, std::ve
 //  - Models with experts take no finer pieces and the coarser estimate: where a row's last kept and first dropped expert are
 //    close, the rounding of another order of the attention's sums picks the other one, and with the few rows of such a step
 //    that is 1-3 % of the logits (20 rows over 406-486 keys, eight inputs: 0.005-0.030 between pieces of 128 and of 1024
-//    keys, 0.000-0.009 with the same pieces).  It costs 4 us of a layer's attention at five requests of 700-3000 keys.
+//    keys, 0.000-0.009 with the same pieces).  It costs 6 us of a layer's attention at five requests of 700-3000 keys (14.9
+//    -> 20.7).
 static int pick_chunk(const sv_ctx* c, const Pass& ps) {
     if (c->attn_chunk_opt) return c->attn_chunk_opt;
     const int Hkv = c->model.n_kv_heads, G = c->model.n_q_heads / Hkv;
