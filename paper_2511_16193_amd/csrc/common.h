@@ -123,8 +123,8 @@ __device__ __forceinline__ void dma2(const char* src, __attribute__((address_spa
     __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 1024, 0);
 }
 
-// 16 bytes per lane from base + lane_off + off, off the same for all lanes, through a buffer descriptor over [base, base + bytes):
-// beyond it nothing is read and zeros return.  base: the same for all lanes.
+// 16 bytes per lane from base + lane_off + off, off the same for all lanes, through a buffer descriptor over [base, base + bytes).
+// base: the same for all lanes.  The caller keeps off inside the range: only lane_off is checked against it.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }

@@ -328,7 +328,8 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
     const int my = wave * MT / 4, ks_mine = (wave * APW) % KA;
     const bf16_t* rows = MODE == 1 ? a.act : one_tile ? a.a : reinterpret_cast<const bf16_t*>(a.y);
     // Both streams are read through buffer descriptors: a slice is a scalar offset, so that the ring needs no lane addresses
-    // (sixteen of them spilled), and a slice past the end is out of the descriptor's range: no memory access, zeros.
+    // (sixteen of them spilled).  The scalar offset is no part of a descriptor's range check, so what is requested past the end
+    // is the last slice or fill again, never the memory behind the matrix.
     const char* a_base = reinterpret_cast<const char*>(rows + ((int64_t)(MODE == 0 && one_tile ? 0 : tile + (my < nt_here ? my : nt_here - 1)) * kslices + ks_mine) * 512);
     const auto a_desc = buffer_of(a_base, (kslices - ks_mine) * 1024), w_desc = buffer_of(w_base, (kslices - 1) * 4096 + 1024);
     auto load_a = [&](int slice) __attribute__((always_inline)) { return buffer_load16(a_desc, lane * 16, slice * 1024); };
@@ -349,9 +350,9 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
-        for (int i = 0; i < APW; ++i) areg[f][i] = load_a(f * KA + i);
+        for (int i = 0; i < APW; ++i) areg[f][i] = load_a(min(f, nfill - 1) * KA + i);
 #pragma unroll
-    for (int s = 0; s < PD; ++s) wring[s] = load_w(s);
+    for (int s = 0; s < PD; ++s) wring[s] = load_w(min(s, kslices - 1));
 #pragma unroll
     for (int i = 0; i < APW; ++i) *reinterpret_cast<u32x4*>(a_dst + i * 1024) = areg[0][i];
 
@@ -361,7 +362,7 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
         __builtin_amdgcn_s_waitcnt(0xC07F);                 // own LDS writes done
         __builtin_amdgcn_s_barrier();
 #pragma unroll
-        for (int i = 0; i < APW; ++i) areg[H][i] = load_a((fill + 2) * KA + i);
+        for (int i = 0; i < APW; ++i) areg[H][i] = load_a(min(fill + 2, nfill - 1) * KA + i);
         const unsigned char* ab = abuf + H * BUF + lane * 16;
         bf16x8 af[2][MT];
 #pragma unroll
@@ -383,7 +384,7 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
                                        : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][j], wf, acc[j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             // refill the slot just consumed (after its readers, so the load lands in place)
-            wring[(H * KA + s) % PD] = load_w(slice + PD);
+            wring[(H * KA + s) % PD] = load_w(min(slice + PD, kslices - 1));
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll

@@ -31,3 +31,10 @@ def test_step_with_the_router_in_sixteen_parts():
     err, exempt, diverged = compare_step(r, g, "bf16", 4)
     assert err < LOGIT_TOL["bf16"] and len(diverged) <= 1
     case.close()
+
+
+@pytest.mark.parametrize("T", [20, 300])
+def test_matrices_that_end_where_their_memory_ends(T):
+    """Stacks of 64 and 32 MiB, whole allocations: the weights requested ahead of the last strips' products, and the rows
+    ahead of the last fills', have nothing behind them that may be read."""
+    check_ffn(T, 1024, 64, 8, 256, 0.0)
