@@ -19,7 +19,8 @@
 // mostly one piece of keys: its work items are (request, 64 stacked rows, piece), their keys end at the last one the rows
 // see, and a request of one piece is finished in the kernel (no partials, no merge).
 //
-// Generic path (fp32 models, other head sizes): one work-group per (row, head).
+// Generic path (fp32 models, other head sizes, page sizes that are no power of two, steps of more than 256 stacked rows per kv
+// head): one work-group per (row, head).
 #include <math.h>
 #include <algorithm>
 #include <type_traits>
@@ -886,14 +887,17 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
     }
 }
 
-bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic) {
-    return !force_generic && dtype == 1 && hd == HD && page_size % TILE_KEYS == 0 && (page_size & (page_size - 1)) == 0;
+// A step's request of more than kStepRows stacked rows stays with the generic kernel: fp32 softmax weights, and a chain that
+// has run into NaN does not touch the others (the MFMA kernels multiply a masked key's V by zero).  No drafter in use
+// stacks so many (8 q heads per kv head and 32 drafts), so the line is drawn for that and not for speed.
+bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic, int step_rows) {
+    return !force_generic && dtype == 1 && hd == HD && page_size % TILE_KEYS == 0 && (page_size & (page_size - 1)) == 0 && step_rows <= kStepRows;
 }
 
 hipError_t attention(const AttnArgs& a, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)a.hd);
     const int G = a.Hq / a.Hkv;
-    if (attn_mfma_ok(a.dtype, a.hd, a.geom.page_size, a.force_generic)) {
+    if (attn_mfma_ok(a.dtype, a.hd, a.geom.page_size, a.force_generic, a.row_items ? 0 : G * a.n_max)) {
         const float sl2 = scale * 1.44269504088896340736f;
         // up to four 16-row tiles per work-group; more stacked rows are split over row groups
         AttnArgs b = a;

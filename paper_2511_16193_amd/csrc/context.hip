@@ -187,9 +187,9 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
     L.act = take(es * Tp * F);
     L.logits = take(sizeof(float) * (size_t)T * m.vocab);
     // the MFMA attention stacks G * n rows per kv head and keeps the partials of a request cut into pieces
-    const int rows_pad = std::max(64, (G * (1 + r.max_chains * r.max_k) + 15) / 16 * 16);
+    const int rows_pad = std::max(64, std::min(kStepRows, (G * (1 + r.max_chains * r.max_k) + 15) / 16 * 16));
     L.part_rows = (long long)r.max_batch * m.n_kv_heads * L.max_chunks * rows_pad;
-    if (attn_mfma_ok(m.dtype, m.head_dim, r.page_size, false)) L.part_rows = std::max(L.part_rows, 2LL * (P * m.n_q_heads + kItemRows * m.n_kv_heads));
+    if (attn_mfma_ok(m.dtype, m.head_dim, r.page_size, false, 0)) L.part_rows = std::max(L.part_rows, 2LL * (P * m.n_q_heads + kItemRows * m.n_kv_heads));
     if (L.part_rows > 0x7fffffffLL) return false;          // partial rows are numbered in 32 bits
     L.part_o = take(sizeof(float) * (size_t)L.part_rows * m.head_dim);
     L.part_ml = take(sizeof(float) * (size_t)L.part_rows * 2);
@@ -733,7 +733,8 @@ static int stage_pass(sv_ctx* c, const Pass& ps) {
     }
     c->n_work = 0;
     c->pass_merge = false;
-    if (attn_mfma_ok(c->model.dtype, c->model.head_dim, c->rt.page_size, c->attn_generic))
+    if (attn_mfma_ok(c->model.dtype, c->model.head_dim, c->rt.page_size, c->attn_generic,
+                     ps.n == 0 ? 0 : c->model.n_q_heads / c->model.n_kv_heads * ps.n))
         build_work(c, ps, st + L.st_req, st + L.st_work);
     st[0] = c->n_work;                                    // read by launches that were captured into a graph
     int nupd = 0;

@@ -104,7 +104,9 @@ struct AttnArgs {
     bool force_generic;                 // take the untuned one-wave-per-row path whatever the shape
 };
 constexpr int kItemRows = 64;               // stacked rows of a prefill item
-bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic);   // the bf16 kernels cover the shape
+constexpr int kStepRows = 256;              // most stacked rows per kv head of a step's request that the bf16 kernels take
+// the bf16 kernels cover the shape; step_rows: stacked rows per kv head of a step's request, 0 for a prefill
+bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic, int step_rows);
 hipError_t attention(const AttnArgs& a, hipStream_t st);
 
 // ---- moe.hip ----

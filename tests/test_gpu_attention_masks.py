@@ -27,6 +27,7 @@ def verifier(dtype, hd, hq, hkv, layers, *, page, pages, k, chains, ff=128, d=No
     ("fp32", 128, 4, 4, 32, 3, 4),
     ("bf16", 64, 8, 2, 64, 2, 5),         # head_dim 64: the generic kernel
     ("bf16", 128, 4, 2, 96, 2, 5),        # a page size that is no power of two: the generic kernel
+    ("bf16", 128, 8, 1, 64, 4, 10),       # 41 rows of 8 heads, 328 stacked rows: the generic kernel
 ])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 def test_masked_entries_do_not_reach_a_row(dtype, hd, hq, hkv, page, chains, k, bad):

@@ -1,5 +1,5 @@
-"""Prefill passes at the edges of how they are cut, and a step whose stacked rows exceed four tiles per kv head many times
-over, against the oracle."""
+"""Prefill passes at the edges of how they are cut, and a step with more stacked rows than the MFMA attention takes, against the
+oracle."""
 import numpy as np
 import pytest
 import torch
@@ -38,7 +38,7 @@ def test_prefill_is_the_oracles_causal_pass(cached, lens):
 
 
 def test_step_with_hundreds_of_stacked_rows():
-    """16 q heads on one kv head, three chains of eight drafts: 400 stacked rows, seven row groups."""
+    """16 q heads on one kv head, three chains of eight drafts: 400 stacked rows, the generic attention's."""
     shape = W.Shape("stacked-bf16", 2, 256, 16, 1, 128, 512, 2048, dtype="bf16", batch=3, k=8, n_chains=3, seed=67)
     case = Case(shape, [5, 333, 2100], verify_mode=OV.STOCHASTIC, sample_mode=OV.SAMPLE_EXP_RACE, packed=True)
     x0 = W.make_tokens((3,), shape.vocab, shape.seed, "x0")
