@@ -348,7 +348,9 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 // groups) this kernel is bound by its matrix products and the power they draw, and three quarters of them are PV
 // products: it runs with PT = 2 (16 significant bits; the 2^-17 relative it leaves is the size of the fp32
 // accumulation error of a few thousand keys, i.e. nothing the result did not carry already), a quarter fewer
-// products than with three terms.  The register kernel above is bound by the stream and keeps three.
+// products than with three terms.  The register kernel above is bound by the stream and keeps three.  So does a prefill, whose
+// rows become the cache that every later step reads: with two terms 1.3 in a thousand outputs are rounded to another bf16
+// value than the exact sums', with three 0.03 to 0.4; 24 prompts of 100-500 tokens 24.56 -> 24.54 ms, one of 777 4.37 -> 4.39.
 template <int R, int W, int D, int PT>
 __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float scale_log2e) {
     // Work item = one piece of one request's keys, cut by the host from its upper bounds of the lengths.
@@ -927,7 +929,7 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
                 case 1: e = launch_regs(attn_bf16_regs_kernel<1>, 1); break;
                 case 2: e = launch(attn_bf16_kernel<2, 2, 2, 2>, 2, 2, 2); break;
                 case 3: e = launch(attn_bf16_kernel<3, 2, 2, 2>, 3, 2, 2); break;
-                default: e = launch(attn_bf16_kernel<4, 2, 2, 2>, 4, 2, 2); break;
+                default: e = a.row_items ? launch(attn_bf16_kernel<4, 2, 2, 3>, 4, 2, 2) : launch(attn_bf16_kernel<4, 2, 2, 2>, 4, 2, 2); break;
             }
         } else {
             switch (R) {

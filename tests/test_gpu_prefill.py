@@ -48,3 +48,61 @@ def test_step_with_hundreds_of_stacked_rows():
     err, exempt, diverged = compare_step(r, g, "bf16", 8)
     assert err < LOGIT_TOL["bf16"] and len(diverged) <= 1
     case.close()
+
+
+def bf16_of(x):
+    """float64 -> the bf16 nearest to it, straight from 64 bits (ties to even)."""
+    f = x.to(torch.float64)
+    m, e = torch.frexp(f)
+    return torch.ldexp(torch.round(m * 256), e - 8)
+
+
+@pytest.mark.parametrize("cached", [0, 2100])
+def test_prefill_sums_unrounded_softmax_weights(cached):
+    """A layer whose output is its attention's: identity output projection, no feed-forward, an embedding a thousandth of the
+    attention's size.  The next layer's V (identity weights) then shows the normalised rows as they are, so that every output of
+    the attention that was rounded to another bf16 value than the exact one is seen.  q = k / 4, so that the cache holds all that
+    the exact attention (float64) needs.
+
+    Bound: with fp32 weights an output's error is that of fp32 sums, a few 1e-7 of the largest V in view (4); outputs of a few
+    hundred to two thousand keys are 0.1 to 0.03, where bf16 values lie 2^-11 to 2^-13 apart.  So up to 5e-4 of the outputs lie
+    close enough to a boundary to cross it.  Weights of two bf16 terms, 2^-17 off each, move 1.3e-3 of them."""
+    import paper_2511_16193_amd as P
+    dev, n, hq, hd = "cuda:0", 300, 4, 128
+    d, V = hq * hd, 1024
+    g = torch.Generator().manual_seed(5)
+    rnd = lambda *s, std=1.0: (torch.randn(s, generator=g) * std).to(torch.bfloat16)
+    wk = rnd(hd, d, std=d ** -0.5)
+    wqkv = torch.cat([wk / 4] * hq + [wk, rnd(hd, d, std=d ** -0.5)])
+    eye = torch.eye(d, dtype=torch.bfloat16)
+    second = torch.zeros(((hq + 2) * hd, d), dtype=torch.bfloat16)
+    second[-hd:, :hd] = torch.eye(hd)
+    one, zero = torch.ones(d, dtype=torch.bfloat16), torch.zeros
+    layers = [{"ln1": one, "wqkv": w, "wo": eye, "ln2": one, "w_gate_up": zero((128, d), dtype=torch.bfloat16), "w_down": zero((d, 64), dtype=torch.bfloat16)}
+              for w in (wqkv, second)]
+    embed = rnd(V, d, std=2.0 ** -10)
+    w = {"embed": embed, "lm_head": rnd(V, d), "final_norm": one, "layers": layers}
+    w = P.pack_weights({k: v.to(dev) if k != "layers" else [{a: b.to(dev) for a, b in lw.items()} for lw in v] for k, v in w.items()})
+    model = dict(n_layers=2, d_model=d, n_q_heads=hq, n_kv_heads=1, head_dim=hd, d_ff=64, vocab=V, n_experts=0, top_k=0, d_expert=0,
+                 dtype="bf16", rope_theta=1.0e4, rms_eps=1.0e-12)
+    ver = P.Verifier(model, w, packed=True, max_batch=1, max_k=4, max_chains=1, max_seqs=1, page_size=64, num_pages=48,
+                     max_pages_per_seq=46, verify_mode=P.SV_MATCH, sample_mode=P.SV_EXP_RACE, temperature=1.0, device=dev)
+    ver.seq_add(0, cached)
+    if cached:
+        kv = rnd(2, cached, 1, hd).to(dev)
+        ver.kv_write(0, 0, 0, kv[0], kv[1])
+        ver.kv_write(0, 1, 0, kv[0], kv[1])
+    tokens = torch.randint(0, V, (n,), generator=g)
+    ver.prefill(0, tokens)
+    k, v = (x[:, 0].double().cpu() for x in ver.kv_read(0, 0, 0, cached + n))
+    shown = ver.kv_read(0, 1, cached, n)[1][:, 0].double().cpu()
+    ver.close()
+    s = k[cached:] @ k.T / 4 / hd ** 0.5
+    s = s.masked_fill(torch.arange(cached + n)[None] > cached + torch.arange(n)[:, None], float("-inf"))
+    o = bf16_of(torch.softmax(s, -1) @ v)
+    h = (embed.double()[tokens] + o.repeat(1, hq)).float()
+    want = bf16_of((h * (1 / torch.sqrt((h.double() ** 2).mean(-1, keepdim=True) + 1e-12)).float()).double()[:, :hd])
+    moved = float((shown != want).double().mean())
+    print("moved", moved)
+    assert float((shown - want).abs().max()) < 0.02 * float(want.abs().max())
+    assert moved < 1e-3
