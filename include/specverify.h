@@ -126,7 +126,9 @@ typedef struct {
     float *logits;         /* device [B*n, vocab] or NULL: receives the target logits (row order = b, then x0, chain 0 drafts, chain 1 ...) */
 } sv_out;
 
-/* Sizes of the two caller-provided device buffers for (model, runtime). 0 on invalid arguments. */
+/* Sizes of the two caller-provided device buffers for (model, runtime). 0 on invalid arguments.  The workspace is what the
+ * verification steps need; a larger one is used for wider prefill passes (sv_workspace_bytes gives the size for a number of
+ * rows). */
 size_t verify_kv_pool_bytes(const sv_model *, const sv_runtime *);
 size_t verify_workspace_bytes(const sv_model *, const sv_runtime *);
 
@@ -163,8 +165,9 @@ int verify_prefill(sv_ctx *, int32_t seq_id, const int32_t *tokens, int32_t n, f
 /* The same for B sequences at once (HOST arrays seq_ids[B], n[B]; all distinct and live): prompt b is row b of
  * the device int32 matrix tokens [B, ld], n[b] <= ld tokens long, and the prompts must come longest first.
  * The prompts go through packed, in prompt order, in as few passes of equal size as hold all their tokens: a pass takes
- * up to 4096 rows (never fewer than a step of the context, nor more than the cache holds; fewer for mixture-of-experts
- * models with many experts), so that the weights stream once for all of them.  max_pages_per_seq must cover cached length
+ * as many rows as the workspace has room for, up to 4096 (never fewer than a step of the context, nor more than the cache
+ * holds; fewer for mixture-of-experts models with many experts and for row-major weights), and streams the weights once for
+ * all of them.  max_pages_per_seq must cover cached length
  * + prompt.  last_logits (device [B, vocab] fp32, may be NULL) receives each
  * prompt's last-token logits.  Errors leave lengths and pages as they were before the failing pass. */
 int verify_prefill_batch(sv_ctx *, const int32_t *seq_ids, int32_t B, const int32_t *tokens, int32_t ld,

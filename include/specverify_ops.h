@@ -17,6 +17,10 @@
 extern "C" {
 #endif
 
+/* Size of a workspace whose prefill passes hold prefill_rows rows (of the up to 4096 they can use, and no more than the
+ * cache holds); prefill_rows = 0: verify_workspace_bytes.  0 on invalid arguments.  Host arithmetic only. */
+size_t sv_workspace_bytes(const sv_model *, const sv_runtime *, int32_t prefill_rows);
+
 /* Dense projection of the forward pass (the part of parallel verification that is bound by matrix
  * throughput at large per-worker batch, Section 3 "Challenge #1"):
  *   out[s][m][n] = sum over k in split s of A[m][k] * W[n][k],   s = 0 .. splits-1

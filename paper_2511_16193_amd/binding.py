@@ -21,10 +21,11 @@ SV_INVERSE_CDF, SV_EXP_RACE = 0, 1
 SV_OPT_GEMM_VARIANT, SV_OPT_ATTN_GENERIC, SV_OPT_ATTN_MIN_ROW_TILES, SV_OPT_ATTN_CHUNK_KEYS, SV_OPT_ATTN_MAX_ROW_TILES, SV_OPT_GRAPH, SV_OPT_GEMM_TILE = 1, 2, 3, 4, 5, 6, 7
 SV_PROF_GEMM, SV_PROF_ATTENTION, SV_PROF_SAMPLER, SV_PROF_ROLLBACK, SV_PROF_MOE = 0, 1, 2, 3, 4
 
+PREFILL_ROWS = 4096
 EXPORTS = [
     "verify_kv_pool_bytes", "verify_workspace_bytes", "verify_init", "verify_destroy", "verify_last_error",
     "verify_seq_add", "verify_seq_remove", "verify_seq_set_len", "verify_seq_len", "verify_kv_write",
-    "verify_kv_read", "verify_prefill", "verify_prefill_batch", "verify_step",
+    "verify_kv_read", "verify_prefill", "verify_prefill_batch", "verify_step", "sv_workspace_bytes",
     "sv_op_gemm_bf16", "sv_op_gemm_bf16_ws", "sv_op_gemm_plan", "sv_op_pack_rows", "sv_op_pack_weight", "sv_op_sample_scratch_bytes", "sv_op_sample", "sv_op_sample_static", "sv_op_moe_scratch_bytes", "sv_op_moe_ffn", "sv_op_attention", "sv_op_layer", "sv_op_rollback", "sv_set_option", "sv_seq_set_lens", "sv_profile_enable",
     "sv_profile_read", "sv_probe_mfma_bf16", "sv_probe_hbm_copy", "sv_probe_hbm_read", "sv_probe_mfma_valu",
     "sv_plan_accept_prob", "sv_plan_tau", "sv_plan_decoupled", "sv_plan_best_window", "sv_fit_affine",
@@ -82,6 +83,8 @@ def load_library() -> C.CDLL:
     lib.verify_kv_pool_bytes.argtypes = [C.POINTER(SvModel), C.POINTER(SvRuntime)]
     lib.verify_workspace_bytes.restype = C.c_size_t
     lib.verify_workspace_bytes.argtypes = [C.POINTER(SvModel), C.POINTER(SvRuntime)]
+    lib.sv_workspace_bytes.restype = C.c_size_t
+    lib.sv_workspace_bytes.argtypes = [C.POINTER(SvModel), C.POINTER(SvRuntime), C.c_int32]
     lib.verify_init.argtypes = [C.POINTER(SvModel), C.POINTER(SvWeights), C.POINTER(SvRuntime), C.c_void_p,
                                 C.POINTER(C.c_void_p)]
     lib.verify_destroy.argtypes = [C.c_void_p]
@@ -166,7 +169,10 @@ class Verifier:
     def __init__(self, model: dict, weights: dict, *, max_batch: int, max_k: int, max_chains: int = 1,
                  max_seqs: int | None = None, page_size: int = 64, num_pages: int, max_pages_per_seq: int,
                  verify_mode: int = SV_STOCHASTIC, sample_mode: int = SV_EXP_RACE, temperature: float = 1.0,
-                 packed: bool = False, device="cuda:0"):
+                 packed: bool = False, device="cuda:0", prefill_rows: int | None = None):
+        """prefill_rows: rows that one pass of a prefill holds, up to 4096, paid for in workspace (the 7B shape: 0.25 GB at
+        2048 rows, 0.50 at 4096); 0 = as many as a step, and no more workspace than a step needs.  None = PREFILL_ROWS, or 0
+        where the device has no room for them."""
         self.lib = lib()
         self.device = torch.device(device)
         self.model = dict(model)
@@ -178,11 +184,17 @@ class Verifier:
         self.rt = SvRuntime(max_batch, max_k, max_chains, max_seqs or max_batch, page_size, num_pages,
                             max_pages_per_seq, verify_mode, sample_mode, temperature, None, 0, None, 0)
         pool_bytes = self.lib.verify_kv_pool_bytes(C.byref(self.m), C.byref(self.rt))
-        ws_bytes = self.lib.verify_workspace_bytes(C.byref(self.m), C.byref(self.rt))
+        ws_bytes = self.lib.sv_workspace_bytes(C.byref(self.m), C.byref(self.rt), PREFILL_ROWS if prefill_rows is None else prefill_rows)
         if pool_bytes == 0 or ws_bytes == 0:
             raise SvError(-1, "invalid model / runtime description")
         self.kv_pool = torch.empty(pool_bytes, dtype=torch.uint8, device=self.device)
-        self.workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=self.device)
+        try:
+            self.workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:
+            if prefill_rows is not None:
+                raise
+            ws_bytes = self.lib.verify_workspace_bytes(C.byref(self.m), C.byref(self.rt))
+            self.workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=self.device)
         self.rt.kv_pool, self.rt.kv_pool_bytes = self.kv_pool.data_ptr(), pool_bytes
         self.rt.workspace, self.rt.workspace_bytes = self.workspace.data_ptr(), ws_bytes
 

@@ -22,13 +22,15 @@ constexpr int kRing = 8;              // pinned staging slots for per-step host 
 constexpr int kMaxSplits = 8;
 constexpr int kMaxSplitsWs = 16;       // weight-streaming kernel: any divisor of the slice count up to this
 constexpr int kChunkKeys = 1024;      // keys per split-KV chunk of the bf16 attention
-// Rows a prefill pass may hold whatever the context was sized for.  A pass streams every weight once, so a prompt that
-// goes through in passes of a step's few dozen rows pays for that stream again and again: one prompt of 777 tokens
-// through a context sized for 40 rows took 22 passes, 29.2 ms over 7 layers of the 7B shape; in one pass 4.7 ms (with the
-// first token's step, 1.2 ms of it).  24 prompts of 100-500 tokens, 7 layers: 47.4 ms in 14 passes with the LM head on
-// every row, 26.4 ms in two passes with it on the prompts' last rows.  From about a thousand rows on the projections are
-// bound by their products; four thousand rows cost 0.4-1 GB of workspace.
+// Most rows of a prefill pass.  A pass streams every weight once, so a prompt that goes through in passes of a step's few dozen
+// rows pays for that stream again and again: one prompt of 777 tokens through a context sized for 40 rows took 22 passes,
+// 29.2 ms over 7 layers of the 7B shape; in one pass 4.7 ms (with the first token's step, 1.2 ms of it).  24 prompts of
+// 100-500 tokens, 7 layers: 47.4 ms in 14 passes with the LM head on every row, 26.4 ms in two passes with it on the
+// prompts' last rows.  From about a thousand rows on the projections are bound by their products.
+// The rows of a pass are the caller's choice, by the size of the workspace: a step's rows where it holds no more (on the 7B
+// shape 5 rows 7 MB, 1024 rows 170, 4096 rows 501).
 constexpr int kPrefillRows = 4096;
+constexpr int kPrefillPlaces = 512;   // work-groups of a prefill's attention that run at once: two per CU
 constexpr int kPlans = 64;            // launch plans a context remembers (five shapes per number of rows)
 constexpr int kCausalK = 1 << 20;     // "drafts per chain" of a prefill pass: one chain, never ending
 
@@ -127,7 +129,11 @@ struct Layout {                       // byte offsets into the workspace
     int st_total;
 };
 
-bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
+// Rows of partial router logits: four parts of a pass, and sixteen of one operand tile (see moe_ffn).
+long long router_rows(int pass_rows) { return std::max(4LL * pass_rows, 16LL * 32); }
+
+// prefill_rows: rows that a prefill pass shall hold, where the cache, the limit above and the expert kernels allow
+bool make_layout(const sv_model& m, const sv_runtime& r, int prefill_rows, Layout& L) {
     if (r.max_batch <= 0 || r.max_k < 0 || r.max_chains <= 0 || r.max_seqs <= 0 || r.page_size <= 0 ||
         r.page_size % kVBlk != 0 || r.num_pages <= 0 || r.max_pages_per_seq <= 0 || r.max_batch > 32767 ||
         (size_t)r.max_pages_per_seq * r.page_size / kChunkKeys > 65535)
@@ -137,7 +143,7 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
     const int qw = m.n_q_heads * m.head_dim, qkvw = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
     const int F = m.n_experts ? m.d_expert : m.d_ff;
     const int G = m.n_q_heads / std::max(1, m.n_kv_heads);
-    int extra = (int)std::min<long long>(kPrefillRows, (long long)r.num_pages * r.page_size);   // no more than the cache holds
+    int extra = (int)std::min<long long>(std::min(kPrefillRows, prefill_rows), (long long)r.num_pages * r.page_size);   // no more than the cache holds
     if (m.n_experts > 0)
         while (extra > T && !moe_shape_ok(extra, m.d_model, m.n_experts, m.top_k, m.d_expert)) extra -= std::min(extra - T, 256);
     const int P = std::max(T, extra);
@@ -168,13 +174,19 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
     L.q = take(es * (size_t)P * qw);
     L.attn = take(es * Tp * qw);
     // split-K partial products: the most splits * rows * features a projection's plan asks for at any number of row
-    // tiles (a plan between two of these sizes that would ask for more is made again with fewer splits)
+    // tiles (a plan between two of these sizes that would ask for more is made again with fewer splits).  The gate/up
+    // product passes through here in row-major bf16 models only, the others have SwiGLU in its epilogue: it is given room
+    // for a step's rows, and a prefill pass of such a model takes as many as that holds (see pass_rows).
     size_t part = 0;
-    const int shapes[4][2] = {{qkvw, m.d_model}, {m.d_model, qw}, {2 * F, m.d_model}, {m.d_model, F}};
+    const int shapes[3][2] = {{qkvw, m.d_model}, {m.d_model, qw}, {m.d_model, F}};
     for (int tm = 1; tm <= (P + 127) / 128; ++tm) {
         const int M = std::min(tm * 128, P);
         for (auto& sh : shapes)
             part = std::max(part, (size_t)(m.dtype == SV_BF16 ? pick_splits(M, sh[0], sh[1]) : 1) * M * sh[0]);
+        if (m.dtype == SV_BF16 && m.n_experts == 0) {
+            const int Ms = std::min(M, T);
+            part = std::max(part, (size_t)pick_splits(Ms, 2 * F, m.d_model) * Ms * 2 * F);
+        }
     }
     if (m.dtype == SV_BF16)                                 // the same for the plans of packed weights
         for (int tm = 1; tm <= (P + 31) / 32; ++tm) {
@@ -189,7 +201,9 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
     // the MFMA attention stacks G * n rows per kv head and keeps the partials of a request cut into pieces
     const int rows_pad = std::max(64, std::min(kStepRows, (G * (1 + r.max_chains * r.max_k) + 15) / 16 * 16));
     L.part_rows = (long long)r.max_batch * m.n_kv_heads * L.max_chunks * rows_pad;
-    if (attn_mfma_ok(m.dtype, m.head_dim, r.page_size, false, 0)) L.part_rows = std::max(L.part_rows, 2LL * (P * m.n_q_heads + kItemRows * m.n_kv_heads));
+    // a prefill cuts keys only where its items are few: kPrefillPlaces of them at most, pieces counted (see build_work)
+    if (attn_mfma_ok(m.dtype, m.head_dim, r.page_size, false, 0))
+        L.part_rows = std::max(L.part_rows, std::min(2LL * (P * m.n_q_heads + kItemRows * m.n_kv_heads), (long long)kPrefillPlaces * kItemRows));
     if (L.part_rows > 0x7fffffffLL) return false;          // partial rows are numbered in 32 bits
     L.part_o = take(sizeof(float) * (size_t)L.part_rows * m.head_dim);
     L.part_ml = take(sizeof(float) * (size_t)L.part_rows * 2);
@@ -204,7 +218,7 @@ bool make_layout(const sv_model& m, const sv_runtime& r, Layout& L) {
         L.moe_inv = take(sizeof(int32_t) * (size_t)P * m.top_k);
         L.moe_act = take(es * 32 * tiles * m.d_expert);
         L.moe_y = take(sizeof(float) * 32 * tiles * m.d_model);
-        L.moe_logits = take(sizeof(float) * 4 * (size_t)P * m.n_experts);
+        L.moe_logits = take(sizeof(float) * (size_t)router_rows(P) * m.n_experts);
     }
     L.total = o;
     return true;
@@ -252,6 +266,7 @@ struct sv_ctx {
     struct PlannedShape { int M, N, K; bool allow_split; WsPlan plan; };
     std::vector<PlannedShape> plans;                      // launch plans of packed projections made so far, at most kPlans
     bool packed;                                          // projection weights are in fragment order
+    int pass_rows;                                        // most rows of a prefill pass
     bool attn_generic;
     int attn_min_rt;
     int attn_max_rt;
@@ -318,6 +333,20 @@ struct ProfScope {
     } while (0)
 #define SV_HIP(ctx, expr) SV_TRY((ctx)->hip((expr), #expr))
 
+// Rows of a prefill pass: what the workspace is laid out for, in row-major bf16 models no more than leave the gate/up product
+// room in the split-K planes.
+static int pass_rows(const sv_ctx* c) {
+    const sv_model& m = c->model;
+    if (m.dtype != SV_BF16 || c->packed) return c->lay.P;
+    int rows = c->lay.T;
+    for (int tm = 1; rows < c->lay.P; ++tm) {
+        const int M = std::min(tm * 128, c->lay.P);
+        if (M > c->lay.T && (size_t)pick_splits(M, 2 * m.d_ff, m.d_model) * M * 2 * m.d_ff > c->lay.part_floats) break;
+        rows = std::max(rows, M);
+    }
+    return rows;
+}
+
 static KvGeom make_geom(const sv_model& m, const sv_runtime& r) {
     KvGeom g;
     g.n_kv_heads = m.n_kv_heads;
@@ -334,18 +363,34 @@ extern "C" size_t verify_kv_pool_bytes(const sv_model* m, const sv_runtime* r) {
     return (size_t)m->n_layers * g.layer_elems * (m->dtype == SV_BF16 ? 2 : 4);
 }
 
-extern "C" size_t verify_workspace_bytes(const sv_model* m, const sv_runtime* r) {
+extern "C" size_t sv_workspace_bytes(const sv_model* m, const sv_runtime* r, int32_t prefill_rows) {
     Layout L;
-    if (!m || !r || !model_ok(*m) || !make_layout(*m, *r, L)) return 0;
+    if (!m || !r || !model_ok(*m) || !make_layout(*m, *r, std::max(0, prefill_rows), L)) return 0;
     return L.total;
+}
+
+extern "C" size_t verify_workspace_bytes(const sv_model* m, const sv_runtime* r) { return sv_workspace_bytes(m, r, 0); }
+
+// The layout with the most prefill rows, in whole 32-row tiles, that a workspace of the given size holds; false if it does
+// not hold a step's rows.
+static bool fit_layout(const sv_model& m, const sv_runtime& r, size_t bytes, Layout& L) {
+    if (make_layout(m, r, kPrefillRows, L) && L.total <= bytes) return true;
+    if (!make_layout(m, r, 0, L) || L.total > bytes) return false;
+    int fits = 0, over = kPrefillRows / 32;
+    while (over - fits > 1) {
+        const int mid = (fits + over) / 2;
+        Layout t;
+        if (make_layout(m, r, 32 * mid, t) && t.total <= bytes) { fits = mid; L = t; } else over = mid;
+    }
+    return true;
 }
 
 extern "C" int verify_init(const sv_model* m, const sv_weights* w, const sv_runtime* r, void* hip_stream, sv_ctx** out) {
     if (!m || !w || !r || !out) return SV_EINVAL;
     *out = nullptr;
     Layout L;
-    if (!model_ok(*m) || !make_layout(*m, *r, L)) return SV_EINVAL;
-    if (!r->kv_pool || !r->workspace || r->kv_pool_bytes < verify_kv_pool_bytes(m, r) || r->workspace_bytes < L.total ||
+    if (!model_ok(*m) || !fit_layout(*m, *r, r->workspace_bytes, L)) return SV_EINVAL;
+    if (!r->kv_pool || !r->workspace || r->kv_pool_bytes < verify_kv_pool_bytes(m, r) ||
         ((uintptr_t)r->kv_pool & 255) || ((uintptr_t)r->workspace & 255))
         return SV_EINVAL;
     if (!(r->temperature > 0.f) || r->verify_mode < 0 || r->verify_mode > 2 || r->sample_mode < 0 || r->sample_mode > 1)
@@ -392,6 +437,7 @@ extern "C" int verify_init(const sv_model* m, const sv_weights* w, const sv_runt
     c->gemm_variant = -1;
     c->gemm_tile = -1;
     c->packed = w->packed != 0;
+    c->pass_rows = pass_rows(c);
     c->attn_generic = false;
     c->attn_min_rt = 1;
     c->use_graph = false;
@@ -666,7 +712,7 @@ static void build_work(sv_ctx* c, const Pass& ps, int32_t* req, int32_t* work) {
         // 64-row groups make the parallelism; where they are too few for two work-groups per CU the keys are cut as well
         long long groups = 0;
         for (int b = 0; b < ps.B; ++b) groups += (G * ps.rq[b].n + kItemRows - 1) / kItemRows;
-        cut = (int)std::max(1LL, 512 / (groups * m.n_kv_heads));
+        cut = (int)std::max(1LL, kPrefillPlaces / (groups * m.n_kv_heads));
     } else {
         chunk = pick_chunk(c, ps);
     }
@@ -903,7 +949,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         ma.a = (const bf16_t*)a_norm; ma.w_router = (const bf16_t*)c->wrouter[l];
         ma.w_gate_up = (const bf16_t*)c->wgu[l]; ma.w_down = (const bf16_t*)c->wdown[l];
         ma.top_ids = c->at<int32_t>(L.moe_ids); ma.top_w = c->at<float>(L.moe_w); ma.router_logits = c->at<float>(L.moe_logits);
-        ma.router_parts = (int)std::min<long long>(16, 4LL * L.P / T);
+        ma.router_parts = (int)std::min<long long>(16, router_rows(L.P) / T);
         ma.cnt = c->at<int32_t>(L.moe_cnt); ma.tile_off = c->at<int32_t>(L.moe_off);
         ma.perm = c->at<int32_t>(L.moe_perm); ma.inv = c->at<int32_t>(L.moe_inv);
         ma.act = c->at<bf16_t>(L.moe_act); ma.y = c->at<float>(L.moe_y); ma.out = nullptr;   // combined by the next norm
@@ -980,9 +1026,9 @@ extern "C" int verify_prefill_batch(sv_ctx* c, const int32_t* seq_ids, int32_t B
     }
     const Prompts pr{tokens, ld};
     std::vector<PassReq> rq;
-    long long passes = (left + c->lay.P - 1) / c->lay.P;
+    long long passes = (left + c->pass_rows - 1) / c->pass_rows;
     for (int b = 0, col = 0; b < B; --passes) {
-        const long long room = std::min<long long>(c->lay.P, ((left + passes - 1) / passes + 31) / 32 * 32);
+        const long long room = std::min<long long>(c->pass_rows, ((left + passes - 1) / passes + 31) / 32 * 32);
         rq.clear();
         const int first = b;
         int T = 0, n_max = 0, ended = 0;
