@@ -435,6 +435,8 @@ __global__ __launch_bounds__(NT) void cdf_kernel(SampleArgs a) {
             for (int i = 0; i < pick; ++i) run += segs[i];
         }
         pick_seg = pick; use_p = up; target = tgt; before = run;
+        // no segment has a weight (NaN logits): id 0, rather than what an earlier draw left there
+        if (pick < 0) reinterpret_cast<floatx4*>(a.draw_part)[blockIdx.x] = floatx4{-INFINITY, 0.f, 0.f, __int_as_float(0)};
     }
     __syncthreads();
     if ((int)threadIdx.x == pick_seg) {

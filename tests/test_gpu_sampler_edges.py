@@ -40,3 +40,23 @@ def test_sampler_edges(B, N, k, V, temp, scale, vmode):
     tol = max(1e-5, 2.0 ** -22 * float(np.abs(logits).max()) / temp)
     assert all(margin[b] < tol for b in bad), [(b, margin[b], ga[b], a[b], gout[b], out[b]) for b in bad]
     assert len(bad) <= max(1, B // 8)
+
+
+@pytest.mark.parametrize("vmode", [OV.STOCHASTIC, OV.MATCH])
+def test_inverse_cdf_over_a_row_of_nan_supplies_a_token_of_its_own(vmode):
+    """No id of a NaN row has a weight: id 0 is supplied, not what a draw of an earlier call left in the scratch."""
+    from paper_2511_16193_amd.binding import op_sample_static
+    V = 1000
+    logits = torch.zeros((2, 1, V), device=DEV)
+    logits[:, 0, 777] = 50.0
+    drafts = torch.zeros((2, 1, 0), dtype=torch.int32, device=DEV)
+    u = torch.full((2, 1, 1), 0.5, device=DEV)
+    acc, best = (torch.empty(2, dtype=torch.int32, device=DEV) for _ in range(2))
+    got = []
+    for poison in (False, True):
+        if poison:
+            logits[1, 0, 5] = float("nan")
+        toks = torch.full((2, 1), -7, dtype=torch.int32, device=DEV)
+        op_sample_static(logits, drafts, None, u, acc, toks, best, verify_mode=vmode, sample_mode=OV.SAMPLE_INVERSE_CDF)
+        got.append(toks.cpu().numpy()[:, 0].tolist())
+    assert got == [[777, 777], [777, 0]]
