@@ -59,7 +59,7 @@ __global__ __launch_bounds__(NS) void row_stats_kernel(SampleArgs a, float inv_t
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (v + i < vend) x[u][i] = row[v + i];
+                    if (v + i < vend && row[v + i] > -INFINITY) x[u][i] = row[v + i];       // a NaN counts as no id at all
             }
         }
     };

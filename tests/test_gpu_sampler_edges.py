@@ -60,3 +60,23 @@ def test_inverse_cdf_over_a_row_of_nan_supplies_a_token_of_its_own(vmode):
         op_sample_static(logits, drafts, None, u, acc, toks, best, verify_mode=vmode, sample_mode=OV.SAMPLE_INVERSE_CDF)
         got.append(toks.cpu().numpy()[:, 0].tolist())
     assert got == [[777, 777], [777, 0]]
+
+
+@pytest.mark.parametrize("vmode", [OV.STOCHASTIC, OV.MATCH])
+def test_nan_logits_of_an_odd_vocabulary_count_as_none(vmode):
+    """Rows that are read one id at a time skip a NaN: the outcome is that of minus infinity in its place."""
+    from paper_2511_16193_amd import op_sample
+    B, N, k, V = 6, 2, 3, 1001
+    logits, drafts, q, u = random_case(B, N, k, V, 9)
+    got = []
+    for value in (-np.inf, np.nan):
+        x = logits.astype(np.float32)
+        x[:, :, 17::250] = value
+        d = np.where(drafts % 250 == 17, 3, drafts)
+        out = op_sample(torch.from_numpy(x).to(DEV), torch.from_numpy(d).to(torch.int32).to(DEV).contiguous(),
+                        torch.as_tensor(q).to(DEV).contiguous() if vmode == OV.STOCHASTIC else None, torch.from_numpy(u).to(DEV),
+                        verify_mode=vmode, sample_mode=OV.SAMPLE_EXP_RACE)
+        got.append([t.cpu().numpy() for t in out])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+    assert all((t >= -1).all() and (t < V).all() for t in (got[1][1],))
