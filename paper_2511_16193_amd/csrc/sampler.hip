@@ -176,11 +176,13 @@ __device__ __forceinline__ void emit(const SampleArgs& a, int b, int best, int a
     }
 }
 
+constexpr int kChains = 1024;                             // chains of a request whose verdicts are in LDS at a time
+
 // One wave per request.  Greedy verification ends here, match verification too (its rows were drawn before: each row's
 // token is folded from the race's parts first); stochastic verification leaves the kept chain for the draw.
 template <int MODE>
 __global__ __launch_bounds__(64) void accept_kernel(SampleArgs a) {
-    extern __shared__ int acc_sh[];                        // [N]
+    __shared__ int acc_sh[kChains];
     const int b = blockIdx.x, lane = threadIdx.x;
     const int n = 1 + a.N * a.k, klim = window_of(a, b);
     const float inv_temp = 1.0f / a.temperature;
@@ -189,34 +191,38 @@ __global__ __launch_bounds__(64) void accept_kernel(SampleArgs a) {
         for (int j = lane; j < n; j += 64)
             if (row_counts(j, a.k, klim)) tok_of[(int64_t)j * a.stat_parts * 4] = __int_as_float(race_winner(a, (int64_t)b * n + j, false));
     }
-    for (int c = lane; c < a.N; c += 64) acc_sh[c] = klim;
-    __syncthreads();
     auto slot_token = [&](int row) {
         return MODE == 2 ? __float_as_int(tok_of[(int64_t)(row - b * n) * a.stat_parts * 4]) : row_stat(a, row, inv_temp).am;
     };
-    for (int i0 = lane; i0 < a.N * a.k; i0 += 64) {
-        const int c = i0 / a.k, i = i0 % a.k + 1;
-        if (i > klim) continue;
-        const int row = slot_row(b, c, i, n, a.k);
-        const int64_t d = (int64_t)b * a.N * a.k + i0;
-        const int x = a.drafts[d];
-        bool ok = false;                                   // not a token of this vocabulary: rejected, nothing is read at it
-        if ((unsigned)x < (unsigned)a.V) {
-            if (MODE == 1) {
-                const Stat st = row_stat(a, row, inv_temp);
-                const float p = expf((a.logits[(int64_t)row * a.V + x] - st.m) * inv_temp) / st.s;
-                const float q = a.draft_probs ? a.draft_probs[d * a.V + x] : 1.0f;
-                ok = a.uniforms[((int64_t)b * a.N + c) * (a.k + 1) + (i - 1)] * q < p;
-            } else {
-                ok = x == slot_token(row);
+    int best = 0, acc = -1;
+    for (int c0 = 0; c0 < a.N; c0 += kChains) {
+        const int chains = min(kChains, a.N - c0);
+        for (int c = lane; c < chains; c += 64) acc_sh[c] = klim;
+        __syncthreads();
+        for (int i0 = lane; i0 < chains * a.k; i0 += 64) {
+            const int c = c0 + i0 / a.k, i = i0 % a.k + 1;
+            if (i > klim) continue;
+            const int row = slot_row(b, c, i, n, a.k);
+            const int64_t d = ((int64_t)b * a.N + c) * a.k + (i - 1);
+            const int x = a.drafts[d];
+            bool ok = false;                               // not a token of this vocabulary: rejected, nothing is read at it
+            if ((unsigned)x < (unsigned)a.V) {
+                if (MODE == 1) {
+                    const Stat st = row_stat(a, row, inv_temp);
+                    const float p = expf((a.logits[(int64_t)row * a.V + x] - st.m) * inv_temp) / st.s;
+                    const float q = a.draft_probs ? a.draft_probs[d * a.V + x] : 1.0f;
+                    ok = a.uniforms[((int64_t)b * a.N + c) * (a.k + 1) + (i - 1)] * q < p;
+                } else {
+                    ok = x == slot_token(row);
+                }
             }
+            if (!ok) atomicMin(&acc_sh[c - c0], i - 1);
         }
-        if (!ok) atomicMin(&acc_sh[c], i - 1);
+        __syncthreads();
+        for (int c = 0; c < chains; ++c)
+            if (acc_sh[c] > acc) { acc = acc_sh[c]; best = c0 + c; }
+        __syncthreads();                                   // read before the next chains start over
     }
-    __syncthreads();
-    int best = 0, acc = acc_sh[0];
-    for (int c = 1; c < a.N; ++c)
-        if (acc_sh[c] > acc) { acc = acc_sh[c]; best = c; }
     if (MODE == 1) {
         if (lane == 0) { a.accepted_len[b] = acc; a.best_chain[b] = best; }
     } else {
@@ -499,18 +505,17 @@ __global__ void commit_len_kernel(RollbackArgs r) {
 hipError_t sample_verify(const SampleArgs& args, hipStream_t st) {
     SampleArgs a = args;
     const int T = a.B * (1 + a.N * a.k);
-    const size_t lds = sizeof(int) * (size_t)a.N;
     a.stat_parts = vocab_parts(T, a.V);
     a.draw_parts = a.sample_mode == 1 ? vocab_parts(a.verify_mode == 2 ? T : a.B, a.V) : 1;
     hipLaunchKernelGGL(row_stats_kernel, dim3(T, a.stat_parts), dim3(NS), 0, st, a, 1.0f / a.temperature);
     if (a.verify_mode == 0) {
-        hipLaunchKernelGGL(accept_kernel<0>, dim3(a.B), dim3(64), lds, st, a);
+        hipLaunchKernelGGL(accept_kernel<0>, dim3(a.B), dim3(64), 0, st, a);
     } else if (a.verify_mode == 2) {
         if (a.sample_mode == 1) hipLaunchKernelGGL(race_kernel<true>, dim3(T, a.draw_parts), dim3(NS), 0, st, a);
         else hipLaunchKernelGGL(cdf_kernel<true>, dim3(T), dim3(NT), 0, st, a);
-        hipLaunchKernelGGL(accept_kernel<2>, dim3(a.B), dim3(64), lds, st, a);
+        hipLaunchKernelGGL(accept_kernel<2>, dim3(a.B), dim3(64), 0, st, a);
     } else {
-        hipLaunchKernelGGL(accept_kernel<1>, dim3(a.B), dim3(64), lds, st, a);
+        hipLaunchKernelGGL(accept_kernel<1>, dim3(a.B), dim3(64), 0, st, a);
         if (a.sample_mode == 1) hipLaunchKernelGGL(race_kernel<false>, dim3(a.B, a.draw_parts), dim3(NS), 0, st, a);
         else hipLaunchKernelGGL(cdf_kernel<false>, dim3(a.B), dim3(NT), 0, st, a);
         hipLaunchKernelGGL(finish_kernel, dim3(a.B), dim3(64), 0, st, a);

@@ -80,3 +80,18 @@ def test_nan_logits_of_an_odd_vocabulary_count_as_none(vmode):
     for a, b in zip(*got):
         assert np.array_equal(a, b)
     assert all((t >= -1).all() and (t < V).all() for t in (got[1][1],))
+
+
+@pytest.mark.parametrize("N", [1024, 1025, 50000])
+@pytest.mark.parametrize("vmode", [OV.GREEDY, OV.STOCHASTIC, OV.MATCH])
+def test_any_number_of_chains(N, vmode):
+    """One chain far behind the others agrees with the target, and so does the last: the lower of the two is kept."""
+    from paper_2511_16193_amd import op_sample
+    V = 64
+    logits = torch.zeros((1, 1 + N, V), device=DEV)
+    logits[:, :, 5] = 60.0
+    drafts = torch.full((1, N, 1), 9, dtype=torch.int32, device=DEV)
+    drafts[0, [N - 3, N - 1]] = 5
+    u = torch.full((1, N, 2), 0.5, device=DEV)
+    acc, toks, best = op_sample(logits, drafts, None, u, verify_mode=vmode, sample_mode=OV.SAMPLE_EXP_RACE)
+    assert (acc.item(), best.item(), toks.cpu().tolist()) == (1, N - 3, [[5, 5]])
