@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void moe_logits_kernel(MoeArgs a, int KQ, int 
 // Router choice of one row by one wave: the planes are added in order (four in flight together; one plane per part, or
 // with QUADS four, of the part's waves), softmax over
 // the experts, top_k by repeated arg-max (lowest id among equals), renormalisation.  Lane j < top_k returns choice j.  The
-// arg-max runs on the probabilities' bit patterns (ordered like the numbers; 0 = taken) by DPP: through shuffles
+// arg-max runs on the probabilities' bit patterns (ordered like the numbers; 0 = taken, or NaN: never chosen) by DPP: through shuffles
 // its sixteen reductions were near half of the time (640 rows: 9.7 -> 5.8 us).
 template <bool QUADS>
 __device__ __forceinline__ void route_row(const MoeArgs& a, int planes, int t, int lane, int& id, float& weight) {
@@ -136,7 +136,7 @@ __device__ __forceinline__ void route_row(const MoeArgs& a, int planes, int t, i
     for (int i = 0; i < PER; ++i) {
         const float p = lane + 64 * i < a.E ? expf(x[i] - mx) : 0.f;
         sum += p > 0.f ? p : 0.f;
-        key[i] = lane + 64 * i < a.E ? min(__float_as_uint(p), 0xfffffffeu) + 1 : 0;
+        key[i] = (lane + 64 * i < a.E && p >= 0.f) ? __float_as_uint(p) + 1 : 0;
     }
     sum = wave_sum(sum);
     float kept_sum = 0.f, mine = 0.f;
@@ -148,11 +148,12 @@ __device__ __forceinline__ void route_row(const MoeArgs& a, int planes, int t, i
         for (int i = 1; i < PER; ++i)
             if (key[i] > best) { best = key[i]; best_e = lane + 64 * i; }    // ascending ids: the first maximum is kept
         const uint32_t top = wave_max_u32(best);
-        const int win = 255 - (int)wave_max_u32(best == top ? 255 - best_e : 0);      // lowest id among the equal maxima
+        // lowest id among the equal maxima; with nothing left but NaN still a valid expert id
+        const int win = top == 0 ? j : 255 - (int)wave_max_u32(best == top ? 255 - best_e : 0);
 #pragma unroll
         for (int i = 0; i < PER; ++i)
             if (lane + 64 * i == win) key[i] = 0;
-        const float p = __uint_as_float(top - 1) / sum;
+        const float p = (top == 0 ? -1.f : __uint_as_float(top - 1)) / sum;
         kept_sum += p;
         if (lane == j) { mine = p; mine_id = win; }
     }

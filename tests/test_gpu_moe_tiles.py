@@ -38,3 +38,25 @@ def test_matrices_that_end_where_their_memory_ends(T):
     """Stacks of 64 and 32 MiB, whole allocations: the weights requested ahead of the last strips' products, and the rows
     ahead of the last fills', have nothing behind them that may be read."""
     check_ffn(T, 1024, 64, 8, 256, 0.0)
+
+
+@pytest.mark.parametrize("T", [20, 40])                # choice and grouping in one launch, and in two
+@pytest.mark.parametrize("dead", [0, 70])
+def test_an_expert_without_a_probability_is_not_chosen(T, dead):
+    """One expert's router row is NaN, so are its logits: the choice is that among the others."""
+    import torch
+    import paper_2511_16193_amd as P
+    d, E, top_k, F = 256, 128, 8, 128
+    g = torch.Generator().manual_seed(T)
+    rnd = lambda *s, std=1.0: (torch.randn(s, generator=g) * std).to(torch.bfloat16)
+    a, w_router, w_gate_up, w_down = rnd(T, d), rnd(E, d, std=0.3), rnd(E, 2 * F, d, std=0.06), rnd(E, d, F, std=0.09)
+    w_router[dead] = float("nan")
+    out, ids, wts = (x.cpu() for x in P.op_moe_ffn(a.cuda(), w_router.cuda(), w_gate_up.cuda(), w_down.cuda(), top_k))
+    logits = a.double() @ w_router.double().T
+    logits[:, dead] = float("-inf")
+    top, want = torch.sort(torch.softmax(logits, -1), -1, descending=True)
+    clear = (top[:, : top_k + 1].diff(dim=-1).abs() > 1e-4 * top[:, :1]).all(-1)      # no two choices that rounding could swap
+    assert clear.sum() >= T // 2
+    assert torch.equal(ids[clear].long(), want[clear, :top_k])
+    assert float((wts[clear] - (top[:, :top_k] / top[:, :top_k].sum(-1, keepdim=True))[clear]).abs().max()) < 5e-5     # as in test_moe_ffn_matches_oracle
+    assert not bool((ids == dead).any()) and bool(torch.isfinite(out).all())
