@@ -18,6 +18,11 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float floatx2;
 
+// The same pieces at any address their elements may have, for buffers that a caller brings (logits, draft probabilities, gains,
+// fp32 matrices may start anywhere inside an allocation).  Global memory takes such accesses: one wide load or store as well.
+typedef floatx4 floatx4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+
 // float -> bf16, round to nearest even: gfx950's v_cvt_pk_bf16_f32.
 __device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
@@ -29,8 +34,8 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
 template <typename T> struct Store;
 template <> struct Store<float> {
     static __device__ __forceinline__ float load(const float* p) { return *p; }
-    static __device__ __forceinline__ void load4(const float* p, float* v) {       // p 16-byte aligned
-        const floatx4 x = *reinterpret_cast<const floatx4*>(p);
+    static __device__ __forceinline__ void load4(const float* p, float* v) {       // any p
+        const floatx4 x = *reinterpret_cast<const floatx4_any*>(p);
         v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
     }
     static __device__ __forceinline__ void store(float* p, float v) { *p = v; }
@@ -40,8 +45,8 @@ template <> struct Store<float> {
 };
 template <> struct Store<bf16_t> {
     static __device__ __forceinline__ float load(const bf16_t* p) { return bf2f(*p); }
-    static __device__ __forceinline__ void load4(const bf16_t* p, float* v) {      // p 8-byte aligned
-        const u32x2 x = *reinterpret_cast<const u32x2*>(p);
+    static __device__ __forceinline__ void load4(const bf16_t* p, float* v) {      // any p
+        const u32x2 x = *reinterpret_cast<const u32x2_any*>(p);
         v[0] = __uint_as_float(x[0] << 16); v[1] = __uint_as_float(x[0] & 0xffff0000u);
         v[2] = __uint_as_float(x[1] << 16); v[3] = __uint_as_float(x[1] & 0xffff0000u);
     }

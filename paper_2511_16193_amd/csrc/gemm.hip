@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 const int n = n0 + (wn * NT + i) * 16 + 4 * lg;
-                *reinterpret_cast<floatx4*>(dst + (int64_t)m * N + n) = acc[i][j];
+                *reinterpret_cast<floatx4_any*>(dst + (int64_t)m * N + n) = acc[i][j];
             }
         }
     }
@@ -843,7 +843,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
     auto load = [&](const float* row, int k) {
         floatx4 v = {0.f, 0.f, 0.f, 0.f};
         if (VEC) {                                         // K % 4 == 0: a piece lies inside or outside as a whole
-            if (k < K) v = *reinterpret_cast<const floatx4*>(row + k);
+            if (k < K) v = *reinterpret_cast<const floatx4_any*>(row + k);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = k + e < K ? row[k + e] : 0.f;

@@ -48,14 +48,14 @@ __global__ __launch_bounds__(NS) void row_stats_kernel(SampleArgs a, float inv_t
     int am = 0x7fffffff;
     const float c2 = inv_temp * 1.4426950408889634f;
     constexpr int kAhead = 4, STEP = 4 * NS * kAhead;
-    const bool vec = (V & 3) == 0;                         // rows start on 16-byte boundaries
+    const bool vec = (V & 3) == 0;                         // rows end with a whole piece
     auto load = [&](int v0, floatx4 (&x)[kAhead]) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             const int v = v0 + u * 4 * NS;
             x[u] = floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
             if (vec) {
-                if (v < vend) x[u] = *reinterpret_cast<const floatx4*>(row + v);
+                if (v < vend) x[u] = *reinterpret_cast<const floatx4_any*>(row + v);
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -121,13 +121,13 @@ __global__ __launch_bounds__(NS) void row_stats_kernel(SampleArgs a, float inv_t
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < NS / 64; ++w) merge(m, s, am, sm[w], ss[w], sa[w]);
-        reinterpret_cast<floatx4*>(a.stat_part)[(int64_t)t * gridDim.y + blockIdx.y] = floatx4{m, s, __int_as_float(am), 0.f};
+        reinterpret_cast<floatx4_any*>(a.stat_part)[(int64_t)t * gridDim.y + blockIdx.y] = floatx4{m, s, __int_as_float(am), 0.f};
     }
 }
 
 // A row's statistics from its parts (ascending ids: of equal maxima the first part's id stays).
 __device__ __forceinline__ Stat row_stat(const SampleArgs& a, int row, float inv_temp) {
-    const floatx4* in = reinterpret_cast<const floatx4*>(a.stat_part) + (int64_t)row * a.stat_parts;
+    const floatx4_any* in = reinterpret_cast<const floatx4_any*>(a.stat_part) + (int64_t)row * a.stat_parts;
     Stat r{-INFINITY, 0.f, 0x7fffffff};
 #pragma unroll 8
     for (int i = 0; i < a.stat_parts; ++i) {
@@ -151,7 +151,7 @@ __device__ __forceinline__ int slot_row(int b, int c, int i, int n, int k) {
 
 // Winner of a race over its parts (larger score; lower id among equals); the residual's if it has one.
 __device__ __forceinline__ int race_winner(const SampleArgs& a, int64_t idx, bool rejected) {
-    const floatx4* in = reinterpret_cast<const floatx4*>(a.draw_part) + idx * a.draw_parts;
+    const floatx4_any* in = reinterpret_cast<const floatx4_any*>(a.draw_part) + idx * a.draw_parts;
     float best_r = -INFINITY, best_p = -INFINITY;
     int arg_r = 0x7fffffff, arg_p = 0x7fffffff;
 #pragma unroll 8
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(NS) void race_kernel(SampleArgs a) {
     auto load4 = [&](const float* src, int v, float fill) __attribute__((always_inline)) {
         floatx4 x = {fill, fill, fill, fill};
         if (vec) {
-            if (v < vend) x = *reinterpret_cast<const floatx4*>(src + v);
+            if (v < vend) x = *reinterpret_cast<const floatx4_any*>(src + v);
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(NS) void race_kernel(SampleArgs a) {
             take(best_r, arg_r, sh_r[w], sh_ar[w]);
             take(best_p, arg_p, sh_p[w], sh_ap[w]);
         }
-        reinterpret_cast<floatx4*>(a.draw_part)[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] =
+        reinterpret_cast<floatx4_any*>(a.draw_part)[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] =
             floatx4{best_r, __int_as_float(arg_r), best_p, __int_as_float(arg_p)};
     }
 }
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(NT) void cdf_kernel(SampleArgs a) {
         }
         pick_seg = pick; use_p = up; target = tgt; before = run;
         // no segment has a weight (NaN logits): id 0, rather than what an earlier draw left there
-        if (pick < 0) reinterpret_cast<floatx4*>(a.draw_part)[blockIdx.x] = floatx4{-INFINITY, 0.f, 0.f, __int_as_float(0)};
+        if (pick < 0) reinterpret_cast<floatx4_any*>(a.draw_part)[blockIdx.x] = floatx4{-INFINITY, 0.f, 0.f, __int_as_float(0)};
     }
     __syncthreads();
     if ((int)threadIdx.x == pick_seg) {
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(NT) void cdf_kernel(SampleArgs a) {
             if (run > target) { tok = v; break; }
         }
         const int drawn = tok >= 0 ? tok : last_pos;
-        reinterpret_cast<floatx4*>(a.draw_part)[blockIdx.x] = floatx4{-INFINITY, 0.f, 0.f, __int_as_float(drawn)};   // a race of one
+        reinterpret_cast<floatx4_any*>(a.draw_part)[blockIdx.x] = floatx4{-INFINITY, 0.f, 0.f, __int_as_float(drawn)};   // a race of one
     }
 }
 

@@ -95,3 +95,41 @@ def test_any_number_of_chains(N, vmode):
     u = torch.full((1, N, 2), 0.5, device=DEV)
     acc, toks, best = op_sample(logits, drafts, None, u, verify_mode=vmode, sample_mode=OV.SAMPLE_EXP_RACE)
     assert (acc.item(), best.item(), toks.cpu().tolist()) == (1, N - 3, [[5, 5]])
+
+
+def test_step_on_buffers_that_start_between_16_byte_boundaries():
+    """Logits, draft probabilities and norm gains one element into their allocations (a slice of a larger tensor): the outcome is
+    that of aligned ones, bit for bit."""
+    import paper_2511_16193_amd as P
+    import workloads as W
+    from harness import to_device
+    shape = W.Shape("offset-bf16", 2, 256, 8, 2, 128, 512, 2048, dtype="bf16", batch=3, k=3, n_chains=2, seed=71)
+    B, N, k, V = 3, 2, 3, shape.vocab
+
+    def apart(t):
+        big = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)
+        out = big[1:].view(t.shape)
+        out.copy_(t)
+        return out
+
+    q = W.make_random_q((B, N, k), V, 1.0, 5)
+    drafts = W.sample_from(q, 5).to(torch.int32).to(DEV).contiguous()
+    u = torch.from_numpy(W.make_uniforms((B, N, k + 1), 5)).to(DEV)
+    x0 = torch.tensor([3, 5, 7], dtype=torch.int32, device=DEV)
+    got = []
+    for move in (lambda t: t, apart):
+        w = P.pack_weights(to_device(W.make_weights(shape, "cpu")))
+        w["final_norm"] = move(w["final_norm"])
+        for lw in w["layers"]:
+            lw["ln1"], lw["ln2"] = move(lw["ln1"]), move(lw["ln2"])
+        ver = P.Verifier(shape.model_fields(), w, packed=True, max_batch=B, max_k=k, max_chains=N, num_pages=16, max_pages_per_seq=4)
+        for b in range(B):
+            ver.seq_add(b, 0)
+            ver.prefill(b, torch.arange(20 + b, dtype=torch.int32))
+        out = {"accepted_len": torch.zeros(B, dtype=torch.int32, device=DEV), "best_chain": torch.zeros(B, dtype=torch.int32, device=DEV),
+               "out_tokens": torch.zeros((B, k + 1), dtype=torch.int32, device=DEV), "logits": move(torch.zeros((B, 1 + N * k, V), device=DEV))}
+        ver.step([0, 1, 2], x0, drafts, move(q.to(DEV)), u, out=out)
+        torch.cuda.synchronize()
+        got.append({n: t.cpu() for n, t in out.items()})
+        ver.close()
+    assert all(torch.equal(got[0][n], got[1][n]) for n in got[0]) and float(got[0]["logits"].std()) > 0.1
