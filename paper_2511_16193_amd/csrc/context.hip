@@ -265,6 +265,8 @@ struct sv_ctx {
     int gemm_tile;                                        // tall projection kernel: -1 = where it pays, 0 = never, 1 = wherever the shape allows
     struct PlannedShape { int M, N, K; bool allow_split; WsPlan plan; };
     std::vector<PlannedShape> plans;                      // launch plans of packed projections made so far, at most kPlans
+    struct GateUp { int T; TallTiles tiles; };
+    std::vector<GateUp> gate_up;                          // the same for the gate/up projection's tall tiles
     bool packed;                                          // projection weights are in fragment order
     int pass_rows;                                        // most rows of a prefill pass
     bool attn_generic;
@@ -832,6 +834,16 @@ static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split) {
     return p;
 }
 
+// The tall tiles of the gate/up projection of T rows, made once per row count as well.
+static TallTiles gate_up_tiles(sv_ctx* c, int T) {
+    for (const auto& g : c->gate_up)
+        if (g.T == T) return g.tiles;
+    const TallTiles tiles = gemm_bf16_tall_plan(T, 2 * c->model.d_ff, c->model.d_model, 1).tiles;
+    if (c->gate_up.size() >= kPlans) c->gate_up.clear();
+    c->gate_up.push_back({T, tiles});
+    return tiles;
+}
+
 static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int N, int K, int* splits_out, bool allow_split = true) {
     ProfScope prof(c, SV_PROF_GEMM);
     if (c->model.dtype == SV_BF16) {
@@ -966,7 +978,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         // holds them, and every further one reads the strip again).  us of the 7B shape at 147 / 192 / 256 / 320 / 512 / 800 rows,
         // weight-streaming against tall: 65 / 86 / 104 / 100 / 160 / 221 against 65 / 66 / 77 / 98 / 144 / 218.
         if (m.d_ff % 128 == 0 && (c->gemm_tile == 1 || (c->gemm_tile != 0 && T > 160))) {
-            const TallTiles tiles = c->gemm_tile == 1 ? gemm_bf16_tall_256(T) : gemm_bf16_tall_plan(T, 2 * m.d_ff, d, 1).tiles;
+            const TallTiles tiles = c->gemm_tile == 1 ? gemm_bf16_tall_256(T) : gate_up_tiles(c, T);
             SV_HIP(c, gemm_bf16_tall((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, tiles, st));
         } else {
             SV_HIP(c, gemm_bf16_ws_glu((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<bf16_t>(L.act), T, m.d_ff, d, st));
