@@ -40,10 +40,23 @@ int sv_op_gemm_bf16_ws(const void *Ap, const void *Wp, float *out, int M, int N,
                        int row_tiles, void *stream);
 
 /* A launch shape for sv_op_gemm_bf16_ws of M rows onto N features over K inputs (HOST pointers out: reduction splits,
- * 256- or 128-feature strips, 32-row tiles per work-group -- 8 = the tall kernel, where its tiles fill the chip four times
- * over).  A verification step uses it up to 128 rows, and above where it expects the tall kernel to take longer.
- * Host arithmetic only.  N % 128 == 0, K % 64 == 0. */
+ * 256- or 128-feature strips, 32-row tiles per work-group -- 8 = 256-row tall tiles, where they fill the chip four times
+ * over).  sv_op_gemm_step_plan gives the launch of a verification step.  Host arithmetic only.  N % 128 == 0, K % 64 == 0. */
 int sv_op_gemm_plan(int M, int N, int K, int *splits, int *wide, int *row_tiles);
+
+/* The launch that a verification step, or a prefill pass, makes for a packed projection of M rows (HOST pointers out).
+ * form 0: QKV, O or down (the reduction may be split), 1: LM head, 2: gate/up with SwiGLU (N = 2 d_ff gate and up rows).
+ * tall[0] != 0: sv_op_gemm_bf16_tall with these tiles and *splits; tall[0] == 0: sv_op_gemm_bf16_ws with *splits, *wide and
+ * *row_tiles, or for form 2 sv_op_gemm_bf16_tall without tiles.  Host arithmetic only.  N % 128 == 0 (form 2: 256), K % 64 == 0. */
+int sv_op_gemm_step_plan(int M, int N, int K, int form, int *splits, int *wide, int *row_tiles, int *tall);
+
+/* The tall packed-operand kernel in given tiles: tall (HOST) = {h, n, ht, nt}, n tiles of 64 h rows x 256 features along the rows,
+ * then nt of 64 ht; h 3..5, ht < h, nt = 0 if and only if ht = 0; together they cover the M rows and no tile lies beyond them.
+ * gated == 0: out fp32 [splits, M, N], the sums of sv_op_gemm_bf16_ws with as many splits.  gated != 0 (splits == 1, N = 2 F,
+ * F % 128 == 0): out = silu(gate) * up, bf16, in the order sv_op_pack_rows writes, [ceil(M/32)*32, F]; tall == NULL: the
+ * same by the weight-streaming kernel.  N % 128 == 0, K % 64 == 0, K % (32 * splits) == 0. */
+int sv_op_gemm_bf16_tall(const void *Ap, const void *Wp, void *out, int M, int N, int K, int splits, int gated,
+                         const int *tall, void *stream);
 
 /* Reorder row-major bf16 activations src [M, K] into dst (ceil(M/32)*32*K elements) in the order the
  * weight-streaming kernel reads them: [ceil(M/32)][K/16][64 lanes][8 elements], lane 32*g + r of a fragment
@@ -155,7 +168,7 @@ int sv_probe_mfma_valu(float *sink, int iters, int valu_per_mfma, int waves_per_
  *   SV_OPT_GEMM_VARIANT  work-group tile of the row-major bf16 projections (0..2; -1 = per shape, default)
  *   SV_OPT_GEMM_TILE  the tall kernel for packed projections: -1 = where the launch plan expects it to pay
  *                     (default), 0 = never, 1 = with 256-row tiles wherever the shape allows (output features a multiple of 256)
- *   SV_OPT_ATTN_GENERIC  1 = always use the untuned one-wave-per-row attention (default 0)
+ *   SV_OPT_ATTN_GENERIC  1 = always use the generic attention, a work-group per row and head (default 0)
  *   SV_OPT_ATTN_MIN_ROW_TILES  lower bound (1..4) on the 16-row tiles the bf16 attention is built for
  *   SV_OPT_ATTN_MAX_ROW_TILES  most 16-row tiles (1..4, default 4) one work-group of the bf16 attention takes;
  *                           more stacked rows are split over row groups that stream the same keys

@@ -834,6 +834,12 @@ static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split) {
     return p;
 }
 
+// Gate/up projection of T rows: from more than five 32-row tiles on by tall tiles (one work-group of the weight-streaming
+// kernel along the rows no longer holds them, and every further one reads the strip again).  us of the 7B shape at 147 / 192 /
+// 256 / 320 / 512 / 800 rows, weight-streaming against tall: 65 / 86 / 104 / 100 / 160 / 221 against 65 / 66 / 77 / 98 / 144 / 218.
+// (The line is that kernel's row limit, not a comparison of the two estimates: they are level at 147 and at 320 rows.)
+static bool gate_up_tall(int T) { return T > 160; }
+
 // The tall tiles of the gate/up projection of T rows, made once per row count as well.
 static TallTiles gate_up_tiles(sv_ctx* c, int T) {
     for (const auto& g : c->gate_up)
@@ -974,10 +980,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     if (c->packed && m.d_ff % 64 == 0) {
         // gate/up projection with SwiGLU in its epilogue: the [T, 2F] fp32 intermediate never exists
         ProfScope prof(c, SV_PROF_GEMM);
-        // More than five 32-row tiles: the tall tiles (one work-group of the weight-streaming kernel along the rows no longer
-        // holds them, and every further one reads the strip again).  us of the 7B shape at 147 / 192 / 256 / 320 / 512 / 800 rows,
-        // weight-streaming against tall: 65 / 86 / 104 / 100 / 160 / 221 against 65 / 66 / 77 / 98 / 144 / 218.
-        if (m.d_ff % 128 == 0 && (c->gemm_tile == 1 || (c->gemm_tile != 0 && T > 160))) {
+        if (m.d_ff % 128 == 0 && (c->gemm_tile == 1 || (c->gemm_tile != 0 && gate_up_tall(T)))) {
             const TallTiles tiles = c->gemm_tile == 1 ? gemm_bf16_tall_256(T) : gate_up_tiles(c, T);
             SV_HIP(c, gemm_bf16_tall((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, tiles, st));
         } else {
@@ -1115,8 +1118,8 @@ static void drop_graphs(sv_ctx* c) {
 // Graph replay of the step's device work.  A step's launches depend on the batch shape and on the caller's
 // buffers only (the lengths reach the kernels through device memory; the attention grid is sized for the most
 // work items the shape can have), so one captured graph serves every step with the same shape and buffers.
-// The first step of a kind runs as plain launches (one-off set-up calls are not capturable), the second is
-// captured, later ones replay.  Returns 1 if the work was enqueued through a graph, 0 if the caller should
+// The first step of a kind runs as plain launches (the runtime loads each kernel at its first launch, which a capture is
+// no place for), the second is captured, later ones replay.  Returns 1 if the work was enqueued through a graph, 0 if the caller should
 // enqueue it itself, < 0 on error.
 static int step_through_graph(sv_ctx* c, const sv_batch* bt, const Pass& ps, const int32_t* drafts, const float* draft_probs,
                               const float* uniforms, const sv_out* out) {
@@ -1211,6 +1214,39 @@ extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int*
     if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0, {}};
     *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
     return SV_OK;
+}
+
+extern "C" int sv_op_gemm_step_plan(int M, int N, int K, int form, int* splits, int* wide, int* row_tiles, int* tall) {
+    if (!splits || !wide || !row_tiles || !tall || M <= 0 || N <= 0 || K <= 0 || form < 0 || form > 2 || N % (form == 2 ? 256 : 128) != 0 || K % 64 != 0)
+        return SV_EINVAL;
+    WsPlan p{1, false, 0, 0.0, {}};
+    if (form == 2) {
+        if (gate_up_tall(M)) p.tall = gemm_bf16_tall_plan(M, N, K, 1).tiles;
+    } else {
+        p = plan_packed(M, N, K, form == 0, -1);
+    }
+    *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
+    tall[0] = p.tall.rw; tall[1] = p.tall.n; tall[2] = p.tall.rwt; tall[3] = p.tall.nt;
+    return SV_OK;
+}
+
+extern "C" int sv_op_gemm_bf16_tall(const void* Ap, const void* Wp, void* out, int M, int N, int K, int splits, int gated,
+                                    const int* tall, void* stream) {
+    if (!Ap || !Wp || !out || M <= 0 || N <= 0 || K <= 0 || splits <= 0 || splits > kMaxSplitsWs || (gated && splits != 1) ||
+        N % (gated ? 256 : 128) != 0 || K % 64 != 0 || K % (32 * splits) != 0)
+        return SV_EINVAL;
+    hipStream_t st = (hipStream_t)stream;
+    if (!tall) {
+        if (!gated) return SV_EINVAL;
+        return gemm_bf16_ws_glu((const bf16_t*)Ap, (const bf16_t*)Wp, (bf16_t*)out, M, N / 2, K, st) == hipSuccess ? SV_OK : SV_EHIP;
+    }
+    const TallTiles tl{tall[0], tall[1], tall[2], tall[3]};
+    // heights that exist; all rows covered, no tile of padding alone (which also bounds the grid)
+    if (tl.rw < 3 || tl.rw > 5 || tl.rwt < 0 || tl.rwt >= tl.rw || (tl.nt > 0) != (tl.rwt > 0) || tl.n < 1 || tl.nt < 0 || tl.n > M || tl.nt > M)
+        return SV_EINVAL;
+    const long long rows = 64LL * tl.rw * tl.n + 64LL * tl.rwt * tl.nt;
+    if (rows < M || rows - 64 * (tl.nt > 0 ? tl.rwt : tl.rw) >= M) return SV_EINVAL;
+    return gemm_bf16_tall((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, gated != 0, tl, st) == hipSuccess ? SV_OK : SV_EHIP;
 }
 
 extern "C" int sv_op_pack_rows(const void* src, void* dst, int M, int K, void* stream) {

@@ -101,7 +101,7 @@ struct AttnArgs {
     int min_row_tiles;                  // lower bound on the 16-row tiles of the bf16 kernel (tuning)
     int max_row_tiles;                  // most 16-row tiles one work-group takes (1..4); more rows -> row groups
     bool out_packed;                    // write `out` in the packed activation order (see act_index)
-    bool force_generic;                 // take the untuned one-wave-per-row path whatever the shape
+    bool force_generic;                 // take the generic path (a work-group per row and head) whatever the shape
 };
 constexpr int kItemRows = 64;               // stacked rows of a prefill item
 constexpr int kStepRows = 256;              // most stacked rows per kv head of a step's request that the bf16 kernels take
