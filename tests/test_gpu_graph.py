@@ -12,8 +12,8 @@ SHAPE = W.Shape("graph-bf16", 3, 256, 8, 2, 128, 512, 2048, dtype="bf16", batch=
                 seed=321)
 
 
-def run_steps(graph: bool, steps: int):
-    """Six requests, k = 4, stochastic verification; the cache advances by the accepted tokens after every step
+def run_steps(graph: bool, steps: int, shape=SHAPE, tile: int = -1):
+    """Requests of `shape`, k = 4, stochastic verification; the cache advances by the accepted tokens after every step
     (no reset), every third step the lengths are put back, so the item list of the attention and the lengths
     differ between replays.  Returns everything a step produces, per step."""
     import paper_2511_16193_amd as P
@@ -21,11 +21,12 @@ def run_steps(graph: bool, steps: int):
     stream = torch.cuda.Stream()                      # graph capture needs a stream of its own
     res = []
     with torch.cuda.stream(stream):
-        case = DeviceCase(SHAPE)
+        case = DeviceCase(shape)
         case.independent_drafts(1.0)
+        case.ver.set_option(P.SV_OPT_GEMM_TILE, tile)
         if graph:
             case.ver.set_option(P.SV_OPT_GRAPH, 1)
-        B, N, k, V = case.B, case.N, case.k, SHAPE.vocab
+        B, N, k, V = case.B, case.N, case.k, shape.vocab
         out = {"accepted_len": torch.empty(B, dtype=torch.int32, device=case.device),
                "out_tokens": torch.empty((B, k + 1), dtype=torch.int32, device=case.device),
                "best_chain": torch.empty(B, dtype=torch.int32, device=case.device),
@@ -52,6 +53,19 @@ def test_graph_replay_matches_plain_launches():
             assert np.array_equal(p[key], g[key]), f"step {s}: {key} differs between plain launches and graph replay"
     assert any(r["accepted_len"].sum() > 0 for r in plain)
     assert not np.array_equal(plain[1]["lens"], plain[2]["lens"])     # the replays did see different lengths
+
+
+@pytest.mark.parametrize("tile", [-1, 1])
+def test_graph_replay_of_tall_projections(tile):
+    """72 requests, 360 rows: gate/up by the tall kernel, whose launches set a kernel attribute inside the capture; with tile 1
+    every projection."""
+    shape = W.Shape("graph-tall", 2, 512, 8, 2, 128, 2048, 4096, dtype="bf16", batch=72, k=4, prefix_lo=10, prefix_hi=300, seed=323)
+    import paper_2511_16193_amd as P
+    assert P.op_gemm_step_plan(360, 4096, 512, 2)["tall"]
+    plain, graph = run_steps(False, 5, shape, tile), run_steps(True, 5, shape, tile)
+    for s, (p, g) in enumerate(zip(plain, graph)):
+        for key in p:
+            assert np.array_equal(p[key], g[key]), f"step {s}: {key} differs between plain launches and graph replay"
 
 
 def test_graph_needs_own_stream():

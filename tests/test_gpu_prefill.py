@@ -28,12 +28,31 @@ def test_prefill_is_the_oracles_causal_pass(cached, lens):
     assert np.max(np.abs(lo - ld)) < LOGIT_TOL["bf16"]
     assert np.array_equal(case.device_lengths(), [a + n for a, n in zip(cached, lens)])
     for b, n in enumerate(lens):
-        for layer, frac, atol in ((0, 0.01, 0.02), (shape.n_layers - 1, 1.0, 0.03)):    # as in the step tests: layer 0 sees equal inputs
+        # layer 0 sees equal inputs: the entries differ where rounding does; behind it every entry may, by little
+        for layer, frac, atol in ((0, 0.01, 0.02), (shape.n_layers - 1, None, 0.03)):
             kd, vd = case.ver.kv_read(b, layer, cached[b], n)
             ko, vo = case.caches[b].k[layer][cached[b]:cached[b] + n], case.caches[b].v[layer][cached[b]:cached[b] + n]
             kd, vd = kd.float().cpu().numpy(), vd.float().cpu().numpy()
             assert np.max(np.abs(kd - ko)) < atol and np.max(np.abs(vd - vo)) < atol
-            assert np.mean(kd != ko) <= frac and np.mean(vd != vo) <= frac
+            assert frac is None or (np.mean(kd != ko) <= frac and np.mean(vd != vo) <= frac)
+    case.close()
+
+
+def test_prefill_behind_rejected_drafts():
+    """A step's rejected drafts leave the host's bounds of the lengths above the live ones; the prompts that follow without the
+    lengths being read back start at the live ends, and see nothing of what was rejected."""
+    shape = W.Shape("behind-bf16", 2, 256, 8, 2, 128, 512, 2048, dtype="bf16", batch=3, k=8, seed=73)
+    case = Case(shape, [30, 250, 1200], verify_mode=OV.STOCHASTIC, sample_mode=OV.SAMPLE_EXP_RACE, packed=True, extra_tokens=160)
+    x0 = W.make_tokens((3,), shape.vocab, shape.seed, "x0")
+    q = W.make_random_q((3, 1, 8), shape.vocab, 1.0, shape.seed)
+    r, g = case.step(x0, W.sample_from(q, shape.seed).numpy(), q, W.make_uniforms((3, 1, 9), shape.seed))
+    assert np.array_equal(g["accepted_len"], r.accepted_len) and (r.accepted_len < 8).sum() >= 2
+    lens = [120, 40, 1]
+    prompts = W.make_tokens((3, 120), shape.vocab, shape.seed, "prompt")
+    lo = np.stack([OV.prefill(case.spec, case.wn, case.caches[b], prompts[b, :n])[-1] for b, n in enumerate(lens)])
+    ld = case.ver.prefill_batch([0, 1, 2], torch.from_numpy(prompts).to(torch.int32), lens).cpu().numpy()
+    assert np.max(np.abs(lo - ld)) < LOGIT_TOL["bf16"]
+    assert np.array_equal(case.device_lengths(), [c.length for c in case.caches])
     case.close()
 
 

@@ -1,5 +1,6 @@
-"""The tall projection kernel: every combination of tall and short row tiles, strips beyond the output's width, reductions
-shorter than its ring, against float64 products and against the weight-streaming kernel inside a step."""
+"""The tall projection kernel: every combination of tall and short row tiles in both of its forms, strips beyond the output's
+width, reductions shorter than its ring, short tiles behind and beside the tall ones -- against float64 products and, bit for
+bit, the weight-streaming kernel -- and in the launch plan's own tiles inside a step."""
 import numpy as np
 import pytest
 import torch
@@ -29,9 +30,9 @@ def test_whole_and_short_row_tiles_match_float64_product(rows, K, splits):
 
 @pytest.mark.parametrize("rows", [129, 161, 225, 321, 385, 450, 650, 865, 897, 1025, 1601, 1665])
 def test_step_equals_the_weight_streaming_kernel(rows):
-    """One decoding step of `rows` requests with the launch plan's own tiles (192, 256 and 320 rows with every remainder: the
-    gated gate/up form, an LM head of 297 strips, the narrow projections), against the same step without the tall kernel.
-    One layer: two correct implementations stay within the tolerance of the step tests."""
+    """One decoding step of `rows` requests in the launch plan's own tiles (an LM head of 297 strips, the narrow projections,
+    from 161 rows on the gated gate/up form), against the same step without the tall kernel.  One layer: two correct
+    implementations (the splits of a reduction differ) stay within the tolerance of the step tests."""
     import paper_2511_16193_amd as P
     d, ff, V = 256, 18944, 38016
     lw = {"ln1": bf16((d,), 0.05, 1) + 1, "wqkv": bf16((512, d), 0.02, 2), "wo": bf16((d, 256), 0.02, 3),
@@ -62,3 +63,61 @@ def test_step_equals_the_weight_streaming_kernel(rows):
     assert float((logits[0] - logits[1]).abs().max()) < LOGIT_TOL["bf16"]
     assert float(logits[0].std()) > 0.1
     ver.close()
+
+
+PAIRS = [(h, ht) for h in (3, 4, 5) for ht in range(h)]
+
+
+def tiles_of(h, ht, n):
+    """n tall tiles and, if there is a height for them, two short ones; the rows they cover but for 37 of the last."""
+    nt = 2 if ht else 0
+    return (h, n, ht, nt), 64 * (h * n + ht * nt) - 37
+
+
+@pytest.mark.parametrize("N,K,splits", [
+    (384, 64, 1),                     # two fills for a ring of three; the last strip half beyond the output
+    (384, 64, 2),                     # one fill a split
+    (384, 576, 3),                    # six fills a split
+    (65664, 64, 1),                   # 257 strips: two tall tiles a strip fill two rounds, the short ones stand beside them
+])
+@pytest.mark.parametrize("h,ht", PAIRS)
+def test_every_pair_of_heights_equals_the_weight_streaming_kernel(h, ht, N, K, splits):
+    """Both kernels add the slices of a split in the same order: equal bits.  float64 tolerance as above."""
+    from paper_2511_16193_amd import op_gemm_bf16_tall, op_gemm_bf16_ws, op_pack_rows, op_pack_weight
+    tall, rows = tiles_of(h, ht, 2 if N > 1000 else 1)
+    a, w = bf16((rows, K), 1.0, rows).to(DEV), bf16((N, K), 0.02, K).to(DEV)
+    ap, wp = op_pack_rows(a), op_pack_weight(w)
+    got = op_gemm_bf16_tall(ap, wp, rows, tall, splits)
+    if K % (64 * splits) == 0:
+        assert torch.equal(got, op_gemm_bf16_ws(ap, wp, rows, splits=splits, wide=False))
+    if N < 1000:
+        want = M.matmul_wt(a.cpu().float().numpy().astype(np.float64), w.cpu().float().numpy())
+        assert np.max(np.abs(got.cpu().numpy().astype(np.float64).sum(axis=0) - want)) < 1e-4
+
+
+@pytest.mark.parametrize("F,K", [(384, 64), (384, 640), (33024, 64)])
+@pytest.mark.parametrize("h,ht", PAIRS)
+def test_every_gated_pair_of_heights_equals_the_weight_streaming_kernel(h, ht, F, K):
+    from paper_2511_16193_amd import op_gemm_bf16_tall, op_pack_rows, op_pack_weight
+    tall, rows = tiles_of(h, ht, 2 if F > 1000 else 1)
+    a, w = bf16((rows, K), 1.0, rows).to(DEV), bf16((2 * F, K), 0.02, K).to(DEV)
+    ap, wp = op_pack_rows(a), op_pack_weight(w)
+    got = op_gemm_bf16_tall(ap, wp, rows, tall, gated=True)
+    assert torch.equal(got, op_gemm_bf16_tall(ap, wp, rows, None, gated=True))
+    if F < 1000:
+        x = a.cpu().double() @ w.cpu().double().T
+        gate, up = torch.nn.functional.silu(x[:, :F]), x[:, F:]
+        pack = lambda t: op_pack_rows(t.to(torch.bfloat16).to(DEV)).float()
+        want, slack = pack(gate * up), pack(gate.abs() + 1.1 * up.abs())
+        # sums within 1e-4 as above (silu's slope is 1.1 at most), then one bf16 spacing where a boundary lies between
+        assert bool(((got.float() - want).abs() <= 2.0 ** -7 * want.abs() + 1e-4 * slack).all())
+        assert float((got.float() != want).float().mean()) < 0.01
+
+
+@pytest.mark.parametrize("tall", [(2, 2, 0, 0), (6, 1, 0, 0), (4, 1, 4, 1), (4, 1, 2, 0), (4, 1, 0, 1), (4, 0, 2, 2), (4, 1, 0, 0), (4, 3, 0, 0), (3, 1, 1, 3)])
+def test_tiles_that_do_not_fit_the_rows_are_refused(tall):
+    """260 rows: heights that do not exist, short tiles without a height, rows left uncovered, tiles of padding alone."""
+    from paper_2511_16193_amd import SvError, op_gemm_bf16_tall
+    a, w = torch.zeros((288, 64), dtype=torch.bfloat16, device=DEV), torch.zeros((256, 64), dtype=torch.bfloat16, device=DEV)
+    with pytest.raises(SvError):
+        op_gemm_bf16_tall(a, w, 260, tall)
