@@ -37,7 +37,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
-PEAK_FP32_TFLOPS = 157.3       # MI355X fp32 vector ALUs
+PEAK_FP32_TFLOPS = 157.3       # MI355X fp32, matrix cores as well as vector ALUs
 
 DEFAULT_CONFIG = "cfg5"
 BRACKET_EVERY = 4          # steps of the timed region between two steps whose dominant-kind launches are bracketed by events
@@ -383,11 +383,11 @@ def main():
     attn_gbs = abytes / (attn_lms * 1e-3) / 1e9
     tag = args.config + (f"_k{k}" if args.config == "cfg3" else "")
     traffic, traffic_src = measured_traffic(tag) if args.batch is None else ({}, None)
-    fp32 = shape.dtype == "fp32"     # fp32 models: plain-ALU projections (fp32 vector peak) and the generic attention kernel
+    fp32 = shape.dtype == "fp32"     # fp32 models: projections on fp32 MFMA (its peak is that of the vector ALUs) and the generic attention
     gemm_peak = PEAK_FP32_TFLOPS if fp32 else PEAK_BF16_TFLOPS
     roofs = {
-        "gemm": {"kernel": "gemm_f32_kernel (all dense projections + LM head)" if fp32 else "gemm_bf16_ws_kernel (all dense projections + LM head)",
-                 "bound": "alu" if fp32 else "mfma", "achieved": gemm_tflops,
+        "gemm": {"kernel": "gemm_f32_kernel (all dense projections + LM head)" if fp32 else "gemm_bf16_ws_kernel or gemm_bf16_tall_kernel (all dense projections + LM head)",
+                 "bound": "mfma", "achieved": gemm_tflops,
                  "peak": gemm_peak, "unit": "TFLOP/s", "frac": gemm_tflops / gemm_peak,
                  "measured_peak": None if fp32 else mfma_meas, "frac_of_measured_peak": None if fp32 else gemm_tflops / mfma_meas,
                  "traffic": traffic.get("gemm"), "avg_launch_ms": gemm_lms, "launches_per_step": gemm_lps},
@@ -398,7 +398,7 @@ def main():
     }
     if moe_lps:
         moe_gbs = moe_bytes_per_layer(shape, T) / (moe_lms * 1e-3) / 1e9
-        roofs["moe"] = {"kernel": "moe_gemm_kernel<0>, <1> + router, grouping, combine (one layer's expert FFN)",
+        roofs["moe"] = {"kernel": "moe_gemm_kernel<0, MTMAX>, <1, MTMAX> + router, grouping, gather (one layer's expert FFN)",
                         "bound": "hbm", "achieved": moe_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                         "frac": moe_gbs / PEAK_HBM_GBS, "measured_peak": hbm_meas, "frac_of_measured_peak": moe_gbs / hbm_meas,
                         "traffic": traffic.get("moe"), "avg_launch_ms": moe_lms, "launches_per_step": moe_lps}
@@ -409,7 +409,7 @@ def main():
     for r in other:
         r["timed_in"] = "pre-pass of %d steps with every kind bracketed" % pre_steps
     samp_gbs = sampler_bytes_per_step(shape, B, N, k) / (samp_ms * 1e-3) / 1e9 if samp_ms > 0 else 0.0
-    sampler = {"kernel": "row_stats, accept, draw (+ merges), select: the whole accept / reject + draw stage of one step",
+    sampler = {"kernel": "row_stats, accept, race or cdf, finish: the whole accept / reject + draw stage of one step",
                "bound": "hbm", "achieved": samp_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": samp_gbs / PEAK_HBM_GBS,
                "frac_of_measured_peak": samp_gbs / hbm_meas, "ms_per_step": samp_ms,
                "bytes_per_step": sampler_bytes_per_step(shape, B, N, k)}

@@ -82,7 +82,9 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
             auto cu_rate = [&](int g) { return base * (g == 1 ? kOne[mt] : kTwo[mt]) * 1e6; };   // flop per microsecond
             for (int s = 1; s <= (allow_split ? max_splits : 1); ++s) {
                 if (slices_all % (4 * s) != 0) continue;
-                if ((K / s) % 128 != 0 && tiles > 5 && mt != 5) continue;     // short fills exist in the five-tile form only
+                // splits whose fills are short: beyond five tiles of rows only the five-tile form of them is considered (up to
+                // there a narrow strip has a form for every height; a wide one runs the five-tile form whatever its height)
+                if ((K / s) % 128 != 0 && tiles > 5 && mt != 5) continue;
                 const double slices = (double)slices_all / s;
                 const double wg_flop = 2.0 * 32 * mt * cols * 16 * slices;
                 const long long blocks = (long long)tiles_m * (N / cols) * s;
@@ -654,11 +656,12 @@ static double attn_list_keys(const std::vector<int>& lens, int kv_heads, std::ve
 //    One request of 6000 keys: pieces of 1024 take 22.2 + 7.2 us per layer (attention + merge), fine ones 13.4 + 5.2; seven
 //    requests of 900-5000 keys 23.8 + 6.0 against 21.4 + 4.9.
 //  - Else as above; a cut costs the merge launch as well.
-//  - Models with experts take no finer pieces and the coarser estimate: where a row's last kept and first dropped expert are
-//    close, the rounding of another order of the attention's sums picks the other one, and with the few rows of such a step
-//    that is 1-3 % of the logits (20 rows over 406-486 keys, eight inputs: 0.005-0.030 between pieces of 128 and of 1024
-//    keys, 0.000-0.009 with the same pieces).  It costs 6 us of a layer's attention at five requests of 700-3000 keys (14.9
-//    -> 20.7).
+//  - Models with experts keep the pieces of 1024 keys and more and the coarser estimate that they were first run with.  Neither
+//    order of the sums is the more exact one, but where a row's last kept and first dropped expert are close another order
+//    picks the other expert, and with the few rows of such a step that is 1-3 % of the logits (20 rows over 406-486 keys,
+//    eight inputs: 0.005-0.030 between pieces of 128 and of 1024 keys, 0.000-0.009 with the same pieces), as much as the
+//    path's results are held to from one version of the kernels to the next.  The price is 6 us of a layer's attention
+//    at five requests of 700-3000 keys (14.9 -> 20.7).
 static int pick_chunk(const sv_ctx* c, const Pass& ps) {
     if (c->attn_chunk_opt) return c->attn_chunk_opt;
     const int Hkv = c->model.n_kv_heads, G = c->model.n_q_heads / Hkv;
@@ -1015,7 +1018,7 @@ static int head_rows(sv_ctx* c, int M, float* logits) {
 extern "C" int verify_prefill(sv_ctx* c, int32_t id, const int32_t* tokens, int32_t n, float* last_logits) {
     if (!c || !tokens) return SV_EINVAL;
     if (n <= 0) return c->fail(SV_EINVAL, "prefill of %d tokens", n);
-    // a batch of one prompt: chunks of as many rows as the kernels take for a single request
+    // a batch of one prompt
     return verify_prefill_batch(c, &id, 1, tokens, n, &n, last_logits);
 }
 

@@ -371,6 +371,8 @@ __global__ __launch_bounds__(256, (NT == 1 || MT <= 3) ? 2 : 1) void gemm_bf16_w
 // A small work-group streams the whole reduction depth of its weight rows whatever its share of the products,
 // so the last round is bound by how often the strips are re-read from L2: 64 rows x 64 features (five readers of
 // 0.9 MB per half strip) take 26 us where 32 rows x 128 features (ten readers of 1.8 MB) took 35 us.
+// (Up-projections of more than 160 rows take the tall kernel by default: what reaches this one is 129 to 160 rows onto 33 to 48
+// thousand features, and more rows with the tall kernel switched off.)
 __global__ __launch_bounds__(256, 1) void gemm_bf16_ws_glu_mixed_kernel(
     const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out, int M, int N, int K,
     int tiles_m, int strips_main, int tiles_m2, int strips_tail) {
