@@ -142,7 +142,7 @@ def main():
     ap.add_argument("--attn-chunk", type=int, default=None, help="keys per split-KV chunk (tuning)")
     ap.add_argument("--attn-max-row-tiles", type=int, default=None, help="16-row tiles per attention work-group (tuning)")
     ap.add_argument("--gemm-tile", type=int, default=None, choices=[-1, 0, 1],
-                    help="256 x 256 projection kernel: -1 where the plan expects it to pay (default), 0 never, 1 wherever the shape allows (tuning)")
+                    help="tall projection kernel: -1 where the plan expects it to pay (default), 0 never, 1 wherever the shape allows (tuning)")
     ap.add_argument("--drafts", choices=["noisy-target", "independent", "one-hot"], default="noisy-target",
                     help="independent: drafts from q = softmax(N(0,1)) without any device decoding step, so that "
                          "every kernel launch of the process has the timed step's shape (used for profiles); "
