@@ -292,6 +292,9 @@ static hipError_t add_rmsnorm_t(float* h, const float* part, int S, const T* w, 
     // Few rows: the more threads the fewer round trips (five rows of 896 pieces: 6.0 us with 256 threads, 4.7 with 1024).
     // Many: as few idle lanes and registers as the width allows (800 rows of 1280 pieces and four planes in flight: eight
     // pieces for each of 256 threads 31.8 us, three for each of 512 17.8).
+    // In between the two are level and the line's place matters little: us of a layer's three norms, 1024 threads against 512, at
+    // 160 / 320 / 480 / 640 / 800 / 1280 rows: 896 pieces 18.5 / 25.2 / 29.4 / 40.2 / 41.1 / 56.3 against 19.0 / 25.3 / 29.5 / 38.9 /
+    // 37.8 / 54.0; 1280 pieces 22.5 / 32.7 / 31.4 / 50.6 / 54.1 / 72.4 against 24.0 / 32.6 / 32.3 / 51.4 / 54.2 / 73.2.
     const bool wide = T_ <= kWideNormRows;
     if (nq <= 512) launch(add_rmsnorm_kernel<T, 1, 512>, 512);
     else if (nq <= 1024 && wide) launch(add_rmsnorm_kernel<T, 1, 1024>, 1024);
