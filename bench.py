@@ -85,9 +85,9 @@ def attention_bytes_per_layer(s, lengths, n):
 
 
 def sampler_bytes_per_step(s, B, N, k):
-    """One pass over the logits (row statistics) plus, per chain, one logits row and one draft-distribution row for
-    the final draw."""
-    return (B * (1 + N * k) * s.vocab + B * N * 2 * s.vocab) * 4.0
+    """One pass over the logits (row statistics) plus, for the kept chain of every request, one logits row and one
+    draft-distribution row for the final draw."""
+    return (B * (1 + N * k) * s.vocab + B * 2 * s.vocab) * 4.0
 
 
 def cpu_baseline(case, n_seqs, lazy_weights):
