@@ -37,7 +37,10 @@ struct Stat { float m, s; int am; };
 
 // A thread's ids are loaded four at a time, kAhead loads per batch and the next batch in flight while one is worked on
 // (one new maximum and one rescale per batch, not per load); the exponentials are the hardware's base-2 ones on
-// pre-scaled arguments.  2304 rows of 152064: 292 us (4.8 TB/s); with work-groups of 1024 threads and one batch each 340.
+// pre-scaled arguments.  2304 rows of 152064: 259 us (5.4 TB/s); with both ways of reading in one kernel, at 86 registers instead
+// of 50, 299; with work-groups of 1024 threads and one batch each 340.
+// VEC: rows end with a whole piece of four ids.  Otherwise they are read one by one, and a NaN among them counts as no id.
+template <bool VEC>
 __global__ __launch_bounds__(NS) void row_stats_kernel(SampleArgs a, float inv_temp) {
     const int t = blockIdx.x, V = a.V, n = 1 + a.N * a.k;
     if (a.draft_lens && !row_counts(t % n, a.k, window_of(a, t / n))) return;
@@ -48,18 +51,17 @@ __global__ __launch_bounds__(NS) void row_stats_kernel(SampleArgs a, float inv_t
     int am = 0x7fffffff;
     const float c2 = inv_temp * 1.4426950408889634f;
     constexpr int kAhead = 4, STEP = 4 * NS * kAhead;
-    const bool vec = (V & 3) == 0;                         // rows end with a whole piece
     auto load = [&](int v0, floatx4 (&x)[kAhead]) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             const int v = v0 + u * 4 * NS;
             x[u] = floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-            if (vec) {
+            if (VEC) {
                 if (v < vend) x[u] = *reinterpret_cast<const floatx4_any*>(row + v);
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (v + i < vend && row[v + i] > -INFINITY) x[u][i] = row[v + i];       // a NaN counts as no id at all
+                    if (v + i < vend) x[u][i] = row[v + i];
             }
         }
     };
@@ -82,6 +84,15 @@ __global__ __launch_bounds__(NS) void row_stats_kernel(SampleArgs a, float inv_t
             for (int u = 0; u < kAhead; ++u)
                 add += (__builtin_amdgcn_exp2f((x[u][0] - m) * c2) + __builtin_amdgcn_exp2f((x[u][1] - m) * c2)) +
                        (__builtin_amdgcn_exp2f((x[u][2] - m) * c2) + __builtin_amdgcn_exp2f((x[u][3] - m) * c2));
+            if (!VEC && __builtin_expect(add != add, 0)) {
+                add = 0.f;
+#pragma unroll 1
+                for (int u = 0; u < 4 * kAhead; ++u) {
+                    const int v = v0 + (u >> 2) * 4 * NS + (u & 3);
+                    const float y = v < vend ? row[v] : -INFINITY;
+                    add += y > -INFINITY ? __builtin_amdgcn_exp2f((y - m) * c2) : 0.f;
+                }
+            }
             s += add;
         }
     };
@@ -508,7 +519,8 @@ hipError_t sample_verify(const SampleArgs& args, hipStream_t st) {
     const int T = a.B * (1 + a.N * a.k);
     a.stat_parts = vocab_parts(T, a.V);
     a.draw_parts = a.sample_mode == 1 ? vocab_parts(a.verify_mode == 2 ? T : a.B, a.V) : 1;
-    hipLaunchKernelGGL(row_stats_kernel, dim3(T, a.stat_parts), dim3(NS), 0, st, a, 1.0f / a.temperature);
+    if (a.V % 4 == 0) hipLaunchKernelGGL(row_stats_kernel<true>, dim3(T, a.stat_parts), dim3(NS), 0, st, a, 1.0f / a.temperature);
+    else hipLaunchKernelGGL(row_stats_kernel<false>, dim3(T, a.stat_parts), dim3(NS), 0, st, a, 1.0f / a.temperature);
     if (a.verify_mode == 0) {
         hipLaunchKernelGGL(accept_kernel<0>, dim3(a.B), dim3(64), 0, st, a);
     } else if (a.verify_mode == 2) {
