@@ -859,7 +859,7 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
         acc *= alpha;
         m = m_new;
         __syncthreads();
-        for (int tile = grp; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) {
+        auto weigh = [&](int tile, auto masked) __attribute__((always_inline)) {
             const int k0 = c0 + tile * TILE_KEYS;           // a tile lies inside a page
             const T* vp = pool + kv_v_index(a.geom, a.layer, pages[k0 / a.geom.page_size], hkv, k0 % a.geom.page_size, dim);
 #pragma unroll
@@ -869,11 +869,14 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float w0 = p[tile * TILE_KEYS + 4 * g + e], w1 = p[tile * TILE_KEYS + 16 + 4 * g + e];
-                    acc = w0 < 0.f ? acc : fmaf(w0, v[e], acc);
-                    acc = w1 < 0.f ? acc : fmaf(w1, v[4 + e], acc);
+                    acc = decltype(masked)::value && w0 < 0.f ? acc : fmaf(w0, v[e], acc);
+                    acc = decltype(masked)::value && w1 < 0.f ? acc : fmaf(w1, v[4 + e], acc);
                 }
             }
-        }
+        };
+        int tile = grp;                                     // every row sees every cached key: those tiles first
+        for (; tile < CK / TILE_KEYS && c0 + (tile + 1) * TILE_KEYS <= L; tile += GROUPS) weigh(tile, std::false_type{});
+        for (; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) weigh(tile, std::true_type{});
         __syncthreads();
     }
     acc_sh[grp][dim] = acc;
