@@ -419,7 +419,7 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     const int nfill = k_per_split / (16 * KA), kslices = K / 16, ks0 = sp * (k_per_split / 16);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave >> 2, wn = wave & 3, l32 = lane & 31, lg = lane >> 5;
+    const int wm = wave >> 2, wn = wave & 3, l16 = lane & 15, lg = lane >> 4;
     const int m_tiles = (M + 31) / 32;
 
     // This wave's share of a fill.  Activations: one of the 2 RW row tiles (RW = 5: waves 0 and 1 a second one; RW < 4: some
@@ -451,54 +451,63 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
         if (loads_a2) wait_vmcnt<6 * L>(); else if (loads_a) wait_vmcnt<4 * L>(); else wait_vmcnt<2 * L>();
     };
 
-    // Operands of a slice, two sets.  The LDS reads are placed by hand, with hand-counted waits: the compiler would wait for
-    // every read as soon as a direct-to-LDS load is in flight.  It takes the reads' registers as written at once, so a
-    // set is waited for in the basic block that reads it (a branch in between may copy registers still in flight).
-    u32x4 a[2][RW], b[2][2];
+    // Operands of a fill.  Lane 16 g + r of a 16x16x32 operand holds row r, elements 8 g .. 8 g + 7 of the fill's 32: slice
+    // g / 2 of the packed order, half g % 2 of its 16.  Weights: four 16-feature operands, two sets (this fill's, the next
+    // one's); activations: 2 RW 16-row operands, in two halves.  The LDS reads are placed by hand, with hand-counted waits: the
+    // compiler would wait for every read as soon as a direct-to-LDS load is in flight.  It takes the reads' registers as written
+    // at once, so what a half reads is waited for in the basic block that reads it (a branch in between may copy registers
+    // still in flight).
+    u32x4 a[2][RW], b[2][4];
     const uint32_t lds0 = (uint32_t)(uintptr_t)SV_LDS_PTR(tall_lds);
-    const uint32_t a_off = lds0 + wm * RW * KA * 1024 + lane * 16;
-    const uint32_t b_off = lds0 + B_OFF + (GLU ? wn * 1024 : (wn >> 1) * KA * 4096 + (wn & 1) * 2048) + lane * 16;
-    constexpr int B_STEP = GLU ? KA * 4096 : 1024;        // from the wave's first feature tile to its second
+    const uint32_t in_piece = (lg & 1) * 512 + l16 * 16;
+    const uint32_t a_off = lds0 + wm * RW * KA * 1024 + (lg >> 1) * 1024 + in_piece;
+    const uint32_t b_off = lds0 + B_OFF + (GLU ? wn * 1024 : (wn >> 1) * KA * 4096 + (wn & 1) * 2048) + (lg >> 1) * 4096 + in_piece;
+    constexpr int B_STEP = GLU ? KA * 4096 : 1024;        // from the wave's first 32 features to its second
     uint32_t a_addr = a_off, b_addr = b_off;
-    auto read = [&](auto set, auto which, auto slice) __attribute__((always_inline)) {   // which: 0, 1 weights, then activations
-        constexpr int SET = decltype(set)::value, R = decltype(which)::value, S = decltype(slice)::value;
-        if constexpr (R < 2) lds_read16<R * B_STEP + S * 4096>(b[SET][R], b_addr);
-        else lds_read16<(R - 2) * KA * 1024 + S * 1024>(a[SET][R - 2], a_addr);
+    auto read_a = [&](auto half, auto which) __attribute__((always_inline)) {
+        constexpr int H = decltype(half)::value, J = decltype(which)::value, X = H * RW + J;
+        lds_read16<(X >> 1) * KA * 1024 + (X & 1) * 256>(a[H][J], a_addr);
     };
-    auto wait_set = [&](auto set) __attribute__((always_inline)) {
-        constexpr int SET = decltype(set)::value;
-        lds_landed(b[SET][0]);
-        lds_landed_too(b[SET][1]);
-#pragma unroll
-        for (int j = 0; j < RW; ++j) lds_landed_too(a[SET][j]);
+    auto read_b = [&](auto set, auto which) __attribute__((always_inline)) {
+        constexpr int S = decltype(set)::value, I = decltype(which)::value;
+        lds_read16<(I >> 1) * B_STEP + (I & 1) * 256>(b[S][I], b_addr);
     };
-    floatx16 acc[2][RW];                                  // [feature tile][row tile]
+    auto wait_a = [&](auto half) __attribute__((always_inline)) {
+        constexpr int H = decltype(half)::value;
+        lds_landed(a[H][0]);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int j = 1; j < RW; ++j) lds_landed_too(a[H][j]);
+    };
+    auto wait_b = [&](auto set) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < RW; ++j)
+        for (int i = 0; i < 4; ++i) lds_landed_too(b[decltype(set)::value][i]);
+    };
+    floatx4 acc[4][2 * RW];                               // [feature operand][row operand]
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    // The products of set SET, one read of the given slice into the other set after each; with `base` the loads of the
-    // fill NB ahead before the last two (only where every wave loads the same: a branch must not come between).
-    auto multiply = [&](auto set, auto next, auto loads, unsigned char* base) __attribute__((always_inline)) {
-        constexpr int SET = decltype(set)::value, NR = RW + 2, NM = 2 * RW;
-        static_assert(NR <= NM + 1, "a read after each product");
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2 * RW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // The products of half H of the rows with weight set S, a read after each: in half 0 the activations of half 1, in half 1 the
+    // next fill's weights and the activations of its half 0; there also the loads of the fill NB ahead, before the last products
+    // (only where every wave loads the same: a branch must not come between).  Weights first, so that a lane holds one
+    // row and four consecutive features.
+    auto multiply = [&](auto half, auto set, unsigned char* base) __attribute__((always_inline)) {
+        constexpr int H = decltype(half)::value, S = decltype(set)::value, NM = 4 * RW, NR = H == 0 ? RW : RW + 4;
         __builtin_amdgcn_sched_barrier(0);
         static_for<NM>([&](auto mi) __attribute__((always_inline)) {
-            constexpr int m = decltype(mi)::value, i = m & 1, j = m >> 1;
-            const bf16x8 wf = __builtin_bit_cast(bf16x8, b[SET][i]), af = __builtin_bit_cast(bf16x8, a[SET][j]);
-            // gated form: weights first, so that a lane holds one row and consecutive features; plain form: activations
-            // first, so that a lane holds one feature and a half wave writes 128 contiguous bytes
-            acc[i][j] = GLU ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af, acc[i][j], 0, 0, 0)
-                            : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, wf, acc[i][j], 0, 0, 0);
+            constexpr int m = decltype(mi)::value, i = m & 3, j = m >> 2;
+            acc[i][H * RW + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[S][i]), __builtin_bit_cast(bf16x8, a[H][j]),
+                                                                         acc[i][H * RW + j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             constexpr int first = m < NR ? m : NR, last = m + 1 == NM ? NR : m + 1 < NR ? m + 1 : NR;
-            static_for<last - first>([&](auto r) __attribute__((always_inline)) {
-                read(std::integral_constant<int, 1 - SET>{}, std::integral_constant<int, first + decltype(r)::value>{}, next);
+            static_for<last - first>([&](auto rr) __attribute__((always_inline)) {
+                constexpr int r = first + decltype(rr)::value;
+                if constexpr (H == 0) read_a(std::integral_constant<int, 1>{}, std::integral_constant<int, r>{});
+                else if constexpr (r < 4) read_b(std::integral_constant<int, 1 - S>{}, std::integral_constant<int, r>{});
+                else read_a(std::integral_constant<int, 0>{}, std::integral_constant<int, r - 4>{});
                 __builtin_amdgcn_sched_barrier(0);
             });
-            if (decltype(loads)::value && RW == 4 && m == NM - 2) { request(base); __builtin_amdgcn_sched_barrier(0); }
+            if (H == 1 && RW == 4 && m == NM - 4) { request(base); __builtin_amdgcn_sched_barrier(0); }
         });
     };
 
@@ -508,12 +517,14 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     for (int i = 0; i < NB; ++i) { request(tall_lds + i * FILL); advance(); }
     wait_fills(std::integral_constant<int, NB - 1>{});
     __builtin_amdgcn_s_barrier();
-    static_for<RW + 2>([&](auto r) __attribute__((always_inline)) { read(i0, r, i0); });
-    wait_set(i0);
+    static_for<4>([&](auto r) __attribute__((always_inline)) { read_b(i0, r); });
+    static_for<RW>([&](auto r) __attribute__((always_inline)) { read_a(i0, r); });
+    wait_a(i0);
+    wait_b(i0);
     int slot = 0;
-    for (int f = 0; f < nfill; ++f) {
-        multiply(i0, i1, std::false_type{}, tall_lds);
-        wait_set(i1);
+    auto fill = [&](auto set) __attribute__((always_inline)) {
+        multiply(i0, set, tall_lds);
+        wait_a(i1);
         // This wave holds all it needs of the fill and its share of the next one has landed; after the barrier so has
         // everyone's, and nobody reads this fill's place in the ring any more.
         wait_fills(std::integral_constant<int, NB - 2>{});
@@ -522,52 +533,50 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
         slot = slot + 1 == NB ? 0 : slot + 1;
         a_addr = a_off + slot * FILL;
         b_addr = b_off + slot * FILL;
-        multiply(i1, i0, std::true_type{}, base);
-        wait_set(i0);
+        multiply(i1, set, base);
+        wait_a(i0);
+        wait_b(std::integral_constant<int, 1 - decltype(set)::value>{});
         if (RW != 4) request(base);
         advance();
-    }
+    };
+    int f = 0;
+    for (; f + 1 < nfill; f += 2) { fill(i0); fill(i1); }
+    if (f < nfill) fill(i0);
     wait_vmcnt<0>();                                      // nothing of this work-group may land in LDS after it has gone
 
-    if (GLU) {
+    // acc[i][x][e] <-> row m0 + 32 RW wm + 16 x + l16, feature 4 lg + e of the wave's 16-feature operand i
+    if (GLU) {                                            // operands 0, 1: gate rows of 32 features, 2, 3: their up rows
         const int F = N / 2;
         bf16_t* act = reinterpret_cast<bf16_t*>(out);
         const int fs = (tn * 128 + wn * 32) / 16;
 #pragma unroll
-        for (int j = 0; j < RW; ++j) {
-            const int mt = m0 / 32 + wm * RW + j;
+        for (int x = 0; x < 2 * RW; ++x) {
+            const int mt = m0 / 32 + wm * RW + (x >> 1);
             if (mt < m_tiles) {
-                bf16_t* dst = act + ((int64_t)mt * (F / 16) + fs) * 512;
+                bf16_t* dst = act + ((int64_t)mt * (F / 16) + fs) * 512 + ((lg >> 1) * 32 + (x & 1) * 16 + l16) * 8 + 4 * (lg & 1);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
+                for (int i = 0; i < 2; ++i) {
                     float r[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float g = acc[0][j][4 * q + e];
-                        r[e] = g / (1.0f + expf(-g)) * acc[1][j][4 * q + e];
+                        const float g = acc[i][x][e];
+                        r[e] = g / (1.0f + expf(-g)) * acc[2 + i][x][e];
                     }
-                    u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
-                    *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
+                    *reinterpret_cast<u32x2*>(dst + i * 512) = u32x2{pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
                 }
             }
         }
         return;
     }
-    // acc[i][j][4 q + r] <-> row m0 + 32 (RW wm + j) + 8 q + 4 lg + r, feature 256 tn + 64 wn + 32 i + l32
     if (tn * 256 + wn * 64 >= N) return;
-    float* dst = out + (int64_t)sp * M * N;
+    float* dst = out + (int64_t)sp * M * N + tn * 256 + wn * 64 + 4 * lg;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int n = tn * 256 + wn * 64 + i * 32 + l32;
+    for (int x = 0; x < 2 * RW; ++x) {
+        const int m = m0 + wm * RW * 32 + 16 * x + l16;
+        if (m < M) {
 #pragma unroll
-        for (int j = 0; j < RW; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = m0 + (wm * RW + j) * 32 + 8 * q + 4 * lg + r;
-                    if (m < M) dst[(int64_t)m * N + n] = acc[i][j][4 * q + r];
-                }
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<floatx4_any*>(dst + (int64_t)m * N + 16 * i) = acc[i][x];
+        }
     }
 }
 
