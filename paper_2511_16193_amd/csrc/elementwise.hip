@@ -241,7 +241,7 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const float* __restrict__ p
         g += src[s * stride + f];
         u += src[s * stride + F + f];
     }
-    act[act_index(t, f, F, packed)] = f2bf(g / (1.0f + expf(-g)) * u);
+    act[act_index(t, f, F, packed)] = f2bf(silu_mul(g, u));
 }
 
 template <typename T>

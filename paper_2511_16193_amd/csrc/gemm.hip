@@ -287,8 +287,7 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
                     float r[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float g = acc[0][j][4 * q + i];
-                        r[i] = g / (1.0f + expf(-g)) * acc[NT - 1][j][4 * q + i];
+                        r[i] = silu_mul(acc[0][j][4 * q + i], acc[NT - 1][j][4 * q + i]);
                     }
                     u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
                     *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
@@ -328,7 +327,7 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
                         for (int i = 0; i < 4; ++i) {
                             const float g = acc[0][j][4 * q + i];
                             const float u = xbuf[((wave * MT + j) * 16 + 4 * q + i) * 64 + lane];
-                            r[i] = g / (1.0f + expf(-g)) * u;
+                            r[i] = silu_mul(g, u);
                         }
                         u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
                         *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
@@ -409,6 +408,16 @@ template <int OFF> __device__ __forceinline__ void lds_read16(u32x4& d, uint32_t
 __device__ __forceinline__ void lds_landed(u32x4& d) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d)); }
 __device__ __forceinline__ void lds_landed_too(u32x4& d) { asm volatile("" : "+v"(d)); }     // no use of d moves above the wait
 
+// 1 KB from global memory straight into LDS: lane l's 16 bytes at base + lane_off go to LDS address lds + 16 l (base and lds the same for
+// all lanes); dma1_below: only in waves below N.  As one statement, so that a load which only some waves make is no branch to the compiler.
+__device__ __forceinline__ void dma1(const char* base, uint32_t lane_off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
+}
+template <int N> __device__ __forceinline__ void dma1_below(int wave, const char* base, uint32_t lane_off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_cmp_lt_u32 %3, %4\n\ts_cbranch_scc0 .Lno_dma%=\n\tglobal_load_lds_dwordx4 %1, %2\n.Lno_dma%=:"
+                 : : "s"(lds), "v"(lane_off), "s"(base), "s"(wave), "n"(N) : "memory", "scc");
+}
+
 template <bool GLU, int RW>
 __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
                                                     int M, int N, int K, int k_per_split, int m0, int tn, int sp) {
@@ -422,33 +431,43 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     const int wm = wave >> 2, wn = wave & 3, l16 = lane & 15, lg = lane >> 4;
     const int m_tiles = (M + 31) / 32;
 
-    // This wave's share of a fill.  Activations: one of the 2 RW row tiles (RW = 5: waves 0 and 1 a second one; RW < 4: some
-    // waves none); weights: half of one 4 KB run (strip, slice).  Row tiles beyond M and a strip beyond N (N an odd
-    // multiple of 128) are read as the last one and never stored.
-    const bool loads_a = RW >= 4 || wave < 2 * RW, loads_a2 = RW == 5 && wave < 2;
-    auto row_tile = [&](int i) {
-        const int mt = m0 / 32 + i;
-        return reinterpret_cast<const char*>(Ap + ((int64_t)(mt < m_tiles ? mt : m_tiles - 1) * kslices + ks0) * 512) + lane * 16;
-    };
-    const char* a_src = row_tile(wave);
-    const char* a_src2 = row_tile(RW == 5 ? 8 + wave : wave);
-    const int run = wave >> 1, half = wave & 1, strip = run / KA, sl = run % KA;
-    const int strip_n = 2 * tn + strip;
-    const int strip_g = GLU ? (strip == 0 ? tn : N / 256 + tn) : strip_n < N / 128 ? strip_n : N / 128 - 1;
-    const char* w_src = reinterpret_cast<const char*>(Wp + (((int64_t)strip_g * kslices + ks0 + sl) * 4 + 2 * half) * 512) + lane * 16;
-    const int a_dst = wave * KA * 1024, w_dst = B_OFF + run * 4096 + half * 2048;
+    // A fill is P pieces of 1 KB: the activations' 2 RW row tiles x 2 slices, then (strip, slice, feature tile) of the weights.  Wave w
+    // requests pieces w, w + 8, ... .  Row tiles beyond M and a strip beyond N (N an odd multiple of 128) are read as the last
+    // one and never stored.
+    constexpr int A_P = KA * 2 * RW, P = A_P + KA * 8, EACH = P / 8, EXTRA = P % 8;
+    const bool extra = wave < EXTRA;
+    const char* src[EACH + 1];
+    int step[EACH + 1];
+#pragma unroll
+    for (int q = 0; q <= EACH; ++q) {
+        const int p = min(wave + 8 * q, P - 1);
+        if (p < A_P) {
+            const int mt = min(m0 / 32 + p / KA, m_tiles - 1);
+            src[q] = reinterpret_cast<const char*>(Ap + ((int64_t)mt * kslices + ks0 + p % KA) * 512);
+            step[q] = KA * 1024;
+        } else {
+            const int w = p - A_P, strip = w / (4 * KA), strip_n = 2 * tn + strip;
+            const int strip_g = GLU ? (strip == 0 ? tn : N / 256 + tn) : min(strip_n, N / 128 - 1);
+            src[q] = reinterpret_cast<const char*>(Wp + (((int64_t)strip_g * kslices + ks0 + w / 4 % KA) * 4 + w % 4) * 512);
+            step[q] = KA * 4096;
+        }
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)SV_LDS_PTR(tall_lds), lane_off = lane * 16;
     int ahead = 0;
-    auto request = [&](unsigned char* base) __attribute__((always_inline)) {
-        if (loads_a) dma2(a_src, SV_LDS_PTR(base + a_dst));
-        if (loads_a2) dma2(a_src2, SV_LDS_PTR(base + a_dst + 8 * KA * 1024));
-        dma2(w_src, SV_LDS_PTR(base + w_dst));
+    auto request = [&](auto which, uint32_t base) __attribute__((always_inline)) {
+        constexpr int Q = decltype(which)::value;
+        if constexpr (Q < EACH) dma1(src[Q], lane_off, base + (wave + 8 * Q) * 1024);
+        else if constexpr (EXTRA > 0) dma1_below<EXTRA>(wave, src[Q], lane_off, base + (wave + 8 * Q) * 1024);
     };
     auto advance = [&]() __attribute__((always_inline)) {  // past the end: the last fill again, so that the counts below hold
-        if (++ahead < nfill) { a_src += KA * 1024; a_src2 += KA * 1024; w_src += KA * 4096; }
+        if (++ahead < nfill) {
+#pragma unroll
+            for (int q = 0; q <= EACH; ++q) src[q] += step[q];
+        }
     };
     auto wait_fills = [&](auto in_flight) __attribute__((always_inline)) {   // all but the newest in_flight fills have landed
         constexpr int L = decltype(in_flight)::value;
-        if (loads_a2) wait_vmcnt<6 * L>(); else if (loads_a) wait_vmcnt<4 * L>(); else wait_vmcnt<2 * L>();
+        if (EXTRA > 0 && extra) wait_vmcnt<(EACH + 1) * L>(); else wait_vmcnt<EACH * L>();
     };
 
     // Operands of a fill.  Lane 16 g + r of a 16x16x32 operand holds row r, elements 8 g .. 8 g + 7 of the fill's 32: slice
@@ -458,7 +477,6 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     // at once, so what a half reads is waited for in the basic block that reads it (a branch in between may copy registers
     // still in flight).
     u32x4 a[2][RW], b[2][4];
-    const uint32_t lds0 = (uint32_t)(uintptr_t)SV_LDS_PTR(tall_lds);
     const uint32_t in_piece = (lg & 1) * 512 + l16 * 16;
     const uint32_t a_off = lds0 + wm * RW * KA * 1024 + (lg >> 1) * 1024 + in_piece;
     const uint32_t b_off = lds0 + B_OFF + (GLU ? wn * 1024 : (wn >> 1) * KA * 4096 + (wn & 1) * 2048) + (lg >> 1) * 4096 + in_piece;
@@ -488,10 +506,11 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
 #pragma unroll
         for (int j = 0; j < 2 * RW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     // The products of half H of the rows with weight set S, a read after each: in half 0 the activations of half 1, in half 1 the
-    // next fill's weights and the activations of its half 0; there also the loads of the fill NB ahead, before the last products
-    // (only where every wave loads the same: a branch must not come between).  Weights first, so that a lane holds one
+    // next fill's weights and the activations of its half 0; there also the requests of the fill NB ahead, spread over the products: the
+    // texture path takes one every 17 cycles from the whole work-group, and a wave whose request waits there does not
+    // multiply.  Weights first, so that a lane holds one
     // row and four consecutive features.
-    auto multiply = [&](auto half, auto set, unsigned char* base) __attribute__((always_inline)) {
+    auto multiply = [&](auto half, auto set, uint32_t base) __attribute__((always_inline)) {
         constexpr int H = decltype(half)::value, S = decltype(set)::value, NM = 4 * RW, NR = H == 0 ? RW : RW + 4;
         __builtin_amdgcn_sched_barrier(0);
         static_for<NM>([&](auto mi) __attribute__((always_inline)) {
@@ -507,14 +526,21 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
                 else read_a(std::integral_constant<int, 0>{}, std::integral_constant<int, r - 4>{});
                 __builtin_amdgcn_sched_barrier(0);
             });
-            if (H == 1 && RW == 4 && m == NM - 4) { request(base); __builtin_amdgcn_sched_barrier(0); }
+            constexpr int NQ = EACH + (EXTRA > 0), q = (m * NQ + NM - 1) / NM;      // request q after product q NM / NQ
+            if constexpr (H == 1 && q < NQ && q * NM / NQ == m) {
+                request(std::integral_constant<int, q>{}, base);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         });
     };
 
     const std::integral_constant<int, 0> i0;
     const std::integral_constant<int, 1> i1;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) { request(tall_lds + i * FILL); advance(); }
+    for (int i = 0; i < NB; ++i) {
+        static_for<EACH + 1>([&](auto q) __attribute__((always_inline)) { request(q, lds0 + i * FILL); });
+        advance();
+    }
     wait_fills(std::integral_constant<int, NB - 1>{});
     __builtin_amdgcn_s_barrier();
     static_for<4>([&](auto r) __attribute__((always_inline)) { read_b(i0, r); });
@@ -523,20 +549,19 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     wait_b(i0);
     int slot = 0;
     auto fill = [&](auto set) __attribute__((always_inline)) {
-        multiply(i0, set, tall_lds);
+        multiply(i0, set, lds0);
         wait_a(i1);
         // This wave holds all it needs of the fill and its share of the next one has landed; after the barrier so has
         // everyone's, and nobody reads this fill's place in the ring any more.
         wait_fills(std::integral_constant<int, NB - 2>{});
         __builtin_amdgcn_s_barrier();
-        unsigned char* base = tall_lds + slot * FILL;
+        const uint32_t base = lds0 + slot * FILL;
         slot = slot + 1 == NB ? 0 : slot + 1;
         a_addr = a_off + slot * FILL;
         b_addr = b_off + slot * FILL;
         multiply(i1, set, base);
         wait_a(i0);
         wait_b(std::integral_constant<int, 1 - decltype(set)::value>{});
-        if (RW != 4) request(base);
         advance();
     };
     int f = 0;
@@ -559,8 +584,7 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
                     float r[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float g = acc[i][x][e];
-                        r[e] = g / (1.0f + expf(-g)) * acc[2 + i][x][e];
+                        r[e] = silu_mul(acc[i][x][e], acc[2 + i][x][e]);
                     }
                     *reinterpret_cast<u32x2*>(dst + i * 512) = u32x2{pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
                 }
@@ -901,7 +925,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (m < M && n + e < N)
-                            out[(int64_t)m * N + n + e] = GLU ? acc[0][0][e] / (1.0f + expf(-acc[0][0][e])) * s[e] : s[e];
+                            out[(int64_t)m * N + n + e] = GLU ? silu_mul(acc[0][0][e], s[e]) : s[e];
                 }
             }
         return;
@@ -917,7 +941,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
             for (int e = 0; e < 4; ++e)
                 if (m < M && n + e < N)
                     out[(int64_t)m * N + n + e] =
-                        GLU ? acc[0][j][e] / (1.0f + expf(-acc[0][j][e])) * acc[NT - 1][j][e] : acc[i][j][e];
+                        GLU ? silu_mul(acc[0][j][e], acc[NT - 1][j][e]) : acc[i][j][e];
         }
     }
 }

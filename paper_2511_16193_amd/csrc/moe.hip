@@ -437,7 +437,7 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
                         for (int i = 0; i < 4; ++i) {
                             const float g = acc[j][4 * q + i];
                             const float u = xbuf[((wave * MT + j) * 16 + 4 * q + i) * 64 + lane];
-                            r[i] = g / (1.0f + expf(-g)) * u;
+                            r[i] = silu_mul(g, u);
                         }
                         // features 8q + 4 lg .. +3 of this wave's 32: slice q/2, half q%2, elements 4 lg ..
                         u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
