@@ -46,8 +46,10 @@ int sv_op_gemm_plan(int M, int N, int K, int *splits, int *wide, int *row_tiles)
 
 /* The launch that a verification step, or a prefill pass, makes for a packed projection of M rows (HOST pointers out).
  * form 0: QKV, O or down (the reduction may be split), 1: LM head, 2: gate/up with SwiGLU (N = 2 d_ff gate and up rows).
- * tall[0] != 0: sv_op_gemm_bf16_tall with these tiles and *splits; tall[0] == 0: sv_op_gemm_bf16_ws with *splits, *wide and
- * *row_tiles, or for form 2 sv_op_gemm_bf16_tall without tiles.  Host arithmetic only.  N % 128 == 0 (form 2: 256), K % 64 == 0. */
+ * *wide > 1: sv_op_gemm_bf16_strip of *wide features with *splits and 2 * tall[0] row tiles, or *row_tiles where tall[0] == 0.
+ * Else tall[0] != 0: sv_op_gemm_bf16_tall with these tiles and *splits; tall[0] == 0: sv_op_gemm_bf16_ws with *splits, *wide and
+ * *row_tiles, or for form 2 sv_op_gemm_bf16_tall without tiles.  (In a model with experts a strip has the splits of the launch that
+ * it replaces.)  Host arithmetic only.  N % 128 == 0 (form 2: 256), K % 64 == 0. */
 int sv_op_gemm_step_plan(int M, int N, int K, int form, int *splits, int *wide, int *row_tiles, int *tall);
 
 /* The tall packed-operand kernel in given tiles: tall (HOST) = {h, n, ht, nt}, n tiles of 64 h rows x 256 features along the rows,
@@ -57,6 +59,12 @@ int sv_op_gemm_step_plan(int M, int N, int K, int form, int *splits, int *wide, 
  * same by the weight-streaming kernel.  N % 128 == 0, K % 64 == 0, K % (32 * splits) == 0. */
 int sv_op_gemm_bf16_tall(const void *Ap, const void *Wp, void *out, int M, int N, int K, int splits, int gated,
                          const int *tall, void *stream);
+
+/* The narrow-strip packed-operand kernel: one work-group holds all M rows, as row_tiles (1..5, 6, 8 or 10) tiles of 32, and a strip of
+ * 128, 160 or 224 features (gated: half of them gate rows, half the up rows of the same features).  out, gated, the sums and
+ * the limits on N, K and splits as for sv_op_gemm_bf16_tall. */
+int sv_op_gemm_bf16_strip(const void *Ap, const void *Wp, void *out, int M, int N, int K, int splits, int gated, int row_tiles,
+                          int features, void *stream);
 
 /* Reorder row-major bf16 activations src [M, K] into dst (ceil(M/32)*32*K elements) in the order the
  * weight-streaming kernel reads them: [ceil(M/32)][K/16][64 lanes][8 elements], lane 32*g + r of a fragment
@@ -166,8 +174,8 @@ int sv_probe_mfma_valu(float *sink, int iters, int valu_per_mfma, int waves_per_
 
 /* Tuning / diagnostic knobs of a context.
  *   SV_OPT_GEMM_VARIANT  work-group tile of the row-major bf16 projections (0..2; -1 = per shape, default)
- *   SV_OPT_GEMM_TILE  the tall kernel for packed projections: -1 = where the launch plan expects it to pay
- *                     (default), 0 = never, 1 = with 256-row tiles wherever the shape allows (output features a multiple of 256)
+ *   SV_OPT_GEMM_TILE  kernels of the packed projections: -1 = as the launch plan expects it to pay (default), 0 = the
+ *                     weight-streaming kernel only, 1 = the tall kernel with 256-row tiles wherever the shape allows (output features a multiple of 256)
  *   SV_OPT_ATTN_GENERIC  1 = always use the generic attention, a work-group per row and head (default 0)
  *   SV_OPT_ATTN_MIN_ROW_TILES  lower bound (1..4) on the 16-row tiles the bf16 attention is built for
  *   SV_OPT_ATTN_MAX_ROW_TILES  most 16-row tiles (1..4, default 4) one work-group of the bf16 attention takes;

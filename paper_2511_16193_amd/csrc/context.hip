@@ -60,11 +60,11 @@ int pick_splits(int M, int N, int K) {
 // fit to a sweep of every (tiles, width, splits) over thirty shapes of the benchmark models on MI355X (rows 5 to
 // 2304), except the lone work-group's pace, which is taken from whole steps (cold weights); on the sweep the plan
 // chosen was within 0.3 % of the best on average and 4.5 % at worst.
-struct WsPlan { int splits; bool wide; int row_tiles; double us; TallTiles tall; };   // tall.n > 0: the tall kernel with those tiles
+struct WsPlan { int splits; bool wide; int row_tiles; double us; TallTiles tall; StripTile strip; };   // strip.tiles > 0: a strip; tall.n > 0: the tall kernel
 WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplitsWs) {
     const int slices_all = K / 16;
     const int tiles = (M + 31) / 32;
-    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M), 1e30, {}};
+    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M), 1e30, {}, {}};
     // up to 160 rows: one work-group along the rows (cutting so few rows only multiplies the readers of a strip)
     const int mt_lo = tiles <= 5 ? tiles : 1, mt_hi = tiles <= 5 ? tiles : 5;
     for (int mt = mt_lo; mt <= mt_hi; ++mt)
@@ -98,7 +98,7 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
                 t = std::max(t, (double)N * K * 2.0 / 4.98e6);                // a weight stream cannot beat the memory system
                 if (s > 1) t += (double)s * M * N * 4.0 / 5.4e6 + (double)(s - 1) * M * N * 4.0 / 4.0e6;   // planes written here, read by the consumer
                 t += 2.3;
-                if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t, {}};
+                if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t, {}, {}};
             }
         }
     return best;
@@ -110,13 +110,54 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
 // down 282 against 263); the tall ones take theirs.
 // us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
 // 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
-// tile_mode: -1 = this rule, 0 = never the tall kernel, 1 = 256-row tiles wherever the width allows.
-WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, int max_splits = kMaxSplitsWs) {
-    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, gemm_bf16_tall_256(M)};
-    const WsPlan ws = plan_ws(M, N, K, allow_split, max_splits);
-    if (tile_mode == 0 || M <= 128) return ws;
-    const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
-    return t.us < 1.10 * ws.us ? WsPlan{t.splits, true, 0, t.us, t.tiles} : ws;
+// Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip, which is how a step of
+// few rows finds it.  Against it the weight-streaming launches take 0.85 to 1.0 of their own estimate up to 160 rows (a whole
+// step's weights are as cold there), 0.93 to 1.05 beyond, 1.2 to 1.3 where the reduction is not split (every work-group along the
+// rows reads its strip again); the tall ones near 0.8.  us alone, strip against what was taken before: 7B down at 160 / 192 / 256 /
+// 320 rows 30.8 / 34.1 / 39.2 / 46.9 against 32.6 / 38.5 / 43.6 / 48.7, LM head at 192 / 320 266 / 313 against 313 / 359; but O at 320 (eight
+// planes against four) 15.5 against 14.0, QKV at 192 14.9 against 12.8.  The LM head of up to 160 rows, 680 to 1190 strips, is
+// level in both and stays.
+// experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
+// replaces, and with them the bits.
+// tile_mode: -1 = this rule, 0 = the weight-streaming kernel only, 1 = 256-row tall tiles wherever the width allows.
+WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, int max_splits = kMaxSplitsWs) {
+    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, gemm_bf16_tall_256(M), {}};
+    WsPlan best = plan_ws(M, N, K, allow_split, max_splits);
+    if (tile_mode == 0 || M < 1) return best;
+    if (M > 128) {
+        const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
+        if (t.us < 1.10 * best.us) best = WsPlan{t.splits, true, 0, t.us, t.tiles, {}};
+    }
+    if (M <= kStripRows) {
+        const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
+        const double over_ws = M <= 160 ? 1.15 : allow_split ? 1.07 : 1.25;
+        if (s.us < (best.tall.n > 0 ? 0.80 : over_ws) * best.us) best = WsPlan{s.splits, false, std::min(s.tile.tiles, 5), s.us, {}, s.tile};
+    }
+    return best;
+}
+
+// Gate/up projection with SwiGLU of T rows (N = 2 d_ff): strips where they come to no more than the CUs; from more than five 32-row
+// tiles on the tall tiles, unless the strips are expected to be well ahead (one work-group of the weight-streaming
+// kernel along the rows no longer holds them, and every further one reads the strip again); else that kernel.  us alone of the 7B
+// shape at 64 / 147 / 192 / 256 / 320 rows, strip against what was taken before: 44 / 52 / 58 / 70 / 78 against 50 / 63 / 70 / 77 / 85; of the 32B
+// shape 95 / 106 / 118 against 96 / 115 / 124, at 256 141 against 125 of the tall tiles.
+// The tall tiles against the weight-streaming kernel at 147 / 192 / 256 / 320 / 512 / 800 rows (in a loop): 65 / 66 / 77 / 98 / 144 / 218
+// against 65 / 86 / 104 / 100 / 160 / 221.
+struct GateUp { TallTiles tall; StripTile strip; };       // neither: the weight-streaming kernel
+GateUp plan_gate_up(int T, int N, int K) {
+    GateUp g{};
+    if (N % 256 != 0) return g;
+    double limit = 1e29;
+    if (T > 160) {
+        const TallPlan t = gemm_bf16_tall_plan(T, N, K, 1);
+        g.tall = t.tiles;
+        limit = 0.80 * t.us;
+    }
+    if (T <= kStripRows) {
+        const StripPlan s = gemm_bf16_strip_plan(T, N, K, 1, 1, true);
+        if (s.us < limit) g = GateUp{{}, s.tile};
+    }
+    return g;
 }
 
 struct Layout {                       // byte offsets into the workspace
@@ -194,7 +235,7 @@ bool make_layout(const sv_model& m, const sv_runtime& r, int prefill_rows, Layou
         for (int tm = 1; tm <= (P + 31) / 32; ++tm) {
             const int M = std::min(tm * 32, P);
             for (auto& sh : shapes)
-                if (sh[1] % 64 == 0) part = std::max(part, (size_t)plan_packed(M, sh[0], sh[1], true, -1).splits * M * sh[0]);
+                if (sh[1] % 64 == 0) part = std::max(part, (size_t)plan_packed(M, sh[0], sh[1], true, -1, m.n_experts > 0).splits * M * sh[0]);
         }
     L.part_floats = part;
     L.part = take(sizeof(float) * part);
@@ -264,11 +305,11 @@ struct sv_ctx {
     int n_work;                                           // attention work items staged for the current pass
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
     int gemm_variant;                                     // -1 = choose per shape
-    int gemm_tile;                                        // tall projection kernel: -1 = where it pays, 0 = never, 1 = wherever the shape allows
+    int gemm_tile;                                        // packed projections: -1 = by the plans, 0 = weight-streaming kernel only, 1 = tall tiles wherever the shape allows
     struct PlannedShape { int M, N, K; bool allow_split; WsPlan plan; };
     std::vector<PlannedShape> plans;                      // launch plans of packed projections made so far, at most kPlans
-    struct GateUp { int T; TallTiles tiles; };
-    std::vector<GateUp> gate_up;                          // the same for the gate/up projection's tall tiles
+    struct PlannedGateUp { int T; GateUp launch; };
+    std::vector<PlannedGateUp> gate_up;                   // the same for the gate/up projection
     bool packed;                                          // projection weights are in fragment order
     int pass_rows;                                        // most rows of a prefill pass
     bool attn_generic;
@@ -830,27 +871,24 @@ static int pick_variant(const sv_ctx* c, int M) {
 static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split) {
     for (const auto& p : c->plans)
         if (p.M == M && p.N == N && p.K == K && p.allow_split == allow_split) return p.plan;
-    WsPlan p = plan_packed(M, N, K, allow_split, c->gemm_tile);
-    while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_packed(M, N, K, allow_split, c->gemm_tile, p.splits - 1);
+    const bool experts = c->model.n_experts > 0;
+    WsPlan p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts);
+    while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, p.splits - 1);
     if (c->plans.size() >= kPlans) c->plans.clear();
     c->plans.push_back({M, N, K, allow_split, p});
     return p;
 }
 
-// Gate/up projection of T rows: from more than five 32-row tiles on by tall tiles (one work-group of the weight-streaming
-// kernel along the rows no longer holds them, and every further one reads the strip again).  us of the 7B shape at 147 / 192 /
-// 256 / 320 / 512 / 800 rows, weight-streaming against tall: 65 / 86 / 104 / 100 / 160 / 221 against 65 / 66 / 77 / 98 / 144 / 218.
-// (The line is that kernel's row limit, not a comparison of the two estimates: they are level at 147 and at 320 rows.)
-static bool gate_up_tall(int T) { return T > 160; }
-
-// The tall tiles of the gate/up projection of T rows, made once per row count as well.
-static TallTiles gate_up_tiles(sv_ctx* c, int T) {
+// The launch of the gate/up projection of T rows, made once per row count as well.
+static GateUp gate_up_launch(sv_ctx* c, int T) {
     for (const auto& g : c->gate_up)
-        if (g.T == T) return g.tiles;
-    const TallTiles tiles = gemm_bf16_tall_plan(T, 2 * c->model.d_ff, c->model.d_model, 1).tiles;
+        if (g.T == T) return g.launch;
+    GateUp g{};
+    if (c->gemm_tile == 1) g.tall = gemm_bf16_tall_256(T);
+    else if (c->gemm_tile != 0) g = plan_gate_up(T, 2 * c->model.d_ff, c->model.d_model);
     if (c->gate_up.size() >= kPlans) c->gate_up.clear();
-    c->gate_up.push_back({T, tiles});
-    return tiles;
+    c->gate_up.push_back({T, g});
+    return g;
 }
 
 static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int N, int K, int* splits_out, bool allow_split = true) {
@@ -859,7 +897,8 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
         if (c->packed) {
             const WsPlan p = planned(c, M, N, K, allow_split);
             *splits_out = p.splits;
-            if (p.tall.n > 0) SV_HIP(c, gemm_bf16_tall((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.tall, c->stream));
+            if (p.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.strip, c->stream));
+            else if (p.tall.n > 0) SV_HIP(c, gemm_bf16_tall((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.tall, c->stream));
             else SV_HIP(c, gemm_bf16_ws((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, p.wide, c->stream, p.row_tiles));
         } else {
             const int s = allow_split ? pick_splits(M, N, K) : 1;
@@ -983,12 +1022,11 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     if (c->packed && m.d_ff % 64 == 0) {
         // gate/up projection with SwiGLU in its epilogue: the [T, 2F] fp32 intermediate never exists
         ProfScope prof(c, SV_PROF_GEMM);
-        if (m.d_ff % 128 == 0 && (c->gemm_tile == 1 || (c->gemm_tile != 0 && gate_up_tall(T)))) {
-            const TallTiles tiles = c->gemm_tile == 1 ? gemm_bf16_tall_256(T) : gate_up_tiles(c, T);
-            SV_HIP(c, gemm_bf16_tall((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, tiles, st));
-        } else {
-            SV_HIP(c, gemm_bf16_ws_glu((const bf16_t*)a_norm, (const bf16_t*)c->wgu[l], c->at<bf16_t>(L.act), T, m.d_ff, d, st));
-        }
+        const GateUp g = m.d_ff % 128 == 0 ? gate_up_launch(c, T) : GateUp{};
+        const bf16_t *ga = (const bf16_t*)a_norm, *gw = (const bf16_t*)c->wgu[l];
+        if (g.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.strip, st));
+        else if (g.tall.n > 0) SV_HIP(c, gemm_bf16_tall(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.tall, st));
+        else SV_HIP(c, gemm_bf16_ws_glu(ga, gw, c->at<bf16_t>(L.act), T, m.d_ff, d, st));
     } else if (m.dtype == SV_FP32) {
         ProfScope prof(c, SV_PROF_GEMM);
         SV_HIP(c, gemm_f32_glu((const float*)a_norm, (const float*)c->wgu[l], c->at<float>(L.act), T, m.d_ff, d, st));
@@ -1214,7 +1252,7 @@ extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int*
     if (!splits || !wide || !row_tiles || M <= 0 || N <= 0 || K <= 0 || N % 128 != 0 || K % 64 != 0) return SV_EINVAL;
     // of the weight-streaming kernel, but where the 256-row tiles fill the chip four times over
     WsPlan p = plan_ws(M, N, K, true);
-    if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0, {}};
+    if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0, {}, {}};
     *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
     return SV_OK;
 }
@@ -1222,13 +1260,17 @@ extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int*
 extern "C" int sv_op_gemm_step_plan(int M, int N, int K, int form, int* splits, int* wide, int* row_tiles, int* tall) {
     if (!splits || !wide || !row_tiles || !tall || M <= 0 || N <= 0 || K <= 0 || form < 0 || form > 2 || N % (form == 2 ? 256 : 128) != 0 || K % 64 != 0)
         return SV_EINVAL;
-    WsPlan p{1, false, 0, 0.0, {}};
+    WsPlan p{1, false, 0, 0.0, {}, {}};
     if (form == 2) {
-        if (gate_up_tall(M)) p.tall = gemm_bf16_tall_plan(M, N, K, 1).tiles;
+        const GateUp g = plan_gate_up(M, N, K);
+        p.tall = g.tall;
+        p.strip = g.strip;
+        p.row_tiles = std::min(g.strip.tiles, 5);
     } else {
-        p = plan_packed(M, N, K, form == 0, -1);
+        p = plan_packed(M, N, K, form == 0, -1, false);
     }
-    *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
+    *splits = p.splits; *wide = p.strip.tiles > 0 ? 32 * p.strip.fs : p.wide ? 1 : 0; *row_tiles = p.row_tiles;
+    if (p.strip.tiles > 5) p.tall = TallTiles{p.strip.tiles / 2, 1, 0, 0};
     tall[0] = p.tall.rw; tall[1] = p.tall.n; tall[2] = p.tall.rwt; tall[3] = p.tall.nt;
     return SV_OK;
 }
@@ -1250,6 +1292,16 @@ extern "C" int sv_op_gemm_bf16_tall(const void* Ap, const void* Wp, void* out, i
     const long long rows = 64LL * tl.rw * tl.n + 64LL * tl.rwt * tl.nt;
     if (rows < M || rows - 64 * (tl.nt > 0 ? tl.rwt : tl.rw) >= M) return SV_EINVAL;
     return gemm_bf16_tall((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, gated != 0, tl, st) == hipSuccess ? SV_OK : SV_EHIP;
+}
+
+extern "C" int sv_op_gemm_bf16_strip(const void* Ap, const void* Wp, void* out, int M, int N, int K, int splits, int gated, int row_tiles,
+                                     int features, void* stream) {
+    if (!Ap || !Wp || !out || M <= 0 || N <= 0 || K <= 0 || splits <= 0 || splits > kMaxSplitsWs || (gated && splits != 1) ||
+        N % (gated ? 256 : 128) != 0 || K % 64 != 0 || K % (32 * splits) != 0 || row_tiles < 1 || row_tiles > 10 || row_tiles == 7 ||
+        row_tiles == 9 || M > 32 * row_tiles || (features != 128 && features != 160 && features != 224))
+        return SV_EINVAL;
+    return gemm_bf16_strip((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, gated != 0, StripTile{row_tiles, features / 32},
+                           (hipStream_t)stream) == hipSuccess ? SV_OK : SV_EHIP;
 }
 
 extern "C" int sv_op_pack_rows(const void* src, void* dst, int M, int K, void* stream) {
@@ -1455,6 +1507,7 @@ extern "C" int sv_set_option(sv_ctx* c, int option, int value) {
             if (value < -1 || value > 1) return c->fail(SV_EINVAL, "gemm tile mode %d", value);
             c->gemm_tile = value;
             c->plans.clear();
+            c->gate_up.clear();
             return SV_OK;
         case SV_OPT_ATTN_GENERIC:
             c->attn_generic = value != 0;

@@ -409,13 +409,13 @@ __device__ __forceinline__ void lds_landed(u32x4& d) { asm volatile("s_waitcnt l
 __device__ __forceinline__ void lds_landed_too(u32x4& d) { asm volatile("" : "+v"(d)); }     // no use of d moves above the wait
 
 // 1 KB from global memory straight into LDS: lane l's 16 bytes at base + lane_off go to LDS address lds + 16 l (base and lds the same for
-// all lanes); dma1_below: only in waves below N.  As one statement, so that a load which only some waves make is no branch to the compiler.
+// all lanes).  dma1_lanes: only the lanes of a mask that is not empty.  All lanes of the wave are running.
 __device__ __forceinline__ void dma1(const char* base, uint32_t lane_off, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
 }
-template <int N> __device__ __forceinline__ void dma1_below(int wave, const char* base, uint32_t lane_off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_cmp_lt_u32 %3, %4\n\ts_cbranch_scc0 .Lno_dma%=\n\tglobal_load_lds_dwordx4 %1, %2\n.Lno_dma%=:"
-                 : : "s"(lds), "v"(lane_off), "s"(base), "s"(wave), "n"(N) : "memory", "scc");
+__device__ __forceinline__ void dma1_lanes(uint64_t lanes, const char* base, uint32_t lane_off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
+                 : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
 }
 
 template <bool GLU, int RW>
@@ -432,10 +432,11 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     const int m_tiles = (M + 31) / 32;
 
     // A fill is P pieces of 1 KB: the activations' 2 RW row tiles x 2 slices, then (strip, slice, feature tile) of the weights.  Wave w
-    // requests pieces w, w + 8, ... .  Row tiles beyond M and a strip beyond N (N an odd multiple of 128) are read as the last
+    // requests pieces w, w + 8, ... ; where they do not come out even, the others take one lane of the last piece once more, so that
+    // every wave counts the same loads without a branch (two branches cost 120 cycles a fill).  Row tiles beyond M and a strip beyond N (N an odd multiple of 128) are read as the last
     // one and never stored.
     constexpr int A_P = KA * 2 * RW, P = A_P + KA * 8, EACH = P / 8, EXTRA = P % 8;
-    const bool extra = wave < EXTRA;
+    const uint64_t last_lanes = wave < EXTRA ? ~0ull : 1;
     const char* src[EACH + 1];
     int step[EACH + 1];
 #pragma unroll
@@ -457,7 +458,7 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     auto request = [&](auto which, uint32_t base) __attribute__((always_inline)) {
         constexpr int Q = decltype(which)::value;
         if constexpr (Q < EACH) dma1(src[Q], lane_off, base + (wave + 8 * Q) * 1024);
-        else if constexpr (EXTRA > 0) dma1_below<EXTRA>(wave, src[Q], lane_off, base + (wave + 8 * Q) * 1024);
+        else if constexpr (EXTRA > 0) dma1_lanes(last_lanes, src[Q], lane_off, base + min(wave + 8 * Q, P - 1) * 1024);
     };
     auto advance = [&]() __attribute__((always_inline)) {  // past the end: the last fill again, so that the counts below hold
         if (++ahead < nfill) {
@@ -467,7 +468,7 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     };
     auto wait_fills = [&](auto in_flight) __attribute__((always_inline)) {   // all but the newest in_flight fills have landed
         constexpr int L = decltype(in_flight)::value;
-        if (EXTRA > 0 && extra) wait_vmcnt<(EACH + 1) * L>(); else wait_vmcnt<EACH * L>();
+        wait_vmcnt<(EACH + (EXTRA > 0)) * L>();
     };
 
     // Operands of a fill.  Lane 16 g + r of a 16x16x32 operand holds row r, elements 8 g .. 8 g + 7 of the fill's 32: slice
@@ -727,6 +728,266 @@ hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M,
         }
     };
     return glu ? form(std::true_type{}) : form(std::false_type{});
+}
+
+// ---- fourth bf16 kernel: the tall kernel's scheme in narrow strips, one work-group for all rows ----
+// Up to 320 rows a projection is bound by its weight stream and by how many CUs stream it.  The weight-streaming kernel above
+// holds the stream in registers, eight slices a wave, and its strips of 128 or 256 features seldom come to the number of CUs; the
+// tall kernel's 256-feature strips of the 7B gate/up projection are 148 work-groups.  Here both operands go through an LDS ring of
+// fills of one reduction step of 32 in pieces of one 16x16x32 operand, so that a strip can be any multiple of 32 features (gated: of
+// 16 gate and 16 up ones): 128, 160 or 224, whichever comes closest to the 256 CUs.  W waves, two of them side by side along
+// the features, each RS 16-row operands x FS 16-feature operands, all of a fill's operands in one of two register sets: one
+// barrier a fill, the next fill's LDS reads and the ring's requests between the products.
+// The request of a ring's fill costs a wave its place at the texture path (17 cycles a piece, one queue per CU): sent in a burst
+// behind the barrier, ten row tiles of 160 features took 1536 cycles a fill on an otherwise idle chip, spread 1062 (800 of them
+// products).  With the chip full the stream adds to that: fills arrive at 5.7 to 6.2 TB/s where the products are few.
+// us alone with weights from HBM, against the kernel that was taken before: gate/up 37888 x 3584 at 5 / 64 / 96 / 128 / 160 / 192 /
+// 256 / 320 rows 46.2 / 49.4 / 54.3 / 58.6 / 62.7 / 69.4 / 76.9 / 88.1 -> 44.2 / 44.0 / 45.0 / 47.7 / 52.1 / 56.6 / 68.9 / 76.8; down 3584 x
+// 18944 at 5 / 64 / 160 rows 23.8 / 25.6 / 31.8 -> 21.3 / 23.0 / 30.6; QKV 4608 x 3584 6.3 / 7.5 / 13.1 -> 4.6 / 6.7 / 11.1.
+// The sums are those of the other two kernels, slice after slice: equal bits at the same splits.
+constexpr int strip_fills(int w, int rs, int fs) {        // fills in the ring: two work-groups of four waves share a CU's LDS
+    const int n = (w == 4 ? 80 : 160) / (w / 2 * rs + 2 * fs);
+    return n < 6 ? n : 6;
+}
+
+template <bool GLU, int W, int RS, int FS>
+__global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
+                                                                 int M, int N, int K, int k_per_split, int splits) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char strip_lds[];   // NB fills; the exchange of the gated form
+    constexpr int WM = W / 2, A_P = WM * RS, B_P = 2 * FS, P = A_P + B_P;          // 1 KB pieces of a fill: 16 rows, 16 features x 32
+    constexpr int EACH = P / W, EXTRA = P % W, FILL = P * 1024, NB = strip_fills(W, RS, FS);                // a wave requests EACH of them, the first EXTRA waves one more
+    const int tiles_n = (N / 2 + 16 * FS - 1) / (16 * FS);
+    const int logical = xcd_remap(blockIdx.x, tiles_n * splits);
+    const int sp = logical % splits, tn = logical / splits;
+    const int nfill = k_per_split / 32, kslices = K / 16, ks0 = sp * (k_per_split / 16);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lg = lane >> 4;
+    const int m_pieces = 2 * ((M + 31) / 32), n_pieces = N / 16;
+
+    // Piece i of a fill, in the lane order of the 16x16x32 operand: lane 16 g + r holds row (feature) r, elements 8 g .. 8 g + 7,
+    // which lie in slice g / 2 of the packed order, half g % 2 of its 16.  Dealt to the waves as in the tall kernel.
+    const uint64_t last_lanes = wave < EXTRA ? ~0ull : 1;
+    const char* src[EACH + 1];
+    int step[EACH + 1];
+    uint32_t lane_off[EACH + 1];
+#pragma unroll
+    for (int q = 0; q <= EACH; ++q) {
+        const int i = min(wave + W * q, P - 1);
+        if (i < A_P) {
+            const int x = min(i, m_pieces - 1);
+            src[q] = reinterpret_cast<const char*>(Ap) + ((int64_t)(x >> 1) * kslices + ks0) * 1024 + (x & 1) * 256;
+            step[q] = 2 * 1024;
+        } else {
+            const int j = i - A_P;                         // GLU: FS pieces of gate rows, then FS of up rows
+            const int x = GLU ? (j < FS ? min(tn * FS + j, n_pieces / 2 - 1) : n_pieces / 2 + min(tn * FS + j - FS, n_pieces / 2 - 1))
+                              : min(tn * 2 * FS + j, n_pieces - 1);
+            src[q] = reinterpret_cast<const char*>(Wp) + ((int64_t)(x >> 3) * kslices + ks0) * 4096 + ((x >> 1) & 3) * 1024 + (x & 1) * 256;
+            step[q] = 2 * 4096;
+        }
+        lane_off[q] = (lg >> 1) * (step[q] / 2) + (lg & 1) * 512 + l16 * 16;
+    }
+    const uint32_t lds_base = (uint32_t)(uintptr_t)SV_LDS_PTR(strip_lds);
+    int ahead = 0;
+    auto request = [&](auto which, uint32_t base) __attribute__((always_inline)) {
+        constexpr int Q = decltype(which)::value;
+        if constexpr (Q < EACH) dma1(src[Q], lane_off[Q], base + (wave + W * Q) * 1024);
+        else if constexpr (EXTRA > 0) dma1_lanes(last_lanes, src[Q], lane_off[Q], base + min(wave + W * Q, P - 1) * 1024);
+    };
+    auto advance = [&]() __attribute__((always_inline)) {  // past the end: the last fill again, so that the counts below hold
+        if (++ahead < nfill) {
+#pragma unroll
+            for (int q = 0; q <= EACH; ++q) src[q] += step[q];
+        }
+    };
+    auto wait_fills = [&](auto in_flight) __attribute__((always_inline)) {
+        constexpr int L = decltype(in_flight)::value;
+        wait_vmcnt<(EACH + (EXTRA > 0)) * L>();
+    };
+
+    u32x4 a[2][RS], b[2][FS];
+    const uint32_t lds0 = lds_base + lane * 16;
+    const uint32_t a_off = lds0 + wm * RS * 1024, b_off = lds0 + (A_P + wn * FS) * 1024;
+    uint32_t a_addr = a_off, b_addr = b_off;
+    auto read = [&](auto set, auto which) __attribute__((always_inline)) {
+        constexpr int S = decltype(set)::value, R = decltype(which)::value;
+        if constexpr (R < FS) lds_read16<R * 1024>(b[S][R], b_addr);
+        else lds_read16<(R - FS) * 1024>(a[S][R - FS], a_addr);
+    };
+    auto wait_set = [&](auto set) __attribute__((always_inline)) {
+        constexpr int S = decltype(set)::value;
+        lds_landed(b[S][0]);
+#pragma unroll
+        for (int i = 1; i < FS; ++i) lds_landed_too(b[S][i]);
+#pragma unroll
+        for (int j = 0; j < RS; ++j) lds_landed_too(a[S][j]);
+    };
+    floatx4 acc[FS][RS];
+#pragma unroll
+    for (int i = 0; i < FS; ++i)
+#pragma unroll
+        for (int j = 0; j < RS; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const std::integral_constant<int, 0> i0;
+    const std::integral_constant<int, 1> i1;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        static_for<EACH + 1>([&](auto q) __attribute__((always_inline)) { request(q, lds_base + i * FILL); });
+        advance();
+    }
+    wait_fills(std::integral_constant<int, NB - 1>{});
+    __builtin_amdgcn_s_barrier();
+    static_for<FS + RS>([&](auto r) __attribute__((always_inline)) { read(i0, r); });
+    wait_set(i0);
+    int slot = 0;
+    auto fill = [&](auto set) __attribute__((always_inline)) {
+        constexpr int S = decltype(set)::value, NM = FS * RS, NR = FS + RS;
+        // this wave holds the whole fill in registers and its share of the next one has landed; after the barrier so has everyone's,
+        // and nobody reads this fill's place in the ring any more
+        wait_fills(std::integral_constant<int, NB - 2>{});
+        __builtin_amdgcn_s_barrier();
+        const uint32_t base = lds_base + slot * FILL;
+        slot = slot + 1 == NB ? 0 : slot + 1;
+        a_addr = a_off + slot * FILL;
+        b_addr = b_off + slot * FILL;
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<NM>([&](auto mi) __attribute__((always_inline)) {
+            constexpr int m = decltype(mi)::value, i = m % FS, j = m / FS;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[S][i]), __builtin_bit_cast(bf16x8, a[S][j]), acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int first = m < NR ? m : NR, last = m + 1 == NM ? NR : m + 1 < NR ? m + 1 : NR;
+            static_for<last - first>([&](auto rr) __attribute__((always_inline)) {
+                read(std::integral_constant<int, 1 - S>{}, std::integral_constant<int, first + decltype(rr)::value>{});
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            constexpr int NQ = EACH + (EXTRA > 0), q = (m * NQ + NM - 1) / NM;      // request q after product q NM / NQ
+            if constexpr (q < NQ && q * NM / NQ == m) {
+                request(std::integral_constant<int, q>{}, base);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+        wait_set(std::integral_constant<int, 1 - S>{});
+        advance();
+    };
+    int f = 0;
+    for (; f + 1 < nfill; f += 2) { fill(i0); fill(i1); }
+    if (f < nfill) fill(i0);
+    wait_vmcnt<0>();                                      // nothing of this work-group may land in LDS after it has gone
+
+    // acc[i][j][e] <-> row 16 (RS wm + j) + l16, feature 4 lg + e of the wave's 16-feature operand i
+    if (GLU) {                                            // even waves hold gate features, odd ones the same features' up halves
+        constexpr int RH = (RS + 1) / 2;                  // the even wave finishes the first RH row operands, the odd one the others
+        __builtin_amdgcn_s_barrier();                     // everyone's last loads have landed and last reads are over
+        floatx4* xbuf = reinterpret_cast<floatx4*>(strip_lds) + wm * FS * RS * 64 + lane;
+        static_for<RS>([&](auto jj) __attribute__((always_inline)) {
+            constexpr int j = decltype(jj)::value;
+            if ((j < RH) != (wn == 0)) {
+#pragma unroll
+                for (int i = 0; i < FS; ++i) xbuf[(i * RS + j) * 64] = acc[i][j];
+            }
+        });
+        __syncthreads();
+        const int F = N / 2;
+        bf16_t* act = reinterpret_cast<bf16_t*>(out);
+        static_for<RS>([&](auto jj) __attribute__((always_inline)) {
+            constexpr int j = decltype(jj)::value;
+            const int x = wm * RS + j;
+            if ((j < RH) == (wn == 0) && x < m_pieces) {
+#pragma unroll
+                for (int i = 0; i < FS; ++i) {
+                    const floatx4 other = xbuf[(i * RS + j) * 64];
+                    float r[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) r[e] = j < RH ? silu_mul(acc[i][j][e], other[e]) : silu_mul(other[e], acc[i][j][e]);
+                    const int fs = tn * FS + i;
+                    if (fs < F / 16)
+                        *reinterpret_cast<u32x2*>(act + ((int64_t)(x >> 1) * (F / 16) + fs) * 512 + ((lg >> 1) * 32 + (x & 1) * 16 + l16) * 8 + 4 * (lg & 1)) =
+                            u32x2{pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
+                }
+            }
+        });
+        return;
+    }
+    float* dst = out + (int64_t)sp * M * N;
+#pragma unroll
+    for (int j = 0; j < RS; ++j) {
+        const int m = 16 * (wm * RS + j) + l16;
+        if (m < M) {
+#pragma unroll
+            for (int i = 0; i < FS; ++i) {
+                const int n = (tn * 2 + wn) * 16 * FS + 16 * i;
+                if (n < N) *reinterpret_cast<floatx4_any*>(dst + (int64_t)m * N + n + 4 * lg) = acc[i][j];
+            }
+        }
+    }
+}
+
+// Microseconds a launch takes, fitted to 400 launches of thirteen shapes (5 to 320 rows, weights from HBM, an idle chip before each;
+// rms error 10 %): a lone work-group's fills at their pace and its epilogue, the weight stream beside them -- the two add up at
+// nearly twice the stream's rate rather than overlap, and never beat the stream itself -- and the planes, written here and read by the
+// consumer.  More work-groups than CUs only where eight waves fill a CU (six row tiles and more: the LM head); two work-groups of
+// four waves on a CU take 1.75 times one's time and more, and nothing is gained over the weight-streaming kernel.
+static double gemm_bf16_strip_us(int M, int N, int K, int splits, bool glu, const StripTile& s) {
+    const int n = (N / 2 + 16 * s.fs - 1) / (16 * s.fs) * splits, area = s.tiles * s.fs;
+    const double wg = (double)K / 32 / splits * (0.062 + 0.007 * area) + 0.11 * area, stream = (double)N * K * 2.0 / 1.0e6;
+    if (n > 256 && s.tiles <= 5) return 1e30;
+    const int rounds = n / 256, rem = n % 256;
+    const double t = n <= 256 ? wg : wg * (rounds + (rem ? 0.5 + rem / 512.0 : 0.0));
+    return std::max(stream / 6.1, t + stream / 11.3) + (glu ? 0.0 : splits * (double)M * N * 4.0 / 6.0e6) + (splits - 1) * (double)M * N * 4.0 / 4.0e6 + 2.3;
+}
+
+// The strip for M <= kStripRows rows: the lowest that holds them, width and splits by the estimate (us 1e30: none).
+StripPlan gemm_bf16_strip_plan(int M, int N, int K, int min_splits, int max_splits, bool glu) {
+    const int need = (M + 31) / 32, tiles = need <= 6 ? need : need <= 8 ? 8 : 10;
+    StripPlan best{1, {tiles, 4}, 1e30};
+    for (int fs : {4, 5, 7})
+        for (int s = min_splits; s <= max_splits; ++s) {
+            if (K % (64 * s) != 0) continue;               // (the form in which every kernel of a packed projection can be split)
+            const double us = gemm_bf16_strip_us(M, N, K, s, glu, {tiles, fs});
+            if (us < best.us) best = {s, {tiles, fs}, us};
+        }
+    return best;
+}
+
+// plain: out [splits][M][N] fp32, N % 128 == 0.  gated: N = 2 F weight rows, out = packed bf16 [ceil(M/32)*32, F], F % 128 == 0,
+// splits == 1.  (K / splits) % 32 == 0.  One work-group holds the M rows in tiles of 32 (1 to 5, 6, 8 or 10 of them).
+hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const StripTile& s, hipStream_t st) {
+    if (splits < 1 || K % splits != 0 || (K / splits) % 32 != 0 || N % (glu ? 256 : 128) != 0 || (glu && splits != 1) || M < 1 || M > 32 * s.tiles)
+        return hipErrorInvalidValue;
+    auto launch = [&](auto kern, int w, int rs, int fs) -> hipError_t {
+        const int tiles_n = (N / 2 + 16 * fs - 1) / (16 * fs);
+        const int lds = std::max(strip_fills(w, rs, fs) * (w / 2 * rs + 2 * fs) * 1024, glu ? w / 2 * rs * fs * 1024 : 0);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3(tiles_n * splits), dim3(64 * w), lds, st, Ap, Wp, out, M, N, K, K / splits, splits);
+        return hipGetLastError();
+    };
+    auto width = [&](auto g, auto w, auto rs) -> hipError_t {
+        constexpr bool G = decltype(g)::value;
+        constexpr int W = decltype(w)::value, RS = decltype(rs)::value;
+        switch (s.fs) {
+            case 4: return launch(gemm_bf16_strip_kernel<G, W, RS, 4>, W, RS, 4);
+            case 5: return launch(gemm_bf16_strip_kernel<G, W, RS, 5>, W, RS, 5);
+            case 7: return launch(gemm_bf16_strip_kernel<G, W, RS, 7>, W, RS, 7);
+            default: return hipErrorInvalidValue;
+        }
+    };
+    auto height = [&](auto g) -> hipError_t {
+        constexpr std::integral_constant<int, 4> w4;
+        constexpr std::integral_constant<int, 8> w8;
+        switch (s.tiles) {
+            case 1: return width(g, w4, std::integral_constant<int, 1>{});
+            case 2: return width(g, w4, std::integral_constant<int, 2>{});
+            case 3: return width(g, w4, std::integral_constant<int, 3>{});
+            case 4: return width(g, w4, std::integral_constant<int, 4>{});
+            case 5: return width(g, w4, std::integral_constant<int, 5>{});
+            case 6: return width(g, w8, std::integral_constant<int, 3>{});
+            case 8: return width(g, w8, std::integral_constant<int, 4>{});
+            case 10: return width(g, w8, std::integral_constant<int, 5>{});
+            default: return hipErrorInvalidValue;
+        }
+    };
+    return glu ? height(std::true_type{}) : height(std::false_type{});
 }
 
 // Activations [M, K] row-major -> packed [ceil(M/32)][K/16][64 lanes][8]: lane 32*g + r of a fragment holds

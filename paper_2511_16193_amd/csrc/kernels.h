@@ -22,6 +22,12 @@ int gemm_bf16_ws_row_tiles(int M);
 struct TallTiles { int rw, n, rwt, nt; };
 struct TallPlan { int splits; TallTiles tiles; double us; };
 hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const TallTiles& tiles, hipStream_t st);
+// Narrow strips: one work-group of 32 `tiles` rows (tiles 1..5, 6, 8 or 10) x 32 fs features (fs 4, 5 or 7); the rest as above
+struct StripTile { int tiles, fs; };
+struct StripPlan { int splits; StripTile tile; double us; };
+constexpr int kStripRows = 320;             // most rows of a strip
+hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const StripTile& tile, hipStream_t st);
+StripPlan gemm_bf16_strip_plan(int M, int N, int K, int min_splits, int max_splits, bool glu);
 TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits);
 TallTiles gemm_bf16_tall_256(int M);
 hipError_t gemm_bf16_ws_glu(const bf16_t* Ap, const bf16_t* Wp, bf16_t* act_out, int M, int F, int K, hipStream_t st);

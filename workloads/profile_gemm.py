@@ -54,7 +54,10 @@ def main(argv=None) -> int:
         form = {"lm_head": 1, "gate_up": 2}.get(name, 0)
         plan = P.op_gemm_step_plan(M, N, K, form)
         ap_, wp = P.op_pack_rows(a), P.op_pack_weight(w)
-        if plan["tall"] or form == 2:
+        if plan["strip"]:
+            tiles = 2 * plan["tall"][0] if plan["tall"] else plan["row_tiles"]
+            ours = mean_us(lambda: P.op_gemm_bf16_strip(ap_, wp, M, tiles, plan["strip"], plan["splits"], gated=form == 2))
+        elif plan["tall"] or form == 2:
             ours = mean_us(lambda: P.op_gemm_bf16_tall(ap_, wp, M, plan["tall"], plan["splits"], gated=form == 2))
         else:
             ours = mean_us(lambda: P.op_gemm_bf16_ws(ap_, wp, M, splits=plan["splits"], wide=plan["wide"], row_tiles=plan["row_tiles"]))
