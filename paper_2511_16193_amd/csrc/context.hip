@@ -163,7 +163,7 @@ GateUp plan_gate_up(int T, int N, int K) {
 struct Layout {                       // byte offsets into the workspace
     size_t seq_len, page_table, stage, row_info, row_part, row_slot, stat_part, draw_part;
     size_t rope, h, a_norm, q, attn, part, act, logits, part_o, part_ml, total;
-    size_t moe_ids, moe_w, moe_cnt, moe_off, moe_perm, moe_inv, moe_act, moe_y, moe_logits;   // mixture-of-experts scratch
+    size_t moe_ids, moe_w, moe_live, moe_off, moe_perm, moe_inv, moe_act, moe_y, moe_logits;   // mixture-of-experts scratch
     int T, P;                         // rows of a step, rows of a pass (a prefill pass may hold more)
     int max_chunks, max_items, max_upd;
     size_t part_floats;               // capacity of part
@@ -250,12 +250,12 @@ bool make_layout(const sv_model& m, const sv_runtime& r, int prefill_rows, Layou
     if (L.part_rows > 0x7fffffffLL) return false;          // partial rows are numbered in 32 bits
     L.part_o = take(sizeof(float) * (size_t)L.part_rows * m.head_dim);
     L.part_ml = take(sizeof(float) * (size_t)L.part_rows * 2);
-    L.moe_ids = L.moe_w = L.moe_cnt = L.moe_off = L.moe_perm = L.moe_inv = L.moe_act = L.moe_y = L.moe_logits = 0;
+    L.moe_ids = L.moe_w = L.moe_live = L.moe_off = L.moe_perm = L.moe_inv = L.moe_act = L.moe_y = L.moe_logits = 0;
     if (m.n_experts > 0) {
         const size_t tiles = (size_t)moe_max_tiles(P, m.n_experts, m.top_k);
         L.moe_ids = take(sizeof(int32_t) * (size_t)P * m.top_k);
         L.moe_w = take(sizeof(float) * (size_t)P * m.top_k);
-        L.moe_cnt = take(sizeof(int32_t) * m.n_experts);
+        L.moe_live = take(sizeof(int32_t) * (2 + 2 * (size_t)m.n_experts));
         L.moe_off = take(sizeof(int32_t) * (m.n_experts + 1));
         L.moe_perm = take(sizeof(int32_t) * 32 * tiles);
         L.moe_inv = take(sizeof(int32_t) * (size_t)P * m.top_k);
@@ -1010,7 +1010,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         ma.w_gate_up = (const bf16_t*)c->wgu[l]; ma.w_down = (const bf16_t*)c->wdown[l];
         ma.top_ids = c->at<int32_t>(L.moe_ids); ma.top_w = c->at<float>(L.moe_w); ma.router_logits = c->at<float>(L.moe_logits);
         ma.router_parts = (int)std::min<long long>(16, router_rows(L.P) / T);
-        ma.cnt = c->at<int32_t>(L.moe_cnt); ma.tile_off = c->at<int32_t>(L.moe_off);
+        ma.live = c->at<int32_t>(L.moe_live); ma.tile_off = c->at<int32_t>(L.moe_off);
         ma.perm = c->at<int32_t>(L.moe_perm); ma.inv = c->at<int32_t>(L.moe_inv);
         ma.act = c->at<bf16_t>(L.moe_act); ma.y = c->at<float>(L.moe_y); ma.out = nullptr;   // combined by the next norm
         ma.T = T; ma.d = d; ma.E = m.n_experts; ma.top_k = m.top_k; ma.F = m.d_expert;
@@ -1337,7 +1337,7 @@ extern "C" size_t sv_op_sample_scratch_bytes(int B, int N, int k) {
     return 2 * sizeof(float) * 4 * sample_part_entries(B * (1 + N * k));
 }
 
-struct MoeScratch { size_t ids, w, cnt, off, perm, inv, act, y, logits, total; };
+struct MoeScratch { size_t ids, w, live, off, perm, inv, act, y, logits, total; };
 static MoeScratch moe_scratch(int T, int d, int E, int top_k, int F) {
     MoeScratch m;
     size_t o = 0;
@@ -1345,7 +1345,7 @@ static MoeScratch moe_scratch(int T, int d, int E, int top_k, int F) {
     const size_t tiles = (size_t)moe_max_tiles(T, E, top_k);
     m.ids = take(sizeof(int32_t) * (size_t)T * top_k);
     m.w = take(sizeof(float) * (size_t)T * top_k);
-    m.cnt = take(sizeof(int32_t) * E);
+    m.live = take(sizeof(int32_t) * (2 + 2 * (size_t)E));
     m.off = take(sizeof(int32_t) * (E + 1));
     m.perm = take(sizeof(int32_t) * 32 * tiles);
     m.inv = take(sizeof(int32_t) * (size_t)T * top_k);
@@ -1374,7 +1374,7 @@ extern "C" int sv_op_moe_ffn(const void* a_packed, const void* w_router, const v
     ma.w_gate_up = (const bf16_t*)w_gate_up_packed; ma.w_down = (const bf16_t*)w_down_packed;
     ma.top_ids = reinterpret_cast<int32_t*>(ws + m.ids); ma.top_w = reinterpret_cast<float*>(ws + m.w);
     ma.router_logits = reinterpret_cast<float*>(ws + m.logits);
-    ma.cnt = reinterpret_cast<int32_t*>(ws + m.cnt); ma.tile_off = reinterpret_cast<int32_t*>(ws + m.off);
+    ma.live = reinterpret_cast<int32_t*>(ws + m.live); ma.tile_off = reinterpret_cast<int32_t*>(ws + m.off);
     ma.perm = reinterpret_cast<int32_t*>(ws + m.perm); ma.inv = reinterpret_cast<int32_t*>(ws + m.inv);
     ma.act = reinterpret_cast<bf16_t*>(ws + m.act); ma.y = reinterpret_cast<float*>(ws + m.y); ma.out = out;
     ma.T = T; ma.d = d; ma.E = E; ma.top_k = top_k; ma.F = F;

@@ -125,7 +125,7 @@ struct MoeArgs {
     int router_parts = 4;     // parts it has room for, at least 4
     int32_t* top_ids;         // [T][top_k] experts in descending probability
     float* top_w;             // [T][top_k] renormalised weights
-    int32_t* cnt;             // [E] rows per expert
+    int32_t* live;            // [2 + 2 E] number of experts that have rows, -; of each: id | tiles << 16, first tile
     int32_t* tile_off;        // [E+1] first 32-row tile of each bucket
     int32_t* perm;            // [32 * max_tiles] source row of a padded row
     int32_t* inv;             // [T * top_k] padded row of an assignment

@@ -176,23 +176,26 @@ __global__ __launch_bounds__(256) void moe_select_kernel(MoeArgs a, int KQ) {
 
 // ------------------------------------------------------------------ grouping
 // First tile of every bucket: exclusive prefix sum of the buckets' tile counts, `mine` that of expert threadIdx.x (E <= 256:
-// four waves scan their 64 experts with lane shifts, then add the totals of the waves before them).  All threads call it.
-__device__ __forceinline__ void bucket_offsets(int mine, int32_t* offs, int E) {
-    __shared__ int wave_tot[4];
-    const int e = threadIdx.x, lane = e & 63;
+// four waves scan their 64 experts with lane shifts, then add the totals of the waves before them); and the list of the experts
+// that have a tile, for the products.  All threads call it.
+__device__ __forceinline__ void bucket_offsets(int mine, int32_t* offs, const MoeArgs& a) {
+    __shared__ int wave_tot[4], wave_live[4];
+    const int e = threadIdx.x, lane = e & 63, E = a.E;
     int incl = mine;
+    const uint64_t live = __ballot(mine > 0);
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const int up = __shfl_up(incl, d);
         if (lane >= d) incl += up;
     }
-    if (e < 256 && lane == 63) wave_tot[e >> 6] = incl;
+    if (e < 256 && lane == 63) { wave_tot[e >> 6] = incl; wave_live[e >> 6] = __popcll(live); }
     __syncthreads();
     if (e < E) {
-        int base = 0;
-        for (int w = 0; w < (e >> 6); ++w) base += wave_tot[w];
+        int base = 0, rank = __popcll(live & ((1ull << lane) - 1));
+        for (int w = 0; w < (e >> 6); ++w) { base += wave_tot[w]; rank += wave_live[w]; }
         offs[e] = base + incl - mine;
-        if (e == E - 1) offs[E] = base + incl;
+        if (mine > 0) reinterpret_cast<u32x2*>(a.live)[1 + rank] = u32x2{(uint32_t)e | (uint32_t)mine << 16, (uint32_t)offs[e]};
+        if (e == E - 1) { offs[E] = base + incl; a.live[0] = rank + (mine > 0); }
     }
     __syncthreads();
 }
@@ -222,7 +225,7 @@ __global__ __launch_bounds__(1024) void moe_route_tile_kernel(MoeArgs a, int pla
         }
     }
     __syncthreads();
-    bucket_offsets(threadIdx.x < a.E ? chosen[threadIdx.x] : 0, offs, a.E);
+    bucket_offsets(threadIdx.x < a.E ? chosen[threadIdx.x] : 0, offs, a);
     if (threadIdx.x <= a.E) a.tile_off[threadIdx.x] = offs[threadIdx.x];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
@@ -260,11 +263,10 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(MoeArgs a) {
         cnts[e] = run;
     }
     __syncthreads();
-    bucket_offsets(threadIdx.x < a.E ? (cnts[threadIdx.x] + 31) / 32 : 0, offs, a.E);
+    bucket_offsets(threadIdx.x < a.E ? (cnts[threadIdx.x] + 31) / 32 : 0, offs, a);
     for (int e = threadIdx.x; e <= a.E; e += 1024) {
         a.tile_off[e] = offs[e];
         if (e < a.E) {
-            a.cnt[e] = cnts[e];
             for (int r = cnts[e]; r < (offs[e + 1] - offs[e]) * 32; ++r) a.perm[offs[e] * 32 + r] = 0;
         }
     }
@@ -457,11 +459,14 @@ __global__ __launch_bounds__(256, MTMAX == 4 ? 2 : 4) void moe_gemm_kernel(MoeAr
     const int Ntot = MODE == 0 ? 2 * a.F : a.d;             // weight rows per expert
     const int strips = MODE == 0 ? a.F / 64 : a.d / 128;
     // consecutive work-group ids go round the eight XCDs: the strips of an expert are given ids eight apart, so
-    // that they share one L2 and the expert's tiles are fetched once (E is a multiple of 8)
+    // that they share one L2 and the expert's tiles are fetched once (E is a multiple of 8).  The experts are those that have
+    // rows, dealt to the XCDs in turn: by their own numbers one XCD may get fourteen of them and another ten (20 rows, 93 of 128
+    // experts: the two products of a layer 184 -> 173 us).
     const int grp = blockIdx.x / (8 * strips), in_grp = blockIdx.x % (8 * strips);
-    const int e = grp * 8 + (in_grp & 7), p = in_grp >> 3;
-    const int tile0 = a.tile_off[e], ntile = a.tile_off[e + 1] - tile0;
-    if (ntile == 0) return;
+    const int at = grp * 8 + (in_grp & 7), p = in_grp >> 3;
+    if (at >= a.live[0]) return;
+    const u32x2 entry = reinterpret_cast<const u32x2*>(a.live)[1 + at];
+    const int e = entry[0] & 0xffff, ntile = entry[0] >> 16, tile0 = entry[1];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int nt_local;                                           // this wave's 32-feature tile among the expert's rows
     if (MODE == 0) nt_local = wave < 2 ? 2 * p + wave : a.F / 32 + 2 * p + (wave - 2);
