@@ -111,12 +111,11 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
 // us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
 // 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
 // Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip, which is how a step of
-// few rows finds it.  Against it the weight-streaming launches take 0.85 to 1.0 of their own estimate up to 160 rows (a whole
-// step's weights are as cold there), 0.93 to 1.05 beyond, 1.2 to 1.3 where the reduction is not split (every work-group along the
-// rows reads its strip again); the tall ones near 0.8.  us alone, strip against what was taken before: 7B down at 160 / 192 / 256 /
-// 320 rows 30.8 / 34.1 / 39.2 / 46.9 against 32.6 / 38.5 / 43.6 / 48.7, LM head at 192 / 320 266 / 313 against 313 / 359; but O at 320 (eight
-// planes against four) 15.5 against 14.0, QKV at 192 14.9 against 12.8.  The LM head of up to 160 rows, 680 to 1190 strips, is
-// level in both and stays.
+// few rows finds it; the factors say where the other two kernels' estimates stand against it inside a step.  us of a layer or an LM
+// head, strip against weight-streaming, 7B: O at 5 / 160 rows even / 2.2 less, down at 5 / 96 / 160 / 224 / 320 2.4 / 1.4 / 2.1 / 0.9 / 3.0
+// less, LM head at 160 / 224 13 / 41 less (up to 96
+// rows within 1 %, and 11 more over 2048 inputs); but QKV at 96 and 128 rows 1.6 more, at 224 and 320 2.0 and 5.4 more, O at 224 1.5 more (a
+// work-group that holds so many rows needs seven or eight planes to fill the chip).  Tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
 // tile_mode: -1 = this rule, 0 = the weight-streaming kernel only, 1 = 256-row tall tiles wherever the width allows.
@@ -130,7 +129,7 @@ WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool ex
     }
     if (M <= kStripRows) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
-        const double over_ws = M <= 160 ? 1.15 : allow_split ? 1.07 : 1.25;
+        const double over_ws = !allow_split ? (M <= 96 ? 0.0 : 1.25) : M <= 160 ? 1.15 : 0.93;
         if (s.us < (best.tall.n > 0 ? 0.80 : over_ws) * best.us) best = WsPlan{s.splits, false, std::min(s.tile.tiles, 5), s.us, {}, s.tile};
     }
     return best;

@@ -924,16 +924,18 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t
 
 // Microseconds a launch takes, fitted to 400 launches of thirteen shapes (5 to 320 rows, weights from HBM, an idle chip before each;
 // rms error 10 %): a lone work-group's fills at their pace and its epilogue, the weight stream beside them -- the two add up at
-// nearly twice the stream's rate rather than overlap, and never beat the stream itself -- and the planes, written here and read by the
-// consumer.  More work-groups than CUs only where eight waves fill a CU (six row tiles and more: the LM head); two work-groups of
-// four waves on a CU take 1.75 times one's time and more, and nothing is gained over the weight-streaming kernel.
+// nearly twice the stream's rate rather than overlap, and never beat the stream itself.  More work-groups than CUs: in rounds where
+// eight waves fill a CU, else two on a CU at 1.35 times their share of one's time (the LM head);
+// 296 strips for 5 rows take 58 us where 237 take 44.  The split-K planes, written here and
+// read by the consumer, cost less inside a step than their bytes at HBM's rate (they mostly meet in L2): O of the 7B shape at 160 rows
+// 2.3 us less a layer in eight parts than in seven, 5.2 less than in four.
 static double gemm_bf16_strip_us(int M, int N, int K, int splits, bool glu, const StripTile& s) {
-    const int n = (N / 2 + 16 * s.fs - 1) / (16 * s.fs) * splits, area = s.tiles * s.fs;
+    const int n = (N / 2 + 16 * s.fs - 1) / (16 * s.fs) * splits, area = s.tiles * s.fs, rounds = n / 256, rem = n % 256;
     const double wg = (double)K / 32 / splits * (0.062 + 0.007 * area) + 0.11 * area, stream = (double)N * K * 2.0 / 1.0e6;
-    if (n > 256 && s.tiles <= 5) return 1e30;
-    const int rounds = n / 256, rem = n % 256;
-    const double t = n <= 256 ? wg : wg * (rounds + (rem ? 0.5 + rem / 512.0 : 0.0));
-    return std::max(stream / 6.1, t + stream / 11.3) + (glu ? 0.0 : splits * (double)M * N * 4.0 / 6.0e6) + (splits - 1) * (double)M * N * 4.0 / 4.0e6 + 2.3;
+    const double t = n <= 256 ? wg : s.tiles <= 5 ? wg * 1.35 * n / 256 : wg * (rounds + (rem ? 0.5 + rem / 512.0 : 0.0));
+    const double planes = glu ? 0.0 : splits == 1 ? (double)M * N * 4.0 / 6.0e6 : (2 * splits - 1) * (double)M * N * 4.0 / 12.0e6;
+    const double uneven = n <= 256 || s.tiles > 5 ? 1.0 : std::sqrt((rounds + (rem ? 1 : 0)) * 256.0 / n);       // CUs with one strip more than others
+    return std::max(stream / 6.1, t + stream / 11.3) * uneven + planes + 2.3;
 }
 
 // The strip for M <= kStripRows rows: the lowest that holds them, width and splits by the estimate (us 1e30: none).
