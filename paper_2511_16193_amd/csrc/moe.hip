@@ -31,7 +31,7 @@ template <int ET>
 __global__ __launch_bounds__(256) void moe_logits_kernel(MoeArgs a, int KQ, int wave_planes) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     float* logit = reinterpret_cast<float*>(smem);           // [4 waves][32][E + 1]
-    const int pitch = a.E + 1, plane = kRouterRows * pitch;
+    constexpr int E = 32 * ET, pitch = E + 1, plane = kRouterRows * pitch;
     // 32-row tile of the packed activations, part of the reduction; wave_planes: work-groups of one wave, a quarter part each
     const int tile = blockIdx.x, kq = wave_planes ? blockIdx.y >> 2 : blockIdx.y;
     const int lane = threadIdx.x & 63, wave = wave_planes ? blockIdx.y & 3 : threadIdx.x >> 6;
@@ -97,35 +97,44 @@ __global__ __launch_bounds__(256) void moe_logits_kernel(MoeArgs a, int KQ, int 
 #pragma unroll
             for (int i = 0; i < 4; ++i) logit[wave * plane + l32 * pitch + et * 32 + 8 * q + 4 * lg + i] = acc[et][4 * q + i];
     __syncthreads();
-    float* dst = a.router_logits + ((int64_t)kq * a.T + (int64_t)tile * 32) * a.E;
-    for (int i = threadIdx.x; i < kRouterRows * a.E; i += 256) {
-        const int r = i / a.E, e = i % a.E;
+    float* dst = a.router_logits + ((int64_t)kq * a.T + (int64_t)tile * 32) * E;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < kRouterRows * E; i += 256) {
+        const int r = i / E, e = i % E;
         if (tile * 32 + r < a.T)
-            dst[(int64_t)r * a.E + e] = (logit[r * pitch + e] + logit[plane + r * pitch + e]) + (logit[2 * plane + r * pitch + e] + logit[3 * plane + r * pitch + e]);
+            dst[(int64_t)r * E + e] = (logit[r * pitch + e] + logit[plane + r * pitch + e]) + (logit[2 * plane + r * pitch + e] + logit[3 * plane + r * pitch + e]);
     }
 }
 
-// Router choice of one row by one wave: the planes are added in order (four in flight together; one plane per part, or
-// with QUADS four, of the part's waves), softmax over
-// the experts, top_k by repeated arg-max (lowest id among equals), renormalisation.  Lane j < top_k returns choice j.  The
+// Router choice of one row by one wave.  router_sum: the row's logits, lane l those of experts l, l + 64, ..., its planes added in
+// order, all of up to sixteen in flight together (one plane per part, or with QUADS four, of the part's waves).  route_row:
+// softmax over the experts, top_k by repeated arg-max (lowest id among equals), renormalisation.  Lane j < top_k returns choice j.  The
 // arg-max runs on the probabilities' bit patterns (ordered like the numbers; 0 = taken, or NaN: never chosen) by DPP: through shuffles
 // its sixteen reductions were near half of the time (640 rows: 9.7 -> 5.8 us).
+constexpr int kPerLane = 4;                                  // experts per lane: E <= 256
 template <bool QUADS>
-__device__ __forceinline__ void route_row(const MoeArgs& a, int planes, int t, int lane, int& id, float& weight) {
-    constexpr int PER = 4;                                   // experts per lane: E <= 256
-    float x[PER] = {0.f, 0.f, 0.f, 0.f};
-    for (int kq0 = 0; kq0 < planes; kq0 += 4) {
-        float part[4][PER];
+__device__ __forceinline__ void router_sum(const MoeArgs& a, int planes, int t, int lane, float (&x)[kPerLane]) {
+    constexpr int BATCH = QUADS ? 16 : 4;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+    for (int i = 0; i < kPerLane; ++i) x[i] = 0.f;
+    for (int kq0 = 0; kq0 < planes; kq0 += BATCH) {
+        float part[BATCH][kPerLane];
 #pragma unroll
-            for (int i = 0; i < PER; ++i)
+        for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i)
                 part[u][i] = kq0 + u < planes && lane + 64 * i < a.E ? a.router_logits[((int64_t)(kq0 + u) * a.T + t) * a.E + lane + 64 * i] : 0.f;
 #pragma unroll
-        for (int i = 0; i < PER; ++i)
-            if (QUADS) x[i] += (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
-            else for (int u = 0; u < 4; ++u) x[i] += part[u][i];
+        for (int i = 0; i < kPerLane; ++i)
+#pragma unroll
+            for (int u = 0; u < BATCH; u += 4)
+                if (QUADS) x[i] += (part[u][i] + part[u + 1][i]) + (part[u + 2][i] + part[u + 3][i]);
+                else for (int v = 0; v < 4; ++v) x[i] += part[u + v][i];
     }
+}
+
+__device__ __forceinline__ void route_row(const MoeArgs& a, const float (&x)[kPerLane], int lane, int& id, float& weight) {
+    constexpr int PER = kPerLane;
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < PER; ++i) mx = lane + 64 * i < a.E ? fmaxf(mx, x[i]) : mx;
@@ -166,8 +175,9 @@ __global__ __launch_bounds__(256) void moe_select_kernel(MoeArgs a, int KQ) {
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= a.T) return;
     int id;
-    float w;
-    route_row<false>(a, KQ, t, lane, id, w);
+    float w, x[kPerLane];
+    router_sum<false>(a, KQ, t, lane, x);
+    route_row(a, x, lane, id, w);
     if (lane < a.top_k) {
         a.top_ids[(size_t)t * a.top_k + lane] = id;
         a.top_w[(size_t)t * a.top_k + lane] = w;
@@ -211,12 +221,16 @@ __global__ __launch_bounds__(1024) void moe_route_tile_kernel(MoeArgs a, int pla
     if (threadIdx.x < 256) chosen[threadIdx.x] = 0;
     __syncthreads();
     int id[2] = {0, 0};
+    float x[2][kPerLane];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        if (wave + 16 * r < a.T) router_sum<QUADS>(a, planes, wave + 16 * r, lane, x[r]);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int t = wave + 16 * r;
         if (t < a.T) {
             float w;
-            route_row<QUADS>(a, planes, t, lane, id[r], w);
+            route_row(a, x[r], lane, id[r], w);
             if (lane < a.top_k) {
                 chosen[id[r]] = 1;
                 a.top_ids[t * a.top_k + lane] = id[r];
@@ -249,9 +263,19 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(MoeArgs a) {
     const int n_asg = a.T * a.top_k;
     for (int i = threadIdx.x; i < a.E * W; i += 1024) bm[i] = 0;
     __syncthreads();
-    for (int i = threadIdx.x; i < n_asg; i += 1024) {
-        const int e = a.top_ids[i], t = i / a.top_k;
-        atomicOr(&bm[e * W + (t >> 5)], 1u << (t & 31));
+    // the ids of eight assignments of a thread in flight together; those of the first eight stay for the second pass
+    constexpr int AHEAD = 8;
+    int kept[AHEAD];
+    for (int i0 = threadIdx.x; i0 < n_asg; i0 += 1024 * AHEAD) {
+        int id[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) id[u] = i0 + 1024 * u < n_asg ? a.top_ids[i0 + 1024 * u] : -1;
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int t = (i0 + 1024 * u) / a.top_k;
+            if (id[u] >= 0) atomicOr(&bm[id[u] * W + (t >> 5)], 1u << (t & 31));
+            if (i0 == (int)threadIdx.x) kept[u] = id[u];
+        }
     }
     __syncthreads();
     for (int e = threadIdx.x; e < a.E; e += 1024) {
@@ -270,12 +294,20 @@ __global__ __launch_bounds__(1024) void moe_group_kernel(MoeArgs a) {
             for (int r = cnts[e]; r < (offs[e + 1] - offs[e]) * 32; ++r) a.perm[offs[e] * 32 + r] = 0;
         }
     }
-    for (int i = threadIdx.x; i < n_asg; i += 1024) {
-        const int e = a.top_ids[i], t = i / a.top_k;
-        const int r = below[e * W + (t >> 5)] + __popc(bm[e * W + (t >> 5)] & ((1u << (t & 31)) - 1u));
-        const int prow = offs[e] * 32 + r;
-        a.inv[i] = prow;
-        a.perm[prow] = t;
+    for (int i0 = threadIdx.x; i0 < n_asg; i0 += 1024 * AHEAD) {
+        if (i0 != (int)threadIdx.x) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) kept[u] = i0 + 1024 * u < n_asg ? a.top_ids[i0 + 1024 * u] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int i = i0 + 1024 * u, t = i / a.top_k, e = kept[u];
+            if (e < 0) continue;
+            const int r = below[e * W + (t >> 5)] + __popc(bm[e * W + (t >> 5)] & ((1u << (t & 31)) - 1u));
+            const int prow = offs[e] * 32 + r;
+            a.inv[i] = prow;
+            a.perm[prow] = t;
+        }
     }
 }
 
