@@ -108,13 +108,16 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
 // tall kernel where that is expected to take less.  Inside a step the weight-streaming launches
 // take 1.10 times the estimate above, which was fitted to single projections in a loop (7B at 2304 rows: QKV 89 us against 78,
 // down 282 against 263); the tall ones take theirs.
+// Where the reduction is not split (LM heads) they take 1.1 to 1.3: every work-group along the rows reads its strip again.  us alone,
+// weight-streaming against tall: 152064 x 3584 at 330 / 400 / 500 / 640 rows 445 / 498 / 549 / 681 against 392 / 411 / 446 / 543, 152064 x
+// 5120 558 / 668 / 770 / 942 against 564 / 567 / 614 / 725.
 // us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
 // 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
 // Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip, which is how a step of
 // few rows finds it; the factors say where the other two kernels' estimates stand against it inside a step.  us of a layer or an LM
 // head, strip against weight-streaming, 7B: O at 5 / 160 rows even / 2.2 less, down at 5 / 96 / 160 / 224 / 320 2.4 / 1.4 / 2.1 / 0.9 / 3.0
 // less, LM head at 160 / 224 13 / 41 less (up to 96
-// rows within 1 %, and 11 more over 2048 inputs); but QKV at 96 and 128 rows 1.6 more, at 224 and 320 2.0 and 5.4 more, O at 224 1.5 more (a
+// rows within 1 %, and 11 more over 2048 inputs; alone, strip against tall at 192 / 256 / 320 rows 267 / 291 / 315 against 276 / 322 / 335); but QKV at 96 and 128 rows 1.6 more, at 224 and 320 2.0 and 5.4 more, O at 224 1.5 more (a
 // work-group that holds so many rows needs seven or eight planes to fill the chip).  Tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
@@ -123,14 +126,15 @@ WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool ex
     if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, gemm_bf16_tall_256(M), {}};
     WsPlan best = plan_ws(M, N, K, allow_split, max_splits);
     if (tile_mode == 0 || M < 1) return best;
+    const double ws_us = best.us;
     if (M > 128) {
         const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
-        if (t.us < 1.10 * best.us) best = WsPlan{t.splits, true, 0, t.us, t.tiles, {}};
+        if (t.us < (allow_split ? 1.10 : 1.25) * best.us) best = WsPlan{t.splits, true, 0, t.us, t.tiles, {}};
     }
     if (M <= kStripRows) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
-        const double over_ws = !allow_split ? (M <= 96 ? 0.0 : 1.25) : M <= 160 ? 1.15 : 0.93;
-        if (s.us < (best.tall.n > 0 ? 0.80 : over_ws) * best.us) best = WsPlan{s.splits, false, std::min(s.tile.tiles, 5), s.us, {}, s.tile};
+        const double limit = !allow_split ? (M <= 96 ? 0.0 : 1.25 * ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
+        if (s.us < limit) best = WsPlan{s.splits, false, std::min(s.tile.tiles, 5), s.us, {}, s.tile};
     }
     return best;
 }
