@@ -62,7 +62,7 @@ int sv_op_gemm_bf16_tall(const void *Ap, const void *Wp, void *out, int M, int N
 
 /* The narrow-strip packed-operand kernel: one work-group holds all M rows, as row_tiles (1..5, 6, 8 or 10) tiles of 32, and a strip of
  * 128, 160 or 224 features (gated: half of them gate rows, half the up rows of the same features).  out, gated, the sums and
- * the limits on N, K and splits as for sv_op_gemm_bf16_tall. */
+ * the limits on N, K and splits as for sv_op_gemm_bf16_tall.  Ap, Wp: 16-byte aligned. */
 int sv_op_gemm_bf16_strip(const void *Ap, const void *Wp, void *out, int M, int N, int K, int splits, int gated, int row_tiles,
                           int features, void *stream);
 

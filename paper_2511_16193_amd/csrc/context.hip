@@ -121,8 +121,9 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
 // work-group that holds so many rows needs seven or eight planes to fill the chip).  Tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
+// strips: false where the weights do not start at 16 bytes (strip_reads).
 // tile_mode: -1 = this rule, 0 = the weight-streaming kernel only, 1 = 256-row tall tiles wherever the width allows.
-WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, int max_splits = kMaxSplitsWs) {
+WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, bool strips = true, int max_splits = kMaxSplitsWs) {
     if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, gemm_bf16_tall_256(M), {}};
     WsPlan best = plan_ws(M, N, K, allow_split, max_splits);
     if (tile_mode == 0 || M < 1) return best;
@@ -131,7 +132,7 @@ WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool ex
         const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
         if (t.us < (allow_split ? 1.10 : 1.25) * best.us) best = WsPlan{t.splits, true, 0, t.us, t.tiles, {}};
     }
-    if (M <= kStripRows) {
+    if (strips && M <= kStripRows) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
         const double limit = !allow_split ? (M <= 96 ? 0.0 : 1.25 * ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
         if (s.us < limit) best = WsPlan{s.splits, false, std::min(s.tile.tiles, 5), s.us, {}, s.tile};
@@ -146,8 +147,12 @@ WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool ex
 // shape 95 / 106 / 118 against 96 / 115 / 124, at 256 141 against 125 of the tall tiles.
 // The tall tiles against the weight-streaming kernel at 147 / 192 / 256 / 320 / 512 / 800 rows (in a loop): 65 / 66 / 77 / 98 / 144 / 218
 // against 65 / 86 / 104 / 100 / 160 / 221.
+// The strips request weights straight into LDS, 16 bytes a lane; the kernel that had the rows of small steps before them loads weights
+// into registers, which may start anywhere.  It keeps those that do not start at 16 bytes.
+bool strip_reads(const void* W) { return reinterpret_cast<uintptr_t>(W) % 16 == 0; }
+
 struct GateUp { TallTiles tall; StripTile strip; };       // neither: the weight-streaming kernel
-GateUp plan_gate_up(int T, int N, int K) {
+GateUp plan_gate_up(int T, int N, int K, bool strips) {
     GateUp g{};
     if (N % 256 != 0) return g;
     double limit = 1e29;
@@ -156,7 +161,7 @@ GateUp plan_gate_up(int T, int N, int K) {
         g.tall = t.tiles;
         limit = 0.80 * t.us;
     }
-    if (T <= kStripRows) {
+    if (strips && T <= kStripRows) {
         const StripPlan s = gemm_bf16_strip_plan(T, N, K, 1, 1, true);
         if (s.us < limit) g = GateUp{{}, s.tile};
     }
@@ -309,9 +314,9 @@ struct sv_ctx {
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
     int gemm_variant;                                     // -1 = choose per shape
     int gemm_tile;                                        // packed projections: -1 = by the plans, 0 = weight-streaming kernel only, 1 = tall tiles wherever the shape allows
-    struct PlannedShape { int M, N, K; bool allow_split; WsPlan plan; };
+    struct PlannedShape { int M, N, K; bool allow_split, strips; WsPlan plan; };
     std::vector<PlannedShape> plans;                      // launch plans of packed projections made so far, at most kPlans
-    struct PlannedGateUp { int T; GateUp launch; };
+    struct PlannedGateUp { int T; bool strips; GateUp launch; };
     std::vector<PlannedGateUp> gate_up;                   // the same for the gate/up projection
     bool packed;                                          // projection weights are in fragment order
     int pass_rows;                                        // most rows of a prefill pass
@@ -871,26 +876,26 @@ static int pick_variant(const sv_ctx* c, int M) {
 }
 
 // The plan of a packed projection, made once per shape (some microseconds of host arithmetic).
-static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split) {
+static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split, bool strips) {
     for (const auto& p : c->plans)
-        if (p.M == M && p.N == N && p.K == K && p.allow_split == allow_split) return p.plan;
+        if (p.M == M && p.N == N && p.K == K && p.allow_split == allow_split && p.strips == strips) return p.plan;
     const bool experts = c->model.n_experts > 0;
-    WsPlan p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts);
-    while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, p.splits - 1);
+    WsPlan p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, strips);
+    while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, strips, p.splits - 1);
     if (c->plans.size() >= kPlans) c->plans.clear();
-    c->plans.push_back({M, N, K, allow_split, p});
+    c->plans.push_back({M, N, K, allow_split, strips, p});
     return p;
 }
 
 // The launch of the gate/up projection of T rows, made once per row count as well.
-static GateUp gate_up_launch(sv_ctx* c, int T) {
+static GateUp gate_up_launch(sv_ctx* c, int T, bool strips) {
     for (const auto& g : c->gate_up)
-        if (g.T == T) return g.launch;
+        if (g.T == T && g.strips == strips) return g.launch;
     GateUp g{};
     if (c->gemm_tile == 1) g.tall = gemm_bf16_tall_256(T);
-    else if (c->gemm_tile != 0) g = plan_gate_up(T, 2 * c->model.d_ff, c->model.d_model);
+    else if (c->gemm_tile != 0) g = plan_gate_up(T, 2 * c->model.d_ff, c->model.d_model, strips);
     if (c->gate_up.size() >= kPlans) c->gate_up.clear();
-    c->gate_up.push_back({T, g});
+    c->gate_up.push_back({T, strips, g});
     return g;
 }
 
@@ -898,7 +903,7 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
     ProfScope prof(c, SV_PROF_GEMM);
     if (c->model.dtype == SV_BF16) {
         if (c->packed) {
-            const WsPlan p = planned(c, M, N, K, allow_split);
+            const WsPlan p = planned(c, M, N, K, allow_split, strip_reads(W));
             *splits_out = p.splits;
             if (p.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.strip, c->stream));
             else if (p.tall.n > 0) SV_HIP(c, gemm_bf16_tall((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.tall, c->stream));
@@ -1025,7 +1030,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     if (c->packed && m.d_ff % 64 == 0) {
         // gate/up projection with SwiGLU in its epilogue: the [T, 2F] fp32 intermediate never exists
         ProfScope prof(c, SV_PROF_GEMM);
-        const GateUp g = m.d_ff % 128 == 0 ? gate_up_launch(c, T) : GateUp{};
+        const GateUp g = m.d_ff % 128 == 0 ? gate_up_launch(c, T, strip_reads(c->wgu[l])) : GateUp{};
         const bf16_t *ga = (const bf16_t*)a_norm, *gw = (const bf16_t*)c->wgu[l];
         if (g.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.strip, st));
         else if (g.tall.n > 0) SV_HIP(c, gemm_bf16_tall(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.tall, st));
@@ -1265,7 +1270,7 @@ extern "C" int sv_op_gemm_step_plan(int M, int N, int K, int form, int* splits, 
         return SV_EINVAL;
     WsPlan p{1, false, 0, 0.0, {}, {}};
     if (form == 2) {
-        const GateUp g = plan_gate_up(M, N, K);
+        const GateUp g = plan_gate_up(M, N, K, true);
         p.tall = g.tall;
         p.strip = g.strip;
         p.row_tiles = std::min(g.strip.tiles, 5);
@@ -1301,7 +1306,7 @@ extern "C" int sv_op_gemm_bf16_strip(const void* Ap, const void* Wp, void* out, 
                                      int features, void* stream) {
     if (!Ap || !Wp || !out || M <= 0 || N <= 0 || K <= 0 || splits <= 0 || splits > kMaxSplitsWs || (gated && splits != 1) ||
         N % (gated ? 256 : 128) != 0 || K % 64 != 0 || K % (32 * splits) != 0 || row_tiles < 1 || row_tiles > 10 || row_tiles == 7 ||
-        row_tiles == 9 || M > 32 * row_tiles || (features != 128 && features != 160 && features != 224))
+        row_tiles == 9 || M > 32 * row_tiles || (features != 128 && features != 160 && features != 224) || !strip_reads(Ap) || !strip_reads(Wp))
         return SV_EINVAL;
     return gemm_bf16_strip((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, gated != 0, StripTile{row_tiles, features / 32},
                            (hipStream_t)stream) == hipSuccess ? SV_OK : SV_EHIP;

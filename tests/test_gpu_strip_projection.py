@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from harness import LOGIT_TOL
 from oracle import model as M
 
 pytestmark = pytest.mark.gpu
@@ -70,3 +71,46 @@ def test_strips_that_do_not_exist_are_refused(tiles, features, splits):
     a, w = torch.zeros((96, 64), dtype=torch.bfloat16, device=DEV), torch.zeros((256, 64), dtype=torch.bfloat16, device=DEV)
     with pytest.raises(SvError):
         op_gemm_bf16_strip(a, w, 70, tiles, features, splits)
+
+
+@pytest.mark.parametrize("rows", [5, 100])
+def test_weights_that_start_off_16_bytes_keep_the_weight_streaming_kernel(rows):
+    """One decoding step with packed projections 8 bytes past a 16-byte boundary: the bits of the step that is told to take that kernel
+    everywhere, and within the step tests' tolerance of the step with the same weights on the boundary (which takes strips)."""
+    import paper_2511_16193_amd as P
+    d, ff, V = 256, 2048, 4096
+    lw = {"ln1": bf16((d,), 0.05, 1) + 1, "wqkv": bf16((512, d), 0.02, 2), "wo": bf16((d, 256), 0.02, 3),
+          "ln2": bf16((d,), 0.05, 4) + 1, "w_gate_up": bf16((2 * ff, d), 0.02, 5), "w_down": bf16((d, ff), 0.02, 6)}
+    lw = {n: P.op_pack_weight(t.to(DEV)) if t.dim() == 2 else t.to(DEV) for n, t in lw.items()}
+    head = P.op_pack_weight(bf16((V, d), 0.02, 8).to(DEV))
+    embed, norm = bf16((V, d), 0.5, 7).to(DEV), (bf16((d,), 0.05, 9) + 1).to(DEV)
+
+    def off(t):
+        return torch.cat([t.new_zeros(4), t.flatten()])[4:].view(t.shape)
+
+    def step(shift, mode):
+        place = off if shift else lambda t: t
+        w = {"embed": embed, "lm_head": place(head), "final_norm": norm,
+             "layers": [{n: place(t) if t.dim() > 1 else t for n, t in lw.items()}]}
+        assert (w["lm_head"].data_ptr() % 16 != 0) == shift and (w["layers"][0]["wo"].data_ptr() % 16 != 0) == shift
+        model = dict(n_layers=1, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=ff, vocab=V, n_experts=0, top_k=0,
+                     d_expert=0, dtype="bf16", rope_theta=1.0e4, rms_eps=1.0e-6)
+        ver = P.Verifier(model, w, packed=True, max_batch=rows, max_k=1, max_chains=1, max_seqs=rows, page_size=32, num_pages=rows + 4,
+                         max_pages_per_seq=2, verify_mode=P.SV_MATCH, sample_mode=P.SV_EXP_RACE, temperature=1.0, device=DEV)
+        ver.set_option(P.SV_OPT_GEMM_TILE, mode)
+        kv = bf16((2, 7, 1, 128), 1.0, 10).to(DEV)
+        for b in range(rows):
+            ver.seq_add(b, 7)
+            ver.kv_write(b, 0, 0, kv[0], kv[1])
+        u = torch.rand((rows, 1, 1), generator=torch.Generator().manual_seed(11)).to(DEV)
+        out = {"accepted_len": torch.zeros(rows, dtype=torch.int32, device=DEV), "out_tokens": torch.zeros((rows, 1), dtype=torch.int32, device=DEV),
+               "best_chain": torch.zeros(rows, dtype=torch.int32, device=DEV), "logits": torch.full((rows, 1, V), float("nan"), device=DEV)}
+        ver.step(list(range(rows)), torch.arange(rows, dtype=torch.int32, device=DEV) * 19 % V, None, None, u, out=out)
+        torch.cuda.synchronize()
+        ver.close()
+        return out["logits"]
+
+    kept = step(True, -1)
+    assert torch.equal(kept, step(True, 0))
+    assert float((kept - step(False, -1)).abs().max()) < LOGIT_TOL["bf16"]
+    assert float(kept.std()) > 0.1
