@@ -761,9 +761,10 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
 
 // Combine the chunk partials of one row: out = sum_c 2^(m_c - M) O_c / sum_c 2^(m_c - M) l_c.  A thread
 // owns four consecutive dimensions of one q head; a work-group covers 256 / 32 = 8 heads of the row.  The 32 threads of a
-// head take one piece's (m, l) each, all at once, and share the factors; eight pieces' O are in flight at a time.
+// head take one piece's (m, l) each, all at once, and share the factors; eight pieces' O are in flight at a time.  Rows that
+// follow each other go to one XCD (their packed output shares cache lines): 320 / 800 rows 6.9 / 19.3 -> 5.8 / 16.0 us.
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
-    const int t = blockIdx.x, h = blockIdx.y * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31, d = lane * 4;
+    const int t = xcd_remap(blockIdx.x, gridDim.x), h = blockIdx.y * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31, d = lane * 4;
     if (h >= a.Hq) return;                                // (whole groups of 32)
     const int4 pt = reinterpret_cast<const int4*>(a.row_part)[t];
     const int nch = pt.w;                                 // 0: a request of one piece, already written

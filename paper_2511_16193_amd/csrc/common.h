@@ -137,6 +137,14 @@ template <typename F, int... I> __device__ __forceinline__ void static_for_each(
 }
 template <int N, typename F> __device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
 
+// Work-groups are dealt to the 8 XCDs round-robin by id.  Give XCD x a contiguous range of logical
+// ids instead, so that neighbours in logical order share an L2.
+__device__ __forceinline__ int xcd_remap(int id, int n) {
+    const int q = n >> 3, r = n & 7;
+    const int x = id & 7, local = id >> 3;
+    return x * q + (x < r ? x : r) + local;
+}
+
 // silu(g) * u = g / (1 + e^-g) * u.  Bounded by the vector ALU in the gated projections' epilogues, where it is all that a CU does:
 // the library's exponential and division, each correct from the smallest to the largest float, take some 45 issue slots, this 24.
 // The exponential is formed as the library's is (the argument's product with log2 e in two parts, 2^whole * 2^rest), clamped instead of

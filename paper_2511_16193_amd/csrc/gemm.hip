@@ -20,14 +20,6 @@ namespace sv {
 constexpr int BK = 64;
 constexpr int LDS_PITCH = BK + 8;
 
-// Work-groups are dealt to the 8 XCDs round-robin by id.  Give XCD x a contiguous range of logical
-// ids instead, so that neighbours in logical order share an L2.
-__device__ __forceinline__ int xcd_remap(int id, int n) {
-    const int q = n >> 3, r = n & 7;
-    const int x = id & 7, local = id >> 3;
-    return x * q + (x < r ? x : r) + local;
-}
-
 template <int MT, int NT, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, float* __restrict__ out,
