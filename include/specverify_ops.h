@@ -44,13 +44,23 @@ int sv_op_gemm_bf16_ws(const void *Ap, const void *Wp, float *out, int M, int N,
  * over).  sv_op_gemm_step_plan gives the launch of a verification step.  Host arithmetic only.  N % 128 == 0, K % 64 == 0. */
 int sv_op_gemm_plan(int M, int N, int K, int *splits, int *wide, int *row_tiles);
 
-/* The launch that a verification step, or a prefill pass, makes for a packed projection of M rows (HOST pointers out).
+/* The better launch, of the weight-streaming and the tall kernel, for a packed projection of M rows (HOST pointers out).
  * form 0: QKV, O or down (the reduction may be split), 1: LM head, 2: gate/up with SwiGLU (N = 2 d_ff gate and up rows).
- * *wide > 1: sv_op_gemm_bf16_strip of *wide features with *splits and 2 * tall[0] row tiles, or *row_tiles where tall[0] == 0.
- * Else tall[0] != 0: sv_op_gemm_bf16_tall with these tiles and *splits; tall[0] == 0: sv_op_gemm_bf16_ws with *splits, *wide and
- * *row_tiles, or for form 2 sv_op_gemm_bf16_tall without tiles.  (In a model with experts a strip has the splits of the launch that
- * it replaces.)  Host arithmetic only.  N % 128 == 0 (form 2: 256), K % 64 == 0. */
+ * tall[0] != 0: sv_op_gemm_bf16_tall with these tiles and *splits; tall[0] == 0: sv_op_gemm_bf16_ws with *splits, *wide and
+ * *row_tiles, or for form 2 sv_op_gemm_bf16_tall without tiles.  A step may take a strip in its place: sv_op_gemm_step_launch says
+ * what it really launches.  Host arithmetic only.  N % 128 == 0 (form 2: 256), K % 64 == 0. */
 int sv_op_gemm_step_plan(int M, int N, int K, int form, int *splits, int *wide, int *row_tiles, int *tall);
+
+/* The launch that a verification step, or a prefill pass, makes for a packed projection of M rows (out: HOST pointer).  form, N, K as
+ * above; tile_mode as SV_OPT_GEMM_TILE; experts: of a model with experts; aligned: weights that start at 16 bytes.
+ *   SV_GEMM_WS     sv_op_gemm_bf16_ws with splits, wide and row_tiles; form 2: sv_op_gemm_bf16_tall without tiles
+ *   SV_GEMM_TALL   sv_op_gemm_bf16_tall with tall and splits
+ *   SV_GEMM_STRIP  sv_op_gemm_bf16_strip with row_tiles, features and splits
+ * A field that the kernel has no use for is 0.  (Where a workspace has no room for the splits, a step takes fewer.)
+ * Host arithmetic only. */
+enum sv_gemm_kernel { SV_GEMM_WS = 0, SV_GEMM_TALL = 1, SV_GEMM_STRIP = 2 };
+typedef struct { int kernel, splits, wide, row_tiles, features, tall[4]; } sv_gemm_launch;
+int sv_op_gemm_step_launch(int M, int N, int K, int form, int tile_mode, int experts, int aligned, sv_gemm_launch *out);
 
 /* The tall packed-operand kernel in given tiles: tall (HOST) = {h, n, ht, nt}, n tiles of 64 h rows x 256 features along the rows,
  * then nt of 64 ht; h 3..5, ht < h, nt = 0 if and only if ht = 0; together they cover the M rows and no tile lies beyond them.

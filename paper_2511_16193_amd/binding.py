@@ -26,7 +26,7 @@ EXPORTS = [
     "verify_kv_pool_bytes", "verify_workspace_bytes", "verify_init", "verify_destroy", "verify_last_error",
     "verify_seq_add", "verify_seq_remove", "verify_seq_set_len", "verify_seq_len", "verify_kv_write",
     "verify_kv_read", "verify_prefill", "verify_prefill_batch", "verify_step", "sv_workspace_bytes",
-    "sv_op_gemm_bf16", "sv_op_gemm_bf16_ws", "sv_op_gemm_plan", "sv_op_gemm_step_plan", "sv_op_gemm_bf16_tall", "sv_op_gemm_bf16_strip", "sv_op_pack_rows", "sv_op_pack_weight", "sv_op_sample_scratch_bytes", "sv_op_sample", "sv_op_sample_static", "sv_op_moe_scratch_bytes", "sv_op_moe_ffn", "sv_op_attention", "sv_op_layer", "sv_op_rollback", "sv_set_option", "sv_seq_set_lens", "sv_profile_enable",
+    "sv_op_gemm_bf16", "sv_op_gemm_bf16_ws", "sv_op_gemm_plan", "sv_op_gemm_step_plan", "sv_op_gemm_step_launch", "sv_op_gemm_bf16_tall", "sv_op_gemm_bf16_strip", "sv_op_pack_rows", "sv_op_pack_weight", "sv_op_sample_scratch_bytes", "sv_op_sample", "sv_op_sample_static", "sv_op_moe_scratch_bytes", "sv_op_moe_ffn", "sv_op_attention", "sv_op_layer", "sv_op_rollback", "sv_set_option", "sv_seq_set_lens", "sv_profile_enable",
     "sv_profile_read", "sv_probe_mfma_bf16", "sv_probe_hbm_copy", "sv_probe_hbm_read", "sv_probe_mfma_valu",
     "sv_plan_accept_prob", "sv_plan_tau", "sv_plan_decoupled", "sv_plan_best_window", "sv_fit_affine",
 ]
@@ -42,6 +42,10 @@ class SvWeights(C.Structure):
     _fields_ = [("embed", C.c_void_p), ("lm_head", C.c_void_p), ("final_norm", C.c_void_p)] + \
                [(n, C.POINTER(C.c_void_p)) for n in ("ln1", "wqkv", "wo", "ln2", "w_gate_up", "w_down", "w_router")] + \
                [("packed", C.c_int32)]
+
+
+class SvGemmLaunch(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("kernel", "splits", "wide", "row_tiles", "features")] + [("tall", C.c_int * 4)]
 
 
 class SvRuntime(C.Structure):
@@ -109,6 +113,7 @@ def load_library() -> C.CDLL:
                                        C.c_void_p]
     lib.sv_op_gemm_plan.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
     lib.sv_op_gemm_step_plan.argtypes = [C.c_int] * 4 + [C.POINTER(C.c_int)] * 4
+    lib.sv_op_gemm_step_launch.argtypes = [C.c_int] * 7 + [C.POINTER(SvGemmLaunch)]
     lib.sv_op_gemm_bf16_strip.argtypes = [C.c_void_p] * 3 + [C.c_int] * 7 + [C.c_void_p]
     lib.sv_op_gemm_bf16_tall.argtypes = [C.c_void_p] * 3 + [C.c_int] * 5 + [C.POINTER(C.c_int), C.c_void_p]
     lib.sv_op_sample_scratch_bytes.restype = C.c_size_t
@@ -443,15 +448,25 @@ def op_gemm_bf16_strip(a_packed: torch.Tensor, w_packed: torch.Tensor, M: int, r
 
 
 def op_gemm_step_plan(M: int, N: int, K: int, form: int = 0) -> dict:
-    """The launch a step makes for a packed projection (form 0: QKV, O, down; 1: LM head; 2: gate/up, N = 2 d_ff):
-    {"splits", "wide", "row_tiles", "tall", "strip"}, tall = (h, n, ht, nt) or None, strip = features of a narrow strip or 0 (its
-    32-row tiles: 2 h of tall, or row_tiles)."""
+    """The better of the weight-streaming and the tall launch for a packed projection (form 0: QKV, O, down; 1: LM head; 2: gate/up,
+    N = 2 d_ff): {"splits", "wide", "row_tiles", "tall"}, tall = (h, n, ht, nt) or None.  A step may take a strip instead:
+    op_gemm_step_launch."""
     s, w, t, tiles = C.c_int(), C.c_int(), C.c_int(), (C.c_int * 4)()
     rc = lib().sv_op_gemm_step_plan(M, N, K, form, C.byref(s), C.byref(w), C.byref(t), tiles)
     if rc != 0:
         raise SvError(rc, "sv_op_gemm_step_plan")
-    return {"splits": s.value, "wide": w.value == 1, "row_tiles": t.value, "tall": tuple(tiles) if tiles[0] else None,
-            "strip": w.value if w.value > 1 else 0}
+    return {"splits": s.value, "wide": bool(w.value), "row_tiles": t.value, "tall": tuple(tiles) if tiles[0] else None}
+
+
+def op_gemm_step_launch(M: int, N: int, K: int, form: int = 0, *, tile_mode: int = -1, experts: bool = False, aligned: bool = True) -> dict:
+    """The launch a step makes for a packed projection (form as above): {"kernel": "ws", "tall" or "strip", "splits", "wide", "row_tiles",
+    "features", "tall"}.  tile_mode: SV_OPT_GEMM_TILE; experts: of a model with experts; aligned: weights at 16 bytes."""
+    g = SvGemmLaunch()
+    rc = lib().sv_op_gemm_step_launch(M, N, K, form, tile_mode, 1 if experts else 0, 1 if aligned else 0, C.byref(g))
+    if rc != 0:
+        raise SvError(rc, "sv_op_gemm_step_launch")
+    return {"kernel": ("ws", "tall", "strip")[g.kernel], "splits": g.splits, "wide": bool(g.wide), "row_tiles": g.row_tiles,
+            "features": g.features, "tall": tuple(g.tall) if g.tall[0] else None}
 
 
 def op_gemm_plan(M: int, N: int, K: int) -> dict:

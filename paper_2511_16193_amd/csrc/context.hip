@@ -60,11 +60,12 @@ int pick_splits(int M, int N, int K) {
 // fit to a sweep of every (tiles, width, splits) over thirty shapes of the benchmark models on MI355X (rows 5 to
 // 2304), except the lone work-group's pace, which is taken from whole steps (cold weights); on the sweep the plan
 // chosen was within 0.3 % of the best on average and 4.5 % at worst.
-struct WsPlan { int splits; bool wide; int row_tiles; double us; TallTiles tall; StripTile strip; };   // strip.tiles > 0: a strip; tall.n > 0: the tall kernel
+// strip.tiles > 0: a strip; tall.n > 0: the tall kernel.  ws_us: the weight-streaming kernel's estimate, whichever it is
+struct WsPlan { int splits; bool wide; int row_tiles; double us, ws_us; TallTiles tall; StripTile strip; };
 WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplitsWs) {
     const int slices_all = K / 16;
     const int tiles = (M + 31) / 32;
-    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M), 1e30, {}, {}};
+    WsPlan best{1, false, gemm_bf16_ws_row_tiles(M), 1e30, 1e30, {}, {}};
     // up to 160 rows: one work-group along the rows (cutting so few rows only multiplies the readers of a strip)
     const int mt_lo = tiles <= 5 ? tiles : 1, mt_hi = tiles <= 5 ? tiles : 5;
     for (int mt = mt_lo; mt <= mt_hi; ++mt)
@@ -98,7 +99,7 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
                 t = std::max(t, (double)N * K * 2.0 / 4.98e6);                // a weight stream cannot beat the memory system
                 if (s > 1) t += (double)s * M * N * 4.0 / 5.4e6 + (double)(s - 1) * M * N * 4.0 / 4.0e6;   // planes written here, read by the consumer
                 t += 2.3;
-                if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t, {}, {}};
+                if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t, t, {}, {}};
             }
         }
     return best;
@@ -113,6 +114,15 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
 // 5120 558 / 668 / 770 / 942 against 564 / 567 / 614 / 725.
 // us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
 // 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
+// tile_mode: -1 = this rule, 0 = the weight-streaming kernel only, 1 = 256-row tall tiles wherever the width allows.
+WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, int max_splits = kMaxSplitsWs) {
+    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, 0.0, gemm_bf16_tall_256(M), {}};
+    const WsPlan ws = plan_ws(M, N, K, allow_split, max_splits);
+    if (tile_mode == 0 || M <= 128) return ws;
+    const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
+    return t.us < (allow_split ? 1.10 : 1.25) * ws.us ? WsPlan{t.splits, true, 0, t.us, ws.us, t.tiles, {}} : ws;
+}
+
 // Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip, which is how a step of
 // few rows finds it; the factors say where the other two kernels' estimates stand against it inside a step.  us of a layer or an LM
 // head, strip against weight-streaming, 7B: O at 5 / 160 rows even / 2.2 less, down at 5 / 96 / 160 / 224 / 320 2.4 / 1.4 / 2.1 / 0.9 / 3.0
@@ -122,20 +132,12 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
 // strips: false where the weights do not start at 16 bytes (strip_reads).
-// tile_mode: -1 = this rule, 0 = the weight-streaming kernel only, 1 = 256-row tall tiles wherever the width allows.
 WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, bool strips = true, int max_splits = kMaxSplitsWs) {
-    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, gemm_bf16_tall_256(M), {}};
-    WsPlan best = plan_ws(M, N, K, allow_split, max_splits);
-    if (tile_mode == 0 || M < 1) return best;
-    const double ws_us = best.us;
-    if (M > 128) {
-        const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
-        if (t.us < (allow_split ? 1.10 : 1.25) * best.us) best = WsPlan{t.splits, true, 0, t.us, t.tiles, {}};
-    }
-    if (strips && M <= kStripRows) {
+    WsPlan best = plan_wide(M, N, K, allow_split, tile_mode, max_splits);
+    if (strips && tile_mode != 0 && M >= 1 && M <= kStripRows) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
-        const double limit = !allow_split ? (M <= 96 ? 0.0 : 1.25 * ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
-        if (s.us < limit) best = WsPlan{s.splits, false, std::min(s.tile.tiles, 5), s.us, {}, s.tile};
+        const double limit = !allow_split ? (M <= 96 ? 0.0 : 1.25 * best.ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
+        if (s.us < limit) best = WsPlan{s.splits, false, 0, s.us, best.ws_us, {}, s.tile};
     }
     return best;
 }
@@ -152,9 +154,10 @@ WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool ex
 bool strip_reads(const void* W) { return reinterpret_cast<uintptr_t>(W) % 16 == 0; }
 
 struct GateUp { TallTiles tall; StripTile strip; };       // neither: the weight-streaming kernel
-GateUp plan_gate_up(int T, int N, int K, bool strips) {
+GateUp plan_gate_up(int T, int N, int K, int tile_mode, bool strips) {
     GateUp g{};
-    if (N % 256 != 0) return g;
+    if (tile_mode == 0 || N % 256 != 0) return g;
+    if (tile_mode == 1) return GateUp{gemm_bf16_tall_256(T), {}};
     double limit = 1e29;
     if (T > 160) {
         const TallPlan t = gemm_bf16_tall_plan(T, N, K, 1);
@@ -891,9 +894,7 @@ static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split, bool str
 static GateUp gate_up_launch(sv_ctx* c, int T, bool strips) {
     for (const auto& g : c->gate_up)
         if (g.T == T && g.strips == strips) return g.launch;
-    GateUp g{};
-    if (c->gemm_tile == 1) g.tall = gemm_bf16_tall_256(T);
-    else if (c->gemm_tile != 0) g = plan_gate_up(T, 2 * c->model.d_ff, c->model.d_model, strips);
+    const GateUp g = plan_gate_up(T, 2 * c->model.d_ff, c->model.d_model, c->gemm_tile, strips);
     if (c->gate_up.size() >= kPlans) c->gate_up.clear();
     c->gate_up.push_back({T, strips, g});
     return g;
@@ -1260,26 +1261,38 @@ extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int*
     if (!splits || !wide || !row_tiles || M <= 0 || N <= 0 || K <= 0 || N % 128 != 0 || K % 64 != 0) return SV_EINVAL;
     // of the weight-streaming kernel, but where the 256-row tiles fill the chip four times over
     WsPlan p = plan_ws(M, N, K, true);
-    if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0, {}, {}};
+    if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0, 0.0, {}, {}};
     *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
     return SV_OK;
 }
 
+static bool step_form_ok(int M, int N, int K, int form) {
+    return M > 0 && N > 0 && K > 0 && form >= 0 && form <= 2 && N % (form == 2 ? 256 : 128) == 0 && K % 64 == 0;
+}
+
 extern "C" int sv_op_gemm_step_plan(int M, int N, int K, int form, int* splits, int* wide, int* row_tiles, int* tall) {
-    if (!splits || !wide || !row_tiles || !tall || M <= 0 || N <= 0 || K <= 0 || form < 0 || form > 2 || N % (form == 2 ? 256 : 128) != 0 || K % 64 != 0)
-        return SV_EINVAL;
-    WsPlan p{1, false, 0, 0.0, {}, {}};
+    if (!splits || !wide || !row_tiles || !tall || !step_form_ok(M, N, K, form)) return SV_EINVAL;
+    WsPlan p{1, false, 0, 0.0, 0.0, {}, {}};
+    if (form == 2) p.tall = M > 160 ? gemm_bf16_tall_plan(M, N, K, 1).tiles : TallTiles{};
+    else p = plan_wide(M, N, K, form == 0, -1);
+    *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
+    tall[0] = p.tall.rw; tall[1] = p.tall.n; tall[2] = p.tall.rwt; tall[3] = p.tall.nt;
+    return SV_OK;
+}
+
+extern "C" int sv_op_gemm_step_launch(int M, int N, int K, int form, int tile_mode, int experts, int aligned, sv_gemm_launch* out) {
+    if (!out || !step_form_ok(M, N, K, form) || tile_mode < -1 || tile_mode > 1) return SV_EINVAL;
+    WsPlan p{1, false, 0, 0.0, 0.0, {}, {}};
     if (form == 2) {
-        const GateUp g = plan_gate_up(M, N, K, true);
+        const GateUp g = plan_gate_up(M, N, K, tile_mode, aligned != 0);
         p.tall = g.tall;
         p.strip = g.strip;
-        p.row_tiles = std::min(g.strip.tiles, 5);
     } else {
-        p = plan_packed(M, N, K, form == 0, -1, false);
+        p = plan_packed(M, N, K, form == 0, tile_mode, experts != 0, aligned != 0);
     }
-    *splits = p.splits; *wide = p.strip.tiles > 0 ? 32 * p.strip.fs : p.wide ? 1 : 0; *row_tiles = p.row_tiles;
-    if (p.strip.tiles > 5) p.tall = TallTiles{p.strip.tiles / 2, 1, 0, 0};
-    tall[0] = p.tall.rw; tall[1] = p.tall.n; tall[2] = p.tall.rwt; tall[3] = p.tall.nt;
+    const bool strip = p.strip.tiles > 0, tall = !strip && p.tall.n > 0;
+    *out = sv_gemm_launch{strip ? SV_GEMM_STRIP : tall ? SV_GEMM_TALL : SV_GEMM_WS, p.splits, !strip && !tall && p.wide ? 1 : 0,
+                          strip ? p.strip.tiles : tall ? 0 : p.row_tiles, 32 * p.strip.fs, {p.tall.rw, p.tall.n, p.tall.rwt, p.tall.nt}};
     return SV_OK;
 }
 

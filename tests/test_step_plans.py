@@ -1,7 +1,7 @@
 """The launch plans of a step's packed projections, host arithmetic: every one is a launch that its kernel takes."""
 import pytest
 
-from paper_2511_16193_amd import SvError, op_gemm_step_plan
+from paper_2511_16193_amd import SvError, op_gemm_step_launch, op_gemm_step_plan
 
 # QKV, O, down; LM head; gate/up of the 7B-, 32B- and expert-shaped decoders, and small models
 SHAPES = {0: [(4608, 3584), (3584, 3584), (3584, 18944), (7168, 5120), (5120, 5120), (5120, 27648), (5120, 2048), (2048, 4096), (256, 1024), (1536, 64)],
@@ -30,7 +30,40 @@ def test_step_plans_are_launchable(form):
                 assert mt * 32 * ((M + 32 * mt - 1) // (32 * mt)) < M + 32 * mt, at
 
 
+ROWS = [1, 5, 33, 40, 96, 97, 128, 129, 147, 160, 161, 192, 200, 256, 289, 320, 321, 500, 777, 1280, 2304, 4096]
+
+
+@pytest.mark.parametrize("experts", [False, True])
+@pytest.mark.parametrize("form", [0, 1, 2])
+def test_step_launches_are_launchable(form, experts):
+    """What a step really launches: each of the three kernels occurs, in a form that it takes, and where it is not a strip it is the
+    launch that op_gemm_step_plan gives."""
+    seen = set()
+    for M in ROWS:
+        for N, K in SHAPES[form]:
+            p, wide = op_gemm_step_launch(M, N, K, form, experts=experts), op_gemm_step_plan(M, N, K, form)
+            s, at = p["splits"], (M, N, K, form, p)
+            seen.add(p["kernel"])
+            assert 1 <= s <= 16 and (form == 0 or s == 1), at
+            if p["kernel"] == "strip":
+                assert p["features"] in (128, 160, 224) and p["row_tiles"] in (1, 2, 3, 4, 5, 6, 8, 10), at
+                assert p["row_tiles"] * 32 >= M > 32 * (p["row_tiles"] - (1 if p["row_tiles"] <= 6 else 2)) and M <= 320, at
+                assert K % (32 * s) == 0 and p["tall"] is None and not p["wide"], at
+                if experts:                                                 # the splits, and the bits, of the launch it replaces
+                    assert s == wide["splits"], at
+            elif p["kernel"] == "tall":
+                assert (p["tall"], s) == (wide["tall"], wide["splits"]) and p["row_tiles"] == p["features"] == 0, at
+            else:
+                assert wide["tall"] is None and p["features"] == 0 and p["tall"] is None, at
+                assert (s, p["wide"], p["row_tiles"]) == (wide["splits"], wide["wide"], wide["row_tiles"]), at
+    assert seen >= ({"strip", "tall"} if form == 2 else {"ws", "tall", "strip"})
+
+
 def test_what_is_no_projection_of_a_step_is_refused():
     for args in [(0, 256, 64, 0), (5, 200, 64, 0), (5, 256, 32, 0), (5, 384, 64, 2), (5, 256, 64, 3), (5, 256, 64, -1)]:
         with pytest.raises(SvError):
             op_gemm_step_plan(*args)
+        with pytest.raises(SvError):
+            op_gemm_step_launch(*args)
+    with pytest.raises(SvError):
+        op_gemm_step_launch(5, 256, 64, 0, tile_mode=2)

@@ -3,7 +3,7 @@
     python -m workloads.profile_gemm [--config cfg5] [--rows 800]
 
 For each projection shape of the model (QKV, O, gate/up, down, LM head) at the given number of rows: the
-library's own kernel in the launch a verification step gives it (sv_op_gemm_step_plan, packed operands), and torch's
+library's own kernel in the launch a verification step gives it (sv_op_gemm_step_launch, packed operands), and torch's
 matmul on the same bf16 operands (hipBLASLt / rocBLAS), each the mean of 20 runs after 3 warm-up runs, with seeded N(0,1)
 activations and N(0,0.02) weights.  The gate/up projection is timed with the SwiGLU epilogue it carries inside a step, the
 library's without.  Prints one JSON line.  Run from the repository root.
@@ -52,12 +52,11 @@ def main(argv=None) -> int:
         a = torch.randn((M, K), generator=g, device=dev).to(torch.bfloat16)
         w = (torch.randn((N, K), generator=g, device=dev) * 0.02).to(torch.bfloat16)
         form = {"lm_head": 1, "gate_up": 2}.get(name, 0)
-        plan = P.op_gemm_step_plan(M, N, K, form)
+        plan = P.op_gemm_step_launch(M, N, K, form, experts=s.n_experts > 0)
         ap_, wp = P.op_pack_rows(a), P.op_pack_weight(w)
-        if plan["strip"]:
-            tiles = 2 * plan["tall"][0] if plan["tall"] else plan["row_tiles"]
-            ours = mean_us(lambda: P.op_gemm_bf16_strip(ap_, wp, M, tiles, plan["strip"], plan["splits"], gated=form == 2))
-        elif plan["tall"] or form == 2:
+        if plan["kernel"] == "strip":
+            ours = mean_us(lambda: P.op_gemm_bf16_strip(ap_, wp, M, plan["row_tiles"], plan["features"], plan["splits"], gated=form == 2))
+        elif plan["kernel"] == "tall" or form == 2:
             ours = mean_us(lambda: P.op_gemm_bf16_tall(ap_, wp, M, plan["tall"], plan["splits"], gated=form == 2))
         else:
             ours = mean_us(lambda: P.op_gemm_bf16_ws(ap_, wp, M, splits=plan["splits"], wide=plan["wide"], row_tiles=plan["row_tiles"]))
