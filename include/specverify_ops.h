@@ -35,7 +35,7 @@ int sv_op_gemm_bf16(const void *A, const void *W, float *out, int M, int N, int 
  * wide != 0: 256 output features per work-group (N % 256 == 0), else 128.  K % (64*splits) == 0.
  * row_tiles: 32-row tiles per work-group, 1..5, or 0 = as few work-groups along the rows as five tiles each allow;
  * 8 = the tall packed-operand kernel instead (256 rows x 256 features per work-group, both operands through LDS, a shorter
- * tile for the rows that are left; needs N % 256 == 0). */
+ * tile for the rows that are left; needs N % 256 == 0; operands that do not start at 16 bytes stay with this kernel). */
 int sv_op_gemm_bf16_ws(const void *Ap, const void *Wp, float *out, int M, int N, int K, int splits, int wide,
                        int row_tiles, void *stream);
 
@@ -66,7 +66,8 @@ int sv_op_gemm_step_launch(int M, int N, int K, int form, int tile_mode, int exp
  * then nt of 64 ht; h 3..5, ht < h, nt = 0 if and only if ht = 0; together they cover the M rows and no tile lies beyond them.
  * gated == 0: out fp32 [splits, M, N], the sums of sv_op_gemm_bf16_ws with as many splits.  gated != 0 (splits == 1, N = 2 F,
  * F % 128 == 0): out = silu(gate) * up, bf16, in the order sv_op_pack_rows writes, [ceil(M/32)*32, F]; tall == NULL: the
- * same by the weight-streaming kernel.  N % 128 == 0, K % 64 == 0, K % (32 * splits) == 0. */
+ * same by the weight-streaming kernel.  N % 128 == 0, K % 64 == 0, K % (32 * splits) == 0.
+ * Operands that do not start at 16 bytes: the same sums by the weight-streaming kernel (K % (64 * splits) == 0). */
 int sv_op_gemm_bf16_tall(const void *Ap, const void *Wp, void *out, int M, int N, int K, int splits, int gated,
                          const int *tall, void *stream);
 
@@ -185,7 +186,8 @@ int sv_probe_mfma_valu(float *sink, int iters, int valu_per_mfma, int waves_per_
 /* Tuning / diagnostic knobs of a context.
  *   SV_OPT_GEMM_VARIANT  work-group tile of the row-major bf16 projections (0..2; -1 = per shape, default)
  *   SV_OPT_GEMM_TILE  kernels of the packed projections: -1 = as the launch plan expects it to pay (default), 0 = the
- *                     weight-streaming kernel only, 1 = the tall kernel with 256-row tiles wherever the shape allows (output features a multiple of 256)
+ *                     weight-streaming kernel only, 1 = the tall kernel with 256-row tiles wherever the shape allows (output features a multiple
+ *                     of 256).  Weights that do not start at 16 bytes take the weight-streaming kernel in every mode
  *   SV_OPT_ATTN_GENERIC  1 = always use the generic attention, a work-group per row and head (default 0)
  *   SV_OPT_ATTN_MIN_ROW_TILES  lower bound (1..4) on the 16-row tiles the bf16 attention is built for
  *   SV_OPT_ATTN_MAX_ROW_TILES  most 16-row tiles (1..4, default 4) one work-group of the bf16 attention takes;

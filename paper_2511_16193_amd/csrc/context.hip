@@ -105,6 +105,10 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
     return best;
 }
 
+// The tall kernel and the strips request their operands straight into LDS, 16 bytes a lane; the weight-streaming kernel loads them into
+// registers, which may start at any element.  It keeps operands that do not start at 16 bytes, at any number of rows.
+bool direct_loads(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
 // Launch plan of a packed projection: the weight-streaming kernel, or from more rows than one of its work-groups holds on the
 // tall kernel where that is expected to take less.  Inside a step the weight-streaming launches
 // take 1.10 times the estimate above, which was fitted to single projections in a loop (7B at 2304 rows: QKV 89 us against 78,
@@ -115,10 +119,11 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
 // us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
 // 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
 // tile_mode: -1 = this rule, 0 = the weight-streaming kernel only, 1 = 256-row tall tiles wherever the width allows.
-WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, int max_splits = kMaxSplitsWs) {
-    if (tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, 0.0, gemm_bf16_tall_256(M), {}};
+// direct: weights that direct_loads takes.
+WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, bool direct, int max_splits = kMaxSplitsWs) {
+    if (direct && tile_mode == 1 && N % 256 == 0) return WsPlan{1, true, 0, 0.0, 0.0, gemm_bf16_tall_256(M), {}};
     const WsPlan ws = plan_ws(M, N, K, allow_split, max_splits);
-    if (tile_mode == 0 || M <= 128) return ws;
+    if (!direct || tile_mode == 0 || M <= 128) return ws;
     const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
     return t.us < (allow_split ? 1.10 : 1.25) * ws.us ? WsPlan{t.splits, true, 0, t.us, ws.us, t.tiles, {}} : ws;
 }
@@ -131,10 +136,9 @@ WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, int max_s
 // work-group that holds so many rows needs seven or eight planes to fill the chip).  Tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
-// strips: false where the weights do not start at 16 bytes (strip_reads).
-WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, bool strips = true, int max_splits = kMaxSplitsWs) {
-    WsPlan best = plan_wide(M, N, K, allow_split, tile_mode, max_splits);
-    if (strips && tile_mode != 0 && M >= 1 && M <= kStripRows) {
+WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, bool direct = true, int max_splits = kMaxSplitsWs) {
+    WsPlan best = plan_wide(M, N, K, allow_split, tile_mode, direct, max_splits);
+    if (direct && tile_mode != 0 && M >= 1 && M <= kStripRows) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
         const double limit = !allow_split ? (M <= 96 ? 0.0 : 1.25 * best.ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
         if (s.us < limit) best = WsPlan{s.splits, false, 0, s.us, best.ws_us, {}, s.tile};
@@ -149,14 +153,10 @@ WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool ex
 // shape 95 / 106 / 118 against 96 / 115 / 124, at 256 141 against 125 of the tall tiles.
 // The tall tiles against the weight-streaming kernel at 147 / 192 / 256 / 320 / 512 / 800 rows (in a loop): 65 / 66 / 77 / 98 / 144 / 218
 // against 65 / 86 / 104 / 100 / 160 / 221.
-// The strips request weights straight into LDS, 16 bytes a lane; the kernel that had the rows of small steps before them loads weights
-// into registers, which may start anywhere.  It keeps those that do not start at 16 bytes.
-bool strip_reads(const void* W) { return reinterpret_cast<uintptr_t>(W) % 16 == 0; }
-
 struct GateUp { TallTiles tall; StripTile strip; };       // neither: the weight-streaming kernel
-GateUp plan_gate_up(int T, int N, int K, int tile_mode, bool strips) {
+GateUp plan_gate_up(int T, int N, int K, int tile_mode, bool direct) {
     GateUp g{};
-    if (tile_mode == 0 || N % 256 != 0) return g;
+    if (!direct || tile_mode == 0 || N % 256 != 0) return g;
     if (tile_mode == 1) return GateUp{gemm_bf16_tall_256(T), {}};
     double limit = 1e29;
     if (T > 160) {
@@ -164,7 +164,7 @@ GateUp plan_gate_up(int T, int N, int K, int tile_mode, bool strips) {
         g.tall = t.tiles;
         limit = 0.80 * t.us;
     }
-    if (strips && T <= kStripRows) {
+    if (T <= kStripRows) {
         const StripPlan s = gemm_bf16_strip_plan(T, N, K, 1, 1, true);
         if (s.us < limit) g = GateUp{{}, s.tile};
     }
@@ -317,9 +317,9 @@ struct sv_ctx {
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
     int gemm_variant;                                     // -1 = choose per shape
     int gemm_tile;                                        // packed projections: -1 = by the plans, 0 = weight-streaming kernel only, 1 = tall tiles wherever the shape allows
-    struct PlannedShape { int M, N, K; bool allow_split, strips; WsPlan plan; };
+    struct PlannedShape { int M, N, K; bool allow_split, direct; WsPlan plan; };
     std::vector<PlannedShape> plans;                      // launch plans of packed projections made so far, at most kPlans
-    struct PlannedGateUp { int T; bool strips; GateUp launch; };
+    struct PlannedGateUp { int T; bool direct; GateUp launch; };
     std::vector<PlannedGateUp> gate_up;                   // the same for the gate/up projection
     bool packed;                                          // projection weights are in fragment order
     int pass_rows;                                        // most rows of a prefill pass
@@ -879,24 +879,24 @@ static int pick_variant(const sv_ctx* c, int M) {
 }
 
 // The plan of a packed projection, made once per shape (some microseconds of host arithmetic).
-static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split, bool strips) {
+static WsPlan planned(sv_ctx* c, int M, int N, int K, bool allow_split, bool direct) {
     for (const auto& p : c->plans)
-        if (p.M == M && p.N == N && p.K == K && p.allow_split == allow_split && p.strips == strips) return p.plan;
+        if (p.M == M && p.N == N && p.K == K && p.allow_split == allow_split && p.direct == direct) return p.plan;
     const bool experts = c->model.n_experts > 0;
-    WsPlan p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, strips);
-    while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, strips, p.splits - 1);
+    WsPlan p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, direct);
+    while (p.splits > 1 && (size_t)p.splits * M * N > c->lay.part_floats) p = plan_packed(M, N, K, allow_split, c->gemm_tile, experts, direct, p.splits - 1);
     if (c->plans.size() >= kPlans) c->plans.clear();
-    c->plans.push_back({M, N, K, allow_split, strips, p});
+    c->plans.push_back({M, N, K, allow_split, direct, p});
     return p;
 }
 
 // The launch of the gate/up projection of T rows, made once per row count as well.
-static GateUp gate_up_launch(sv_ctx* c, int T, bool strips) {
+static GateUp gate_up_launch(sv_ctx* c, int T, bool direct) {
     for (const auto& g : c->gate_up)
-        if (g.T == T && g.strips == strips) return g.launch;
-    const GateUp g = plan_gate_up(T, 2 * c->model.d_ff, c->model.d_model, c->gemm_tile, strips);
+        if (g.T == T && g.direct == direct) return g.launch;
+    const GateUp g = plan_gate_up(T, 2 * c->model.d_ff, c->model.d_model, c->gemm_tile, direct);
     if (c->gate_up.size() >= kPlans) c->gate_up.clear();
-    c->gate_up.push_back({T, strips, g});
+    c->gate_up.push_back({T, direct, g});
     return g;
 }
 
@@ -904,7 +904,7 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
     ProfScope prof(c, SV_PROF_GEMM);
     if (c->model.dtype == SV_BF16) {
         if (c->packed) {
-            const WsPlan p = planned(c, M, N, K, allow_split, strip_reads(W));
+            const WsPlan p = planned(c, M, N, K, allow_split, direct_loads(W));
             *splits_out = p.splits;
             if (p.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.strip, c->stream));
             else if (p.tall.n > 0) SV_HIP(c, gemm_bf16_tall((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.tall, c->stream));
@@ -1031,7 +1031,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     if (c->packed && m.d_ff % 64 == 0) {
         // gate/up projection with SwiGLU in its epilogue: the [T, 2F] fp32 intermediate never exists
         ProfScope prof(c, SV_PROF_GEMM);
-        const GateUp g = m.d_ff % 128 == 0 ? gate_up_launch(c, T, strip_reads(c->wgu[l])) : GateUp{};
+        const GateUp g = m.d_ff % 128 == 0 ? gate_up_launch(c, T, direct_loads(c->wgu[l])) : GateUp{};
         const bf16_t *ga = (const bf16_t*)a_norm, *gw = (const bf16_t*)c->wgu[l];
         if (g.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.strip, st));
         else if (g.tall.n > 0) SV_HIP(c, gemm_bf16_tall(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.tall, st));
@@ -1252,8 +1252,9 @@ extern "C" int sv_op_gemm_bf16_ws(const void* Ap, const void* Wp, float* out, in
     if (!Ap || !Wp || !out || M <= 0 || N <= 0 || K <= 0 || splits <= 0 || N % (wide ? 256 : 128) != 0 ||
         K % (64 * splits) != 0 || row_tiles < 0 || (row_tiles > 5 && row_tiles != 8) || (row_tiles == 8 && N % 256 != 0))
         return SV_EINVAL;
-    const hipError_t e = row_tiles == 8 ? gemm_bf16_tall((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, false, gemm_bf16_tall_256(M), (hipStream_t)stream)
-                                        : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, wide != 0, (hipStream_t)stream, row_tiles);
+    const bool tall = row_tiles == 8 && direct_loads(Ap) && direct_loads(Wp);      // (the other kernel's sums are the same)
+    const hipError_t e = tall ? gemm_bf16_tall((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, false, gemm_bf16_tall_256(M), (hipStream_t)stream)
+                                        : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, wide != 0, (hipStream_t)stream, row_tiles == 8 ? 0 : row_tiles);
     return e == hipSuccess ? SV_OK : SV_EHIP;
 }
 
@@ -1274,7 +1275,7 @@ extern "C" int sv_op_gemm_step_plan(int M, int N, int K, int form, int* splits, 
     if (!splits || !wide || !row_tiles || !tall || !step_form_ok(M, N, K, form)) return SV_EINVAL;
     WsPlan p{1, false, 0, 0.0, 0.0, {}, {}};
     if (form == 2) p.tall = M > 160 ? gemm_bf16_tall_plan(M, N, K, 1).tiles : TallTiles{};
-    else p = plan_wide(M, N, K, form == 0, -1);
+    else p = plan_wide(M, N, K, form == 0, -1, true);
     *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
     tall[0] = p.tall.rw; tall[1] = p.tall.n; tall[2] = p.tall.rwt; tall[3] = p.tall.nt;
     return SV_OK;
@@ -1302,16 +1303,19 @@ extern "C" int sv_op_gemm_bf16_tall(const void* Ap, const void* Wp, void* out, i
         N % (gated ? 256 : 128) != 0 || K % 64 != 0 || K % (32 * splits) != 0)
         return SV_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    if (!tall) {
-        if (!gated) return SV_EINVAL;
-        return gemm_bf16_ws_glu((const bf16_t*)Ap, (const bf16_t*)Wp, (bf16_t*)out, M, N / 2, K, st) == hipSuccess ? SV_OK : SV_EHIP;
-    }
+    auto weight_streaming = [&]() -> int {
+        const hipError_t e = gated ? gemm_bf16_ws_glu((const bf16_t*)Ap, (const bf16_t*)Wp, (bf16_t*)out, M, N / 2, K, st)
+                                   : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, N % 256 == 0, st);
+        return e == hipSuccess ? SV_OK : SV_EHIP;
+    };
+    if (!tall) return gated ? weight_streaming() : SV_EINVAL;
     const TallTiles tl{tall[0], tall[1], tall[2], tall[3]};
     // heights that exist; all rows covered, no tile of padding alone (which also bounds the grid)
     if (tl.rw < 3 || tl.rw > 5 || tl.rwt < 0 || tl.rwt >= tl.rw || (tl.nt > 0) != (tl.rwt > 0) || tl.n < 1 || tl.nt < 0 || tl.n > M || tl.nt > M)
         return SV_EINVAL;
     const long long rows = 64LL * tl.rw * tl.n + 64LL * tl.rwt * tl.nt;
     if (rows < M || rows - 64 * (tl.nt > 0 ? tl.rwt : tl.rw) >= M) return SV_EINVAL;
+    if (!direct_loads(Ap) || !direct_loads(Wp)) return K % (64 * splits) == 0 ? weight_streaming() : SV_EINVAL;     // the same sums
     return gemm_bf16_tall((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, gated != 0, tl, st) == hipSuccess ? SV_OK : SV_EHIP;
 }
 
@@ -1319,7 +1323,7 @@ extern "C" int sv_op_gemm_bf16_strip(const void* Ap, const void* Wp, void* out, 
                                      int features, void* stream) {
     if (!Ap || !Wp || !out || M <= 0 || N <= 0 || K <= 0 || splits <= 0 || splits > kMaxSplitsWs || (gated && splits != 1) ||
         N % (gated ? 256 : 128) != 0 || K % 64 != 0 || K % (32 * splits) != 0 || row_tiles < 1 || row_tiles > 10 || row_tiles == 7 ||
-        row_tiles == 9 || M > 32 * row_tiles || (features != 128 && features != 160 && features != 224) || !strip_reads(Ap) || !strip_reads(Wp))
+        row_tiles == 9 || M > 32 * row_tiles || (features != 128 && features != 160 && features != 224) || !direct_loads(Ap) || !direct_loads(Wp))
         return SV_EINVAL;
     return gemm_bf16_strip((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, gated != 0, StripTile{row_tiles, features / 32},
                            (hipStream_t)stream) == hipSuccess ? SV_OK : SV_EHIP;

@@ -114,6 +114,24 @@ def test_every_gated_pair_of_heights_equals_the_weight_streaming_kernel(h, ht, F
         assert float((got.float() != want).float().mean()) < 0.01
 
 
+@pytest.mark.parametrize("which", ["weights", "rows"])
+def test_operands_off_16_bytes_take_the_weight_streaming_kernel(which):
+    """The same sums through every entry point that can ask for tall tiles; a split of an odd number of fills, which the other kernel has
+    no form for, is refused."""
+    from paper_2511_16193_amd import SvError, op_gemm_bf16_tall, op_gemm_bf16_ws, op_pack_rows, op_pack_weight
+    M_, N, K = 260, 512, 192
+    ap, wp = op_pack_rows(bf16((M_, K), 1.0, 1).to(DEV)), op_pack_weight(bf16((N, K), 0.02, 2).to(DEV))
+    off = lambda t: torch.cat([t.new_zeros(4), t.flatten()])[4:].view(t.shape)
+    a, w = (off(ap), wp) if which == "rows" else (ap, off(wp))
+    assert a.data_ptr() % 16 or w.data_ptr() % 16
+    assert torch.equal(op_gemm_bf16_tall(a, w, M_, (4, 1, 1, 1), 3), op_gemm_bf16_tall(ap, wp, M_, (4, 1, 1, 1), 3))
+    assert torch.equal(op_gemm_bf16_ws(a, w, M_, splits=3, wide=True, row_tiles=8), op_gemm_bf16_ws(ap, wp, M_, splits=3, wide=True, row_tiles=8))
+    rows = lambda t: t.view(-1, N // 32, 2, 32, 8).permute(0, 3, 1, 2, 4).reshape(-1, N // 2)[:M_]
+    assert torch.equal(rows(op_gemm_bf16_tall(a, w, M_, (4, 1, 1, 1), gated=True)), rows(op_gemm_bf16_tall(ap, wp, M_, (4, 1, 1, 1), gated=True)))
+    with pytest.raises(SvError):
+        op_gemm_bf16_tall(a, w, M_, (4, 1, 1, 1), 2)
+
+
 @pytest.mark.parametrize("tall", [(2, 2, 0, 0), (6, 1, 0, 0), (4, 1, 4, 1), (4, 1, 2, 0), (4, 1, 0, 1), (4, 0, 2, 2), (4, 1, 0, 0), (4, 3, 0, 0), (3, 1, 1, 3)])
 def test_tiles_that_do_not_fit_the_rows_are_refused(tall):
     """260 rows: heights that do not exist, short tiles without a height, rows left uncovered, tiles of padding alone."""

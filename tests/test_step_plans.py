@@ -59,6 +59,18 @@ def test_step_launches_are_launchable(form, experts):
     assert seen >= ({"strip", "tall"} if form == 2 else {"ws", "tall", "strip"})
 
 
+@pytest.mark.parametrize("tile_mode", [-1, 0, 1])
+@pytest.mark.parametrize("form", [0, 1, 2])
+def test_weights_off_16_bytes_keep_the_kernel_with_ordinary_loads(form, tile_mode):
+    """The tall kernel and the strips request 16 bytes a lane straight into LDS; the weight-streaming kernel loads into registers."""
+    for M in ROWS:
+        for N, K in SHAPES[form]:
+            p = op_gemm_step_launch(M, N, K, form, tile_mode=tile_mode, aligned=False)
+            assert p["kernel"] == "ws", (M, N, K, p)
+            if form != 2:
+                assert K % (64 * p["splits"]) == 0 and (not p["wide"] or N % 256 == 0) and 1 <= p["row_tiles"] <= 5, (M, N, K, p)
+
+
 def test_what_is_no_projection_of_a_step_is_refused():
     for args in [(0, 256, 64, 0), (5, 200, 64, 0), (5, 256, 32, 0), (5, 384, 64, 2), (5, 256, 64, 3), (5, 256, 64, -1)]:
         with pytest.raises(SvError):
