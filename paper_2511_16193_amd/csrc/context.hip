@@ -146,11 +146,17 @@ WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool ex
     return best;
 }
 
-// Gate/up projection with SwiGLU of T rows (N = 2 d_ff): strips where they come to no more than the CUs; from more than five 32-row
-// tiles on the tall tiles, unless the strips are expected to be well ahead (one work-group of the weight-streaming
-// kernel along the rows no longer holds them, and every further one reads the strip again); else that kernel.  us alone of the 7B
-// shape at 64 / 147 / 192 / 256 / 320 rows, strip against what was taken before: 44 / 52 / 58 / 70 / 78 against 50 / 63 / 70 / 77 / 85; of the 32B
-// shape 95 / 106 / 118 against 96 / 115 / 124, at 256 141 against 125 of the tall tiles.
+// Gate/up projection with SwiGLU of T rows (N = 2 d_ff): up to five 32-row tiles strips or the weight-streaming kernel, from then on
+// strips or tall tiles (one work-group of the weight-streaming kernel along the rows no longer holds them, and every further one
+// reads the strip again).  Strips where they come to no more than the CUs and, from 161 rows on, are expected to be well ahead.  us of a
+// layer inside steps, strip against weight-streaming at 5 / 96 / 160 rows: 18944 x 3584 1.6 / 8.6 / 9.6 less, 27648 x 5120 0.4 more / 1.2 / 3.4
+// less, 14336 x 4096 11 / 14 / 48 less, 11008 x 2048 7 / 6 / 11 less; against tall at 192 / 256 / 320 18944 x 3584 11.9 / 6.0 / 5.0 less,
+// 27648 x 5120 1.1 / 1.6 / 0.4 more, 14336 x 4096 14.2 / 2.8 less / 6.0 more (ten row tiles are estimated too low: 0.77 for 0.80 there).
+// Two exceptions up to 160 rows.  More strips than CUs where the weight-streaming kernel's own strips of 128 features are still one
+// round: 29568 x 8192 (462 against 231) 5.3 / 23 / 32 more, 30720 x 4096 alone 87 / 97 / 114 us against 86 / 90 / 101; with a second round in both,
+// 33792, 40960 and 53248 x 4096 101 / 114 / 126, 115 / 122 / 139 and 151 / 161 / 174 against 128 / 140 / 124, 131 / 144 / 154 and 152 / 161 / 179.
+// And 129 to 160 rows of so few features that the weight-streaming kernel's five 32-row tiles of every strip run at once: 4864 x 896 3.3
+// more, alone 5120 and 6400 x 2048 26.4 and 25.9 against 23.2 and 23.4, but 7168 (56 strips) 26.8 against 31.1.
 // The tall tiles against the weight-streaming kernel at 147 / 192 / 256 / 320 / 512 / 800 rows (in a loop): 65 / 66 / 77 / 98 / 144 / 218
 // against 65 / 86 / 104 / 100 / 160 / 221.
 struct GateUp { TallTiles tall; StripTile strip; };       // neither: the weight-streaming kernel
@@ -158,17 +164,17 @@ GateUp plan_gate_up(int T, int N, int K, int tile_mode, bool direct) {
     GateUp g{};
     if (!direct || tile_mode == 0 || N % 256 != 0) return g;
     if (tile_mode == 1) return GateUp{gemm_bf16_tall_256(T), {}};
-    double limit = 1e29;
+    const StripPlan s = T <= kStripRows ? gemm_bf16_strip_plan(T, N, K, 1, 1, true) : StripPlan{1, {0, 4}, 1e30};
+    const bool one_round = gemm_bf16_strips(N, s.tile) <= 256;
+    bool strip;
     if (T > 160) {
         const TallPlan t = gemm_bf16_tall_plan(T, N, K, 1);
         g.tall = t.tiles;
-        limit = 0.80 * t.us;
+        strip = one_round && s.us < (T > 256 ? 0.77 : 0.80) * t.us;
+    } else {
+        strip = s.us < 1e29 && (one_round || N / 256 > 256) && (T <= 128 || 5 * (N / 256) > 256);
     }
-    if (T <= kStripRows) {
-        const StripPlan s = gemm_bf16_strip_plan(T, N, K, 1, 1, true);
-        if (s.us < limit) g = GateUp{{}, s.tile};
-    }
-    return g;
+    return strip ? GateUp{{}, s.tile} : g;
 }
 
 struct Layout {                       // byte offsets into the workspace

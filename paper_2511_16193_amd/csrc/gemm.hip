@@ -922,7 +922,7 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t
 // read by the consumer, cost less inside a step than their bytes at HBM's rate (they mostly meet in L2): O of the 7B shape at 160 rows
 // 2.3 us less a layer in eight parts than in seven, 5.2 less than in four.
 static double gemm_bf16_strip_us(int M, int N, int K, int splits, bool glu, const StripTile& s) {
-    const int n = (N / 2 + 16 * s.fs - 1) / (16 * s.fs) * splits, area = s.tiles * s.fs, rounds = n / 256, rem = n % 256;
+    const int n = gemm_bf16_strips(N, s) * splits, area = s.tiles * s.fs, rounds = n / 256, rem = n % 256;
     const double wg = (double)K / 32 / splits * (0.062 + 0.007 * area) + 0.11 * area, stream = (double)N * K * 2.0 / 1.0e6;
     const double t = n <= 256 ? wg : s.tiles <= 5 ? wg * 1.35 * n / 256 : wg * (rounds + (rem ? 0.5 + rem / 512.0 : 0.0));
     const double planes = glu ? 0.0 : splits == 1 ? (double)M * N * 4.0 / 6.0e6 : (2 * splits - 1) * (double)M * N * 4.0 / 12.0e6;
@@ -949,7 +949,7 @@ hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M
     if (splits < 1 || K % splits != 0 || (K / splits) % 32 != 0 || N % (glu ? 256 : 128) != 0 || (glu && splits != 1) || M < 1 || M > 32 * s.tiles)
         return hipErrorInvalidValue;
     auto launch = [&](auto kern, int w, int rs, int fs) -> hipError_t {
-        const int tiles_n = (N / 2 + 16 * fs - 1) / (16 * fs);
+        const int tiles_n = gemm_bf16_strips(N, s);
         const int lds = std::max(strip_fills(w, rs, fs) * (w / 2 * rs + 2 * fs) * 1024, glu ? w / 2 * rs * fs * 1024 : 0);
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;

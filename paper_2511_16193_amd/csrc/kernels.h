@@ -26,6 +26,7 @@ hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M,
 struct StripTile { int tiles, fs; };
 struct StripPlan { int splits; StripTile tile; double us; };
 constexpr int kStripRows = 320;             // most rows of a strip
+inline int gemm_bf16_strips(int N, const StripTile& s) { return (N / 2 + 16 * s.fs - 1) / (16 * s.fs); }    // strips of N features
 hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const StripTile& tile, hipStream_t st);
 StripPlan gemm_bf16_strip_plan(int M, int N, int K, int min_splits, int max_splits, bool glu);
 TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits);

@@ -71,6 +71,25 @@ def test_weights_off_16_bytes_keep_the_kernel_with_ordinary_loads(form, tile_mod
                 assert K % (64 * p["splits"]) == 0 and (not p["wide"] or N % 256 == 0) and 1 <= p["row_tiles"] <= 5, (M, N, K, p)
 
 
+@pytest.mark.parametrize("F,K,kernels", [
+    (18944, 3584, {5: "strip", 96: "strip", 160: "strip", 161: "strip", 320: "strip", 321: "tall"}),
+    (27648, 5120, {5: "strip", 160: "strip", 192: "strip", 321: "tall"}),
+    (28672, 8192, {5: "strip", 160: "strip"}),                             # 256 strips of 112 features
+    (29568, 8192, {5: "ws", 64: "ws", 96: "ws", 160: "ws", 161: "tall", 320: "tall"}),       # 462 strips, a last round of 206
+    (32768, 4096, {5: "ws", 160: "ws"}),                                   # 256 strips of the weight-streaming kernel: one round
+    (49152, 6144, {5: "strip", 64: "strip", 160: "strip", 161: "tall", 320: "tall"}),        # 384 of them: a second round in any case
+    (14336, 4096, {160: "strip", 256: "strip", 320: "tall"}),
+    (5632, 2048, {128: "strip", 129: "ws", 160: "ws", 161: "strip"}),      # 44 strips of five 32-row tiles fit the CUs at once
+    (6528, 2048, {160: "ws"}), (6656, 2048, {160: "strip"}),               # 51 and 52 strips
+])
+def test_gate_up_takes_strips_where_they_are_measured_to_pay(F, K, kernels):
+    for M, kernel in kernels.items():
+        p = op_gemm_step_launch(M, 2 * F, K, 2)
+        assert p["kernel"] == kernel, (M, F, K, p)
+        if kernel == "strip" and F < 40000:                                 # one round of work-groups
+            assert -(-2 * F // p["features"]) <= 256, (M, F, K, p)
+
+
 def test_what_is_no_projection_of_a_step_is_refused():
     for args in [(0, 256, 64, 0), (5, 200, 64, 0), (5, 256, 32, 0), (5, 384, 64, 2), (5, 256, 64, 3), (5, 256, 64, -1)]:
         with pytest.raises(SvError):
