@@ -31,6 +31,7 @@ constexpr int kChunkKeys = 1024;      // keys per split-KV chunk of the bf16 att
 // shape 5 rows 7 MB, 1024 rows 170, 4096 rows 501).
 constexpr int kPrefillRows = 4096;
 constexpr int kPrefillPlaces = 512;   // work-groups of a prefill's attention that run at once: two per CU
+constexpr int kStripInputs = 4096;    // a split reduction of no more inputs takes no strips (see plan_packed)
 constexpr int kPlans = 64;            // launch plans a context remembers (five shapes per number of rows)
 constexpr int kCausalK = 1 << 20;     // "drafts per chain" of a prefill pass: one chain, never ending
 
@@ -128,17 +129,22 @@ WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, bool dire
     return t.us < (allow_split ? 1.10 : 1.25) * ws.us ? WsPlan{t.splits, true, 0, t.us, ws.us, t.tiles, {}} : ws;
 }
 
-// Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip, which is how a step of
-// few rows finds it; the factors say where the other two kernels' estimates stand against it inside a step.  us of a layer or an LM
-// head, strip against weight-streaming, 7B: O at 5 / 160 rows even / 2.2 less, down at 5 / 96 / 160 / 224 / 320 2.4 / 1.4 / 2.1 / 0.9 / 3.0
-// less, LM head at 160 / 224 13 / 41 less (up to 96
-// rows within 1 %, and 11 more over 2048 inputs; alone, strip against tall at 192 / 256 / 320 rows 267 / 291 / 315 against 276 / 322 / 335); but QKV at 96 and 128 rows 1.6 more, at 224 and 320 2.0 and 5.4 more, O at 224 1.5 more (a
-// work-group that holds so many rows needs seven or eight planes to fill the chip).  Tall tiles: see plan_gate_up.
+// Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip; what they give inside a
+// step, us of a layer against weight-streaming at 5 / 42 / 96 / 160 rows:
+//   down 3584 x 18944 2.5 / 2.9 / 1.1 / 0.6 less, 5120 x 27648 1.7 / 5.7 / 8.9 / 1.4, 2048 x 11008 6.5 / 5.3 / 2.2 / 1.0, 896 x 4864 3.0 / 2.3 / 2.0 / 0.3; at
+//   192 / 256 / 288 / 320 3584 x 18944 1.3 less / 1.2 more / 2.5 less / 0.2 more, 4096 x 14336 3.5 less / 3.0 more / - / 1.9 more
+//   QKV and O of up to 4096 inputs nothing at 5 and 42 rows (0.2 less to 1.6 more), at 96 and 160 1.3 and 0.8 more (4608 x 3584), 0.9 and 0.8
+//   (6144 x 4096), 1.0 and 0.3 (5120 x 2048), 1.9 less and 1.4 more (4096 x 4096); from 161 rows on 0.7 to 12 more, as a work-group that
+//   holds so many rows needs seven or eight planes to fill the chip.  From 5120 inputs on 2.8 less to 1.5 more, 10240 x 8192 3 to 10 less
+// so short reductions take none, and from 161 rows on a strip has to be expected ahead (8192 x 29568 at 320 rows 38 less; 8192 x 8192
+// and 4096 x 14336 there, 2.9 and 1.9 more of about 50, are still among them).
+// LM heads of 97 to 320 rows: 152064 x 3584 at 112 / 160 / 192 / 320 7.9 / 5.9 / 51 / 39 less (up to 96 rows 0.8 to 4.4 less and, over 2048
+// inputs, 1 to 4 more).  Tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
 WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, bool direct = true, int max_splits = kMaxSplitsWs) {
     WsPlan best = plan_wide(M, N, K, allow_split, tile_mode, direct, max_splits);
-    if (direct && tile_mode != 0 && M >= 1 && M <= kStripRows) {
+    if (direct && tile_mode != 0 && M >= 1 && M <= kStripRows && (!allow_split || K > kStripInputs)) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
         const double limit = !allow_split ? (M <= 96 ? 0.0 : 1.25 * best.ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
         if (s.us < limit) best = WsPlan{s.splits, false, 0, s.us, best.ws_us, {}, s.tile};

@@ -90,6 +90,18 @@ def test_gate_up_takes_strips_where_they_are_measured_to_pay(F, K, kernels):
             assert -(-2 * F // p["features"]) <= 256, (M, F, K, p)
 
 
+def test_short_reductions_of_qkv_and_o_take_no_strips():
+    """Up to 4096 inputs a strip gains nothing inside a step; longer ones take strips."""
+    for M in ROWS:
+        for N, K in [(4608, 3584), (3584, 3584), (6144, 4096), (4096, 4096), (5120, 2048), (1152, 896), (2048, 1024)]:
+            p, wide = op_gemm_step_launch(M, N, K), op_gemm_step_plan(M, N, K)
+            assert p["kernel"] != "strip" and (p["splits"], p["tall"]) == (wide["splits"], wide["tall"]), (M, N, K, p)
+    for M in (5, 40, 96, 160):
+        for N, K in [(3584, 18944), (5120, 27648), (4096, 14336), (7168, 5120), (10240, 8192)] + [(896, 4864), (2048, 11008)] * (M < 160):
+            assert op_gemm_step_launch(M, N, K)["kernel"] == "strip", (M, N, K)
+    assert op_gemm_step_launch(320, 3584, 18944)["kernel"] == "strip"
+
+
 def test_what_is_no_projection_of_a_step_is_refused():
     for args in [(0, 256, 64, 0), (5, 200, 64, 0), (5, 256, 32, 0), (5, 384, 64, 2), (5, 256, 64, 3), (5, 256, 64, -1)]:
         with pytest.raises(SvError):
