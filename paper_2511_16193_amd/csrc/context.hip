@@ -31,6 +31,7 @@ constexpr int kChunkKeys = 1024;      // keys per split-KV chunk of the bf16 att
 // shape 5 rows 7 MB, 1024 rows 170, 4096 rows 501).
 constexpr int kPrefillRows = 4096;
 constexpr int kPrefillPlaces = 512;   // work-groups of a prefill's attention that run at once: two per CU
+constexpr int kHeadInputs = 2048;      // LM heads of so many inputs or more: see plan_wide
 constexpr int kStripInputs = 4096;    // a split reduction of no more inputs takes no strips (see plan_packed)
 constexpr int kPlans = 64;            // launch plans a context remembers (five shapes per number of rows)
 constexpr int kCausalK = 1 << 20;     // "drafts per chain" of a prefill pass: one chain, never ending
@@ -116,7 +117,8 @@ bool direct_loads(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 ==
 // down 282 against 263); the tall ones take theirs.
 // Where the reduction is not split (LM heads) they take 1.1 to 1.3: every work-group along the rows reads its strip again.  us alone,
 // weight-streaming against tall: 152064 x 3584 at 330 / 400 / 500 / 640 rows 445 / 498 / 549 / 681 against 392 / 411 / 446 / 543, 152064 x
-// 5120 558 / 668 / 770 / 942 against 564 / 567 / 614 / 725.
+// 5120 558 / 668 / 770 / 942 against 564 / 567 / 614 / 725.  Shorter ones (kHeadInputs) lie by the other line, as the weights read again are
+// little beside the logits written: 151936 x 1024 at 161 / 192 / 256 rows 101 / 105 / 120 against 104 / 109 / 123, x 896 inside a step 20 less.
 // us in a loop, weight-streaming against tall, 7B: QKV at 320 / 512 / 1280 / 2304 rows 21 / 30 / 52 / 98 against
 // 24 / 23 / 43 / 71, down 48 / 83 / 180 / 282 against 54 / 65 / 152 / 243.
 // tile_mode: -1 = this rule, 0 = the weight-streaming kernel only, 1 = 256-row tall tiles wherever the width allows.
@@ -126,7 +128,7 @@ WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, bool dire
     const WsPlan ws = plan_ws(M, N, K, allow_split, max_splits);
     if (!direct || tile_mode == 0 || M <= 128) return ws;
     const TallPlan t = gemm_bf16_tall_plan(M, N, K, allow_split ? std::min(max_splits, kMaxSplits) : 1);
-    return t.us < (allow_split ? 1.10 : 1.25) * ws.us ? WsPlan{t.splits, true, 0, t.us, ws.us, t.tiles, {}} : ws;
+    return t.us < (allow_split || K < kHeadInputs ? 1.10 : 1.25) * ws.us ? WsPlan{t.splits, true, 0, t.us, ws.us, t.tiles, {}} : ws;
 }
 
 // Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip; what they give inside a
@@ -135,18 +137,22 @@ WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, bool dire
 //   192 / 256 / 288 / 320 3584 x 18944 1.3 less / 1.2 more / 2.5 less / 0.2 more, 4096 x 14336 3.5 less / 3.0 more / - / 1.9 more
 //   QKV and O of up to 4096 inputs nothing at 5 and 42 rows (0.2 less to 1.6 more), at 96 and 160 1.3 and 0.8 more (4608 x 3584), 0.9 and 0.8
 //   (6144 x 4096), 1.0 and 0.3 (5120 x 2048), 1.9 less and 1.4 more (4096 x 4096); from 161 rows on 0.7 to 12 more, as a work-group that
-//   holds so many rows needs seven or eight planes to fill the chip.  From 5120 inputs on 2.8 less to 1.5 more, 10240 x 8192 3 to 10 less
+//   holds so many rows needs seven or eight planes to fill the chip.  From 5120 inputs on 2.8 less to 1.5 more, 10240 x 8192 0.6 to 6 less
 // so short reductions take none, and from 161 rows on a strip has to be expected ahead (8192 x 29568 at 320 rows 38 less; 8192 x 8192
 // and 4096 x 14336 there, 2.9 and 1.9 more of about 50, are still among them).
 // LM heads of 97 to 320 rows: 152064 x 3584 at 112 / 160 / 192 / 320 7.9 / 5.9 / 51 / 39 less (up to 96 rows 0.8 to 4.4 less and, over 2048
-// inputs, 1 to 4 more).  Tall tiles: see plan_gate_up.
+// inputs, 1 to 4 more), where tall tiles are 48 and 12 less at 192 and 320; 151936 x 2048 within 2 of the tall tiles up to 256 rows and 7
+// less at 320, 151936 x 1024 alone 5 to 13 less from 192 rows on, whatever the estimates say; where the strips are one round (225 of 50304 x
+// 1024) and the tall estimate is lower, 6 to 8 more.
+// Other tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
 WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, bool direct = true, int max_splits = kMaxSplitsWs) {
     WsPlan best = plan_wide(M, N, K, allow_split, tile_mode, direct, max_splits);
     if (direct && tile_mode != 0 && M >= 1 && M <= kStripRows && (!allow_split || K > kStripInputs)) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
-        const double limit = !allow_split ? (M <= 96 ? 0.0 : 1.25 * best.ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
+        const bool tall_head = best.tall.n > 0 && gemm_bf16_strips(N, s.tile) <= 256 && s.us > 1.05 * best.us;
+        const double limit = !allow_split ? (M <= 96 || tall_head ? 0.0 : 1.25 * best.ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;
         if (s.us < limit) best = WsPlan{s.splits, false, 0, s.us, best.ws_us, {}, s.tile};
     }
     return best;

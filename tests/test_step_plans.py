@@ -102,6 +102,19 @@ def test_short_reductions_of_qkv_and_o_take_no_strips():
     assert op_gemm_step_launch(320, 3584, 18944)["kernel"] == "strip"
 
 
+@pytest.mark.parametrize("N,K,kernels", [
+    (152064, 3584, {96: "ws", 97: "strip", 160: "strip", 192: "strip", 320: "strip", 321: "tall", 2304: "tall"}),
+    (151936, 2048, {96: "ws", 192: "strip", 320: "strip", 400: "tall"}),
+    (151936, 1024, {176: "ws", 192: "ws", 320: "strip", 640: "tall"}),     # short reductions: tall tiles by the line of the other projections
+    (151936, 896, {176: "ws", 192: "ws"}),
+    (50304, 1024, {128: "strip", 192: "tall", 256: "tall", 320: "tall"}),  # tall tiles expected ahead of one round of strips
+])
+def test_lm_heads(N, K, kernels):
+    for M, kernel in kernels.items():
+        p = op_gemm_step_launch(M, N, K, 1)
+        assert p["kernel"] == kernel and p["splits"] == 1, (M, N, K, p)
+
+
 def test_what_is_no_projection_of_a_step_is_refused():
     for args in [(0, 256, 64, 0), (5, 200, 64, 0), (5, 256, 32, 0), (5, 384, 64, 2), (5, 256, 64, 3), (5, 256, 64, -1)]:
         with pytest.raises(SvError):
