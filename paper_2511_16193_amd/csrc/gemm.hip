@@ -401,7 +401,10 @@ __device__ __forceinline__ void lds_landed(u32x4& d) { asm volatile("s_waitcnt l
 __device__ __forceinline__ void lds_landed_too(u32x4& d) { asm volatile("" : "+v"(d)); }     // no use of d moves above the wait
 
 // 1 KB from global memory straight into LDS: lane l's 16 bytes at base + lane_off go to LDS address lds + 16 l (base and lds the same for
-// all lanes).  dma1_lanes: only the lanes of a mask that is not empty.  All lanes of the wave are running.
+// all lanes).  dma1_lanes: only the lanes of a mask that is not empty.
+// Both write m0, and the second exec: reserved registers, which the compiler takes no clobber for.  So they are for kernels in which
+// nothing else uses m0 (no builtin that loads into LDS, whose m0 the compiler may carry from one to the next), and dma1_lanes for places
+// that all 64 lanes of the wave reach: exec is all ones before it and after it.
 __device__ __forceinline__ void dma1(const char* base, uint32_t lane_off, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
 }
@@ -425,8 +428,8 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
 
     // A fill is P pieces of 1 KB: the activations' 2 RW row tiles x 2 slices, then (strip, slice, feature tile) of the weights.  Wave w
     // requests pieces w, w + 8, ... ; where they do not come out even, the others take one lane of the last piece once more, so that
-    // every wave counts the same loads without a branch (two branches cost 120 cycles a fill).  Row tiles beyond M and a strip beyond N (N an odd multiple of 128) are read as the last
-    // one and never stored.
+    // every wave counts the same loads without a branch (two branches cost 120 cycles a fill).  Row tiles beyond M and a strip beyond N
+    // (N an odd multiple of 128) are read as the last one and never stored.
     constexpr int A_P = KA * 2 * RW, P = A_P + KA * 8, EACH = P / 8, EXTRA = P % 8;
     const uint64_t last_lanes = wave < EXTRA ? ~0ull : 1;
     const char* src[EACH + 1];
@@ -619,8 +622,11 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_tall_kernel(const bf16_t* __
     else gemm_bf16_tall_body<GLU, RWT == 0 ? RW : RWT>(Ap, Wp, out, M, N, K, k_per_split, n * 64 * RW + (tm - n) * 64 * RWT, tn, sp);
 }
 
-// Microseconds a launch of the tall kernel takes, by the same kind of play-through as the weight-streaming plan (fitted to 900
-// launches of 17 row counts from 128 to 3500, three shapes and four split counts; nine in ten estimates lie between 0.77 and
+// Microseconds a launch of the tall kernel takes, by the same kind of play-through as the weight-streaming plan.  Fitted to the kernel's
+// earlier form on 32x32x16 products; for this one it is up to 26 % high: gate/up 37888 x 3584 at 192 / 320 rows 78 / 103 where it takes 72 / 89,
+// 28672 x 4096 at 320 90 for 71, down of the 7B shape at 2304 269 for 230; LM heads of 152 thousand features within 2 %.  Of the lines that
+// weigh it against the other kernels 0.80 and 1.25 were measured with this form, 1.10 with the earlier one.  (The fit: 900
+// launches of 17 row counts from 128 to 3500, three shapes and four split counts; nine in ten estimates lay between 0.77 and
 // 1.05 of the measured time, and over 63 other launches the tiles it prefers take 2 % longer than the best on average.  Two
 // heights against one and a remainder: gate/up of 55296 over K = 5120 at 800 rows, one tile of 320 and two of 256: 445 us,
 // three of 256 and one of 64: 468; of 37888 over 3584 at 777 rows 198 us against 224).
