@@ -1,5 +1,5 @@
 """The narrow-strip projection kernel: every height and width in both of its forms, rows and strips that end inside a tile, reductions
-shorter than its ring and of an odd number of fills, more strips than CUs -- bit for bit the weight-streaming kernel's sums, and
+shorter than its ring and of odd numbers of fills, more strips than CUs -- bit for bit the weight-streaming kernel's sums, and
 against float64 products."""
 import numpy as np
 import pytest
@@ -37,6 +37,25 @@ def test_plain_strips(tiles, features):
             if N < 1000:
                 want = M.matmul_wt(a.cpu().float().numpy().astype(np.float64), w.cpu().float().numpy())
                 assert np.max(np.abs(got.cpu().numpy().astype(np.float64).sum(axis=0) - want)) < 1e-4, (N, K, splits, rows)
+
+
+@pytest.mark.parametrize("K,splits", [(576, 2), (448, 2), (192, 2)])
+@pytest.mark.parametrize("features", [128, 160, 224])
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 6, 8, 10])
+def test_odd_numbers_of_fills(tiles, features, K, splits):
+    """9, 7 and 3 fills a split: the loop over pairs of fills, then the one left over, with the ring wrapped round and not.  The
+    weight-streaming kernel has no such splits: against float64 (tolerance as above), and the sums of tall tiles, bit for bit."""
+    from paper_2511_16193_amd import op_gemm_bf16_strip, op_gemm_bf16_tall, op_pack_rows, op_pack_weight
+    rows, N = 32 * tiles - 5, 384
+    a, w = bf16((rows, K), 1.0, tiles).to(DEV), bf16((N, K), 0.02, K).to(DEV)
+    ap, wp = op_pack_rows(a), op_pack_weight(w)
+    got = op_gemm_bf16_strip(ap, wp, rows, tiles, features, splits)
+    need = (rows + 63) // 64
+    assert torch.equal(got, op_gemm_bf16_tall(ap, wp, rows, (max(3, need), 1, 0, 0), splits))
+    halves = [slice(s * K // splits, (s + 1) * K // splits) for s in range(splits)]
+    for s, h in enumerate(halves):
+        want = M.matmul_wt(a[:, h].cpu().float().numpy().astype(np.float64), w[:, h].cpu().float().numpy())
+        assert np.max(np.abs(got[s].cpu().numpy().astype(np.float64) - want)) < 1e-4, s
 
 
 @pytest.mark.parametrize("features", [128, 160, 224])

@@ -95,6 +95,20 @@ def test_every_pair_of_heights_equals_the_weight_streaming_kernel(h, ht, N, K, s
         assert np.max(np.abs(got.cpu().numpy().astype(np.float64).sum(axis=0) - want)) < 1e-4
 
 
+@pytest.mark.parametrize("K,splits", [(576, 2), (192, 2)])
+@pytest.mark.parametrize("h,ht", PAIRS)
+def test_odd_numbers_of_fills(h, ht, K, splits):
+    """9 and 3 fills a split, which the weight-streaming kernel has no form for: every split against its float64 product."""
+    from paper_2511_16193_amd import op_gemm_bf16_tall, op_pack_rows, op_pack_weight
+    tall, rows = tiles_of(h, ht, 1)
+    a, w = bf16((rows, K), 1.0, rows).to(DEV), bf16((384, K), 0.02, K).to(DEV)
+    got = op_gemm_bf16_tall(op_pack_rows(a), op_pack_weight(w), rows, tall, splits)
+    for s in range(splits):
+        part = slice(s * K // splits, (s + 1) * K // splits)
+        want = M.matmul_wt(a[:, part].cpu().float().numpy().astype(np.float64), w[:, part].cpu().float().numpy())
+        assert np.max(np.abs(got[s].cpu().numpy().astype(np.float64) - want)) < 1e-4, s
+
+
 @pytest.mark.parametrize("F,K", [(384, 64), (384, 640), (33024, 64)])
 @pytest.mark.parametrize("h,ht", PAIRS)
 def test_every_gated_pair_of_heights_equals_the_weight_streaming_kernel(h, ht, F, K):
