@@ -32,7 +32,7 @@ constexpr int kChunkKeys = 1024;      // keys per split-KV chunk of the bf16 att
 constexpr int kPrefillRows = 4096;
 constexpr int kPrefillPlaces = 512;   // work-groups of a prefill's attention that run at once: two per CU
 constexpr int kHeadInputs = 2048;      // LM heads of so many inputs or more: see plan_wide
-constexpr int kStripInputs = 4096;    // a split reduction of no more inputs takes no strips (see plan_packed)
+constexpr int kStripInputs = 4096;    // split reductions of no more inputs take strips at some numbers of rows only: see plan_packed
 constexpr int kPlans = 64;            // launch plans a context remembers (five shapes per number of rows)
 constexpr int kCausalK = 1 << 20;     // "drafts per chain" of a prefill pass: one chain, never ending
 
@@ -134,12 +134,14 @@ WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, bool dire
 // Up to 320 rows the narrow strips come in between.  Their estimate was fitted to launches on an idle chip; what they give inside a
 // step, us of a layer against weight-streaming at 5 / 42 / 96 / 160 rows:
 //   down 3584 x 18944 2.5 / 2.9 / 1.1 / 0.6 less, 5120 x 27648 1.7 / 5.7 / 8.9 / 1.4, 2048 x 11008 6.5 / 5.3 / 2.2 / 1.0, 896 x 4864 3.0 / 2.3 / 2.0 / 0.3; at
-//   192 / 256 / 288 / 320 3584 x 18944 1.3 less / 1.2 more / 2.5 less / 0.2 more, 4096 x 14336 3.5 less / 3.0 more / - / 1.9 more
-//   QKV and O of up to 4096 inputs nothing at 5 and 42 rows (0.2 less to 1.6 more), at 96 and 160 1.3 and 0.8 more (4608 x 3584), 0.9 and 0.8
-//   (6144 x 4096), 1.0 and 0.3 (5120 x 2048), 1.9 less and 1.4 more (4096 x 4096); from 161 rows on 0.7 to 12 more, as a work-group that
-//   holds so many rows needs seven or eight planes to fill the chip.  From 5120 inputs on 2.8 less to 1.5 more, 10240 x 8192 0.6 to 6 less
-// so short reductions take none, and from 161 rows on a strip has to be expected ahead (8192 x 29568 at 320 rows 38 less; 8192 x 8192
-// and 4096 x 14336 there, 2.9 and 1.9 more of about 50, are still among them).
+//   192 / 256 / 288 / 320 3584 x 18944 1.3 less / 1.2 more / 2.5 less / 0.2 more, 4096 x 14336 3.5 less / 3.0 more / - / 1.9 more.  From 161 rows
+//   on a strip has to be expected ahead (8192 x 29568 at 320 rows 38 less; 8192 x 8192 and 4096 x 14336 there, 2.9 and 1.9 more of about 50,
+//   are still among them)
+//   QKV and O together, before the attention of 1 to 8 thousand keys, at 5 / 40 / 65 / 96 / 128 / 130 / 160 / 190 rows: 3584 inputs 0.4 / 0.9 / 0.8
+//   less, 0.8 / 0.7 more, 2.1 / 2.6 less, 5.4 more; 4096 inputs 0.5 / 0.4 / 2.4 less, 1.0 more, 0.6 / 3.3 / 4.4 less, 2.0 more; 5120 inputs 1.4 / 1.0 / 0.1
+//   less, 2.6 / 0.6 more, 2.4 / 1.9 less, 1.2 more; 2048 inputs (10 and 21 MB of QKV) 1.5 / 1.2 / 0.0 / 0.3 / 0.2 more, 0.6 less, 0.5 / 8.4 more and
+//   0.3 less, 0.9 / 0.0 / 0.9 / 0.4 more, 0.3 less, 0.5 / 4.7 more
+// so reductions of up to kStripInputs take strips for one, two and five row tiles, if their weights are a stream worth the name.
 // LM heads of 97 to 320 rows: 152064 x 3584 at 112 / 160 / 192 / 320 7.9 / 5.9 / 51 / 39 less (up to 96 rows 0.8 to 4.4 less and, over 2048
 // inputs, 1 to 4 more), where tall tiles are 48 and 12 less at 192 and 320; 151936 x 2048 within 2 of the tall tiles up to 256 rows and 7
 // less at 320, 151936 x 1024 alone 5 to 13 less from 192 rows on, whatever the estimates say; where the strips are one round (225 of 50304 x
@@ -147,9 +149,11 @@ WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, bool dire
 // Other tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
+bool strip_pays(int M, int N, int K) { return K > kStripInputs || ((int64_t)N * K >= 12000000 && (M <= 64 || (M > 128 && M <= 160))); }
+
 WsPlan plan_packed(int M, int N, int K, bool allow_split, int tile_mode, bool experts, bool direct = true, int max_splits = kMaxSplitsWs) {
     WsPlan best = plan_wide(M, N, K, allow_split, tile_mode, direct, max_splits);
-    if (direct && tile_mode != 0 && M >= 1 && M <= kStripRows && (!allow_split || K > kStripInputs)) {
+    if (direct && tile_mode != 0 && M >= 1 && M <= kStripRows && (!allow_split || strip_pays(M, N, K))) {
         const StripPlan s = gemm_bf16_strip_plan(M, N, K, experts ? best.splits : 1, experts ? best.splits : allow_split ? max_splits : 1, false);
         const bool tall_head = best.tall.n > 0 && gemm_bf16_strips(N, s.tile) <= 256 && s.us > 1.05 * best.us;
         const double limit = !allow_split ? (M <= 96 || tall_head ? 0.0 : 1.25 * best.ws_us) : best.tall.n > 0 ? 0.80 * best.us : (M <= 160 ? 1.15 : 0.93) * best.us;

@@ -90,10 +90,12 @@ def test_gate_up_takes_strips_where_they_are_measured_to_pay(F, K, kernels):
             assert -(-2 * F // p["features"]) <= 256, (M, F, K, p)
 
 
-def test_short_reductions_of_qkv_and_o_take_no_strips():
-    """Up to 4096 inputs a strip gains nothing inside a step; longer ones take strips."""
+def test_strips_of_short_reductions():
+    """Up to 4096 inputs strips of one, two or five row tiles, if the weights are 24 MB; longer ones take strips up to 160 rows."""
     for M in ROWS:
-        for N, K in [(4608, 3584), (3584, 3584), (6144, 4096), (4096, 4096), (5120, 2048), (1152, 896), (2048, 1024)]:
+        for N, K in [(4608, 3584), (3584, 3584), (6144, 4096), (4096, 4096)]:
+            assert (op_gemm_step_launch(M, N, K)["kernel"] == "strip") == (M <= 64 or 129 <= M <= 160), (M, N, K)
+        for N, K in [(5120, 2048), (2048, 4096), (1152, 896), (2048, 1024)]:
             p, wide = op_gemm_step_launch(M, N, K), op_gemm_step_plan(M, N, K)
             assert p["kernel"] != "strip" and (p["splits"], p["tall"]) == (wide["splits"], wide["tall"]), (M, N, K, p)
     for M in (5, 40, 96, 160):
