@@ -624,7 +624,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_tall_kernel(const bf16_t* __
 
 // Microseconds a launch of the tall kernel takes, by the same kind of play-through as the weight-streaming plan.  Fitted to the kernel's
 // earlier form on 32x32x16 products; for this one it is up to 26 % high: gate/up 37888 x 3584 at 192 / 320 rows 78 / 103 where it takes 72 / 89,
-// 28672 x 4096 at 320 90 for 71, down of the 7B shape at 2304 269 for 230; LM heads of 152 thousand features within 2 %.  Of the lines that
+// 28672 x 4096 at 320 90 for 71, down of the 7B shape at 2304 269 for 230; LM heads of 152 thousand features 13 % low (2048 inputs) to 8 % high (5120).  Of the lines that
 // weigh it against the other kernels 0.80 and 1.25 were measured with this form, 1.10 with the earlier one.  (The fit: 900
 // launches of 17 row counts from 128 to 3500, three shapes and four split counts; nine in ten estimates lay between 0.77 and
 // 1.05 of the measured time, and over 63 other launches the tiles it prefers take 2 % longer than the best on average.  Two
@@ -733,8 +733,9 @@ hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M,
 // holds the stream in registers, eight slices a wave, and its strips of 128 or 256 features seldom come to the number of CUs; the
 // tall kernel's 256-feature strips of the 7B gate/up projection are 148 work-groups.  Here both operands go through an LDS ring of
 // fills of one reduction step of 32 in pieces of one 16x16x32 operand, so that a strip can be any multiple of 32 features (gated: of
-// 16 gate and 16 up ones): 128, 160 or 224, whichever comes closest to the 256 CUs.  W waves, two of them side by side along
-// the features, each RS 16-row operands x FS 16-feature operands, all of a fill's operands in one of two register sets: one
+// 16 gate and 16 up ones): 128, 160 or 224, whichever comes closest to the 256 CUs (widths between them are not built: a width is 16
+// kernels, and a shape that just misses one round at one of them puts 183 strips or more on the CUs at the next).  W waves, two of them
+// side by side along the features, each RS 16-row operands x FS 16-feature operands, all of a fill's operands in one of two register sets: one
 // barrier a fill, the next fill's LDS reads and the ring's requests between the products.
 // The request of a ring's fill costs a wave its place at the texture path (17 cycles a piece, one queue per CU): sent in a burst
 // behind the barrier, ten row tiles of 160 features took 1536 cycles a fill on an otherwise idle chip, spread 1062 (800 of them
