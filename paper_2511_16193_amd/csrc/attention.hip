@@ -807,14 +807,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // its weight is marked below zero and its V, which may hold anything, is not multiplied; only tiles that hold such keys are
 // looked at for it (in all of them it cost 4 to 8 %; so, the fp32 prefill 1 % and the steps nothing).  (With a lane per key
 // holding all D accumulators, V element by element and D wave reductions at the end, the step of 20 rows with 132 keys took 43 us
-// a layer; 5.7 us now.)
+// a layer; 5.7 us now.)  A row's cached length comes with its other descriptions, and the first tile of V is requested before the
+// softmax: one read less in the chain that a small step's launch consists of.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float scale) {
     constexpr int CK = 256, GROUPS = 256 / D, EP = 16 / (int)sizeof(T);
     const int t = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
     const int4 info = reinterpret_cast<const int4*>(a.row_info)[t];
     const int seq = info.x, j = info.y;
-    const int L = a.seq_len[seq], total = L + info.z;
+    const int L = info.w, total = L + info.z;
     const int end = a.row_items ? L + j + 1 : total;      // a prefill row sees nothing beyond itself
     const int all_seen = a.row_items ? end : L;           // up to here it sees every key
     const int hkv = h / (a.Hq / a.Hkv);
@@ -835,6 +836,11 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
         }
     };
     const int dim = tid % D, grp = tid / D;
+    auto load_v = [&](int k0, float (&v)[4][8]) {          // keys 4 g .. 4 g + 3 and 16 + 4 g .. of a tile, which lies inside a page
+        const T* vp = pool + kv_v_index(a.geom, a.layer, pages[k0 / a.geom.page_size], hkv, k0 % a.geom.page_size, dim);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) load8(vp + g * 128, v[g]);
+    };
     float m = -INFINITY, l = 0.f, acc = 0.f;
     for (int c0 = 0; c0 < end; c0 += CK) {
         const int key = c0 + tid;
@@ -852,6 +858,9 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
             }
             s *= scale;
         }
+        float v[4][8];
+        if (c0 + grp * TILE_KEYS < end) load_v(c0 + grp * TILE_KEYS, v);        // on its way during the softmax
+        __builtin_amdgcn_sched_barrier(0);
         const float mw = wave_max(s);
         if ((tid & 63) == 0) red[tid >> 6] = mw;
         __syncthreads();
@@ -863,24 +872,21 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
         acc *= alpha;
         m = m_new;
         __syncthreads();
-        auto weigh = [&](int tile, auto masked) __attribute__((always_inline)) {
-            const int k0 = c0 + tile * TILE_KEYS;           // a tile lies inside a page
-            const T* vp = pool + kv_v_index(a.geom, a.layer, pages[k0 / a.geom.page_size], hkv, k0 % a.geom.page_size, dim);
+        auto weigh = [&](int tile, const float (&v)[4][8], auto masked) __attribute__((always_inline)) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float v[8];
-                load8(vp + g * 128, v);                     // keys 4 g .. 4 g + 3 and 16 + 4 g .. of the tile
+            for (int g = 0; g < 4; ++g)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float w0 = p[tile * TILE_KEYS + 4 * g + e], w1 = p[tile * TILE_KEYS + 16 + 4 * g + e];
-                    acc = decltype(masked)::value && w0 < 0.f ? acc : fmaf(w0, v[e], acc);
-                    acc = decltype(masked)::value && w1 < 0.f ? acc : fmaf(w1, v[4 + e], acc);
+                    acc = decltype(masked)::value && w0 < 0.f ? acc : fmaf(w0, v[g][e], acc);
+                    acc = decltype(masked)::value && w1 < 0.f ? acc : fmaf(w1, v[g][4 + e], acc);
                 }
-            }
         };
-        int tile = grp;                                     // first the tiles in which nothing is masked
-        for (; tile < CK / TILE_KEYS && c0 + (tile + 1) * TILE_KEYS <= all_seen; tile += GROUPS) weigh(tile, std::false_type{});
-        for (; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) weigh(tile, std::true_type{});
+        for (int tile = grp; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) {
+            if (tile != grp) load_v(c0 + tile * TILE_KEYS, v);
+            if (c0 + (tile + 1) * TILE_KEYS <= all_seen) weigh(tile, v, std::false_type{});      // nothing in it is masked
+            else weigh(tile, v, std::true_type{});
+        }
         __syncthreads();
     }
     acc_sh[grp][dim] = acc;

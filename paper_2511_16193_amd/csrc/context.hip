@@ -938,7 +938,7 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
         }
     } else {
         *splits_out = 1;
-        SV_HIP(c, gemm_f32((const float*)A, (const float*)W, out, M, N, K, c->stream));
+        SV_HIP(c, gemm_f32((const float*)A, (const float*)W, out, M, N, K, false, F32Norm{}, c->stream));
     }
     return SV_OK;
 }
@@ -1015,16 +1015,23 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     float* h = c->at<float>(L.h);
     float* part = c->at<float>(L.part);
     void* a_norm = c->at<void>(L.a_norm);
+    // fp32: the projections write the residual themselves, and where their rows are few they take the norms and rotary with them
+    const bool f32 = m.dtype == SV_FP32, f32_qkv = f32 && gemm_f32_fuses(T, qkvw, d, kF32Qkv), f32_up = f32 && gemm_f32_fuses(T, m.d_ff, d, kF32Glu);
+    auto norm_by = [&](const void* gain) { return F32Norm{(const float*)gain, m.rms_eps}; };
 
-    SV_TRY(add_norm(c, T, pending, c->ln1[l]));
-    pending = 0;
-    int s_qkv = 1;
-    SV_TRY(gemm(c, a_norm, c->wqkv[l], part, T, qkvw, d, &s_qkv));
     RopeAppend ra;
-    ra.qkv_part = part; ra.S = s_qkv; ra.rope = c->at<float>(L.rope); ra.row_slot = c->at<int32_t>(L.row_slot);
+    ra.qkv_part = part; ra.S = 1; ra.rope = c->at<float>(L.rope); ra.row_slot = c->at<int32_t>(L.row_slot);
     ra.q_out = c->at<void>(L.q); ra.pool = c->rt.kv_pool; ra.geom = c->geom; ra.layer = l;
     ra.T = T; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.dtype = m.dtype;
-    SV_HIP(c, rope_append(ra, st));
+    if (f32_qkv) {
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, gemm_f32_qkv(h, (const float*)c->wqkv[l], d, norm_by(c->ln1[l]), ra, st));
+    } else {
+        SV_TRY(add_norm(c, T, pending, c->ln1[l]));
+        SV_TRY(gemm(c, a_norm, c->wqkv[l], part, T, qkvw, d, &ra.S));
+        SV_HIP(c, rope_append(ra, st));
+    }
+    pending = 0;
 
     const AttnArgs aa = attn_args(c, ps, l, ra.q_out, c->at<void>(L.attn), c->packed);
     {
@@ -1032,9 +1039,14 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         SV_HIP(c, attention(aa, st));
     }
 
-    int s_o = 1;
-    SV_TRY(gemm(c, aa.out, c->wo[l], part, T, d, qw, &s_o));
-    SV_HIP(c, add_rmsnorm(h, part, s_o, c->ln2[l], a_norm, m.dtype, T, d, m.rms_eps, c->packed, st));
+    int s_o = 0;
+    if (f32) {
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, gemm_f32((const float*)aa.out, (const float*)c->wo[l], h, T, d, qw, true, F32Norm{}, st));
+    } else {
+        SV_TRY(gemm(c, aa.out, c->wo[l], part, T, d, qw, &s_o));
+    }
+    if (!f32_up) SV_HIP(c, add_rmsnorm(h, part, s_o, c->ln2[l], a_norm, m.dtype, T, d, m.rms_eps, c->packed, st));
     if (m.n_experts > 0) {
         MoeArgs ma;
         ma.a = (const bf16_t*)a_norm; ma.w_router = (const bf16_t*)c->wrouter[l];
@@ -1058,9 +1070,12 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         if (g.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.strip, st));
         else if (g.tall.n > 0) SV_HIP(c, gemm_bf16_tall(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.tall, st));
         else SV_HIP(c, gemm_bf16_ws_glu(ga, gw, c->at<bf16_t>(L.act), T, m.d_ff, d, st));
-    } else if (m.dtype == SV_FP32) {
+    } else if (f32) {
         ProfScope prof(c, SV_PROF_GEMM);
-        SV_HIP(c, gemm_f32_glu((const float*)a_norm, (const float*)c->wgu[l], c->at<float>(L.act), T, m.d_ff, d, st));
+        SV_HIP(c, gemm_f32_glu(f32_up ? h : (const float*)a_norm, (const float*)c->wgu[l], c->at<float>(L.act), T, m.d_ff, d,
+                               f32_up ? norm_by(c->ln2[l]) : F32Norm{}, st));
+        SV_HIP(c, gemm_f32(c->at<float>(L.act), (const float*)c->wdown[l], h, T, d, m.d_ff, true, F32Norm{}, st));
+        return SV_OK;
     } else {
         int s_gu = 1;
         SV_TRY(gemm(c, a_norm, c->wgu[l], part, T, 2 * m.d_ff, d, &s_gu));
@@ -1149,10 +1164,17 @@ static int step_device_work(sv_ctx* c, const sv_batch* bt, const Pass& ps, const
     const int B = bt->B, k = bt->k, N = bt->N;
     int pending = 0;
     SV_TRY(forward_layers(c, ps, bt->last_tokens, drafts, nullptr, pending));
-    SV_TRY(add_norm(c, ps.T, pending, c->final_norm));
     const Layout& L = c->lay;
+    const sv_model& m = c->model;
     float* logits = out->logits ? out->logits : c->at<float>(L.logits);   // a caller that wants them has them written in place
-    SV_TRY(head_rows(c, ps.T, logits));
+    if (m.dtype == SV_FP32 && gemm_f32_fuses(ps.T, m.vocab, m.d_model, kF32Plain)) {
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, gemm_f32(c->at<float>(L.h), (const float*)c->lm_head, logits, ps.T, m.vocab, m.d_model, false,
+                           F32Norm{(const float*)c->final_norm, m.rms_eps}, c->stream));
+    } else {
+        SV_TRY(add_norm(c, ps.T, pending, c->final_norm));
+        SV_TRY(head_rows(c, ps.T, logits));
+    }
 
     SampleArgs sa;
     sa.logits = logits; sa.drafts = drafts; sa.draft_probs = draft_probs; sa.uniforms = uniforms;

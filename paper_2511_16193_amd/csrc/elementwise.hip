@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(RowPrep p) {
     if (threadIdx.x == 0) {
         const int slot = L + j;
         p.row_slot[t] = p.page_table[(int64_t)seq * p.max_pages_per_seq + slot / p.page_size] * p.page_size + slot % p.page_size;
-        reinterpret_cast<int4*>(p.row_info)[t] = int4{seq, j, n, 0};
+        reinterpret_cast<int4*>(p.row_info)[t] = int4{seq, j, n, L};
         // pieces that start below the live end (they were cut from the host's upper bound of the length)
         const int nch = rq[3] > 1 ? min(rq[3], (L + n + rq[2] - 1) / rq[2]) : 0;
         reinterpret_cast<int4*>(p.row_part)[t] = int4{rq[4] + j * p.group, rq[5], rq[6], nch};

@@ -1107,31 +1107,40 @@ hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, i
 // fp32 path (small models): v_mfma_f32_16x16x4_f32, operands straight from global memory.  A wave holds MT x NT tiles of
 // 16 rows x 16 features; lane 16 g + r of an operand tile loads four consecutive k (4 g .. 4 g + 3) of its row r in one
 // 16-byte piece and feeds them to four MFMAs, the reduction index of an MFMA being only a label as long as both operands
-// agree on it.  Two groups of 16 k are in flight.  KW waves of a work-group share the reduction (each takes every KW-th group
+// agree on it.  D groups of 32 k are in flight (four where a CU holds one tile).  KW waves of a work-group share the reduction (each takes every KW-th group
 // of 32 k) and add their tiles up in LDS; the other waves of the work-group have tiles of their own.
 // What bounds it at the few rows of a small model's step is one chain of load latencies, so the reduction is spread over
 // eight waves: 20 rows, K = 256..1024: 38 us with a scalar 32 x 32 tile per work-group (one FMA per 1.25 LDS reads, 24-64
 // work-groups, K walked serially), 5 us now.  Many rows take 64 x 64 tiles per wave.
-// GLU: NT = 2, tile 0 gate rows, tile 1 the up rows of the same features (W has 2 F rows); out [M][F] = silu(gate) * up.
+// And because a launch of such a step is little more than its own start (2.3 us of 4 to 6), the passes between the projections ride in
+// them: NORM reads the residual rows and normalises them on the way in (every work-group adds up the squares of its rows), kF32Qkv
+// rotates q and k and appends k and v to the cache on the way out, kF32Plain may add to what is there (the residual).  Two layers
+// of 20 rows: norm 2.9 + QKV 4.1 + rotary 3.3 -> 6.0 us, norm 2.9 + gate/up 5.2 -> 5.7, the step of 22 launches 92.0 -> 76.9 with 15.
+// kF32Glu: NT = 2, tile 0 gate rows, tile 1 the up rows of the same features (W has 2 F rows); out [M][F] = silu(gate) * up.
+// kF32Qkv: NT = 2, 16 dimensions of a head and their partners half a head away.
 // N, K and M are arbitrary: rows and features beyond the end read the last one and are not stored, k beyond the end counts
 // as zero.
-template <int MT, int NT, int KW, int WAVES, bool GLU, bool VEC>
-__global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
-                                                              float* __restrict__ out, int M, int N, int K, int tiles_m) {
+template <int MT, int NT, int KW, int WAVES, int FORM, bool VEC, bool NORM>
+__global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, float* __restrict__ out,
+                                                              int M, int N, int K, int tiles_m, int add, F32Norm norm, RopeAppend rope) {
     constexpr int TILES = WAVES / KW;                      // wave tiles per work-group, side by side along the features
+    constexpr int D = MT == 1 ? 4 : 1;
     static_assert(TILES == 1 || KW == 1, "the exchange area holds one wave tile");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert((FORM == kF32Qkv || NORM) ? KW > 1 && VEC : true, "fused forms: small tiles, whole pieces");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int kw = wave % KW, sub = wave / KW;
     const int m0 = (blockIdx.x % tiles_m) * 16 * MT;
-    const int n0 = ((blockIdx.x / tiles_m) * TILES + sub) * 16 * (GLU ? 1 : NT);
+    const int tn = (blockIdx.x / tiles_m) * TILES + sub;
+    const int half = FORM == kF32Qkv ? rope.hd / 2 : 0, head = FORM == kF32Qkv ? 16 * tn / half : 0, dim = 16 * tn - head * half;
+    const int n0 = FORM == kF32Qkv ? head * rope.hd + dim : tn * 16 * (FORM == kF32Glu ? 1 : NT);
     const float* a_row[MT];
     const float* w_row[NT];
 #pragma unroll
     for (int j = 0; j < MT; ++j) a_row[j] = A + (int64_t)min(m0 + 16 * j + r, M - 1) * K;
 #pragma unroll
     for (int i = 0; i < NT; ++i)
-        w_row[i] = W + (int64_t)(GLU ? i * N + min(n0 + r, N - 1) : min(n0 + 16 * i + r, N - 1)) * K;
+        w_row[i] = W + (int64_t)(FORM == kF32Glu ? i * N + min(n0 + r, N - 1) : FORM == kF32Qkv ? n0 + i * half + r : min(n0 + 16 * i + r, N - 1)) * K;
     floatx4 acc[NT][MT];
 #pragma unroll
     for (int i = 0; i < NT; ++i)
@@ -1147,25 +1156,111 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
         }
         return v;
     };
-    for (int k0 = kw * 32; k0 < K; k0 += 32 * KW) {
-        floatx4 a[2][MT], w[2][NT];
+    floatx4 a[D][2][MT], w[D][2][NT], gain[D][2];
+    auto load_groups = [&](int k0) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int s = 0; s < D; ++s)
+            if (k0 + s * 32 * KW < K) {
 #pragma unroll
-            for (int j = 0; j < MT; ++j) a[u][j] = load(a_row[j], k0 + 16 * u + 4 * g);
+                for (int u = 0; u < 2; ++u) {
+                    const int k = k0 + s * 32 * KW + 16 * u + 4 * g;
+                    if (NORM) gain[s][u] = load(norm.gain, k);
 #pragma unroll
-            for (int i = 0; i < NT; ++i) w[u][i] = load(w_row[i], k0 + 16 * u + 4 * g);
+                    for (int j = 0; j < MT; ++j) a[s][u][j] = load(a_row[j], k);
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) w[s][u][i] = load(w_row[i], k);
+                }
+            }
+    };
+    load_groups(kw * 32);
+    // what the wave that adds up row tile kw needs besides, requested with the rest
+    const int my_row = min(m0 + 16 * kw + r, M - 1);
+    floatx4 before[FORM == kF32Plain ? NT : 1], cs0, cs1;
+    int slot = 0;
+    if (KW > 1 && kw < MT) {
+        if (FORM == kF32Plain && add) {
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+                if (n0 + 16 * i + 4 * g + 3 < N) before[i] = *reinterpret_cast<const floatx4_any*>(out + (int64_t)my_row * N + n0 + 16 * i + 4 * g);
+        }
+        if (FORM == kF32Qkv) {
+            const float* tab = rope.rope + ((int64_t)my_row * half + dim + 4 * g) * 2;
+            cs0 = *reinterpret_cast<const floatx4*>(tab);
+            cs1 = *reinterpret_cast<const floatx4*>(tab + 4);
+            slot = rope.row_slot[my_row];
+        }
+    }
+    float scale[MT];
+    if (NORM) {                                           // wave w: rows w, w + KW, ... of the tile
+        constexpr int EACH = 16 * MT / KW;
+        __shared__ float scales[16 * MT];
+        __builtin_amdgcn_sched_barrier(0);
+        float ss[EACH];
+#pragma unroll
+        for (int i = 0; i < EACH; ++i) ss[i] = 0.f;
+        for (int k = lane * 4; k < K; k += 256) {
+            floatx4 x[EACH];
+#pragma unroll
+            for (int i = 0; i < EACH; ++i) x[i] = *reinterpret_cast<const floatx4*>(A + (int64_t)min(m0 + wave + KW * i, M - 1) * K + k);
+#pragma unroll
+            for (int i = 0; i < EACH; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ss[i] = fmaf(x[i][e], x[i][e], ss[i]);
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < EACH; ++i) ss[i] += __shfl_xor(ss[i], o);
+        if (lane == 0) {
+#pragma unroll
+            for (int i = 0; i < EACH; ++i) scales[wave + KW * i] = 1.0f / sqrtf(ss[i] / (float)K + norm.eps);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < MT; ++j) scale[j] = scales[16 * j + r];
+    }
+    for (int k0 = kw * 32; k0 < K; k0 += 32 * KW * D) {
+        if (k0 != kw * 32) load_groups(k0);
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+            if (k0 + s * 32 * KW < K) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (NORM) {
+#pragma unroll
+                        for (int j = 0; j < MT; ++j)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) a[s][u][j][e] = a[s][u][j][e] * scale[j] * gain[s][u][e];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int i = 0; i < NT; ++i)
+#pragma unroll
+                            for (int j = 0; j < MT; ++j)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][u][i][e], a[s][u][j][e], acc[i][j], 0, 0, 0);
+                }
+            }
+    }
+    auto put = [&](int m, int n, floatx4 v) {              // four features of a row
+        if (m >= M) return;
+        float* dst = out + (int64_t)m * N + n;
+        if (n + 3 < N) *reinterpret_cast<floatx4_any*>(dst) = v;
+        else
 #pragma unroll
             for (int e = 0; e < 4; ++e)
+                if (n + e < N) dst[e] = v[e];
+    };
+    auto rest = [&](int m, int n) {                        // what is there, where fewer than four features are left
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < NT; ++i)
-#pragma unroll
-                    for (int j = 0; j < MT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][e], a[u][j][e], acc[i][j], 0, 0, 0);
-    }
+        for (int e = 0; e < 4; ++e)
+            if (m < M && n + e < N) v[e] = out[(int64_t)m * N + n + e];
+        return v;
+    };
+    auto gated = [&](const floatx4& gate, const floatx4& up) {
+        return floatx4{silu_mul(gate[0], up[0]), silu_mul(gate[1], up[1]), silu_mul(gate[2], up[2]), silu_mul(gate[3], up[3])};
+    };
     if (KW > 1) {
         __shared__ floatx4 part[KW > 1 ? KW : 1][NT * MT][64];
 #pragma unroll
@@ -1173,55 +1268,112 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
 #pragma unroll
             for (int j = 0; j < MT; ++j) part[kw][i * MT + j][lane] = acc[i][j];
         __syncthreads();
-        // every wave adds up and stores a share of the tiles; gate and up of a feature stay together
-        for (int j = kw; j < MT; j += KW)
+        // wave j adds up and stores row tile j; the features that belong together stay together
+        if (kw < MT) {
+            const int m = m0 + 16 * kw + r;
+            floatx4 s[NT];
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                floatx4 s = part[0][i * MT + j][lane];
+                s[i] = part[0][i * MT + kw][lane];
 #pragma unroll
-                for (int q = 1; q < KW; ++q) s += part[q][i * MT + j][lane];
-                acc[i][0] = s;
-                if (!GLU || i == NT - 1) {
-                    const int m = m0 + 16 * j + r;
-                    const int n = n0 + (GLU ? 0 : 16 * i) + 4 * g;
+                for (int q = 1; q < KW; ++q) s[i] += part[q][i * MT + kw][lane];
+            }
+            if (FORM == kF32Glu) {
+                put(m, n0 + 4 * g, gated(s[0], s[NT - 1]));
+            } else if (FORM == kF32Qkv) {
+                if (m >= M) return;
+                const int d = dim + 4 * g;
+                const floatx4 x1 = s[0], x2 = s[NT - 1];
+                if (head >= rope.Hq + rope.Hkv) {          // V as it is
+                    float* pool = reinterpret_cast<float*>(rope.pool);
+                    const int page = slot / rope.geom.page_size, tok = slot % rope.geom.page_size, kh = head - rope.Hq - rope.Hkv;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (m < M && n + e < N)
-                            out[(int64_t)m * N + n + e] = GLU ? silu_mul(acc[0][0][e], s[e]) : s[e];
+                    for (int e = 0; e < 4; ++e) {
+                        pool[kv_v_index(rope.geom, rope.layer, page, kh, tok, d + e)] = x1[e];
+                        pool[kv_v_index(rope.geom, rope.layer, page, kh, tok, d + half + e)] = x2[e];
+                    }
+                    return;
+                }
+                const floatx4 c = {cs0[0], cs0[2], cs1[0], cs1[2]}, sn = {cs0[1], cs0[3], cs1[1], cs1[3]};
+                const floatx4 o1 = x1 * c - x2 * sn, o2 = x2 * c + x1 * sn;
+                float *d1, *d2;
+                if (head < rope.Hq) {
+                    d1 = reinterpret_cast<float*>(rope.q_out) + ((int64_t)m * rope.Hq + head) * rope.hd + d;
+                    d2 = d1 + half;
+                } else {
+                    float* pool = reinterpret_cast<float*>(rope.pool);
+                    const int page = slot / rope.geom.page_size, tok = slot % rope.geom.page_size;
+                    d1 = pool + kv_k_index(rope.geom, rope.layer, page, head - rope.Hq, tok, d);
+                    d2 = pool + kv_k_index(rope.geom, rope.layer, page, head - rope.Hq, tok, d + half);
+                }
+                *reinterpret_cast<floatx4*>(d1) = o1;
+                *reinterpret_cast<floatx4*>(d2) = o2;
+            } else {
+#pragma unroll
+                for (int i = 0; i < NT; ++i) {
+                    const int n = n0 + 16 * i + 4 * g;
+                    if (add) s[i] += n + 3 < N ? before[i] : rest(m, n);
+                    put(m, n, s[i]);
                 }
             }
+        }
         return;
     }
     // acc[i][j][e] <-> feature n0 + 16 i + 4 g + e, row m0 + 16 j + r
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
         const int m = m0 + 16 * j + r;
+        if (FORM == kF32Glu) put(m, n0 + 4 * g, gated(acc[0][j], acc[NT - 1][j]));
+        else
 #pragma unroll
-        for (int i = 0; i < (GLU ? 1 : NT); ++i) {
-            const int n = n0 + 16 * i + 4 * g;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (m < M && n + e < N)
-                    out[(int64_t)m * N + n + e] =
-                        GLU ? silu_mul(acc[0][j][e], acc[NT - 1][j][e]) : acc[i][j][e];
-        }
+            for (int i = 0; i < NT; ++i) {
+                const int n = n0 + 16 * i + 4 * g;
+                put(m, n, add ? acc[i][j] + rest(m, n) : acc[i][j]);
+            }
     }
 }
 
-template <bool GLU>
-static hipError_t launch_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st) {
-    auto launch = [&](auto vec, auto novec, int rows, int feats, int threads) {
+// 64-row wave tiles once they make a work-group for every other CU; below that eight waves share a reduction, on tiles of 32 rows, or of 16
+// while each of those has a CU to itself: half the products (a wave's 64 on K = 1024 take 1.9 us of the matrix unit) and half the
+// loads of a work-group.  20 rows, K = 256 and 1024 in turn: 6.4 -> 5.3 us a launch.
+static bool f32_large(int M, int N, bool glu) {
+    const int f = glu ? 64 : 256;
+    return (long long)((M + 63) / 64) * ((N + f - 1) / f) >= 128;
+}
+
+static bool f32_low(int M, int N, int feats) { return (long long)((M + 15) / 16) * ((N + feats - 1) / feats) <= 256; }
+
+// Where the norm and what follows QKV ride in the projection: 16-row tiles only, since every work-group goes over its rows a second time
+// and more work-groups than CUs would do so in turn.  us of a two-layer step, launches of their own against fused, without that line: 256
+// inputs at 60 / 160 / 320 / 640 rows 99 / 118 / 154 / 230 against 90 / 115 / 156 / 238, 512 at 20 / 160 116 / 221 against 112 / 243, 1024 at 1 / 20 / 160
+// 146 / 166 / 504 against 143 / 170 / 526.  Longer rows, of which a work-group would read 16 one after the other, keep the launches.
+bool gemm_f32_fuses(int M, int N, int K, F32Form form) {
+    return K % 4 == 0 && K <= 1024 && f32_low(M, N, form == kF32Qkv ? 32 : 16);
+}
+
+template <int FORM>
+static hipError_t launch_f32(const float* A, const float* W, float* out, int M, int N, int K, bool add, const F32Norm& norm, const RopeAppend& rope,
+                             hipStream_t st) {
+    constexpr bool GLU = FORM == kF32Glu;
+    auto launch = [&](auto kern, int rows, int feats, int threads) {
         const int tiles_m = (M + rows - 1) / rows, tiles_n = (N + feats - 1) / feats;
-        if (K % 4 == 0) hipLaunchKernelGGL(vec, dim3(tiles_m * tiles_n), dim3(threads), 0, st, A, W, out, M, N, K, tiles_m);
-        else hipLaunchKernelGGL(novec, dim3(tiles_m * tiles_n), dim3(threads), 0, st, A, W, out, M, N, K, tiles_m);
+        hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(threads), 0, st, A, W, out, M, N, K, tiles_m, add ? 1 : 0, norm, rope);
         return hipGetLastError();
     };
-    // 64-row wave tiles once they make a work-group for every other CU; below that eight waves share a reduction
-    constexpr int NTB = GLU ? 2 : 4, NTS = GLU ? 2 : 1, FB = GLU ? 64 : 256, FS = 16;
-    if ((long long)((M + 63) / 64) * ((N + FB - 1) / FB) >= 128)
-        return launch(gemm_f32_kernel<4, NTB, 1, 4, GLU, true>, gemm_f32_kernel<4, NTB, 1, 4, GLU, false>, 64, FB, 256);
-    if (M <= 16) return launch(gemm_f32_kernel<1, NTS, 8, 8, GLU, true>, gemm_f32_kernel<1, NTS, 8, 8, GLU, false>, 16, FS, 512);
-    return launch(gemm_f32_kernel<2, NTS, 8, 8, GLU, true>, gemm_f32_kernel<2, NTS, 8, 8, GLU, false>, 32, FS, 512);
+    constexpr int NTB = GLU ? 2 : 4, NTS = FORM == kF32Plain ? 1 : 2, FB = GLU ? 64 : 256, FS = FORM == kF32Qkv ? 32 : 16;
+    const bool low = f32_low(M, N, FS);
+    if (norm.gain) {
+        if (!gemm_f32_fuses(M, N, K, (F32Form)FORM)) return hipErrorInvalidValue;
+        return launch(gemm_f32_kernel<1, NTS, 8, 8, FORM, true, true>, 16, FS, 512);
+    }
+    if constexpr (FORM == kF32Qkv) return hipErrorInvalidValue;
+    else {
+        const bool vec = K % 4 == 0;
+        if (f32_large(M, N, GLU))
+            return vec ? launch(gemm_f32_kernel<4, NTB, 1, 4, FORM, true, false>, 64, FB, 256) : launch(gemm_f32_kernel<4, NTB, 1, 4, FORM, false, false>, 64, FB, 256);
+        if (low) return vec ? launch(gemm_f32_kernel<1, NTS, 8, 8, FORM, true, false>, 16, FS, 512) : launch(gemm_f32_kernel<1, NTS, 8, 8, FORM, false, false>, 16, FS, 512);
+        return vec ? launch(gemm_f32_kernel<2, NTS, 8, 8, FORM, true, false>, 32, FS, 512) : launch(gemm_f32_kernel<2, NTS, 8, 8, FORM, false, false>, 32, FS, 512);
+    }
 }
 
 template <int MT, int NT, int WM, int WN>
@@ -1280,12 +1432,17 @@ hipError_t gemm_bf16(const bf16_t* A, const bf16_t* W, float* out, int M, int N,
     }
 }
 
-hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st) {
-    return launch_f32<false>(A, W, out, M, N, K, st);
+hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, bool add, const F32Norm& norm, hipStream_t st) {
+    return launch_f32<kF32Plain>(A, W, out, M, N, K, add, norm, RopeAppend{}, st);
 }
 
-hipError_t gemm_f32_glu(const float* A, const float* W, float* act, int M, int F, int K, hipStream_t st) {
-    return launch_f32<true>(A, W, act, M, F, K, st);
+hipError_t gemm_f32_glu(const float* A, const float* W, float* act, int M, int F, int K, const F32Norm& norm, hipStream_t st) {
+    return launch_f32<kF32Glu>(A, W, act, M, F, K, false, norm, RopeAppend{}, st);
+}
+
+hipError_t gemm_f32_qkv(const float* h, const float* W, int K, const F32Norm& norm, const RopeAppend& rope, hipStream_t st) {
+    if (rope.dtype != 0 || rope.hd % 32 != 0) return hipErrorInvalidValue;
+    return launch_f32<kF32Qkv>(h, W, nullptr, rope.T, (rope.Hq + 2 * rope.Hkv) * rope.hd, K, false, norm, rope, st);
 }
 
 }  // namespace sv

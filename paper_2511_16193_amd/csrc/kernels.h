@@ -32,9 +32,17 @@ StripPlan gemm_bf16_strip_plan(int M, int N, int K, int min_splits, int max_spli
 TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits);
 TallTiles gemm_bf16_tall_256(int M);
 hipError_t gemm_bf16_ws_glu(const bf16_t* Ap, const bf16_t* Wp, bf16_t* act_out, int M, int F, int K, hipStream_t st);
-hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, hipStream_t st);
+// fp32.  norm.gain != null: A are residual rows, a * rsqrt(mean(a^2) + eps) * gain is what is multiplied (rows 16-byte aligned; where
+// gemm_f32_fuses says so).  add: out += the product
+struct F32Norm { const float* gain; float eps; };
+enum F32Form { kF32Plain, kF32Glu, kF32Qkv };
+bool gemm_f32_fuses(int M, int N, int K, F32Form form);
+hipError_t gemm_f32(const float* A, const float* W, float* out, int M, int N, int K, bool add, const F32Norm& norm, hipStream_t st);
 // W [2F][K] (gate rows, then up rows): act [M][F] = silu(gate) * up
-hipError_t gemm_f32_glu(const float* A, const float* W, float* act, int M, int F, int K, hipStream_t st);
+hipError_t gemm_f32_glu(const float* A, const float* W, float* act, int M, int F, int K, const F32Norm& norm, hipStream_t st);
+// QKV projection, rotary embedding and append in one (rope.qkv_part unused); norm.gain != null
+struct RopeAppend;
+hipError_t gemm_f32_qkv(const float* h, const float* W, int K, const F32Norm& norm, const RopeAppend& rope, hipStream_t st);
 
 // ---- elementwise.hip ----
 // One pass of rows, described by the host in one staged block (ints): per request kReqInts of
@@ -51,7 +59,7 @@ struct RowPrep {
     const int32_t* tok_matrix; int tok_ld;   // prefill: the prompts instead of last_tokens / drafts
     const void* embed; int dtype; float* h; int d;   // embed != null: h[t,:] = the row's embedding (fp32)
     int32_t* row_slot;          // [T] physical cache slot: page * page_size + position in the page
-    int32_t* row_info;          // [T][4] sequence id, index among the request's rows, the request's rows, 0
+    int32_t* row_info;          // [T][4] sequence id, index among the request's rows, the request's rows, its cached length
     int32_t* row_part;          // [T][4] row of the first attention partial (kv head 0, piece 0, q head 0 of the group), partial
                                 //        rows per kv head, per piece, pieces to merge (0: the attention writes the row itself)
     float* rope;                // [T, head_dim/2, 2] cos, sin

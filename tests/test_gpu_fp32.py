@@ -26,3 +26,23 @@ def test_fp32_step(batch, k, chains, hd, d, ff, vocab, lo, hi):
     err, exempt, diverged = compare_step(r, g, "fp32", k)
     assert err < LOGIT_TOL["fp32"] and len(diverged) <= 1
     case.close()
+
+
+@pytest.mark.parametrize("batch,k,hd,d,ff,vocab", [
+    (1, 0, 128, 4, 31, 7),            # one reduction group, most of it beyond the end; fewer features than a tile
+    (4, 3, 64, 260, 130, 2061),       # 16 rows, one whole tile; the vocabulary ends in a tile of 13 features
+    (17, 0, 64, 1024, 516, 1026),     # 17 rows; the longest reduction that the projections normalise themselves
+    (17, 0, 128, 1028, 516, 1026),    # just beyond it: norms and rotary as launches of their own
+    (51, 4, 64, 64, 320, 128),        # 255 rows, 16 tiles of gate/up features in 16 rows: the last that a CU each holds
+    (52, 4, 64, 64, 320, 128),        # 260 rows: one tile more than CUs
+])
+def test_fp32_step_where_norms_and_rotary_ride_in_the_projections(batch, k, hd, d, ff, vocab):
+    shape = W.Shape("f32-fused", 2, d, 4, 2, hd, ff, vocab, dtype="fp32", rope_theta=1e4, batch=batch, k=k, n_chains=1, seed=33)
+    case = Case(shape, np.random.default_rng(9).integers(0, 70, size=batch), verify_mode=OV.STOCHASTIC, sample_mode=OV.SAMPLE_EXP_RACE)
+    x0 = W.make_tokens((batch,), vocab, shape.seed, "x0")
+    q = W.make_random_q((batch, 1, k), vocab, 1.0, shape.seed) if k else None
+    drafts = W.sample_from(q, shape.seed).numpy() if k else np.zeros((batch, 1, 0), dtype=np.int64)
+    r, g = case.step(x0, drafts, q, W.make_uniforms((batch, 1, k + 1), shape.seed))
+    err, exempt, diverged = compare_step(r, g, "fp32", k)
+    assert err < LOGIT_TOL["fp32"] and len(diverged) <= 1
+    case.close()
