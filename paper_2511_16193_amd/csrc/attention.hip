@@ -764,11 +764,16 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
 // head take one piece's (m, l) each, all at once, and share the factors; eight pieces' O are in flight at a time.  Rows that
 // follow each other go to one XCD (their packed output shares cache lines): 320 / 800 rows 6.9 / 19.3 -> 5.8 / 16.0 us.
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
-    const int t = xcd_remap(blockIdx.x, gridDim.x), h = blockIdx.y * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31, d = lane * 4;
+    const int t_out = xcd_remap(blockIdx.x, gridDim.x), h = blockIdx.y * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31, d = lane * 4;
     if (h >= a.Hq) return;                                // (whole groups of 32)
+    const int t = a.last_of ? a.last_of[t_out * kReqInts] + a.last_of[t_out * kReqInts + 1] - 1 : t_out;
+    bf16_t* dst = reinterpret_cast<bf16_t*>(a.last_of ? a.last_out : a.out) + act_index(t_out, h * HD + d, a.Hq * HD, a.out_packed);
     const int4 pt = reinterpret_cast<const int4*>(a.row_part)[t];
     const int nch = pt.w;                                 // 0: a request of one piece, already written
-    if (nch == 0) return;
+    if (nch == 0) {
+        if (a.last_of) *reinterpret_cast<u32x2*>(dst) = *reinterpret_cast<const u32x2*>(reinterpret_cast<const bf16_t*>(a.out) + act_index(t, h * HD + d, a.Hq * HD, a.out_packed));
+        return;
+    }
     const int G = a.Hq / a.Hkv, hkv = h / G;
     const int64_t base = (int64_t)pt.x + (int64_t)hkv * pt.y + h % G;
     const floatx2* ml = reinterpret_cast<const floatx2*>(a.part_ml) + base;
@@ -797,7 +802,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o, 32);
     // four consecutive dimensions stay inside one 8-element piece of either output order
     u32x2 pk = {pack2bf(num[0] / den, num[1] / den), pack2bf(num[2] / den, num[3] / den)};
-    *reinterpret_cast<u32x2*>(reinterpret_cast<bf16_t*>(a.out) + act_index(t, h * HD + d, a.Hq * HD, a.out_packed)) = pk;
+    *reinterpret_cast<u32x2*>(dst) = pk;
 }
 
 // Generic path: one work-group of four waves per (new row, q head), keys in chunks of 256.  Scores with a thread per
@@ -812,7 +817,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float scale) {
     constexpr int CK = 256, GROUPS = 256 / D, EP = 16 / (int)sizeof(T);
-    const int t = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+    const int t_out = blockIdx.x, t = a.last_of ? a.last_of[t_out * kReqInts] + a.last_of[t_out * kReqInts + 1] - 1 : t_out, h = blockIdx.y, tid = threadIdx.x;
     const int4 info = reinterpret_cast<const int4*>(a.row_info)[t];
     const int seq = info.x, j = info.y;
     const int L = info.w, total = L + info.z;
@@ -898,7 +903,7 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
 #pragma unroll
         for (int g = 1; g < GROUPS; ++g) v += acc_sh[g][tid];
         const float den = (red[0] + red[1]) + (red[2] + red[3]);
-        Store<T>::store(reinterpret_cast<T*>(a.out) + act_index(t, h * D + tid, a.Hq * D, a.out_packed), v / den);
+        Store<T>::store(reinterpret_cast<T*>(a.last_of ? a.last_out : a.out) + act_index(t_out, h * D + tid, a.Hq * D, a.out_packed), v / den);
     }
 }
 
@@ -952,10 +957,10 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
             }
         }
         if (e != hipSuccess) return e;
-        if (a.merge) hipLaunchKernelGGL(attn_merge_kernel, dim3(a.T, (a.Hq + 7) / 8), dim3(256), 0, st, b);
+        if (a.merge || a.last_of) hipLaunchKernelGGL(attn_merge_kernel, dim3(a.last_of ? a.n_last : a.T, (a.Hq + 7) / 8), dim3(256), 0, st, b);
         return hipGetLastError();
     }
-    dim3 grid(a.T, a.Hq);
+    dim3 grid(a.last_of ? a.n_last : a.T, a.Hq);
     if (a.dtype == 1 && a.hd == 128)
         hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 128>), grid, dim3(256), 0, st, a, scale);
     else if (a.dtype == 1 && a.hd == 64)

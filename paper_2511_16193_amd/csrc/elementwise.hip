@@ -76,11 +76,12 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
                                                           int64_t part_stride, const T* __restrict__ w,
                                                           T* __restrict__ a, int d, float eps, bool packed,
                                                           const int32_t* __restrict__ inv, const float* __restrict__ wts,
-                                                          int top_k, const int32_t* __restrict__ last_of) {
+                                                          int top_k, LastRows last) {
     constexpr int U = NV == 1 ? 8 : 4;                   // planes, or expert rows, in flight
     __shared__ float red[NTH / 64];
     const int t_out = xcd_remap(blockIdx.x, gridDim.x);
-    const int t = last_of ? last_of[t_out * kReqInts] + last_of[t_out * kReqInts + 1] - 1 : t_out;
+    const int t = last.of ? last.of[t_out * kReqInts] + last.of[t_out * kReqInts + 1] - 1 : t_out;
+    const int ta = last.dense ? t_out : t;               // row of what is added
     const int nq = d >> 2;                               // float4 pieces per row
     floatx4* hr = reinterpret_cast<floatx4*>(h + (int64_t)t * d);
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -102,8 +103,8 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int j = j0 + u < top_k ? j0 + u : j0;
-                wj[u] = j0 + u < top_k ? wts[(int64_t)t * top_k + j] : 0.f;
-                const floatx4* pr = reinterpret_cast<const floatx4*>(part + (int64_t)inv[(int64_t)t * top_k + j] * d);
+                wj[u] = j0 + u < top_k ? wts[(int64_t)ta * top_k + j] : 0.f;
+                const floatx4* pr = reinterpret_cast<const floatx4*>(part + (int64_t)inv[(int64_t)ta * top_k + j] * d);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     const int i = threadIdx.x + v * NTH;
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
             floatx4 y[U][NV];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const floatx4* pr = reinterpret_cast<const floatx4*>(part + (s0 + u < S ? s0 + u : s0) * part_stride + (int64_t)t * d);
+                const floatx4* pr = reinterpret_cast<const floatx4*>(part + (s0 + u < S ? s0 + u : s0) * part_stride + (int64_t)ta * d);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     const int i = threadIdx.x + v * NTH;
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
     for (int v = 0; v < NV; ++v) {
         const int i = threadIdx.x + v * NTH;
         if (i < nq) {
-            if ((S > 0 || inv) && !last_of) hr[i] = x[v];
+            if ((S > 0 || inv) && (!last.of || last.dense)) hr[i] = x[v];
             ss = fmaf(x[v][0], x[v][0], ss);
             ss = fmaf(x[v][1], x[v][1], ss);
             ss = fmaf(x[v][2], x[v][2], ss);
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = x[v][e] * r * gain[v][e];
             // four consecutive columns are contiguous in either output order
-            Store<T>::store4(a + act_index(t_out, 4 * i, d, packed), o);
+            Store<T>::store4(a + act_index(last.row0 + t_out, 4 * i, d, packed), o);
         }
     }
 }
@@ -286,13 +287,13 @@ constexpr int kWideNormRows = 640;
 
 template <typename T>
 static hipError_t add_rmsnorm_t(float* h, const float* part, int S, const T* w, T* a, int T_, int d, float eps, bool packed,
-                                const int32_t* inv, const float* wts, int top_k, const int32_t* last_of, int n_out, hipStream_t st) {
-    const int64_t stride = (int64_t)T_ * d;
+                                const int32_t* inv, const float* wts, int top_k, const LastRows& last, hipStream_t st) {
+    const int64_t stride = (int64_t)(last.dense ? last.n : T_) * d;
     const int nq = d / 4;
     if (d % 4 != 0 || nq > 256 * 8) return hipErrorInvalidValue;
-    const dim3 grid(last_of ? n_out : T_);
+    const dim3 grid(last.of ? last.n : T_);
     auto launch = [&](auto kern, int threads) {
-        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k, last_of);
+        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, st, h, part, S, stride, w, a, d, eps, packed, inv, wts, top_k, last);
     };
     // Few rows: the more threads the fewer round trips (five rows of 896 pieces: 6.0 us with 256 threads, 4.7 with 1024).
     // Many: as few idle lanes and registers as the width allows (800 rows of 1280 pieces and four planes in flight: eight
@@ -300,7 +301,7 @@ static hipError_t add_rmsnorm_t(float* h, const float* part, int S, const T* w, 
     // In between the two are level and the line's place matters little: us of a layer's three norms, 1024 threads against 512, at
     // 160 / 320 / 480 / 640 / 800 / 1280 rows: 896 pieces 18.5 / 25.2 / 29.4 / 40.2 / 41.1 / 56.3 against 19.0 / 25.3 / 29.5 / 38.9 /
     // 37.8 / 54.0; 1280 pieces 22.5 / 32.7 / 31.4 / 50.6 / 54.1 / 72.4 against 24.0 / 32.6 / 32.3 / 51.4 / 54.2 / 73.2.
-    const bool wide = T_ <= kWideNormRows;
+    const bool wide = (int)grid.x <= kWideNormRows;
     if (nq <= 512) launch(add_rmsnorm_kernel<T, 1, 512>, 512);
     else if (nq <= 1024 && wide) launch(add_rmsnorm_kernel<T, 1, 1024>, 1024);
     else if (nq <= 1024) launch(add_rmsnorm_kernel<T, 2, 512>, 512);
@@ -311,15 +312,15 @@ static hipError_t add_rmsnorm_t(float* h, const float* part, int S, const T* w, 
 }
 
 hipError_t add_rmsnorm(float* h, const float* part, int S, const void* w, void* a, int dtype, int T, int d, float eps,
-                       bool packed, hipStream_t st, const int32_t* last_of, int n_out) {
+                       bool packed, hipStream_t st, const LastRows& last) {
     if (dtype == 1)
-        return add_rmsnorm_t<bf16_t>(h, part, S, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, nullptr, nullptr, 0, last_of, n_out, st);
-    return add_rmsnorm_t<float>(h, part, S, (const float*)w, (float*)a, T, d, eps, packed, nullptr, nullptr, 0, last_of, n_out, st);
+        return add_rmsnorm_t<bf16_t>(h, part, S, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, nullptr, nullptr, 0, last, st);
+    return add_rmsnorm_t<float>(h, part, S, (const float*)w, (float*)a, T, d, eps, packed, nullptr, nullptr, 0, last, st);
 }
 
 hipError_t add_rmsnorm_experts(float* h, const float* y, const int32_t* inv, const float* wts, int top_k, const void* w, void* a,
-                               int T, int d, float eps, bool packed, hipStream_t st, const int32_t* last_of, int n_out) {
-    return add_rmsnorm_t<bf16_t>(h, y, 0, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, inv, wts, top_k, last_of, n_out, st);
+                               int T, int d, float eps, bool packed, hipStream_t st, const LastRows& last) {
+    return add_rmsnorm_t<bf16_t>(h, y, 0, (const bf16_t*)w, (bf16_t*)a, T, d, eps, packed, inv, wts, top_k, last, st);
 }
 
 hipError_t rope_append(const RopeAppend& p, hipStream_t st) {

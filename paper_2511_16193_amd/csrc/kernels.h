@@ -68,13 +68,14 @@ struct RowPrep {
 };
 hipError_t prep_rows(const RowPrep& p, hipStream_t st);
 // h[t,:] += sum_s part[s][t,:] (S may be 0), then a[t,:] = storage(h * rsqrt(mean(h^2)+eps) * w)
-// last_of != null (a prefill's final norm): only the last row of each of n_out requests of that table is normalised, to
-// rows 0 .. n_out-1 of a, and h is left as it was
+// last.of != null (the end of a prefill): only the last row of each of last.n requests of that table is normalised, to rows last.row0,
+// last.row0 + 1, ... of a.  dense: what is added has one row for each of these and no others
+struct LastRows { const int32_t* of; int n; bool dense; int row0; };
 hipError_t add_rmsnorm(float* h, const float* part, int S, const void* w, void* a, int dtype, int T, int d, float eps,
-                       bool packed, hipStream_t st, const int32_t* last_of = nullptr, int n_out = 0);
+                       bool packed, hipStream_t st, const LastRows& last = LastRows{});
 // the same with the addend = weighted sum of the row's top_k expert outputs y[inv[t*top_k + j]] (bf16 models)
 hipError_t add_rmsnorm_experts(float* h, const float* y, const int32_t* inv, const float* wts, int top_k, const void* w, void* a,
-                               int T, int d, float eps, bool packed, hipStream_t st, const int32_t* last_of = nullptr, int n_out = 0);
+                               int T, int d, float eps, bool packed, hipStream_t st, const LastRows& last = LastRows{});
 struct RopeAppend {
     const float* qkv_part; int S;       // [S][T][(Hq+2Hkv)*hd]
     const float* rope;                  // [T][hd/2][2]
@@ -113,6 +114,8 @@ struct AttnArgs {
     int grid_items;                     // when > 0: items the grid is sized for (an upper bound of the item count)
     bool row_items;                     // prefill: an item is 64 stacked rows of a request, whose keys end at the last one it sees
     bool merge;                         // some request has several pieces
+    const int32_t* last_of; int n_last; // when set (the last layer of a prefill): only the last rows of the first n_last requests of that
+    void* last_out;                     //       table are wanted, in rows 0 .. n_last - 1 of this buffer, which is not `out` (work: items that hold them)
     int min_row_tiles;                  // lower bound on the 16-row tiles of the bf16 kernel (tuning)
     int max_row_tiles;                  // most 16-row tiles one work-group takes (1..4); more rows -> row groups
     bool out_packed;                    // write `out` in the packed activation order (see act_index)

@@ -38,6 +38,34 @@ def test_prefill_is_the_oracles_causal_pass(cached, lens):
     case.close()
 
 
+@pytest.mark.parametrize("dtype,packed,experts,hd,page,cached,lens", [
+    ("bf16", True, 0, 128, 64, [0] * 33, [4] * 31 + [3, 1]),      # 33 last rows of 128: two operand tiles, the most that are taken alone
+    ("bf16", True, 0, 128, 64, [0] * 33, [4] * 30 + [3, 2, 2]),   # of 127: one row short of that, all rows go on
+    ("bf16", True, 0, 128, 64, [5, 70], [63, 1]),                 # one tile of 64 rows, a prompt of one token
+    ("bf16", True, 64, 128, 64, [3, 0], [40, 24]),                # experts: the last rows alone are routed
+    ("bf16", False, 0, 128, 64, [0, 9], [90, 17]),                # row-major weights
+    ("bf16", True, 0, 64, 64, [0, 9], [90, 17]),                  # the generic attention, packed output
+    ("bf16", True, 0, 128, 96, [0, 9], [90, 17]),                 # the same by the page size
+    ("fp32", False, 0, 64, 64, [0, 9, 0], [90, 17, 17]),          # fp32, norms and rotary as launches of their own behind it
+])
+def test_last_layer_of_a_prefill_on_the_prompts_last_rows(dtype, packed, experts, hd, page, cached, lens):
+    # (experts: weights with which no row's last kept and first dropped expert are closer than 2.6e-3 of their probability in the first
+    # layer, 9e-3 for the rows that the last one routes; the two sides' inputs of a layer differ by some 1e-3)
+    shape = W.Shape("last-rows", 2, 256, 8, 2, hd, 0 if experts else 512, 2048, dtype=dtype, batch=len(lens), k=4, seed=105 if experts else 83,
+                    n_experts=experts, top_k=4 if experts else 0, d_expert=128 if experts else 0)
+    case = Case(shape, cached, verify_mode=OV.STOCHASTIC, synthetic_kv=True, extra_tokens=max(lens) + 8, packed=packed, page_size=page)
+    prompts = W.make_tokens((len(lens), max(lens)), shape.vocab, shape.seed, "prompt")
+    lo = np.stack([OV.prefill(case.spec, case.wn, case.caches[b], prompts[b, :n])[-1] for b, n in enumerate(lens)])
+    ld = case.ver.prefill_batch(list(range(len(lens))), torch.from_numpy(prompts).to(torch.int32), lens).cpu().numpy()
+    assert np.max(np.abs(lo - ld)) < LOGIT_TOL[dtype]
+    assert np.array_equal(case.device_lengths(), [a + n for a, n in zip(cached, lens)])
+    for b, n in enumerate(lens):
+        kd, vd = case.ver.kv_read(b, shape.n_layers - 1, cached[b], n)
+        ko, vo = case.caches[b].k[-1][cached[b]:cached[b] + n], case.caches[b].v[-1][cached[b]:cached[b] + n]
+        assert np.max(np.abs(kd.float().cpu().numpy() - ko)) < 0.03 and np.max(np.abs(vd.float().cpu().numpy() - vo)) < 0.03
+    case.close()
+
+
 def test_prefill_behind_rejected_drafts():
     """A step's rejected drafts leave the host's bounds of the lengths above the live ones; the prompts that follow without the
     lengths being read back start at the live ends, and see nothing of what was rejected."""
