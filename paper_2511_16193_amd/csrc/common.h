@@ -104,6 +104,12 @@ __host__ __device__ __forceinline__ bool row_sees(int i, int j, int k) {
     return (i - 1) / k == (j - 1) / k && j <= i;
 }
 
+// What a launch leaves for later ones and does not read again itself, written as a stream: such lines are the first to leave an XCD's L2.
+// As ordinary stores they lie there dirty until the next launch's weight stream pushes them out, and that stream waits for the
+// write-backs.  For stores that fill whole 128-byte lines at once, or whole halves that are put together before they leave; the pieces of 8
+// and 16 bytes of a packed row do not (the norm's operands so written: 24 -> 41 us at 2304 rows).
+template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
+
 // ---- waits and direct-to-LDS loads ----
 #define SV_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 

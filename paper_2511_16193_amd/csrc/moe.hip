@@ -331,7 +331,7 @@ __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const u32x4*>(src + (int64_t)(s0 + i) * 512);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(dst + (int64_t)(s0 + i) * 512) = v[i];
+        for (int i = 0; i < 4; ++i) store_stream(reinterpret_cast<u32x4*>(dst + (int64_t)(s0 + i) * 512), v[i]);
     }
 }
 
@@ -348,6 +348,9 @@ __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
 // expert) 171.9 + 88.8 -> 160.5 + 85.6 us, 20 rows (one) 129.7 + 65.7 -> 118.1 + 63.9 (4.9 TB/s of weights; a plain
 // stream reaches 6.0).  Sixteen weight fragments in flight instead of eight, where one tile leaves registers for them, 2 %;
 // with two tiles they cost the fourth work-group and gain nothing.
+// The gathered tiles, silu(gate) * up and the outputs leave as streams (store_stream): the 31 MB of gathered tiles of 640 rows lay dirty in the L2s
+// when the weights came through.  640 rows: gather 11.6 -> 10.7 us, products 167 + 88.5 -> 157 + 87, the next layer's attention 235 -> 231, the
+// norm that combines the outputs 8.8 -> 9.3; 20 rows 114 + 58.6 -> 112 + 58.7.
 constexpr int kMoeSlices = 8;                               // 16-wide slices per fill
 
 template <int MODE, int MT>
@@ -440,7 +443,7 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) dst[(int64_t)(8 * q + r) * a.d] = acc[j][4 * q + r];
+                    for (int r = 0; r < 4; ++r) store_stream(dst + (int64_t)(8 * q + r) * a.d, (float)acc[j][4 * q + r]);
             }
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);
@@ -475,7 +478,7 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
                         }
                         // features 8q + 4 lg .. +3 of this wave's 32: slice q/2, half q%2, elements 4 lg ..
                         u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
-                        *reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg) = pk;
+                        store_stream(reinterpret_cast<u32x2*>(dst + ((q >> 1) * 64 + l32 + 32 * (q & 1)) * 8 + 4 * lg), pk);
                     }
                 }
             }
