@@ -30,6 +30,12 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
+// What a launch leaves for later ones and does not read again itself, written as a stream: such lines are the first to leave an XCD's L2.
+// As ordinary stores they lie there dirty until the next launch's weight stream pushes them out, and that stream waits for the
+// write-backs.  For stores that fill whole 128-byte lines at once, or whole halves that are put together before they leave; the pieces of 8
+// and 16 bytes of a packed row do not (the norm's operands so written: 24 -> 41 us at 2304 rows).
+template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
+
 // Storage-type traits: T is float (fp32 model) or bf16_t (bf16 model).
 template <typename T> struct Store;
 template <> struct Store<float> {
@@ -42,6 +48,7 @@ template <> struct Store<float> {
     static __device__ __forceinline__ void store4(float* p, const float* v) {      // p 16-byte aligned
         *reinterpret_cast<floatx4*>(p) = floatx4{v[0], v[1], v[2], v[3]};
     }
+    static __device__ __forceinline__ void stream4(float* p, const float* v) { store_stream(reinterpret_cast<floatx4*>(p), floatx4{v[0], v[1], v[2], v[3]}); }
 };
 template <> struct Store<bf16_t> {
     static __device__ __forceinline__ float load(const bf16_t* p) { return bf2f(*p); }
@@ -53,6 +60,9 @@ template <> struct Store<bf16_t> {
     static __device__ __forceinline__ void store(bf16_t* p, float v) { *p = f2bf(v); }
     static __device__ __forceinline__ void store4(bf16_t* p, const float* v) {     // p 8-byte aligned
         *reinterpret_cast<u32x2*>(p) = u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
+    }
+    static __device__ __forceinline__ void stream4(bf16_t* p, const float* v) {
+        store_stream(reinterpret_cast<u32x2*>(p), u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])});
     }
 };
 
@@ -103,12 +113,6 @@ __host__ __device__ __forceinline__ bool row_sees(int i, int j, int k) {
     if (i == 0) return false;
     return (i - 1) / k == (j - 1) / k && j <= i;
 }
-
-// What a launch leaves for later ones and does not read again itself, written as a stream: such lines are the first to leave an XCD's L2.
-// As ordinary stores they lie there dirty until the next launch's weight stream pushes them out, and that stream waits for the
-// write-backs.  For stores that fill whole 128-byte lines at once, or whole halves that are put together before they leave; the pieces of 8
-// and 16 bytes of a packed row do not (the norm's operands so written: 24 -> 41 us at 2304 rows).
-template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
 
 // ---- waits and direct-to-LDS loads ----
 #define SV_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))

@@ -70,7 +70,8 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(RowPrep p) {
 // accumulated in slot order.
 // A row's packed output is 16-byte pieces of cache lines that it shares with its neighbours: rows that follow each other go to one
 // XCD, whose L2 puts the lines together (dealt round-robin, 320 rows of 3584 wrote 8.7 MiB where they hold 6.5): 320 / 2304 / 3520 rows
-// 10.0 / 30.5 / 41 -> 8.7 / 24.5 / 32 us.
+// 10.0 / 30.5 / 41 -> 8.7 / 24.5 / 32 us.  The residual leaves as a stream: 320 / 800 / 2304 rows 8.5 / 16.5 / 23.3 -> 8.2 / 16.1 / 22.8 us, and the
+// gate/up weights of 147 rows after it 121 -> 115.
 template <typename T, int NV, int NTH>
 __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h, const float* __restrict__ part, int S,
                                                           int64_t part_stride, const T* __restrict__ w,
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
     for (int v = 0; v < NV; ++v) {
         const int i = threadIdx.x + v * NTH;
         if (i < nq) {
-            if ((S > 0 || inv) && (!last.of || last.dense)) hr[i] = x[v];
+            if ((S > 0 || inv) && (!last.of || last.dense)) store_stream(hr + i, x[v]);
             ss = fmaf(x[v][0], x[v][0], ss);
             ss = fmaf(x[v][1], x[v][1], ss);
             ss = fmaf(x[v][2], x[v][2], ss);
@@ -178,6 +179,7 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
 // contiguous in the cache's K tiles); V is stored transposed, one element at a time.  head_dim % 8 == 0 (it is 64 or 128).
 // Rows that follow each other are a request's or a prompt's next tokens as a rule, with V elements two bytes apart: they go to one
 // XCD (320 / 800 / 3520 rows 7.7 / 15.5 / 28 -> 7.1 / 14.1 / 25.5 us, writes of 800 rows 21.0 -> 12.1 MiB).
+// q, whole half heads a store, is streamed as well (320 / 777 rows 7.15 / 8.45 -> 6.7 / 7.9); K's pieces of 8 bytes and V's of 2 are not.
 // Five rows, eight planes: 4.8 us; with one work-group per row and the planes one after the other 10.5.
 template <typename T>
 __global__ __launch_bounds__(256) void rope_append_vec_kernel(RopeAppend p) {
@@ -218,8 +220,8 @@ __global__ __launch_bounds__(256) void rope_append_vec_kernel(RopeAppend p) {
         }
         if (head < p.Hq) {
             T* q = reinterpret_cast<T*>(p.q_out) + ((int64_t)t * p.Hq + head) * hd;
-            Store<T>::store4(q + i, o1);
-            Store<T>::store4(q + i + half, o2);
+            Store<T>::stream4(q + i, o1);
+            Store<T>::stream4(q + i + half, o2);
         } else {
             const int kh = head - p.Hq;
             Store<T>::store4(pool + kv_k_index(p.geom, p.layer, page, kh, tok, i), o1);

@@ -330,6 +330,9 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
         return;
     }
     // acc[i][j][4 q + r] <-> row m0 + 32 j + 8 q + 4 lg + r, feature n0 + 32 (wave NT + i) + l32
+    // A half wave fills a line of 128 bytes: streamed, so that the next kernel's loads do not push them out of L2 first (LM head of 96 rows, 58 MB of
+    // logits, 224 -> 213 us; QKV and O planes of 96 rows 12.5 + 10.5 -> 12.1 + 9.9, the attention between them 162 -> 160.5, norm and rotary + 0.4 and + 0.2).
+    // The tall and the strip kernel write half lines, which as streams cost the next norm more than they save.
     float* dst = out + (int64_t)sp * M * N;
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -341,7 +344,7 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int m = m0 + j * 32 + 8 * q + 4 * lg + r;
-                    if (m < M) dst[(int64_t)m * N + n] = acc[i][j][4 * q + r];
+                    if (m < M) store_stream(dst + (int64_t)m * N + n, (float)acc[i][j][4 * q + r]);
                 }
     }
 }
@@ -899,9 +902,14 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t
 #pragma unroll
                     for (int e = 0; e < 4; ++e) r[e] = j < RH ? silu_mul(acc[i][j][e], other[e]) : silu_mul(other[e], acc[i][j][e]);
                     const int fs = tn * FS + i;
-                    if (fs < F / 16)
-                        *reinterpret_cast<u32x2*>(act + ((int64_t)(x >> 1) * (F / 16) + fs) * 512 + ((lg >> 1) * 32 + (x & 1) * 16 + l16) * 8 + 4 * (lg & 1)) =
-                            u32x2{pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
+                    if (fs < F / 16) {
+                        u32x2* dst = reinterpret_cast<u32x2*>(act + ((int64_t)(x >> 1) * (F / 16) + fs) * 512 + ((lg >> 1) * 32 + (x & 1) * 16 + l16) * 8 + 4 * (lg & 1));
+                        const u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
+                        // streamed up to 160 rows (the down projection of 96 / 147 rows 36.0 -> 31.4 / 68.0 -> 60.6 us); of 320 rows it would
+                        // take longer, 52.8 -> 54.8
+                        if constexpr (W == 4) store_stream(dst, pk);
+                        else *dst = pk;
+                    }
                 }
             }
         });
