@@ -419,12 +419,14 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
     }
 
     floatx4 o[8][R];
-    float m_run[R], mc[R], l_run[R];      // reference maximum (raw score), the same times scale*log2(e), partial sum
+    // reference (log2 units), partial sum, and the raw score above which the reference moves: -inf until the row has seen a key
+    float mc[R], l_run[R], limit[R];
+    const float unscale = 1.0f / scale_log2e;
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) {
-        m_run[rt] = -INFINITY;
         mc[rt] = 0.f;
         l_run[rt] = 0.f;
+        limit[rt] = -INFINITY;
 #pragma unroll
         for (int ht = 0; ht < 8; ++ht) o[ht][rt] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
@@ -554,12 +556,14 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
             // that share the row (they feed one MFMA accumulator) and is only moved when some score would
             // make 2^(c(s - m_ref)) exceed 2^16 (or on the row's first visible key): fp32 has the range to
             // spare, and the cross-lane reduction + accumulator rescale leave the per-tile path.
+            // One comparison with that score a row (it took four vector instructions; 280 -> 260 a tile besides the products): 125 stacked rows
+            // of 16k-32k keys 692 -> 682 and 689 -> 671 us a layer, 63 rows 515 -> 512.  (In the register kernel, bound by the stream: no change.)
             bool trig = false;
             float lmax[R];
 #pragma unroll
             for (int rt = 0; rt < R; ++rt) {
                 lmax[rt] = max8(s_cur[0][rt], s_cur[1][rt]);
-                trig |= ((m_run[rt] == -INFINITY) & (lmax[rt] > -INFINITY)) | (fmaf(lmax[rt], scale_log2e, -mc[rt]) > 16.0f);
+                trig |= lmax[rt] > limit[rt];
             }
             if (QK) {
 #pragma unroll
@@ -577,10 +581,10 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
                     float mx = lmax[rt];
                     mx = fmaxf(mx, __shfl_xor(mx, 16));
                     mx = fmaxf(mx, __shfl_xor(mx, 32));
-                    const float m_new = fmaxf(m_run[rt], mx);
-                    const float mc_new = m_new == -INFINITY ? 0.f : ceilf(m_new * scale_log2e);
+                    const bool seen = limit[rt] > -INFINITY, some = mx > -INFINITY;
+                    const float to = ceilf(mx * scale_log2e), mc_new = !some ? mc[rt] : seen ? fmaxf(mc[rt], to) : to;
                     const int shift = (int)fmaxf(mc[rt] - mc_new, -200.f);
-                    const float alpha = m_run[rt] == -INFINITY ? 0.f : ldexpf(1.0f, shift);
+                    const float alpha = seen ? ldexpf(1.0f, shift) : 0.f;
                     l_run[rt] *= alpha;
 #pragma unroll
                     for (int ht = 0; ht < 8; ++ht) {
@@ -602,8 +606,8 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
                                 pf_prev[rt][tm][i] = (__builtin_bit_cast(uint32_t, lo) >> 16) | (__builtin_bit_cast(uint32_t, hi) & 0xffff0000u);
                             }
                     }
-                    m_run[rt] = m_new;
                     mc[rt] = mc_new;
+                    limit[rt] = seen | some ? (mc_new + 16.0f) * unscale : -INFINITY;
                 }
             }
         }
@@ -681,8 +685,9 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
     }
 
     // ---- merge the waves of the group through LDS (maxima in log2 units from here on) ----
+    float m_run[R];
 #pragma unroll
-    for (int rt = 0; rt < R; ++rt) m_run[rt] = m_run[rt] == -INFINITY ? -INFINITY : mc[rt];
+    for (int rt = 0; rt < R; ++rt) m_run[rt] = limit[rt] > -INFINITY ? mc[rt] : -INFINITY;
     float (*o_sh)[HD][RP + 1] = reinterpret_cast<float (*)[HD][RP + 1]>(attn_lds);   // [W waves][HD][RP + 1], over the rings
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) {
