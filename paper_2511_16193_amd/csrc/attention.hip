@@ -53,6 +53,8 @@ __device__ __forceinline__ float max8(const floatx4& a, const floatx4& b) {
 // online softmax, PV, not skewed.  At these sizes the kernel runs at the rate the cache can be streamed at, and
 // inside a verification step it measured 3-14 % faster than the skewed kernel below (which is ahead once the
 // products dominate: four row tiles, or several row groups streaming the same keys).
+// A tile is read by this work-group only and as a stream (load_stream): 320 rows of 64 requests 131 -> 119 us a layer, 96 requests' single rows
+// 164 -> 151, 640 rows beside 8 q heads a kv head 230 -> 210, five rows of one request 13.6 -> 13.0.
 template <int R>
 __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(AttnArgs a, float scale_log2e) {
     // work item = one piece of one request's keys, cut by the host from its upper bounds of the lengths.
@@ -142,8 +144,8 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
             const bf16_t* vp = pool + uniform(vi + kb * 2048);
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
-                t.k[kb][kk] = *reinterpret_cast<const u32x4*>(kp + kk * 512 + lane_off);
-                t.v[kb * 4 + kk] = *reinterpret_cast<const u32x4*>(vp + kk * 512 + lane_off);
+                t.k[kb][kk] = load_stream(reinterpret_cast<const u32x4*>(kp + kk * 512 + lane_off));
+                t.v[kb * 4 + kk] = load_stream(reinterpret_cast<const u32x4*>(vp + kk * 512 + lane_off));
             }
         }
     };
@@ -344,6 +346,8 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 
 // R row tiles per work-group, W waves, D slots per wave for K and for V in the LDS ring (W * D * 16 KB of LDS).
 // Run as W = 2, D = 2: two work-groups share a CU.
+// ONCE: no other row group or item reads these keys, they come as a stream (load_stream; 63 rows of 256 requests 497 -> 445 us; with a second
+// row group to find them in L2 685 -> 703).
 // PT: bf16 terms the softmax weights are split into for the PV products.  With four row tiles (or several row
 // groups) this kernel is bound by its matrix products and the power they draw, and three quarters of them are PV
 // products: it runs with PT = 2 (16 significant bits; the 2^-17 relative it leaves is the size of the fp32
@@ -351,7 +355,7 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 // products than with three terms.  The register kernel above is bound by the stream and keeps three.  So does a prefill, whose
 // rows become the cache that every later step reads: with two terms 1.3 in a thousand outputs are rounded to another bf16
 // value than the exact sums', with three 0.03 to 0.4; 24 prompts of 100-500 tokens 24.56 -> 24.54 ms, one of 777 4.37 -> 4.39.
-template <int R, int W, int D, int PT>
+template <int R, int W, int D, int PT, bool ONCE = false>
 __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float scale_log2e) {
     // Work item = one piece of one request's keys, cut by the host from its upper bounds of the lengths.
     // Launch order: the kv heads of an item are neighbours, so the list's longest-first order holds chip-wide.
@@ -458,8 +462,8 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
         const int64_t ke = uniform(head_base + (int64_t)page * a.geom.page_elems + off * HD + half * v_off);
         unsigned char* dst = ring + (half * D + slot) * 8192;
         const char* src = reinterpret_cast<const char*>(pool + ke) + lane_bytes;
-        dma4(src, SV_LDS_PTR(dst));
-        dma4(src + 4096, SV_LDS_PTR(dst + 4096));
+        dma4<ONCE ? kStreamLoad : 0>(src, SV_LDS_PTR(dst));
+        dma4<ONCE ? kStreamLoad : 0>(src + 4096, SV_LDS_PTR(dst + 4096));
     };
 
     // Wave w takes tiles w, w + 4, ... of the piece: its tile t starts at key tile_key(t).
@@ -952,7 +956,8 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
                 case 1: e = launch_regs(attn_bf16_regs_kernel<1>, 1); break;
                 case 2: e = launch(attn_bf16_kernel<2, 2, 2, 2>, 2, 2, 2); break;
                 case 3: e = launch(attn_bf16_kernel<3, 2, 2, 2>, 3, 2, 2); break;
-                default: e = a.row_items ? launch(attn_bf16_kernel<4, 2, 2, 3>, 4, 2, 2) : launch(attn_bf16_kernel<4, 2, 2, 2>, 4, 2, 2); break;
+                default: e = a.row_items ? launch(attn_bf16_kernel<4, 2, 2, 3>, 4, 2, 2)
+                           : b.row_groups == 1 ? launch(attn_bf16_kernel<4, 2, 2, 2, true>, 4, 2, 2) : launch(attn_bf16_kernel<4, 2, 2, 2>, 4, 2, 2); break;
             }
         } else {
             switch (R) {

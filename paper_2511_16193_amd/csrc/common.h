@@ -36,6 +36,10 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
 // and 16 bytes of a packed row do not (the norm's operands so written: 24 -> 41 us at 2304 rows).
 template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
 
+// What is read once in a launch, and by one work-group only, read as a stream: such lines give way first in L2 and leave it to what is shared.
+template <typename T> __device__ __forceinline__ T load_stream(const T* p) { return __builtin_nontemporal_load(p); }
+constexpr int kStreamLoad = 2;                              // the same hint in the cache-policy operand of the load builtins
+
 // Storage-type traits: T is float (fp32 model) or bf16_t (bf16 model).
 template <typename T> struct Store;
 template <> struct Store<float> {
@@ -125,11 +129,12 @@ __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC
 
 // 4 KB from global memory straight into LDS: four wave-wide loads of 16 bytes per lane.  src is the lane's own
 // address (base + 16 * lane), dst the wave's LDS base; lane l's bytes land at dst + 16 * l + the immediate.
+template <int POLICY = 0>
 __device__ __forceinline__ void dma4(const char* src, __attribute__((address_space(3))) void* dst) {
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 1024, 0);
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 2048, 0);
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 3072, 0);
+    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 0, POLICY);
+    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 1024, POLICY);
+    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 2048, POLICY);
+    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 3072, POLICY);
 }
 
 // 16 bytes per lane from base + lane_off + off, off the same for all lanes, through a buffer descriptor over [base, base + bytes).
@@ -137,8 +142,9 @@ __device__ __forceinline__ void dma4(const char* src, __attribute__((address_spa
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }
+template <int POLICY = 0>
 __device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t d, uint32_t lane_off, uint32_t off) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(d, lane_off, off, 0));
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(d, lane_off, off, POLICY));
 }
 
 // f(std::integral_constant<int, 0>{}), ... , f(std::integral_constant<int, N - 1>{}): a loop whose index is a constant expression
