@@ -350,7 +350,8 @@ __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
 // with two tiles they cost the fourth work-group and gain nothing.
 // The gathered tiles, silu(gate) * up and the outputs leave as streams (store_stream): the 31 MB of gathered tiles of 640 rows lay dirty in the L2s
 // when the weights came through.  640 rows: gather 11.6 -> 10.7 us, products 167 + 88.5 -> 157 + 87, the next layer's attention 235 -> 231, the
-// norm that combines the outputs 8.8 -> 9.3; 20 rows 114 + 58.6 -> 112 + 58.7.
+// norm that combines the outputs 8.8 -> 9.3; 20 rows 114 + 58.6 -> 112 + 58.7.  The weights are read as a stream as well: 640 rows 157 + 88.5 -> 146 + 86.5,
+// 20 rows 111 + 57.7 -> 104 + 58.4.
 constexpr int kMoeSlices = 8;                               // 16-wide slices per fill
 
 template <int MODE, int MT>
@@ -371,7 +372,7 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
     const char* a_base = reinterpret_cast<const char*>(rows + ((int64_t)(MODE == 0 && one_tile ? 0 : tile + (my < nt_here ? my : nt_here - 1)) * kslices + ks_mine) * 512);
     const auto a_desc = buffer_of(a_base, (kslices - ks_mine) * 1024), w_desc = buffer_of(w_base, (kslices - 1) * 4096 + 1024);
     auto load_a = [&](int slice) __attribute__((always_inline)) { return buffer_load16(a_desc, lane * 16, slice * 1024); };
-    auto load_w = [&](int slice) __attribute__((always_inline)) { return buffer_load16(w_desc, lane * 16, slice * 4096); };
+    auto load_w = [&](int slice) __attribute__((always_inline)) { return buffer_load16<kStreamLoad>(w_desc, lane * 16, slice * 4096); };
     unsigned char* a_dst = abuf + (wave * APW) * 1024 + lane * 16;
     constexpr int BUF = MT * KA * 1024;
 
