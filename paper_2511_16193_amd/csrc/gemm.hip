@@ -137,7 +137,7 @@ typedef __attribute__((ext_vector_type(16))) float floatx16;
 // reads, PD k-slices ahead, with no LDS and no barrier on that path.  Only the activations, which every
 // wave needs, go through LDS: KA 16-wide slices of all MT 32-token tiles per fill (packed order too, so
 // a fill is a handful of contiguous 1 KB copies), double buffered, one barrier per fill.
-template <int MT, int NT, int KA, int PD, bool GLU>
+template <int MT, int NT, int KA, int PD, bool GLU, bool STREAM>
 __device__ __forceinline__ void gemm_bf16_ws_body(
     const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
     int M, int N, int K, int k_per_split, int splits, int tiles_m, int tiles_n, int tn0, int block_id) {
@@ -186,6 +186,11 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
         w_src[i] = Wp + (((int64_t)(nt >> 2) * kslices + ks0) * 4 + (nt & 3)) * 512 + lane * 8;
     }
     constexpr int W_STEP = 4 * 512;                       // elements between consecutive slices of a tile
+    // STREAM: no other row tile reads these weights
+    auto load_w = [&](int i, int slice) __attribute__((always_inline)) {
+        const u32x4* p = reinterpret_cast<const u32x4*>(w_src[i] + (int64_t)slice * W_STEP);
+        return STREAM ? load_stream(p) : *p;
+    };
 
     floatx16 acc[NT][MT];
 #pragma unroll
@@ -201,7 +206,7 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
     for (int p = 0; p < PD; ++p)
 #pragma unroll
         for (int i = 0; i < NT; ++i)
-            wring[p][i] = *reinterpret_cast<const u32x4*>(w_src[i] + (int64_t)(p < total_slices ? p : total_slices - 1) * W_STEP);
+            wring[p][i] = load_w(i, p < total_slices ? p : total_slices - 1);
 
     // first fill
     u32x4 areg[APW];
@@ -255,7 +260,7 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
             const int ahead = slice + PD < total_slices ? slice + PD : total_slices - 1;
 #pragma unroll
             for (int i = 0; i < NT; ++i)
-                wring[s % PD][i] = *reinterpret_cast<const u32x4*>(w_src[i] + (int64_t)ahead * W_STEP);
+                wring[s % PD][i] = load_w(i, ahead);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
@@ -352,11 +357,11 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
 // Two work-groups share a CU where the accumulator tile leaves room (up to 96 rows x 256 features, or 128-feature
 // strips): more, smaller work-groups resident at once, which evens out a launch whose work-group count is not a
 // multiple of the 256 CUs.
-template <int MT, int NT, int KA, int PD, bool GLU = false>
+template <int MT, int NT, int KA, int PD, bool GLU = false, bool STREAM = false>
 __global__ __launch_bounds__(256, (NT == 1 || MT <= 3) ? 2 : 1) void gemm_bf16_ws_kernel(
     const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
     int M, int N, int K, int k_per_split, int splits, int tiles_m, int tiles_n, int tn0) {
-    gemm_bf16_ws_body<MT, NT, KA, PD, GLU>(Ap, Wp, out, M, N, K, k_per_split, splits, tiles_m, tiles_n, tn0, blockIdx.x);
+    gemm_bf16_ws_body<MT, NT, KA, PD, GLU, STREAM>(Ap, Wp, out, M, N, K, k_per_split, splits, tiles_m, tiles_n, tn0, blockIdx.x);
 }
 
 // Gate/up projection with a short last round: the first n_main work-groups are 160-row ones over the 128-feature
@@ -372,9 +377,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ws_glu_mixed_kernel(
     int tiles_m, int strips_main, int tiles_m2, int strips_tail) {
     const int n_main = tiles_m * strips_main;
     if ((int)blockIdx.x < n_main)
-        gemm_bf16_ws_body<5, 2, 8, 8, true>(Ap, Wp, out, M, N, K, K, 1, tiles_m, strips_main, 0, blockIdx.x);
+        gemm_bf16_ws_body<5, 2, 8, 8, true, false>(Ap, Wp, out, M, N, K, K, 1, tiles_m, strips_main, 0, blockIdx.x);
     else
-        gemm_bf16_ws_body<2, 1, 8, 8, true>(Ap, Wp, out, M, N, K, K, 1, tiles_m2, 2 * strips_tail, 2 * strips_main, blockIdx.x - n_main);
+        gemm_bf16_ws_body<2, 1, 8, 8, true, false>(Ap, Wp, out, M, N, K, K, 1, tiles_m2, 2 * strips_tail, 2 * strips_main, blockIdx.x - n_main);
 }
 
 // ---- third bf16 kernel: tall tiles, 64 RW rows x 256 features per work-group, both operands through LDS ----
@@ -408,12 +413,20 @@ __device__ __forceinline__ void lds_landed_too(u32x4& d) { asm volatile("" : "+v
 // Both write m0, and the second exec: reserved registers, which the compiler takes no clobber for.  So they are for kernels in which
 // nothing else uses m0 (no builtin that loads into LDS, whose m0 the compiler may carry from one to the next), and dma1_lanes for places
 // that all 64 lanes of the wave reach: exec is all ones before it and after it.
+// STREAM: with the hint of load_stream.
+template <bool STREAM = false>
 __device__ __forceinline__ void dma1(const char* base, uint32_t lane_off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
+    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
 }
+template <bool STREAM = false>
 __device__ __forceinline__ void dma1_lanes(uint64_t lanes, const char* base, uint32_t lane_off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
-                 : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\ts_mov_b64 exec, -1"
+                     : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
+                     : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
 }
 
 template <bool GLU, int RW>
@@ -746,6 +759,8 @@ hipError_t gemm_bf16_tall(const bf16_t* Ap, const bf16_t* Wp, float* out, int M,
 // us alone with weights from HBM, against the kernel that was taken before: gate/up 37888 x 3584 at 5 / 64 / 96 / 128 / 160 / 192 /
 // 256 / 320 rows 46.2 / 49.4 / 54.3 / 58.6 / 62.7 / 69.4 / 76.9 / 88.1 -> 44.2 / 44.0 / 45.0 / 47.7 / 52.1 / 56.6 / 68.9 / 76.8; down 3584 x
 // 18944 at 5 / 64 / 160 rows 23.8 / 25.6 / 31.8 -> 21.3 / 23.0 / 30.6; QKV 4608 x 3584 6.3 / 7.5 / 13.1 -> 4.6 / 6.7 / 11.1.
+// Weights read with the hint of load_stream, us inside a step: gate/up of 5 / 42 / 96 rows 49.3 / 49.9 / 51.7 -> 45.2 / 46.6 / 49.4, of 55296 x 5120 at
+// 147 rows 121 -> 106; down of 5 rows 26.1 -> 24.4; LM head of 147 rows 333 -> 308.
 // The sums are those of the other two kernels, slice after slice: equal bits at the same splits.
 constexpr int strip_fills(int w, int rs, int fs) {        // fills in the ring: two work-groups of four waves share a CU's LDS
     const int n = (w == 4 ? 80 : 160) / (w / 2 * rs + 2 * fs);
@@ -793,8 +808,16 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t
     int ahead = 0;
     auto request = [&](auto which, uint32_t base) __attribute__((always_inline)) {
         constexpr int Q = decltype(which)::value;
-        if constexpr (Q < EACH) dma1(src[Q], lane_off[Q], base + (wave + W * Q) * 1024);
-        else if constexpr (EXTRA > 0) dma1_lanes(last_lanes, src[Q], lane_off[Q], base + min(wave + W * Q, P - 1) * 1024);
+        // pieces Q W .. Q W + W - 1, one a wave: of rows, which every strip reads, or of weights, which only this one does and which come as a
+        // stream.  Eight waves, bound by their products, do not gain (320 rows: gate/up 85.6 -> 84.1, down 53.1 -> 56.5, LM head 319 -> 323)
+        constexpr bool weights = W == 4 && Q * W >= A_P, mixed = W == 4 && !weights && Q * W + W > A_P;
+        if constexpr (Q < EACH) {
+            const uint32_t to = base + (wave + W * Q) * 1024;
+            if (mixed && wave + W * Q >= A_P) dma1<true>(src[Q], lane_off[Q], to);
+            else dma1<weights>(src[Q], lane_off[Q], to);
+        } else if constexpr (EXTRA > 0) {
+            dma1_lanes<weights>(last_lanes, src[Q], lane_off[Q], base + min(wave + W * Q, P - 1) * 1024);
+        }
     };
     auto advance = [&]() __attribute__((always_inline)) {  // past the end: the last fill again, so that the counts below hold
         if (++ahead < nfill) {
@@ -1025,8 +1048,14 @@ static hipError_t launch_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int 
     constexpr int BM = 32 * MT, BN = 128 * NT;
     if (N % BN != 0 || (K / splits) % (16 * KA) != 0) return hipErrorInvalidValue;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
-    hipLaunchKernelGGL((gemm_bf16_ws_kernel<MT, NT, KA, PD>), dim3(tiles_m * tiles_n * splits), dim3(256), 0, st, Ap, Wp,
-                       out, M, N, K, K / splits, splits, tiles_m, tiles_n, 0);
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(256), 0, st, Ap, Wp,
+                           out, M, N, K, K / splits, splits, tiles_m, tiles_n, 0);
+    };
+    // one row tile: the weights are read once, as a stream (LM heads of 152 thousand features at 5 / 20 / 42 / 96 rows 193 / 122 / 207 / 219 -> 168 / 107 /
+    // 190 / 202 us; QKV and O of 96 rows level).  Several: they find each other's in L2 (O of 5120 x 5120 at 800 rows, so read, 66.5 -> 72.6)
+    if (tiles_m == 1) launch(gemm_bf16_ws_kernel<MT, NT, KA, PD, false, true>);
+    else launch(gemm_bf16_ws_kernel<MT, NT, KA, PD>);
     return hipGetLastError();
 }
 
