@@ -1372,7 +1372,9 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
 
 // 64-row wave tiles once they make a work-group for every other CU; below that eight waves share a reduction, on tiles of 32 rows, or of 16
 // while each of those has a CU to itself: half the products (a wave's 64 on K = 1024 take 1.9 us of the matrix unit) and half the
-// loads of a work-group.  20 rows, K = 256 and 1024 in turn: 6.4 -> 5.3 us a launch.
+// loads of a work-group.  20 rows, K = 256 and 1024 in turn: 6.4 -> 5.3 us a launch.  Up to 16 rows always: a 32-row tile has the same
+// work-groups there and rows that are not there in its second half (16 rows, feed-forward and vocabulary of nine times the inputs, 512 / 768
+// inputs: 132.6 / 170.0 us a two-layer step with 32-row tiles, 127.8 / 163.5 with 16-row ones).
 static bool f32_large(int M, int N, bool glu) {
     const int f = glu ? 64 : 256;
     return (long long)((M + 63) / 64) * ((N + f - 1) / f) >= 128;
@@ -1408,7 +1410,7 @@ static hipError_t launch_f32(const float* A, const float* W, float* out, int M, 
         const bool vec = K % 4 == 0;
         if (f32_large(M, N, GLU))
             return vec ? launch(gemm_f32_kernel<4, NTB, 1, 4, FORM, true, false>, 64, FB, 256) : launch(gemm_f32_kernel<4, NTB, 1, 4, FORM, false, false>, 64, FB, 256);
-        if (low) return vec ? launch(gemm_f32_kernel<1, NTS, 8, 8, FORM, true, false>, 16, FS, 512) : launch(gemm_f32_kernel<1, NTS, 8, 8, FORM, false, false>, 16, FS, 512);
+        if (low || M <= 16) return vec ? launch(gemm_f32_kernel<1, NTS, 8, 8, FORM, true, false>, 16, FS, 512) : launch(gemm_f32_kernel<1, NTS, 8, 8, FORM, false, false>, 16, FS, 512);
         return vec ? launch(gemm_f32_kernel<2, NTS, 8, 8, FORM, true, false>, 32, FS, 512) : launch(gemm_f32_kernel<2, NTS, 8, 8, FORM, false, false>, 32, FS, 512);
     }
 }

@@ -46,3 +46,21 @@ def test_fp32_step_where_norms_and_rotary_ride_in_the_projections(batch, k, hd, 
     err, exempt, diverged = compare_step(r, g, "fp32", k)
     assert err < LOGIT_TOL["fp32"] and len(diverged) <= 1
     case.close()
+
+
+@pytest.mark.parametrize("batch,k,hd,d,ff,vocab", [
+    (1, 0, 64, 64, 4097, 64),         # one row; one feature more in gate/up than a CU a tile
+    (4, 3, 64, 132, 4112, 4097),      # 16 rows; gate/up and the vocabulary just beyond that line
+    (4, 3, 64, 68, 4103, 64),         # down over 4103 inputs: no whole 16-byte pieces
+    (17, 0, 64, 64, 4097, 4097),      # 17 rows: 32-row tiles beyond the line
+])
+def test_fp32_step_of_few_rows_over_many_features(batch, k, hd, d, ff, vocab):
+    shape = W.Shape("f32-wide", 2, d, 4, 2, hd, ff, vocab, dtype="fp32", rope_theta=1e4, batch=batch, k=k, n_chains=1, seed=37)
+    case = Case(shape, np.random.default_rng(11).integers(0, 70, size=batch), verify_mode=OV.STOCHASTIC, sample_mode=OV.SAMPLE_EXP_RACE)
+    x0 = W.make_tokens((batch,), vocab, shape.seed, "x0")
+    q = W.make_random_q((batch, 1, k), vocab, 1.0, shape.seed) if k else None
+    drafts = W.sample_from(q, shape.seed).numpy() if k else np.zeros((batch, 1, 0), dtype=np.int64)
+    r, g = case.step(x0, drafts, q, W.make_uniforms((batch, 1, k + 1), shape.seed))
+    err, exempt, diverged = compare_step(r, g, "fp32", k)
+    assert err < LOGIT_TOL["fp32"] and len(diverged) <= 1
+    case.close()
