@@ -1144,8 +1144,10 @@ hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, i
 // fp32 path (small models): v_mfma_f32_16x16x4_f32, operands straight from global memory.  A wave holds MT x NT tiles of
 // 16 rows x 16 features; lane 16 g + r of an operand tile loads four consecutive k (4 g .. 4 g + 3) of its row r in one
 // 16-byte piece and feeds them to four MFMAs, the reduction index of an MFMA being only a label as long as both operands
-// agree on it.  D groups of 32 k are in flight (four where a CU holds one tile).  KW waves of a work-group share the reduction (each takes every KW-th group
-// of 32 k) and add their tiles up in LDS; the other waves of the work-group have tiles of their own.
+// agree on it.  Two groups of 16 k are in flight.  KW waves of a work-group share the reduction (each takes every KW-th group of 32 k)
+// and add their tiles up in LDS; the other waves of the work-group have tiles of their own.  (With four groups of 32 k in flight, all of a
+// wave's share up to K = 1024, the code is twice as long and every launch slower: 16 rows, two layers of 512 / 768 / 1024 inputs 98.1 / 118.2 /
+// 140.5 us a step against 95.7 / 112.1 / 134.5, 20 rows 99.7 / 123.5 / 145.2 against 97.0 / 116.1 / 138.5.)
 // What bounds it at the few rows of a small model's step is one chain of load latencies, so the reduction is spread over
 // eight waves: 20 rows, K = 256..1024: 38 us with a scalar 32 x 32 tile per work-group (one FMA per 1.25 LDS reads, 24-64
 // work-groups, K walked serially), 5 us now.  Many rows take 64 x 64 tiles per wave.
@@ -1161,7 +1163,6 @@ template <int MT, int NT, int KW, int WAVES, int FORM, bool VEC, bool NORM>
 __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, float* __restrict__ out,
                                                               int M, int N, int K, int tiles_m, int add, F32Norm norm, RopeAppend rope) {
     constexpr int TILES = WAVES / KW;                      // wave tiles per work-group, side by side along the features
-    constexpr int D = MT == 1 ? 4 : 1;
     static_assert(TILES == 1 || KW == 1, "the exchange area holds one wave tile");
     static_assert((FORM == kF32Qkv || NORM) ? KW > 1 && VEC : true, "fused forms: small tiles, whole pieces");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1193,23 +1194,19 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
         }
         return v;
     };
-    floatx4 a[D][2][MT], w[D][2][NT], gain[D][2];
-    auto load_groups = [&](int k0) {
+    floatx4 a[2][MT], w[2][NT], gain[2];
+    auto load_group = [&](int k0) {
 #pragma unroll
-        for (int s = 0; s < D; ++s)
-            if (k0 + s * 32 * KW < K) {
+        for (int u = 0; u < 2; ++u) {
+            const int k = k0 + 16 * u + 4 * g;
+            if (NORM) gain[u] = load(norm.gain, k);
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int k = k0 + s * 32 * KW + 16 * u + 4 * g;
-                    if (NORM) gain[s][u] = load(norm.gain, k);
+            for (int j = 0; j < MT; ++j) a[u][j] = load(a_row[j], k);
 #pragma unroll
-                    for (int j = 0; j < MT; ++j) a[s][u][j] = load(a_row[j], k);
-#pragma unroll
-                    for (int i = 0; i < NT; ++i) w[s][u][i] = load(w_row[i], k);
-                }
-            }
+            for (int i = 0; i < NT; ++i) w[u][i] = load(w_row[i], k);
+        }
     };
-    load_groups(kw * 32);
+    load_group(kw * 32);
     // what the wave that adds up row tile kw needs besides, requested with the rest
     const int my_row = min(m0 + 16 * kw + r, M - 1);
     floatx4 before[FORM == kF32Plain ? NT : 1], cs0, cs1;
@@ -1256,28 +1253,24 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
 #pragma unroll
         for (int j = 0; j < MT; ++j) scale[j] = scales[16 * j + r];
     }
-    for (int k0 = kw * 32; k0 < K; k0 += 32 * KW * D) {
-        if (k0 != kw * 32) load_groups(k0);
+    for (int k0 = kw * 32; k0 < K; k0 += 32 * KW) {
+        if (k0 != kw * 32) load_group(k0);
 #pragma unroll
-        for (int s = 0; s < D; ++s)
-            if (k0 + s * 32 * KW < K) {
+        for (int u = 0; u < 2; ++u) {
+            if (NORM) {
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    if (NORM) {
+                for (int j = 0; j < MT; ++j)
 #pragma unroll
-                        for (int j = 0; j < MT; ++j)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) a[s][u][j][e] = a[s][u][j][e] * scale[j] * gain[s][u][e];
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int i = 0; i < NT; ++i)
-#pragma unroll
-                            for (int j = 0; j < MT; ++j)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][u][i][e], a[s][u][j][e], acc[i][j], 0, 0, 0);
-                }
+                    for (int e = 0; e < 4; ++e) a[u][j][e] = a[u][j][e] * scale[j] * gain[u][e];
             }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+#pragma unroll
+                    for (int j = 0; j < MT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][e], a[u][j][e], acc[i][j], 0, 0, 0);
+        }
     }
     auto put = [&](int m, int n, floatx4 v) {              // four features of a row
         if (m >= M) return;
