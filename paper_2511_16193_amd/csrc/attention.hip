@@ -821,11 +821,14 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // its weight is marked below zero and its V, which may hold anything, is not multiplied; only tiles that hold such keys are
 // looked at for it (in all of them it cost 4 to 8 %; so, the fp32 prefill 1 % and the steps nothing).  (With a lane per key
 // holding all D accumulators, V element by element and D wave reductions at the end, the step of 20 rows with 132 keys took 43 us
-// a layer; 5.7 us now.)  A row's cached length comes with its other descriptions, and the first tile of V is requested before the
-// softmax: one read less in the chain that a small step's launch consists of.
+// a layer; 6.2 us now.)  A row's cached length comes with its other descriptions, and with 64 dimensions, where a group takes two of a
+// chunk's tiles, the first tile of V is requested before the softmax: one read less in the chain that a small step's launch consists of.
+// With 128 it is not: two layers, 16 rows of 128 / 700 / 2000 keys 163.6 / 184.7 / 238.7 us a step, requested ahead 172.0 / 207.5 / 298.0; 64
+// dimensions, 20 rows of 128 / 1500 keys 76.4 / 109.3 against 76.2 / 111.5 without.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float scale) {
     constexpr int CK = 256, GROUPS = 256 / D, EP = 16 / (int)sizeof(T);
+    constexpr bool AHEAD = D == 64;
     const int t_out = blockIdx.x, t = a.last_of ? a.last_of[t_out * kReqInts] + a.last_of[t_out * kReqInts + 1] - 1 : t_out, h = blockIdx.y, tid = threadIdx.x;
     const int4 info = reinterpret_cast<const int4*>(a.row_info)[t];
     const int seq = info.x, j = info.y;
@@ -873,8 +876,10 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
             s *= scale;
         }
         float v[4][8];
-        if (c0 + grp * TILE_KEYS < end) load_v(c0 + grp * TILE_KEYS, v);        // on its way during the softmax
-        __builtin_amdgcn_sched_barrier(0);
+        if (AHEAD) {
+            if (c0 + grp * TILE_KEYS < end) load_v(c0 + grp * TILE_KEYS, v);    // on its way during the softmax
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const float mw = wave_max(s);
         if ((tid & 63) == 0) red[tid >> 6] = mw;
         __syncthreads();
@@ -897,7 +902,7 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
                 }
         };
         for (int tile = grp; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) {
-            if (tile != grp) load_v(c0 + tile * TILE_KEYS, v);
+            if (!AHEAD || tile != grp) load_v(c0 + tile * TILE_KEYS, v);
             if (c0 + (tile + 1) * TILE_KEYS <= all_seen) weigh(tile, v, std::false_type{});      // nothing in it is masked
             else weigh(tile, v, std::true_type{});
         }

@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
     (1, 0, 1, 64, 128, 333, 1001, 0, 0),        # one row, reductions of 333 and vocabularies of 1001: no whole 16-byte pieces
     (4, 3, 1, 64, 252, 64, 515, 254, 258),      # 16 rows; contexts that end around a chunk of 256 keys
     (3, 5, 2, 128, 128, 1024, 640, 30, 700),    # 33 rows; several chunks, two chains, head_dim 128
+    (6, 2, 1, 128, 128, 64, 515, 250, 262),     # head_dim 128: contexts that end around a chunk of 256 keys
+    (6, 2, 1, 128, 128, 64, 515, 506, 546),     # and around two, in the first tiles of the third
     (220, 4, 1, 64, 64, 128, 2053, 1, 40),      # 1100 rows: 64-row tiles per wave, remainders in rows and features
 ])
 def test_fp32_step(batch, k, chains, hd, d, ff, vocab, lo, hi):
