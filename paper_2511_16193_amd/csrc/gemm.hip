@@ -1376,9 +1376,11 @@ static bool f32_large(int M, int N, bool glu) {
 static bool f32_low(int M, int N, int feats) { return (long long)((M + 15) / 16) * ((N + feats - 1) / feats) <= 256; }
 
 // Where the norm and what follows QKV ride in the projection: 16-row tiles only, since every work-group goes over its rows a second time
-// and more work-groups than CUs would do so in turn.  us of a two-layer step, launches of their own against fused, without that line: 256
-// inputs at 60 / 160 / 320 / 640 rows 99 / 118 / 154 / 230 against 90 / 115 / 156 / 238, 512 at 20 / 160 116 / 221 against 112 / 243, 1024 at 1 / 20 / 160
-// 146 / 166 / 504 against 143 / 170 / 526.  Longer rows, of which a work-group would read 16 one after the other, keep the launches.
+// and more work-groups than CUs would do so in turn (without that line 256 inputs at 320 / 640 rows 154 / 230 us a two-layer step with launches
+// of their own against 156 / 238 fused, 512 at 160 221 against 243).  Within it, launches of their own against fused at 1 / 5 / 10 / 16 / 20 / 32 / 48 rows: 512
+// inputs 91 / 96 / 98 / 101 / 103 / 103 / 108 against 85 / 89 / 93 / 95 / 97 / 98 / 104, 768 inputs 105 / 107 / 111 / 115 / 119 / 122 / 139 against 100 / 104 / 108 /
+// 112 / 117 / 120 / 136, 1024 inputs 123 / 125 / 135 / 135 / 140 / 142 / 163 against 119 / 123 / 128 / 134 / 138 / 141 / 158.  Longer rows, of which a
+// work-group would read 16 one after the other, keep the launches: the gain is down to 1 us in 1024.
 bool gemm_f32_fuses(int M, int N, int K, F32Form form) {
     return K % 4 == 0 && K <= 1024 && f32_low(M, N, form == kF32Qkv ? 32 : 16);
 }
