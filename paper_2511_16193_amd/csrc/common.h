@@ -35,6 +35,11 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
 // write-backs.  For stores that fill whole 128-byte lines at once, or whole halves that are put together before they leave; the pieces of 8
 // and 16 bytes of a packed row do not (the norm's operands so written: 24 -> 41 us at 2304 rows).
 template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
+// Few rows leave little behind, and the launch that reads it, all of it one chain of latencies, does better to find it in L2 (after streamed
+// planes the norm of five rows takes 4.8 us for 4.1, rotary 7.7 for 6.1).  The line is where steps are level, ordinary against streamed stores at 5 /
+// 20 / 49 / 65 / 100 rows: 1024 wide, 12 layers 608 / 620 / 685 / 753 / 817 against 643 / 648 / 701 / 765 / 811 us, 2048 wide, 4 layers 286 / 299 / 346 / 378 / 408 against
+// 292 / 305 / 346 / 375 / 402, 3584 wide, 3 layers 519 / 549 / 615 / 651 / 695 against 524 / 549 / 596 / 624 / 676.
+__host__ __device__ __forceinline__ bool leaves_stream(int64_t rows, int width) { return rows * width >= 96 * 1024; }
 
 // What is read once in a launch, and by one work-group only, read as a stream: such lines give way first in L2 and leave it to what is shared.
 template <typename T> __device__ __forceinline__ T load_stream(const T* p) { return __builtin_nontemporal_load(p); }
@@ -52,7 +57,10 @@ template <> struct Store<float> {
     static __device__ __forceinline__ void store4(float* p, const float* v) {      // p 16-byte aligned
         *reinterpret_cast<floatx4*>(p) = floatx4{v[0], v[1], v[2], v[3]};
     }
-    static __device__ __forceinline__ void stream4(float* p, const float* v) { store_stream(reinterpret_cast<floatx4*>(p), floatx4{v[0], v[1], v[2], v[3]}); }
+    static __device__ __forceinline__ void stream4(float* p, const float* v, bool stream) {
+        if (stream) store_stream(reinterpret_cast<floatx4*>(p), floatx4{v[0], v[1], v[2], v[3]});
+        else store4(p, v);
+    }
 };
 template <> struct Store<bf16_t> {
     static __device__ __forceinline__ float load(const bf16_t* p) { return bf2f(*p); }
@@ -65,8 +73,9 @@ template <> struct Store<bf16_t> {
     static __device__ __forceinline__ void store4(bf16_t* p, const float* v) {     // p 8-byte aligned
         *reinterpret_cast<u32x2*>(p) = u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
     }
-    static __device__ __forceinline__ void stream4(bf16_t* p, const float* v) {
-        store_stream(reinterpret_cast<u32x2*>(p), u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])});
+    static __device__ __forceinline__ void stream4(bf16_t* p, const float* v, bool stream) {
+        if (stream) store_stream(reinterpret_cast<u32x2*>(p), u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])});
+        else store4(p, v);
     }
 };
 

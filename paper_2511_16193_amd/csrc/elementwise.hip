@@ -83,6 +83,7 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
     const int t_out = xcd_remap(blockIdx.x, gridDim.x);
     const int t = last.of ? last.of[t_out * kReqInts] + last.of[t_out * kReqInts + 1] - 1 : t_out;
     const int ta = last.dense ? t_out : t;               // row of what is added
+    const bool stream = leaves_stream(gridDim.x, d);
     const int nq = d >> 2;                               // float4 pieces per row
     floatx4* hr = reinterpret_cast<floatx4*>(h + (int64_t)t * d);
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -146,7 +147,10 @@ __global__ __launch_bounds__(NTH) void add_rmsnorm_kernel(float* __restrict__ h,
     for (int v = 0; v < NV; ++v) {
         const int i = threadIdx.x + v * NTH;
         if (i < nq) {
-            if ((S > 0 || inv) && (!last.of || last.dense)) store_stream(hr + i, x[v]);
+            if ((S > 0 || inv) && (!last.of || last.dense)) {
+                if (stream) store_stream(hr + i, x[v]);
+                else hr[i] = x[v];
+            }
             ss = fmaf(x[v][0], x[v][0], ss);
             ss = fmaf(x[v][1], x[v][1], ss);
             ss = fmaf(x[v][2], x[v][2], ss);
@@ -220,8 +224,9 @@ __global__ __launch_bounds__(256) void rope_append_vec_kernel(RopeAppend p) {
         }
         if (head < p.Hq) {
             T* q = reinterpret_cast<T*>(p.q_out) + ((int64_t)t * p.Hq + head) * hd;
-            Store<T>::stream4(q + i, o1);
-            Store<T>::stream4(q + i + half, o2);
+            const bool stream = leaves_stream(p.T, p.Hq * hd);
+            Store<T>::stream4(q + i, o1, stream);
+            Store<T>::stream4(q + i + half, o2, stream);
         } else {
             const int kh = head - p.Hq;
             Store<T>::store4(pool + kv_k_index(p.geom, p.layer, page, kh, tok, i), o1);

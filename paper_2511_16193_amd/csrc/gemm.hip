@@ -137,7 +137,7 @@ typedef __attribute__((ext_vector_type(16))) float floatx16;
 // reads, PD k-slices ahead, with no LDS and no barrier on that path.  Only the activations, which every
 // wave needs, go through LDS: KA 16-wide slices of all MT 32-token tiles per fill (packed order too, so
 // a fill is a handful of contiguous 1 KB copies), double buffered, one barrier per fill.
-template <int MT, int NT, int KA, int PD, bool GLU, bool STREAM>
+template <int MT, int NT, int KA, int PD, bool GLU, bool STREAM, bool LEAVE>
 __device__ __forceinline__ void gemm_bf16_ws_body(
     const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
     int M, int N, int K, int k_per_split, int splits, int tiles_m, int tiles_n, int tn0, int block_id) {
@@ -335,7 +335,7 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
         return;
     }
     // acc[i][j][4 q + r] <-> row m0 + 32 j + 8 q + 4 lg + r, feature n0 + 32 (wave NT + i) + l32
-    // A half wave fills a line of 128 bytes: streamed, so that the next kernel's loads do not push them out of L2 first (LM head of 96 rows, 58 MB of
+    // A half wave fills a line of 128 bytes: streamed (LEAVE; where leaves_stream says so), so that the next kernel's loads do not push them out of L2 first (LM head of 96 rows, 58 MB of
     // logits, 224 -> 213 us; QKV and O planes of 96 rows 12.5 + 10.5 -> 12.1 + 9.9, the attention between them 162 -> 160.5, norm and rotary + 0.4 and + 0.2).
     // The tall and the strip kernel write half lines, which as streams cost the next norm more than they save.
     float* dst = out + (int64_t)sp * M * N;
@@ -349,7 +349,9 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int m = m0 + j * 32 + 8 * q + 4 * lg + r;
-                    if (m < M) store_stream(dst + (int64_t)m * N + n, (float)acc[i][j][4 * q + r]);
+                    if (m >= M) continue;
+                    if (LEAVE) store_stream(dst + (int64_t)m * N + n, (float)acc[i][j][4 * q + r]);
+                    else dst[(int64_t)m * N + n] = acc[i][j][4 * q + r];
                 }
     }
 }
@@ -357,11 +359,11 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
 // Two work-groups share a CU where the accumulator tile leaves room (up to 96 rows x 256 features, or 128-feature
 // strips): more, smaller work-groups resident at once, which evens out a launch whose work-group count is not a
 // multiple of the 256 CUs.
-template <int MT, int NT, int KA, int PD, bool GLU = false, bool STREAM = false>
+template <int MT, int NT, int KA, int PD, bool GLU = false, bool STREAM = false, bool LEAVE = false>
 __global__ __launch_bounds__(256, (NT == 1 || MT <= 3) ? 2 : 1) void gemm_bf16_ws_kernel(
     const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
     int M, int N, int K, int k_per_split, int splits, int tiles_m, int tiles_n, int tn0) {
-    gemm_bf16_ws_body<MT, NT, KA, PD, GLU, STREAM>(Ap, Wp, out, M, N, K, k_per_split, splits, tiles_m, tiles_n, tn0, blockIdx.x);
+    gemm_bf16_ws_body<MT, NT, KA, PD, GLU, STREAM, LEAVE>(Ap, Wp, out, M, N, K, k_per_split, splits, tiles_m, tiles_n, tn0, blockIdx.x);
 }
 
 // Gate/up projection with a short last round: the first n_main work-groups are 160-row ones over the 128-feature
@@ -377,9 +379,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ws_glu_mixed_kernel(
     int tiles_m, int strips_main, int tiles_m2, int strips_tail) {
     const int n_main = tiles_m * strips_main;
     if ((int)blockIdx.x < n_main)
-        gemm_bf16_ws_body<5, 2, 8, 8, true, false>(Ap, Wp, out, M, N, K, K, 1, tiles_m, strips_main, 0, blockIdx.x);
+        gemm_bf16_ws_body<5, 2, 8, 8, true, false, false>(Ap, Wp, out, M, N, K, K, 1, tiles_m, strips_main, 0, blockIdx.x);
     else
-        gemm_bf16_ws_body<2, 1, 8, 8, true, false>(Ap, Wp, out, M, N, K, K, 1, tiles_m2, 2 * strips_tail, 2 * strips_main, blockIdx.x - n_main);
+        gemm_bf16_ws_body<2, 1, 8, 8, true, false, false>(Ap, Wp, out, M, N, K, K, 1, tiles_m2, 2 * strips_tail, 2 * strips_main, blockIdx.x - n_main);
 }
 
 // ---- third bf16 kernel: tall tiles, 64 RW rows x 256 features per work-group, both operands through LDS ----
@@ -928,9 +930,9 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t
                     if (fs < F / 16) {
                         u32x2* dst = reinterpret_cast<u32x2*>(act + ((int64_t)(x >> 1) * (F / 16) + fs) * 512 + ((lg >> 1) * 32 + (x & 1) * 16 + l16) * 8 + 4 * (lg & 1));
                         const u32x2 pk = {pack2bf(r[0], r[1]), pack2bf(r[2], r[3])};
-                        // streamed up to 160 rows (the down projection of 96 / 147 rows 36.0 -> 31.4 / 68.0 -> 60.6 us); of 320 rows it would
-                        // take longer, 52.8 -> 54.8
-                        if constexpr (W == 4) store_stream(dst, pk);
+                        // streamed from 33 to 160 rows (the down projection of 96 / 147 rows 36.0 -> 31.4 / 68.0 -> 60.6 us); of 320 rows it would
+                        // take longer, 52.8 -> 54.8.  By the form, not by leaves_stream: with a branch here 65 to 100 rows lose 1 to 2 % of a step
+                        if constexpr (W == 4 && RS > 1) store_stream(dst, pk);
                         else *dst = pk;
                     }
                 }
@@ -1052,10 +1054,15 @@ static hipError_t launch_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int 
         hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(256), 0, st, Ap, Wp,
                            out, M, N, K, K / splits, splits, tiles_m, tiles_n, 0);
     };
+    auto form = [&](auto stream) {
+        // (a branch in the kernel makes its end twice as long: 3.65 -> 3.9 us a launch of five rows)
+        if (leaves_stream(M, N < K ? N : K)) launch(gemm_bf16_ws_kernel<MT, NT, KA, PD, false, decltype(stream)::value, true>);
+        else launch(gemm_bf16_ws_kernel<MT, NT, KA, PD, false, decltype(stream)::value, false>);
+    };
     // one row tile: the weights are read once, as a stream (LM heads of 152 thousand features at 5 / 20 / 42 / 96 rows 193 / 122 / 207 / 219 -> 168 / 107 /
     // 190 / 202 us; QKV and O of 96 rows level).  Several: they find each other's in L2 (O of 5120 x 5120 at 800 rows, so read, 66.5 -> 72.6)
-    if (tiles_m == 1) launch(gemm_bf16_ws_kernel<MT, NT, KA, PD, false, true>);
-    else launch(gemm_bf16_ws_kernel<MT, NT, KA, PD>);
+    if (tiles_m == 1) form(std::true_type{});
+    else form(std::false_type{});
     return hipGetLastError();
 }
 
