@@ -821,14 +821,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // its weight is marked below zero and its V, which may hold anything, is not multiplied; only tiles that hold such keys are
 // looked at for it (in all of them it cost 4 to 8 %; so, the fp32 prefill 1 % and the steps nothing).  (With a lane per key
 // holding all D accumulators, V element by element and D wave reductions at the end, the step of 20 rows with 132 keys took 43 us
-// a layer; 6.2 us now.)  A row's cached length comes with its other descriptions, and with 64 dimensions, where a group takes two of a
-// chunk's tiles, the first tile of V is requested before the softmax: one read less in the chain that a small step's launch consists of.
-// With 128 it is not: two layers, 16 rows of 128 / 700 / 2000 keys 163.6 / 184.7 / 238.7 us a step, requested ahead 172.0 / 207.5 / 298.0; 64
-// dimensions, 20 rows of 128 / 1500 keys 76.4 / 109.3 against 76.2 / 111.5 without.
+// a layer; 6.2 us now.)  A row's cached length comes with its other descriptions, and in fp32 with 64 dimensions, where a group takes two of
+// a chunk's tiles, the first tile of V is requested before the softmax: one read less in the chain that a small step's launch consists of (two layers, 20
+// rows of 128 / 1500 / 4000 keys 76.4 / 108.2 / 167.7 us a step, 75.6 / 108.4 / 172.3 without).  Not otherwise, us a step with that request against without:
+// fp32, 128 dimensions, two layers, 16 rows of 128 / 700 / 2000 keys 172.0 / 207.5 / 298.0 against 165.2 / 182.6 / 233.8; bf16, 64 dimensions, three layers of
+// 32 heads, 80 rows of 600 / 3000 keys 360 / 715 against 353 / 684, 240 rows of 600 654 against 636 (but of 3000 2268 against 2486).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float scale) {
     constexpr int CK = 256, GROUPS = 256 / D, EP = 16 / (int)sizeof(T);
-    constexpr bool AHEAD = D == 64;
+    constexpr bool AHEAD = D == 64 && sizeof(T) == 4;
     const int t_out = blockIdx.x, t = a.last_of ? a.last_of[t_out * kReqInts] + a.last_of[t_out * kReqInts + 1] - 1 : t_out, h = blockIdx.y, tid = threadIdx.x;
     const int4 info = reinterpret_cast<const int4*>(a.row_info)[t];
     const int seq = info.x, j = info.y;
@@ -891,7 +892,8 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
         acc *= alpha;
         m = m_new;
         __syncthreads();
-        auto weigh = [&](int tile, const float (&v)[4][8], auto masked) __attribute__((always_inline)) {
+        auto weigh = [&](int tile, auto masked) __attribute__((always_inline)) {
+            if (!AHEAD || tile != grp) load_v(c0 + tile * TILE_KEYS, v);
 #pragma unroll
             for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -901,11 +903,9 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
                     acc = decltype(masked)::value && w1 < 0.f ? acc : fmaf(w1, v[g][4 + e], acc);
                 }
         };
-        for (int tile = grp; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) {
-            if (!AHEAD || tile != grp) load_v(c0 + tile * TILE_KEYS, v);
-            if (c0 + (tile + 1) * TILE_KEYS <= all_seen) weigh(tile, v, std::false_type{});      // nothing in it is masked
-            else weigh(tile, v, std::true_type{});
-        }
+        int tile = grp;                                     // first the tiles in which nothing is masked
+        for (; tile < CK / TILE_KEYS && c0 + (tile + 1) * TILE_KEYS <= all_seen; tile += GROUPS) weigh(tile, std::false_type{});
+        for (; tile < CK / TILE_KEYS && c0 + tile * TILE_KEYS < end; tile += GROUPS) weigh(tile, std::true_type{});
         __syncthreads();
     }
     acc_sh[grp][dim] = acc;

@@ -58,3 +58,33 @@ def test_masked_entries_do_not_reach_a_row(dtype, hd, hq, hkv, page, chains, k, 
     seen = got[1][:, [k] + list(range(k + 1, 2 * k + 1))]
     assert not bool(torch.isfinite(seen).any())             # a row that sees such an entry shows it
     ver.close()
+
+
+@pytest.mark.parametrize("dtype,hd,hq,hkv,page,lens", [
+    ("fp32", 64, 4, 2, 64, (127, 253)),   # the rows' own keys run across the end of a tile and of a chunk of 256 keys
+    ("fp32", 128, 4, 4, 32, (253, 510)),
+    ("bf16", 64, 8, 2, 64, (253, 510)),
+    ("bf16", 128, 4, 2, 96, (28, 766)),   # inside the first tile; around three chunks
+])
+def test_generic_attention_around_the_ends_of_tiles_and_chunks(dtype, hd, hq, hkv, page, lens):
+    k, n, cap = 5, 6, 800
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ver = verifier(dtype, hd, hq, hkv, 1, page=page, pages=-(-cap // page), k=k, chains=1)
+    g = torch.Generator().manual_seed(5)
+    kv = [torch.randn((2, cap, hkv, hd), generator=g).to(dt) for _ in lens]
+    q = torch.randn((2 * n, hq, hd), generator=g).to(dt)
+    for b, L in enumerate(lens):
+        ver.seq_add(b, L + n)
+        ver.kv_write(b, 0, 0, kv[b][0, : L + n].contiguous().to(DEV), kv[b][1, : L + n].contiguous().to(DEV))
+        ver.seq_set_len(b, L)
+    got = ver.op_attention([0, 1], n, k, 0, q.to(DEV)).view(2, n, hq, hd).double().cpu()
+    for b, L in enumerate(lens):
+        for j in range(n):
+            x = kv[b][:, : L + j + 1].double().repeat_interleave(hq // hkv, dim=2)
+            p = torch.softmax(torch.einsum("hd,khd->hk", q.view(2, n, hq, hd)[b, j].double(), x[0]) / hd ** 0.5, dim=-1)
+            want = torch.einsum("hk,khd->hd", p, x[1])
+            # the output's own rounding (bf16 keeps 8 significant bits: half a unit of the last is 2^-8 of the value at most) and fp32 sums
+            # of some 800 keys, scores of magnitude ten among them
+            bound = (2.0 ** -8 * want.abs() if dtype == "bf16" else 0.0) + 2e-5 * torch.einsum("hk,khd->hd", p, x[1].abs())
+            assert bool(((got[b, j] - want).abs() <= bound).all()), (b, j)
+    ver.close()
