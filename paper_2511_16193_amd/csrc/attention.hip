@@ -53,9 +53,9 @@ __device__ __forceinline__ float max8(const floatx4& a, const floatx4& b) {
 // online softmax, PV, not skewed.  At these sizes the kernel runs at the rate the cache can be streamed at, and
 // inside a verification step it measured 3-14 % faster than the skewed kernel below (which is ahead once the
 // products dominate: four row tiles, or several row groups streaming the same keys).
-// A tile is read by this work-group only and as a stream (load_stream): 320 rows of 64 requests 131 -> 119 us a layer, 96 requests' single rows
+// ONCE: a tile is read by this work-group only, and from HBM: as a stream (load_stream): 320 rows of 64 requests 131 -> 119 us a layer, 96 requests' single rows
 // 164 -> 151, 640 rows beside 8 q heads a kv head 230 -> 210, five rows of one request 13.6 -> 13.0.
-template <int R>
+template <int R, bool ONCE>
 __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(AttnArgs a, float scale_log2e) {
     // work item = one piece of one request's keys, cut by the host from its upper bounds of the lengths.
     // Launch order: the kv heads of an item are neighbours, so the list's longest-first order holds chip-wide.
@@ -144,8 +144,9 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
             const bf16_t* vp = pool + uniform(vi + kb * 2048);
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
-                t.k[kb][kk] = load_stream(reinterpret_cast<const u32x4*>(kp + kk * 512 + lane_off));
-                t.v[kb * 4 + kk] = load_stream(reinterpret_cast<const u32x4*>(vp + kk * 512 + lane_off));
+                const u32x4 *ks = reinterpret_cast<const u32x4*>(kp + kk * 512 + lane_off), *vs = reinterpret_cast<const u32x4*>(vp + kk * 512 + lane_off);
+                t.k[kb][kk] = ONCE ? load_stream(ks) : *ks;
+                t.v[kb * 4 + kk] = ONCE ? load_stream(vs) : *vs;
             }
         }
     };
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 
 // R row tiles per work-group, W waves, D slots per wave for K and for V in the LDS ring (W * D * 16 KB of LDS).
 // Run as W = 2, D = 2: two work-groups share a CU.
-// ONCE: no other row group or item reads these keys, they come as a stream (load_stream; 63 rows of 256 requests 497 -> 445 us; with a second
+// ONCE: no other row group or item reads these keys, and they come from HBM: as a stream (load_stream; 63 rows of 256 requests 497 -> 445 us; with a second
 // row group to find them in L2 685 -> 703).
 // PT: bf16 terms the softmax weights are split into for the PV products.  With four row tiles (or several row
 // groups) this kernel is bound by its matrix products and the power they draw, and three quarters of them are PV
@@ -956,19 +957,20 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
             return hipGetLastError();
         };
         hipError_t e;
+        const bool once = a.cold && b.row_groups == 1 && !a.row_items;
         if (b.row_groups > 1 || R >= 4) {
             switch (R) {
-                case 1: e = launch_regs(attn_bf16_regs_kernel<1>, 1); break;
+                case 1: e = launch_regs(attn_bf16_regs_kernel<1, false>, 1); break;
                 case 2: e = launch(attn_bf16_kernel<2, 2, 2, 2>, 2, 2, 2); break;
                 case 3: e = launch(attn_bf16_kernel<3, 2, 2, 2>, 3, 2, 2); break;
                 default: e = a.row_items ? launch(attn_bf16_kernel<4, 2, 2, 3>, 4, 2, 2)
-                           : b.row_groups == 1 ? launch(attn_bf16_kernel<4, 2, 2, 2, true>, 4, 2, 2) : launch(attn_bf16_kernel<4, 2, 2, 2>, 4, 2, 2); break;
+                           : once ? launch(attn_bf16_kernel<4, 2, 2, 2, true>, 4, 2, 2) : launch(attn_bf16_kernel<4, 2, 2, 2>, 4, 2, 2); break;
             }
         } else {
             switch (R) {
-                case 1: e = launch_regs(attn_bf16_regs_kernel<1>, 1); break;
-                case 2: e = launch_regs(attn_bf16_regs_kernel<2>, 2); break;
-                default: e = launch_regs(attn_bf16_regs_kernel<3>, 3); break;
+                case 1: e = once ? launch_regs(attn_bf16_regs_kernel<1, true>, 1) : launch_regs(attn_bf16_regs_kernel<1, false>, 1); break;
+                case 2: e = once ? launch_regs(attn_bf16_regs_kernel<2, true>, 2) : launch_regs(attn_bf16_regs_kernel<2, false>, 2); break;
+                default: e = once ? launch_regs(attn_bf16_regs_kernel<3, true>, 3) : launch_regs(attn_bf16_regs_kernel<3, false>, 3); break;
             }
         }
         if (e != hipSuccess) return e;

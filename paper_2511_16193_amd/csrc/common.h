@@ -42,6 +42,11 @@ template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { 
 __host__ __device__ __forceinline__ bool leaves_stream(int64_t rows, int width) { return rows * width >= 96 * 1024; }
 
 // What is read once in a launch, and by one work-group only, read as a stream: such lines give way first in L2 and leave it to what is shared.
+// For what comes from HBM: a pass that reads less than kCacheBytes finds it in the chip's memory-side cache, where the one before left it, and
+// ordinary loads are the faster ones then ("cold" names passes that read more).  Steps of a 1024-wide model, 4 / 6 / 8 / 10 / 14 layers, 162 / 210 / 258 / 307 /
+// 403 MB of weights, 5 rows: 210 / 303 / 417 / 528 / 735 us with ordinary loads, 223 / 319 / 417 / 510 / 701 streamed; 4 layers and 49 / 196 / 786 MB of
+// cached keys and values (4 / 16 / 64 requests) 221 / 320 / 512 against 238 / 319 / 486.
+constexpr size_t kCacheBytes = (size_t)256 << 20;
 template <typename T> __device__ __forceinline__ T load_stream(const T* p) { return __builtin_nontemporal_load(p); }
 constexpr int kStreamLoad = 2;                              // the same hint in the cache-policy operand of the load builtins
 

@@ -338,6 +338,8 @@ struct sv_ctx {
     int n_work;                                           // attention work items staged for the current pass
     int n_last_work;                                      // prefill: items behind them that hold the last rows asked for; -1: no room for the list
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
+    size_t weight_bytes, expert_bytes;                    // of all layers and the LM head; of one expert in all layers
+    bool cold;                                            // what the current pass reads once comes from HBM (see kCacheBytes)
     int gemm_variant;                                     // -1 = choose per shape
     int gemm_tile;                                        // packed projections: -1 = by the plans, 0 = weight-streaming kernel only, 1 = tall tiles wherever the shape allows
     struct PlannedShape { int M, N, K; bool allow_split, direct; WsPlan plan; };
@@ -512,6 +514,12 @@ extern "C" int verify_init(const sv_model* m, const sv_weights* w, const sv_runt
     c->seqs.resize(r->max_seqs);
     c->free_pages.resize(r->num_pages);
     for (int i = 0; i < r->num_pages; ++i) c->free_pages[i] = r->num_pages - 1 - i;   // pop_back yields 0,1,2..
+    {
+        const size_t es = m->dtype == SV_BF16 ? 2 : 4, layers = m->n_layers, d = m->d_model;
+        c->expert_bytes = m->n_experts > 0 ? es * layers * 3 * m->d_expert * d : 0;
+        c->weight_bytes = es * (layers * (2 * (size_t)(m->n_q_heads + m->n_kv_heads) * m->head_dim + (m->n_experts > 0 ? 0 : 3 * (size_t)m->d_ff)) * d + (size_t)m->vocab * d);
+    }
+    c->cold = false;
     c->ring_pos = 0;
     c->gemm_variant = -1;
     c->gemm_tile = -1;
@@ -835,6 +843,16 @@ static void build_work(sv_ctx* c, const Pass& ps, int32_t* req, int32_t* work) {
         if (it.last) memcpy(work + at++ * kItemInts, it.v, sizeof(it.v));
 }
 
+// Does the pass read more than the memory-side cache holds?  (All weights, experts as many as its rows can choose, all cached keys and values.
+// A captured step keeps what held when it was captured: the results are the same bits either way.)
+static bool reads_past_cache(const sv_ctx* c, const Pass& ps) {
+    const sv_model& m = c->model;
+    const size_t token = (size_t)2 * m.n_kv_heads * m.head_dim * (m.dtype == SV_BF16 ? 2 : 4) * m.n_layers;
+    size_t bytes = c->weight_bytes + c->expert_bytes * std::min<long long>(m.n_experts, (long long)ps.T * m.top_k);
+    for (int b = 0; b < ps.B; ++b) bytes += token * (c->seqs[ps.rq[b].seq].len_ub + ps.rq[b].n);
+    return bytes > kCacheBytes;
+}
+
 // Make sure every request's sequence holds pages for its new rows; describe the pass (requests, attention work list,
 // new page-table entries) to the device in one copy.  Nothing changes if the pool cannot cover the whole batch.
 static int stage_pass(sv_ctx* c, const Pass& ps) {
@@ -867,6 +885,7 @@ static int stage_pass(sv_ctx* c, const Pass& ps) {
     }
     c->n_work = c->n_last_work = 0;
     c->pass_merge = false;
+    c->cold = reads_past_cache(c, ps);
     if (attn_mfma_ok(c->model.dtype, c->model.head_dim, c->rt.page_size, c->attn_generic,
                      ps.n == 0 ? 0 : c->model.n_q_heads / c->model.n_kv_heads * ps.n))
         build_work(c, ps, st + L.st_req, st + L.st_work);
@@ -937,9 +956,9 @@ static int gemm(sv_ctx* c, const void* A, const void* W, float* out, int M, int 
         if (c->packed) {
             const WsPlan p = planned(c, M, N, K, allow_split, direct_loads(W));
             *splits_out = p.splits;
-            if (p.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.strip, c->stream));
+            if (p.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.strip, c->cold, c->stream));
             else if (p.tall.n > 0) SV_HIP(c, gemm_bf16_tall((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, false, p.tall, c->stream));
-            else SV_HIP(c, gemm_bf16_ws((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, p.wide, c->stream, p.row_tiles));
+            else SV_HIP(c, gemm_bf16_ws((const bf16_t*)A, (const bf16_t*)W, out, M, N, K, p.splits, p.wide, c->cold, c->stream, p.row_tiles));
         } else {
             const int s = allow_split ? pick_splits(M, N, K) : 1;
             *splits_out = s;
@@ -1001,7 +1020,7 @@ static AttnArgs attn_args(const sv_ctx* c, const Pass& ps, int layer, const void
     aa.T = ps.T; aa.n_max = ps.n_max; aa.k = ps.k; aa.Hq = m.n_q_heads; aa.Hkv = m.n_kv_heads; aa.hd = m.head_dim; aa.dtype = m.dtype;
     aa.work = c->at<int32_t>(L.stage) + L.st_work; aa.n_work = c->n_work;
     aa.last_of = nullptr; aa.n_last = 0; aa.last_out = nullptr;
-    aa.row_items = ps.n == 0; aa.merge = c->pass_merge;
+    aa.row_items = ps.n == 0; aa.merge = c->pass_merge; aa.cold = c->cold;
     aa.n_work_dev = nullptr; aa.grid_items = 0;
     if (c->graph_launch_shape) {      // nothing in the launch may depend on the lengths
         aa.n_work_dev = c->at<int32_t>(L.stage);
@@ -1084,7 +1103,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         ma.live = c->at<int32_t>(L.moe_live); ma.tile_off = c->at<int32_t>(L.moe_off);
         ma.perm = c->at<int32_t>(L.moe_perm); ma.inv = c->at<int32_t>(L.moe_inv);
         ma.act = c->at<bf16_t>(L.moe_act); ma.y = c->at<float>(L.moe_y); ma.out = nullptr;   // combined by the next norm
-        ma.T = T; ma.d = d; ma.E = m.n_experts; ma.top_k = m.top_k; ma.F = m.d_expert;
+        ma.T = T; ma.d = d; ma.E = m.n_experts; ma.top_k = m.top_k; ma.F = m.d_expert; ma.cold = c->cold;
         ProfScope prof(c, SV_PROF_MOE);
         SV_HIP(c, moe_ffn(ma, st));
         pending = -1;
@@ -1095,7 +1114,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         ProfScope prof(c, SV_PROF_GEMM);
         const GateUp g = m.d_ff % 128 == 0 ? gate_up_launch(c, T, direct_loads(c->wgu[l])) : GateUp{};
         const bf16_t *ga = (const bf16_t*)a_norm, *gw = (const bf16_t*)c->wgu[l];
-        if (g.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.strip, st));
+        if (g.strip.tiles > 0) SV_HIP(c, gemm_bf16_strip(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.strip, c->cold, st));
         else if (g.tall.n > 0) SV_HIP(c, gemm_bf16_tall(ga, gw, c->at<float>(L.act), T, 2 * m.d_ff, d, 1, true, g.tall, st));
         else SV_HIP(c, gemm_bf16_ws_glu(ga, gw, c->at<bf16_t>(L.act), T, m.d_ff, d, st));
     } else if (f32) {
@@ -1330,6 +1349,8 @@ extern "C" int verify_step(sv_ctx* c, const sv_batch* bt, const int32_t* drafts,
 
 // -------------------------------------------------- single-operation entry points ---
 
+static bool op_cold(size_t weights) { return weights * sizeof(bf16_t) > kCacheBytes; }      // one projection again and again finds smaller weights in the cache
+
 extern "C" int sv_op_gemm_bf16(const void* A, const void* W, float* out, int M, int N, int K, int splits, int variant,
                                void* stream) {
     if (!A || !W || !out || M <= 0 || !gemm_bf16_shape_ok(N, K, splits) || !gemm_bf16_variant_ok(variant, N)) return SV_EINVAL;
@@ -1342,9 +1363,9 @@ extern "C" int sv_op_gemm_bf16_ws(const void* Ap, const void* Wp, float* out, in
     if (!Ap || !Wp || !out || M <= 0 || N <= 0 || K <= 0 || splits <= 0 || N % (wide ? 256 : 128) != 0 ||
         K % (64 * splits) != 0 || row_tiles < 0 || (row_tiles > 5 && row_tiles != 8) || (row_tiles == 8 && N % 256 != 0))
         return SV_EINVAL;
-    const bool tall = row_tiles == 8 && direct_loads(Ap) && direct_loads(Wp);      // (the other kernel's sums are the same)
+    const bool tall = row_tiles == 8 && direct_loads(Ap) && direct_loads(Wp), cold = op_cold((size_t)N * K);     // (the other kernel's sums are the same)
     const hipError_t e = tall ? gemm_bf16_tall((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, false, gemm_bf16_tall_256(M), (hipStream_t)stream)
-                                        : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, wide != 0, (hipStream_t)stream, row_tiles == 8 ? 0 : row_tiles);
+                                        : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, out, M, N, K, splits, wide != 0, cold, (hipStream_t)stream, row_tiles == 8 ? 0 : row_tiles);
     return e == hipSuccess ? SV_OK : SV_EHIP;
 }
 
@@ -1395,7 +1416,7 @@ extern "C" int sv_op_gemm_bf16_tall(const void* Ap, const void* Wp, void* out, i
     hipStream_t st = (hipStream_t)stream;
     auto weight_streaming = [&]() -> int {
         const hipError_t e = gated ? gemm_bf16_ws_glu((const bf16_t*)Ap, (const bf16_t*)Wp, (bf16_t*)out, M, N / 2, K, st)
-                                   : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, N % 256 == 0, st);
+                                   : gemm_bf16_ws((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, N % 256 == 0, op_cold((size_t)N * K), st);
         return e == hipSuccess ? SV_OK : SV_EHIP;
     };
     if (!tall) return gated ? weight_streaming() : SV_EINVAL;
@@ -1416,7 +1437,7 @@ extern "C" int sv_op_gemm_bf16_strip(const void* Ap, const void* Wp, void* out, 
         row_tiles == 9 || M > 32 * row_tiles || (features != 128 && features != 160 && features != 224) || !direct_loads(Ap) || !direct_loads(Wp))
         return SV_EINVAL;
     return gemm_bf16_strip((const bf16_t*)Ap, (const bf16_t*)Wp, (float*)out, M, N, K, splits, gated != 0, StripTile{row_tiles, features / 32},
-                           (hipStream_t)stream) == hipSuccess ? SV_OK : SV_EHIP;
+                           op_cold((size_t)N * K), (hipStream_t)stream) == hipSuccess ? SV_OK : SV_EHIP;
 }
 
 extern "C" int sv_op_pack_rows(const void* src, void* dst, int M, int K, void* stream) {
@@ -1493,6 +1514,7 @@ extern "C" int sv_op_moe_ffn(const void* a_packed, const void* w_router, const v
     ma.perm = reinterpret_cast<int32_t*>(ws + m.perm); ma.inv = reinterpret_cast<int32_t*>(ws + m.inv);
     ma.act = reinterpret_cast<bf16_t*>(ws + m.act); ma.y = reinterpret_cast<float*>(ws + m.y); ma.out = out;
     ma.T = T; ma.d = d; ma.E = E; ma.top_k = top_k; ma.F = F;
+    ma.cold = op_cold((size_t)3 * F * d * std::min<long long>(E, (long long)T * top_k));
     hipStream_t st = (hipStream_t)stream;
     if (moe_ffn(ma, st) != hipSuccess) return SV_EHIP;
     if (top_ids && hipMemcpyAsync(top_ids, ma.top_ids, sizeof(int32_t) * (size_t)T * top_k, hipMemcpyDeviceToDevice, st) != hipSuccess)

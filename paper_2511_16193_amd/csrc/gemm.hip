@@ -769,7 +769,7 @@ constexpr int strip_fills(int w, int rs, int fs) {        // fills in the ring: 
     return n < 6 ? n : 6;
 }
 
-template <bool GLU, int W, int RS, int FS>
+template <bool GLU, int W, int RS, int FS, bool STREAM>
 __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
                                                                  int M, int N, int K, int k_per_split, int splits) {
     extern __shared__ __attribute__((aligned(16))) unsigned char strip_lds[];   // NB fills; the exchange of the gated form
@@ -811,8 +811,8 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t
     auto request = [&](auto which, uint32_t base) __attribute__((always_inline)) {
         constexpr int Q = decltype(which)::value;
         // pieces Q W .. Q W + W - 1, one a wave: of rows, which every strip reads, or of weights, which only this one does and which come as a
-        // stream.  Eight waves, bound by their products, do not gain (320 rows: gate/up 85.6 -> 84.1, down 53.1 -> 56.5, LM head 319 -> 323)
-        constexpr bool weights = W == 4 && Q * W >= A_P, mixed = W == 4 && !weights && Q * W + W > A_P;
+        // stream (STREAM).  Eight waves, bound by their products, do not gain (320 rows: gate/up 85.6 -> 84.1, down 53.1 -> 56.5, LM head 319 -> 323)
+        constexpr bool weights = STREAM && Q * W >= A_P, mixed = STREAM && !weights && Q * W + W > A_P;
         if constexpr (Q < EACH) {
             const uint32_t to = base + (wave + W * Q) * 1024;
             if (mixed && wave + W * Q >= A_P) dma1<true>(src[Q], lane_off[Q], to);
@@ -985,7 +985,7 @@ StripPlan gemm_bf16_strip_plan(int M, int N, int K, int min_splits, int max_spli
 
 // plain: out [splits][M][N] fp32, N % 128 == 0.  gated: N = 2 F weight rows, out = packed bf16 [ceil(M/32)*32, F], F % 128 == 0,
 // splits == 1.  (K / splits) % 32 == 0.  One work-group holds the M rows in tiles of 32 (1 to 5, 6, 8 or 10 of them).
-hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const StripTile& s, hipStream_t st) {
+hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const StripTile& s, bool cold, hipStream_t st) {
     if (splits < 1 || K % splits != 0 || (K / splits) % 32 != 0 || N % (glu ? 256 : 128) != 0 || (glu && splits != 1) || M < 1 || M > 32 * s.tiles)
         return hipErrorInvalidValue;
     auto launch = [&](auto kern, int w, int rs, int fs) -> hipError_t {
@@ -999,10 +999,15 @@ hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M
     auto width = [&](auto g, auto w, auto rs) -> hipError_t {
         constexpr bool G = decltype(g)::value;
         constexpr int W = decltype(w)::value, RS = decltype(rs)::value;
+        auto form = [&](auto fs) -> hipError_t {
+            constexpr int FS = decltype(fs)::value;
+            if (W == 4 && cold) return launch(gemm_bf16_strip_kernel<G, W, RS, FS, W == 4>, W, RS, FS);
+            return launch(gemm_bf16_strip_kernel<G, W, RS, FS, false>, W, RS, FS);
+        };
         switch (s.fs) {
-            case 4: return launch(gemm_bf16_strip_kernel<G, W, RS, 4>, W, RS, 4);
-            case 5: return launch(gemm_bf16_strip_kernel<G, W, RS, 5>, W, RS, 5);
-            case 7: return launch(gemm_bf16_strip_kernel<G, W, RS, 7>, W, RS, 7);
+            case 4: return form(std::integral_constant<int, 4>{});
+            case 5: return form(std::integral_constant<int, 5>{});
+            case 7: return form(std::integral_constant<int, 7>{});
             default: return hipErrorInvalidValue;
         }
     };
@@ -1046,7 +1051,7 @@ hipError_t pack_rows(const bf16_t* src, bf16_t* dst, int M, int K, hipStream_t s
 }
 
 template <int MT, int NT, int KA, int PD>
-static hipError_t launch_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, hipStream_t st) {
+static hipError_t launch_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool cold, hipStream_t st) {
     constexpr int BM = 32 * MT, BN = 128 * NT;
     if (N % BN != 0 || (K / splits) % (16 * KA) != 0) return hipErrorInvalidValue;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
@@ -1061,7 +1066,7 @@ static hipError_t launch_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int 
     };
     // one row tile: the weights are read once, as a stream (LM heads of 152 thousand features at 5 / 20 / 42 / 96 rows 193 / 122 / 207 / 219 -> 168 / 107 /
     // 190 / 202 us; QKV and O of 96 rows level).  Several: they find each other's in L2 (O of 5120 x 5120 at 800 rows, so read, 66.5 -> 72.6)
-    if (tiles_m == 1) form(std::true_type{});
+    if (tiles_m == 1 && cold) form(std::true_type{});
     else form(std::false_type{});
     return hipGetLastError();
 }
@@ -1121,30 +1126,30 @@ int gemm_bf16_ws_row_tiles(int M) {
     return (tiles + groups - 1) / groups;
 }
 
-hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool wide,
+hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool wide, bool cold,
                         hipStream_t st, int row_tiles) {
     const bool long_fill = (K / splits) % 128 == 0;
     const int mt = row_tiles >= 1 && row_tiles <= 5 ? row_tiles : gemm_bf16_ws_row_tiles(M);
     if (!long_fill) {        // short fills (small models; many splits of a deep reduction at a few rows): narrow strips of
                              // one to four row tiles, else the five-tile form.  96 rows, down of the 7B shape in eight splits of
                              // 18.5 fills, cold weights: five tiles, two of them padding, 39.9 us, three 31.5.
-        if (!wide && mt == 1) return launch_ws<1, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, st);
-        if (!wide && mt == 2) return launch_ws<2, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, st);
-        if (!wide && mt == 3) return launch_ws<3, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, st);
-        if (!wide && mt == 4) return launch_ws<4, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, st);
-        return wide ? launch_ws<5, 2, 4, 4>(Ap, Wp, out, M, N, K, splits, st) : launch_ws<5, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, st);
+        if (!wide && mt == 1) return launch_ws<1, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, cold, st);
+        if (!wide && mt == 2) return launch_ws<2, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, cold, st);
+        if (!wide && mt == 3) return launch_ws<3, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, cold, st);
+        if (!wide && mt == 4) return launch_ws<4, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, cold, st);
+        return wide ? launch_ws<5, 2, 4, 4>(Ap, Wp, out, M, N, K, splits, cold, st) : launch_ws<5, 1, 4, 4>(Ap, Wp, out, M, N, K, splits, cold, st);
     }
     switch (mt * 2 + (wide ? 1 : 0)) {
-        case 2: return launch_ws<1, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 3: return launch_ws<1, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 4: return launch_ws<2, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 5: return launch_ws<2, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 6: return launch_ws<3, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 7: return launch_ws<3, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 8: return launch_ws<4, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 9: return launch_ws<4, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        case 10: return launch_ws<5, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
-        default: return launch_ws<5, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, st);
+        case 2: return launch_ws<1, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 3: return launch_ws<1, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 4: return launch_ws<2, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 5: return launch_ws<2, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 6: return launch_ws<3, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 7: return launch_ws<3, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 8: return launch_ws<4, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 9: return launch_ws<4, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        case 10: return launch_ws<5, 1, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
+        default: return launch_ws<5, 2, 8, 8>(Ap, Wp, out, M, N, K, splits, cold, st);
     }
 }
 

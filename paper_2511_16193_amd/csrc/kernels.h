@@ -13,8 +13,9 @@ hipError_t gemm_bf16(const bf16_t* A, const bf16_t* W, float* out, int M, int N,
                      hipStream_t st);
 hipError_t pack_weight(const bf16_t* src, bf16_t* dst, int N, int K, hipStream_t st);
 hipError_t pack_rows(const bf16_t* src, bf16_t* dst, int M, int K, hipStream_t st);
-// row_tiles: 32-row tiles per work-group (1..5; 0 = as few work-groups along the rows as five tiles each allow)
-hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool wide,
+// row_tiles: 32-row tiles per work-group (1..5; 0 = as few work-groups along the rows as five tiles each allow); cold, here and below: the
+// weights come from HBM (see kCacheBytes)
+hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool wide, bool cold,
                         hipStream_t st, int row_tiles = 0);
 int gemm_bf16_ws_row_tiles(int M);
 // Tall tiles, 64 rw rows (rw 3..5) x 256 features, both operands through LDS: n of them along the rows, then nt of 64 rwt
@@ -27,7 +28,7 @@ struct StripTile { int tiles, fs; };
 struct StripPlan { int splits; StripTile tile; double us; };
 constexpr int kStripRows = 320;             // most rows of a strip
 inline int gemm_bf16_strips(int N, const StripTile& s) { return (N / 2 + 16 * s.fs - 1) / (16 * s.fs); }    // strips of N features
-hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const StripTile& tile, hipStream_t st);
+hipError_t gemm_bf16_strip(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, int N, int K, int splits, bool glu, const StripTile& tile, bool cold, hipStream_t st);
 StripPlan gemm_bf16_strip_plan(int M, int N, int K, int min_splits, int max_splits, bool glu);
 TallPlan gemm_bf16_tall_plan(int M, int N, int K, int max_splits);
 TallTiles gemm_bf16_tall_256(int M);
@@ -114,6 +115,7 @@ struct AttnArgs {
     int grid_items;                     // when > 0: items the grid is sized for (an upper bound of the item count)
     bool row_items;                     // prefill: an item is 64 stacked rows of a request, whose keys end at the last one it sees
     bool merge;                         // some request has several pieces
+    bool cold;                          // the keys and values come from HBM (see kCacheBytes)
     const int32_t* last_of; int n_last; // when set (the last layer of a prefill): only the last rows of the first n_last requests of that
     void* last_out;                     //       table are wanted, in rows 0 .. n_last - 1 of this buffer, which is not `out` (work: items that hold them)
     int min_row_tiles;                  // lower bound on the 16-row tiles of the bf16 kernel (tuning)
@@ -145,6 +147,7 @@ struct MoeArgs {
     float* y;                 // [32 * max_tiles][d] expert outputs (until the first product has read them: the buckets' rows as bf16 operand tiles)
     float* out;               // [T][d] combined result
     int T, d, E, top_k, F;
+    bool cold;                // the expert weights come from HBM (see kCacheBytes)
 };
 int moe_shape_ok(int T, int d, int E, int top_k, int F);
 size_t moe_group_lds_bytes(int T, int E);

@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
 // 20 rows 111 + 57.7 -> 104 + 58.4.
 constexpr int kMoeSlices = 8;                               // 16-wide slices per fill
 
-template <int MODE, int MT>
+template <int MODE, int MT, bool STREAM>
 __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf, const char* w_base, int p, int tile, int nt_here, bool one_tile) {
     constexpr int KA = kMoeSlices, PD = (MT == 1 ? 2 : 1) * kMoeSlices, APW = MT * KA / 4;
     const int K = MODE == 0 ? a.d : a.F;                    // reduction width
@@ -372,7 +372,7 @@ __device__ __forceinline__ void moe_tiles(const MoeArgs& a, unsigned char* abuf,
     const char* a_base = reinterpret_cast<const char*>(rows + ((int64_t)(MODE == 0 && one_tile ? 0 : tile + (my < nt_here ? my : nt_here - 1)) * kslices + ks_mine) * 512);
     const auto a_desc = buffer_of(a_base, (kslices - ks_mine) * 1024), w_desc = buffer_of(w_base, (kslices - 1) * 4096 + 1024);
     auto load_a = [&](int slice) __attribute__((always_inline)) { return buffer_load16(a_desc, lane * 16, slice * 1024); };
-    auto load_w = [&](int slice) __attribute__((always_inline)) { return buffer_load16<kStreamLoad>(w_desc, lane * 16, slice * 4096); };
+    auto load_w = [&](int slice) __attribute__((always_inline)) { return buffer_load16<STREAM ? kStreamLoad : 0>(w_desc, lane * 16, slice * 4096); };
     unsigned char* a_dst = abuf + (wave * APW) * 1024 + lane * 16;
     constexpr int BUF = MT * KA * 1024;
 
@@ -509,12 +509,17 @@ __global__ __launch_bounds__(256, MTMAX == 4 ? 2 : 4) void moe_gemm_kernel(MoeAr
     else nt_local = 4 * p + wave;
     const int nt = e * (Ntot / 32) + nt_local, kslices = (MODE == 0 ? a.d : a.F) / 16;
     const char* w_base = reinterpret_cast<const char*>((MODE == 0 ? a.w_gate_up : a.w_down) + (((int64_t)(nt >> 2) * kslices) * 4 + (nt & 3)) * 512);
-    for (int g0 = 0; g0 < ntile; g0 += MTMAX) {
-        const int left = ntile - g0, nt_here = left < MTMAX ? left : MTMAX;
-        if (MTMAX == 1 || nt_here == 1) moe_tiles<MODE, 1>(a, abuf, w_base, p, tile0 + g0, 1, one_tile);
-        else if (MTMAX == 2 || nt_here == 2) moe_tiles<MODE, 2>(a, abuf, w_base, p, tile0 + g0, 2, one_tile);
-        else if constexpr (MTMAX == 4) moe_tiles<MODE, 4>(a, abuf, w_base, p, tile0 + g0, nt_here, one_tile);
-    }
+    auto groups = [&](auto stream) __attribute__((always_inline)) {
+        constexpr bool STREAM = decltype(stream)::value;
+        for (int g0 = 0; g0 < ntile; g0 += MTMAX) {
+            const int left = ntile - g0, nt_here = left < MTMAX ? left : MTMAX;
+            if (MTMAX == 1 || nt_here == 1) moe_tiles<MODE, 1, STREAM>(a, abuf, w_base, p, tile0 + g0, 1, one_tile);
+            else if (MTMAX == 2 || nt_here == 2) moe_tiles<MODE, 2, STREAM>(a, abuf, w_base, p, tile0 + g0, 2, one_tile);
+            else if constexpr (MTMAX == 4) moe_tiles<MODE, 4, STREAM>(a, abuf, w_base, p, tile0 + g0, nt_here, one_tile);
+        }
+    };
+    if (a.cold) groups(std::true_type{});
+    else groups(std::false_type{});
 }
 
 // ------------------------------------------------------------------ combine
