@@ -96,3 +96,20 @@ def test_experts_that_the_cache_holds_and_more_give_the_same_bits():
     args = (_bf16((E, d), 42, 0.05), _bf16((E, 2 * F, d), 43, 0.02), _bf16((E, d, F), 44, 0.02), top_k)
     few, more = P.op_moe_ffn(a[:5].contiguous(), *args), P.op_moe_ffn(a, *args)
     assert torch.equal(few[1], more[1][:5]) and torch.equal(few[0], more[0][:5])
+
+
+def test_an_expert_of_more_rows_than_a_group_gives_the_bits_of_its_tiles_alone():
+    """All 96 rows choose expert 3: its weights are read twice and ordinarily, the others', which one group covers, as a stream; 32 rows at a
+    time every strip is read once."""
+    E, d, F, top_k, rows = 64, 2048, 1024, 2, 96
+    a = _bf16((rows, d), 51)
+    a[:, 0] = 8.0
+    router = _bf16((E, d), 52, 0.02)
+    router[:, 0] = 0.0
+    router[3, 0] = 4.0
+    args = (router, _bf16((E, 2 * F, d), 53, 0.02), _bf16((E, d, F), 54, 0.02), top_k)
+    out, ids, _ = P.op_moe_ffn(a, *args)
+    assert bool((ids[:, 0] == 3).all()) and len(ids[:, 1].unique()) > 20
+    for r0 in range(0, rows, 32):
+        part, part_ids, _ = P.op_moe_ffn(a[r0:r0 + 32].contiguous(), *args)
+        assert torch.equal(part_ids, ids[r0:r0 + 32]) and torch.equal(part, out[r0:r0 + 32])
