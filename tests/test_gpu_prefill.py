@@ -153,3 +153,114 @@ def test_prefill_sums_unrounded_softmax_weights(cached):
     print("moved", moved)
     assert float((shown - want).abs().max()) < 0.02 * float(want.abs().max())
     assert moved < 1e-3
+
+
+def other_verifier(case, *, prefill_rows, num_pages, pages_per_seq, page_size=64, max_k=0):
+    """A second context over the case's weights, its cache holding what the case's oracle caches hold."""
+    from paper_2511_16193_amd import Verifier
+    B, dt = len(case.lengths), torch.bfloat16 if case.shape.dtype == "bf16" else torch.float32
+    ver = Verifier(case.shape.model_fields(), case.wd, max_batch=B, max_k=max_k, max_chains=1, max_seqs=B, page_size=page_size, num_pages=num_pages,
+                   max_pages_per_seq=pages_per_seq, verify_mode=case.verify_mode, packed=case.packed,
+                   prefill_rows=prefill_rows, device=case.device)
+    for b, L in enumerate(case.lengths):
+        ver.seq_add(b, int(L))
+        for l in range(case.shape.n_layers) if L else ():
+            k, v = (torch.from_numpy(x[l][:L]).to(dt).to(case.device).contiguous() for x in (case.caches[b].k, case.caches[b].v))
+            ver.kv_write(b, l, 0, k, v)
+    return ver
+
+
+def case_of(dtype, packed, vocab, cached, **kw):
+    shape = W.Shape("passes", 2, 256, 8, 2, kw.pop("hd", 128), 512, vocab, dtype=dtype, batch=len(cached), k=0, seed=91)
+    case = Case(shape, cached, verify_mode=OV.STOCHASTIC, packed=packed, extra_tokens=kw.pop("extra", 16), **kw)
+    case.packed = packed
+    return case
+
+
+@pytest.mark.parametrize("dtype,packed,vocab,B,n,rows", [
+    ("bf16", True, 2048, 72, 4, 160),     # passes that end 40 and 32 prompts, taken alone: kept rows cross an operand tile in mid-pass
+    ("bf16", True, 2048, 100, 2, 100),    # 50 and 50 of 100 rows: too many to be taken alone
+    ("bf16", False, 2048, 72, 4, 160),
+    ("fp32", False, 2048, 72, 4, 160),
+    ("bf16", True, 128, 24, 4, 64),       # a small vocabulary: no room to keep normalised rows, an LM head for each pass
+])
+def test_prompts_that_end_in_several_passes(dtype, packed, vocab, B, n, rows):
+    case = case_of(dtype, packed, vocab, [0] * B, hd=64 if dtype == "fp32" else 128)
+    ver = other_verifier(case, prefill_rows=rows, num_pages=B + 2, pages_per_seq=2)
+    prompts = W.make_tokens((B, n), vocab, 91, "prompt")
+    lo = np.stack([OV.prefill(case.spec, case.wn, case.caches[b], prompts[b])[-1] for b in range(B)])
+    tokens = torch.from_numpy(prompts).to(torch.int32)
+    ld = ver.prefill_batch(list(range(B)), tokens, [n] * B)
+    assert np.max(np.abs(lo - ld.cpu().numpy())) < LOGIT_TOL[dtype]
+    last = case.shape.n_layers - 1
+    entries = [ver.kv_read(b, last, 0, n) for b in range(B)]
+    ver.seq_set_lens(list(range(B)), [0] * B)
+    assert ver.prefill_batch(list(range(B)), tokens, [n] * B, want_logits=False) is None      # nothing beyond the cache entries
+    for b in range(B):
+        assert ver.seq_len(b) == n and all(torch.equal(x, y) for x, y in zip(entries[b], ver.kv_read(b, last, 0, n)))
+    ver.close()
+    case.close()
+
+
+@pytest.mark.parametrize("cached,lens", [
+    ([5000, 3000], [70, 64]),             # the last rows' keys in pieces, of both
+    ([5000, 0], [70, 70]),                # of one; the other's output comes from one piece
+])
+def test_last_rows_alone_over_keys_in_pieces(cached, lens):
+    case = case_of("bf16", True, 2048, cached, extra=max(lens) + 8)
+    prompts = W.make_tokens((2, max(lens)), 2048, 91, "prompt")
+    lo = np.stack([OV.prefill(case.spec, case.wn, case.caches[b], prompts[b, :n])[-1] for b, n in enumerate(lens)])
+    ld = case.ver.prefill_batch([0, 1], torch.from_numpy(prompts).to(torch.int32), lens).cpu().numpy()
+    assert np.max(np.abs(lo - ld)) < LOGIT_TOL["bf16"]
+    case.close()
+
+
+@pytest.mark.parametrize("vocab", [2048, 128])    # normalised rows kept until the last pass; no room for them
+def test_pages_that_run_out_in_a_later_pass(vocab):
+    """The second of two passes does not get its pages: the error, the first prompt's logits, and lengths and cache as the first pass left them."""
+    import ctypes as C
+    lens = [40, 40, 20]                               # 64 rows and 36
+    case = case_of("bf16", True, vocab, [0, 0, 0], extra=48)
+    ver = other_verifier(case, prefill_rows=64, num_pages=4, pages_per_seq=3, page_size=32, max_k=1)
+    prompts = W.make_tokens((3, 40), vocab, 91, "prompt")
+    want = OV.prefill(case.spec, case.wn, case.caches[0], prompts[0])[-1]
+    tokens = torch.from_numpy(prompts).to(torch.int32).to(case.device)
+    out = torch.full((3, vocab), 77.0, dtype=torch.float32, device=case.device)
+    rc = ver.lib.verify_prefill_batch(ver.ctx, (C.c_int32 * 3)(0, 1, 2), 3, C.c_void_p(tokens.data_ptr()), 40, (C.c_int32 * 3)(*lens), C.c_void_p(out.data_ptr()))
+    assert rc == -2 and ver.lib.verify_last_error(ver.ctx).decode() == "need 2 more pages, 1 free"
+    assert np.max(np.abs(out[0].cpu().numpy() - want)) < LOGIT_TOL["bf16"] and bool((out[1:] == 77.0).all())
+    assert [ver.seq_len(b) for b in range(3)] == [40, 24, 0]
+    ver.seq_remove(0)                                  # its pages let the others go on
+    rest = torch.zeros((2, 20), dtype=torch.int32)
+    rest[0, :16], rest[1] = tokens[1, 24:].cpu(), tokens[2, :20].cpu()
+    ld = ver.prefill_batch([1, 2], rest, [16, 20]).cpu().numpy()
+    for b in (1, 2):
+        lo = OV.prefill(case.spec, case.wn, case.caches[b], prompts[b, :lens[b]])[-1]
+        assert np.max(np.abs(ld[b - 1] - lo)) < LOGIT_TOL["bf16"]
+    ver.close()
+    case.close()
+
+
+def test_more_last_rows_than_the_work_list_holds():
+    """4096 prompts of two tokens and 33 q heads on one kv head: every prompt's last row lies in two work items, and the list has no room for those
+    again.  The last layer then takes all rows; the prompts a thousand at a time do not come to that."""
+    import paper_2511_16193_amd as P
+    dev, B, d, hq, hd, V = "cuda:0", 4096, 128, 33, 128, 256
+    g = torch.Generator(dev).manual_seed(3)
+    rnd = lambda *s, std=1.0: torch.empty(s, dtype=torch.bfloat16, device=dev).normal_(0.0, std, generator=g)
+    one = torch.ones(d, dtype=torch.bfloat16, device=dev)
+    w = P.pack_weights({"embed": rnd(V, d), "lm_head": rnd(V, d, std=0.1), "final_norm": one, "layers": [
+        {"ln1": one, "wqkv": rnd((hq + 2) * hd, d, std=0.1), "wo": rnd(d, hq * hd, std=0.02), "ln2": one, "w_gate_up": rnd(256, d, std=0.1),
+         "w_down": rnd(d, 128, std=0.1)} for _ in range(2)]})
+    model = dict(n_layers=2, d_model=d, n_q_heads=hq, n_kv_heads=1, head_dim=hd, d_ff=128, vocab=V, n_experts=0, top_k=0, d_expert=0, dtype="bf16",
+                 rope_theta=1.0e4, rms_eps=1.0e-6)
+    ver = P.Verifier(model, w, packed=True, max_batch=B, max_k=1, max_chains=1, max_seqs=B, page_size=32, num_pages=B + 4, max_pages_per_seq=1,
+                     verify_mode=P.SV_MATCH, prefill_rows=0, device=dev)
+    tokens = torch.randint(0, V, (B, 2), generator=g, device=dev).to(torch.int32)
+    for b in range(B):
+        ver.seq_add(b, 0)
+    all_at_once = ver.prefill_batch(list(range(B)), tokens, [2] * B)
+    ver.seq_set_lens(list(range(B)), [0] * B)
+    by_parts = torch.cat([ver.prefill_batch(list(range(b, b + 1024)), tokens[b:b + 1024], [2] * 1024) for b in range(0, B, 1024)])
+    assert float((all_at_once - by_parts).abs().max()) < LOGIT_TOL["bf16"] and float(by_parts.std()) > 0.1
+    ver.close()
