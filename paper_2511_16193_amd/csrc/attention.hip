@@ -612,7 +612,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
                             }
                     }
                     mc[rt] = mc_new;
-                    limit[rt] = seen | some ? (mc_new + 16.0f) * unscale : -INFINITY;
+                    limit[rt] = (seen | some) ? (mc_new + 16.0f) * unscale : -INFINITY;
                 }
             }
         }
@@ -822,15 +822,12 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // its weight is marked below zero and its V, which may hold anything, is not multiplied; only tiles that hold such keys are
 // looked at for it (in all of them it cost 4 to 8 %; so, the fp32 prefill 1 % and the steps nothing).  (With a lane per key
 // holding all D accumulators, V element by element and D wave reductions at the end, the step of 20 rows with 132 keys took 43 us
-// a layer; 6.2 us now.)  A row's cached length comes with its other descriptions, and in fp32 with 64 dimensions, where a group takes two of
-// a chunk's tiles, the first tile of V is requested before the softmax: one read less in the chain that a small step's launch consists of (two layers, 20
-// rows of 128 / 1500 / 4000 keys 76.4 / 108.2 / 167.7 us a step, 75.6 / 108.4 / 172.3 without).  Not otherwise, us a step with that request against without:
-// fp32, 128 dimensions, two layers, 16 rows of 128 / 700 / 2000 keys 172.0 / 207.5 / 298.0 against 165.2 / 182.6 / 233.8; bf16, 64 dimensions, three layers of
-// 32 heads, 80 rows of 600 / 3000 keys 360 / 715 against 353 / 684, 240 rows of 600 654 against 636 (but of 3000 2268 against 2486).
+// a layer; 6.2 us now.)  A row's cached length comes with its other descriptions, one read less in the chain that a small step's launch
+// consists of.  (The chunk's first tile of V requested before the softmax saves another, 1 to 3 % of a step of few rows with 64 fp32 dimensions, but
+// costs many rows 3 to 4 % -- two layers of 12 heads, 99 / 288 rows of 4200 / 1500 keys 574 / 964 -> 599 / 993 us a step --, 128 dimensions up to 20 % and bf16 5 %.)
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float scale) {
     constexpr int CK = 256, GROUPS = 256 / D, EP = 16 / (int)sizeof(T);
-    constexpr bool AHEAD = D == 64 && sizeof(T) == 4;
     const int t_out = blockIdx.x, t = a.last_of ? a.last_of[t_out * kReqInts] + a.last_of[t_out * kReqInts + 1] - 1 : t_out, h = blockIdx.y, tid = threadIdx.x;
     const int4 info = reinterpret_cast<const int4*>(a.row_info)[t];
     const int seq = info.x, j = info.y;
@@ -855,11 +852,6 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
         }
     };
     const int dim = tid % D, grp = tid / D;
-    auto load_v = [&](int k0, float (&v)[4][8]) {          // keys 4 g .. 4 g + 3 and 16 + 4 g .. of a tile, which lies inside a page
-        const T* vp = pool + kv_v_index(a.geom, a.layer, pages[k0 / a.geom.page_size], hkv, k0 % a.geom.page_size, dim);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) load8(vp + g * 128, v[g]);
-    };
     float m = -INFINITY, l = 0.f, acc = 0.f;
     for (int c0 = 0; c0 < end; c0 += CK) {
         const int key = c0 + tid;
@@ -877,11 +869,6 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
             }
             s *= scale;
         }
-        float v[4][8];
-        if (AHEAD) {
-            if (c0 + grp * TILE_KEYS < end) load_v(c0 + grp * TILE_KEYS, v);    // on its way during the softmax
-            __builtin_amdgcn_sched_barrier(0);
-        }
         const float mw = wave_max(s);
         if ((tid & 63) == 0) red[tid >> 6] = mw;
         __syncthreads();
@@ -894,15 +881,19 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a, float sca
         m = m_new;
         __syncthreads();
         auto weigh = [&](int tile, auto masked) __attribute__((always_inline)) {
-            if (!AHEAD || tile != grp) load_v(c0 + tile * TILE_KEYS, v);
+            const int k0 = c0 + tile * TILE_KEYS;           // a tile lies inside a page
+            const T* vp = pool + kv_v_index(a.geom, a.layer, pages[k0 / a.geom.page_size], hkv, k0 % a.geom.page_size, dim);
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int g = 0; g < 4; ++g) {
+                float v[8];
+                load8(vp + g * 128, v);                     // keys 4 g .. 4 g + 3 and 16 + 4 g .. of the tile
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float w0 = p[tile * TILE_KEYS + 4 * g + e], w1 = p[tile * TILE_KEYS + 16 + 4 * g + e];
-                    acc = decltype(masked)::value && w0 < 0.f ? acc : fmaf(w0, v[g][e], acc);
-                    acc = decltype(masked)::value && w1 < 0.f ? acc : fmaf(w1, v[g][4 + e], acc);
+                    acc = decltype(masked)::value && w0 < 0.f ? acc : fmaf(w0, v[e], acc);
+                    acc = decltype(masked)::value && w1 < 0.f ? acc : fmaf(w1, v[4 + e], acc);
                 }
+            }
         };
         int tile = grp;                                     // first the tiles in which nothing is masked
         for (; tile < CK / TILE_KEYS && c0 + (tile + 1) * TILE_KEYS <= all_seen; tile += GROUPS) weigh(tile, std::false_type{});
