@@ -30,10 +30,10 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
-// What a launch leaves for later ones and does not read again itself, written as a stream: such lines are the first to leave an XCD's L2.
-// As ordinary stores they lie there dirty until the next launch's weight stream pushes them out, and that stream waits for the
-// write-backs.  For stores that fill whole 128-byte lines at once, or whole halves that are put together before they leave; the pieces of 8
-// and 16 bytes of a packed row do not (the norm's operands so written: 24 -> 41 us at 2304 rows).
+// What a launch leaves for later ones and does not read again itself, written with the non-temporal hint.  It is kept for what it measures: the
+// launches that follow, streaming weights or keys, are the faster ones (down of 96 rows 36.0 -> 31.4 us).  The counters do not say why: launches
+// run one by one write and read the same bytes with it and without.  For stores that fill whole 128-byte lines at once, or whole halves that are
+// put together before they leave; not the pieces of 8 and 16 bytes of a packed row (the norm's operands so written: 24 -> 41 us at 2304 rows).
 template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
 // Few rows leave little behind, and the launch that reads it, all of it one chain of latencies, does better to find it in L2 (after streamed
 // planes the norm of five rows takes 4.8 us for 4.1, rotary 7.7 for 6.1).  The line is where steps are level, ordinary against streamed stores at 5 /
@@ -41,7 +41,7 @@ template <typename T> __device__ __forceinline__ void store_stream(T* p, T v) { 
 // 292 / 305 / 346 / 375 / 402, 3584 wide, 3 layers 519 / 549 / 615 / 651 / 695 against 524 / 549 / 596 / 624 / 676.
 __host__ __device__ __forceinline__ bool leaves_stream(int64_t rows, int width) { return rows * width >= 96 * 1024; }
 
-// What is read once in a launch, and by one work-group only, read as a stream: such lines give way first in L2 and leave it to what is shared.
+// What is read once in a launch, and by one work-group only, read with the same hint (not what several work-groups share: see the kernels).
 // For what comes from HBM: a pass that reads less than kCacheBytes finds it in the chip's memory-side cache, where the one before left it, and
 // ordinary loads are the faster ones then ("cold" names passes that read more).  Steps of a 1024-wide model, 4 / 6 / 8 / 10 / 14 layers, 162 / 210 / 258 / 307 /
 // 403 MB of weights, 5 rows: 210 / 303 / 417 / 528 / 735 us with ordinary loads, 223 / 319 / 417 / 510 / 701 streamed; 4 layers and 49 / 196 / 786 MB of

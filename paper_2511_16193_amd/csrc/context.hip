@@ -58,7 +58,8 @@ int pick_splits(int M, int N, int K) {
 // smaller ones); a CU works its share off at a rate that grows with the rows it holds (the weight stream is
 // shared by more products), no faster than a lone work-group can walk its reduction slices; the chip as a whole
 // sustains about 1.2 PFLOP/s on random data (it is power-limited well below the MFMA peak) and 5 TB/s of
-// weights; a partial plane costs its bytes, written here and read again by the consumer.  The constants are a
+// weights (ordinary loads; streamed, as one row tile reads cold ones, 5.4 to 6.5: what this estimate decides by itself, splits and widths, was not
+// fitted again); a partial plane costs its bytes, written here and read again by the consumer.  The constants are a
 // fit to a sweep of every (tiles, width, splits) over thirty shapes of the benchmark models on MI355X (rows 5 to
 // 2304), except the lone work-group's pace, which is taken from whole steps (cold weights); on the sweep the plan
 // chosen was within 0.3 % of the best on average and 4.5 % at worst.
@@ -98,7 +99,7 @@ WsPlan plan_ws(int M, int N, int K, bool allow_split, int max_splits = kMaxSplit
                 const long long cap = 256LL * per_cu, full = blocks / cap, rem = blocks % cap;
                 double t = full * round_time(cap) + (rem ? round_time(rem) : 0.0);
                 t = std::max(t, 2.0 * M * (double)N * K / 1198.0e6);          // the chip's sustained rate
-                t = std::max(t, (double)N * K * 2.0 / 4.98e6);                // a weight stream cannot beat the memory system
+                t = std::max(t, (double)N * K * 2.0 / 4.98e6);                // the weights, as ordinary loads bring them
                 if (s > 1) t += (double)s * M * N * 4.0 / 5.4e6 + (double)(s - 1) * M * N * 4.0 / 4.0e6;   // planes written here, read by the consumer
                 t += 2.3;
                 if (t < best.us - 1e-9) best = WsPlan{s, wide != 0, mt, t, t, {}, {}};
@@ -146,6 +147,12 @@ WsPlan plan_wide(int M, int N, int K, bool allow_split, int tile_mode, bool dire
 // inputs, 1 to 4 more), where tall tiles are 48 and 12 less at 192 and 320; 151936 x 2048 within 2 of the tall tiles up to 256 rows and 7
 // less at 320, 151936 x 1024 alone 5 to 13 less from 192 rows on, whatever the estimates say; where the strips are one round (225 of 50304 x
 // 1024) and the tall estimate is lower, 6 to 8 more.
+// Once more with weights read and planes left as streams, us a launch inside a step, weight-streaming against strip at 5 / 65 / 96 / 128 / 147 rows: LM heads
+// 152064 x 3584 161 / 199 / 201 / 217 / - against 162 / 206 / 207 / 216 / 225, x 5120 229 / 276 / 279 / 288 / - against 227 / 285 / 290 / 297 / 312, 32000 x
+// 2048 21.7 / 28.2 / 27.1 / 30.2 / 34.1 against 21.6 / 28.7 / 26.4 / 30.1 / 33.4; down 3584 x 18944 26.4 / 34.1 / 34.5 / 39.4 / - against 23.0 / 29.7 / 29.2 / 33.4 /
+// -; QKV 4608 x 3584 7.4 / 12.4 / 12.7 / 14.0 / 16.2 against 7.3 / 12.3 / 14.3 / 16.6 / 17.4.  Those lines stand.  Not where strips lose now and are still
+// taken: QKV 7168 x 5120 13.3 / 19.5 / 20.5 / 22.5 / 23.9 against 13.0 / 20.4 / 22.1 / 23.8 / 25.0, O 5120 x 5120 at 147 rows 18.0 against 20.7; down 2048 x 5632
+// 6.7 / 9.1 / 9.4 / 13.0 / 12.0 against 6.4 / 11.0 / 11.6 / 14.0 / 14.6 (as before the streams).
 // Other tall tiles: see plan_gate_up.
 // experts: a model with a router, whose choices turn on the last bits of the rows: a strip keeps the splits of the launch that it
 // replaces, and with them the bits.
@@ -1051,7 +1058,10 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     float* part = c->at<float>(L.part);
     void* a_norm = c->at<void>(L.a_norm);
     // fp32: the projections write the residual themselves, and where their rows are few they take the norms and rotary with them
-    const bool f32 = m.dtype == SV_FP32, end = l == m.n_layers - 1 && ps.last >= 0, few = end && last_rows_only(c, ps), f32_qkv = f32 && gemm_f32_fuses(T, qkvw, d, kF32Qkv), f32_up = f32 && !few && gemm_f32_fuses(T, m.d_ff, d, kF32Glu);
+    const bool end = l == m.n_layers - 1 && ps.last >= 0, few = end && last_rows_only(c, ps);
+    const bool f32 = m.dtype == SV_FP32;
+    const bool f32_qkv = f32 && gemm_f32_fuses(T, qkvw, d, kF32Qkv);
+    const bool f32_up = f32 && !few && gemm_f32_fuses(T, m.d_ff, d, kF32Glu);
     auto norm_by = [&](const void* gain) { return F32Norm{(const float*)gain, m.rms_eps}; };
 
     RopeAppend ra;
@@ -1159,9 +1169,9 @@ extern "C" int verify_prefill(sv_ctx* c, int32_t id, const int32_t* tokens, int3
 // fit, through the same kernels as a verification step (requests of different sizes, one causal chain each).  The passes
 // are as few as hold all tokens, and of equal size.  Only the rows that end a prompt are wanted beyond their K and V: within a pass they
 // belong to its first requests.  The last layer's attention, O and feed-forward take these rows only (7 layers of the 7B shape with the first
-// step, 24 prompts of
-// 100-500 tokens 21.6 -> 19.2 ms, one of 777 4.25 -> 4.00), and where there is room their normalised rows are kept until all passes are done and
-// the LM head's weights stream once, straight into the caller's logits.
+// step, 24 prompts of 100-500 tokens 21.6 -> 19.2 ms, one of 777 4.25 -> 4.00; their launch plans are those of few rows, so the sums are added up in
+// another order), and where there is room their normalised rows are kept until all passes are done and the LM head's weights stream
+// once, straight into the caller's logits.
 extern "C" int verify_prefill_batch(sv_ctx* c, const int32_t* seq_ids, int32_t B, const int32_t* tokens, int32_t ld,
                                     const int32_t* n, float* last_logits) {
     if (!c || !seq_ids || !tokens || !n) return SV_EINVAL;

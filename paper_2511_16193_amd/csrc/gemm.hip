@@ -335,9 +335,9 @@ __device__ __forceinline__ void gemm_bf16_ws_body(
         return;
     }
     // acc[i][j][4 q + r] <-> row m0 + 32 j + 8 q + 4 lg + r, feature n0 + 32 (wave NT + i) + l32
-    // A half wave fills a line of 128 bytes: streamed (LEAVE; where leaves_stream says so), so that the next kernel's loads do not push them out of L2 first (LM head of 96 rows, 58 MB of
-    // logits, 224 -> 213 us; QKV and O planes of 96 rows 12.5 + 10.5 -> 12.1 + 9.9, the attention between them 162 -> 160.5, norm and rotary + 0.4 and + 0.2).
-    // The tall and the strip kernel write half lines, which as streams cost the next norm more than they save.
+    // A half wave fills a line of 128 bytes: streamed (LEAVE; where leaves_stream says so; LM head of 96 rows, 58 MB of logits, 224 -> 213 us; QKV
+    // and O planes of 96 rows 12.5 + 10.5 -> 12.1 + 9.9, the attention between them 162 -> 160.5, norm and rotary + 0.4 and + 0.2).  The tall and
+    // the strip kernel write half lines, which as streams cost the next norm more than they save.
     float* dst = out + (int64_t)sp * M * N;
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -1065,7 +1065,7 @@ static hipError_t launch_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int 
         else launch(gemm_bf16_ws_kernel<MT, NT, KA, PD, false, decltype(stream)::value, false>);
     };
     // one row tile: the weights are read once, as a stream (LM heads of 152 thousand features at 5 / 20 / 42 / 96 rows 193 / 122 / 207 / 219 -> 168 / 107 /
-    // 190 / 202 us; QKV and O of 96 rows level).  Several: they find each other's in L2 (O of 5120 x 5120 at 800 rows, so read, 66.5 -> 72.6)
+    // 190 / 202 us; QKV and O of 96 rows level).  Several row tiles share them through L2 (O of 5120 x 5120 at 800 rows, so read, 66.5 -> 72.6)
     if (tiles_m == 1 && cold) form(std::true_type{});
     else form(std::false_type{});
     return hipGetLastError();
@@ -1166,7 +1166,7 @@ hipError_t gemm_bf16_ws(const bf16_t* Ap, const bf16_t* Wp, float* out, int M, i
 // And because a launch of such a step is little more than its own start (2.3 us of 4 to 6), the passes between the projections ride in
 // them: NORM reads the residual rows and normalises them on the way in (every work-group adds up the squares of its rows), kF32Qkv
 // rotates q and k and appends k and v to the cache on the way out, kF32Plain may add to what is there (the residual).  Two layers
-// of 20 rows: norm 2.9 + QKV 4.1 + rotary 3.3 -> 6.0 us, norm 2.9 + gate/up 5.2 -> 5.7, the step of 22 launches 92.0 -> 76.9 with 15.
+// of 20 rows: norm 2.9 + QKV 4.1 + rotary 3.3 -> 5.9 us, norm 2.9 + gate/up 5.2 -> 5.6, the step of 22 launches 91 -> 76 with 15.
 // kF32Glu: NT = 2, tile 0 gate rows, tile 1 the up rows of the same features (W has 2 F rows); out [M][F] = silu(gate) * up.
 // kF32Qkv: NT = 2, 16 dimensions of a head and their partners half a head away.
 // N, K and M are arbitrary: rows and features beyond the end read the last one and are not stored, k beyond the end counts
@@ -1377,7 +1377,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_kernel(const float* __res
 
 // 64-row wave tiles once they make a work-group for every other CU; below that eight waves share a reduction, on tiles of 32 rows, or of 16
 // while each of those has a CU to itself: half the products (a wave's 64 on K = 1024 take 1.9 us of the matrix unit) and half the
-// loads of a work-group.  20 rows, K = 256 and 1024 in turn: 6.4 -> 5.3 us a launch.  Up to 16 rows always: a 32-row tile has the same
+// loads of a work-group.  20 rows, K = 256 and 1024 in turn: 6.4 -> 4.9 us a launch.  Up to 16 rows always: a 32-row tile has the same
 // work-groups there and rows that are not there in its second half (16 rows, feed-forward and vocabulary of nine times the inputs, 512 / 768
 // inputs: 132.6 / 170.0 us a two-layer step with 32-row tiles, 127.8 / 163.5 with 16-row ones).
 static bool f32_large(int M, int N, bool glu) {

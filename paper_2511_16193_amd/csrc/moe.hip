@@ -348,10 +348,9 @@ __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
 // expert) 171.9 + 88.8 -> 160.5 + 85.6 us, 20 rows (one) 129.7 + 65.7 -> 118.1 + 63.9 (4.9 TB/s of weights; a plain
 // stream reaches 6.0).  Sixteen weight fragments in flight instead of eight, where one tile leaves registers for them, 2 %;
 // with two tiles they cost the fourth work-group and gain nothing.
-// The gathered tiles, silu(gate) * up and the outputs leave as streams (store_stream): the 31 MB of gathered tiles of 640 rows lay dirty in the L2s
-// when the weights came through.  640 rows: gather 11.6 -> 10.7 us, products 167 + 88.5 -> 157 + 87, the next layer's attention 235 -> 231, the
-// norm that combines the outputs 8.8 -> 9.3; 20 rows 114 + 58.6 -> 112 + 58.7.  The weights are read as a stream as well: 640 rows 157 + 88.5 -> 146 + 86.5,
-// 20 rows 111 + 57.7 -> 104 + 58.4.
+// The gathered tiles, silu(gate) * up and the outputs leave as streams (store_stream; of 640 rows 31, 12 and 62 MB).  640 rows: gather 11.6 -> 10.7
+// us, products 167 + 88.5 -> 157 + 87, the next layer's attention 235 -> 231, the norm that combines the outputs 8.8 -> 9.3; 20 rows 114 + 58.6 ->
+// 112 + 58.7; one to ten rows level.  The weights are read as a stream as well: 640 rows 157 + 88.5 -> 146 + 86.5, 20 rows 111 + 57.7 -> 104 + 58.4.
 constexpr int kMoeSlices = 8;                               // 16-wide slices per fill
 
 template <int MODE, int MT, bool STREAM>
