@@ -54,7 +54,7 @@ __device__ __forceinline__ float max8(const floatx4& a, const floatx4& b) {
 // inside a verification step it measured 3-14 % faster than the skewed kernel below (which is ahead once the
 // products dominate: four row tiles, or several row groups streaming the same keys).
 // ONCE: a tile is read by this work-group only, and from HBM: as a stream (load_stream): 320 rows of 64 requests 131 -> 119 us a layer, 96 requests' single rows
-// 164 -> 151, 640 rows beside 8 q heads a kv head 230 -> 210.
+// 164 -> 151, 640 rows beside 8 q heads a kv head 230 -> 210, five rows of one request 13.6 -> 13.0.
 template <int R, bool ONCE>
 __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(AttnArgs a, float scale_log2e) {
     // work item = one piece of one request's keys, cut by the host from its upper bounds of the lengths.

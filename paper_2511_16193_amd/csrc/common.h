@@ -47,10 +47,6 @@ __host__ __device__ __forceinline__ bool leaves_stream(int64_t rows, int width) 
 // 403 MB of weights, 5 rows: 210 / 303 / 417 / 528 / 735 us with ordinary loads, 223 / 319 / 417 / 510 / 701 streamed; 4 layers and 49 / 196 / 786 MB of
 // cached keys and values (4 / 16 / 64 requests) 221 / 320 / 512 against 238 / 319 / 486.
 constexpr size_t kCacheBytes = (size_t)256 << 20;
-// Keys and values as a stream from so many bytes a layer on.  Streamed against ordinary at 48 / 96 / 144 / 200 / 300 MB a layer, us a step: 2048 wide, four
-// layers, 16 requests x 5 rows 397 / 435 / 476 / 512 / 578 against 386 / 438 / 488 / 525 / 589, 64 x 1 349 / 369 / 401 / 435 / 490 against 337 / 371 / 409 / 442 / 502;
-// 3584 wide, three layers, 16 x 5 669 / 697 / 725 / 753 / 811 against 666 / 702 / 730 / 762 / 819.
-constexpr size_t kStreamKeys = (size_t)64 << 20;
 template <typename T> __device__ __forceinline__ T load_stream(const T* p) { return __builtin_nontemporal_load(p); }
 constexpr int kStreamLoad = 2;                              // the same hint in the cache-policy operand of the load builtins
 

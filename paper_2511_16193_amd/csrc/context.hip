@@ -346,7 +346,7 @@ struct sv_ctx {
     int n_last_work;                                      // prefill: items behind them that hold the last rows asked for; -1: no room for the list
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
     size_t weight_bytes, expert_bytes;                    // of all layers and the LM head; of one expert in all layers
-    bool cold, cold_keys;                                 // what the current pass reads once comes from HBM (see kCacheBytes); keys to stream (kStreamKeys)
+    bool cold;                                            // what the current pass reads once comes from HBM (see kCacheBytes)
     int gemm_variant;                                     // -1 = choose per shape
     int gemm_tile;                                        // packed projections: -1 = by the plans, 0 = weight-streaming kernel only, 1 = tall tiles wherever the shape allows
     struct PlannedShape { int M, N, K; bool allow_split, direct; WsPlan plan; };
@@ -526,7 +526,7 @@ extern "C" int verify_init(const sv_model* m, const sv_weights* w, const sv_runt
         c->expert_bytes = m->n_experts > 0 ? es * layers * 3 * m->d_expert * d : 0;
         c->weight_bytes = es * (layers * (2 * (size_t)(m->n_q_heads + m->n_kv_heads) * m->head_dim + (m->n_experts > 0 ? 0 : 3 * (size_t)m->d_ff)) * d + (size_t)m->vocab * d);
     }
-    c->cold = c->cold_keys = false;
+    c->cold = false;
     c->ring_pos = 0;
     c->gemm_variant = -1;
     c->gemm_tile = -1;
@@ -852,14 +852,12 @@ static void build_work(sv_ctx* c, const Pass& ps, int32_t* req, int32_t* work) {
 
 // Does the pass read more than the memory-side cache holds?  (All weights, experts as many as its rows can choose, all cached keys and values.
 // A captured step keeps what held when it was captured: the results are the same bits either way.)
-static void size_pass(sv_ctx* c, const Pass& ps) {
+static bool reads_past_cache(const sv_ctx* c, const Pass& ps) {
     const sv_model& m = c->model;
-    size_t tokens = 0;
-    for (int b = 0; b < ps.B; ++b) tokens += c->seqs[ps.rq[b].seq].len_ub + ps.rq[b].n;
-    const size_t keys = tokens * 2 * m.n_kv_heads * m.head_dim * (m.dtype == SV_BF16 ? 2 : 4);       // of one layer
-    const size_t experts = c->expert_bytes * std::min<long long>(m.n_experts, (long long)ps.T * m.top_k);
-    c->cold = c->weight_bytes + experts + keys * m.n_layers > kCacheBytes;
-    c->cold_keys = c->cold && keys >= kStreamKeys;
+    const size_t token = (size_t)2 * m.n_kv_heads * m.head_dim * (m.dtype == SV_BF16 ? 2 : 4) * m.n_layers;
+    size_t bytes = c->weight_bytes + c->expert_bytes * std::min<long long>(m.n_experts, (long long)ps.T * m.top_k);
+    for (int b = 0; b < ps.B; ++b) bytes += token * (c->seqs[ps.rq[b].seq].len_ub + ps.rq[b].n);
+    return bytes > kCacheBytes;
 }
 
 // Make sure every request's sequence holds pages for its new rows; describe the pass (requests, attention work list,
@@ -894,7 +892,7 @@ static int stage_pass(sv_ctx* c, const Pass& ps) {
     }
     c->n_work = c->n_last_work = 0;
     c->pass_merge = false;
-    size_pass(c, ps);
+    c->cold = reads_past_cache(c, ps);
     if (attn_mfma_ok(c->model.dtype, c->model.head_dim, c->rt.page_size, c->attn_generic,
                      ps.n == 0 ? 0 : c->model.n_q_heads / c->model.n_kv_heads * ps.n))
         build_work(c, ps, st + L.st_req, st + L.st_work);
@@ -1029,7 +1027,7 @@ static AttnArgs attn_args(const sv_ctx* c, const Pass& ps, int layer, const void
     aa.T = ps.T; aa.n_max = ps.n_max; aa.k = ps.k; aa.Hq = m.n_q_heads; aa.Hkv = m.n_kv_heads; aa.hd = m.head_dim; aa.dtype = m.dtype;
     aa.work = c->at<int32_t>(L.stage) + L.st_work; aa.n_work = c->n_work;
     aa.last_of = nullptr; aa.n_last = 0; aa.last_out = nullptr;
-    aa.row_items = ps.n == 0; aa.merge = c->pass_merge; aa.cold = c->cold_keys;
+    aa.row_items = ps.n == 0; aa.merge = c->pass_merge; aa.cold = c->cold;
     aa.n_work_dev = nullptr; aa.grid_items = 0;
     if (c->graph_launch_shape) {      // nothing in the launch may depend on the lengths
         aa.n_work_dev = c->at<int32_t>(L.stage);

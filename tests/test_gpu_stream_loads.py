@@ -67,18 +67,18 @@ def test_gated_strips_of_weights_that_the_cache_holds_and_larger_ones_give_the_s
     assert torch.equal(small, large[:, :F // 16])
 
 
-@pytest.mark.parametrize("hq,k", [(4, 1), (16, 1), (16, 2), (16, 3), (16, 5)])      # 4 to 96 stacked rows: one to four row tiles, two groups of three
+@pytest.mark.parametrize("hq,k", [(4, 1), (16, 1), (16, 2), (16, 3), (16, 5)])      # per kv head 2, 8 to 48 stacked rows: one to four row tiles
 def test_attention_over_keys_from_the_cache_and_as_a_stream_has_the_same_bits(hq, k):
-    hd, hkv, n, lens = 128, 1 if hq == 16 else 2, 1 + k, (70000, 65001)       # 66 MiB of keys and values a layer and more
+    hd, hkv, n, lens = 128, 1 if hq == 16 else 2, 1 + k, (37, 1500)
     out = []
     for vocab in (1024, 140032):                           # an LM head of 140032 x 1024: more than the cache holds
-        d = 1024
+        d, cap = 1024, 1600
         z = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda:0")
         weights = {"embed": z(vocab, d), "lm_head": z(vocab, d), "final_norm": z(d), "layers": [
             {"ln1": z(d), "wqkv": z((hq + 2 * hkv) * hd, d), "wo": z(d, hq * hd), "ln2": z(d), "w_gate_up": z(256, d), "w_down": z(d, 128)}]}
         model = dict(n_layers=1, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=128, vocab=vocab, n_experts=0, top_k=0, d_expert=0,
                      dtype="bf16", rope_theta=1.0e4, rms_eps=1.0e-6)
-        ver = P.Verifier(model, weights, packed=True, max_batch=2, max_k=k, max_chains=1, max_seqs=2, page_size=64, num_pages=2120, max_pages_per_seq=1096,
+        ver = P.Verifier(model, weights, packed=True, max_batch=2, max_k=k, max_chains=1, max_seqs=2, page_size=64, num_pages=60, max_pages_per_seq=26,
                          verify_mode=P.SV_MATCH, sample_mode=P.SV_EXP_RACE, temperature=1.0, device="cuda:0")
         for b, L in enumerate(lens):
             kv = _bf16((2, L + n, hkv, hd), 20 + b)
@@ -87,8 +87,7 @@ def test_attention_over_keys_from_the_cache_and_as_a_stream_has_the_same_bits(hq
             ver.seq_set_len(b, L)
         out.append(ver.op_attention([0, 1], n, k, 0, _bf16((2 * n, hq, hd), 30)).clone())
         ver.close()
-    # (70000 values of V of unit size, however weighted, leave 70000^-1/2 = 0.0038 at least)
-    assert torch.equal(out[0], out[1]) and float(out[0].float().std()) > 0.003
+    assert torch.equal(out[0], out[1]) and float(out[0].float().std()) > 0.01
 
 
 def test_experts_that_the_cache_holds_and_more_give_the_same_bits():
