@@ -345,8 +345,8 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
     }
 }
 
-// R row tiles per work-group, W waves, D slots per wave for K and for V in the LDS ring (W * D * 16 KB of LDS).
-// Run as W = 2, D = 2: two work-groups share a CU.
+// R row tiles per work-group, W waves, two slots per wave for K and for V in the LDS ring (W * 32 KB of LDS).
+// Run as W = 2: two work-groups share a CU.
 // ONCE: no other row group or item reads these keys, and they come from HBM: as a stream (load_stream; 63 rows of 256 requests 497 -> 445 us; with a second
 // row group to find them in L2 685 -> 703).
 // PT: bf16 terms the softmax weights are split into for the PV products.  With four row tiles (or several row
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 // products than with three terms.  The register kernel above is bound by the stream and keeps three.  So does a prefill, whose
 // rows become the cache that every later step reads: with two terms 1.3 in a thousand outputs are rounded to another bf16
 // value than the exact sums', with three 0.03 to 0.4; 24 prompts of 100-500 tokens 24.56 -> 24.54 ms, one of 777 4.37 -> 4.39.
-template <int R, int W, int D, int PT, bool ONCE = false>
+template <int R, int W, int PT, bool ONCE = false>
 __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float scale_log2e) {
     // Work item = one piece of one request's keys, cut by the host from its upper bounds of the lengths.
     // Launch order: the kv heads of an item are neighbours, so the list's longest-first order holds chip-wide.
@@ -436,258 +436,272 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
         for (int ht = 0; ht < 8; ++ht) o[ht][rt] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // K/V tiles travel HBM -> LDS -> registers.  Each wave owns a ring of D slots for K and D for V (8 KB each)
+    // K/V tiles travel HBM -> LDS -> registers.  Each wave owns a ring of two slots for K and two for V (8 KB each)
     // in LDS that it fills with direct-to-LDS loads (16 bytes per lane, 1 KB per instruction, no registers held
-    // while in flight) and reads back into one register set: two tiles on their way per wave where a second
-    // register set could hold one, and the registers go to the skewed stages instead.  A wave reads only what it
-    // loaded itself: no barriers.
+    // while in flight) and reads back into one register set.  A wave reads only what it loaded itself: no barriers.
     // The tile's base address is wave-uniform (scalar page number, head, offset) and kept in scalar registers.
     auto uniform = [](int64_t v) {
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
         return (int64_t)(((uint64_t)hi << 32) | lo);
     };
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_lds[];
-    unsigned char* ring = attn_lds + wave * (D * kTileBytes);          // K slots 0..D-1, then V slots 0..D-1, 8 KB each
     // Tiles start on multiples of 32 keys, where the cache's index functions reduce to
     //   K: layer * layer_elems + page * page_elems + (head * page_size + key_in_page) * 128,   V: the same + v_off
     // (kv_k_index / kv_v_index with tok % 32 == 0, dim == 0); K and V of a tile are 8 KB each, contiguous, and are
-    // copied verbatim: 4 loads per 4 KB share one scalar base, one LDS base, and differ in the immediate offset,
-    // which the instruction adds to both addresses.
-    const int64_t head_base = (int64_t)a.layer * a.geom.layer_elems + (int64_t)hkv * a.geom.page_size * HD;
-    const int64_t v_off = (int64_t)a.geom.n_kv_heads * a.geom.page_size * HD;
+    // copied verbatim.
+    const char* head_base = reinterpret_cast<const char*>(pool + ((int64_t)a.layer * a.geom.layer_elems + (int64_t)hkv * a.geom.page_size * HD));
+    const int64_t v_off = (int64_t)a.geom.n_kv_heads * a.geom.page_size * HD * 2;
     const uint32_t lane_bytes = lane * 16;
-    // Ring layout per wave: K slots 0,1 then V slots 0,1 (8 KB each).  half = 0 for K, 1 for V.
-    auto issue_half = [&](int key0, int half, int slot) __attribute__((always_inline)) {
-        const int page = pages[key0 >> page_shift];
-        const int off = key0 & page_mask;
-        const int64_t ke = uniform(head_base + (int64_t)page * a.geom.page_elems + off * HD + half * v_off);
-        unsigned char* dst = ring + (half * D + slot) * 8192;
-        const char* src = reinterpret_cast<const char*>(pool + ke) + lane_bytes;
-        dma4<ONCE ? kStreamLoad : 0>(src, SV_LDS_PTR(dst));
-        dma4<ONCE ? kStreamLoad : 0>(src + 4096, SV_LDS_PTR(dst + 4096));
+    // Ring layout per wave: K slots 0, 1, then V slots 0, 1 (8 KB each).
+    const uint32_t ring = (uint32_t)(uintptr_t)SV_LDS_PTR(attn_lds) + wave * (2 * kTileBytes), ring_lane = ring + lane_bytes;
+    // KB `piece` of the eight of a tile's K (or V) into the ring slot at `dst`, in order: 0 and 4 set what the next three go by
+    auto request = [&](const char* src, uint32_t dst, auto piece) __attribute__((always_inline)) {
+        constexpr int F = decltype(piece)::value;
+        dma_piece<F % 4, ONCE>(src + F / 4 * 4096, lane_bytes, dst + F / 4 * 4096);
     };
 
-    // Wave w takes tiles w, w + 4, ... of the piece: its tile t starts at key tile_key(t).
+    // Wave w takes tiles w, w + W, ... of the piece: its tile t starts at key tile_key(t).
     const int ntiles = (kend - kbeg + TILE_KEYS - 1) / TILE_KEYS;
     const int last = ntiles - 1;
     const int n_my = wave < ntiles ? (ntiles - wave + W - 1) / W : 0;
     auto tile_key = [&](int t) { return kbeg + min(wave + W * t, last) * TILE_KEYS; };   // past the end: a valid tile
+    auto page_of = [&](int t) { return pages[tile_key(t) >> page_shift]; };
+    auto k_of = [&](int t, int page) { return head_base + uniform(((int64_t)page * a.geom.page_elems + (tile_key(t) & page_mask) * HD) * 2); };
 
     // The three stages of a tile -- scores S^T = K Q^T (MFMA), softmax (vector ALU), O^T += V^T P^T (MFMA) -- depend
     // on each other, and a wave alone on its SIMD issues one instruction at a time: done tile after tile, the
-    // matrix unit idles through the softmax and the vector ALU through the products.  So the loop is skewed: trip
-    // j forms the scores of tile j + 1, the softmax of tile j and the PV products of tile j - 1, three independent
-    // strands that the scheduling directives below weave into one instruction stream (one MFMA, then a few ALU
-    // instructions that execute while it runs).  Carried from trip to trip: s_cur (scores of tile j), pf_prev
-    // (P^T of tile j - 1 as bf16 terms).  K of tile t is read from the ring in trip t - 1, V in trip t + 1; trip j
-    // then refills the two 8 KB slots it has emptied with K of tile j + 3 and V of tile j + 1 (16 loads a trip,
-    // always, so that the wait at the top of a trip is a constant: all but the previous trip's loads).
-    floatx4 s_cur[2][R], s_next[2][R];
-    u32x4 pf_prev[R][PT];
+    // matrix unit idles through the softmax and the vector ALU through the products.  So the loop is skewed: trip j adds the PV
+    // products of tile j - 1 and forms the scores of tile j + 1, with the softmax of tile j woven in, a few vector instructions behind
+    // each product.  The softmax follows one row tile behind the products that read the terms of P it writes, and is ahead of
+    // the products that write the scores it reads, so one set of registers holds each of them and nothing is copied.
+    // K and V of a tile are read from the ring while the other one is multiplied (K of tile j + 1 beside the PV products, V of
+    // tile j beside the scores); a slot is requested again as soon as it has been read (K of tile j + 3, V of tile j + 2), a KB at a time
+    // between the products.  Each half starts with everything landed but the newest 24 requests.
+    // The page of a tile is looked up a trip before its K is requested; V lies a fixed distance behind K.
+    // Two products in a row add to the same accumulators (the terms of P, the slices of the head dimension): the chip's power is what a long run of
+    // this kernel is bound by, and such pairs draw less of it (a loop of products alone sustains 2.13 PFLOP/s, 2.01 with other accumulators every
+    // time); with the terms outermost the loop takes 3 % fewer cycles and a step 3 % longer.
+    // 32 requests of 16k-32k keys, 125 stacked rows, us a layer: woven by the compiler from three parts with two sets of scores, all requests at the
+    // head of a trip 693, so 658; million cycles summed over the dies 10.2 and 9.8; the step of eight layers 1.5 to 2 % shorter.
+    floatx4 s[2][R];                                      // [key block][row tile]
+    u32x4 pf[R][PT];                                      // P^T as bf16 terms
     u32x4 kreg[2][4], vreg[8];
-#pragma unroll
-    for (int rt = 0; rt < R; ++rt)
-#pragma unroll
-        for (int tm = 0; tm < PT; ++tm) pf_prev[rt][tm] = u32x4{0, 0, 0, 0};
-
-    auto pv_products = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int rt = 0; rt < R; ++rt)
-#pragma unroll
-            for (int ht = 0; ht < 8; ++ht)
-#pragma unroll
-                for (int tm = PT - 1; tm >= 0; --tm)
-                    o[ht][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vreg[ht]),
-                                                                        __builtin_bit_cast(bf16x8, pf_prev[rt][tm]), o[ht][rt], 0, 0, 0);
+    float lmax[R];
+    const char *k2 = k_of(1, page_of(1)), *k3 = k_of(2, page_of(2));     // K of tiles j + 2, j + 3 (j = -1)
+    int page4 = page_of(3);                               // page of tile j + 4
+    uint32_t odd = 0;                                     // 8192 x parity of tile j + 1: where its K lies, and V of tile j - 1
+    auto fence = []() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+    auto read_k = [&](uint32_t addr, auto piece) __attribute__((always_inline)) {
+        constexpr int F = decltype(piece)::value;
+        lds_read16<F * 1024>(kreg[F >> 2][F & 3], addr);
     };
-
-    auto trip = [&](auto qk_c, auto sm_c, auto pv_c, auto first_c, int j) __attribute__((always_inline)) {
-        constexpr bool QK = decltype(qk_c)::value, SM = decltype(sm_c)::value, PV = decltype(pv_c)::value;
-        const int slot = D == 1 ? 0 : (j + 1) & 1;
-        if (decltype(first_c)::value) wait_vmcnt<8 * D>(); else wait_vmcnt<16 * (D - 1)>();
-        __builtin_amdgcn_sched_barrier(0);
-        const unsigned char* src = ring + slot * 8192 + lane * 16;
-        if (QK) {
+    auto read_v = [&](uint32_t addr, auto piece) __attribute__((always_inline)) {
+        constexpr int F = decltype(piece)::value;
+        lds_read16<2 * 8192 + F * 1024>(vreg[F], addr);
+    };
+    auto wait_k = [&]() __attribute__((always_inline)) {
+        lds_landed(kreg[0][0]);
 #pragma unroll
-            for (int f = 0; f < 8; ++f) kreg[f >> 2][f & 3] = *reinterpret_cast<const u32x4*>(src + f * 1024);
-        }
-        if (PV) {
+        for (int f = 1; f < 8; ++f) lds_landed_too(kreg[f >> 2][f & 3]);
+    };
+    auto wait_v = [&]() __attribute__((always_inline)) {
+        lds_landed(vreg[0]);
 #pragma unroll
-            for (int f = 0; f < 8; ++f) vreg[f] = *reinterpret_cast<const u32x4*>(src + D * 8192 + f * 1024);
-        }
-        if (SM) {
-            const int key0 = kbeg + (wave + W * j) * TILE_KEYS;
-            if (key0 + TILE_KEYS > L) {   // tile touches the new rows or the end: apply visibility
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int rt = 0; rt < R; ++rt)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int key = key0 + kb * 16 + 4 * lg + i;
-                            // bitwise, not short-circuit: this must stay a compare + select chain.  (With
-                            // && / || the compiler built branches here and dropped the value of the first
-                            // element on the path "beyond L, yet visible".)
-                            const bool vis = (key <= L) | ((key >= vis_lo[rt]) & (key < vis_hi[rt]));
-                            s_cur[kb][rt][i] = vis ? s_cur[kb][rt][i] : -INFINITY;
-                        }
+        for (int f = 1; f < 8; ++f) lds_landed_too(vreg[f]);
+    };
+    // Step `step` of the softmax of row tile rt: two keys of each of its rows take 2 PT steps.
+    // P goes to the MFMA as PT bf16 terms (8 significant bits each).  One term would leave a 2^-9
+    // relative error in the output however many keys there are (V has zero mean, so the output is
+    // as small as the error's random walk): as much as the rounding of the output itself.
+    float e0, e1, sum_a, sum_b;
+    uint32_t high;
+    auto soft = [&](auto row, auto which) __attribute__((always_inline)) {
+        constexpr int rt = decltype(row)::value, step = decltype(which)::value % (2 * PT), q = decltype(which)::value / (2 * PT);
+        constexpr int i = (q & 1) * 2 + (q >> 1), t = step / 2 - 1;      // pairs of keys 0, 2, 1, 3; steps 2, 3: term 0; 4, 5: term 1
+        if constexpr (step == 0) {
+            e0 = fmaf(s[i >> 1][rt][2 * (i & 1)], scale_log2e, -mc[rt]);
+            e1 = fmaf(s[i >> 1][rt][2 * (i & 1) + 1], scale_log2e, -mc[rt]);
+        } else if constexpr (step == 1) {
+            e0 = __builtin_amdgcn_exp2f(e0);
+            e1 = __builtin_amdgcn_exp2f(e1);
+        } else if constexpr (step % 2 == 0) {
+            if constexpr (step == 2) {
+                if constexpr (q == 0) sum_a = e0 + e1;
+                else if constexpr (q == 1) sum_a += e0 + e1;
+                else if constexpr (q == 2) sum_b = e0 + e1;
+                else l_run[rt] += sum_a + (sum_b + (e0 + e1));
             }
+            high = pack2bf(e0, e1);
+            pf[rt][t][i] = high;
+        } else {
+            e0 -= __uint_as_float(high << 16);
+            e1 -= __uint_as_float(high & 0xffff0000u);
+            if constexpr (t == PT - 2) pf[rt][PT - 1][i] = pack2bf(e0, e1);
         }
-        // the slots just read are free once the reads have returned
-        __builtin_amdgcn_sched_barrier(0);
-        wait_lgkmcnt0();
-        issue_half(tile_key(j + 1 + D), 0, slot);
-        // (V of tile 0 is requested before the first trip, beside K: the trips whose turn it would be skip it)
-        if (!(decltype(first_c)::value || (D == 1 && !PV))) issue_half(tile_key(j - 1 + D), 1, slot);
-        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int kSteps = 8 * PT;                        // steps of a row tile's softmax, and its PV products
+    constexpr int GS = R == 2 ? 1 : 2;                    // row tiles whose scores are formed together
+    auto scores = [&](auto soft_c, auto read_c) __attribute__((always_inline)) {         // of tile j + 1; softmax of the last row tile of tile j
+        constexpr int NM = 8 * R, AHEAD = 8 * GS * ((R - 1) / GS), EACH = (kSteps + AHEAD - 1) / AHEAD;      // products before the last row tile's scores are written
+        static_for<NM>([&](auto mi) __attribute__((always_inline)) {
+            constexpr int m = decltype(mi)::value, grp = m / (8 * GS), gs = R - grp * GS < GS ? R - grp * GS : GS, x = m - grp * 8 * GS;
+            constexpr int kk = x % 4, kb = x / 4 % 2, rt = grp * GS + x / 8;
+            const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+            s[kb][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kreg[kb][kk]), __builtin_bit_cast(bf16x8, qf[rt][kk]),
+                                                                kk == 0 ? zero : s[kb][rt], 0, 0, 0);
+            fence();
+            if constexpr (decltype(soft_c)::value)
+                static_for<EACH>([&](auto u) __attribute__((always_inline)) {
+                    constexpr int st = m * EACH + decltype(u)::value;
+                    if constexpr (st < kSteps) { soft(std::integral_constant<int, R - 1>{}, std::integral_constant<int, st>{}); fence(); }
+                });
+            if constexpr (decltype(read_c)::value && m < 8) { read_v(ring_lane + (odd ^ 8192), mi); fence(); }
+            if constexpr (decltype(read_c)::value && m == NM / 2 - 1) wait_v();
+            if constexpr (m >= NM / 2 && m % (NM / 16) == 0 && (m - NM / 2) / (NM / 16) < 8) {
+                request(k2 + v_off, ring + 2 * 8192 + (odd ^ 8192), std::integral_constant<int, (m - NM / 2) / (NM / 16)>{});
+                fence();
+            }
+        });
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt)                    // into ordinary registers: arithmetic cannot read the accumulation ones
+            asm volatile("" : "+v"(s[0][rt]), "+v"(s[1][rt]));
+    };
+    auto products = [&](auto row, auto with) __attribute__((always_inline)) {          // PV products of a row tile, with(product) behind each
+        constexpr int rt = decltype(row)::value;
+        static_for<kSteps>([&](auto mi) __attribute__((always_inline)) {
+            constexpr int m = decltype(mi)::value, tm = PT - 1 - m % PT, ht = m / PT;
+            o[ht][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vreg[ht]), __builtin_bit_cast(bf16x8, pf[rt][tm]),
+                                                                o[ht][rt], 0, 0, 0);
+            fence();
+            with(mi);
+        });
+    };
+    auto nothing = [](auto) __attribute__((always_inline)) {};
+    const std::integral_constant<int, 0> i0;
 
-        // ---- strand 1: S^T = K Q^T of tile j + 1 (raw dot products):
-        //      s[kb][rt][i] <-> key key0 + kb*16 + 4*lg + i, row rt*16 + l16
-        if (QK) {
+    auto trip = [&](auto pv_c, int j) __attribute__((always_inline)) {
+        constexpr bool PV = decltype(pv_c)::value;
+        wait_vmcnt<24>();
+        const int key0 = kbeg + (wave + W * j) * TILE_KEYS;
+        if (key0 + TILE_KEYS > L) {   // tile touches the new rows or the end: apply visibility
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int rt = 0; rt < R; ++rt) {
-                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int kk = 0; kk < 4; ++kk)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, kreg[kb][kk]), __builtin_bit_cast(bf16x8, qf[rt][kk]), acc, 0, 0, 0);
-                    s_next[kb][rt] = acc;
-                }
-        }
-        if (SM) {
-            // Lazy reference maximum.  The softmax reference m_ref of a row is common to the 4 lane groups
-            // that share the row (they feed one MFMA accumulator) and is only moved when some score would
-            // make 2^(c(s - m_ref)) exceed 2^16 (or on the row's first visible key): fp32 has the range to
-            // spare, and the cross-lane reduction + accumulator rescale leave the per-tile path.
-            // One comparison with that score a row (it took four vector instructions; 280 -> 260 a tile besides the products): 125 stacked rows
-            // of 16k-32k keys 692 -> 682 and 689 -> 671 us a layer, 63 rows 515 -> 512.  (In the register kernel, bound by the stream: no change.)
-            bool trig = false;
-            float lmax[R];
-#pragma unroll
-            for (int rt = 0; rt < R; ++rt) {
-                lmax[rt] = max8(s_cur[0][rt], s_cur[1][rt]);
-                trig |= lmax[rt] > limit[rt];
-            }
-            if (QK) {
-#pragma unroll
-                for (int g = 0; g < 8 * R; ++g) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);     // two vector ALU instructions
-                }
-            }
-            if (__builtin_expect(__any(trig), 0)) {
-                // Move the reference.  It is kept at a whole number of log2 units, so the factor between the old and
-                // the new one is a power of two: what was accumulated against the old reference (the sums, the
-                // accumulators, and the bf16 terms of P^T whose PV products are still pending) is rescaled exactly.
-#pragma unroll
-                for (int rt = 0; rt < R; ++rt) {
-                    float mx = lmax[rt];
-                    mx = fmaxf(mx, __shfl_xor(mx, 16));
-                    mx = fmaxf(mx, __shfl_xor(mx, 32));
-                    const bool seen = limit[rt] > -INFINITY, some = mx > -INFINITY;
-                    const float to = ceilf(mx * scale_log2e), mc_new = !some ? mc[rt] : seen ? fmaxf(mc[rt], to) : to;
-                    const int shift = (int)fmaxf(mc[rt] - mc_new, -200.f);
-                    const float alpha = seen ? ldexpf(1.0f, shift) : 0.f;
-                    l_run[rt] *= alpha;
-#pragma unroll
-                    for (int ht = 0; ht < 8; ++ht) {
-                        // The accumulators live in the accumulation registers, which arithmetic cannot read.  The empty
-                        // statement pins their copy to ordinary registers here, on the rare path (the compiler otherwise
-                        // makes those 32 R copies at the head of every trip of the loop, needed or not).
-                        floatx4 t = o[ht][rt];
-                        asm volatile("" : "+v"(t));
-                        o[ht][rt] = t * alpha;
-                    }
-                    if (PV) {
-#pragma unroll
-                        for (int tm = 0; tm < PT; ++tm)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const uint32_t w = pf_prev[rt][tm][i];
-                                const float lo = __builtin_bit_cast(float, w << 16) * alpha;
-                                const float hi = __builtin_bit_cast(float, w & 0xffff0000u) * alpha;
-                                pf_prev[rt][tm][i] = (__builtin_bit_cast(uint32_t, lo) >> 16) | (__builtin_bit_cast(uint32_t, hi) & 0xffff0000u);
-                            }
-                    }
-                    mc[rt] = mc_new;
-                    limit[rt] = (seen | some) ? (mc_new + 16.0f) * unscale : -INFINITY;
-                }
-            }
-        }
-        // ---- strand 2: softmax of tile j;  strand 3: PV products of tile j - 1
-        u32x4 pf_cur[R][PT];
-        if (SM) {
-#pragma unroll
-            for (int rt = 0; rt < R; ++rt) {
-                floatx2 p[4];
-                float psum = 0.f;
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    p[i] = floatx2{__builtin_amdgcn_exp2f(fmaf(s_cur[0][rt][2 * i], scale_log2e, -mc[rt])),
-                                   __builtin_amdgcn_exp2f(fmaf(s_cur[0][rt][2 * i + 1], scale_log2e, -mc[rt]))};
-                    p[2 + i] = floatx2{__builtin_amdgcn_exp2f(fmaf(s_cur[1][rt][2 * i], scale_log2e, -mc[rt])),
-                                       __builtin_amdgcn_exp2f(fmaf(s_cur[1][rt][2 * i + 1], scale_log2e, -mc[rt]))};
-                    psum += (p[i].x + p[i].y) + (p[2 + i].x + p[2 + i].y);
-                }
-                l_run[rt] += psum;
-                // P goes to the MFMA as PT bf16 terms (8 significant bits each).  One term would leave a 2^-9
-                // relative error in the output however many keys there are (V has zero mean, so the output is
-                // as small as the error's random walk): as much as the rounding of the output itself.
-#pragma unroll
-                for (int tm = 0; tm < PT; ++tm)
+                for (int rt = 0; rt < R; ++rt)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const bf16x2 hb = __builtin_convertvector(p[i], bf16x2);
-                        pf_cur[rt][tm][i] = __builtin_bit_cast(uint32_t, hb);
-                        if (tm < PT - 1) p[i] = p[i] - __builtin_convertvector(hb, floatx2);
+                        const int key = key0 + kb * 16 + 4 * lg + i;
+                        // bitwise, not short-circuit: this must stay a compare + select chain.  (With
+                        // && / || the compiler built branches here and dropped the value of the first
+                        // element on the path "beyond L, yet visible".)
+                        const bool vis = (key <= L) | ((key >= vis_lo[rt]) & (key < vis_hi[rt]));
+                        s[kb][rt][i] = vis ? s[kb][rt][i] : -INFINITY;
                     }
+        }
+        // Lazy reference maximum.  The softmax reference m_ref of a row is common to the 4 lane groups
+        // that share the row (they feed one MFMA accumulator) and is only moved when some score would
+        // make 2^(c(s - m_ref)) exceed 2^16 (or on the row's first visible key): fp32 has the range to
+        // spare, and the cross-lane reduction + accumulator rescale leave the per-tile path.
+        // One comparison with that score a row (it took four vector instructions; 280 -> 260 a tile besides the products): 125 stacked rows
+        // of 16k-32k keys 692 -> 682 and 689 -> 671 us a layer, 63 rows 515 -> 512.  (In the register kernel, bound by the stream: no change.)
+        bool trig = false;
+        fence();
+        auto first = [&](auto mi) __attribute__((always_inline)) {
+            constexpr int m = decltype(mi)::value;
+            if constexpr (m < 8) { read_k(ring_lane + odd, mi); fence(); }
+            else if constexpr (m < 8 + R) {
+                lmax[m - 8] = max8(s[0][m - 8], s[1][m - 8]);
+                trig |= lmax[m - 8] > limit[m - 8];
+                fence();
+            }
+        };
+        if constexpr (PV) products(i0, first);
+        else static_for<kSteps>(first);
+        wait_k();
+        if (__builtin_expect(__any(trig), 0)) {
+            // Move the reference.  It is kept at a whole number of log2 units, so the factor between the old and
+            // the new one is a power of two: what was accumulated against the old reference (the sums, the
+            // accumulators, and the bf16 terms of P^T whose PV products are still pending) is rescaled exactly.
+#pragma unroll
+            for (int rt = 0; rt < R; ++rt) {
+                float mx = lmax[rt];
+                mx = fmaxf(mx, __shfl_xor(mx, 16));
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const bool seen = limit[rt] > -INFINITY, some = mx > -INFINITY;
+                const float to = ceilf(mx * scale_log2e), mc_new = !some ? mc[rt] : seen ? fmaxf(mc[rt], to) : to;
+                const int shift = (int)fmaxf(mc[rt] - mc_new, -200.f);
+                const float alpha = seen ? ldexpf(1.0f, shift) : 0.f;
+                l_run[rt] *= alpha;
+#pragma unroll
+                for (int ht = 0; ht < 8; ++ht) {
+                    // The accumulators live in the accumulation registers, which arithmetic cannot read.  The empty
+                    // statement pins their copy to ordinary registers here, on the rare path (the compiler otherwise
+                    // makes those 32 R copies at the head of every trip of the loop, needed or not).
+                    floatx4 t = o[ht][rt];
+                    asm volatile("" : "+v"(t));
+                    o[ht][rt] = t * alpha;
+                }
+                if (PV && rt > 0) {
+#pragma unroll
+                    for (int tm = 0; tm < PT; ++tm)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t w = pf[rt][tm][i];
+                            const float lo = __builtin_bit_cast(float, w << 16) * alpha;
+                            const float hi = __builtin_bit_cast(float, w & 0xffff0000u) * alpha;
+                            pf[rt][tm][i] = (__builtin_bit_cast(uint32_t, lo) >> 16) | (__builtin_bit_cast(uint32_t, hi) & 0xffff0000u);
+                        }
+                }
+                mc[rt] = mc_new;
+                limit[rt] = (seen | some) ? (mc_new + 16.0f) * unscale : -INFINITY;
             }
         }
-        if (PV) pv_products();
-        if (SM && PV) {
-#pragma unroll
-            for (int g = 0; g < 8 * PT * R; ++g) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x402, PT == 3 ? 3 : 4, 0);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (SM) {
-#pragma unroll
-            for (int rt = 0; rt < R; ++rt)
-#pragma unroll
-                for (int tm = 0; tm < PT; ++tm) pf_prev[rt][tm] = pf_cur[rt][tm];
-        }
-        if (QK) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int rt = 0; rt < R; ++rt) s_cur[kb][rt] = s_next[kb][rt];
-        }
+        fence();
+        static_for<R - 1>([&](auto prev) __attribute__((always_inline)) {
+            constexpr int rt = decltype(prev)::value + 1, N = kSteps * (R - 1);
+            auto behind = [&](auto mi) __attribute__((always_inline)) {
+                constexpr int m = decltype(mi)::value, at = kSteps * (rt - 1) + m;
+                soft(prev, mi);
+                fence();
+                if constexpr (at % (N / 8) == N / 8 - 1 && at / (N / 8) < 8) {
+                    request(k3, ring + odd, std::integral_constant<int, at / (N / 8)>{});
+                    fence();
+                }
+            };
+            if constexpr (PV) products(std::integral_constant<int, rt>{}, behind);
+            else static_for<kSteps>(behind);
+        });
+        wait_vmcnt<24>();
+        fence();
+        scores(std::true_type{}, std::true_type{});
+        odd ^= 8192;
+        k2 = k3;
+        k3 = k_of(j + 4, page4);
+        page4 = page_of(j + 5);
+        fence();
     };
-
-    {
-        constexpr std::true_type yes{};
-        constexpr std::false_type no{};
-        issue_half(tile_key(0), 0, 0);
-        if (D == 2) issue_half(tile_key(1), 0, 1);
-        issue_half(tile_key(0), 1, 0);
-        if (n_my > 0) {
-            trip(yes, no, no, yes, -1);
-            if (n_my == 1) {
-                trip(no, yes, no, no, 0);
-                trip(no, no, yes, no, 1);
-            } else {
-                trip(yes, yes, no, no, 0);
-                for (int j = 1; j <= n_my - 2; ++j) trip(yes, yes, yes, no, j);
-                trip(no, yes, yes, no, n_my - 1);
-                trip(no, no, yes, no, n_my);
-            }
-        }
-        wait_vmcnt<0>();                                  // the ring is about to be reused for the merge
+    if (n_my > 0) {
+        const char* k1 = k_of(0, page_of(0));
+        static_for<8>([&](auto f) __attribute__((always_inline)) { request(k1, ring, f); });
+        static_for<8>([&](auto f) __attribute__((always_inline)) { request(k2, ring + 8192, f); });
+        static_for<8>([&](auto f) __attribute__((always_inline)) { request(k1 + v_off, ring + 2 * 8192, f); });
+        wait_vmcnt<16>();
+        fence();
+        static_for<8>([&](auto f) __attribute__((always_inline)) { read_k(ring_lane, f); });
+        wait_k();
+        fence();
+        static_for<8>([&](auto f) __attribute__((always_inline)) { request(k3, ring, f); });
+        scores(std::false_type{}, std::false_type{});
+        odd = 8192;
+        k2 = k3;
+        k3 = k_of(3, page4);
+        page4 = page_of(4);
+        fence();
+        trip(std::false_type{}, 0);
+        for (int j = 1; j < n_my; ++j) trip(std::true_type{}, j);
+        static_for<R>([&](auto rt) __attribute__((always_inline)) { products(rt, nothing); });
     }
+    wait_vmcnt<0>();                                      // the ring is about to be reused for the merge
 
     // ---- merge the waves of the group through LDS (maxima in log2 units from here on) ----
     float m_run[R];
@@ -933,8 +947,8 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
         const int R = b.row_groups == 1 ? std::max(tiles, a.min_row_tiles) : (tiles + b.row_groups - 1) / b.row_groups;
         const int items = a.grid_items > 0 ? a.grid_items : a.n_work;
         dim3 grid((items * a.Hkv + 7) / 8 * 8 * b.row_groups);
-        auto launch = [&](auto kern, int r, int waves, int depth) -> hipError_t {
-            const size_t lds = std::max((size_t)waves * HD * (16 * r + 1) * sizeof(float), (size_t)waves * depth * kTileBytes);
+        auto launch = [&](auto kern, int r, int waves) -> hipError_t {
+            const size_t lds = std::max((size_t)waves * HD * (16 * r + 1) * sizeof(float), (size_t)waves * 2 * kTileBytes);
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(kern, grid, dim3(64 * waves), lds, st, b, sl2);
@@ -952,10 +966,10 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
         if (b.row_groups > 1 || R >= 4) {
             switch (R) {
                 case 1: e = launch_regs(attn_bf16_regs_kernel<1, false>, 1); break;
-                case 2: e = launch(attn_bf16_kernel<2, 2, 2, 2>, 2, 2, 2); break;
-                case 3: e = launch(attn_bf16_kernel<3, 2, 2, 2>, 3, 2, 2); break;
-                default: e = a.row_items ? launch(attn_bf16_kernel<4, 2, 2, 3>, 4, 2, 2)
-                           : once ? launch(attn_bf16_kernel<4, 2, 2, 2, true>, 4, 2, 2) : launch(attn_bf16_kernel<4, 2, 2, 2>, 4, 2, 2); break;
+                case 2: e = launch(attn_bf16_kernel<2, 2, 2>, 2, 2); break;
+                case 3: e = launch(attn_bf16_kernel<3, 2, 2>, 3, 2); break;
+                default: e = a.row_items ? launch(attn_bf16_kernel<4, 2, 3>, 4, 2)
+                           : once ? launch(attn_bf16_kernel<4, 2, 2, true>, 4, 2) : launch(attn_bf16_kernel<4, 2, 2>, 4, 2); break;
             }
         } else {
             switch (R) {

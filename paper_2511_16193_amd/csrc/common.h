@@ -141,16 +141,43 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 }
 __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
-// 4 KB from global memory straight into LDS: four wave-wide loads of 16 bytes per lane.  src is the lane's own
-// address (base + 16 * lane), dst the wave's LDS base; lane l's bytes land at dst + 16 * l + the immediate.
-template <int POLICY = 0>
-__device__ __forceinline__ void dma4(const char* src, __attribute__((address_space(3))) void* dst) {
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 0, POLICY);
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 1024, POLICY);
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 2048, POLICY);
-    __builtin_amdgcn_global_load_lds((const void*)src, dst, 16, 3072, POLICY);
+// LDS reads placed by hand, with hand-placed waits: the compiler would wait for every request that is in flight into LDS before a read of
+// it.  It takes the registers as written at once, so what is read is waited for in the basic block that reads it (a branch in between may
+// copy registers still in flight).
+template <int OFF> __device__ __forceinline__ void lds_read16(u32x4& d, uint32_t addr) {
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
+}
+__device__ __forceinline__ void lds_landed(u32x4& d) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d)); }
+__device__ __forceinline__ void lds_landed_too(u32x4& d) { asm volatile("" : "+v"(d)); }     // no use of d moves above the wait
+
+// 1 KB from global memory straight into LDS: lane l's 16 bytes at base + lane_off go to LDS address lds + 16 l (base and lds the same for
+// all lanes).  dma1_lanes: only the lanes of a mask that is not empty.
+// Both write m0, and the second exec: reserved registers, which the compiler takes no clobber for.  So they are for kernels in which
+// nothing else uses m0 (no builtin that loads into LDS, whose m0 the compiler may carry from one to the next), and dma1_lanes for places
+// that all 64 lanes of the wave reach: exec is all ones before it and after it.
+// STREAM: with the hint of load_stream.
+template <bool STREAM = false>
+__device__ __forceinline__ void dma1(const char* base, uint32_t lane_off, uint32_t lds) {
+    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
+}
+template <bool STREAM = false>
+__device__ __forceinline__ void dma1_lanes(uint64_t lanes, const char* base, uint32_t lane_off, uint32_t lds) {
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\ts_mov_b64 exec, -1"
+                     : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
+                     : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
 }
 
+// KB F (0 to 3) of 4 KB that lie together on both sides, in order: the first sets m0, the others add their offset to it and to base.
+template <int F, bool STREAM = false>
+__device__ __forceinline__ void dma_piece(const char* base, uint32_t lane_off, uint32_t lds) {
+    if constexpr (F == 0) dma1<STREAM>(base, lane_off, lds);
+    else if constexpr (STREAM) asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2 nt" : : "v"(lane_off), "s"(base), "n"(F * 1024) : "memory");
+    else asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" : : "v"(lane_off), "s"(base), "n"(F * 1024) : "memory");
+}
 // 16 bytes per lane from base + lane_off + off, off the same for all lanes, through a buffer descriptor over [base, base + bytes).
 // base: the same for all lanes.  The caller keeps off inside the range: only lane_off is checked against it.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {

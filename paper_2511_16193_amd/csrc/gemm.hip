@@ -404,33 +404,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ws_glu_mixed_kernel(
 constexpr int kTallFills = 3;                             // fills in the LDS ring
 constexpr int kTallSlices = 2;                            // 16-wide slices per fill
 
-template <int OFF> __device__ __forceinline__ void lds_read16(u32x4& d, uint32_t addr) {
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
-}
-__device__ __forceinline__ void lds_landed(u32x4& d) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d)); }
-__device__ __forceinline__ void lds_landed_too(u32x4& d) { asm volatile("" : "+v"(d)); }     // no use of d moves above the wait
-
-// 1 KB from global memory straight into LDS: lane l's 16 bytes at base + lane_off go to LDS address lds + 16 l (base and lds the same for
-// all lanes).  dma1_lanes: only the lanes of a mask that is not empty.
-// Both write m0, and the second exec: reserved registers, which the compiler takes no clobber for.  So they are for kernels in which
-// nothing else uses m0 (no builtin that loads into LDS, whose m0 the compiler may carry from one to the next), and dma1_lanes for places
-// that all 64 lanes of the wave reach: exec is all ones before it and after it.
-// STREAM: with the hint of load_stream.
-template <bool STREAM = false>
-__device__ __forceinline__ void dma1(const char* base, uint32_t lane_off, uint32_t lds) {
-    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_off), "s"(base) : "memory");
-}
-template <bool STREAM = false>
-__device__ __forceinline__ void dma1_lanes(uint64_t lanes, const char* base, uint32_t lane_off, uint32_t lds) {
-    if constexpr (STREAM)
-        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\ts_mov_b64 exec, -1"
-                     : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
-                     : : "s"(lds), "v"(lane_off), "s"(base), "s"(lanes) : "memory");
-}
-
 template <bool GLU, int RW>
 __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Wp, float* __restrict__ out,
                                                     int M, int N, int K, int k_per_split, int m0, int tn, int sp) {
