@@ -497,11 +497,13 @@ __device__ __forceinline__ void gemm_bf16_tall_body(const bf16_t* __restrict__ A
     // texture path takes one every 17 cycles from the whole work-group, and a wave whose request waits there does not
     // multiply.  Weights first, so that a lane holds one
     // row and four consecutive features.
+    // The features turn round with each row operand, so that two products in a row differ in one operand only: less power drawn, which is what
+    // bounds the large launches (a loop of products alone 2.01 -> 2.05 PFLOP/s; steps of 2304 rows and prefills 0.7 to 0.9 % shorter).
     auto multiply = [&](auto half, auto set, uint32_t base) __attribute__((always_inline)) {
         constexpr int H = decltype(half)::value, S = decltype(set)::value, NM = 4 * RW, NR = H == 0 ? RW : RW + 4;
         __builtin_amdgcn_sched_barrier(0);
         static_for<NM>([&](auto mi) __attribute__((always_inline)) {
-            constexpr int m = decltype(mi)::value, i = m & 3, j = m >> 2;
+            constexpr int m = decltype(mi)::value, j = m >> 2, i = (j + H * RW) & 1 ? 3 - (m & 3) : m & 3;
             acc[i][H * RW + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[S][i]), __builtin_bit_cast(bf16x8, a[H][j]),
                                                                          acc[i][H * RW + j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -852,7 +854,7 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_bf16_strip_kernel(const bf16_t
         b_addr = b_off + slot * FILL;
         __builtin_amdgcn_sched_barrier(0);
         static_for<NM>([&](auto mi) __attribute__((always_inline)) {
-            constexpr int m = decltype(mi)::value, i = m % FS, j = m / FS;
+            constexpr int m = decltype(mi)::value, j = m / FS, i = j & 1 ? FS - 1 - m % FS : m % FS;
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[S][i]), __builtin_bit_cast(bf16x8, a[S][j]), acc[i][j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             constexpr int first = m < NR ? m : NR, last = m + 1 == NM ? NR : m + 1 < NR ? m + 1 : NR;
