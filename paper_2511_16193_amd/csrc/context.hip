@@ -1063,6 +1063,10 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     const bool f32_qkv = f32 && gemm_f32_fuses(T, qkvw, d, kF32Qkv);
     const bool f32_up = f32 && !few && gemm_f32_fuses(T, m.d_ff, d, kF32Glu);
     auto norm_by = [&](const void* gain) { return F32Norm{(const float*)gain, m.rms_eps}; };
+    // a few rows of a packed dense model: likewise (`lean`)
+    const bool lean = c->packed && m.n_experts == 0 && c->gemm_tile < 0;
+    auto lean_ok = [&](const void* W, int N, int K, FewForm form, bool norm) { return lean && direct_loads(W) && few_rows_ok(T, N, K, form, norm); };
+    auto few_norm = [&](const void* gain) { return FewNorm{(const bf16_t*)gain, m.rms_eps}; };
 
     RopeAppend ra;
     ra.qkv_part = part; ra.S = 1; ra.rope = c->at<float>(L.rope); ra.row_slot = c->at<int32_t>(L.row_slot);
@@ -1071,6 +1075,11 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     if (f32_qkv) {
         ProfScope prof(c, SV_PROF_GEMM);
         SV_HIP(c, gemm_f32_qkv(h, (const float*)c->wqkv[l], d, norm_by(c->ln1[l]), ra, st));
+    } else if (lean_ok(c->wqkv[l], qkvw, d, kFewQkv, false)) {
+        const bool fused = pending == 0 && few_rows_ok(T, qkvw, d, kFewQkv, true);
+        if (!fused) SV_TRY(add_norm(c, T, pending, c->ln1[l]));
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, few_rows_qkv(fused ? (const void*)h : a_norm, (const bf16_t*)c->wqkv[l], d, fused ? few_norm(c->ln1[l]) : FewNorm{}, ra, c->cold, st));
     } else {
         SV_TRY(add_norm(c, T, pending, c->ln1[l]));
         SV_TRY(gemm(c, a_norm, c->wqkv[l], part, T, qkvw, d, &ra.S));
@@ -1100,10 +1109,14 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     if (f32 && !few) {
         ProfScope prof(c, SV_PROF_GEMM);
         SV_HIP(c, gemm_f32((const float*)aa.out, (const float*)c->wo[l], h, T, d, qw, true, F32Norm{}, st));
+    } else if (!few && lean_ok(c->wo[l], d, qw, kFewAdd, false)) {
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, few_rows_add((const bf16_t*)aa.out, (const bf16_t*)c->wo[l], h, T, d, qw, c->cold, st));
     } else {
         SV_TRY(gemm(c, aa.out, c->wo[l], part, T, d, qw, &s_o));
     }
-    if (!f32_up) SV_HIP(c, add_rmsnorm(h, part, s_o, c->ln2[l], a_norm, m.dtype, T, d, m.rms_eps, c->packed, st, last));
+    const bool lean_up = !few && s_o == 0 && lean_ok(c->wgu[l], 2 * m.d_ff, d, kFewGlu, true);
+    if (!f32_up && !lean_up) SV_HIP(c, add_rmsnorm(h, part, s_o, c->ln2[l], a_norm, m.dtype, T, d, m.rms_eps, c->packed, st, last));
     if (m.n_experts > 0) {
         MoeArgs ma;
         ma.a = (const bf16_t*)a_norm; ma.w_router = (const bf16_t*)c->wrouter[l];
@@ -1119,7 +1132,10 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         pending = -1;
         return SV_OK;
     }
-    if (c->packed && m.d_ff % 64 == 0) {
+    if (lean_up) {
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, few_rows_glu(h, (const bf16_t*)c->wgu[l], c->at<bf16_t>(L.act), T, m.d_ff, d, few_norm(c->ln2[l]), c->cold, st));
+    } else if (c->packed && m.d_ff % 64 == 0) {
         // gate/up projection with SwiGLU in its epilogue: the [T, 2F] fp32 intermediate never exists
         ProfScope prof(c, SV_PROF_GEMM);
         const GateUp g = m.d_ff % 128 == 0 ? gate_up_launch(c, T, direct_loads(c->wgu[l])) : GateUp{};
@@ -1139,6 +1155,11 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
         int s_gu = 1;
         SV_TRY(gemm(c, a_norm, c->wgu[l], part, T, 2 * m.d_ff, d, &s_gu));
         SV_HIP(c, swiglu(part, s_gu, c->at<void>(L.act), T, m.d_ff, c->packed, st));
+    }
+    if (!few && lean_ok(c->wdown[l], d, m.d_ff, kFewAdd, false)) {
+        ProfScope prof(c, SV_PROF_GEMM);
+        SV_HIP(c, few_rows_add(c->at<bf16_t>(L.act), (const bf16_t*)c->wdown[l], h, T, d, m.d_ff, c->cold, st));
+        return SV_OK;
     }
     SV_TRY(gemm(c, c->at<void>(L.act), c->wdown[l], part, T, d, m.d_ff, &pending));
     return SV_OK;

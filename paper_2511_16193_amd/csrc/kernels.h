@@ -93,6 +93,19 @@ hipError_t set_i32(int32_t* p, int32_t v, hipStream_t st);
 // seq_len[request's sequence] += the request's rows (end of a prefill pass)
 hipError_t add_rows(int32_t* seq_len, const int32_t* req, int B, hipStream_t st);
 
+// ---- few.hip ----
+// Projections of up to 16 rows (packed weights that start at 16 bytes).  norm.gain != null: `in` are up to 8 fp32 residual rows, normalised
+// on the way in; else packed operands.  few_rows_ok: the shapes that each form takes (N features of the matrix)
+struct FewNorm { const bf16_t* gain; float eps; };
+enum FewForm { kFewAdd, kFewGlu, kFewQkv };
+bool few_rows_ok(int M, int N, int K, FewForm form, bool norm);
+// QKV projection, rotary embedding and append (rope.qkv_part unused)
+hipError_t few_rows_qkv(const void* in, const bf16_t* W, int K, const FewNorm& norm, const RopeAppend& rope, bool cold, hipStream_t st);
+// h [M][N] += act W^T
+hipError_t few_rows_add(const bf16_t* act, const bf16_t* W, float* h, int M, int N, int K, bool cold, hipStream_t st);
+// act = silu(gate) * up of the normalised rows, packed
+hipError_t few_rows_glu(const float* h, const bf16_t* W, bf16_t* act, int M, int F, int K, const FewNorm& norm, bool cold, hipStream_t st);
+
 // ---- attention.hip ----
 constexpr int kItemInts = 8;
 struct AttnArgs {
