@@ -346,7 +346,7 @@ __global__ __launch_bounds__(256, R == 1 ? 2 : 1) void attn_bf16_regs_kernel(Att
 }
 
 // R row tiles per work-group, W waves, two slots per wave for K and for V in the LDS ring (W * 32 KB of LDS).
-// Run as W = 2: two work-groups share a CU.
+// Run as W = 2, two work-groups to a CU, and in a small prefill as W = 4.
 // ONCE: no other row group or item reads these keys, and they come from HBM: as a stream (load_stream; 63 rows of 256 requests 497 -> 445 us; with a second
 // row group to find them in L2 685 -> 703).
 // PT: bf16 terms the softmax weights are split into for the PV products.  With four row tiles (or several row
@@ -934,6 +934,13 @@ bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic, int step
     return !force_generic && dtype == 1 && hd == HD && page_size % TILE_KEYS == 0 && (page_size & (page_size - 1)) == 0 && step_rows <= kStepRows;
 }
 
+// Up to here a prefill's work-groups are all resident, and as long as their longest: four waves share its keys instead of two (one work-group a CU).
+// One prompt of 777 tokens, 340 work-groups, 44.0 -> 38.4 us a layer, its last rows' 8 in the last one 48 -> 33; seven layers with the first
+// token's step, one prompt of 300 / 600 / 1100 tokens 2490 / 3215 / 4369 -> 2460 / 3172 / 4334 us.  Beyond, where places are
+// scarce, two waves; and where the keys are few, whose merge is then the larger part (eight prompts of 60 to 150 tokens, 384 work-groups, 3717
+// with two waves, 3759 with four).
+constexpr int kPrefillFew = 512, kPrefillLong = 256;
+
 hipError_t attention(const AttnArgs& a, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)a.hd);
     const int G = a.Hq / a.Hkv;
@@ -968,7 +975,7 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
                 case 1: e = launch_regs(attn_bf16_regs_kernel<1, false>, 1); break;
                 case 2: e = launch(attn_bf16_kernel<2, 2, 2>, 2, 2); break;
                 case 3: e = launch(attn_bf16_kernel<3, 2, 2>, 3, 2); break;
-                default: e = a.row_items ? launch(attn_bf16_kernel<4, 2, 3>, 4, 2)
+                default: e = a.row_items ? (items * a.Hkv <= kPrefillFew && a.longest >= kPrefillLong ? launch(attn_bf16_kernel<4, 4, 3>, 4, 4) : launch(attn_bf16_kernel<4, 2, 3>, 4, 2))
                            : once ? launch(attn_bf16_kernel<4, 2, 2, true>, 4, 2) : launch(attn_bf16_kernel<4, 2, 2>, 4, 2); break;
             }
         } else {

@@ -345,6 +345,7 @@ struct sv_ctx {
     int n_work;                                           // attention work items staged for the current pass
     int n_last_work;                                      // prefill: items behind them that hold the last rows asked for; -1: no room for the list
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
+    int longest_work;                                     // most keys of an item
     size_t weight_bytes, expert_bytes;                    // of all layers and the LM head; of one expert in all layers
     bool cold;                                            // what the current pass reads once comes from HBM (see kCacheBytes)
     int gemm_variant;                                     // -1 = choose per shape
@@ -842,6 +843,7 @@ static void build_work(sv_ctx* c, const Pass& ps, int32_t* req, int32_t* work) {
     std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.len > y.len; });
     for (size_t i = 0; i < items.size(); ++i) memcpy(work + i * kItemInts, items[i].v, sizeof(items[i].v));
     c->n_work = (int)items.size();
+    c->longest_work = items.empty() || m.n_experts > 0 ? 0 : items[0].len;      // (models with experts keep their waves: see pick_chunk)
     c->n_last_work = 0;
     for (const Item& it : items) c->n_last_work += it.last;
     if (c->n_work + c->n_last_work > L.max_items) { c->n_last_work = -1; return; }
@@ -890,7 +892,7 @@ static int stage_pass(sv_ctx* c, const Pass& ps) {
         memcpy(q, v, sizeof(v));
         t0 += r.n;
     }
-    c->n_work = c->n_last_work = 0;
+    c->n_work = c->n_last_work = c->longest_work = 0;
     c->pass_merge = false;
     c->cold = reads_past_cache(c, ps);
     if (attn_mfma_ok(c->model.dtype, c->model.head_dim, c->rt.page_size, c->attn_generic,
@@ -1027,7 +1029,7 @@ static AttnArgs attn_args(const sv_ctx* c, const Pass& ps, int layer, const void
     aa.T = ps.T; aa.n_max = ps.n_max; aa.k = ps.k; aa.Hq = m.n_q_heads; aa.Hkv = m.n_kv_heads; aa.hd = m.head_dim; aa.dtype = m.dtype;
     aa.work = c->at<int32_t>(L.stage) + L.st_work; aa.n_work = c->n_work;
     aa.last_of = nullptr; aa.n_last = 0; aa.last_out = nullptr;
-    aa.row_items = ps.n == 0; aa.merge = c->pass_merge; aa.cold = c->cold;
+    aa.row_items = ps.n == 0; aa.merge = c->pass_merge; aa.longest = c->longest_work; aa.cold = c->cold;
     aa.n_work_dev = nullptr; aa.grid_items = 0;
     if (c->graph_launch_shape) {      // nothing in the launch may depend on the lengths
         aa.n_work_dev = c->at<int32_t>(L.stage);

@@ -128,6 +128,7 @@ struct AttnArgs {
     int grid_items;                     // when > 0: items the grid is sized for (an upper bound of the item count)
     bool row_items;                     // prefill: an item is 64 stacked rows of a request, whose keys end at the last one it sees
     bool merge;                         // some request has several pieces
+    int longest;                        // most keys of an item
     bool cold;                          // the keys and values come from HBM (see kCacheBytes)
     const int32_t* last_of; int n_last; // when set (the last layer of a prefill): only the last rows of the first n_last requests of that
     void* last_out;                     //       table are wanted, in rows 0 .. n_last - 1 of this buffer, which is not `out` (work: items that hold them)
