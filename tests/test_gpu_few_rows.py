@@ -1,8 +1,12 @@
 """A dense decoder layer over up to sixteen rows: norm, rotary, append and residual inside the projections."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2511_16193_amd as P
+from harness import Case, LOGIT_TOL
+from oracle import verify as OV
+import workloads as W
 
 pytestmark = pytest.mark.gpu
 DEV, THETA, EPS = "cuda:0", 1.0e4, 1.0e-6
@@ -79,3 +83,19 @@ def test_layer_against_float64(rows, d, hq, hkv, hd, ff):
     gate, up = (_norm(h1, w["ln2"]) @ w["w_gate_up"].double().T).chunk(2, -1)
     want = h1 + _round(torch.nn.functional.silu(gate) * up) @ w["w_down"].double().T
     assert float((got - want).norm() / (want - h0).norm()) < 2.0 ** -8
+
+
+@pytest.mark.parametrize("cached,lens", [([0], [8]), ([70, 3, 0], [7, 5, 3]), ([40], [1])])       # 8, 15 and 1 rows
+def test_prefill_of_a_few_rows_is_the_oracles_causal_pass(cached, lens):
+    shape = W.Shape("few-bf16", 2, 256, 8, 2, 128, 512, 2048, dtype="bf16", batch=len(lens), k=4, seed=91)
+    case = Case(shape, cached, verify_mode=OV.STOCHASTIC, synthetic_kv=True, extra_tokens=24, packed=True)
+    prompts = W.make_tokens((len(lens), max(lens)), shape.vocab, shape.seed, "prompt")
+    lo = np.stack([OV.prefill(case.spec, case.wn, case.caches[b], prompts[b, :n])[-1] for b, n in enumerate(lens)])
+    ld = case.ver.prefill_batch(list(range(len(lens))), torch.from_numpy(prompts).to(torch.int32), lens).cpu().numpy()
+    assert np.max(np.abs(lo - ld)) < LOGIT_TOL["bf16"]
+    for b, n in enumerate(lens):
+        for layer in range(shape.n_layers):
+            kd, vd = case.ver.kv_read(b, layer, cached[b], n)
+            ko, vo = case.caches[b].k[layer][cached[b]:cached[b] + n], case.caches[b].v[layer][cached[b]:cached[b] + n]
+            assert np.max(np.abs(kd.float().cpu().numpy() - ko)) < 0.03 and np.max(np.abs(vd.float().cpu().numpy() - vo)) < 0.03
+    case.close()
