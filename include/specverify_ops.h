@@ -47,18 +47,22 @@ int sv_op_gemm_plan(int M, int N, int K, int *splits, int *wide, int *row_tiles)
 /* The better launch, of the weight-streaming and the tall kernel, for a packed projection of M rows (HOST pointers out).
  * form 0: QKV, O or down (the reduction may be split), 1: LM head, 2: gate/up with SwiGLU (N = 2 d_ff gate and up rows).
  * tall[0] != 0: sv_op_gemm_bf16_tall with these tiles and *splits; tall[0] == 0: sv_op_gemm_bf16_ws with *splits, *wide and
- * *row_tiles, or for form 2 sv_op_gemm_bf16_tall without tiles.  A step may take a strip in its place: sv_op_gemm_step_launch says
- * what it really launches.  Host arithmetic only.  N % 128 == 0 (form 2: 256), K % 64 == 0. */
+ * *row_tiles, or for form 2 sv_op_gemm_bf16_tall without tiles.  A step may take a strip or a launch for a few rows in its place:
+ * sv_op_gemm_step_launch says what it really launches.  Host arithmetic only.  N % 128 == 0 (form 2: 256), K % 64 == 0. */
 int sv_op_gemm_step_plan(int M, int N, int K, int form, int *splits, int *wide, int *row_tiles, int *tall);
 
-/* The launch that a verification step, or a prefill pass, makes for a packed projection of M rows (out: HOST pointer).  form, N, K as
- * above; tile_mode as SV_OPT_GEMM_TILE; experts: of a model with experts; aligned: weights that start at 16 bytes.
+/* The launch that a verification step, or a prefill pass, makes for a packed projection of M rows (out: HOST pointer).  N, K as above; form
+ * as above, but 0 is O or down and 4 is QKV (they differ in SV_GEMM_FEW alone); tile_mode as SV_OPT_GEMM_TILE; experts: of a model with
+ * experts; aligned: weights that start at 16 bytes.
  *   SV_GEMM_WS     sv_op_gemm_bf16_ws with splits, wide and row_tiles; form 2: sv_op_gemm_bf16_tall without tiles
  *   SV_GEMM_TALL   sv_op_gemm_bf16_tall with tall and splits
  *   SV_GEMM_STRIP  sv_op_gemm_bf16_strip with row_tiles, features and splits
+ *   SV_GEMM_FEW    up to 16 rows of a dense model: a launch that norm, rotary and append or the residual ride in, with no entry point of its
+ *                  own (sv_op_layer runs it).  Not gate/up behind an O that does not take it, and neither O, gate/up nor down where the last
+ *                  layer of a prefill goes on with the prompts' last rows only
  * A field that the kernel has no use for is 0.  (Where a workspace has no room for the splits, a step takes fewer.)
  * Host arithmetic only. */
-enum sv_gemm_kernel { SV_GEMM_WS = 0, SV_GEMM_TALL = 1, SV_GEMM_STRIP = 2 };
+enum sv_gemm_kernel { SV_GEMM_WS = 0, SV_GEMM_TALL = 1, SV_GEMM_STRIP = 2, SV_GEMM_FEW = 3 };
 typedef struct { int kernel, splits, wide, row_tiles, features, tall[4]; } sv_gemm_launch;
 int sv_op_gemm_step_launch(int M, int N, int K, int form, int tile_mode, int experts, int aligned, sv_gemm_launch *out);
 
@@ -187,7 +191,8 @@ int sv_probe_mfma_valu(float *sink, int iters, int valu_per_mfma, int waves_per_
  *   SV_OPT_GEMM_VARIANT  work-group tile of the row-major bf16 projections (0..2; -1 = per shape, default)
  *   SV_OPT_GEMM_TILE  kernels of the packed projections: -1 = as the launch plan expects it to pay (default), 0 = the
  *                     weight-streaming kernel only, 1 = the tall kernel with 256-row tiles wherever the shape allows (output features a multiple
- *                     of 256).  Weights that do not start at 16 bytes take the weight-streaming kernel in every mode
+ *                     of 256).  0 and 1 also keep up to 16 rows of a dense model in launches apart from norm, rotary and residual.  Weights
+ *                     that do not start at 16 bytes take the weight-streaming kernel in every mode
  *   SV_OPT_ATTN_GENERIC  1 = always use the generic attention, a work-group per row and head (default 0)
  *   SV_OPT_ATTN_MIN_ROW_TILES  lower bound (1..4) on the 16-row tiles the bf16 attention is built for
  *   SV_OPT_ATTN_MAX_ROW_TILES  most 16-row tiles (1..4, default 4) one work-group of the bf16 attention takes;

@@ -449,8 +449,8 @@ def op_gemm_bf16_strip(a_packed: torch.Tensor, w_packed: torch.Tensor, M: int, r
 
 def op_gemm_step_plan(M: int, N: int, K: int, form: int = 0) -> dict:
     """The better of the weight-streaming and the tall launch for a packed projection (form 0: QKV, O, down; 1: LM head; 2: gate/up,
-    N = 2 d_ff): {"splits", "wide", "row_tiles", "tall"}, tall = (h, n, ht, nt) or None.  A step may take a strip instead:
-    op_gemm_step_launch."""
+    N = 2 d_ff): {"splits", "wide", "row_tiles", "tall"}, tall = (h, n, ht, nt) or None.  A step may take a strip or a launch for a few rows
+    instead: op_gemm_step_launch."""
     s, w, t, tiles = C.c_int(), C.c_int(), C.c_int(), (C.c_int * 4)()
     rc = lib().sv_op_gemm_step_plan(M, N, K, form, C.byref(s), C.byref(w), C.byref(t), tiles)
     if rc != 0:
@@ -459,13 +459,13 @@ def op_gemm_step_plan(M: int, N: int, K: int, form: int = 0) -> dict:
 
 
 def op_gemm_step_launch(M: int, N: int, K: int, form: int = 0, *, tile_mode: int = -1, experts: bool = False, aligned: bool = True) -> dict:
-    """The launch a step makes for a packed projection (form as above): {"kernel": "ws", "tall" or "strip", "splits", "wide", "row_tiles",
-    "features", "tall"}.  tile_mode: SV_OPT_GEMM_TILE; experts: of a model with experts; aligned: weights at 16 bytes."""
+    """The launch a step makes for a packed projection (form as above, but 0: O or down, 4: QKV): {"kernel": "ws", "tall", "strip" or "few",
+    "splits", "wide", "row_tiles", "features", "tall"}.  "few": norm, rotary or residual ride in it; it has no entry point of its own.  tile_mode: SV_OPT_GEMM_TILE; experts: of a model with experts; aligned: weights at 16 bytes."""
     g = SvGemmLaunch()
     rc = lib().sv_op_gemm_step_launch(M, N, K, form, tile_mode, 1 if experts else 0, 1 if aligned else 0, C.byref(g))
     if rc != 0:
         raise SvError(rc, "sv_op_gemm_step_launch")
-    return {"kernel": ("ws", "tall", "strip")[g.kernel], "splits": g.splits, "wide": bool(g.wide), "row_tiles": g.row_tiles,
+    return {"kernel": ("ws", "tall", "strip", "few")[g.kernel], "splits": g.splits, "wide": bool(g.wide), "row_tiles": g.row_tiles,
             "features": g.features, "tall": tuple(g.tall) if g.tall[0] else None}
 
 

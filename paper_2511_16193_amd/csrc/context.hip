@@ -1048,6 +1048,11 @@ static bool last_rows_only(const sv_ctx* c, const Pass& ps) {
     return ps.last > 0 && c->n_last_work >= 0 && tiles <= c->lay.P && 2 * tiles <= ps.T;
 }
 
+// Does a layer send this projection of M rows to the launch that takes norm, rotary, append or residual along?  (norm: rows that it normalises itself)
+static bool takes_few_rows(int M, int N, int K, FewForm form, bool norm, int tile_mode, bool experts, bool aligned) {
+    return !experts && tile_mode < 0 && aligned && few_rows_ok(M, N, K, form, norm);
+}
+
 // One decoder layer over the prepared rows.  On entry the residual stream h lacks `pending` (see add_norm) of
 // the previous layer; on exit it lacks this layer's feed-forward output, described by the new `pending`.
 static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
@@ -1065,9 +1070,10 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     const bool f32_qkv = f32 && gemm_f32_fuses(T, qkvw, d, kF32Qkv);
     const bool f32_up = f32 && !few && gemm_f32_fuses(T, m.d_ff, d, kF32Glu);
     auto norm_by = [&](const void* gain) { return F32Norm{(const float*)gain, m.rms_eps}; };
-    // a few rows of a packed dense model: likewise (`lean`)
-    const bool lean = c->packed && m.n_experts == 0 && c->gemm_tile < 0;
-    auto lean_ok = [&](const void* W, int N, int K, FewForm form, bool norm) { return lean && direct_loads(W) && few_rows_ok(T, N, K, form, norm); };
+    // a few rows of a packed dense model: likewise
+    auto lean_ok = [&](const void* W, int N, int K, FewForm form, bool norm) {
+        return c->packed && takes_few_rows(T, N, K, form, norm, c->gemm_tile, m.n_experts > 0, direct_loads(W));
+    };
     auto few_norm = [&](const void* gain) { return FewNorm{(const bf16_t*)gain, m.rms_eps}; };
 
     RopeAppend ra;
@@ -1411,6 +1417,8 @@ extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int*
     return SV_OK;
 }
 
+constexpr int kFormQkv = 4;                               // a step's launch only: where QKV may take another kernel than O and down
+
 static bool step_form_ok(int M, int N, int K, int form) {
     return M > 0 && N > 0 && K > 0 && form >= 0 && form <= 2 && N % (form == 2 ? 256 : 128) == 0 && K % 64 == 0;
 }
@@ -1426,7 +1434,13 @@ extern "C" int sv_op_gemm_step_plan(int M, int N, int K, int form, int* splits, 
 }
 
 extern "C" int sv_op_gemm_step_launch(int M, int N, int K, int form, int tile_mode, int experts, int aligned, sv_gemm_launch* out) {
+    const bool qkv = form == kFormQkv;
+    if (qkv) form = 0;
     if (!out || !step_form_ok(M, N, K, form) || tile_mode < -1 || tile_mode > 1) return SV_EINVAL;
+    if (form != 1 && takes_few_rows(M, N, K, form == 2 ? kFewGlu : qkv ? kFewQkv : kFewAdd, form == 2, tile_mode, experts != 0, aligned != 0)) {
+        *out = sv_gemm_launch{SV_GEMM_FEW, 1, 0, 0, 0, {0, 0, 0, 0}};
+        return SV_OK;
+    }
     WsPlan p{1, false, 0, 0.0, 0.0, {}, {}};
     if (form == 2) {
         const GateUp g = plan_gate_up(M, N, K, tile_mode, aligned != 0);

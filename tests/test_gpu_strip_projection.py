@@ -95,7 +95,8 @@ def test_strips_that_do_not_exist_are_refused(tiles, features, splits):
 @pytest.mark.parametrize("rows", [5, 100, 200, 400])
 def test_weights_that_start_off_16_bytes_keep_the_weight_streaming_kernel(rows):
     """One decoding step with packed projections 8 bytes past a 16-byte boundary: the bits of the step that is told to take that kernel
-    everywhere, and within the step tests' tolerance of the step with the same weights on the boundary (which takes strips, and tall tiles from 200 rows on)."""
+    everywhere, and within the step tests' tolerance of the step with the same weights on the boundary (which takes the launches for a few rows at 5, else strips, and tall tiles
+    from 200 rows on)."""
     import paper_2511_16193_amd as P
     d, ff, V = 256, 2048, 4096
     lw = {"ln1": bf16((d,), 0.05, 1) + 1, "wqkv": bf16((512, d), 0.02, 2), "wo": bf16((d, 256), 0.02, 3),

@@ -34,18 +34,22 @@ ROWS = [1, 5, 33, 40, 96, 97, 128, 129, 147, 160, 161, 192, 200, 256, 289, 320, 
 
 
 @pytest.mark.parametrize("experts", [False, True])
-@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("form", [0, 1, 2, 4])
 def test_step_launches_are_launchable(form, experts):
-    """What a step really launches: each of the three kernels occurs, in a form that it takes, and where it is not a strip it is the
-    launch that op_gemm_step_plan gives."""
+    """What a step really launches: each of the kernels occurs, in a form that it takes, and where it is neither a strip nor the launch for a
+    few rows it is the launch that op_gemm_step_plan gives."""
     seen = set()
     for M in ROWS:
-        for N, K in SHAPES[form]:
-            p, wide = op_gemm_step_launch(M, N, K, form, experts=experts), op_gemm_step_plan(M, N, K, form)
+        for N, K in SHAPES[form & 3]:
+            p, wide = op_gemm_step_launch(M, N, K, form, experts=experts), op_gemm_step_plan(M, N, K, form & 3)
             s, at = p["splits"], (M, N, K, form, p)
             seen.add(p["kernel"])
-            assert 1 <= s <= 16 and (form == 0 or s == 1), at
-            if p["kernel"] == "strip":
+            assert 1 <= s <= 16 and (form in (0, 4) or s == 1), at
+            if p["kernel"] == "few":
+                assert M <= (8 if form == 2 else 16) and form != 1 and not experts, at
+                assert (s, p["wide"], p["row_tiles"], p["features"], p["tall"]) == (1, False, 0, 0, None), at
+                assert op_gemm_step_launch(M, N, K, form, tile_mode=0)["kernel"] == "ws", at
+            elif p["kernel"] == "strip":
                 assert p["features"] in (128, 160, 224) and p["row_tiles"] in (1, 2, 3, 4, 5, 6, 8, 10), at
                 assert p["row_tiles"] * 32 >= M > 32 * (p["row_tiles"] - (1 if p["row_tiles"] <= 6 else 2)) and M <= 320, at
                 assert K % (32 * s) == 0 and p["tall"] is None and not p["wide"], at
@@ -56,7 +60,22 @@ def test_step_launches_are_launchable(form, experts):
             else:
                 assert wide["tall"] is None and p["features"] == 0 and p["tall"] is None, at
                 assert (s, p["wide"], p["row_tiles"]) == (wide["splits"], wide["wide"], wide["row_tiles"]), at
-    assert seen >= ({"strip", "tall"} if form == 2 else {"ws", "tall", "strip"})
+    assert seen >= ({"strip", "tall"} if form == 2 else {"ws", "tall", "strip"}) and ("few" in seen) == (form != 1 and not experts)
+
+
+@pytest.mark.parametrize("N,K,form,most", [
+    (4608, 3584, 4, 16), (3584, 3584, 0, 16), (37888, 3584, 2, 8), (3584, 18944, 0, 8),          # QKV, O, gate/up and down of the 7B-shaped decoder
+    (7168, 5120, 4, 16), (5120, 5120, 0, 8), (55296, 5120, 2, 8), (5120, 27648, 0, 8),           # of the 32B-shaped one
+    (10240, 5120, 4, 0), (10240, 5120, 0, 0),                              # more than 8192 features
+    (37888, 6208, 2, 0), (57600, 3584, 2, 0),                              # rows too wide to be normalised inside; more gate features than 7 x 16 x 256
+    (4096, 128, 4, 0), (152064, 3584, 1, 0),                               # no step for every wave; an LM head
+])
+def test_a_few_rows(N, K, form, most):
+    """Up to `most` rows norm, rotary or residual ride in the projection, unless experts, the option or the weights' alignment forbid it."""
+    for M in (1, 5, 8, 9, 12, 16, 17):
+        assert (op_gemm_step_launch(M, N, K, form)["kernel"] == "few") == (M <= most), (M, N, K, form)
+        for kw in (dict(experts=True), dict(aligned=False), dict(tile_mode=0), dict(tile_mode=1)):
+            assert op_gemm_step_launch(M, N, K, form, **kw)["kernel"] != "few", (M, N, K, form, kw)
 
 
 @pytest.mark.parametrize("tile_mode", [-1, 0, 1])
@@ -72,8 +91,8 @@ def test_weights_off_16_bytes_keep_the_kernel_with_ordinary_loads(form, tile_mod
 
 
 @pytest.mark.parametrize("F,K,kernels", [
-    (18944, 3584, {5: "strip", 96: "strip", 160: "strip", 161: "strip", 320: "strip", 321: "tall"}),
-    (27648, 5120, {5: "strip", 160: "strip", 192: "strip", 321: "tall"}),
+    (18944, 3584, {9: "strip", 96: "strip", 160: "strip", 161: "strip", 320: "strip", 321: "tall"}),
+    (27648, 5120, {9: "strip", 160: "strip", 192: "strip", 321: "tall"}),
     (28672, 8192, {5: "strip", 160: "strip"}),                             # 256 strips of 112 features
     (29568, 8192, {5: "ws", 64: "ws", 96: "ws", 160: "ws", 161: "tall", 320: "tall"}),       # 462 strips, a last round of 206
     (32768, 4096, {5: "ws", 160: "ws"}),                                   # 256 strips of the weight-streaming kernel: one round
@@ -91,14 +110,15 @@ def test_gate_up_takes_strips_where_they_are_measured_to_pay(F, K, kernels):
 
 
 def test_strips_of_short_reductions():
-    """Up to 4096 inputs strips of one, two or five row tiles, if the weights are 24 MB; longer ones take strips up to 160 rows."""
-    for M in ROWS:
+    """Beyond a few rows: up to 4096 inputs strips of one, two or five row tiles, if the weights are 24 MB; longer ones take strips up to
+    160 rows."""
+    for M in ROWS[2:]:
         for N, K in [(4608, 3584), (3584, 3584), (6144, 4096), (4096, 4096)]:
             assert (op_gemm_step_launch(M, N, K)["kernel"] == "strip") == (M <= 64 or 129 <= M <= 160), (M, N, K)
         for N, K in [(5120, 2048), (2048, 4096), (1152, 896), (2048, 1024)]:
             p, wide = op_gemm_step_launch(M, N, K), op_gemm_step_plan(M, N, K)
             assert p["kernel"] != "strip" and (p["splits"], p["tall"]) == (wide["splits"], wide["tall"]), (M, N, K, p)
-    for M in (5, 40, 96, 160):
+    for M in (17, 40, 96, 160):
         for N, K in [(3584, 18944), (5120, 27648), (4096, 14336), (7168, 5120), (10240, 8192)] + [(896, 4864), (2048, 11008)] * (M < 160):
             assert op_gemm_step_launch(M, N, K)["kernel"] == "strip", (M, N, K)
     assert op_gemm_step_launch(320, 3584, 18944)["kernel"] == "strip"
