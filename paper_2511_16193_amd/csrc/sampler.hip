@@ -144,7 +144,7 @@ __device__ __forceinline__ Stat row_stat(const SampleArgs& a, int row, float inv
     for (int i = 0; i < a.stat_parts; ++i) {
         const float m = in[i][0];
         const int am = __float_as_int(in[i][2]);
-        if (m > r.m || (m == r.m && am < r.am)) r.am = am;
+        r.am = m > r.m ? am : r.am;
         r.m = fmaxf(r.m, m);
     }
 #pragma unroll 8
@@ -289,9 +289,11 @@ __device__ __forceinline__ Draw draw_of(const SampleArgs& a, int idx) {
 // rounding of its argument, near 120, is the larger error: 1e-5).  A wave shares its best score; it runs
 // the logarithms for a few of its ids only.  One draw per request over 152064 ids, with both logarithms for every id
 // before: 256 requests 186 -> 112 us, 128 requests 86 -> 66, one request 29 -> 19 (start-up chain: verdict, row, parts).
-// The test starts from the score of the row's most likely id, which the statistics name: every wave began with none, and worked its way up
-// through half a dozen rounds of logarithms.  Where that id holds most of the probability 256 requests take 117 -> 86 us, 128 requests
-// 79 -> 58, match draws of 147 rows 66 -> 52 and of 96 rows 55 -> 46, five requests 17.3 -> 15.4.
+// The test starts from a lower bound of the score of the row's most likely id, which the statistics name: every wave began with none, and
+// worked its way up through half a dozen rounds of logarithms.  Where that id holds 0.9 of the probability 256 requests take 95 -> 68 us, 128
+// requests 71 -> 55, five 17.2 -> 12.6, match draws of 147 rows 67 -> 52 and of 96 rows 51 -> 41; in flat rows (logits of standard deviation 0.3), which the
+// bound does not help, 94.0 -> 93.7, 70.3 -> 70.5, 16.9 -> 18.1, 66 -> 66, 51 -> 51.  (Its exact score, by the library's logarithms, and branches over the parts for
+// the id cost flat rows 3 to 4 us: code that runs once is mostly waited for.)
 template <bool ROWS>
 __global__ __launch_bounds__(NS) void race_kernel(SampleArgs a) {
     const Draw d = draw_of<ROWS>(a, blockIdx.x);
@@ -333,15 +335,15 @@ __global__ __launch_bounds__(NS) void race_kernel(SampleArgs a) {
     auto uniform_of = [](uint64_t seed) __attribute__((always_inline)) {
         return ((float)(uint32_t)(splitmix_finalise(seed) >> 32) + 0.5f) * 2.3283064365386963e-10f;
     };
-    // e^(a score that the row's winner has at least): the wave's best, and from the start that of the most likely id, whichever part holds it
+    // e^(a score that the row's winner has at least): the wave's best, and from the start a lower bound of that of the most likely id, whichever
+    // part holds it: p a thousandth too small, and at least as much as -log1p(-U) in the place of it (U + U^2 / 2 + ... below 2^-8).
     float floor_p = 0.f, floor_r = 0.f;
     if ((unsigned)st.am < (unsigned)V) {
-        const float ln_e = logf(-log1pf(-uniform_of(key + (uint64_t)(st.am + 1) * kStride)));
-        floor_p = expf(-log_sum - ln_e);
-        if (d.rejected) {
-            const float w = expf(-log_sum) - (d.qrow ? d.qrow[st.am] : st.am == d.xrej ? 1.0f : 0.0f);
-            if (w > 0.f) floor_r = expf(logf(w) - ln_e);
-        }
+        const float U = uniform_of(key + (uint64_t)(st.am + 1) * kStride);
+        const float over_e = __builtin_amdgcn_rcpf(U < 0.00390625f ? U * 1.005f : __builtin_amdgcn_logf(1.0f - U) * -0.694f);
+        const float p = __builtin_amdgcn_rcpf(st.s) * 0.999f;
+        floor_p = p * over_e;
+        if (d.rejected) floor_r = fmaxf(0.f, (p - (d.qrow ? d.qrow[st.am] : st.am == d.xrej ? 1.0f : 0.0f)) * over_e);
     }
     float thr_p = floor_p, thr_r = floor_r;
     auto four = [&](int v, const Ids& t) __attribute__((always_inline)) {

@@ -1,4 +1,4 @@
-"""The exponential race where one id holds most of the probability, so that its score rules the others out from the start."""
+"""The exponential race where one id holds most of the probability, so that its score rules the others out from the start, and where none does."""
 import numpy as np
 import pytest
 import torch
