@@ -477,6 +477,8 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
     // K and V of a tile are read from the ring while the other one is multiplied (K of tile j + 1 beside the PV products, V of
     // tile j beside the scores); a slot is requested again as soon as it has been read (K of tile j + 3, V of tile j + 2), a KB at a time
     // between the products.  Each half starts with everything landed but the newest 24 requests.
+    // The last trip forms no scores and requests nothing more (with 63 to 125 rows of 256 requests behind 60 to 200 keys, two to four tiles a wave, that is
+    // 1 to 3 % of the launch).
     // The page of a tile is looked up a trip before its K is requested; V lies a fixed distance behind K.
     // Two products in a row add to the same accumulators (the terms of P, the slices of the head dimension): the chip's power is what a long run of
     // this kernel is bound by, and such pairs draw less of it (a loop of products alone sustains 2.13 PFLOP/s, 2.01 with other accumulators every
@@ -541,14 +543,17 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
     };
     constexpr int kSteps = 8 * PT;                        // steps of a row tile's softmax, and its PV products
     constexpr int GS = R == 2 ? 1 : 2;                    // row tiles whose scores are formed together
-    auto scores = [&](auto soft_c, auto read_c) __attribute__((always_inline)) {         // of tile j + 1; softmax of the last row tile of tile j
+    // of tile j + 1; softmax of the last row tile of tile j.  LAST: there is no tile j + 1
+    auto scores = [&](auto soft_c, auto read_c, auto last_c) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last_c)::value;
         constexpr int NM = 8 * R, AHEAD = 8 * GS * ((R - 1) / GS), EACH = (kSteps + AHEAD - 1) / AHEAD;      // products before the last row tile's scores are written
         static_for<NM>([&](auto mi) __attribute__((always_inline)) {
-            constexpr int m = decltype(mi)::value, grp = m / (8 * GS), gs = R - grp * GS < GS ? R - grp * GS : GS, x = m - grp * 8 * GS;
+            constexpr int m = decltype(mi)::value, grp = m / (8 * GS), x = m - grp * 8 * GS;
             constexpr int kk = x % 4, kb = x / 4 % 2, rt = grp * GS + x / 8;
             const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-            s[kb][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kreg[kb][kk]), __builtin_bit_cast(bf16x8, qf[rt][kk]),
-                                                                kk == 0 ? zero : s[kb][rt], 0, 0, 0);
+            if constexpr (!LAST)
+                s[kb][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kreg[kb][kk]), __builtin_bit_cast(bf16x8, qf[rt][kk]),
+                                                                    kk == 0 ? zero : s[kb][rt], 0, 0, 0);
             fence();
             if constexpr (decltype(soft_c)::value)
                 static_for<EACH>([&](auto u) __attribute__((always_inline)) {
@@ -557,14 +562,15 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
                 });
             if constexpr (decltype(read_c)::value && m < 8) { read_v(ring_lane + (odd ^ 8192), mi); fence(); }
             if constexpr (decltype(read_c)::value && m == NM / 2 - 1) wait_v();
-            if constexpr (m >= NM / 2 && m % (NM / 16) == 0 && (m - NM / 2) / (NM / 16) < 8) {
+            if constexpr (!LAST && m >= NM / 2 && m % (NM / 16) == 0 && (m - NM / 2) / (NM / 16) < 8) {
                 request(k2 + v_off, ring + 2 * 8192 + (odd ^ 8192), std::integral_constant<int, (m - NM / 2) / (NM / 16)>{});
                 fence();
             }
         });
+        if constexpr (!LAST)
 #pragma unroll
-        for (int rt = 0; rt < R; ++rt)                    // into ordinary registers: arithmetic cannot read the accumulation ones
-            asm volatile("" : "+v"(s[0][rt]), "+v"(s[1][rt]));
+            for (int rt = 0; rt < R; ++rt)                // into ordinary registers: arithmetic cannot read the accumulation ones
+                asm volatile("" : "+v"(s[0][rt]), "+v"(s[1][rt]));
     };
     auto products = [&](auto row, auto with) __attribute__((always_inline)) {          // PV products of a row tile, with(product) behind each
         constexpr int rt = decltype(row)::value;
@@ -579,9 +585,9 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
     auto nothing = [](auto) __attribute__((always_inline)) {};
     const std::integral_constant<int, 0> i0;
 
-    auto trip = [&](auto pv_c, int j) __attribute__((always_inline)) {
-        constexpr bool PV = decltype(pv_c)::value;
-        wait_vmcnt<24>();
+    auto trip = [&](auto pv_c, auto last_c, int j) __attribute__((always_inline)) {
+        constexpr bool PV = decltype(pv_c)::value, LAST = decltype(last_c)::value;
+        if constexpr (!LAST) wait_vmcnt<24>();
         const int key0 = kbeg + (wave + W * j) * TILE_KEYS;
         if (key0 + TILE_KEYS > L) {   // tile touches the new rows or the end: apply visibility
 #pragma unroll
@@ -608,8 +614,9 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
         fence();
         auto first = [&](auto mi) __attribute__((always_inline)) {
             constexpr int m = decltype(mi)::value;
-            if constexpr (m < 8) { read_k(ring_lane + odd, mi); fence(); }
-            else if constexpr (m < 8 + R) {
+            if constexpr (m < 8) {
+                if constexpr (!LAST) { read_k(ring_lane + odd, mi); fence(); }
+            } else if constexpr (m < 8 + R) {
                 lmax[m - 8] = max8(s[0][m - 8], s[1][m - 8]);
                 trig |= lmax[m - 8] > limit[m - 8];
                 fence();
@@ -617,7 +624,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
         };
         if constexpr (PV) products(i0, first);
         else static_for<kSteps>(first);
-        wait_k();
+        if constexpr (!LAST) wait_k();
         if (__builtin_expect(__any(trig), 0)) {
             // Move the reference.  It is kept at a whole number of log2 units, so the factor between the old and
             // the new one is a power of two: what was accumulated against the old reference (the sums, the
@@ -663,7 +670,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
                 constexpr int m = decltype(mi)::value, at = kSteps * (rt - 1) + m;
                 soft(prev, mi);
                 fence();
-                if constexpr (at % (N / 8) == N / 8 - 1 && at / (N / 8) < 8) {
+                if constexpr (!LAST && at % (N / 8) == N / 8 - 1 && at / (N / 8) < 8) {
                     request(k3, ring + odd, std::integral_constant<int, at / (N / 8)>{});
                     fence();
                 }
@@ -671,9 +678,10 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
             if constexpr (PV) products(std::integral_constant<int, rt>{}, behind);
             else static_for<kSteps>(behind);
         });
-        wait_vmcnt<24>();
+        wait_vmcnt<LAST ? 16 : 24>();
         fence();
-        scores(std::true_type{}, std::true_type{});
+        scores(std::true_type{}, std::true_type{}, last_c);
+        if constexpr (LAST) return;
         odd ^= 8192;
         k2 = k3;
         k3 = k_of(j + 4, page4);
@@ -691,14 +699,19 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_kernel(AttnArgs a, float 
         wait_k();
         fence();
         static_for<8>([&](auto f) __attribute__((always_inline)) { request(k3, ring, f); });
-        scores(std::false_type{}, std::false_type{});
+        scores(std::false_type{}, std::false_type{}, std::false_type{});
         odd = 8192;
         k2 = k3;
         k3 = k_of(3, page4);
         page4 = page_of(4);
         fence();
-        trip(std::false_type{}, 0);
-        for (int j = 1; j < n_my; ++j) trip(std::true_type{}, j);
+        if (n_my == 1) {
+            trip(std::false_type{}, std::true_type{}, 0);
+        } else {
+            trip(std::false_type{}, std::false_type{}, 0);
+            for (int j = 1; j < n_my - 1; ++j) trip(std::true_type{}, std::false_type{}, j);
+            trip(std::true_type{}, std::true_type{}, n_my - 1);
+        }
         static_for<R>([&](auto rt) __attribute__((always_inline)) { products(rt, nothing); });
     }
     wait_vmcnt<0>();                                      // the ring is about to be reused for the merge
