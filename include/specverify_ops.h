@@ -39,6 +39,10 @@ int sv_op_gemm_bf16(const void *A, const void *W, float *out, int M, int N, int 
 int sv_op_gemm_bf16_ws(const void *Ap, const void *Wp, float *out, int M, int N, int K, int splits, int wide,
                        int row_tiles, void *stream);
 
+/* Waves (2 or 4; HOST pointers) of a work-group of a dense bf16 model's prefill attention, whose items (64 stacked rows and a piece of their keys)
+ * hold these numbers of keys, in any order; each item is n_kv_heads work-groups.  Host arithmetic only. */
+int sv_op_prefill_waves(const int *keys, int items, int n_kv_heads, int *waves);
+
 /* A launch shape for sv_op_gemm_bf16_ws of M rows onto N features over K inputs (HOST pointers out: reduction splits,
  * 256- or 128-feature strips, 32-row tiles per work-group -- 8 = 256-row tall tiles, where they fill the chip four times
  * over).  sv_op_gemm_step_plan gives the launch of a verification step.  Host arithmetic only.  N % 128 == 0, K % 64 == 0. */

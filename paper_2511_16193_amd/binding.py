@@ -26,7 +26,7 @@ EXPORTS = [
     "verify_kv_pool_bytes", "verify_workspace_bytes", "verify_init", "verify_destroy", "verify_last_error",
     "verify_seq_add", "verify_seq_remove", "verify_seq_set_len", "verify_seq_len", "verify_kv_write",
     "verify_kv_read", "verify_prefill", "verify_prefill_batch", "verify_step", "sv_workspace_bytes",
-    "sv_op_gemm_bf16", "sv_op_gemm_bf16_ws", "sv_op_gemm_plan", "sv_op_gemm_step_plan", "sv_op_gemm_step_launch", "sv_op_gemm_bf16_tall", "sv_op_gemm_bf16_strip", "sv_op_pack_rows", "sv_op_pack_weight", "sv_op_sample_scratch_bytes", "sv_op_sample", "sv_op_sample_static", "sv_op_moe_scratch_bytes", "sv_op_moe_ffn", "sv_op_attention", "sv_op_layer", "sv_op_rollback", "sv_set_option", "sv_seq_set_lens", "sv_profile_enable",
+    "sv_op_gemm_bf16", "sv_op_gemm_bf16_ws", "sv_op_prefill_waves", "sv_op_gemm_plan", "sv_op_gemm_step_plan", "sv_op_gemm_step_launch", "sv_op_gemm_bf16_tall", "sv_op_gemm_bf16_strip", "sv_op_pack_rows", "sv_op_pack_weight", "sv_op_sample_scratch_bytes", "sv_op_sample", "sv_op_sample_static", "sv_op_moe_scratch_bytes", "sv_op_moe_ffn", "sv_op_attention", "sv_op_layer", "sv_op_rollback", "sv_set_option", "sv_seq_set_lens", "sv_profile_enable",
     "sv_profile_read", "sv_probe_mfma_bf16", "sv_probe_hbm_copy", "sv_probe_hbm_read", "sv_probe_mfma_valu",
     "sv_plan_accept_prob", "sv_plan_tau", "sv_plan_decoupled", "sv_plan_best_window", "sv_fit_affine",
 ]
@@ -111,6 +111,7 @@ def load_library() -> C.CDLL:
     lib.sv_op_pack_rows.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p]
     lib.sv_op_gemm_bf16_ws.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int,
                                        C.c_void_p]
+    lib.sv_op_prefill_waves.argtypes = [C.POINTER(C.c_int), C.c_int, C.c_int, C.POINTER(C.c_int)]
     lib.sv_op_gemm_plan.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
     lib.sv_op_gemm_step_plan.argtypes = [C.c_int] * 4 + [C.POINTER(C.c_int)] * 4
     lib.sv_op_gemm_step_launch.argtypes = [C.c_int] * 7 + [C.POINTER(SvGemmLaunch)]
@@ -467,6 +468,15 @@ def op_gemm_step_launch(M: int, N: int, K: int, form: int = 0, *, tile_mode: int
         raise SvError(rc, "sv_op_gemm_step_launch")
     return {"kernel": ("ws", "tall", "strip", "few")[g.kernel], "splits": g.splits, "wide": bool(g.wide), "row_tiles": g.row_tiles,
             "features": g.features, "tall": tuple(g.tall) if g.tall[0] else None}
+
+
+def op_prefill_waves(keys, n_kv_heads: int) -> int:
+    """Waves of a work-group of a dense model's prefill attention over items of these numbers of keys."""
+    w = C.c_int()
+    rc = lib().sv_op_prefill_waves((C.c_int * len(keys))(*keys), len(keys), n_kv_heads, C.byref(w))
+    if rc != 0:
+        raise SvError(rc, "sv_op_prefill_waves")
+    return w.value
 
 
 def op_gemm_plan(M: int, N: int, K: int) -> dict:

@@ -947,12 +947,23 @@ bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic, int step
     return !force_generic && dtype == 1 && hd == HD && page_size % TILE_KEYS == 0 && (page_size & (page_size - 1)) == 0 && step_rows <= kStepRows;
 }
 
-// Up to here a prefill's work-groups are all resident, and as long as their longest: four waves share its keys instead of two (one work-group a CU).
-// One prompt of 777 tokens, 340 work-groups, 44.0 -> 38.4 us a layer, its last rows' 8 in the last one 48 -> 33; seven layers with the first
-// token's step, one prompt of 300 / 600 / 1100 tokens 2490 / 3215 / 4369 -> 2460 / 3172 / 4334 us.  Beyond, where places are
-// scarce, two waves; and where the keys are few, whose merge is then the larger part (eight prompts of 60 to 150 tokens, 384 work-groups, 3717
-// with two waves, 3759 with four).
-constexpr int kPrefillFew = 512, kPrefillLong = 256;
+// Four waves take most of a CU's LDS: one work-group a CU, where two waves leave room for another.  So up to 256 work-groups, each as long as its keys,
+// they run in half the time (one prompt's last rows, 8 work-groups, 48 -> 33 us), but for the few keys of whose time the merge of the waves is the
+// larger part.  Of 257 to 512 some wait for a place, shortest last: still ahead where the pairs that share one are no longer than the longest alone
+// (one prompt of 777 tokens, 340 work-groups, 44.0 -> 38.4 us; of 1100, 484, 7 us a layer less), behind where all are alike (pieces of 832 to 1100 keys in 300 to 512
+// work-groups 5 to 12 us more, of 260 to 400 keys, four prompts, 2 to 6) -- until the keys are so many that a lone work-group's pace decides (4200 to
+// 5440 keys 3 less to 1 more, 8160 and up 7 to 43 less).  us a layer in a prefill, over 2 to 16 kv heads.
+constexpr int kPrefillLong = 256, kPrefillPairs = 512, kPrefillEndless = 4096;
+
+bool prefill_four_waves(const int* keys, int items, int Hkv) {
+    constexpr int CUS = 256;
+    const long long wgs = (long long)items * Hkv;
+    if (items == 0 || wgs > 2 * CUS || keys[0] < kPrefillLong) return false;
+    if (wgs <= CUS || keys[0] >= kPrefillEndless) return true;
+    int pair = 0;                                         // most keys of two that share a place
+    for (int i = CUS; i < wgs; ++i) pair = std::max(pair, keys[i / Hkv] + keys[(2 * CUS - 1 - i) / Hkv]);
+    return keys[0] >= kPrefillPairs && 10 * pair <= 11 * keys[0];
+}
 
 hipError_t attention(const AttnArgs& a, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)a.hd);
@@ -988,7 +999,7 @@ hipError_t attention(const AttnArgs& a, hipStream_t st) {
                 case 1: e = launch_regs(attn_bf16_regs_kernel<1, false>, 1); break;
                 case 2: e = launch(attn_bf16_kernel<2, 2, 2>, 2, 2); break;
                 case 3: e = launch(attn_bf16_kernel<3, 2, 2>, 3, 2); break;
-                default: e = a.row_items ? (items * a.Hkv <= kPrefillFew && a.longest >= kPrefillLong ? launch(attn_bf16_kernel<4, 4, 3>, 4, 4) : launch(attn_bf16_kernel<4, 2, 3>, 4, 2))
+                default: e = a.row_items ? (a.four_waves ? launch(attn_bf16_kernel<4, 4, 3>, 4, 4) : launch(attn_bf16_kernel<4, 2, 3>, 4, 2))
                            : once ? launch(attn_bf16_kernel<4, 2, 2, true>, 4, 2) : launch(attn_bf16_kernel<4, 2, 2>, 4, 2); break;
             }
         } else {

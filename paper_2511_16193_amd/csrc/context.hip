@@ -345,7 +345,7 @@ struct sv_ctx {
     int n_work;                                           // attention work items staged for the current pass
     int n_last_work;                                      // prefill: items behind them that hold the last rows asked for; -1: no room for the list
     bool pass_merge;                                      // some request of it has its keys cut into several pieces
-    int longest_work;                                     // most keys of an item
+    bool four_waves, last_four_waves;                     // prefill: waves of the work-groups over these items, over those behind them
     size_t weight_bytes, expert_bytes;                    // of all layers and the LM head; of one expert in all layers
     bool cold;                                            // what the current pass reads once comes from HBM (see kCacheBytes)
     int gemm_variant;                                     // -1 = choose per shape
@@ -843,9 +843,17 @@ static void build_work(sv_ctx* c, const Pass& ps, int32_t* req, int32_t* work) {
     std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.len > y.len; });
     for (size_t i = 0; i < items.size(); ++i) memcpy(work + i * kItemInts, items[i].v, sizeof(items[i].v));
     c->n_work = (int)items.size();
-    c->longest_work = items.empty() || m.n_experts > 0 ? 0 : items[0].len;      // (models with experts keep their waves: see pick_chunk)
     c->n_last_work = 0;
     for (const Item& it : items) c->n_last_work += it.last;
+    if (prefill && m.n_experts == 0) {                    // (models with experts keep their waves: see pick_chunk)
+        std::vector<int> keys, last_keys;
+        for (const Item& it : items) {
+            keys.push_back(it.len);
+            if (it.last) last_keys.push_back(it.len);
+        }
+        c->four_waves = prefill_four_waves(keys.data(), c->n_work, m.n_kv_heads);
+        c->last_four_waves = prefill_four_waves(last_keys.data(), c->n_last_work, m.n_kv_heads);
+    }
     if (c->n_work + c->n_last_work > L.max_items) { c->n_last_work = -1; return; }
     int at = c->n_work;
     for (const Item& it : items)
@@ -892,7 +900,8 @@ static int stage_pass(sv_ctx* c, const Pass& ps) {
         memcpy(q, v, sizeof(v));
         t0 += r.n;
     }
-    c->n_work = c->n_last_work = c->longest_work = 0;
+    c->n_work = c->n_last_work = 0;
+    c->four_waves = c->last_four_waves = false;
     c->pass_merge = false;
     c->cold = reads_past_cache(c, ps);
     if (attn_mfma_ok(c->model.dtype, c->model.head_dim, c->rt.page_size, c->attn_generic,
@@ -1029,7 +1038,7 @@ static AttnArgs attn_args(const sv_ctx* c, const Pass& ps, int layer, const void
     aa.T = ps.T; aa.n_max = ps.n_max; aa.k = ps.k; aa.Hq = m.n_q_heads; aa.Hkv = m.n_kv_heads; aa.hd = m.head_dim; aa.dtype = m.dtype;
     aa.work = c->at<int32_t>(L.stage) + L.st_work; aa.n_work = c->n_work;
     aa.last_of = nullptr; aa.n_last = 0; aa.last_out = nullptr;
-    aa.row_items = ps.n == 0; aa.merge = c->pass_merge; aa.longest = c->longest_work; aa.cold = c->cold;
+    aa.row_items = ps.n == 0; aa.merge = c->pass_merge; aa.four_waves = c->four_waves; aa.cold = c->cold;
     aa.n_work_dev = nullptr; aa.grid_items = 0;
     if (c->graph_launch_shape) {      // nothing in the launch may depend on the lengths
         aa.n_work_dev = c->at<int32_t>(L.stage);
@@ -1100,7 +1109,7 @@ static int layer_rows(sv_ctx* c, int l, const Pass& ps, int& pending) {
     LastRows last{};
     if (few) {
         aa.last_of = c->at<int32_t>(L.stage) + L.st_req; aa.n_last = ps.last; aa.last_out = c->at<void>(L.q);
-        aa.work += (size_t)kItemInts * c->n_work; aa.n_work = c->n_last_work;
+        aa.work += (size_t)kItemInts * c->n_work; aa.n_work = c->n_last_work; aa.four_waves = c->last_four_waves;
         if (!attn_mfma_ok(m.dtype, m.head_dim, c->rt.page_size, c->attn_generic, 0)) aa.last_out = c->at<void>(L.attn);   // (reads q, writes nothing but these rows)
         last = LastRows{aa.last_of, ps.last, true, 0};
     }
@@ -1414,6 +1423,15 @@ extern "C" int sv_op_gemm_plan(int M, int N, int K, int* splits, int* wide, int*
     WsPlan p = plan_ws(M, N, K, true);
     if (N % 256 == 0 && M >= 1024 && (long long)((M + 255) / 256) * (N / 256) >= 4 * 256) p = WsPlan{1, true, 8, 0.0, 0.0, {}, {}};
     *splits = p.splits; *wide = p.wide ? 1 : 0; *row_tiles = p.row_tiles;
+    return SV_OK;
+}
+
+extern "C" int sv_op_prefill_waves(const int* keys, int items, int n_kv_heads, int* waves) {
+    if (!keys || !waves || items <= 0 || n_kv_heads <= 0) return SV_EINVAL;
+    std::vector<int> lens(keys, keys + items);
+    std::sort(lens.begin(), lens.end(), std::greater<int>());
+    if (lens.back() <= 0) return SV_EINVAL;
+    *waves = prefill_four_waves(lens.data(), items, n_kv_heads) ? 4 : 2;
     return SV_OK;
 }
 

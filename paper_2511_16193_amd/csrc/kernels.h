@@ -128,7 +128,7 @@ struct AttnArgs {
     int grid_items;                     // when > 0: items the grid is sized for (an upper bound of the item count)
     bool row_items;                     // prefill: an item is 64 stacked rows of a request, whose keys end at the last one it sees
     bool merge;                         // some request has several pieces
-    int longest;                        // most keys of an item
+    bool four_waves;                    // prefill: four waves a work-group instead of two
     bool cold;                          // the keys and values come from HBM (see kCacheBytes)
     const int32_t* last_of; int n_last; // when set (the last layer of a prefill): only the last rows of the first n_last requests of that
     void* last_out;                     //       table are wanted, in rows 0 .. n_last - 1 of this buffer, which is not `out` (work: items that hold them)
@@ -141,6 +141,8 @@ constexpr int kItemRows = 64;               // stacked rows of a prefill item
 constexpr int kStepRows = 256;              // most stacked rows per kv head of a step's request that the bf16 kernels take
 // the bf16 kernels cover the shape; step_rows: stacked rows per kv head of a step's request, 0 for a prefill
 bool attn_mfma_ok(int dtype, int hd, int page_size, bool force_generic, int step_rows);
+// do a prefill's work-groups take four waves?  (keys of its items, longest first)
+bool prefill_four_waves(const int* keys, int items, int Hkv);
 hipError_t attention(const AttnArgs& a, hipStream_t st);
 
 // ---- moe.hip ----

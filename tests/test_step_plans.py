@@ -1,7 +1,7 @@
-"""The launch plans of a step's packed projections, host arithmetic: every one is a launch that its kernel takes."""
+"""The launch plans of a step's packed projections and of a prefill's attention, host arithmetic: every one is a launch that its kernel takes."""
 import pytest
 
-from paper_2511_16193_amd import SvError, op_gemm_step_launch, op_gemm_step_plan
+from paper_2511_16193_amd import SvError, op_gemm_step_launch, op_gemm_step_plan, op_prefill_waves
 
 # QKV, O, down; LM head; gate/up of the 7B-, 32B- and expert-shaped decoders, and small models
 SHAPES = {0: [(4608, 3584), (3584, 3584), (3584, 18944), (7168, 5120), (5120, 5120), (5120, 27648), (5120, 2048), (2048, 4096), (256, 1024), (1536, 64)],
@@ -145,3 +145,31 @@ def test_what_is_no_projection_of_a_step_is_refused():
             op_gemm_step_launch(*args)
     with pytest.raises(SvError):
         op_gemm_step_launch(5, 256, 64, 0, tile_mode=2)
+
+
+def _prompt(group, n, cached=0, cut=1):
+    """Keys of a prompt's attention items: 64 stacked rows each, cut into equal parts of whole 32-key tiles."""
+    total = cached + n
+    part = (-(-total // cut) + 31) // 32 * 32
+    ends = [cached + (min(64 * (g + 1), group * n) - 1) // group + 1 for g in range(-(-group * n // 64))]
+    return [max(1, min(e, at + part) - at) for e in ends for at in range(0, total, part)]
+
+
+@pytest.mark.parametrize("heads,keys,waves", [
+    (4, _prompt(7, 777), 4), (4, _prompt(7, 1100), 4), (8, _prompt(2, 2048), 4),       # one prompt: 340, 484 and 512 work-groups, the shortest share places
+    (8, _prompt(2, 2049), 2), (4, _prompt(7, 1200), 2),                                # more than 512
+    (4, _prompt(7, 400) * 2, 2), (4, _prompt(7, 300) * 2, 2), (16, _prompt(1, 260) * 4, 2),       # several short ones: 352, 264, 320
+    (8, _prompt(4, 100, 4000, 4) * 2, 2), (8, _prompt(5, 64, 1000) * 8, 2), (8, _prompt(5, 40, 16000, 16), 2),    # pieces of one length, more than 256
+    (8, [1000] * 32, 4), (8, [1000] * 33, 2), (8, [4096] * 64, 4), (8, [4096] * 65, 2),
+    (4, [256], 4), (4, [255], 2), (4, [255] * 64, 2),
+    (1, [600] * 256 + [60], 4), (1, [60] + [600] * 256, 4), (1, [600] * 256 + [61], 2), (1, [511] * 256 + [1], 2), (16, [512] * 16 + [48], 4),
+])
+def test_waves_of_a_prefills_attention(heads, keys, waves):
+    """Four where every work-group has a place, or those that wait for one are short."""
+    assert op_prefill_waves(keys, heads) == waves
+
+
+def test_prefill_waves_refuses_nonsense():
+    for keys, heads in (([], 4), ([100], 0), ([100, 0], 4)):
+        with pytest.raises(SvError):
+            op_prefill_waves(keys, heads)
