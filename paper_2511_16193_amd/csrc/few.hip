@@ -225,6 +225,13 @@ __global__ __launch_bounds__(64 * kFewWaves, OCC) void few_rows_kernel(const voi
 }
 
 constexpr int kFewShort = 8192;                           // reductions up to here are a handful of steps for each wave
+constexpr int kFewNarrow = 2560;                          // features of fewer than 160 work-groups of 16
+// can the launch that O or down replaces cut the reduction into eight parts or more?
+static bool splits_well(int K) {
+    for (int s = 8; s <= 16; ++s)
+        if (K % (64 * s) == 0) return true;
+    return false;
+}
 static int few_features(int F) {                          // 16-feature gate operands of a work-group; 0: with none of the widths one round of work-groups
     for (int fs : {4, 5, 7})
         if ((F / 16 + fs - 1) / fs <= 256) return fs;
@@ -239,11 +246,17 @@ static int few_features(int F) {                          // 16-feature gate ope
 // 5120 x 5120 11.7 against 10.6 and down 26.3 against 23.1 and 53.5 against 49.3.  More work-groups than CUs: no (QKV of 10240 and 15360 features, steps of
 // 12 and 16 rows level to 0.6 % longer).  Steps of five rows of smaller models, whose streams are shorter: 896 wide 691 -> 566 us (12 layers), 1024 wide 630 -> 539,
 // 2048 wide 537 -> 479 and 659 -> 563 (8 layers), 4096 wide 696 -> 656 (6 layers), 8192 wide 992 -> 970 (3).
+// O and down of narrow models: with one CU to 16 features and the whole reduction, long reductions are bound by what a CU draws, where split-K fills
+// the chip.  us a layer that the launch saves (all that it replaces; 240 shapes of 256 to 3072 features x 1024 to 24576 inputs) at five / eight / sixteen
+// rows: 1024 features x 4096 inputs 2.8 / 2.1 / 1.0, x 6144 -1.0 / -1.2 / -1.5, x 8192 -1.6 / -2.3 / -2.3, x 16384 -5.5 / -5.9; 2048 x 6144 0.2 / -0.3 / -0.7,
+// x 8960 -1.6 / -2.0, x 16384 -2.3 / -3.1; 512 x 10240 1.1 / 0.1, x 12288 -2.4 / -3.2; 2560 x 16384 1.0 / 0.7, and from there on -1 to 2.  Reductions that split into four
+// parts at most (11008 and 4864 inputs) 4 to 7 / 3.5 to 6.5 / 2.7 at any width.
 bool few_rows_ok(int M, int N, int K, FewForm form, bool norm) {
     if (M < 1 || M > 16 || K % 64 != 0 || K < 32 * kFewWaves || N % 128 != 0) return false;
     if (norm && (M > kFewWaves || K > 256 * kFewWaves * 3)) return false;
     if (form != kFewGlu && N > 256 * 32) return false;
     if (form == kFewAdd && M > kFewWaves && (K > kFewShort || N > 256 * 16)) return false;
+    if (form == kFewAdd && splits_well(K) && (M > kFewWaves ? K > 4096 && N < kFewNarrow : K > 6144 && N < kFewNarrow && (K > 10240 || N > 512))) return false;
     return form != kFewGlu || few_features(N / 2) > 0;
 }
 

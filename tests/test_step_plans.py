@@ -69,6 +69,9 @@ def test_step_launches_are_launchable(form, experts):
     (10240, 5120, 4, 0), (10240, 5120, 0, 0),                              # more than 8192 features
     (37888, 6208, 2, 0), (57600, 3584, 2, 0),                              # rows too wide to be normalised inside; more gate features than 7 x 16 x 256
     (4096, 128, 4, 0), (152064, 3584, 1, 0),                               # no step for every wave; an LM head
+    (1024, 4096, 0, 16), (1024, 4160, 0, 8), (1024, 6144, 0, 8), (2048, 6656, 0, 0), (1024, 16384, 0, 0), (2432, 8192, 0, 0),     # narrow: long reductions are
+    (512, 10240, 0, 8), (512, 10752, 0, 0), (640, 10240, 0, 0), (2560, 8192, 0, 16), (2560, 24576, 0, 8),                         # split instead, where they
+    (2048, 11008, 0, 8), (896, 4864, 0, 16), (1024, 17152, 0, 8), (2048, 16384, 4, 16), (32768, 2048, 2, 8),                      # can be in eight
 ])
 def test_a_few_rows(N, K, form, most):
     """Up to `most` rows norm, rotary or residual ride in the projection, unless experts, the option or the weights' alignment forbid it."""
