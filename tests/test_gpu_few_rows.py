@@ -99,3 +99,43 @@ def test_prefill_of_a_few_rows_is_the_oracles_causal_pass(cached, lens):
             ko, vo = case.caches[b].k[layer][cached[b]:cached[b] + n], case.caches[b].v[layer][cached[b]:cached[b] + n]
             assert np.max(np.abs(kd.float().cpu().numpy() - ko)) < 0.03 and np.max(np.abs(vd.float().cpu().numpy() - vo)) < 0.03
     case.close()
+
+
+@pytest.mark.parametrize("rows", [5, 12])
+@pytest.mark.parametrize("off", [("wo", "w_down"), ("w_down", "wqkv"), ("w_gate_up", "wo"), ("wqkv", "w_gate_up"), ("w_down", None)])
+def test_layers_of_which_one_matrix_starts_off_16_bytes(rows, off):
+    """That one keeps the launch with planes, which the next norm adds up whoever runs it, beside neighbours that take the others along: the logits of the
+    step whose matrices all start at 16 bytes, but for values that another order of the sums rounds to another bf16 number (2^-8 of
+    them), through two layers: 2^-7 by the 2-norm."""
+    d, ff, V = 256, 1152, 2048
+    g = lambda *shape, seed, std: _t(shape, seed, std)
+    layers = [{"ln1": 1 + _t((d,), 9 * l + 1, 0.1), "wqkv": g(512, d, seed=9 * l + 2, std=d ** -0.5), "wo": g(d, 256, seed=9 * l + 3, std=0.1), "ln2": 1 + _t((d,), 9 * l + 4, 0.1),
+               "w_gate_up": g(2 * ff, d, seed=9 * l + 5, std=2 * d ** -0.5), "w_down": g(d, ff, seed=9 * l + 6, std=0.05)} for l in range(2)]
+    layers = [{n: P.op_pack_weight(x.to(DEV)) if x.dim() == 2 else x.to(DEV) for n, x in w.items()} for w in layers]
+    top = {"embed": _t((V, d), 40).to(DEV), "lm_head": P.op_pack_weight(_t((V, d), 41, d ** -0.5).to(DEV)), "final_norm": (1 + _t((d,), 42, 0.1)).to(DEV)}
+    model = dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=ff, vocab=V, n_experts=0, top_k=0, d_expert=0, dtype="bf16",
+                 rope_theta=THETA, rms_eps=EPS)
+    kv = _t((2, 7, 1, 128), 43).to(DEV)
+
+    def moved(x):
+        y = torch.cat([x.new_zeros(4), x.flatten()])[4:].view(x.shape)
+        assert y.data_ptr() % 16 == 8
+        return y
+
+    def step(off):
+        ws = [{n: moved(x) if n == o else x for n, x in w.items()} for w, o in zip(layers, off)]
+        ver = P.Verifier(model, dict(top, layers=ws), packed=True, max_batch=rows, max_k=1, max_chains=1, max_seqs=rows, page_size=32, num_pages=rows + 4,
+                         max_pages_per_seq=2, verify_mode=P.SV_MATCH, sample_mode=P.SV_EXP_RACE, temperature=1.0, device=DEV)
+        for b in range(rows):
+            ver.seq_add(b, 7)
+            for l in range(2):
+                ver.kv_write(b, l, 0, kv[0], kv[1])
+        u = torch.rand((rows, 1, 1), generator=torch.Generator().manual_seed(44)).to(DEV)
+        out = ver.step(list(range(rows)), (torch.arange(rows, dtype=torch.int32) * 19).to(DEV), None, None, u, want_logits=True)
+        entries = torch.cat([torch.cat(ver.kv_read(b, 1, 7, 1)) for b in range(rows)]).double()
+        torch.cuda.synchronize()
+        ver.close()
+        return out["logits"].double(), entries
+
+    for got, want in zip(step(off), step((None, None))):
+        assert float((got - want).norm() / want.norm()) < 2.0 ** -7

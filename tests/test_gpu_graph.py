@@ -68,6 +68,18 @@ def test_graph_replay_of_tall_projections(tile):
             assert np.array_equal(p[key], g[key]), f"step {s}: {key} differs between plain launches and graph replay"
 
 
+@pytest.mark.parametrize("batch", [1, 2, 3])
+def test_graph_replay_of_a_few_rows(batch):
+    """5, 10 and 15 rows: norm, rotary and residual inside the projections, whose launches set a kernel attribute inside the capture."""
+    shape = W.Shape("graph-few", 2, 512, 8, 2, 128, 1024, 4096, dtype="bf16", batch=batch, k=4, prefix_lo=10, prefix_hi=900, seed=327)
+    import paper_2511_16193_amd as P
+    assert P.op_gemm_step_launch(5 * batch, 1536, 512, 4)["kernel"] == P.op_gemm_step_launch(5 * batch, 512, 1024, 0)["kernel"] == "few"
+    plain, graph = run_steps(False, 8, shape), run_steps(True, 8, shape)
+    for s, (p, g) in enumerate(zip(plain, graph)):
+        for key in p:
+            assert np.array_equal(p[key], g[key]), f"step {s}: {key} differs between plain launches and graph replay"
+
+
 def test_graph_needs_own_stream():
     import paper_2511_16193_amd as P
     from workloads.device_case import DeviceCase
