@@ -386,7 +386,7 @@ def main():
     fp32 = shape.dtype == "fp32"     # fp32 models: projections on fp32 MFMA (its peak is that of the vector ALUs) and the generic attention
     gemm_peak = PEAK_FP32_TFLOPS if fp32 else PEAK_BF16_TFLOPS
     roofs = {
-        "gemm": {"kernel": "gemm_f32_kernel (all dense projections + LM head)" if fp32 else "gemm_bf16_ws_kernel, gemm_bf16_tall_kernel or gemm_bf16_strip_kernel (all dense projections + LM head)",
+        "gemm": {"kernel": "gemm_f32_kernel (all dense projections + LM head)" if fp32 else "gemm_bf16_ws_kernel, gemm_bf16_tall_kernel, gemm_bf16_strip_kernel or few_rows_kernel (all dense projections + LM head)",
                  "bound": "mfma", "achieved": gemm_tflops,
                  "peak": gemm_peak, "unit": "TFLOP/s", "frac": gemm_tflops / gemm_peak,
                  "measured_peak": None if fp32 else mfma_meas, "frac_of_measured_peak": None if fp32 else gemm_tflops / mfma_meas,

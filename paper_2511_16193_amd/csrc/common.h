@@ -139,7 +139,6 @@ __host__ __device__ __forceinline__ bool row_sees(int i, int j, int k) {
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
-__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
 // LDS reads placed by hand, with hand-placed waits: the compiler would wait for every request that is in flight into LDS before a read of
 // it.  It takes the registers as written at once, so what is read is waited for in the basic block that reads it (a branch in between may
