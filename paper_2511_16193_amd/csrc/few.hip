@@ -11,8 +11,9 @@
 //     nothing but the rows is shared.
 //   * NORM: the waves normalise the rows (M <= 8) into LDS as bf16, while the weights of the first steps are on their way: the rows and gains are
 //     requested ahead of them, since loads return in order.
-// The work-groups come to the number of CUs or a little less: 16 features of O and down of the 7B shape (224), 16 and their rotary partners of QKV (144), 5 or
-// 7 times 16 gate and up features (237 and 247).
+// The work-groups of the 7B and 32B shapes come to the number of CUs or less: 16 features of O and down (224), 16 and their rotary partners of QKV (144, 224), 5 or
+// 7 times 16 gate and up features (237 and 247).  Narrower models have no gate/up of less than 64 features a work-group, 76 of them for 4864 gate features: the
+// launches it replaces made no more, and with its norm it saves them 0.4 to 4 us a layer.
 #include <algorithm>
 #include <type_traits>
 #include "common.h"
@@ -238,8 +239,9 @@ static int few_features(int F) {                          // 16-feature gate ope
     return 0;
 }
 
-// Up to eight rows, whose 16-byte pieces share a cache line, all forms are ahead.  us a launch, weights from HBM, one, five and eight rows against the
-// launches that they replace at five: QKV of 4608 x 3584 normalised, rotated and appended 9.5 / 10.7 / 12.0 against 4.5 + 7.4 + 4.8, of 7168 x 5120
+// Up to eight rows, whose 16-byte pieces share a cache line, QKV and gate/up are ahead of the launches that they replace; O and down are level with theirs by
+// themselves, and ahead by the planes that the next launch need not add up, which lets it normalise.  us a launch, weights from HBM, one, five and eight rows
+// against the launches that they replace at five: QKV of 4608 x 3584 normalised, rotated and appended 9.5 / 10.7 / 12.0 against 4.5 + 7.4 + 4.8, of 7168 x 5120
 // 14.7 / 16.3 / 17.4 against 4.8 + 13.3 + 4.7; gate/up of 37888 x 3584 43.5 / 44.5 / 45.6 against 4.5 + 43.4, of 55296 x 5120 85.7 / 87.2 / 88.0
 // against 4.8 + 85.5; O of 3584 x 3584 6.1 against 6.7, of 5120 x 5120 10.7 against 10.6; down of 3584 x 18944 23.4 against 23.1, of 5120 x 27648 48.1
 // against 49.3.  Nine to sixteen: QKV after a norm of its own 9.2 against 7.4 + 4.8 and O 6.7 against 6.7 (with no planes for the norm to read), but O of
